@@ -128,5 +128,37 @@ __device__ __forceinline__ void park_hidden(const floatx16 (&acc)[2], int piece,
     *reinterpret_cast<u32x2*>(&H[l32 * stride + 64 * wave + 32 * nt + 8 * g + 4 * half]) = o;
 }
 
+// The last layer (w3 . relu(H2) per row) runs on the matrix cores too, chained onto the second layer's result.  A lane
+// holds 16 units of its row per 32-unit block (accumulator register i = unit 8 (i/4) + 4 half + i%4); rounded to bfloat16
+// in pairs, registers 8 hq .. 8 hq + 7 of a block are, as they stand, the B operand of one 32x32x16 MFMA whose depth index
+// (half, j) means unit 16 hq + 8 (j/4) + 4 half + j%4 of the block: any numbering of the depth will do as long as the A
+// operand uses the same one.  The A operand is w3 in that numbering in row 0 and zero elsewhere, so row 0 of the product
+// (register 0 of lanes 0..31) is the wavefront's share of the dot product for the 32 rows: four MFMAs per 32 rows take
+// the place of 128 vector instructions (unpacking and FMAs), which is what the loop is short of.
+__device__ __forceinline__ void last_layer_pack(const floatx16 (&acc)[2], int pair, uint32_t (&pk)[16])
+{
+    const int nt = pair >> 3, j = pair & 7;
+    pk[pair] = relu_bf16x2(acc[nt][2 * j], acc[nt][2 * j + 1]);
+}
+__device__ __forceinline__ void last_layer_mfma(floatx16& acc3, int q, const bf16x8 (&w3f)[4], const uint32_t (&pk)[16])
+{
+    const u32x4 b = {pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]};
+    floatx16 zero;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) zero[i] = 0.f;
+    acc3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w3f[q], __builtin_bit_cast(bf16x8, b), q == 0 ? zero : acc3, 0, 0, 0);
+}
+
+// The A operand of fragment q = 2 nt + hq from the wavefront's 64 last-layer weights in LDS (bfloat16, 8-byte aligned).
+__device__ __forceinline__ bf16x8 last_layer_weights(const uint16_t* w64, int q, int l32, int half)
+{
+    const int n0 = 32 * (q >> 1) + 16 * (q & 1) + 4 * half;
+    const u32x2 lo = *reinterpret_cast<const u32x2*>(&w64[n0]), hi = *reinterpret_cast<const u32x2*>(&w64[n0 + 8]);
+    u32x4 f = {lo[0], lo[1], hi[0], hi[1]};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) f[e] = l32 == 0 ? f[e] : 0u;
+    return __builtin_bit_cast(bf16x8, f);
+}
+
 }  // namespace tile
 }  // namespace pruner

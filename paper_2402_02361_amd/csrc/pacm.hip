@@ -19,9 +19,9 @@
 //   pacm_head_kernel   the head's hidden layer on the matrix cores (64 candidates per tile) and its output dot product
 // The pooled vectors travel through the workspace as the bfloat16 operands that the head's layer takes.
 //
-// Measured (statement counts 3..8, blocks 0..5; eight padded slots per candidate in either branch and binary32
-// pooled vectors before): 131,072 candidates: statement kernel 345 -> 203 us, dataflow 170 -> 59, head 43 -> 35, the call
-// 560 -> 284; 8,192 candidates: 29.8 -> 18.6, 23.7 -> 12.3, 10.7 -> 9.7, the call 60.5 -> 38.5.
+// Measured, before = eight padded slots per candidate in either branch and binary32 pooled vectors (statement counts 3..8,
+// blocks 0..5): 131,072 candidates: statement kernel 345 -> 180 us, dataflow 170 -> 55, head 43 -> 28, the call 512-560 -> 246;
+// 8,192 candidates: 29.8 -> 17.6, 23.7 -> 12.3, 10.7 -> 9.6, the call 60.4 -> 37.1.
 #include "common.h"
 #include "mfma_tile.h"
 
@@ -165,6 +165,7 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
     __shared__ uint16_t before[kLocalCap + 64 + 2];   // valid rows of this workgroup's candidates 0..l-1 (at most 8 x kLocalCap)
     __shared__ int32_t row_src[kTM];                  // what the rows of one tile are: candidate * 8 + statement, or -1
     __shared__ uint32_t scan_tot[4];
+    __shared__ uint32_t tainted[kLocalCap / 32];      // tiles to do again, by their first candidate
     __bf16* X = arena;                   // feature tile, bfloat16 [kTM][kXs]
     __bf16* H1 = arena + kTM * kXs;      // first hidden layer of the tile [kTM][kHs]
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -230,6 +231,7 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
         uint32_t first, end;
         int cand;
     };
+    int stop = n_local, most = 32;   // tiles end before candidate `stop` and take at most `most` candidates
     auto tile_at = [&](int start) {
         Tile t;
         t.start = start;
@@ -238,7 +240,7 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
         const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
         t.first = b0 - base;
         t.end = b1v - base;
-        const bool in = start + l32 < n_local && t.end <= (uint32_t)kTM;
+        const bool in = start + l32 < stop && l32 < most && t.end <= (uint32_t)kTM;
         t.count = (int)__popcll(__ballot(in) & 0xFFFFFFFFull);   // (the counts grow, so the candidates that fit are the first ones)
         t.cand = in ? global_of(start + l32) : -1;
         t.first = in ? t.first : 0u;
@@ -280,13 +282,7 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
         *reinterpret_cast<u32x2*>(&X[(f_row + ps * (kThreads / kRowThreads)) * kXs + (col < kF4 ? 4 * col : kK1)]) = o;   // depth 176..179 is never read
     };
 
-    Tile cur = tile_at(0);
-    if (wave == 0) write_rows(cur);
-    __syncthreads();
-    fetch_read();
-#pragma unroll
-    for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
-    // the second layer's matrix is requested after the first tile's features: it is needed later
+    // the second layer's matrix: not needed before the first tile's second layer
     load_slices<kH / 16, kH / 16, u32x4>(w2r, W2, kH, wave, l32, half);
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)   // weights in the accumulation registers (see verify_mlp.hip)
@@ -297,16 +293,7 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
         const int r = q / ((kXs - kF) / 4), j = q % ((kXs - kF) / 4);
         *reinterpret_cast<uint2*>(&X[r * kXs + kF + 4 * j]) = j == 0 ? make_uint2(0x3F803F80u, 0x00003F80u) : make_uint2(0, 0);
     }
-    Tile nxt = tile_at(cur.start + cur.count);
-    __syncthreads();   // everyone has read the first tile's rows
-    if (wave == 0) write_rows(nxt);
-#pragma unroll
-    for (int i = 0; i < kXLoads; ++i) park_piece(i);
-    __syncthreads();
-    fetch_read();
-#pragma unroll
-    for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
-
+    for (int i = threadIdx.x; i < kLocalCap / 32; i += kThreads) tainted[i] = 0u;
     floatx16 b2r[2];
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)
@@ -317,19 +304,20 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
     floatx16 pooled[2];          // sums of the tile in the making: units 64 wave + 32 nt + .. of the lane's candidate
     uint32_t pk[16];             // a half's second hidden layer, pairs of neighbouring rows
     bf16x8 member[4];            // the 0/1 matrix of the tile being pooled: 16 rows each
-    uint64_t mine_rows = 0;      // of the tile being pooled (for the careful path)
-    int pool_cand = -1, pool_count = 0;
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) acc0[nt][i] = acc1[nt][i] = pooled[nt][i] = 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) member[q] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+    uint32_t top;                // the largest of a half's activations (a lane's pairs), as 16-bit integers
+    bool special;                // the tile being pooled holds an infinity or a NaN
+    int pool_start, pool_count;
+    uint32_t pool_to;            // where the lane's candidate goes (bytes from v_s), or past the end of the buffer: no store
+    constexpr uint32_t kNowhere = 0xFFFF0000u;
+    const auto out = __builtin_amdgcn_make_buffer_rsrc(v_s, 0, n_d * kH * 2, 0x00027000);
 
     auto pack_pair = [&](const floatx16(&acc)[2], int pair) {
         const int nt = pair >> 3, j = pair & 7;
         pk[pair] = relu_bf16x2(acc[nt][2 * j], acc[nt][2 * j + 1]);
+        // (not negative, so the order of the bit patterns is the order of the values, infinity and NaN last)
+        top = pair == 0 ? pk[0] : __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, top), __builtin_bit_cast(i16x2, pk[pair])));
     };
+    auto is_special = [&]() { return __ballot((top & 0xFFFFu) >= 0x7F80u || (top >> 16) >= 0x7F80u) != 0ull; };
     auto pool_mfma = [&](int hh, int q) {   // q = 2 nt + hq
         const u32x4 h = {pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]};
         if (hh == 0 && (q & 1) == 0) {
@@ -341,122 +329,127 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
             pooled[q >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, h), member[2 * hh + (q & 1)], pooled[q >> 1], 0, 0, 0);
         }
     };
-    // 0 times an infinity or a NaN of one candidate would reach the others of its tile: such a half (the activations are
-    // not negative, so as 16-bit integers they say it by their largest) is summed candidate by candidate, the other
-    // candidates' rows cleared.
-    auto any_special = [&]() {
-        i16x2 top = __builtin_bit_cast(i16x2, pk[0]);
-#pragma unroll
-        for (int i = 1; i < 16; ++i) top = __builtin_elementwise_max(top, __builtin_bit_cast(i16x2, pk[i]));
-        return __ballot(top[0] >= (short)0x7F80 || top[1] >= (short)0x7F80) != 0ull;
+    auto pool_store = [&](int piece) {   // four units of the lane's candidate
+        const int nt = piece >> 2, g = piece & 3;
+        const u32x2 o = {bf16x2_of(pooled[nt][4 * g + 0], pooled[nt][4 * g + 1]), bf16x2_of(pooled[nt][4 * g + 2], pooled[nt][4 * g + 3])};
+        __builtin_amdgcn_raw_buffer_store_b64(o, out, (int)(pool_to + 2u * (uint32_t)(32 * nt + 8 * g)), 0, 0);
     };
-    auto pool_carefully = [&](int hh) {
-        floatx16 sum[2];
+    // 0 times an infinity or a NaN of one candidate would reach the others of its tile: such a tile is noted and done again
+    // when the others are through, one candidate at a time.
+    auto note_special = [&]() {
+        if (special && pool_count > 1 && lane == 0) atomicOr(&tainted[pool_start >> 5], 1u << (pool_start & 31));
+    };
+
+    int begin = 0, again = 0;   // candidates from `again` on may belong to noted tiles (second and later rounds)
+    for (;;) {
+        special = false;
+        pool_start = pool_count = 0;
+        pool_to = kNowhere;
+        top = 0u;
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) sum[nt][i] = hh == 0 ? 0.f : pooled[nt][i];
-        for (int c = 0; c < pool_count; ++c) {
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine_rows, c), hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(mine_rows >> 32), c);
-            const uint32_t rows = hh ? hi : lo;
+            for (int i = 0; i < 16; ++i) acc0[nt][i] = acc1[nt][i] = pooled[nt][i] = 0.f;
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
-                floatx16 one;
+        for (int q = 0; q < 4; ++q) member[q] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
+        Tile cur = tile_at(begin);
+        if (wave == 0) write_rows(cur);
+        __syncthreads();
+        fetch_read();
 #pragma unroll
-                for (int i = 0; i < 16; ++i) one[i] = 0.f;
+        for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
+        Tile nxt = tile_at(cur.start + cur.count);
+        __syncthreads();   // everyone has read the first tile's rows
+        if (wave == 0) write_rows(nxt);
 #pragma unroll
-                for (int hq = 0; hq < 2; ++hq) {
-                    u32x4 h;
+        for (int i = 0; i < kXLoads; ++i) park_piece(i);
+        __syncthreads();
+        fetch_read();
 #pragma unroll
-                    for (int p = 0; p < 4; ++p) {
-                        const uint32_t two = rows >> (16 * hq + 8 * (p >> 1) + 4 * half + 2 * (p & 1));
-                        h[p] = pk[8 * nt + 4 * hq + p] & ((two & 1u ? 0xFFFFu : 0u) | (two & 2u ? 0xFFFF0000u : 0u));
-                    }
-                    one = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, h), member[2 * hh + hq], one, 0, 0, 0);
-                }
-#pragma unroll
-                for (int i = 0; i < 16; ++i) sum[nt][i] = l32 == c ? sum[nt][i] + one[i] : sum[nt][i];
-            }
-        }
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) pooled[nt] = sum[nt];
-    };
-    auto pool_half = [&](int hh) {
-        if (any_special()) {
-            pool_carefully(hh);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) pool_mfma(hh, q);
-        }
-    };
-    auto pool_store = [&](int piece) {   // four units of the lane's candidate
-        const int nt = piece >> 2, g = piece & 3;
-        if (pool_cand >= 0) store_pooled(pooled[nt], g, v_s + (size_t)pool_cand * kH + 64 * wave + 32 * nt + 8 * g + 4 * half);
-    };
+        for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
 
-    // A tile in four stages, each a layer of one half of the rows with other work between its MFMAs.  At the loop's head X
-    // holds this tile's rows and the next tile's are on their way to registers.
-    bool have_prev = false;
-    while (cur.count > 0) {
-        // layer 1, rows 0..31.  Meanwhile: the sums of the previous tile's rows 32..63.
-        layer_from<kK1 / 16>(acc0, nullptr, w1r, X, kXs, l32, half, [&](int i) {
-            if (i < 8) {
-                pack_pair(acc1, 2 * i);
-                pack_pair(acc1, 2 * i + 1);
-            }
-            if (i == 9 && have_prev) pool_half(1);
-        });
-        // layer 1, rows 32..63.  Meanwhile: hidden layer 1 of rows 0..31 to LDS, the previous tile's sums to memory.
-        layer_from<kK1 / 16>(acc1, nullptr, w1r, X + 32 * kXs, kXs, l32, half, [&](int i) {
-            if (i >= 4 && i < 20 && !(i & 1)) park_hidden(acc0, (i - 4) >> 1, H1, kHs, wave, l32, half);
-            if (i >= 1 && i < 17 && (i & 1) && have_prev) pool_store(i >> 1);
-            if (i == 17) {
-                pool_cand = cur.cand;
-                pool_count = cur.count;
-                mine_rows = rows_of(cur);
-            }
-            if (i >= 18) member[i - 18] = member_fragment((uint32_t)(mine_rows >> (i >= 20 ? 32 : 0)), (i - 18) & 1, half);
-        });
-        __syncthreads();   // rows 0..31 of H1 complete; X no longer read
-        // layer 2, rows 0..31.  Meanwhile: hidden layer 1 of rows 32..63 and the next tile's features to LDS, and what the
-        // rows of the tile after next are.
+        // A tile in four stages, each a layer of one half of the rows with other work between its MFMAs.  At the loop's head
+        // X holds this tile's rows and the next tile's are on their way to registers.
+        while (cur.count > 0) {
+            // layer 1, rows 0..31.  Meanwhile: the sums of the previous tile's rows 32..63.
+            layer_from<kK1 / 16>(acc0, nullptr, w1r, X, kXs, l32, half, [&](int i) {
+                if (i < 8) {
+                    pack_pair(acc1, 2 * i);
+                    pack_pair(acc1, 2 * i + 1);
+                    if (i & 1) pool_mfma(1, i >> 1);
+                }
+                if (i == 8) special = special || is_special();
+            });
+            // layer 1, rows 32..63.  Meanwhile: hidden layer 1 of rows 0..31 to LDS, the previous tile's sums to memory.
+            layer_from<kK1 / 16>(acc1, nullptr, w1r, X + 32 * kXs, kXs, l32, half, [&](int i) {
+                if (i >= 4 && i < 20 && !(i & 1)) park_hidden(acc0, (i - 4) >> 1, H1, kHs, wave, l32, half);
+                if (i >= 1 && i < 17 && (i & 1)) pool_store(i >> 1);
+                if (i == 17) note_special();
+                if (i == 18) {
+                    pool_start = cur.start;
+                    pool_count = cur.count;
+                    pool_to = cur.cand >= 0 ? 2u * ((uint32_t)cur.cand * kH + 64 * wave + 4 * half) : kNowhere;
+                }
+                if (i >= 18) member[i - 18] = member_fragment((uint32_t)(rows_of(cur) >> (i >= 20 ? 32 : 0)), (i - 18) & 1, half);
+            });
+            __syncthreads();   // rows 0..31 of H1 complete; X no longer read
+            // layer 2, rows 0..31.  Meanwhile: hidden layer 1 of rows 32..63 and the next tile's features to LDS, and what
+            // the rows of the tile after next are.
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt)   // (no instruction: the register class, and in the first tile the wait for the matrix)
-            asm volatile("" : "+a"(w2r[nt][0]), "+a"(w2r[nt][1]), "+a"(w2r[nt][2]), "+a"(w2r[nt][3]), "+a"(w2r[nt][4]), "+a"(w2r[nt][5]),
-                              "+a"(w2r[nt][6]), "+a"(w2r[nt][7]), "+a"(w2r[nt][8]), "+a"(w2r[nt][9]), "+a"(w2r[nt][10]), "+a"(w2r[nt][11]),
-                              "+a"(w2r[nt][12]), "+a"(w2r[nt][13]), "+a"(w2r[nt][14]), "+a"(w2r[nt][15]));
-        static_assert(kH / 16 == 16, "the second layer's sixteen depth steps are listed above");
-        Tile after = nxt;
-        layer_rows<kH / 16>(acc0, b2r, w2r, H1, kHs, l32, half, [&](int i) {
-            if (i & 1) {
-                if (i >= 2 * (kH / 16 - kXLoads)) park_piece((i - 2 * (kH / 16 - kXLoads)) >> 1);   // as late as the layer allows
-                return;
-            }
-            if (i < 16) park_hidden(acc1, i >> 1, H1 + 32 * kHs, kHs, wave, l32, half);
-            if (i == 18) after = tile_at(nxt.start + nxt.count);
-            if (i == 26 && wave == 0) write_rows(after);
-        });
-        __syncthreads();   // rows 32..63 of H1, X (the next tile's rows) and the rows' table complete
-        // layer 2, rows 32..63.  Meanwhile: the sums of rows 0..31, and the requests for the rows of the tile after next.
-        layer_rows<kH / 16>(acc1, b2r, w2r, H1 + 32 * kHs, kHs, l32, half, [&](int i) {
-            if (!(i & 1) && i < 16) {
-                pack_pair(acc0, i);
-                pack_pair(acc0, i + 1);
-            }
-            if (i == 0) fetch_read();
-            if ((i & 1) && i < 2 * kXLoads) fetch_issue(i >> 1);
-            if (i == 18) pool_half(0);
-        });
-        have_prev = true;
-        cur = nxt;
-        nxt = after;
-    }
-    if (have_prev) {   // the last tile's second half
+            for (int nt = 0; nt < 2; ++nt)   // (no instruction: the register class, and in the first tile the wait for the matrix)
+                asm volatile("" : "+a"(w2r[nt][0]), "+a"(w2r[nt][1]), "+a"(w2r[nt][2]), "+a"(w2r[nt][3]), "+a"(w2r[nt][4]), "+a"(w2r[nt][5]),
+                                  "+a"(w2r[nt][6]), "+a"(w2r[nt][7]), "+a"(w2r[nt][8]), "+a"(w2r[nt][9]), "+a"(w2r[nt][10]), "+a"(w2r[nt][11]),
+                                  "+a"(w2r[nt][12]), "+a"(w2r[nt][13]), "+a"(w2r[nt][14]), "+a"(w2r[nt][15]));
+            static_assert(kH / 16 == 16, "the second layer's sixteen depth steps are listed above");
+            Tile after = nxt;
+            layer_rows<kH / 16>(acc0, b2r, w2r, H1, kHs, l32, half, [&](int i) {
+                if (i & 1) {
+                    if (i >= 2 * (kH / 16 - kXLoads)) park_piece((i - 2 * (kH / 16 - kXLoads)) >> 1);   // as late as the layer allows
+                    return;
+                }
+                if (i < 16) park_hidden(acc1, i >> 1, H1 + 32 * kHs, kHs, wave, l32, half);
+                if (i == 18) after = tile_at(nxt.start + nxt.count);
+                if (i == 26 && wave == 0) write_rows(after);
+            });
+            __syncthreads();   // rows 32..63 of H1, X (the next tile's rows) and the rows' table complete
+            // layer 2, rows 32..63.  Meanwhile: the sums of rows 0..31, and the requests for the rows of the tile after next.
+            layer_rows<kH / 16>(acc1, b2r, w2r, H1 + 32 * kHs, kHs, l32, half, [&](int i) {
+                if (!(i & 1) && i < 16) {
+                    pack_pair(acc0, i);
+                    pack_pair(acc0, i + 1);
+                }
+                if ((i & 3) == 3 && i < 16) pool_mfma(0, i >> 2);
+                if (i == 0) fetch_read();
+                if ((i & 1) && i < 2 * kXLoads) fetch_issue(i >> 1);
+                if (i == 18) special = is_special();
+            });
+            cur = nxt;
+            nxt = after;
+        }
+        // the last tile's second half
 #pragma unroll
         for (int pair = 0; pair < 16; ++pair) pack_pair(acc1, pair);
-        pool_half(1);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) pool_mfma(1, q);
+        special = special || is_special();
 #pragma unroll
         for (int piece = 0; piece < 8; ++piece) pool_store(piece);
+        note_special();
+        // the next noted tile, if there is one
+        __syncthreads();
+        int found = -1;
+        for (int w = again >> 5; w < (n_local + 31) / 32 && found < 0; ++w) {
+            const uint32_t bits = tainted[w] & (w == again >> 5 ? ~0u << (again & 31) : ~0u);
+            if (bits) found = 32 * w + __builtin_ctz(bits);
+        }
+        if (found < 0) break;
+        begin = again = found;
+        stop = n_local;
+        most = 32;
+        const Tile t = tile_at(found);   // (the tile as it was: its first candidate names it)
+        stop = found + t.count;
+        most = 1;
+        again = stop;
     }
 }
 
@@ -474,7 +467,7 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
 // 0 times an infinity or a NaN of one candidate would reach the others of its tile: a tile whose sums hold a NaN is done
 // again candidate by candidate.
 // Bound: vector instructions (the softmax, the pieces).  Eight slots per candidate, softmax and products with the weights on
-// the vector ALU and every stage through LDS took 170 us where this takes 59 (131,072 candidates, 2.8 blocks on average).
+// the vector ALU and every stage through LDS took 170 us where this takes 55 (131,072 candidates, 2.8 blocks on average).
 
 constexpr int kFlowWaves = 4;                 // wavefronts per workgroup, each with tiles of its own
 constexpr int kFlowThreads = 64 * kFlowWaves;
@@ -754,83 +747,105 @@ pacm_flow_kernel(const float* __restrict__ flow, const int32_t* __restrict__ n_b
 }
 
 // ---- head ------------------------------------------------------------------------------------------------------------
+// The two 32-row halves of a tile run one after the other on the matrix cores; rounding, the output dot product (matrix cores
+// as well, see last_layer_mfma) and the stores of one half, and the next tile's way into LDS, are issued between the MFMAs
+// of the other.  Two tiles' operands in LDS: one barrier per tile.  Bound: memory at scale (640 bytes per candidate), weights
+// and launch for small sets.
 
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ v_d, int32_t n_d, const uint16_t* __restrict__ Wh,
                  const float* __restrict__ bh, const uint16_t* __restrict__ wo, float bo, float* __restrict__ y)
 {
-    __shared__ __attribute__((aligned(16))) __bf16 U[kTM * kUs];   // the tile's concatenated pooled vectors, bfloat16
+    __shared__ __attribute__((aligned(16))) __bf16 U[2][kTM * kUs];   // a tile's concatenated pooled vectors
     __shared__ __attribute__((aligned(16))) float cst[kH];
-    __shared__ float red[4][kTM];
+    __shared__ __attribute__((aligned(16))) uint16_t wo_lds[kH];
+    __shared__ float red[2][4][kTM];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, l32 = lane & 31;
     const int n_tiles = (n_d + kTM - 1) / kTM;
 
+    constexpr int kU8 = kU / 8;   // 16-byte pieces per row (40)
+    constexpr int kPieces = kTM * kU8 / kThreads;
+    static_assert(kTM * kU8 % kThreads == 0, "every thread fetches the same number of pieces");
+    u32x4 piece[kPieces];
+    auto fetch_piece = [&](int tile, int i) {
+        const int q = threadIdx.x + i * kThreads, row = q / kU8, col = q % kU8;
+        int cand = tile * kTM + row;
+        cand = cand < n_d ? cand : 0;   // rows past the end repeat candidate 0; their outputs are not stored
+        piece[i] = col < kH / 8 ? *reinterpret_cast<const u32x4*>(v_s + (size_t)cand * kH + 8 * col)
+                                : *reinterpret_cast<const u32x4*>(v_d + (size_t)cand * kE + 8 * (col - kH / 8));
+    };
+    auto park_piece = [&](int buf, int i) {
+        const int q = threadIdx.x + i * kThreads;
+        *reinterpret_cast<u32x4*>(&U[buf][(q / kU8) * kUs + 8 * (q % kU8)]) = piece[i];
+    };
+    int tile = blockIdx.x;   // (no more workgroups than tiles)
+#pragma unroll
+    for (int i = 0; i < kPieces; ++i) fetch_piece(tile, i);
     bf16x8 whr[2][kU / 16];
     load_slices<kU / 16, kU / 16, u32x4>(whr, Wh, kU, wave, l32, half);
-    float wor[2][16];   // this lane's output weights, in accumulator order
+    static_assert(kThreads == kH, "one thread per hidden unit");
+    cst[threadIdx.x] = bh[threadIdx.x];
+    wo_lds[threadIdx.x] = wo[threadIdx.x];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
+    for (int i = 0; i < kPieces; ++i) park_piece(0, i);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) wor[nt][i] = __uint_as_float((uint32_t)wo[64 * wave + 32 * nt + 8 * (i / 4) + 4 * half + (i % 4)] << 16);
-    for (int n = threadIdx.x; n < kH; n += kThreads) cst[n] = bh[n];
+    for (int i = 0; i < kPieces; ++i) fetch_piece(tile + (int)gridDim.x, i);
+    __syncthreads();
+    floatx16 bhr[2];
+    bias_init(bhr, cst, wave, half);
+    bf16x8 wof[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wof[q] = last_layer_weights(wo_lds + 64 * wave, q, l32, half);
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int ks = 0; ks < kU / 16; ++ks) asm volatile("" : "+a"(whr[nt][ks]));
-    const auto nothing = [](int) {};
-    constexpr int kU8 = kU / 8;   // 16-byte pieces per row (40)
-    // A tile's pooled vectors, ten pieces per thread, are requested while the tile before is on the matrix cores and
-    // parked when that tile is done.
-    constexpr int kPieces = kTM * kU8 / kThreads;
-    static_assert(kTM * kU8 % kThreads == 0, "every thread fetches the same number of pieces");
-    u32x4 piece[kPieces];
-    auto fetch = [&](int tile) {
+
+    floatx16 acc0[2], acc1[2], y0, y1;
+    uint32_t pk[16];
 #pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int q = threadIdx.x + i * kThreads, row = q / kU8, col = q % kU8;
-            int cand = tile * kTM + row;
-            cand = cand < n_d ? cand : 0;   // rows past the end repeat candidate 0; their outputs are not stored
-            piece[i] = col < kH / 8 ? *reinterpret_cast<const u32x4*>(v_s + (size_t)cand * kH + 8 * col)
-                                    : *reinterpret_cast<const u32x4*>(v_d + (size_t)cand * kE + 8 * (col - kH / 8));
-        }
+    for (int i = 0; i < 16; ++i) acc1[0][i] = acc1[1][i] = y0[i] = y1[i] = 0.f;
+    auto store_rows = [&](int t, int buf) {   // a finished tile: the four wavefronts' shares of each row
+        const int cand = t * kTM + (int)threadIdx.x;
+        if (threadIdx.x < kTM && cand < n_d)
+            y[cand] = (((red[buf][0][threadIdx.x] + red[buf][1][threadIdx.x]) + red[buf][2][threadIdx.x]) + red[buf][3][threadIdx.x]) + bo;
     };
-    if ((int)blockIdx.x < n_tiles) fetch(blockIdx.x);
-    for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
-        __syncthreads();   // cst written (first round); U and red free (later rounds)
-#pragma unroll
-        for (int i = 0; i < kPieces; ++i) {
-            const int q = threadIdx.x + i * kThreads;
-            *reinterpret_cast<u32x4*>(&U[(q / kU8) * kUs + 8 * (q % kU8)]) = piece[i];
-        }
-        if (tile + (int)gridDim.x < n_tiles) fetch(tile + gridDim.x);
-        __syncthreads();
-        floatx16 acc0[2], acc1[2];
-        bias_init(acc0, cst, wave, half);
-        layer<kU / 16>(acc0, whr, U, kUs, l32, half, nothing);
-        bias_init(acc1, cst, wave, half);
-        layer<kU / 16>(acc1, whr, U + 32 * kUs, kUs, l32, half, nothing);
-#pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            const floatx16(&acc)[2] = hh ? acc1 : acc0;
-            float part = 0.f;
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int p = 0; p < 8; ++p) {
-                    const uint32_t pr = relu_bf16x2(acc[nt][2 * p], acc[nt][2 * p + 1]);
-                    part = __builtin_fmaf(__uint_as_float(pr << 16), wor[nt][2 * p], part);
-                    part = __builtin_fmaf(__uint_as_float(pr & 0xFFFF0000u), wor[nt][2 * p + 1], part);
-                }
-            part += __shfl_xor(part, 32, 64);
-            if (half == 0) red[wave][32 * hh + l32] = part;
-        }
-        __syncthreads();
-        if (threadIdx.x < kTM) {
-            const int cand = tile * kTM + threadIdx.x;
-            if (cand < n_d) y[cand] = (((red[0][threadIdx.x] + red[1][threadIdx.x]) + red[2][threadIdx.x]) + red[3][threadIdx.x]) + bo;
-        }
+    int buf = 0, done = 0;
+    for (; tile < n_tiles; tile += gridDim.x, buf ^= 1, ++done) {
+        // rows 0..31.  Meanwhile: the output of the previous tile's rows 32..63, the next tile's vectors to LDS.
+        layer_from<kU / 16>(acc0, bhr, whr, U[buf], kUs, l32, half, [&](int i) {
+            if (i < 8) {
+                last_layer_pack(acc1, 2 * i, pk);
+                last_layer_pack(acc1, 2 * i + 1, pk);
+                if (i & 1) last_layer_mfma(y1, i >> 1, wof, pk);
+            }
+            if (i == 16 && half == 0) red[buf ^ 1][wave][32 + l32] = y1[0];
+            if (i >= 20 && !(i & 1)) park_piece(buf ^ 1, (i - 20) >> 1);
+        });
+        static_assert(kPieces == 10 && kU / 16 == 20, "the ten pieces fit the layer's last twenty gaps");
+        __syncthreads();   // the next tile's vectors and the previous tile's row outputs complete
+        // rows 32..63.  Meanwhile: the output of rows 0..31, the requests for the tile after next, the previous tile's scores.
+        layer_from<kU / 16>(acc1, bhr, whr, U[buf] + 32 * kUs, kUs, l32, half, [&](int i) {
+            if (i < 8) {
+                last_layer_pack(acc0, 2 * i, pk);
+                last_layer_pack(acc0, 2 * i + 1, pk);
+                if (i & 1) last_layer_mfma(y0, i >> 1, wof, pk);
+            }
+            if (i >= 8 && i < 8 + kPieces) fetch_piece(tile + 2 * (int)gridDim.x, i - 8);
+            if (i == 20 && half == 0) red[buf][wave][l32] = y0[0];
+            if (i == 24 && done > 0) store_rows(tile - (int)gridDim.x, buf ^ 1);
+        });
+        __syncthreads();   // this tile's buffer may be written again
     }
+    // the last tile's rows 32..63
+#pragma unroll
+    for (int pair = 0; pair < 16; ++pair) last_layer_pack(acc1, pair, pk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) last_layer_mfma(y1, q, wof, pk);
+    if (half == 0) red[buf ^ 1][wave][32 + l32] = y1[0];
+    __syncthreads();
+    store_rows(tile - (int)gridDim.x, buf ^ 1);
 }
 
 }  // namespace

@@ -52,27 +52,6 @@ __device__ __forceinline__ int32_t clamp_stmt(int32_t v) { return v < 0 ? 0 : v 
 
 // ---- mlp_kernel ----------------------------------------------------------------------------------------------------
 
-// The last layer (w3 . relu(H2) per row) runs on the matrix cores too, chained onto the second layer's result.  A lane
-// holds 16 units of its row per 32-unit block (accumulator register i = unit 8 (i/4) + 4 half + i%4); rounded to bfloat16
-// in pairs, registers 8 hq .. 8 hq + 7 of a block are, as they stand, the B operand of one 32x32x16 MFMA whose depth index
-// (half, j) means unit 16 hq + 8 (j/4) + 4 half + j%4 of the block: any numbering of the depth will do as long as the A
-// operand uses the same one.  The A operand is w3 in that numbering in row 0 and zero elsewhere, so row 0 of the product
-// (register 0 of lanes 0..31) is the wavefront's share of the dot product for the 32 rows: four MFMAs per 32 rows take
-// the place of 128 vector instructions (unpacking and FMAs), which is what the loop is short of.
-__device__ __forceinline__ void last_layer_pack(const floatx16 (&acc)[2], int pair, uint32_t (&pk)[16])
-{
-    const int nt = pair >> 3, j = pair & 7;
-    pk[pair] = relu_bf16x2(acc[nt][2 * j], acc[nt][2 * j + 1]);
-}
-__device__ __forceinline__ void last_layer_mfma(floatx16& acc3, int q, const bf16x8 (&w3f)[4], const uint32_t (&pk)[16])
-{
-    const u32x4 b = {pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]};
-    floatx16 zero;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) zero[i] = 0.f;
-    acc3 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w3f[q], __builtin_bit_cast(bf16x8, b), q == 0 ? zero : acc3, 0, 0, 0);
-}
-
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 mlp_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, int32_t n_d, int32_t kGroup, const uint16_t* __restrict__ W1,
            const float* __restrict__ b1, const uint16_t* __restrict__ W2, const float* __restrict__ b2, const uint16_t* __restrict__ w3, float b3,
@@ -251,14 +230,7 @@ mlp_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, i
             for (int j = 0; j < 4; ++j) b2r[nt][4 * g + j] = b[j];
         }
 #pragma unroll
-        for (int hq = 0; hq < 2; ++hq) {
-            const int n0 = 64 * wave + 32 * nt + 16 * hq + 4 * half;
-            const u32x2 lo = *reinterpret_cast<const u32x2*>(&w3_lds[n0]), hi = *reinterpret_cast<const u32x2*>(&w3_lds[n0 + 8]);
-            u32x4 f = {lo[0], lo[1], hi[0], hi[1]};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) f[e] = l32 == 0 ? f[e] : 0u;
-            w3f[2 * nt + hq] = __builtin_bit_cast(bf16x8, f);
-        }
+        for (int hq = 0; hq < 2; ++hq) w3f[2 * nt + hq] = last_layer_weights(w3_lds + 64 * wave, 2 * nt + hq, l32, half);
     }
     asm volatile("" : "+a"(w3f[0]), "+a"(w3f[1]), "+a"(w3f[2]), "+a"(w3f[3]));
 
