@@ -111,19 +111,40 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
 int draft_check(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
                 const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes);
 struct MutArgs;   // lse_child.h
-// whether a population of n candidates is scored by one launch per loop-nest class (given the full load width)
-bool draft_launches_by_class(int64_t n);
-// (also: an upload prepared by someone else whose destination lies in the same allocation shortly after this call's own tables)
-// Draft scores; when first_digit is not null and the launch shape allows it (*counted says so), the kernel also adds
-// every score's first selection digit to first_digit ([copies][n_sg][2048], cleared by the caller) and, when block_max is
-// not null, writes the largest key of every 256 neighbouring candidates of a segment there (block_max_slot).
-// mut: the explorer loop's mutation is due on this population; when the launch shape allows it (*mutated says so) the
-// kernels make the children from S_spec, store them over `tiles` (which is then written) and score them in one pass;
-// otherwise nothing of the kind happens and the caller mutates the population before calling.
+
+// The draft launches of a call: planned once (everything pruner_draft_score refuses is refused here), their tables uploaded
+// to the workspace's begin, then run, as often as the population's shape stays the same.
+struct DraftPlan {
+    struct Launch {
+        int cls;
+        int32_t first_seg, n_seg;
+        int64_t blocks, candidates, bytes;   // workgroups; candidates and their algorithmic bytes
+        const void *fn, *fn_read;            // the kernel; the same without making its candidates
+    };
+    std::vector<Launch> launches;
+    std::vector<char> image;   // the tables
+    size_t descs_at = 0;
+    int64_t n = 0, tiles_pitch = 0;
+    int32_t n_sg = 0, flags = 0;
+    bool counts = false;   // the kernels add every score's first selection digit to a histogram (full load width)
+    bool makes = false;    // the kernels can make their candidates (the explorer loop's mutation) instead of reading them
+};
+// count_digits: the caller has histograms to add to (plan->counts says whether the launch shape allows it); mut: the kernels
+// are to make their candidates from the second run on (plan->makes says whether they can).
+int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool mut, DraftPlan* plan);
+// (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables)
+int draft_upload(const DraftPlan& plan, void* workspace, hipStream_t stream, const Upload* also);
+// Draft scores.  With plan.counts, every score's first selection digit is added to first_digit ([copies][n_sg][2048], cleared
+// by the caller), when that is not null, and the largest key of every 256 neighbouring candidates of a segment goes to
+// block_max (block_max_slot), when that is not null either.  mut (needs plan.makes): the kernels make the children of
+// S_spec, store them over `tiles` (which is then written) and score them in one pass.
+int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tiles, float* score, int64_t* symbols, hipStream_t stream,
+              uint32_t* first_digit, uint32_t* block_max, int copies, const MutArgs* mut);
+// the three in one
 int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch,
                  int32_t flags, float* score, int64_t* symbols, void* workspace, size_t workspace_bytes, hipStream_t stream,
-                 uint32_t* first_digit, uint32_t* block_max, int copies, bool* counted, const Upload* also = nullptr,
-                 const MutArgs* mut = nullptr, bool* mutated = nullptr);
+                 uint32_t* first_digit, uint32_t* block_max, int copies, bool* counted, const Upload* also = nullptr);
 
 // workspace needs of the entry points (each defined next to its kernels)
 size_t draft_workspace_bytes(int32_t n_sg);

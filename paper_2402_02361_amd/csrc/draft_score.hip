@@ -465,6 +465,16 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
             for (int w = 0; w < kAosWords; ++w) f[e][w] = f[0][w];
         }
     }
+    if (mut.child_aos) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (e < live) {
+#pragma unroll
+                for (int q = 0; q < NP; ++q)
+                    mut.child_aos[(c0 + e) * (kAosSlots / 8) + q] = make_uint4(f[e][4 * q], f[e][4 * q + 1], f[e][4 * q + 2], f[e][4 * q + 3]);
+            }
+        }
+    }
     // row by row: the factor of each of the four children, as a column load would deliver it
     u32x2 T[kAosSlots];
 #pragma unroll
@@ -767,7 +777,7 @@ __device__ __forceinline__ void analyze_fused(const SgDesc& d, const Symbols (&y
 template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST>
 __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles<Nest, VEC>& raw, int64_t c0, int64_t c_end,
                                                  int32_t flags, const float* p2m_tab, float* __restrict__ score,
-                                                 int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist,
+                                                 int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist, bool count_digits,
                                                  uint32_t* __restrict__ block_max, int seg_index)
 {
     constexpr int NSP = Nest::NSP, NRD = Nest::NRD;
@@ -902,7 +912,7 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
         }
     }
 
-    if constexpr (HIST) {
+    if (HIST && count_digits) {
         // the selection stage's first pass, done here while the scores are in registers.  Plain LDS atomics: even
         // when all lanes hit one bin (equal scores) their serialisation stays hidden under this kernel's loads.
         uint32_t top = 0;   // below the key of every number
@@ -947,8 +957,8 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
 template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
 __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg, int32_t b, const uint16_t* __restrict__ tiles,
                                              int64_t pitch, int32_t flags, const float* p2m_tab, float* __restrict__ score,
-                                             int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist, uint32_t* __restrict__ block_max,
-                                             const MutArgs& mut)
+                                             int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist, bool count_digits,
+                                             uint32_t* __restrict__ block_max, const MutArgs& mut)
 {
     const int64_t step = (int64_t)seg.blocks * kBlock * VEC;
     RawTiles<Nest, VEC> cur{}, nxt{};
@@ -965,7 +975,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
             for (int it = 0; it < seg.iters; ++it) {
                 if (c0 < seg.end) {
                     make_children<Nest>(d, ms, mut, out, pitch, c0, seg.end, cur);
-                    score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, block_max, seg.seg);
+                    score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
                 }
                 c0 += step;
             }
@@ -978,7 +988,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
         for (int it = 0; it < seg.iters; ++it) {
             if (c0 < seg.end) {
                 load_tiles<Nest, VEC>(d, tiles, pitch, c0, cur);
-                score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, block_max, seg.seg);
+                score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
             }
             c0 += step;
         }
@@ -988,7 +998,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
     for (int it = 0; it < seg.iters; ++it) {
         const int64_t c1 = c0 + step;
         if (it + 1 < seg.iters && c1 < seg.end) load_tiles<Nest, VEC>(d, tiles, pitch, c1, nxt);
-        if (c0 < seg.end) score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, block_max, seg.seg);
+        if (c0 < seg.end) score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
         cur = nxt;
         c0 = c1;
     }
@@ -1019,7 +1029,9 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
     // three memory statements look them up.
     __shared__ float tab[kTabMax + 1];
     __shared__ uint32_t digit_hist[HIST ? kBins : 1];
-    if constexpr (HIST) {
+    // (the kernels that make their candidates also serve populations whose selection counts its digits itself)
+    const bool count_digits = HIST && (!MUT || first_digit != nullptr);
+    if (HIST && count_digits) {
         for (int i = threadIdx.x; i < kBins; i += kBlock) digit_hist[i] = 0;
         if (!seg.use_tab) __syncthreads();
     }
@@ -1034,7 +1046,7 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
     }
     const float* p2m_tab = seg.use_tab ? tab : nullptr;
 
-#define PRUNER_WALK(NEST) walk_segment<NEST, VEC, DUMP, EXACT, HIST, MUT>(d, seg, b, tiles, pitch, flags, p2m_tab, score, symbols, n_total, digit_hist, block_max, mut)
+#define PRUNER_WALK(NEST) walk_segment<NEST, VEC, DUMP, EXACT, HIST, MUT>(d, seg, b, tiles, pitch, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, mut)
     if constexpr (CLS == kGemm) PRUNER_WALK(NestGemm);
     else if constexpr (CLS == kBatchedGemm) PRUNER_WALK(NestBatchedGemm);
     else if constexpr (CLS == kConv2d) PRUNER_WALK(NestConv2d);
@@ -1050,7 +1062,7 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
         }
     }
 #undef PRUNER_WALK
-    if constexpr (HIST) {
+    if (HIST && count_digits) {
         __syncthreads();
         flush_hist<kBlock>(digit_hist, first_digit, copies, n_sg_all, seg.seg);
     }
@@ -1067,7 +1079,7 @@ template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, b
     }
     if constexpr (!DUMP) {
         if constexpr (CLS != kAnyClass) {
-            if (hist && mut) return draft_kernel<CLS, 4, false, EXACT, true, true>;
+            if (mut) return draft_kernel<CLS, 4, false, EXACT, true, true>;
         }
         if (hist) return draft_kernel<CLS, 4, false, EXACT, true, false>;
     }
@@ -1084,7 +1096,7 @@ template <bool DUMP, bool EXACT> DraftFn pick_class(int cls, int vec, bool hist,
         default: return pick_vec<kAnyClass, DUMP, EXACT>(vec, hist, mut);
     }
 }
-// mut is honoured for the per-class kernels at the full load width that also count the first selection digit
+// mut is honoured for the per-class kernels at the full load width (they count the first selection digit if asked to)
 DraftFn pick_kernel(int cls, int vec, bool dump, bool exact, bool hist, bool mut)
 {
     if (dump) return exact ? pick_class<true, true>(cls, vec, hist, mut) : pick_class<true, false>(cls, vec, hist, mut);
@@ -1388,12 +1400,9 @@ void* g_time_start = nullptr;
 void* g_time_stop = nullptr;
 int64_t* g_time_bytes = nullptr;
 
-int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch,
-                 int32_t flags, float* score, int64_t* symbols, void* workspace, size_t workspace_bytes, hipStream_t st,
-                 uint32_t* first_digit, uint32_t* block_max, int copies, bool* counted, const Upload* also, const MutArgs* mut, bool* mutated)
+int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool mut, DraftPlan* out)
 {
-    if (counted) *counted = false;
-    if (mutated) *mutated = false;
     if (!sg || !seg_off || n_sg < 1 || n_sg > PRUNER_MAX_SUBGRAPHS) return PRUNER_EINVAL;
     if (flags & ~(PRUNER_NO_COMPUTE_PENALTY | PRUNER_NO_MEMORY_PENALTY | PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) return PRUNER_EINVAL;
     if ((flags & PRUNER_REFERENCE_ROUNDING) && (flags & PRUNER_FUSED_ARITHMETIC)) return PRUNER_EINVAL;
@@ -1422,9 +1431,13 @@ int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off
         }
         desc_of[s] = found;
     }
+    *out = DraftPlan();
+    out->n = n;
+    out->n_sg = n_sg;
+    out->flags = flags;
+    out->tiles_pitch = tiles_pitch;
     if (n == 0) {
-        if (counted) *counted = first_digit != nullptr;   // nothing to count
-        if (also && also->dst) return put_table(also->dst, also->bytes.data(), also->bytes.size(), st, also->zero, also->zero_bytes);
+        out->counts = count_digits;   // nothing to count
         return PRUNER_OK;
     }
 
@@ -1438,34 +1451,50 @@ int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off
     };
     while (vec > 1 && !fits(vec)) vec >>= 1;
 
-    // Launch plan.  Large populations at the full load width: one launch per loop-nest class present, the table
-    // grouped by class; otherwise a single launch of the kernel that branches on the class.  A launch has at most
-    // as many workgroups as the device holds at once; they walk through the chunks of their segment.
-    struct Launch { int cls; int32_t first_seg, n_seg; int64_t blocks, chunks; DraftFn fn; };
-    std::vector<Launch> plan;
+    // Launch plan.  At the full load width: one launch per loop-nest class present, the table grouped by class, when the
+    // population is large, when there is only one class (its own kernel needs half the registers of the one that branches
+    // on the class and a fraction of its code: 4,096 GEMM candidates take 5.7 us in the one and 6.4 in the other,
+    // 65,536 convolution candidates 7.7 and 9.6), and, when the kernels make their candidates, up to two classes
+    // (a launch of the mutation is then saved); otherwise a single launch of the kernel that branches on the class.  A
+    // launch has at most as many workgroups as the device holds at once; they walk through the chunks of their segment.
     std::vector<int32_t> order(n_sg);
-    for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
-    const bool by_class = vec == 4 && n >= kPerClassMin;
+    uint32_t classes = 0;
+    for (int32_t s = 0; s < n_sg; ++s) {
+        order[s] = s;
+        classes |= 1u << descs[desc_of[s]].cls;
+    }
+    const bool large = vec == 4 && n >= kPerClassMin;
+    const bool by_class = vec == 4 && (large || __builtin_popcount(classes) <= (mut ? 2 : 1));
     if (by_class)
         std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return descs[desc_of[a]].cls < descs[desc_of[b]].cls; });
-    // Arithmetic of Eq. 1: one rounded operation per step of the definitions wherever the call is a single launch (below
-    // 2^20 candidates a call is bound by launch latency, and the dozen divisions per candidate cost nothing measurable),
-    // the multiplied-out form in the per-class launches of large populations, unless a flag asks for one of them.
-    const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !by_class);
-    const bool hist = first_digit != nullptr && vec == 4 && symbols == nullptr && copies >= 1;
-    const bool fused = mut != nullptr && by_class && hist;   // every launch of the plan then makes its candidates itself
+    // Arithmetic of Eq. 1: one rounded operation per step of the definitions below 2^20 candidates (a call is then bound by
+    // launch latency, and the dozen divisions per candidate cost nothing measurable) and at the narrow load widths, the
+    // multiplied-out form for large populations, unless a flag asks for one of them.
+    const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !large);
+    const bool hist = count_digits && vec == 4 && symbols == nullptr;
+    const bool fused = mut && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
+    std::vector<int64_t> chunks_of;
     for (int32_t i = 0; i < n_sg; ++i) {
-        const int cls = by_class ? descs[desc_of[order[i]]].cls : kAnyClass;
-        if (plan.empty() || plan.back().cls != cls) plan.push_back(Launch{cls, i, 0, 0, 0, pick_kernel(cls, vec, symbols != nullptr, exact, hist, fused)});
-        const int64_t len = seg_off[order[i] + 1] - seg_off[order[i]];
-        plan.back().chunks += (len + chunk - 1) / chunk;
-        plan.back().n_seg += 1;
+        const int32_t s = order[i];
+        const int cls = by_class ? descs[desc_of[s]].cls : kAnyClass;
+        if (out->launches.empty() || out->launches.back().cls != cls) {
+            out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, fused)),
+                                                      reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, false))});
+            chunks_of.push_back(0);
+        }
+        DraftPlan::Launch& L = out->launches.back();
+        const int64_t len = seg_off[s + 1] - seg_off[s];
+        chunks_of.back() += (len + chunk - 1) / chunk;
+        L.n_seg += 1;
+        L.candidates += len;
+        L.bytes += len * (2 * (int64_t)(sg[s].n_sp * 4 + sg[s].n_rd * sg[s].rd_levels) + 4);
     }
     std::vector<SegEnt> segs(n_sg);
-    for (Launch& L : plan) {
-        const int64_t room = resident_blocks(L.fn);
-        const int64_t depth = (L.chunks + room - 1) / room;   // chunks per workgroup when the launch fills the device once
+    for (size_t li = 0; li < out->launches.size(); ++li) {
+        DraftPlan::Launch& L = out->launches[li];
+        const int64_t room = resident_blocks(reinterpret_cast<DraftFn>(const_cast<void*>(L.fn)));
+        const int64_t depth = (chunks_of[li] + room - 1) / room;   // chunks per workgroup when the launch fills the device once
         for (int32_t i = L.first_seg; i < L.first_seg + L.n_seg; ++i) {
             const int32_t s = order[i];
             const SgDesc& dd = descs[desc_of[s]];
@@ -1478,70 +1507,77 @@ int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off
             L.blocks += blocks;
         }
     }
-
-    char* ws = static_cast<char*>(workspace);
-    SegEnt* d_segs = reinterpret_cast<SegEnt*>(ws);
-    SgDesc* d_descs = reinterpret_cast<SgDesc*>(ws + round_up((size_t)n_sg * sizeof(SegEnt), 256));
-    // both tables travel in one launch: the workspace image is assembled on the host
-    const size_t descs_at = round_up((size_t)n_sg * sizeof(SegEnt), 256);
-    std::vector<char> image(descs_at + descs.size() * sizeof(SgDesc), 0);
-    memcpy(image.data(), segs.data(), segs.size() * sizeof(SegEnt));
-    memcpy(image.data() + descs_at, descs.data(), descs.size() * sizeof(SgDesc));
-    void* zero = nullptr;
-    size_t zero_bytes = 0;
-    bool apart = false;
-    if (also && also->dst) {
-        // the other table rides along in the same launch if it starts shortly behind this call's tables (with many
-        // subgraphs that share descriptors the reserved room is much larger than the tables: then it travels by itself)
-        const ptrdiff_t at = static_cast<const char*>(also->dst) - ws;
-        if (at < (ptrdiff_t)image.size()) return PRUNER_EINVAL;
-        if (at <= (ptrdiff_t)image.size() + 4096) {
-            image.resize((size_t)at, 0);
-            image.insert(image.end(), also->bytes.begin(), also->bytes.end());
-            zero = also->zero;
-            zero_bytes = also->zero_bytes;
-        } else {
-            apart = true;
-        }
-    }
-    int rc = put_table(ws, image.data(), image.size(), st, zero, zero_bytes);
-    if (rc) return rc;
-    if (apart) {
-        rc = put_table(also->dst, also->bytes.data(), also->bytes.size(), st, also->zero, also->zero_bytes);
-        if (rc) return rc;
-    }
-
-    // measurement hook: events around the launch that covers the most candidates
-    const Launch* timed = nullptr;
-    int64_t timed_candidates = -1, timed_bytes = 0;
-    if (g_time_start && g_time_stop) {
-        for (const Launch& L : plan) {
-            if (L.blocks == 0) continue;
-            int64_t cands = 0, bytes = 0;
-            for (int32_t i = L.first_seg; i < L.first_seg + L.n_seg; ++i) {
-                const int32_t sub = order[i];
-                const int64_t len = seg_off[sub + 1] - seg_off[sub];
-                cands += len;
-                bytes += len * (2 * (int64_t)(sg[sub].n_sp * 4 + sg[sub].n_rd * sg[sub].rd_levels) + 4);
-            }
-            if (cands > timed_candidates) timed = &L, timed_candidates = cands, timed_bytes = bytes;
-        }
-        if (g_time_bytes) *g_time_bytes = timed ? timed_bytes : 0;
-    }
-    for (const Launch& L : plan) {
-        if (L.blocks == 0) continue;
-        if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_start), st) != hipSuccess) return PRUNER_EHIP;
-        hipLaunchKernelGGL(L.fn, dim3((unsigned)L.blocks), dim3(kBlock), 0, st, d_segs + L.first_seg, L.n_seg, d_descs, tiles, tiles_pitch,
-                           flags, score, symbols, n, first_digit, block_max, copies, n_sg, fused ? *mut : MutArgs{});
-        if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_stop), st) != hipSuccess) return PRUNER_EHIP;
-        PRUNER_LAUNCH_CHECK();
-    }
-    if (counted) *counted = hist;
-    if (mutated) *mutated = fused;
+    // the tables as they will stand at the workspace's begin
+    out->descs_at = round_up((size_t)n_sg * sizeof(SegEnt), 256);
+    out->image.assign(out->descs_at + descs.size() * sizeof(SgDesc), 0);
+    memcpy(out->image.data(), segs.data(), segs.size() * sizeof(SegEnt));
+    memcpy(out->image.data() + out->descs_at, descs.data(), descs.size() * sizeof(SgDesc));
+    out->counts = hist;
+    out->makes = fused;
     return PRUNER_OK;
 }
 
-bool draft_launches_by_class(int64_t n) { return n >= kPerClassMin; }
+int draft_upload(const DraftPlan& plan, void* workspace, hipStream_t st, const Upload* also)
+{
+    char* ws = static_cast<char*>(workspace);
+    if (plan.n == 0) return also && also->dst ? put_table(also->dst, also->bytes.data(), also->bytes.size(), st, also->zero, also->zero_bytes) : PRUNER_OK;
+    if (!also || !also->dst) return put_table(ws, plan.image.data(), plan.image.size(), st);
+    // the other table rides along in the same launch if it starts shortly behind this call's tables (with many
+    // subgraphs that share descriptors the reserved room is much larger than the tables: then it travels by itself)
+    const ptrdiff_t at = static_cast<const char*>(also->dst) - ws;
+    if (at < (ptrdiff_t)plan.image.size()) return PRUNER_EINVAL;
+    if (at <= (ptrdiff_t)plan.image.size() + 4096) {
+        std::vector<char> image(plan.image);
+        image.resize((size_t)at, 0);
+        image.insert(image.end(), also->bytes.begin(), also->bytes.end());
+        return put_table(ws, image.data(), image.size(), st, also->zero, also->zero_bytes);
+    }
+    const int rc = put_table(ws, plan.image.data(), plan.image.size(), st);
+    if (rc) return rc;
+    return put_table(also->dst, also->bytes.data(), also->bytes.size(), st, also->zero, also->zero_bytes);
+}
+
+int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tiles, float* score, int64_t* symbols, hipStream_t st,
+              uint32_t* first_digit, uint32_t* block_max, int copies, const MutArgs* mut)
+{
+    const SegEnt* d_segs = static_cast<const SegEnt*>(workspace);
+    const SgDesc* d_descs = reinterpret_cast<const SgDesc*>(static_cast<const char*>(workspace) + plan.descs_at);
+    // measurement hook: events around the launch that covers the most candidates
+    const DraftPlan::Launch* timed = nullptr;
+    if (g_time_start && g_time_stop) {
+        for (const DraftPlan::Launch& L : plan.launches)
+            if (L.blocks > 0 && (!timed || L.candidates > timed->candidates)) timed = &L;
+        if (g_time_bytes) *g_time_bytes = timed ? timed->bytes : 0;
+    }
+    if (!plan.counts) first_digit = block_max = nullptr;
+    for (const DraftPlan::Launch& L : plan.launches) {
+        if (L.blocks == 0) continue;
+        if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_start), st) != hipSuccess) return PRUNER_EHIP;
+        const DraftFn fn = reinterpret_cast<DraftFn>(const_cast<void*>(mut ? L.fn : L.fn_read));
+        hipLaunchKernelGGL(fn, dim3((unsigned)L.blocks), dim3(kBlock), 0, st, d_segs + L.first_seg, L.n_seg, d_descs, tiles, plan.tiles_pitch,
+                           plan.flags, score, symbols, plan.n, first_digit, block_max, copies, plan.n_sg, mut ? *mut : MutArgs{});
+        if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_stop), st) != hipSuccess) return PRUNER_EHIP;
+        PRUNER_LAUNCH_CHECK();
+    }
+    return PRUNER_OK;
+}
+
+int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch,
+                 int32_t flags, float* score, int64_t* symbols, void* workspace, size_t workspace_bytes, hipStream_t st,
+                 uint32_t* first_digit, uint32_t* block_max, int copies, bool* counted, const Upload* also)
+{
+    if (counted) *counted = false;
+    DraftPlan plan;
+    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes,
+                        first_digit != nullptr && copies >= 1, false, &plan);
+    if (rc) return rc;
+    rc = draft_upload(plan, workspace, st, also);
+    if (rc) return rc;
+    rc = draft_run(plan, workspace, tiles, score, symbols, st, first_digit, block_max, copies, nullptr);
+    if (rc) return rc;
+    if (counted) *counted = plan.counts;
+    return PRUNER_OK;
+}
 
 }  // namespace pruner
 

@@ -14,13 +14,18 @@
 //   lse_mutate  one thread per child: a parent drawn uniformly from S_spec (truncation selection: the paper names a
 //               genetic algorithm guided by the draft fitness and gives no operator), and with the given probability
 //               one prime factor of one tile factor moved to another level of the same axis, fragment multiples kept
-// When the population is large enough for one draft launch per loop-nest class, the mutation of a step is not a
-// launch of its own: the next step's draft kernels make the children, store them and score them while they are in
-// registers (the population is then written once per step and never read for scoring); only the last step's
-// mutation, whose children nobody scores, is a launch.
+// Short segments with a small S_spec (kShortMax entries, k up to kShortK: the populations of an ordinary tuning round) take
+// one launch for the selection and all of PriorFilter instead:
+//   lse_select  one workgroup per subgraph: the k best of S_x from keys in registers, their schedules' hashes, the union
+//               with S_spec and the new S_spec's records
+// When the population gets one draft launch per loop-nest class, the mutation of a step is not a launch of its own: the
+// next step's draft kernels make the children, store them and score them while they are in registers (the population is
+// then written once per step and never read for scoring); only the last step's mutation, whose children nobody scores, is
+// a launch.
 // Random numbers are counter-based (SplitMix64, Steele/Lea/Flood OOPSLA 2014: draw c is the c-th output of the
 // generator started from the seed), so the result does not depend on how the work is laid out.
 #include "lse_child.h"
+#include "select_common.h"
 
 #include <string.h>
 
@@ -266,6 +271,382 @@ __global__ void __launch_bounds__(kLseThreads) lse_merge_kernel(int k, int P, in
     if (threadIdx.x == 0) new_count[s] = (int32_t)count;
 }
 
+// ---- short segments: selection and PriorFilter in one launch -----------------------------------------------------------
+// One workgroup of 1024 threads per subgraph; thread t holds entries t, t + 1024, ... of the segment as keys.
+//   1. the key of rank k: histograms of 2048 bins over the range the keys span, then over the range of the bin that holds
+//      rank k, and so on until that bin holds exactly what is still to take, or few entries (then ranked by counting), or one
+//      key value only (then its first entries in index order are taken).  Keys are ordered like logarithms: a bin of the
+//      first pass is a fraction of a per cent to a few per cent of a score;
+//   2. the chosen entries' schedules (one per thread; from the second step on the draft kernels leave the children as records
+//      too, a record being one or two requests where a column's rows are one each), their hashes, and their order by (score,
+//      hash, age): every wavefront sorts its 64 in registers, and neighbouring runs are merged, an entry's place being its
+//      place in its run plus, by bisection, the greater ones in the other;
+//   3. the union with the old S_spec, whose keys come in order from the step before, as in lse_merge; every thread then
+//      writes the record it holds to the record's new place.
+// Bound: the latency of these dependent stages (a compute unit works alone on a subgraph).  8,000 entries, k = 512: 23 us
+// where selection (26), keys (9), merge (18) and copy (7) took 60 in four launches.
+
+constexpr int kShortPer = 32;
+constexpr int kShortMax = kLseThreads * kShortPer;   // entries of a segment
+constexpr int kShortK = 1024;                        // S_spec: one old and one new member per thread
+constexpr int kShortBin = 256;                       // entries of rank k's bin that are ranked by counting instead of split further
+
+__device__ __forceinline__ void wave_sort_descending(uint64_t& hi, uint64_t& lo)   // the wavefront's 64 pairs over its lanes, largest first
+{
+    const int lane = lane_id();
+    auto exchange = [&](auto stride_c, int size) {
+        constexpr int stride = decltype(stride_c)::value;
+        const uint64_t oh = lane_xor_u64<stride>(hi), ol = lane_xor_u64<stride>(lo);
+        const bool lower = (lane & stride) == 0, down = (lane & size) == 0;
+        const bool keep = (lower == down) == key_greater(hi, lo, oh, ol);
+        hi = keep ? hi : oh;
+        lo = keep ? lo : ol;
+    };
+#pragma unroll
+    for (int size = 2; size <= kWave; size <<= 1) {
+        if (size >= 64) exchange(std::integral_constant<int, 32>{}, size);
+        if (size >= 32) exchange(std::integral_constant<int, 16>{}, size);
+        if (size >= 16) exchange(std::integral_constant<int, 8>{}, size);
+        if (size >= 8) exchange(std::integral_constant<int, 4>{}, size);
+        if (size >= 4) exchange(std::integral_constant<int, 2>{}, size);
+        exchange(std::integral_constant<int, 1>{}, size);
+    }
+}
+
+// S_spec between the steps of the short route: its keys in order and its records, by subgraph
+struct ShortSpec {
+    uint64_t *hi, *lo;   // [n_sg][k]
+    uint4* aos;          // [n_sg][k][kAosSlots / 8]
+    int32_t* count;      // [n_sg]
+};
+
+// PER: entries of a segment per thread (the longest segment decides).  first: there is no S_spec yet.  spec_tiles,
+// spec_score and spec_count are written when they are not null (the last step).
+template <int PER>
+__global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* __restrict__ segs, int k, bool first, const float* __restrict__ score,
+                                                                 const uint16_t* __restrict__ tiles, int64_t pitch,
+                                                                 const uint4* __restrict__ child_aos /* or null */, ShortSpec before, ShortSpec now,
+                                                                 int64_t spec_pitch, int rows, uint16_t* __restrict__ spec_tiles,
+                                                                 float* __restrict__ spec_score, int32_t* __restrict__ spec_count)
+{
+    __shared__ uint32_t hist[kBins];                 // later: which entry holds each place of the union, and its rank in the new S_spec
+    __shared__ __attribute__((aligned(16))) uint64_t list_hi[2 * kShortK], list_lo[2 * kShortK];   // the chosen entries: sorted runs, merged from one half into the other (list_hi
+                                                                       // first holds the chosen words, list_lo the words of rank k's bin)
+    __shared__ uint64_t old_hi[kShortK], old_lo[kShortK];
+    __shared__ __attribute__((aligned(16))) uint16_t record[kShortK * kAosSlots];   // the chosen entries' schedules
+    __shared__ uint32_t wave_tot[16], found[3], low_of[16], high_of[16];
+    __shared__ uint32_t fill, bin_fill, bin_rank[kShortBin];
+    uint16_t* who = reinterpret_cast<uint16_t*>(hist);
+    uint16_t* rank_of = who + 2 * kShortK;
+    static_assert(sizeof(hist) >= 4 * kShortK * sizeof(uint16_t), "places and ranks of the union's 2 k entries");
+    const int s = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    const LseSeg seg = segs[s];
+    const int len = (int)(seg.end - seg.begin);
+    const int64_t col0 = (int64_t)s * k;
+
+    uint32_t key[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * kLseThreads + tid;
+        key[j] = i < len ? key_of(score[seg.begin + i]) : 0u;   // 0 is below every key of a number
+    }
+    // Thread t holds the chosen entry t and, for an S_spec of at most half the threads, old member t - kLseThreads / 2 (the two
+    // groups then work side by side), else old member t.
+    const bool side_by_side = k <= kLseThreads / 2;
+    const int old_at = side_by_side ? tid - kLseThreads / 2 : tid;
+    // the old S_spec travels meanwhile
+    int n_old = first ? 0 : before.count[s];
+    n_old = n_old < 0 ? 0 : n_old > k ? k : n_old;
+    uint64_t oh = 0, ol = 0;
+    uint4 old_rec[kAosSlots / 8];
+    const bool has_old = old_at >= 0 && old_at < n_old;
+    if (has_old) {
+        oh = before.hi[col0 + old_at];
+        ol = before.lo[col0 + old_at];
+#pragma unroll
+        for (int q = 0; q < kAosSlots / 8; ++q) old_rec[q] = before.aos[(col0 + old_at) * (kAosSlots / 8) + q];
+    }
+
+    // 1. the key of rank k
+    {
+        uint32_t hi_key = 0, inv_lo = 0;   // the largest key, and the largest complement of one
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            hi_key = key[j] > hi_key ? key[j] : hi_key;
+            const uint32_t inv = key[j] ? ~key[j] : 0u;
+            inv_lo = inv > inv_lo ? inv : inv_lo;
+        }
+        hi_key = wave_inclusive_max(hi_key);
+        inv_lo = wave_inclusive_max(inv_lo);
+        if (lane == kWave - 1) {
+            high_of[wave] = hi_key;
+            low_of[wave] = inv_lo;
+        }
+        if (tid == 0) fill = bin_fill = 0;
+        if (tid < kShortBin) bin_rank[tid] = 0;
+    }
+    __syncthreads();
+    uint32_t lo_key, width;   // the keys lo_key .. lo_key + width hold rank k
+    {
+        uint32_t h = 0, l = 0;
+#pragma unroll
+        for (int w = 0; w < kLseThreads / kWave; ++w) {
+            h = high_of[w] > h ? high_of[w] : h;
+            l = low_of[w] > l ? low_of[w] : l;
+        }
+        lo_key = ~l;
+        width = h - lo_key;
+    }
+    uint32_t k_rem = (uint32_t)k, in_bin;
+    for (;;) {
+        const int bits = width ? 32 - __clz(width) : 0, shift = bits > 11 ? bits - 11 : 0;
+        for (int i = tid; i < kBins; i += kLseThreads) hist[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            if (j * kLseThreads < len) light_hist_add(hist, (key[j] - lo_key) >> shift, key[j] != 0u && key[j] - lo_key <= width);
+        }
+        __syncthreads();
+        find_bucket(hist, k_rem, wave_tot, found);
+        lo_key += found[0] << shift;
+        width = (1u << shift) - 1u;
+        k_rem = found[1];
+        in_bin = found[2];
+        __syncthreads();
+        if (shift == 0 || in_bin == k_rem || in_bin <= (uint32_t)kShortBin) break;
+    }
+    // entries above the bin are taken; of the bin's all, or the best k_rem: by rank among a few, or (ties) in index order
+    const bool all = in_bin == k_rem, few = !all && in_bin <= (uint32_t)kShortBin, ties = !all && !few;
+    if (ties) {
+        // ties of each (round j, wavefront), numbered in index order: one scan over PER x 16 counts
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const unsigned long long m = __ballot(key[j] == lo_key);
+            if (lane == 0) hist[j * 16 + wave] = (uint32_t)__popcll(m);
+        }
+        __syncthreads();
+        uint32_t total;
+        const uint32_t c = tid < PER * 16 ? hist[tid] : 0u;
+        const uint32_t before_mine = block_excl_scan<kLseThreads>(c, wave_tot, &total);
+        if (tid < PER * 16) hist[tid] = before_mine;
+        __syncthreads();
+    }
+    {
+        uint32_t take = 0, in_few = 0;   // bit j: entry j is chosen / goes to the list of the bin's few
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const bool in = key[j] != 0u && key[j] - lo_key <= width;
+            bool chosen = key[j] > lo_key && (!in || all);
+            chosen = chosen || (in && all);
+            if (ties) {
+                const unsigned long long m = __ballot(in);
+                chosen = chosen || (in && hist[j * 16 + wave] + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) < k_rem);
+            }
+            take |= chosen ? 1u << j : 0u;
+            in_few |= in && few ? 1u << j : 0u;
+        }
+        // (both counts of a thread in one word: a workgroup holds at most 2^15 entries)
+        const uint32_t mine = (uint32_t)__popc(take) | ((uint32_t)__popc(in_few) << 16);
+        const uint32_t upto = wave_inclusive_sum(mine);
+        uint32_t base = 0, few_base = 0;
+        if (lane == kWave - 1) {
+            if (upto & 0xFFFFu) base = atomicAdd(&fill, upto & 0xFFFFu);
+            if (upto >> 16) few_base = atomicAdd(&bin_fill, upto >> 16);
+        }
+        uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1) + ((upto - mine) & 0xFFFFu);
+        uint32_t at_few = (uint32_t)__builtin_amdgcn_readlane((int)few_base, kWave - 1) + ((upto - mine) >> 16);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const uint32_t i = (uint32_t)(j * kLseThreads + tid);
+            if ((take >> j) & 1u) {
+                if (at < (uint32_t)k) list_hi[at] = compose(key[j], i);
+                ++at;
+            }
+            if ((in_few >> j) & 1u) {
+                if (at_few < (uint32_t)kShortBin) list_lo[at_few] = compose(key[j], i);
+                ++at_few;
+            }
+        }
+    }
+    __syncthreads();
+    if (few) {
+        const int n_bin = (int)in_bin, e = tid & (kShortBin - 1), quarter = tid / kShortBin;
+        static_assert(kLseThreads == 4 * kShortBin, "four threads count for an entry");
+        const uint64_t me = e < n_bin ? list_lo[e] : ~0ull;
+        uint32_t greater = 0;
+        const int per = (n_bin + 3) >> 2, from = quarter * per, to = from + per < n_bin ? from + per : n_bin;
+#pragma unroll 4
+        for (int x = from; x < to; ++x) greater += list_lo[x] > me ? 1u : 0u;
+        if (e < n_bin && greater) atomicAdd(&bin_rank[e], greater);
+        __syncthreads();
+        if (tid < n_bin && bin_rank[tid] < k_rem) {
+            const uint32_t at = atomicAdd(&fill, 1u);
+            if (at < (uint32_t)k) list_hi[at] = me;
+        }
+        __syncthreads();
+    }
+
+    // 2. the chosen entries' schedules, one per thread.  (The loops from here on are kept rolled: a workgroup runs this code
+    // once, and most of what unrolled code would cost is its way into the instruction cache.)
+    uint64_t nh = 0, nl = 0;
+    const bool has_new = tid < k;
+    if (has_new) {
+        const uint64_t w = list_hi[tid];
+        const uint32_t i = index_of(w) < (uint32_t)len ? index_of(w) : 0u;   // (always inside the segment)
+        uint16_t* rec = record + tid * kAosSlots;
+        if (child_aos) {
+            const uint4* from = child_aos + (seg.begin + i) * (kAosSlots / 8);
+            uint4 p[kAosSlots / 8];
+#pragma unroll
+            for (int q = 0; q < kAosSlots / 8; ++q) {
+                p[q] = make_uint4(0u, 0u, 0u, 0u);
+                if (8 * q < seg.n_slots) p[q] = from[q];
+            }
+#pragma unroll
+            for (int q = 0; q < kAosSlots / 8; ++q) *reinterpret_cast<uint4*>(rec + 8 * q) = p[q];
+        } else {
+            const uint16_t* col = tiles + seg.begin + i;
+            uint16_t f[kAosSlots];
+#pragma unroll
+            for (int r = 0; r < kAosSlots; ++r) f[r] = r < PRUNER_MAX_SLOTS && r < seg.n_slots ? col[r * pitch] : (uint16_t)0;
+#pragma unroll
+            for (int q = 0; q < kAosSlots / 8; ++q) {
+                uint32_t p[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) p[e] = (uint32_t)f[8 * q + 2 * e] | ((uint32_t)f[8 * q + 2 * e + 1] << 16);
+                *reinterpret_cast<uint4*>(rec + 8 * q) = make_uint4(p[0], p[1], p[2], p[3]);
+            }
+        }
+        uint64_t h = (uint64_t)seg.n_slots;
+#pragma unroll 1
+        for (int r = 0; r < seg.n_slots; ++r) h = splitmix64_draw(h, (uint64_t)rec[r] + 1);
+        const uint64_t inv = ~h;
+        nh = (w & 0xFFFFFFFF00000000ull) | (inv >> 32);
+        nl = (inv << 32) | (uint64_t)(0xFFFFFFFFu - ((uint32_t)k + i));   // younger than S_spec's members, then by index
+    }
+    if (has_old) {
+        old_hi[old_at] = oh;
+        old_lo[old_at] = ol;
+    }
+    int sorted = kWave;   // 64 or the power of two at or above k
+    while (sorted < k) sorted <<= 1;
+    if (!has_new) nl = (uint64_t)tid;   // fillers: behind every entry (no entry has hi = 0), and distinct
+    __syncthreads();   // the chosen words have been read
+    if (tid < sorted) {
+        uint64_t sh = nh, sl = nl;
+        wave_sort_descending(sh, sl);
+        list_hi[tid] = sh;
+        list_lo[tid] = sl;
+    }
+    __syncthreads();
+    // entries of a run of n that are greater than (xh, xl)
+    auto greater_in = [](const uint64_t* hi, const uint64_t* lo, int n, uint64_t xh, uint64_t xl) {
+        int a = 0;
+#pragma unroll 1
+        for (int step = 1 << (31 - __clz(n | 1)); step > 0; step >>= 1) {
+            const bool there = a + step <= n;
+            const int at = there ? a + step - 1 : 0;
+            a += there && key_greater(hi[at], lo[at], xh, xl) ? step : 0;
+        }
+        return a;
+    };
+    int rank = 0, from = 0;   // the entry's place in its run; the half of the lists that holds the runs
+    if (tid < sorted) rank = greater_in(list_hi + 64 * wave, list_lo + 64 * wave, kWave, nh, nl);
+#pragma unroll 1
+    for (int run = kWave; run < sorted; run *= 2) {
+        if (tid < sorted) {
+            const int other = from + ((tid & ~(run - 1)) ^ run);
+            rank += greater_in(list_hi + other, list_lo + other, run, nh, nl);
+            const int to = (from ^ kShortK) + (tid & ~(2 * run - 1)) + rank;
+            list_hi[to] = nh;
+            list_lo[to] = nl;
+        }
+        from ^= kShortK;
+        __syncthreads();
+    }
+    const uint64_t *new_hi = list_hi + from, *new_lo = list_lo + from;   // all chosen entries in order
+
+    // 3. places in the union (all 128-bit keys differ: they carry the age): one's own rank and the greater ones of the other list
+    int place_new = 0, place_old = 0;
+    if (side_by_side) {
+        const bool mine_new = tid < kLseThreads / 2;
+        const int greater = greater_in(mine_new ? old_hi : new_hi, mine_new ? old_lo : new_lo, mine_new ? n_old : k, mine_new ? nh : oh, mine_new ? nl : ol);
+        place_new = rank + greater;
+        place_old = old_at + greater;
+    } else {
+        place_new = rank + greater_in(old_hi, old_lo, n_old, nh, nl);
+        place_old = old_at + greater_in(new_hi, new_lo, k, oh, ol);
+    }
+    if (has_new) who[place_new] = (uint16_t)(kShortK + rank);
+    if (has_old) who[place_old] = (uint16_t)old_at;
+    __syncthreads();
+    const int m = n_old + k;
+    uint32_t keep = 0;
+    {
+        uint64_t ph = 0, pl = 0;
+#pragma unroll
+        for (int j = -1; j < 2; ++j) {
+            const int at = 2 * tid + j;
+            uint64_t xh = 0, xl = 0;
+            if (at >= 0 && at < m) {
+                const int id = who[at];
+                xh = id < kShortK ? old_hi[id] : new_hi[id - kShortK];
+                xl = id < kShortK ? old_lo[id] : new_lo[id - kShortK];
+            }
+            // a copy has the key and the hash of its predecessor
+            if (j >= 0 && at < m && !(at > 0 && xh == ph && (xl >> 32) == (pl >> 32))) keep |= 1u << j;
+            ph = xh, pl = xl;
+        }
+    }
+    uint32_t total;
+    const uint32_t at_rank = block_excl_scan<kLseThreads>((uint32_t)__popc(keep), wave_tot, &total);
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const uint32_t r = at_rank + (j == 1 ? keep & 1u : 0u);
+        if (2 * tid + j < m) rank_of[2 * tid + j] = (keep >> j) & 1u && r < (uint32_t)k ? (uint16_t)r : (uint16_t)0xFFFFu;
+    }
+    __syncthreads();
+    const uint32_t count = total < (uint32_t)k ? total : (uint32_t)k;
+    auto write = [&](int r, uint64_t xh, uint64_t xl, const uint4 (&w)[kAosSlots / 8]) {
+        now.hi[col0 + r] = xh;
+        now.lo[col0 + r] = (xl & 0xFFFFFFFF00000000ull) | (uint64_t)(0xFFFFFFFFu - (uint32_t)r);
+#pragma unroll
+        for (int q = 0; q < kAosSlots / 8; ++q) now.aos[(col0 + r) * (kAosSlots / 8) + q] = w[q];
+        if (spec_tiles) {
+            spec_score[col0 + r] = lse_score_of((uint32_t)(xh >> 32));
+#pragma unroll
+            for (int q = 0; q < kAosSlots / 8; ++q) {
+                const uint4 v = w[q];
+                const uint32_t p[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (8 * q + e < PRUNER_MAX_SLOTS && 8 * q + e < rows) spec_tiles[(8 * q + e) * spec_pitch + col0 + r] = (uint16_t)(p[e >> 1] >> (16 * (e & 1)));
+            }
+        }
+    };
+    const int r_new = has_new ? (int)rank_of[place_new] : 0xFFFF, r_old = has_old ? (int)rank_of[place_old] : 0xFFFF;
+#pragma unroll 1
+    for (int turn = side_by_side ? 1 : 0; turn < 2; ++turn) {   // (side by side a thread has one of the two)
+        const bool mine_new = side_by_side ? tid < kLseThreads / 2 : turn == 0;
+        const int r = mine_new ? r_new : r_old;
+        uint4 w[kAosSlots / 8];
+#pragma unroll
+        for (int q = 0; q < kAosSlots / 8; ++q) {
+            const uint4 mine = *reinterpret_cast<const uint4*>(record + tid * kAosSlots + 8 * q);
+            w[q] = make_uint4(mine_new ? mine.x : old_rec[q].x, mine_new ? mine.y : old_rec[q].y, mine_new ? mine.z : old_rec[q].z, mine_new ? mine.w : old_rec[q].w);
+        }
+        if (r != 0xFFFF) write(r, mine_new ? nh : oh, mine_new ? nl : ol, w);
+    }
+    if (tid == 0) now.count[s] = (int32_t)count;
+    if (spec_tiles) {
+        if (tid == 0) spec_count[s] = (int32_t)count;
+        for (int r = (int)count + tid; r < k; r += kLseThreads) {
+            spec_score[col0 + r] = -__builtin_inff();
+            for (int row = 0; row < rows; ++row) spec_tiles[row * spec_pitch + col0 + r] = 0;
+        }
+    }
+}
+
 // The tile factors of the new S_spec; rows a subgraph does not own and entries past the count are cleared.  A second
 // copy holds each schedule's factors side by side (32 x uint16 = 64 bytes): the mutation reads a parent from there
 // with four loads instead of one per factor.
@@ -377,7 +758,7 @@ __global__ void __launch_bounds__(256) lse_mutate_kernel(const LseSeg* __restric
 }
 
 struct LseLayout {
-    size_t filter, table, best_idx, best_val, alt_tiles, alt_score, alt_count, zero_count, source, key_hi, key_lo, aos, total;
+    size_t filter, table, best_idx, best_val, alt_tiles, alt_score, alt_count, zero_count, source, key_hi, key_lo, aos, aos_b, children, total;
 };
 
 LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
@@ -402,6 +783,10 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
     L.key_hi = take(4 * cols * sizeof(uint64_t));   // P < 4k entries per subgraph (2k rounded up to a power of two)
     L.key_lo = take(4 * cols * sizeof(uint64_t));
     L.aos = take(cols * kAosSlots * sizeof(uint16_t));
+    // the short route's records take turns, and so a population that may take it has its children as records
+    const bool may_be_short = k <= kShortK && n <= (int64_t)n_sg * kShortMax;
+    L.aos_b = take((may_be_short ? cols : 0) * kAosSlots * sizeof(uint16_t));
+    L.children = take((may_be_short ? (size_t)n : 0) * kAosSlots * sizeof(uint16_t));
     L.total = off;
     return L;
 }
@@ -482,23 +867,68 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     int32_t* spec_n[2] = {spec_count, reinterpret_cast<int32_t*>(ws + L.alt_count)};
     const int64_t spec_pitch = (int64_t)n_sg * k;
 
+    auto mutate = [&](int32_t t, const int32_t* count, const uint4* records) {   // SchMutation of step t, in place (parents come from S_spec, not from S_x)
+        if (tiles_pitch % 4 == 0 && aligned(tiles, 8))
+            hipLaunchKernelGGL(lse_mutate_kernel<4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, d_table, n_sg, k, n, tiles, tiles_pitch,
+                               records, count, seed, (uint64_t)t, mutate_q16);
+        else
+            hipLaunchKernelGGL(lse_mutate_kernel<1>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d_table, n_sg, k, n, tiles, tiles_pitch,
+                               records, count, seed, (uint64_t)t, mutate_q16);
+    };
+    void* const draft_ws = ws + L.filter;
+
+    // The short route: every segment in one workgroup's registers, S_spec's members one per thread.
+    int64_t longest = 0;
+    for (int32_t s = 0; s < n_sg; ++s) longest = seg_off[s + 1] - seg_off[s] > longest ? seg_off[s + 1] - seg_off[s] : longest;
+    if (longest <= kShortMax && k <= kShortK) {
+        DraftPlan plan;
+        rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, false, n_steps > 1, &plan);
+        if (rc) return rc;
+        // all tables in one launch: this route has no selection workspace, the segment table stands in its place
+        d_table = reinterpret_cast<LseSeg*>(ws + L.filter + draft_bytes);
+        Upload pending;
+        pending.bytes.assign(reinterpret_cast<const char*>(table.data()), reinterpret_cast<const char*>(table.data() + table.size()));
+        pending.dst = d_table;
+        rc = draft_upload(plan, draft_ws, st, &pending);
+        if (rc) return rc;
+        uint64_t* const keys[2] = {key_hi, key_lo};
+        const ShortSpec spec[2] = {ShortSpec{keys[0], keys[0] + spec_pitch, aos, zero_count},
+                                   ShortSpec{keys[1], keys[1] + spec_pitch, reinterpret_cast<uint4*>(ws + L.aos_b), reinterpret_cast<int32_t*>(ws + L.alt_count)}};
+        for (int32_t t = 0; t < n_steps; ++t) {
+            const ShortSpec &now = spec[t & 1], &before = spec[(t & 1) ^ 1];
+            uint4* const children = reinterpret_cast<uint4*>(ws + L.children);
+            const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, children};
+            const bool made = t > 0 && plan.makes;
+            if (t > 0 && !plan.makes) {
+                mutate(t - 1, before.count, before.aos);
+                PRUNER_LAUNCH_CHECK();
+            }
+            rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, nullptr, nullptr, 1, made ? &owed : nullptr);
+            if (rc) return rc;
+            const bool last = t + 1 == n_steps;
+            uint16_t* const to_tiles = last ? spec_tiles : nullptr;
+            float* const to_score = last ? spec_score : nullptr;
+            int32_t* const to_count = last ? spec_count : nullptr;
+#define PRUNER_SELECT(PER) hipLaunchKernelGGL(lse_select_kernel<PER>, dim3((unsigned)n_sg), dim3(kLseThreads), 0, st, d_table, k, t == 0, score, tiles, tiles_pitch, made ? children : nullptr, before, now, \
+                                              spec_pitch, tile_rows, to_tiles, to_score, to_count)
+            if (longest <= 8 * kLseThreads) PRUNER_SELECT(8);
+            else PRUNER_SELECT(kShortPer);
+#undef PRUNER_SELECT
+            PRUNER_LAUNCH_CHECK();
+        }
+        mutate(n_steps - 1, spec_count, spec[(n_steps - 1) & 1].aos);
+        PRUNER_LAUNCH_CHECK();
+        return PRUNER_OK;
+    }
+
     // the table, and the "no S_spec yet" counts of the first step, in one launch
     rc = put_table(d_table, table.data(), table.size() * sizeof(LseSeg), st, zero_count, round_up((size_t)n_sg * sizeof(int32_t), 4));
     if (rc) return rc;
 
     const size_t filter_bytes = L.table - L.filter;
-    auto mutate = [&](int32_t t, const int32_t* count) {   // SchMutation of step t, in place (parents come from S_spec, not from S_x)
-        if (tiles_pitch % 4 == 0 && aligned(tiles, 8))
-            hipLaunchKernelGGL(lse_mutate_kernel<4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, d_table, n_sg, k, n, tiles, tiles_pitch,
-                               aos, count, seed, (uint64_t)t, mutate_q16);
-        else
-            hipLaunchKernelGGL(lse_mutate_kernel<1>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d_table, n_sg, k, n, tiles, tiles_pitch,
-                               aos, count, seed, (uint64_t)t, mutate_q16);
-    };
     // The mutation of step t - 1 is owed when step t begins: the draft kernels of step t make, store and score the
-    // children in one pass if their launch shape allows it (large populations), else it runs as a launch of its own
-    // first.  Which of the two is decided by the first step's launches (the shape does not change between steps).
-    bool fuses = false;
+    // children in one pass if their launch shape allows it, else it runs as a launch of its own first.
+    DraftPlan plan_first, plan_later;
     for (int32_t t = 0; t < n_steps; ++t) {
         const int now = (n_steps - 1 - t) & 1, before = now ^ 1;   // the last step writes the caller's arrays (index 0)
         // C_SA over S_x and its k best: the launches of pruner_prior_filter
@@ -506,19 +936,21 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         Upload pending;
         rc = topk_prepare(seg_off, n_sg, k, ws + L.filter + draft_bytes, filter_bytes - draft_bytes, st, &ctx, &pending);
         if (rc) return rc;
-        const MutArgs owed{d_table, aos, spec_n[before], seed, (uint64_t)(t - 1), mutate_q16, k};
-        if (t > 0 && !fuses) {
-            mutate(t - 1, spec_n[before]);
+        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, false, &plan_first);
+        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, true, &plan_later);
+        if (rc) return rc;
+        const DraftPlan& plan = t == 0 ? plan_first : plan_later;
+        const MutArgs owed{d_table, aos, spec_n[before], seed, (uint64_t)(t - 1), mutate_q16, k, nullptr};
+        if (t > 0 && !plan.makes) {
+            mutate(t - 1, spec_n[before], aos);
             PRUNER_LAUNCH_CHECK();
         }
-        bool counted = false, mutated = false;
-        rc = draft_launch(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws + L.filter, draft_bytes, st,
-                          ctx.large ? ctx.d_hist : nullptr, ctx.large ? ctx.d_block_max : nullptr, ctx.copies, &counted, &pending,
-                          t > 0 && fuses ? &owed : nullptr, &mutated);
+        rc = draft_upload(plan, draft_ws, st, &pending);
         if (rc) return rc;
-        if (t == 0) fuses = ctx.large && counted && draft_launches_by_class(n);
-        else if (fuses != mutated) return PRUNER_EHIP;   // (the shape is the same in every step)
-        rc = topk_finish(ctx, score, seg_off, best_idx, best_val, ctx.large && counted, st);
+        rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, ctx.large ? ctx.d_hist : nullptr, ctx.large ? ctx.d_block_max : nullptr, ctx.copies,
+                       t > 0 && plan.makes ? &owed : nullptr);
+        if (rc) return rc;
+        rc = topk_finish(ctx, score, seg_off, best_idx, best_val, ctx.large && plan.counts, st);
         if (rc) return rc;
         // PriorFilter over the union, then the new S_spec's tile factors
         const int32_t* old_n = t == 0 ? zero_count : spec_n[before];
@@ -533,7 +965,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         PRUNER_LAUNCH_CHECK();
     }
     // the last step's mutation: S_x as the caller receives it
-    mutate(n_steps - 1, spec_n[0]);
+    mutate(n_steps - 1, spec_n[0], aos);
     PRUNER_LAUNCH_CHECK();
     return PRUNER_OK;
 }

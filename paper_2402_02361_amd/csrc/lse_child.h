@@ -122,6 +122,7 @@ struct MutArgs {
     uint64_t seed, step;
     uint32_t mutate_q16;
     int32_t k;
+    uint4* child_aos;          // the children as records too, [n][kAosSlots / 8] (the pieces their slots reach); or null
 };
 
 }  // namespace pruner

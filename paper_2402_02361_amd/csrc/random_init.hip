@@ -61,7 +61,7 @@ __device__ __forceinline__ uint32_t compositions(int m, int parts)
 // Row R of a space's table: the factors of the R-th ordered factorisation, level 0 in the low half of .x
 __global__ void __launch_bounds__(256) ri_table_kernel(const RiSpace* __restrict__ spaces, uint2* __restrict__ table)
 {
-    const RiSpace sp = spaces[blockIdx.y];
+    const RiSpace& sp = spaces[blockIdx.y];   // (by reference: a copy would put its arrays, indexed by a loop, into scratch memory)
     uint32_t R = blockIdx.x * 256 + threadIdx.x;
     if (R >= sp.count) return;
     const uint32_t row = sp.table_off + R;
@@ -71,7 +71,9 @@ __global__ void __launch_bounds__(256) ri_table_kernel(const RiSpace* __restrict
         R /= sp.C[i];
         // the composition of e into `levels` parts with lexicographic rank r
         int rest = (int)sp.e[i];
-        for (int l = 0; l < sp.levels; ++l) {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            if (l >= sp.levels) continue;
             int v = rest;   // the last part takes what is left
             if (l < sp.levels - 1) {
                 const int after = sp.levels - l - 1;   // parts after this one
@@ -85,8 +87,8 @@ __global__ void __launch_bounds__(256) ri_table_kernel(const RiSpace* __restrict
             rest -= v;
         }
     }
-    f[sp.levels - 1] *= (uint32_t)sp.frag;
-    for (int l = sp.levels; l < 4; ++l) f[l] = 0u;
+#pragma unroll
+    for (int l = 0; l < 4; ++l) f[l] = l == sp.levels - 1 ? f[l] * (uint32_t)sp.frag : l >= sp.levels ? 0u : f[l];
     table[row] = make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16));
 }
 
@@ -297,12 +299,14 @@ extern "C" int pruner_random_init(const pruner_subgraph* sg, int32_t n_sg, const
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
-    rc = put_table(ws + L.spaces, plan.spaces.data(), plan.spaces.size() * sizeof(RiSpace), st);
-    if (rc) return rc;
-    rc = put_table(ws + L.axes, plan.axes.data(), plan.axes.size() * sizeof(RiAxis), st);
-    if (rc) return rc;
-    rc = put_table(ws + L.segs, plan.segs.data(), plan.segs.size() * sizeof(RiSeg), st);
-    if (rc) return rc;
+    {   // the three tables lie one behind the other: one upload (a launch as a rule)
+        std::vector<char> image(L.segs + plan.segs.size() * sizeof(RiSeg), 0);
+        memcpy(image.data() + L.spaces, plan.spaces.data(), plan.spaces.size() * sizeof(RiSpace));
+        memcpy(image.data() + L.axes, plan.axes.data(), plan.axes.size() * sizeof(RiAxis));
+        memcpy(image.data() + L.segs, plan.segs.data(), plan.segs.size() * sizeof(RiSeg));
+        rc = put_table(ws, image.data(), image.size(), st);
+        if (rc) return rc;
+    }
     uint2* table = reinterpret_cast<uint2*>(ws + L.table);
     hipLaunchKernelGGL(ri_table_kernel, dim3((plan.max_count + 255) / 256, (unsigned)plan.spaces.size()), dim3(256), 0, st,
                        reinterpret_cast<const RiSpace*>(ws + L.spaces), table);

@@ -68,6 +68,62 @@ __device__ __forceinline__ void wave_hist_add(uint32_t* hist, uint32_t digit, bo
     if (active) atomicAdd(&hist[digit], 1u);
 }
 
+// The same for digits that scatter as a rule: the lanes that share the first active lane's bin are counted with one atomic
+// only when they are sixteen or more, everyone else adds 1 (a dozen instructions where wave_hist_add has fifty).
+__device__ __forceinline__ void light_hist_add(uint32_t* hist, uint32_t digit, bool active)
+{
+    const unsigned long long there = __ballot(active);
+    if (there == 0ull) return;
+    const int leader = __ffsll(there) - 1;
+    const uint32_t d0 = (uint32_t)__builtin_amdgcn_readlane((int)digit, leader);
+    const bool same = active && digit == d0;
+    const uint32_t n_same = (uint32_t)__popcll(__ballot(same));
+    const bool together = n_same >= 16u;
+    if (active && !(together && same)) atomicAdd(&hist[digit], 1u);
+    if (together && lane_id() == leader) atomicAdd(&hist[d0], n_same);
+}
+
+// Exclusive prefix sum over the workgroup (NT threads, NT/64 <= 16 wavefronts); all threads must call.
+// wave_tot: LDS, 16 entries.  *total receives the workgroup sum.
+template <int NT> __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_tot, uint32_t* total)
+{
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const uint32_t incl = wave_inclusive_sum(v);
+    __syncthreads();  // wave_tot may still be read from an earlier call
+    if (lane == kWave - 1) wave_tot[wave] = incl;
+    __syncthreads();
+    uint32_t before = 0, all = 0;
+#pragma unroll
+    for (int w = 0; w < NT / kWave; ++w) {
+        const uint32_t t = wave_tot[w];
+        before += w < wave ? t : 0u;
+        all += t;
+    }
+    *total = all;
+    return before + incl - v;
+}
+
+// Digit bucket that holds the entry of rank k_rem (ranks counted from the largest digit down) and the rank left
+// inside that bucket (out[0], out[1]) and the bucket's population (out[2]).  hist: kBins counters (LDS or global);
+// 1024 threads, two bins each.
+__device__ __forceinline__ void find_bucket(const uint32_t* hist, uint32_t k_rem, uint32_t* wave_tot, uint32_t* out /* [3] in LDS */)
+{
+    const int a = kBins - 1 - 2 * (int)threadIdx.x, b = a - 1;
+    const uint32_t ha = hist[a], hb = hist[b];
+    uint32_t total;
+    const uint32_t above = block_excl_scan<kBins / 2>(ha + hb, wave_tot, &total);
+    if (above < k_rem && k_rem <= above + ha) {
+        out[0] = (uint32_t)a;
+        out[1] = k_rem - above;
+        out[2] = ha;
+    } else if (above + ha < k_rem && k_rem <= above + ha + hb) {
+        out[0] = (uint32_t)b;
+        out[1] = k_rem - above - ha;
+        out[2] = hb;
+    }
+    __syncthreads();
+}
+
 // Merge a workgroup's LDS histogram into its copy of segment s's global histogram ([copies][n_seg][kBins]).
 template <int NT>
 __device__ __forceinline__ void flush_hist(const uint32_t* hist, uint32_t* __restrict__ ghist, int copies, int n_seg, int s)

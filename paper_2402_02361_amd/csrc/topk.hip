@@ -51,48 +51,7 @@ template <int PASS> __device__ __forceinline__ bool matches(uint32_t key, uint32
     return PASS == 0 ? true : PASS == 1 ? (key >> 21) == prefix : (key >> 10) == prefix;
 }
 
-// ---- wavefront / workgroup primitives -----------------------------------------------------------------------
-
-// Exclusive prefix sum over the workgroup (NT threads, NT/64 <= 16 wavefronts); all threads must call.
-// wave_tot: LDS, 16 entries.  *total receives the workgroup sum.
-template <int NT> __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wave_tot, uint32_t* total)
-{
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
-    const uint32_t incl = wave_inclusive_sum(v);
-    __syncthreads();  // wave_tot may still be read from an earlier call
-    if (lane == kWave - 1) wave_tot[wave] = incl;
-    __syncthreads();
-    uint32_t before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < NT / kWave; ++w) {
-        const uint32_t t = wave_tot[w];
-        before += w < wave ? t : 0u;
-        all += t;
-    }
-    *total = all;
-    return before + incl - v;
-}
-
-// Digit bucket that holds the entry of rank k_rem (ranks counted from the largest digit down) and the rank left
-// inside that bucket (out[0], out[1]) and the bucket's population (out[2]).  hist: kBins counters (LDS or global);
-// NT = 1024 threads, two bins each.
-__device__ __forceinline__ void find_bucket(const uint32_t* hist, uint32_t k_rem, uint32_t* wave_tot, uint32_t* out /* [3] in LDS */)
-{
-    const int a = kBins - 1 - 2 * (int)threadIdx.x, b = a - 1;
-    const uint32_t ha = hist[a], hb = hist[b];
-    uint32_t total;
-    const uint32_t above = block_excl_scan<kSmallThreads>(ha + hb, wave_tot, &total);
-    if (above < k_rem && k_rem <= above + ha) {
-        out[0] = (uint32_t)a;
-        out[1] = k_rem - above;
-        out[2] = ha;
-    } else if (above + ha < k_rem && k_rem <= above + ha + hb) {
-        out[0] = (uint32_t)b;
-        out[1] = k_rem - above - ha;
-        out[2] = hb;
-    }
-    __syncthreads();
-}
+// ---- the selection in LDS ---------------------------------------------------------------------------------------
 
 // The selection lives in LDS with one spare word after every 32: neighbouring threads of the sort then touch different
 // banks also when they walk 8-word groups (logical index e sits in slot(e)).
