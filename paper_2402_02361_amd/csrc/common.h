@@ -67,7 +67,7 @@ struct PerDeviceFlag {
 // Stream-ordered copy of a small host table into device memory without staging buffers: the bytes travel as
 // kernel arguments (copied by the runtime at launch), so the host copy may be freed as soon as the call returns
 // and the launch can be captured into a graph.
-constexpr int kPutBytes = 3584;
+constexpr int kPutBytes = 4032;   // with the kernel's other arguments below the 4 KB that a launch carries
 struct PutPayload {
     uint4 q[kPutBytes / 16];
 };
@@ -87,22 +87,23 @@ struct Upload {
 // Selection in two steps, so that a caller inside the library can produce the first-digit histograms itself
 // between them (the draft kernel does, while the scores are still in registers).
 struct TopkCtx {
-    bool large;            // segments too long for the one-workgroup route
+    bool large;            // the route counts first digits (not the tiny one)
+    bool pick;             // ... and takes one launch behind that
+    uint32_t window;       // where the first digit's bins are narrow (first_digit_of)
     int32_t n_sg, k;
     int64_t n, span;
     int32_t blocks;        // workgroups of a sweep launch
     int copies;            // copies of the first digit's histogram
-    bool wide;             // set by topk_finish
     void *d_segs, *d_state, *d_stage;
     uint32_t* d_hist;      // [copies][n_sg][2048] first digit, then one copy each for the second and third
     uint32_t* d_block_max; // largest key of every 256 neighbouring entries (block_max_slot), or null: the workspace holds none
-    char inline_segs[4096];  // small route: the segment table when it travels as a kernel argument
+    char inline_segs[4096];  // tiny route: the segment table when it travels as a kernel argument
     bool inline_ok;
 };
 // validates, uploads the segment table, clears the histograms (large route)
 // (defer: do not launch the upload, describe it there instead)
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t stream, TopkCtx* ctx,
-                 Upload* defer = nullptr, bool with_block_max = true);
+                 Upload* defer, bool with_block_max, uint32_t window);
 // the remaining launches; have_first_digit: d_hist already holds the first digit's counts of every segment
 int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, int32_t* idx_out, float* val_out, bool have_first_digit,
                 hipStream_t stream);
@@ -133,8 +134,13 @@ struct DraftPlan {
 // are to make their candidates from the second run on (plan->makes says whether they can).
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
                const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool mut, DraftPlan* plan);
-// (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables)
+// (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables
+// and behind which nothing else lies that must stay.  An upload that begins right behind the tables (place_behind) shares
+// their launch.
 int draft_upload(const DraftPlan& plan, void* workspace, hipStream_t stream, const Upload* also);
+// Moves the pending table to the first free place behind the plan's tables in the same workspace (it was prepared for a later
+// one, so it fits); returns where it will lie.
+void* place_behind(const DraftPlan& plan, void* workspace, Upload* also);
 // Draft scores.  With plan.counts, every score's first selection digit is added to first_digit ([copies][n_sg][2048], cleared
 // by the caller), when that is not null, and the largest key of every 256 neighbouring candidates of a segment goes to
 // block_max (block_max_slot), when that is not null either.  mut (needs plan.makes): the kernels make the children of

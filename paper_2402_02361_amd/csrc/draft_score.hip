@@ -380,26 +380,25 @@ template <bool DUMP, bool SMALL> __device__ __forceinline__ void NestGeneric::sy
 
 // VEC consecutive uint16 tile factors of one slot, as loaded: kept packed while a later chunk's loads are in flight.
 // Every tile byte is read exactly once, so the loads carry the streaming (non-temporal) hint and leave the caches
-// to the scores, which the selection stage reads back right away.
+// to the scores, which the selection stage reads back right away.  The vector memory unit takes 8- and 16-byte accesses at any
+// address that is a multiple of the element (a wavefront then touches one cache line more), so segments that start at any
+// candidate, and populations of any pitch, are read and written at the full width: ten ragged segments of all classes,
+// 3.3 M candidates,
+// score with the digits of the selection counted along the way in the time (43 us) that single-element loads took without,
+// and the selection's own pass over the scores (16 us) is gone.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
 template <int VEC> struct Packed;
 template <> struct Packed<1> {
     typedef uint32_t type;
     __device__ static type load(const uint16_t* p) { return __builtin_nontemporal_load(p); }
     __device__ static void unpack(type w, uint32_t* out) { out[0] = w; }
 };
-template <> struct Packed<2> {
-    typedef uint32_t type;
-    __device__ static type load(const uint16_t* p) { return __builtin_nontemporal_load(reinterpret_cast<const uint32_t*>(p)); }
-    __device__ static void unpack(type w, uint32_t* out)
-    {
-        out[0] = w & 0xFFFFu;
-        out[1] = w >> 16;
-    }
-};
 template <> struct Packed<4> {
     typedef u32x2 type;
-    __device__ static type load(const uint16_t* p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(p)); }
+    __device__ static type load(const uint16_t* p) { return __builtin_nontemporal_load(reinterpret_cast<const u32x2_a2*>(p)); }
     __device__ static void unpack(type w, uint32_t* out)
     {
         out[0] = w.x & 0xFFFFu;
@@ -486,7 +485,7 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
             if (row < ms.seg.n_slots) {
                 uint16_t* dst = tiles + (int64_t)row * pitch + c0;
                 if (live == 4) {
-                    *reinterpret_cast<u32x2*>(dst) = T[row];
+                    *reinterpret_cast<u32x2_a2*>(dst) = T[row];
                 } else {
 #pragma unroll
                     for (int e = 0; e < 3; ++e)
@@ -774,8 +773,10 @@ __device__ __forceinline__ void analyze_fused(const SgDesc& d, const Symbols (&y
     for (int v = 0; v < VEC; ++v) score[v] = -__builtin_fmaf(sum[v], w[v], L[v]);
 }
 
+// raw holds candidates c0 .. c0 + VEC - 1; those in [c_lo, c_end) are scored (c_lo is c0 but for the thread that would read past
+// the end of a row: it reads the row's last VEC and leaves the first of them to its neighbour).
 template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST>
-__device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles<Nest, VEC>& raw, int64_t c0, int64_t c_end,
+__device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles<Nest, VEC>& raw, int64_t c0, int64_t c_lo, int64_t c_end,
                                                  int32_t flags, const float* p2m_tab, float* __restrict__ score,
                                                  int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist, bool count_digits,
                                                  uint32_t* __restrict__ block_max, int seg_index)
@@ -895,7 +896,7 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             const int64_t c = c0 + v;
-            if (c < c_end) {
+            if (c >= c_lo && c < c_end) {
                 symbols[PRUNER_SYM_S1 * n_total + c] = S1[v];
                 symbols[PRUNER_SYM_S2 * n_total + c] = (int64_t)y[v].S2;
                 symbols[PRUNER_SYM_S3 * n_total + c] = y[v].S3;
@@ -918,9 +919,9 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
         uint32_t top = 0;   // below the key of every number
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
-            if (c0 + v < c_end) {
+            if (c0 + v >= c_lo && c0 + v < c_end) {
                 const uint32_t key = key_of(out[v]);
-                atomicAdd(&digit_hist[key >> 21], 1u);
+                atomicAdd(&digit_hist[first_digit_of(key, kDraftWindow)], 1u);
                 top = key > top ? key : top;
             }
         }
@@ -931,23 +932,17 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
             if (block_max) {
                 top = wave_inclusive_max(top);
                 const int last = 63 - __clzll(__ballot(true));
-                if (lane_id() == last) block_max[block_max_slot(c0 - 4 * last, seg_index)] = top;
+                if (lane_id() == last) block_max[block_max_slot(c_lo - 4 * last, seg_index)] = top;
             }
         }
     }
 
-    if (c0 + VEC <= c_end) {
-        if constexpr (VEC == 4) {
-            *reinterpret_cast<float4*>(score + c0) = make_float4(out[0], out[1], out[2], out[3]);
-        } else if constexpr (VEC == 2) {
-            *reinterpret_cast<float2*>(score + c0) = make_float2(out[0], out[1]);
-        } else {
-            score[c0] = out[0];
-        }
+    if (VEC == 4 && c0 >= c_lo && c0 + VEC <= c_end) {
+        *reinterpret_cast<f32x4_a4*>(score + c0) = f32x4{out[0], out[1 % VEC], out[2 % VEC], out[3 % VEC]};
     } else {
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
-            if (c0 + v < c_end) score[c0 + v] = out[v];
+            if (c0 + v >= c_lo && c0 + v < c_end) score[c0 + v] = out[v];
     }
 }
 
@@ -962,6 +957,8 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
 {
     const int64_t step = (int64_t)seg.blocks * kBlock * VEC;
     RawTiles<Nest, VEC> cur{}, nxt{};
+    // where a thread's loads start: its first candidate, or the last place from which VEC candidates still lie inside a row
+    auto inside = [&](int64_t c) { return c + VEC <= pitch ? c : pitch - VEC; };
     int64_t c0 = seg.begin + ((int64_t)(b - seg.first_block) * kBlock + threadIdx.x) * VEC;
     if constexpr (MUT) {
         static_assert(VEC == 4, "children are made four at a time");
@@ -975,7 +972,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
             for (int it = 0; it < seg.iters; ++it) {
                 if (c0 < seg.end) {
                     make_children<Nest>(d, ms, mut, out, pitch, c0, seg.end, cur);
-                    score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
+                    score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
                 }
                 c0 += step;
             }
@@ -987,18 +984,18 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
         // (and in the kernels that make their candidates this path only serves a subgraph without S_spec)
         for (int it = 0; it < seg.iters; ++it) {
             if (c0 < seg.end) {
-                load_tiles<Nest, VEC>(d, tiles, pitch, c0, cur);
-                score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
+                load_tiles<Nest, VEC>(d, tiles, pitch, inside(c0), cur);
+                score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, inside(c0), c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
             }
             c0 += step;
         }
         return;
     }
-    if (c0 < seg.end) load_tiles<Nest, VEC>(d, tiles, pitch, c0, cur);
+    if (c0 < seg.end) load_tiles<Nest, VEC>(d, tiles, pitch, inside(c0), cur);
     for (int it = 0; it < seg.iters; ++it) {
         const int64_t c1 = c0 + step;
-        if (it + 1 < seg.iters && c1 < seg.end) load_tiles<Nest, VEC>(d, tiles, pitch, c1, nxt);
-        if (c0 < seg.end) score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
+        if (it + 1 < seg.iters && c1 < seg.end) load_tiles<Nest, VEC>(d, tiles, pitch, inside(c1), nxt);
+        if (c0 < seg.end) score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, inside(c0), c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
         cur = nxt;
         c0 = c1;
     }
@@ -1074,7 +1071,6 @@ using DraftFn = void (*)(const SegEnt*, int32_t, const SgDesc*, const uint16_t*,
 template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, bool mut)
 {
     if constexpr (CLS == kAnyClass) {
-        if (vec == 2) return draft_kernel<CLS, 2, DUMP, EXACT, false, false>;
         if (vec == 1) return draft_kernel<CLS, 1, DUMP, EXACT, false, false>;
     }
     if constexpr (!DUMP) {
@@ -1441,18 +1437,15 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
         return PRUNER_OK;
     }
 
-    // widest vector load that keeps every thread's first candidate aligned
-    int vec = 4;
-    auto fits = [&](int v) {
-        if (tiles_pitch % v || !aligned(tiles, 2 * (size_t)v) || !aligned(score, 4 * (size_t)v)) return false;
-        for (int32_t s = 0; s < n_sg; ++s)
-            if (seg_off[s] % v) return false;
-        return true;
-    };
-    while (vec > 1 && !fits(vec)) vec >>= 1;
+    // four candidates per thread wherever a row holds that many
+    const int vec = tiles_pitch >= 4 ? 4 : 1;
+    bool in_fours = tiles_pitch % 4 == 0 && aligned(tiles, 8) && aligned(score, 16);   // every thread's candidates start at a multiple of four
+    for (int32_t s = 0; s < n_sg; ++s) in_fours = in_fours && seg_off[s] % 4 == 0;
 
     // Launch plan.  At the full load width: one launch per loop-nest class present, the table grouped by class, when the
-    // population is large, when there is only one class (its own kernel needs half the registers of the one that branches
+    // population is large (with more than two classes: 2^20 candidates for each, since every launch begins and ends with a
+    // partly empty device: ten segments of four classes, 3.3 M candidates, take 56 us in four launches and 43 in one), when
+    // there is only one class (its own kernel needs half the registers of the one that branches
     // on the class and a fraction of its code: 4,096 GEMM candidates take 5.7 us in the one and 6.4 in the other,
     // 65,536 convolution candidates 7.7 and 9.6), and, when the kernels make their candidates, up to two classes
     // (a launch of the mutation is then saved); otherwise a single launch of the kernel that branches on the class.  A
@@ -1464,13 +1457,15 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
         classes |= 1u << descs[desc_of[s]].cls;
     }
     const bool large = vec == 4 && n >= kPerClassMin;
-    const bool by_class = vec == 4 && (large || __builtin_popcount(classes) <= (mut ? 2 : 1));
+    const int n_classes = __builtin_popcount(classes);
+    const bool by_class = vec == 4 && ((large && (mut || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (mut ? 2 : 1));
     if (by_class)
         std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return descs[desc_of[a]].cls < descs[desc_of[b]].cls; });
     // Arithmetic of Eq. 1: one rounded operation per step of the definitions below 2^20 candidates (a call is then bound by
-    // launch latency, and the dozen divisions per candidate cost nothing measurable) and at the narrow load widths, the
-    // multiplied-out form for large populations, unless a flag asks for one of them.
-    const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !large);
+    // launch latency, and the dozen divisions per candidate cost nothing measurable) and where the population is not laid
+    // out in fours (the boundary says so; it was the narrow loads' rule), the multiplied-out form for the other large
+    // populations, unless a flag asks for one of them.
+    const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !(large && in_fours));
     const bool hist = count_digits && vec == 4 && symbols == nullptr;
     const bool fused = mut && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
@@ -1515,6 +1510,13 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     out->counts = hist;
     out->makes = fused;
     return PRUNER_OK;
+}
+
+void* place_behind(const DraftPlan& plan, void* workspace, Upload* also)
+{
+    char* at = static_cast<char*>(workspace) + round_up(plan.image.size(), 16);
+    if (also->dst && !plan.image.empty() && at < static_cast<char*>(also->dst)) also->dst = at;
+    return also->dst;
 }
 
 int draft_upload(const DraftPlan& plan, void* workspace, hipStream_t st, const Upload* also)

@@ -5,6 +5,7 @@
 // selection digit of every score while it still holds the score in a register, and the selection skips its first
 // pass over the score array.  The result is the same as that of the two separate calls, bit for bit.
 #include "common.h"
+#include "select_common.h"
 
 namespace pruner {
 
@@ -37,12 +38,16 @@ extern "C" int pruner_prior_filter(const pruner_subgraph* sg, int32_t n_sg, cons
     // histograms the draft kernel adds to.
     TopkCtx ctx;
     Upload pending;
-    int rc = topk_prepare(seg_off, n_sg, k, ws + draft_bytes, workspace_bytes - draft_bytes, st, &ctx, &pending);
+    int rc = topk_prepare(seg_off, n_sg, k, ws + draft_bytes, workspace_bytes - draft_bytes, st, &ctx, &pending, true, kDraftWindow);
     if (rc) return rc;
-    bool counted = false;
-    rc = draft_launch(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, st,
-                      ctx.large ? ctx.d_hist : nullptr, ctx.large ? ctx.d_block_max : nullptr, ctx.copies, &counted, &pending);
+    DraftPlan plan;
+    rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, ctx.large, false, &plan);
+    if (rc) return rc;
+    if (pending.dst) ctx.d_segs = place_behind(plan, ws, &pending);
+    rc = draft_upload(plan, ws, st, &pending);
+    if (rc) return rc;
+    rc = draft_run(plan, ws, tiles, score, nullptr, st, ctx.large ? ctx.d_hist : nullptr, ctx.large ? ctx.d_block_max : nullptr, ctx.copies, nullptr);
     if (rc) return rc;
     if (scored_event && hipEventRecord(static_cast<hipEvent_t>(scored_event), st) != hipSuccess) return PRUNER_EHIP;
-    return topk_finish(ctx, score, seg_off, idx_out, val_out, ctx.large && counted, st);
+    return topk_finish(ctx, score, seg_off, idx_out, val_out, ctx.large && plan.counts, st);
 }

@@ -16,6 +16,36 @@ __device__ __forceinline__ uint32_t key_of(float x)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
+// The first digit of the selection: a bin of 2048 that grows with the key.  Scores that are worth choosing among lie within a
+// few octaves, so the bins are narrow there: 32 to an octave (three per cent of a score) in a window of seventeen octaves on
+// either side of zero, two to an octave outside it.  (With the key's upper eleven bits, four bins to an octave, the bin of
+// rank k held thousands of entries; now it holds tens to hundreds, and most populations are settled by this digit alone.)
+// `window`: 32 x the biased exponent at which the window begins, a multiple of 16.  Two more digits of up to eleven bits
+// settle any bin (a bin spans 2^18 keys, or 2^22 outside the window).
+constexpr uint32_t kFine = 17 * 32;
+constexpr uint32_t kDraftWindow = (127 - 23) * 32;   // latencies: 2^-23 .. 2^-6 seconds
+constexpr uint32_t kScoreWindow = (127 - 10) * 32;   // scores in general: 2^-10 .. 2^7
+__device__ __forceinline__ uint32_t first_digit_of(uint32_t key, uint32_t window)
+{
+    const uint32_t below_zero = ~(uint32_t)((int32_t)key >> 31);   // all ones for a negative score
+    const uint32_t x = ((key ^ below_zero) & 0x7FFFFFFFu) >> 18;   // the magnitude in units of 1/32 octave
+    const uint32_t low = x < window ? x : window, rest = x - low, fine = rest < kFine ? rest : kFine;
+    const uint32_t b = (low >> 4) + fine + ((rest - fine) >> 4);   // 0 .. 1021
+    return (b + 1024u) ^ (below_zero & 0x7FFu);                    // 1024 + b, or 1023 - b
+}
+// The keys of a bin: lowest .. lowest + width.
+__device__ __forceinline__ void first_digit_range(uint32_t bin, uint32_t window, uint32_t& lowest, uint32_t& width)
+{
+    const bool negative = bin < 1024u;
+    const uint32_t b = negative ? 1023u - bin : bin - 1024u;
+    auto begin = [&](uint32_t v) { return v < (window >> 4) ? v << 4 : v < (window >> 4) + kFine ? window + (v - (window >> 4)) : window + kFine + ((v - (window >> 4) - kFine) << 4); };
+    const uint32_t from = begin(b) << 18, to = begin(b + 1) << 18;
+    lowest = negative ? 0x80000000u - to : 0x80000000u + from;
+    width = to - from - 1u;
+}
+// The digits after it: the offset from the range's lowest key, its upper eleven bits first.  The shift of that first one.
+__device__ __forceinline__ int next_shift(uint32_t width) { const int bits = width ? 32 - __clz(width) : 0; return bits > 11 ? bits - 11 : 0; }
+
 // The score with a given key (every key but the one that -0.0 and +0.0 share belongs to exactly one bit pattern).
 constexpr uint32_t kZeroKey = 0x80000000u;
 __device__ __forceinline__ float score_of_key(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key); }

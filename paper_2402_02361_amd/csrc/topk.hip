@@ -1,19 +1,21 @@
 // Selection of the k best entries per segment (PriorFilter of Alg. 2; the choice of S_measured in Alg. 1).
 //
-// Exact radix selection on an order-preserving 32-bit image of the scores: three digit passes (11, 11, 10 bits,
-// most significant first) find the key T of rank k; entries above T are all taken, entries equal to T are taken
-// in index order until k is reached; the k survivors are then sorted by (key descending, index ascending) with a
-// bitonic network in LDS.  Nothing depends on the order in which blocks or wavefronts run.
+// Exact selection on an order-preserving 32-bit image of the scores (key): a first digit of 2048 bins, narrow where scores
+// crowd (first_digit_of), and where it does not settle the matter two more digits inside its bin; ties are taken in index
+// order; the k survivors are ranked by (key descending, index ascending).  Nothing depends on the order in which blocks or
+// wavefronts run.
 //
-// Two routes, same result:
-//   small  - every segment fits one workgroup's patience (<= kSmallMax entries): one launch, one workgroup of
-//            1024 threads per segment does all passes (the final selection after the verify stage; beyond 32768
-//            entries the passes of a single workgroup take longer than the large route's six launches);
-//   large  - segments are cut into spans of whole 16384-entry sweeps, one workgroup of 1024 threads each; the
-//            scores are read twice at most (first-digit histogram, which also notes the largest key of every 256
-//            entries; then everything at or above that digit's rank-k bucket is set aside, a few thousand entries as
-//            a rule, and blocks of 256 whose largest key lies below the bucket are not read again) and the later
-//            passes work on what was set aside; six launches.
+// Three routes, same result:
+//   tiny   - segments of at most 8192 entries and k up to 64 (the final selection after the verify stage, small draft
+//            populations): one launch, no digits (tiny_select in select_common.h);
+//   pick   - segments of at most kPickMax entries: one launch behind whoever counted the first digit (the draft kernel as a
+//            rule, else one pass).  Several workgroups per segment, each of which goes through the whole segment, keeps the
+//            few entries at or above rank k's bin, and ranks its share of them;
+//   spans  - longer segments are cut into spans of whole 16384-entry sweeps, one workgroup of 1024 threads each; the scores
+//            are read twice at most (first-digit histogram, which also notes the largest key of every 256 entries; then
+//            everything at or above that digit's rank-k bin is set aside, a few thousand entries as a rule, and blocks of
+//            256 whose largest key lies below the bin are not read again) and the later passes work on what was set aside;
+//            six launches.
 #include "select_common.h"
 
 #include <string.h>
@@ -24,9 +26,6 @@ namespace pruner {
 namespace {
 
 constexpr int kSmallThreads = 1024;
-constexpr int64_t kSmallMax = 32768;
-constexpr int kTieCap = 1024;        // ties the small route ranks instead of scanning for
-constexpr int kSmallPer = 8;         // loads a thread of the small route keeps in flight
 
 struct alignas(8) SegT {
     int64_t begin, end;
@@ -34,22 +33,11 @@ struct alignas(8) SegT {
 };
 
 struct alignas(16) SelState {
-    uint32_t prefix;   // digits fixed so far (after the last pass: the key T of rank k)
-    uint32_t k_rem;    // entries still to take among those matching the prefix (after the last pass: ties to take)
-    uint32_t n_gt;     // entries above T
-    uint32_t gt_fill;  // fill counter of the unordered "above T" part of the selection
+    uint32_t lowest;   // lowest key of the range that holds rank k (after the last pass: the key T of rank k)
+    uint32_t k_rem;    // entries still to take of that range (after the last pass: ties to take)
+    uint32_t n_gt;     // entries above T (after the last pass)
+    uint32_t shift;    // the range's keys are split by (key - lowest) >> shift next, then by what is left
 };
-
-// ---- keys ------------------------------------------------------------------------------------------------------
-
-template <int PASS> __device__ __forceinline__ uint32_t digit_of(uint32_t key)
-{
-    return PASS == 0 ? key >> 21 : PASS == 1 ? (key >> 10) & 0x7FFu : key & 0x3FFu;
-}
-template <int PASS> __device__ __forceinline__ bool matches(uint32_t key, uint32_t prefix)
-{
-    return PASS == 0 ? true : PASS == 1 ? (key >> 21) == prefix : (key >> 10) == prefix;
-}
 
 // ---- the selection in LDS ---------------------------------------------------------------------------------------
 
@@ -141,7 +129,7 @@ __device__ __forceinline__ void finish_segment(uint64_t* sel, int k, const float
     }
 }
 
-// Output rows for n of the k selected words (their positions: which[i], or first + i * stride without a list) without
+// Output rows (those of the first row_len) for n of the k collected words (their positions: which[i], or first + i * stride without a list) without
 // sorting: the words are distinct
 // (they carry the index), so the rank of a word is the number of larger words among all k.  A wavefront holds
 // R = 64, 32 or 16 of the n words at a time (the fewest lanes that still hold them all: idle lanes would cost the same
@@ -179,7 +167,7 @@ __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint
             uint32_t r = 0;
             for (int q = lane; q < NT; q += R) r += cnt[q];   // the counts of this word from every piece
             const uint32_t gi = index_of(mine);
-            if (r < (uint32_t)k) {
+            if (r < (uint32_t)row_len) {
                 idx_out[row * row_len + r] = (int32_t)gi;
                 if (val_out) val_out[row * row_len + r] = gi >= seg_begin && gi < seg_end ? score[gi] : 0.f;   // never read outside the segment
             }
@@ -188,132 +176,11 @@ __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint
     }
 }
 
-// ---- small route: one workgroup per segment -------------------------------------------------------------------
-
-template <int PASS, bool RES>
-__device__ __forceinline__ void small_pass(const float* __restrict__ seg_score, int64_t len, const uint32_t (&held)[kSmallPer],
-                                           uint32_t* hist, uint32_t* wave_tot, uint32_t* found, uint32_t& prefix, uint32_t& k_rem)
-{
-    for (int i = threadIdx.x; i < kBins; i += kSmallThreads) hist[i] = 0;
-    __syncthreads();
-    if constexpr (RES) {
-        // the whole segment sits in registers (one batch): no memory traffic in this pass
-#pragma unroll
-        for (int j = 0; j < kSmallPer; ++j) {
-            const int64_t i = j * kSmallThreads + threadIdx.x;
-            wave_hist_add(hist, digit_of<PASS>(held[j]), i < len && matches<PASS>(held[j], prefix));
-        }
-    } else {
-        for (int64_t base = 0; base < len; base += kSmallThreads * kSmallPer) {
-            float val[kSmallPer];   // a batch of loads in flight together
-#pragma unroll
-            for (int j = 0; j < kSmallPer; ++j) {
-                const int64_t i = base + j * kSmallThreads + threadIdx.x;
-                val[j] = i < len ? seg_score[i] : 0.f;
-            }
-#pragma unroll
-            for (int j = 0; j < kSmallPer; ++j) {
-                const int64_t i = base + j * kSmallThreads + threadIdx.x;
-                const uint32_t key = key_of(val[j]);
-                wave_hist_add(hist, digit_of<PASS>(key), i < len && matches<PASS>(key, prefix));
-            }
-        }
-    }
-    __syncthreads();
-    find_bucket(hist, k_rem, wave_tot, found);
-    prefix = PASS == 2 ? (prefix << 10) | found[0] : (prefix << 11) | found[0];
-    k_rem = found[1];
-    __syncthreads();
-}
-
 // Up to kInlineSegs segment ranges travel as kernel arguments (no table upload, one launch for the whole call).
 constexpr int kInlineSegs = 128;
 struct InlineSegs {
     SegT s[kInlineSegs];
 };
-
-// RES: no segment is longer than one batch (8192 entries): its keys are loaded once and stay in registers.
-template <bool INLINE, bool RES>
-__global__ void __launch_bounds__(kSmallThreads) topk_small_kernel(const float* __restrict__ score, const SegT* __restrict__ segs,
-                                                                   InlineSegs inl, int k, int32_t* __restrict__ idx_out,
-                                                                   float* __restrict__ val_out)
-{
-    __shared__ uint32_t hist[kBins];
-    __shared__ uint32_t wave_tot[16];
-    __shared__ uint32_t found[3];
-    __shared__ uint32_t gt_fill, tie_fill;
-    __shared__ uint32_t tie_buf[kTieCap];
-    __shared__ uint64_t sel[kSelWords];
-
-    const SegT seg = INLINE ? inl.s[blockIdx.x] : segs[blockIdx.x];
-    const float* seg_score = score + seg.begin;
-    const int64_t len = seg.end - seg.begin;
-
-    uint32_t held[kSmallPer];
-#pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) {
-        const int64_t i = j * kSmallThreads + threadIdx.x;
-        held[j] = RES && i < len ? key_of(seg_score[i]) : 0u;   // 0 is below every key of a number
-    }
-    uint32_t prefix = 0, k_rem = (uint32_t)k;
-    small_pass<0, RES>(seg_score, len, held, hist, wave_tot, found, prefix, k_rem);
-    small_pass<1, RES>(seg_score, len, held, hist, wave_tot, found, prefix, k_rem);
-    small_pass<2, RES>(seg_score, len, held, hist, wave_tot, found, prefix, k_rem);
-    const uint32_t T = prefix, k_eq = k_rem, n_gt = (uint32_t)k - k_eq;
-
-    const uint32_t n_tie = found[2];   // entries equal to T in the whole segment
-    if (threadIdx.x == 0) gt_fill = tie_fill = 0;
-    __syncthreads();
-    if (n_tie <= (uint32_t)kTieCap) {
-        // few ties: gather their indices in any order, then keep the k_eq smallest by rank
-        for (int64_t base = 0; base < len; base += kSmallThreads * kSmallPer) {
-            uint32_t key[kSmallPer];
-#pragma unroll
-            for (int j = 0; j < kSmallPer; ++j) {
-                const int64_t i = base + j * kSmallThreads + threadIdx.x;
-                key[j] = RES ? held[j] : i < len ? key_of(seg_score[i]) : 0u;   // 0 is below every key of a number
-            }
-#pragma unroll
-            for (int j = 0; j < kSmallPer; ++j) {
-                const int64_t i = base + j * kSmallThreads + threadIdx.x;
-                if (key[j] > T) sel[slot(atomicAdd(&gt_fill, 1u))] = compose(key[j], (uint32_t)(seg.begin + i));
-                else if (key[j] == T) tie_buf[atomicAdd(&tie_fill, 1u)] = (uint32_t)(seg.begin + i);
-            }
-        }
-        __syncthreads();
-        for (uint32_t i = threadIdx.x; i < n_tie; i += kSmallThreads) {
-            const uint32_t me = tie_buf[i];
-            uint32_t rank = 0;
-            for (uint32_t j = 0; j < n_tie; ++j) rank += tie_buf[j] < me ? 1u : 0u;
-            if (rank < k_eq) sel[slot(n_gt + rank)] = compose(T, me);
-        }
-    } else {
-        // many ties: walk the segment in index order and number the ties with a workgroup scan until enough are taken
-        uint32_t eq_before = 0;  // ties seen in earlier rounds (same value in every thread)
-        for (int64_t base = 0; base < len; base += kSmallThreads * kSmallPer) {
-            uint32_t key[kSmallPer];
-#pragma unroll
-            for (int j = 0; j < kSmallPer; ++j) {
-                const int64_t i = base + j * kSmallThreads + threadIdx.x;
-                key[j] = RES ? held[j] : i < len ? key_of(seg_score[i]) : 0u;
-            }
-#pragma unroll
-            for (int j = 0; j < kSmallPer; ++j) {
-                const int64_t i = base + j * kSmallThreads + threadIdx.x;
-                if (key[j] > T) sel[slot(atomicAdd(&gt_fill, 1u))] = compose(key[j], (uint32_t)(seg.begin + i));
-                if (eq_before < k_eq) {
-                    const bool tie = key[j] == T;
-                    uint32_t total;
-                    const uint32_t rank = eq_before + block_excl_scan<kSmallThreads>(tie ? 1u : 0u, wave_tot, &total);
-                    if (tie && rank < k_eq) sel[slot(n_gt + rank)] = compose(key[j], (uint32_t)(seg.begin + i));
-                    eq_before += total;
-                }
-            }
-        }
-    }
-    __syncthreads();
-    finish_segment<kSmallThreads>(sel, k, score, idx_out, val_out, blockIdx.x, seg.begin, seg.end, k);
-}
 
 // ---- tiny route: segments of at most 8192 entries, k at most 64 ---------------------------------------------------
 // (tiny_select in select_common.h: the final selection after the verify stage and small draft populations)
@@ -359,32 +226,23 @@ struct Stage {
     uint64_t cand[kCandCap];                   // composed words of entries in the first digit's rank-k bucket, any order
 };
 
-// One sweep of a workgroup over kRow consecutive entries starting at `row`: thread t receives kBigPer of them.
-// WIDE (segments start on 16-byte boundaries): four neighbours per 16-byte load; else one entry per load.
+// One sweep of a workgroup over kRow consecutive entries starting at `row`: thread t receives kBigPer of them, four neighbours
+// per 16-byte load (at any address: the memory unit asks for multiples of an element only).
 // sweep_index gives the global index of the thread's j-th entry; entries at or past `hi` read as 0.
-template <bool WIDE> __device__ __forceinline__ int64_t sweep_index(int64_t row, int j)
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+__device__ __forceinline__ int64_t sweep_index(int64_t row, int j) { return row + ((int64_t)(j >> 2) * kBigThreads + threadIdx.x) * 4 + (j & 3); }
+__device__ __forceinline__ void load_sweep(const float* __restrict__ score, int64_t row, int64_t hi, float (&val)[kBigPer])
 {
-    return WIDE ? row + ((int64_t)(j >> 2) * kBigThreads + threadIdx.x) * 4 + (j & 3) : row + (int64_t)j * kBigThreads + threadIdx.x;
-}
-template <bool WIDE> __device__ __forceinline__ void load_sweep(const float* __restrict__ score, int64_t row, int64_t hi, float (&val)[kBigPer])
-{
-    if (WIDE) {
 #pragma unroll
-        for (int q = 0; q < kBigPer / 4; ++q) {
-            const int64_t i = sweep_index<true>(row, 4 * q);
-            if (i + 3 < hi) {
-                const float4 v = *reinterpret_cast<const float4*>(score + i);
-                val[4 * q] = v.x, val[4 * q + 1] = v.y, val[4 * q + 2] = v.z, val[4 * q + 3] = v.w;
-            } else {
+    for (int q = 0; q < kBigPer / 4; ++q) {
+        const int64_t i = sweep_index(row, 4 * q);
+        if (i + 3 < hi) {
+            const f32x4 v = *reinterpret_cast<const f32x4_a4*>(score + i);
+            val[4 * q] = v.x, val[4 * q + 1] = v.y, val[4 * q + 2] = v.z, val[4 * q + 3] = v.w;
+        } else {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) val[4 * q + e] = i + e < hi ? score[i + e] : 0.f;
-            }
-        }
-    } else {
-#pragma unroll
-        for (int j = 0; j < kBigPer; ++j) {
-            const int64_t i = sweep_index<false>(row, j);
-            val[j] = i < hi ? score[i] : 0.f;
+            for (int e = 0; e < 4; ++e) val[4 * q + e] = i + e < hi ? score[i + e] : 0.f;
         }
     }
 }
@@ -413,10 +271,9 @@ __device__ __forceinline__ void bucket_of_pass(const uint32_t* __restrict__ ghis
     find_bucket(hist, k_rem, wave_tot, found);
 }
 
-template <bool WIDE>
 __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
-                                                            int64_t span, int R, uint32_t* __restrict__ ghist /* [R][n_seg][kBins] */,
-                                                            uint32_t* __restrict__ block_max /* WIDE only; or null */)
+                                                            int64_t span, int R, uint32_t window, uint32_t* __restrict__ ghist /* [R][n_seg][kBins] */,
+                                                            uint32_t* __restrict__ block_max /* or null */)
 {
     __shared__ uint32_t hist[kBins];
     const int s = segment_of_block(segs, n_seg, blockIdx.x);
@@ -427,24 +284,22 @@ __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restr
     const int64_t hi = lo + span < seg.end ? lo + span : seg.end;
     for (int64_t row = lo; row < hi; row += kRow) {
         float val[kBigPer];
-        load_sweep<WIDE>(score, row, hi, val);
+        load_sweep(score, row, hi, val);
         uint32_t top[kBigPer / 4] = {};
 #pragma unroll
         for (int j = 0; j < kBigPer; ++j) {
-            const int64_t i = sweep_index<WIDE>(row, j);
+            const int64_t i = sweep_index(row, j);
             const uint32_t key = key_of(val[j]);
-            wave_hist_add(hist, digit_of<0>(key), i < hi);
+            light_hist_add(hist, first_digit_of(key, window), i < hi);
             if (i < hi && key > top[j >> 2]) top[j >> 2] = key;
         }
-        if constexpr (WIDE) {
-            // a wavefront's q-th load is one block of 256 neighbouring entries (spans are whole sweeps from the segment's begin)
-            if (block_max) {
+        // a wavefront's q-th load is one block of 256 neighbouring entries (spans are whole sweeps from the segment's begin)
+        if (block_max) {
 #pragma unroll
-                for (int q = 0; q < kBigPer / 4; ++q) {
-                    const uint32_t m = wave_inclusive_max(top[q]);
-                    const int64_t first = sweep_index<true>(row, 4 * q) - 4 * lane_id();
-                    if (lane_id() == 63 && first < hi) block_max[block_max_slot(first, s)] = m;
-                }
+            for (int q = 0; q < kBigPer / 4; ++q) {
+                const uint32_t m = wave_inclusive_max(top[q]);
+                const int64_t first = sweep_index(row, 4 * q) - 4 * lane_id();
+                if (lane_id() == 63 && first < hi) block_max[block_max_slot(first, s)] = m;
             }
         }
     }
@@ -452,17 +307,16 @@ __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restr
     flush_hist<kBigThreads>(hist, ghist, R, n_seg, s);
 }
 
-// BLK (with WIDE): block_max holds the largest key of every block of 256 neighbouring entries; a block whose maximum
+// BLK: block_max holds the largest key of every block of 256 neighbouring entries; a block whose maximum
 // lies below the bucket is not read.  Wavefront w takes blocks w, w + 16, ... of the span, 64 of them per look at the
 // maxima (one per lane), and reads those that are left four at a time.
 // (held to 64 registers: a compute unit then holds two of these workgroups, and a launch of up to 512 runs in one round)
-template <bool WIDE, bool BLK>
+template <bool BLK>
 __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(8))) funnel_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
-                                                             int64_t span, int R, int k, const uint32_t* __restrict__ ghist0,
+                                                             int64_t span, int R, uint32_t window, int k, const uint32_t* __restrict__ ghist0,
                                                              uint32_t* __restrict__ ghist1, SelState* __restrict__ state,
                                                              Stage* __restrict__ stage, const uint32_t* __restrict__ block_max)
 {
-    static_assert(WIDE || !BLK, "blocks are what the wide loads cover");
     __shared__ uint32_t hist[kBins];
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t found[3];
@@ -481,17 +335,20 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
         const int64_t b = wave + 16 * lane_id();
         if (b < n_blk) top = block_max[block_max_slot(lo + (b << 8), s)];
     } else {
-        load_sweep<WIDE>(score, lo, hi, val);
+        load_sweep(score, lo, hi, val);
     }
     bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
-    const uint32_t b0 = found[0], k_rem = found[1];
+    const uint32_t k_rem = found[1];
+    uint32_t lowest, width;
+    first_digit_range(found[0], window, lowest, width);
+    const int shift = next_shift(width);
     if constexpr (BLK) {
         // how many of the span's (first 1024) blocks will have to be read
-        const unsigned long long first_left = __ballot(top >= (b0 << 21) && wave + 16 * lane_id() < n_blk);
+        const unsigned long long first_left = __ballot(top >= lowest && wave + 16 * lane_id() < n_blk);
         if (lane_id() == 0) atomicAdd(&live_blocks, (uint32_t)__popcll(first_left));
     }
     __syncthreads();
-    if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[s] = SelState{b0, k_rem, (uint32_t)k - k_rem, 0u};
+    if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[s] = SelState{lowest, k_rem, (uint32_t)k - k_rem, (uint32_t)shift};
     for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
     if (threadIdx.x == 0) n_gt = n_cand = 0;
     __syncthreads();
@@ -499,23 +356,22 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     // the others gains nothing and the plain sweeps, whole rows of loads in flight, are the faster way through the span.
     const bool dense = BLK && 2 * (int64_t)live_blocks > (n_blk < 16 * kWave ? n_blk : 16 * kWave);
     Stage& mine = stage[blockIdx.x];
-    // The smallest score whose first digit is b0.  Nearly every entry lies below it, and one comparison tells: a
-    // wavefront steps over an entry unless one of its lanes is not below (a NaN never is; the exact test follows).
-    const uint32_t low_key = b0 << 21;
-    const float t0 = __uint_as_float((low_key & 0x80000000u) ? (low_key & 0x7FFFFFFFu) : ~low_key);
+    // The smallest score of the bin.  Nearly every entry lies below it, and one comparison tells: a wavefront steps over an
+    // entry unless one of its lanes is not below (a NaN never is; the exact test follows).
+    const uint32_t low_key = lowest;
+    const float t0 = score_of_key(low_key);
     // What happens to one entry (every lane of the wavefront calls it, `mine_to_look_at` says whether the lane holds one).
     auto look_at = [&](float x, int64_t i, bool mine_to_look_at, bool list_open) {
         const uint32_t key = mine_to_look_at && i < hi ? key_of(x) : 0u;   // 0 is below every key of a number
-        const uint32_t d0 = digit_of<0>(key);
-        const bool inside = mine_to_look_at && i < hi && d0 == b0;
-        if (mine_to_look_at && i < hi && d0 > b0) {
+        const bool inside = key != 0u && key - lowest <= width;
+        if (key > lowest && !inside) {
             const uint32_t at = atomicAdd(&n_gt, 1u);
             if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
         } else if (inside && list_open) {
             const uint32_t at = atomicAdd(&n_cand, 1u);
             if (at < kCandCap) mine.cand[at] = compose(key, (uint32_t)i);
         }
-        wave_hist_add(hist, digit_of<1>(key), inside);
+        light_hist_add(hist, (key - lowest) >> shift, inside);
     };
     if constexpr (BLK) {
         for (int64_t g = 0; !dense && g < n_blk; g += 16 * kWave) {
@@ -540,7 +396,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
                 for (int u = 0; u < 4; ++u) {
                     const int64_t i = at[u];
                     if (i >= 0 && i + 3 < hi) {
-                        const float4 v = *reinterpret_cast<const float4*>(score + i);
+                        const f32x4 v = *reinterpret_cast<const f32x4_a4*>(score + i);
                         val[4 * u] = v.x, val[4 * u + 1] = v.y, val[4 * u + 2] = v.z, val[4 * u + 3] = v.w;
                     } else {
 #pragma unroll
@@ -578,7 +434,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
         }
     }
     for (int64_t row = lo; (!BLK || dense) && row < hi; row += kRow) {
-        if (BLK || row > lo) load_sweep<WIDE>(score, row, hi, val);
+        if (BLK || row > lo) load_sweep(score, row, hi, val);
         // once the candidate list has overflowed, the later passes read the span again: nothing more is staged in it
         // (the count only has to stay above the list's capacity)
         const bool list_open = n_cand <= (uint32_t)kCandCap;
@@ -586,7 +442,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
         for (int j = 0; j < kBigPer; ++j) {
             // a wavefront steps over an entry unless one of its lanes is not below the bucket's smallest score
             if (__ballot(!(val[j] < t0)) == 0ull) continue;
-            look_at(val[j], sweep_index<WIDE>(row, j), true, list_open);
+            look_at(val[j], sweep_index(row, j), true, list_open);
         }
     }
     __syncthreads();
@@ -598,7 +454,6 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     flush_hist<kBigThreads>(hist, ghist1, 1, n_seg, s);   // few contributors as a rule: one copy
 }
 
-template <bool WIDE>
 __global__ void __launch_bounds__(kBigThreads) refine_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
                                                              int64_t span, const uint32_t* __restrict__ ghist1,
                                                              uint32_t* __restrict__ ghist2, SelState* __restrict__ state,
@@ -611,7 +466,7 @@ __global__ void __launch_bounds__(kBigThreads) refine_kernel(const float* __rest
     const SegT seg = segs[s];
     const SelState before = state[s];
     bucket_of_pass<1>(ghist1, 1, n_seg, s, before.k_rem, hist, wave_tot, found);
-    const uint32_t prefix = (before.prefix << 11) | found[0], k_rem = found[1];
+    const uint32_t lowest = before.lowest + (found[0] << before.shift), width = (1u << before.shift) - 1u, k_rem = found[1];
     __syncthreads();
     for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
     __syncthreads();
@@ -621,29 +476,28 @@ __global__ void __launch_bounds__(kBigThreads) refine_kernel(const float* __rest
         for (uint32_t base = 0; base < n_cand; base += kBigThreads) {
             const uint32_t i = base + threadIdx.x;
             const uint32_t key = i < n_cand ? (uint32_t)(mine.cand[i] >> 32) : 0u;
-            wave_hist_add(hist, digit_of<2>(key), i < n_cand && matches<2>(key, prefix));
+            light_hist_add(hist, key - lowest, i < n_cand && key - lowest <= width);
         }
     } else {
         const int64_t lo = seg.begin + (int64_t)(blockIdx.x - seg.first_block) * span;
         const int64_t hi = lo + span < seg.end ? lo + span : seg.end;
         for (int64_t row = lo; row < hi; row += kRow) {
             float val[kBigPer];
-            load_sweep<WIDE>(score, row, hi, val);
+            load_sweep(score, row, hi, val);
 #pragma unroll
             for (int j = 0; j < kBigPer; ++j) {
-                const int64_t i = sweep_index<WIDE>(row, j);
+                const int64_t i = sweep_index(row, j);
                 const uint32_t key = key_of(val[j]);
-                wave_hist_add(hist, digit_of<2>(key), i < hi && matches<2>(key, prefix));
+                light_hist_add(hist, key - lowest, i < hi && key - lowest <= width);
             }
         }
     }
     __syncthreads();
     flush_hist<kBigThreads>(hist, ghist2, 1, n_seg, s);
     // every workgroup of the segment has read the old state before this launch ends; the new one is for the next launch
-    if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[n_seg + s] = SelState{prefix, k_rem, before.n_gt, 0u};
+    if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[n_seg + s] = SelState{lowest, k_rem, before.n_gt, before.shift};
 }
 
-template <bool WIDE>
 __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
                                                              int64_t span, int k, const uint32_t* __restrict__ ghist2,
                                                              SelState* __restrict__ state, Stage* __restrict__ stage)
@@ -656,7 +510,7 @@ __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __rest
     const SegT seg = segs[s];
     const SelState before = state[n_seg + s];
     bucket_of_pass<1>(ghist2, 1, n_seg, s, before.k_rem, hist, wave_tot, found);
-    const uint32_t T = (before.prefix << 10) | found[0], k_eq = found[1];
+    const uint32_t T = before.lowest + found[0], k_eq = found[1];
     __syncthreads();
     if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[2 * n_seg + s] = SelState{T, k_eq, (uint32_t)k - k_eq, 0u};
     Stage& mine = stage[blockIdx.x];
@@ -686,17 +540,24 @@ __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __rest
         const int64_t hi = lo + span < seg.end ? lo + span : seg.end;
         for (int64_t row = lo; row < hi; row += kRow) {
             float val[kBigPer];
-            load_sweep<WIDE>(score, row, hi, val);
+            load_sweep(score, row, hi, val);
 #pragma unroll
             for (int j = 0; j < kBigPer; ++j) {
-                const int64_t i = sweep_index<WIDE>(row, j);
+                const int64_t i = sweep_index(row, j);
                 const uint32_t key = i < hi ? key_of(val[j]) : 0u;   // 0 is below every key of a number
-                if (key > T) {
-                    const uint32_t at = atomicAdd(&n_gt, 1u);
-                    if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
-                } else if (key == T) {
-                    const uint32_t at = atomicAdd(&n_tie, 1u);
-                    if (at < kStageCap) mine.tie[at] = (uint32_t)i;
+                const unsigned long long above = __ballot(key > T), ties = __ballot(key == T);
+                if (above) {
+                    if (key > T) {
+                        const uint32_t at = atomicAdd(&n_gt, 1u);
+                        if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
+                    }
+                }
+                if (ties) {   // one reservation per wavefront; places past the list's end are only counted
+                    uint32_t base = 0;
+                    const int leader = __ffsll(ties) - 1;
+                    if (lane_id() == leader) base = atomicAdd(&n_tie, (uint32_t)__popcll(ties));
+                    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(ties & ((1ull << lane_id()) - 1ull));
+                    if (key == T && at < kStageCap) mine.tie[at] = (uint32_t)i;
                 }
             }
         }
@@ -768,7 +629,7 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
     const int s = blockIdx.x / share, part = blockIdx.x % share;
     const SegT seg = segs[s];
     const SelState st = state[2 * n_seg + s];   // as left by the settle launch
-    const uint32_t T = st.prefix, k_eq = st.k_rem;
+    const uint32_t T = st.lowest, k_eq = st.k_rem;
     const uint32_t n_gt = st.n_gt < (uint32_t)k ? st.n_gt : (uint32_t)k;   // (a workspace that overlapping calls share must not turn into wild addresses)
     const int b0 = seg.first_block, b1 = s + 1 < n_seg ? segs[s + 1].first_block : total_blocks;
     if (threadIdx.x == 0) {
@@ -977,6 +838,144 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
     }
 }
 
+// ---- pick route ---------------------------------------------------------------------------------------------------------
+// `share` workgroups per segment of at most kPickMax entries.  Each finds rank k's bin from the first digit's histogram, goes
+// through the whole segment (it comes from the cache: 256 KB at most), notes the places of the entries at or above the bin,
+// and ranks those whose index hashes to it among all of them: no lists between launches, no second and third digit as long as
+// the collection fits (its size follows from the histogram).  Where it does not, the bin is split by two more passes over the
+// segment; ties beyond that are written in index order by the segment's first workgroup.
+// Bound: the latency of its stages.  A sweep costs four instructions per entry (one comparison and one add with carry build
+// a thread's mask of sixteen; places, not scores, are noted, so nothing is selected out of registers).  20 segments of 50,000
+// entries, k = 512: 16 us where staging, refining, settling and ranking took 31 in four launches.
+
+constexpr int kPickMax = 65536;
+constexpr int kPickCap = 8192;                                  // words a workgroup collects
+constexpr int kPickWords = kPickCap + kPickCap / 32 + 2;
+static_assert(kPickCap >= 2 * PRUNER_MAX_K, "the entries above rank k's bin fit, and as many of the bin's");
+
+__global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int R,
+                                                           uint32_t window, int k, int share, const uint32_t* __restrict__ ghist0,
+                                                           int32_t* __restrict__ idx_out, float* __restrict__ val_out)
+{
+    __shared__ __align__(16) uint64_t sel[kPickWords];
+    __shared__ uint32_t place[kPickCap];      // indices inside the segment; later: which words this workgroup ranks
+    __shared__ uint32_t hist[kBins];          // later: the ranking's counts
+    __shared__ uint32_t wave_tot[16];
+    __shared__ uint32_t found[3];
+    __shared__ uint32_t fill, n_own;
+    uint16_t* own = reinterpret_cast<uint16_t*>(place);
+    const int s = blockIdx.x / share, part = blockIdx.x % share;
+    const SegT seg = segs[s];
+    const int len = (int)(seg.end - seg.begin);
+    const float* seg_score = score + seg.begin;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+
+    float val[kBigPer];
+    load_sweep(seg_score, 0, len, val);   // the first sweep travels while the bin is looked up
+    bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+    uint32_t lowest, width, k_rem = found[1], in_bin = found[2];
+    first_digit_range(found[0], window, lowest, width);
+    for (int i = threadIdx.x; i < kPickWords; i += kBigThreads) sel[i] = 0;   // spare words must read as "below everything"
+    if (threadIdx.x == 0) fill = n_own = 0;
+    __syncthreads();
+    // more than fits: split the bin (the same decision in every workgroup of the segment)
+    while ((uint32_t)k - k_rem + in_bin > (uint32_t)kPickCap && width != 0u) {
+        const int shift = next_shift(width);
+        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+        __syncthreads();
+        for (int row = 0; row < len; row += kRow) {
+            float again[kBigPer];
+            load_sweep(seg_score, row, len, again);
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) {
+                const uint32_t key = sweep_index(row, j) < len ? key_of(again[j]) : 0u;
+                light_hist_add(hist, (key - lowest) >> shift, key != 0u && key - lowest <= width);
+            }
+        }
+        __syncthreads();
+        find_bucket(hist, k_rem, wave_tot, found);
+        lowest += found[0] << shift;
+        width = (1u << shift) - 1u;
+        k_rem = found[1];
+        in_bin = found[2];
+        __syncthreads();
+    }
+    // entries at or above `lowest` are collected; if the ties alone are too many, those above it
+    const bool ties_apart = (uint32_t)k - k_rem + in_bin > (uint32_t)kPickCap;
+    const int n = (int)(ties_apart ? (uint32_t)k - k_rem : (uint32_t)k - k_rem + in_bin);
+    const uint32_t from_key = ties_apart ? lowest + 1u : lowest;
+    float t0 = score_of_key(from_key);   // (a key beyond the infinities' names a NaN: then every number is at or above it)
+    t0 = t0 != t0 ? -__builtin_inff() : t0;
+    for (int row = 0; row < len; row += kRow) {
+        float next[kBigPer];
+        if (row + kRow < len) load_sweep(seg_score, row + kRow, len, next);
+        uint32_t mask = 0;   // bit 15 - j: entry j is at or above the threshold
+#pragma unroll
+        for (int j = 0; j < kBigPer; ++j) mask = 2 * mask + (val[j] >= t0 ? 1u : 0u);
+        if (row + kRow > len) {   // the segment's last sweep: entries past its end (read as 0) are none
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) mask &= sweep_index(row, j) < len ? ~0u : ~(1u << (kBigPer - 1 - j));
+        }
+        const uint32_t mine = (uint32_t)__popc(mask);
+        const uint32_t upto = wave_inclusive_sum(mine);
+        uint32_t base = 0;
+        if (lane == kWave - 1 && upto) base = atomicAdd(&fill, upto);
+        uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1) + upto - mine;
+        while (mask) {
+            const int j = kBigPer - 1 - (31 - __clz(mask));
+            mask &= ~(1u << (kBigPer - 1 - j));
+            if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, j);
+            ++at;
+        }
+#pragma unroll
+        for (int j = 0; j < kBigPer; ++j) val[j] = next[j];
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < n; e += kBigThreads) {
+        const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
+        sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
+    }
+    __syncthreads();
+    // (every workgroup has its own order of the words: a hash of the index decides who ranks a word)
+    for (int e = threadIdx.x; e < n; e += kBigThreads) {
+        const uint32_t h = (index_of(sel[slot((uint32_t)e)]) * 2654435761u) >> 16;
+        if ((int)(h % (uint32_t)share) == part) own[atomicAdd(&n_own, 1u)] = (uint16_t)e;
+    }
+    __syncthreads();
+    if (n > 0) rank_rows<kBigThreads>(sel, n, own, 0, 1, (int)n_own, hist, score, idx_out, val_out, s, seg.begin, seg.end, k);
+    if (ties_apart && part == 0) {
+        // ties, all of the key `lowest`, in index order: the tie of rank r owns row n + r.  A wavefront takes 16 x 64
+        // neighbouring entries; one exchange of the wavefronts' counts per sweep.
+        uint32_t before = 0;
+        for (int row = 0; row < len && before < k_rem; row += kRow) {
+            const int first = row + wave * (kWave * kBigPer) + lane;
+            uint32_t before_mine[kBigPer], wave_ties = 0;
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) {
+                const int i = first + j * kWave;
+                const bool tie = i < len && key_of(seg_score[i < len ? i : 0]) == lowest;
+                const unsigned long long m = __ballot(tie);
+                before_mine[j] = tie ? wave_ties + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : 0xFFFFFFFFu;
+                wave_ties += (uint32_t)__popcll(m);
+            }
+            __syncthreads();
+            if (lane == 0) wave_tot[wave] = wave_ties;
+            __syncthreads();
+            uint32_t wave_before = before, all = 0;
+#pragma unroll
+            for (int w = 0; w < kBigThreads / kWave; ++w) {
+                wave_before += w < wave ? wave_tot[w] : 0u;
+                all += wave_tot[w];
+            }
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j)
+                if (before_mine[j] != 0xFFFFFFFFu && wave_before + before_mine[j] < k_rem)
+                    put_tie_row(k, (uint32_t)n + wave_before + before_mine[j], (uint32_t)(seg.begin + first + j * kWave), lowest, score, idx_out, val_out, s, seg.begin, seg.end);
+            before += all;
+        }
+    }
+}
+
 struct Layout {
     size_t segs, state, hist, stage, block_max, total;
     size_t stage_slots;
@@ -1050,7 +1049,7 @@ static int topk_check(const int64_t* seg_off, int32_t n_sg, int32_t k, int64_t* 
 }
 
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t st, TopkCtx* ctx,
-                 Upload* defer, bool with_block_max)
+                 Upload* defer, bool with_block_max, uint32_t window)
 {
     int64_t longest = 0;
     const int bad = topk_check(seg_off, n_sg, k, &longest);
@@ -1062,7 +1061,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
 
     char* ws = static_cast<char*>(workspace);
     SegT* d_segs = reinterpret_cast<SegT*>(ws + L.segs);
-    const bool small = longest <= kSmallMax;
+    const bool tiny = longest <= kTinyMax && k <= kTinyK, pick = !tiny && longest <= kPickMax;
     const int64_t span = span_for(n, n_sg);
 
     // the segment table: on the stack when it is short (a call that must not allocate stays off the heap as well)
@@ -1075,14 +1074,15 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
         segs[s] = SegT{seg_off[s], seg_off[s + 1], (int32_t)blocks, 0};
         blocks += (seg_off[s + 1] - seg_off[s] + span - 1) / span;
     }
-    ctx->large = !small;
+    ctx->large = !tiny;
+    ctx->pick = pick;
+    ctx->window = window;
     ctx->n_sg = n_sg;
     ctx->k = k;
     ctx->n = n;
     ctx->span = span;
     ctx->blocks = (int32_t)blocks;
     ctx->copies = L.R;
-    ctx->wide = false;
     ctx->d_segs = d_segs;
     ctx->d_state = ws + L.state;
     ctx->d_hist = reinterpret_cast<uint32_t*>(ws + L.hist);
@@ -1090,11 +1090,11 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     // Block maxima pay where nearly every block of 256 entries can be stepped over: at most one entry in 1024 selected
     // in the longest segment (with k = 512 of 50,000 nine blocks in ten hold a selected entry and the maxima are one
     // more read: 10.7 -> 11.5 us measured).
-    const bool sparse = longest >= (int64_t)k * 1024;
+    const bool sparse = !pick && longest >= (int64_t)k * 1024;
     ctx->d_block_max = with_block_max && sparse ? reinterpret_cast<uint32_t*>(ws + L.block_max) : nullptr;
     ctx->inline_ok = false;
     static_assert(sizeof(InlineSegs) <= sizeof(ctx->inline_segs), "inline segment table");
-    if (small) {
+    if (tiny) {
         if (n_sg <= kInlineSegs) {
             memset(ctx->inline_segs, 0, sizeof(InlineSegs));
             memcpy(ctx->inline_segs, segs, (size_t)n_sg * sizeof(SegT));
@@ -1111,7 +1111,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     if ((size_t)blocks > L.stage_slots) return PRUNER_EWORKSPACE;   // cannot happen: spans are sized for at most that many
     // segment table, and histograms cleared, in one launch
     const size_t per_pass = (size_t)n_sg * kBins;
-    const size_t hist_bytes = ((size_t)L.R + 2) * per_pass * sizeof(uint32_t);
+    const size_t hist_bytes = ((size_t)L.R + (pick ? 0 : 2)) * per_pass * sizeof(uint32_t);
     if (defer) {
         defer->bytes.assign(reinterpret_cast<const char*>(segs), reinterpret_cast<const char*>(segs + n_sg));
         defer->dst = d_segs;
@@ -1129,30 +1129,14 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     if (!aligned(score, 4) || !aligned(idx_out, 4) || (val_out && !aligned(val_out, 4))) return PRUNER_EINVAL;
     const int32_t n_sg = ctx.n_sg, k = ctx.k;
     const SegT* d_segs = static_cast<const SegT*>(ctx.d_segs);
-    bool resident = true;   // small route: every segment fits one batch of a workgroup
-    for (int32_t s2 = 0; s2 < n_sg; ++s2) resident = resident && seg_off[s2 + 1] - seg_off[s2] <= (int64_t)kSmallThreads * kSmallPer;
     if (!ctx.large) {
         InlineSegs args;
         memset(&args, 0, sizeof args);
-        bool tiny = k <= kTinyK;
-        for (int32_t s2 = 0; s2 < n_sg; ++s2) tiny = tiny && seg_off[s2 + 1] - seg_off[s2] <= (int64_t)kTinyMax;
-        if (tiny) {
-            if (ctx.inline_ok) {
-                memcpy(&args, ctx.inline_segs, sizeof args);
-                hipLaunchKernelGGL(topk_tiny_kernel<true>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
-            } else {
-                hipLaunchKernelGGL(topk_tiny_kernel<false>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
-            }
-            PRUNER_LAUNCH_CHECK();
-            return PRUNER_OK;
-        }
         if (ctx.inline_ok) {
             memcpy(&args, ctx.inline_segs, sizeof args);
-            if (resident) hipLaunchKernelGGL((topk_small_kernel<true, true>), dim3(n_sg), dim3(kSmallThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
-            else hipLaunchKernelGGL((topk_small_kernel<true, false>), dim3(n_sg), dim3(kSmallThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
+            hipLaunchKernelGGL(topk_tiny_kernel<true>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
         } else {
-            if (resident) hipLaunchKernelGGL((topk_small_kernel<false, true>), dim3(n_sg), dim3(kSmallThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
-            else hipLaunchKernelGGL((topk_small_kernel<false, false>), dim3(n_sg), dim3(kSmallThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
+            hipLaunchKernelGGL(topk_tiny_kernel<false>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
         }
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
@@ -1165,30 +1149,31 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     const size_t per_pass = (size_t)n_sg * kBins;
     uint32_t *hist0 = ctx.d_hist, *hist1 = ctx.d_hist + (size_t)R * per_pass, *hist2 = hist1 + per_pass;
     const dim3 chunks((unsigned)ctx.blocks);
-    bool wide = aligned(score, 16);
-    for (int32_t s2 = 0; s2 < n_sg; ++s2) wide = wide && seg_off[s2] % 4 == 0;
-#define PRUNER_SWEEP_LAUNCH(KERNEL, ...)                                                                          \
-    do {                                                                                                          \
-        if (wide) hipLaunchKernelGGL((KERNEL<true>), chunks, dim3(kBigThreads), 0, st, __VA_ARGS__);              \
-        else hipLaunchKernelGGL((KERNEL<false>), chunks, dim3(kBigThreads), 0, st, __VA_ARGS__);                  \
-        PRUNER_LAUNCH_CHECK();                                                                                    \
-    } while (0)
-    // (the draft kernel writes the block maxima when it counts the first digit: at its full load width, which is `wide` here)
-    uint32_t* const block_max = wide ? ctx.d_block_max : nullptr;
-    if (!have_first_digit) PRUNER_SWEEP_LAUNCH(hist0_kernel, score, d_segs, n_sg, span, R, hist0, block_max);
-    if (block_max) hipLaunchKernelGGL((funnel_kernel<true, true>), chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, d_state, d_stage, block_max);
-    else if (wide) hipLaunchKernelGGL((funnel_kernel<true, false>), chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, d_state, d_stage, block_max);
-    else hipLaunchKernelGGL((funnel_kernel<false, false>), chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, d_state, d_stage, block_max);
-    PRUNER_LAUNCH_CHECK();
-    PRUNER_SWEEP_LAUNCH(refine_kernel, score, d_segs, n_sg, span, hist1, hist2, d_state, d_stage);
-    PRUNER_SWEEP_LAUNCH(settle_kernel, score, d_segs, n_sg, span, k, hist2, d_state, d_stage);
-#undef PRUNER_SWEEP_LAUNCH
+    // (the draft kernel writes the block maxima when it counts the first digit)
+    uint32_t* const block_max = ctx.d_block_max;
+    if (!have_first_digit) {
+        hipLaunchKernelGGL(hist0_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, hist0, block_max);
+        PRUNER_LAUNCH_CHECK();
+    }
     // the ranking of a segment's k rows is shared out over up to k / 32 workgroups, as long as the launch is one
     // workgroup per compute unit at most (a compute unit holds one of these workgroups at a time: a launch of more
     // takes a second round, which costs more than longer rankings do)
     int share = (k + 31) / 32;
     if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
     if (share < 1) share = 1;
+    if (ctx.pick) {
+        hipLaunchKernelGGL(pick_kernel, dim3((unsigned)(n_sg * share)), dim3(kBigThreads), 0, st, score, d_segs, n_sg, R, ctx.window, k, share, hist0, idx_out,
+                           val_out);
+        PRUNER_LAUNCH_CHECK();
+        return PRUNER_OK;
+    }
+    if (block_max) hipLaunchKernelGGL(funnel_kernel<true>, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, k, hist0, hist1, d_state, d_stage, block_max);
+    else hipLaunchKernelGGL(funnel_kernel<false>, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, k, hist0, hist1, d_state, d_stage, block_max);
+    PRUNER_LAUNCH_CHECK();
+    hipLaunchKernelGGL(refine_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, hist1, hist2, d_state, d_stage);
+    PRUNER_LAUNCH_CHECK();
+    hipLaunchKernelGGL(settle_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, k, hist2, d_state, d_stage);
+    PRUNER_LAUNCH_CHECK();
     hipLaunchKernelGGL(gather_sort_kernel, dim3((unsigned)(n_sg * share)), dim3(kSmallThreads), 0, st, score, d_segs, n_sg, ctx.blocks, span,
                        d_state, d_stage, k, share, idx_out, val_out);
     PRUNER_LAUNCH_CHECK();
@@ -1206,7 +1191,7 @@ extern "C" int pruner_topk(const float* score, const int64_t* seg_off, int32_t n
     if (!aligned(score, 4) || !aligned(idx_out, 4) || (val_out && !aligned(val_out, 4))) return PRUNER_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     TopkCtx ctx;
-    const int rc = topk_prepare(seg_off, n_sg, k, workspace, workspace_bytes, st, &ctx);
+    const int rc = topk_prepare(seg_off, n_sg, k, workspace, workspace_bytes, st, &ctx, nullptr, true, kScoreWindow);
     if (rc) return rc;
     return topk_finish(ctx, score, seg_off, idx_out, val_out, false, st);
 }
@@ -1244,7 +1229,7 @@ extern "C" int pruner_topk_static(const float* score, const int64_t* seg_off, in
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     TopkCtx ctx;
-    const int rc = topk_prepare(seg_off, n_sg, k, g_scratch_ptr[dev], kStaticScratchBytes, st, &ctx, nullptr, false);
+    const int rc = topk_prepare(seg_off, n_sg, k, g_scratch_ptr[dev], kStaticScratchBytes, st, &ctx, nullptr, false, kScoreWindow);
     if (rc) return rc;
     return topk_finish(ctx, score, seg_off, idx_out, val_out, false, st);
 }
