@@ -920,8 +920,9 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
 #pragma unroll
         for (int v = 0; v < VEC; ++v) {
             if (c0 + v >= c_lo && c0 + v < c_end) {
-                const uint32_t key = key_of(out[v]);
-                atomicAdd(&digit_hist[first_digit_of(key, kDraftWindow)], 1u);
+                uint32_t digit;
+                const uint32_t key = key_and_digit(out[v], kDraftWindow, digit);
+                atomicAdd(&digit_hist[digit], 1u);
                 top = key > top ? key : top;
             }
         }
@@ -1002,6 +1003,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
 }
 
 constexpr int kAnyClass = -1;
+constexpr int kProducts = -2;   // plain and batched matrix products: the kernel branches between these two only
 
 // One launch scores the segments of one loop-nest class (CLS), so that each class gets the register budget, and with
 // it the occupancy, of its own symbol code; CLS = kAnyClass branches on the class at run time instead and serves
@@ -1049,6 +1051,10 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
     else if constexpr (CLS == kConv2d) PRUNER_WALK(NestConv2d);
     else if constexpr (CLS == kDepthwiseConv2d) PRUNER_WALK(NestDepthwiseConv2d);
     else if constexpr (CLS == kGeneric) PRUNER_WALK(NestGeneric);
+    else if constexpr (CLS == kProducts) {
+        if (d.cls == kGemm) PRUNER_WALK(NestGemm);
+        else PRUNER_WALK(NestBatchedGemm);
+    }
     else {
         switch (d.cls) {
             case kGemm: PRUNER_WALK(NestGemm); break;
@@ -1075,7 +1081,9 @@ template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, b
     }
     if constexpr (!DUMP) {
         if constexpr (CLS != kAnyClass) {
-            if (mut) return draft_kernel<CLS, 4, false, EXACT, true, true>;
+            if constexpr (CLS != kProducts) {
+                if (mut) return draft_kernel<CLS, 4, false, EXACT, true, true>;
+            }
         }
         if (hist) return draft_kernel<CLS, 4, false, EXACT, true, false>;
     }
@@ -1089,6 +1097,7 @@ template <bool DUMP, bool EXACT> DraftFn pick_class(int cls, int vec, bool hist,
         case kConv2d: return pick_vec<kConv2d, DUMP, EXACT>(vec, hist, mut);
         case kDepthwiseConv2d: return pick_vec<kDepthwiseConv2d, DUMP, EXACT>(vec, hist, mut);
         case kGeneric: return pick_vec<kGeneric, DUMP, EXACT>(vec, hist, mut);
+        case kProducts: return pick_vec<kProducts, DUMP, EXACT>(vec, hist, mut);
         default: return pick_vec<kAnyClass, DUMP, EXACT>(vec, hist, mut);
     }
 }
@@ -1448,7 +1457,9 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // there is only one class (its own kernel needs half the registers of the one that branches
     // on the class and a fraction of its code: 4,096 GEMM candidates take 5.7 us in the one and 6.4 in the other,
     // 65,536 convolution candidates 7.7 and 9.6), and, when the kernels make their candidates, up to two classes
-    // (a launch of the mutation is then saved); otherwise a single launch of the kernel that branches on the class.  A
+    // (a launch of the mutation is then saved); otherwise a single launch of the kernel that branches on the class, or
+    // of the one that branches between the two kinds of matrix products where there are no others (an encoder's tasks:
+    // half the registers, twice the workgroups at once: 20 x 50,000 candidates take 13.3 us instead of 14.8).  A
     // launch has at most as many workgroups as the device holds at once; they walk through the chunks of their segment.
     std::vector<int32_t> order(n_sg);
     uint32_t classes = 0;
@@ -1472,7 +1483,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     std::vector<int64_t> chunks_of;
     for (int32_t i = 0; i < n_sg; ++i) {
         const int32_t s = order[i];
-        const int cls = by_class ? descs[desc_of[s]].cls : kAnyClass;
+        const int cls = by_class ? descs[desc_of[s]].cls : vec == 4 && classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : kAnyClass;
         if (out->launches.empty() || out->launches.back().cls != cls) {
             out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, fused)),
                                                       reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, false))});
