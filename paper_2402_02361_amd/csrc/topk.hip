@@ -169,7 +169,9 @@ __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint
             const uint32_t gi = index_of(mine);
             if (r < (uint32_t)row_len) {
                 idx_out[row * row_len + r] = (int32_t)gi;
-                if (val_out) val_out[row * row_len + r] = gi >= seg_begin && gi < seg_end ? score[gi] : 0.f;   // never read outside the segment
+                // a key names its score (no read to wait for), except the one that -0.0 and +0.0 share
+                const uint32_t key = (uint32_t)(mine >> 32);
+                if (val_out) val_out[row * row_len + r] = key != kZeroKey ? score_of_key(key) : gi >= seg_begin && gi < seg_end ? score[gi] : 0.f;   // never read outside the segment
             }
         }
         __syncthreads();
@@ -844,16 +846,18 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
 // and ranks those whose index hashes to it among all of them: no lists between launches, no second and third digit as long as
 // the collection fits (its size follows from the histogram).  Where it does not, the bin is split by two more passes over the
 // segment; ties beyond that are written in index order by the segment's first workgroup.
-// Bound: the latency of its stages.  A sweep costs four instructions per entry (one comparison and one add with carry build
-// a thread's mask of sixteen; places, not scores, are noted, so nothing is selected out of registers).  20 segments of 50,000
-// entries, k = 512: 16 us where staging, refining, settling and ranking took 31 in four launches.
+// Bound: the latency of its stages.  The whole segment is requested at once, before the histogram is looked at, and a thread's
+// sixty-four comparisons leave a mask; places, not scores, are noted, so nothing is selected out of registers.  20 segments of
+// 50,000 entries, k = 512: 12 us where staging, refining, settling and ranking took 31 in four launches (bin 2.6 us, masks and
+// places 2, words 1.7, ranks 2; sweeping in four steps took 3 us more).
 
 constexpr int kPickMax = 65536;
+constexpr int kXcds = 8;                                        // parts of the device with a cache of their own; workgroups go to them in turn
 constexpr int kPickCap = 8192;                                  // words a workgroup collects
-constexpr int kPickWords = kPickCap + kPickCap / 32 + 2;
+constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
 static_assert(kPickCap >= 2 * PRUNER_MAX_K, "the entries above rank k's bin fit, and as many of the bin's");
 
-__global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int R,
+__global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int n_total, int R,
                                                            uint32_t window, int k, int share, const uint32_t* __restrict__ ghist0,
                                                            int32_t* __restrict__ idx_out, float* __restrict__ val_out)
 {
@@ -864,18 +868,31 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     __shared__ uint32_t found[3];
     __shared__ uint32_t fill, n_own;
     uint16_t* own = reinterpret_cast<uint16_t*>(place);
-    const int s = blockIdx.x / share, part = blockIdx.x % share;
+    // The workgroups of a segment go to one of the eight parts of the device: its cache then reads the segment once for all.
+    const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    if (job >= n_seg * share) return;
+    const int s = job / share, part = job % share;
     const SegT seg = segs[s];
     const int len = (int)(seg.end - seg.begin);
     const float* seg_score = score + seg.begin;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
 
-    float val[kBigPer];
-    load_sweep(seg_score, 0, len, val);   // the first sweep travels while the bin is looked up
+    // The whole segment travels while the bin is looked up: sixteen groups of four neighbours per thread.  A group that would
+    // reach past the end of the scores starts earlier; what lies outside the segment is masked out below.
+    constexpr int kGroups = kPickMax / (4 * kBigThreads);
+    const int last = n_total - 4 - (int)seg.begin;   // (there are thousands of scores in all)
+    auto group_begin = [](int g) { return (g * kBigThreads + (int)threadIdx.x) * 4; };
+    f32x4 val[kGroups];
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        if (g * 4 * kBigThreads < len) {
+            const int i = group_begin(g);
+            val[g] = *reinterpret_cast<const f32x4_a4*>(seg_score + (i < last ? i : last));
+        }
+    }
     bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
     uint32_t lowest, width, k_rem = found[1], in_bin = found[2];
     first_digit_range(found[0], window, lowest, width);
-    for (int i = threadIdx.x; i < kPickWords; i += kBigThreads) sel[i] = 0;   // spare words must read as "below everything"
     if (threadIdx.x == 0) fill = n_own = 0;
     __syncthreads();
     // more than fits: split the bin (the same decision in every workgroup of the segment)
@@ -883,6 +900,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         const int shift = next_shift(width);
         for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
         __syncthreads();
+#pragma unroll 1
         for (int row = 0; row < len; row += kRow) {
             float again[kBigPer];
             load_sweep(seg_score, row, len, again);
@@ -906,30 +924,37 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     const uint32_t from_key = ties_apart ? lowest + 1u : lowest;
     float t0 = score_of_key(from_key);   // (a key beyond the infinities' names a NaN: then every number is at or above it)
     t0 = t0 != t0 ? -__builtin_inff() : t0;
-    for (int row = 0; row < len; row += kRow) {
-        float next[kBigPer];
-        if (row + kRow < len) load_sweep(seg_score, row + kRow, len, next);
-        uint32_t mask = 0;   // bit 15 - j: entry j is at or above the threshold
+    {
+        uint64_t mask = 0;   // bit 4 g + e: entry e of group g is at or above the threshold
 #pragma unroll
-        for (int j = 0; j < kBigPer; ++j) mask = 2 * mask + (val[j] >= t0 ? 1u : 0u);
-        if (row + kRow > len) {   // the segment's last sweep: entries past its end (read as 0) are none
+        for (int g = 0; g < kGroups; ++g) {
+            if (g * 4 * kBigThreads < len) {
+                uint32_t four = 0;
 #pragma unroll
-            for (int j = 0; j < kBigPer; ++j) mask &= sweep_index(row, j) < len ? ~0u : ~(1u << (kBigPer - 1 - j));
+                for (int e = 3; e >= 0; --e) four = 2 * four + (val[g][e] >= t0 ? 1u : 0u);
+                if ((g + 1) * 4 * kBigThreads > len) {   // the segment's last groups
+                    const int i = group_begin(g), begun = i < last ? i : last, left = len - i;
+                    four = left <= 0 ? 0u : (four >> (i - begun)) & (left < 4 ? (1u << left) - 1u : 15u);
+                }
+                mask |= (uint64_t)four << (4 * g);
+            }
         }
-        const uint32_t mine = (uint32_t)__popc(mask);
+        const uint32_t mine = (uint32_t)__popcll(mask);
         const uint32_t upto = wave_inclusive_sum(mine);
         uint32_t base = 0;
         if (lane == kWave - 1 && upto) base = atomicAdd(&fill, upto);
         uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1) + upto - mine;
         while (mask) {
-            const int j = kBigPer - 1 - (31 - __clz(mask));
-            mask &= ~(1u << (kBigPer - 1 - j));
-            if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, j);
+            const int bit = __ffsll((unsigned long long)mask) - 1;
+            mask &= mask - 1;
+            if (at < (uint32_t)kPickCap) place[at] = (uint32_t)(group_begin(bit >> 2) + (bit & 3));
             ++at;
         }
-#pragma unroll
-        for (int j = 0; j < kBigPer; ++j) val[j] = next[j];
     }
+    // spare words and those behind the last must read as "below everything"
+    const int n_raw = n > 0 ? (int)slot((uint32_t)n - 1u) + 1 : 0;
+    for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
+        if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
     __syncthreads();
     for (int e = threadIdx.x; e < n; e += kBigThreads) {
         const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
@@ -1162,7 +1187,7 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
     if (share < 1) share = 1;
     if (ctx.pick) {
-        hipLaunchKernelGGL(pick_kernel, dim3((unsigned)(n_sg * share)), dim3(kBigThreads), 0, st, score, d_segs, n_sg, R, ctx.window, k, share, hist0, idx_out,
+        hipLaunchKernelGGL(pick_kernel, dim3((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds)), dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, ctx.window, k, share, hist0, idx_out,
                            val_out);
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
