@@ -5,12 +5,16 @@
 // order; the k survivors are ranked by (key descending, index ascending).  Nothing depends on the order in which blocks or
 // wavefronts run.
 //
-// Three routes, same result:
+// Four routes, same result:
 //   tiny   - segments of at most 8192 entries and k up to 64 (the final selection after the verify stage, small draft
 //            populations): one launch, no digits (tiny_select in select_common.h);
 //   pick   - segments of at most kPickMax entries: one launch behind whoever counted the first digit (the draft kernel as a
 //            rule, else one pass).  Several workgroups per segment, each of which goes through the whole segment, keeps the
 //            few entries at or above rank k's bin, and ranks its share of them;
+//   lists  - segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
+//            16384-entry sweeps, one workgroup each) and sets the entries at or above the bin aside in a list per span; the
+//            workgroups of a segment then collect from its lists (and go through the segment themselves only if a list
+//            overflowed or the collection does not fit);
 //   spans  - longer segments are cut into spans of whole 16384-entry sweeps, one workgroup of 1024 threads each; the scores
 //            are read twice at most (first-digit histogram, which also notes the largest key of every 256 entries; then
 //            everything at or above that digit's rank-k bin is set aside, a few thousand entries as a rule, and blocks of
@@ -857,9 +861,85 @@ constexpr int kPickCap = 8192;                                  // words a workg
 constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
 static_assert(kPickCap >= 2 * PRUNER_MAX_K, "the entries above rank k's bin fit, and as many of the bin's");
 
+// The lists route: at most 32 spans per segment, so that a segment that has to be gone through again by one workgroup is still
+// a matter of microseconds.
+constexpr int64_t kListsMax = 32 * (int64_t)kRow;
+constexpr int kListCap = 1280;
+struct List {                 // the entries of one span at or above the bin (lies in the span's Stage)
+    uint32_t count, pad;      // may exceed the capacity
+    uint64_t word[kListCap];  // in no order
+};
+static_assert(sizeof(List) <= sizeof(Stage), "a list lies where the spans route keeps its stage");
+
+// A thread's sixteen entries of a sweep as a mask (bit j: entry j is at or above t0).
+__device__ __forceinline__ uint32_t mask_of_sweep(const float (&val)[kBigPer], float t0, int64_t row, int64_t hi)
+{
+    uint32_t mask = 0;
+#pragma unroll
+    for (int j = kBigPer - 1; j >= 0; --j) mask = 2 * mask + (val[j] >= t0 ? 1u : 0u);
+    if (row + kRow > hi) {   // the last sweep: entries past the end (read as 0) are none
+#pragma unroll
+        for (int j = 0; j < kBigPer; ++j) mask &= sweep_index(row, j) < hi ? ~0u : ~(1u << j);
+    }
+    return mask;
+}
+// The smallest score at or above a key (a key beyond the infinities' names a NaN: then every number is).
+__device__ __forceinline__ float threshold_of(uint32_t key)
+{
+    const float t = score_of_key(key);
+    return t != t ? -__builtin_inff() : t;
+}
+// Consecutive places of a list for the `mine` entries of each thread: the wavefront's threads share out what one reserves.
+__device__ __forceinline__ uint32_t reserve(uint32_t* fill, uint32_t mine)
+{
+    const uint32_t upto = wave_inclusive_sum(mine);
+    uint32_t base = 0;
+    if (lane_id() == kWave - 1 && upto) base = atomicAdd(fill, upto);
+    return (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1) + upto - mine;
+}
+
+__global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(8))) list_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
+                                                                                                    int64_t span, int R, uint32_t window, int k,
+                                                                                                    const uint32_t* __restrict__ ghist0, Stage* __restrict__ stage)
+{
+    __shared__ uint32_t hist[kBins];
+    __shared__ uint32_t wave_tot[16];
+    __shared__ uint32_t found[3];
+    __shared__ uint32_t fill;
+    const int s = segment_of_block(segs, n_seg, blockIdx.x);
+    const SegT seg = segs[s];
+    const int64_t lo = seg.begin + (int64_t)(blockIdx.x - seg.first_block) * span;
+    const int64_t hi = lo + span < seg.end ? lo + span : seg.end;
+    float val[kBigPer];
+    load_sweep(score, lo, hi, val);   // the first sweep travels while the bin is looked up
+    bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+    uint32_t lowest, width;
+    first_digit_range(found[0], window, lowest, width);
+    const float t0 = threshold_of(lowest);
+    if (threadIdx.x == 0) fill = 0;
+    __syncthreads();
+    List& mine = *reinterpret_cast<List*>(&stage[blockIdx.x]);
+    for (int64_t row = lo; row < hi; row += kRow) {
+        if (row > lo) load_sweep(score, row, hi, val);
+        uint32_t mask = mask_of_sweep(val, t0, row, hi);
+        uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
+        while (mask) {
+            const int64_t i = sweep_index(row, __ffs(mask) - 1);
+            mask &= mask - 1;
+            if (at < (uint32_t)kListCap) mine.word[at] = compose(key_of(score[i]), (uint32_t)i);
+            ++at;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) mine.count = fill;
+}
+
+// LISTS: the lists route.
+template <bool LISTS>
 __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int n_total, int R,
                                                            uint32_t window, int k, int share, const uint32_t* __restrict__ ghist0,
-                                                           int32_t* __restrict__ idx_out, float* __restrict__ val_out)
+                                                           const Stage* __restrict__ stage, int n_stages, int32_t* __restrict__ idx_out,
+                                                           float* __restrict__ val_out)
 {
     __shared__ __align__(16) uint64_t sel[kPickWords];
     __shared__ uint32_t place[kPickCap];      // indices inside the segment; later: which words this workgroup ranks
@@ -879,15 +959,21 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
 
     // The whole segment travels while the bin is looked up: sixteen groups of four neighbours per thread.  A group that would
     // reach past the end of the scores starts earlier; what lies outside the segment is masked out below.
-    constexpr int kGroups = kPickMax / (4 * kBigThreads);
+    constexpr int kGroups = LISTS ? 1 : kPickMax / (4 * kBigThreads);
     const int last = n_total - 4 - (int)seg.begin;   // (there are thousands of scores in all)
     auto group_begin = [](int g) { return (g * kBigThreads + (int)threadIdx.x) * 4; };
     f32x4 val[kGroups];
+    const int b0 = seg.first_block, n_lists = LISTS ? (s + 1 < n_seg ? segs[s + 1].first_block : n_stages) - b0 : 0;
+    uint32_t my_count = 0;   // of list `lane`
+    if constexpr (LISTS) {
+        if (lane < n_lists) my_count = reinterpret_cast<const List*>(&stage[b0 + lane])->count;
+    } else {
 #pragma unroll
-    for (int g = 0; g < kGroups; ++g) {
-        if (g * 4 * kBigThreads < len) {
-            const int i = group_begin(g);
-            val[g] = *reinterpret_cast<const f32x4_a4*>(seg_score + (i < last ? i : last));
+        for (int g = 0; g < kGroups; ++g) {
+            if (g * 4 * kBigThreads < len) {
+                const int i = group_begin(g);
+                val[g] = *reinterpret_cast<const f32x4_a4*>(seg_score + (i < last ? i : last));
+            }
         }
     }
     bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
@@ -896,7 +982,9 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     if (threadIdx.x == 0) fill = n_own = 0;
     __syncthreads();
     // more than fits: split the bin (the same decision in every workgroup of the segment)
+    bool whole = true;   // the bin is the first digit's, as the lists know it
     while ((uint32_t)k - k_rem + in_bin > (uint32_t)kPickCap && width != 0u) {
+        whole = false;
         const int shift = next_shift(width);
         for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
         __syncthreads();
@@ -921,10 +1009,34 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     // entries at or above `lowest` are collected; if the ties alone are too many, those above it
     const bool ties_apart = (uint32_t)k - k_rem + in_bin > (uint32_t)kPickCap;
     const int n = (int)(ties_apart ? (uint32_t)k - k_rem : (uint32_t)k - k_rem + in_bin);
-    const uint32_t from_key = ties_apart ? lowest + 1u : lowest;
-    float t0 = score_of_key(from_key);   // (a key beyond the infinities' names a NaN: then every number is at or above it)
-    t0 = t0 != t0 ? -__builtin_inff() : t0;
-    {
+    const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
+    bool from_lists = false;
+    if constexpr (LISTS) {
+        // (every wavefront holds the counts: at most 33 lists)
+        from_lists = whole && !ties_apart && __ballot(my_count > (uint32_t)kListCap) == 0ull;
+        if (from_lists) {
+            const uint32_t upto = wave_inclusive_sum(my_count);
+            for (int l = wave; l < n_lists; l += kBigThreads / kWave) {   // a wavefront copies whole lists
+                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l), at = (uint32_t)__builtin_amdgcn_readlane((int)upto, l) - cnt;
+                const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
+                for (uint32_t e = lane; e < cnt; e += kWave)
+                    if (at + e < (uint32_t)n) sel[slot(at + e)] = from[e];
+            }
+        } else {
+#pragma unroll 1
+            for (int row = 0; row < len; row += kRow) {
+                float again[kBigPer];
+                load_sweep(seg_score, row, len, again);
+                uint32_t mask = mask_of_sweep(again, t0, row, len);
+                uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
+                while (mask) {
+                    if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, __ffs(mask) - 1);
+                    mask &= mask - 1;
+                    ++at;
+                }
+            }
+        }
+    } else {
         uint64_t mask = 0;   // bit 4 g + e: entry e of group g is at or above the threshold
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
@@ -939,11 +1051,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                 mask |= (uint64_t)four << (4 * g);
             }
         }
-        const uint32_t mine = (uint32_t)__popcll(mask);
-        const uint32_t upto = wave_inclusive_sum(mine);
-        uint32_t base = 0;
-        if (lane == kWave - 1 && upto) base = atomicAdd(&fill, upto);
-        uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1) + upto - mine;
+        uint32_t at = reserve(&fill, (uint32_t)__popcll(mask));
         while (mask) {
             const int bit = __ffsll((unsigned long long)mask) - 1;
             mask &= mask - 1;
@@ -956,11 +1064,13 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
         if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
     __syncthreads();
-    for (int e = threadIdx.x; e < n; e += kBigThreads) {
-        const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
-        sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
+    if (!from_lists) {
+        for (int e = threadIdx.x; e < n; e += kBigThreads) {
+            const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
+            sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
+        }
+        __syncthreads();
     }
-    __syncthreads();
     // (every workgroup has its own order of the words: a hash of the index decides who ranks a word)
     for (int e = threadIdx.x; e < n; e += kBigThreads) {
         const uint32_t h = (index_of(sel[slot((uint32_t)e)]) * 2654435761u) >> 16;
@@ -1074,7 +1184,7 @@ static int topk_check(const int64_t* seg_off, int32_t n_sg, int32_t k, int64_t* 
 }
 
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t st, TopkCtx* ctx,
-                 Upload* defer, bool with_block_max, uint32_t window)
+                 Upload* defer, bool with_block_max, uint32_t window, bool copies)
 {
     int64_t longest = 0;
     const int bad = topk_check(seg_off, n_sg, k, &longest);
@@ -1101,6 +1211,8 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     }
     ctx->large = !tiny;
     ctx->pick = pick;
+    // (a population of copies, as the explorer loop keeps it, would have its lists overflow as a rule: it takes the spans route)
+    ctx->lists = !tiny && !pick && longest <= kListsMax && !copies;
     ctx->window = window;
     ctx->n_sg = n_sg;
     ctx->k = k;
@@ -1115,7 +1227,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     // Block maxima pay where nearly every block of 256 entries can be stepped over: at most one entry in 1024 selected
     // in the longest segment (with k = 512 of 50,000 nine blocks in ten hold a selected entry and the maxima are one
     // more read: 10.7 -> 11.5 us measured).
-    const bool sparse = !pick && longest >= (int64_t)k * 1024;
+    const bool sparse = !pick && !ctx->lists && longest >= (int64_t)k * 1024;
     ctx->d_block_max = with_block_max && sparse ? reinterpret_cast<uint32_t*>(ws + L.block_max) : nullptr;
     ctx->inline_ok = false;
     static_assert(sizeof(InlineSegs) <= sizeof(ctx->inline_segs), "inline segment table");
@@ -1136,7 +1248,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     if ((size_t)blocks > L.stage_slots) return PRUNER_EWORKSPACE;   // cannot happen: spans are sized for at most that many
     // segment table, and histograms cleared, in one launch
     const size_t per_pass = (size_t)n_sg * kBins;
-    const size_t hist_bytes = ((size_t)L.R + (pick ? 0 : 2)) * per_pass * sizeof(uint32_t);
+    const size_t hist_bytes = ((size_t)L.R + (pick || ctx->lists ? 0 : 2)) * per_pass * sizeof(uint32_t);
     if (defer) {
         defer->bytes.assign(reinterpret_cast<const char*>(segs), reinterpret_cast<const char*>(segs + n_sg));
         defer->dst = d_segs;
@@ -1186,9 +1298,17 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     int share = (k + 31) / 32;
     if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
     if (share < 1) share = 1;
-    if (ctx.pick) {
-        hipLaunchKernelGGL(pick_kernel, dim3((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds)), dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, ctx.window, k, share, hist0, idx_out,
-                           val_out);
+    if (ctx.pick || ctx.lists) {
+        const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
+        if (ctx.lists) {
+            hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, k, hist0, d_stage);
+            PRUNER_LAUNCH_CHECK();
+            hipLaunchKernelGGL(pick_kernel<true>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, ctx.window, k, share, hist0, d_stage,
+                               ctx.blocks, idx_out, val_out);
+        } else {
+            hipLaunchKernelGGL(pick_kernel<false>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, ctx.window, k, share, hist0, d_stage,
+                               ctx.blocks, idx_out, val_out);
+        }
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }
@@ -1216,7 +1336,7 @@ extern "C" int pruner_topk(const float* score, const int64_t* seg_off, int32_t n
     if (!aligned(score, 4) || !aligned(idx_out, 4) || (val_out && !aligned(val_out, 4))) return PRUNER_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     TopkCtx ctx;
-    const int rc = topk_prepare(seg_off, n_sg, k, workspace, workspace_bytes, st, &ctx, nullptr, true, kScoreWindow);
+    const int rc = topk_prepare(seg_off, n_sg, k, workspace, workspace_bytes, st, &ctx, nullptr, true, kScoreWindow, false);
     if (rc) return rc;
     return topk_finish(ctx, score, seg_off, idx_out, val_out, false, st);
 }
@@ -1254,7 +1374,7 @@ extern "C" int pruner_topk_static(const float* score, const int64_t* seg_off, in
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     TopkCtx ctx;
-    const int rc = topk_prepare(seg_off, n_sg, k, g_scratch_ptr[dev], kStaticScratchBytes, st, &ctx, nullptr, false, kScoreWindow);
+    const int rc = topk_prepare(seg_off, n_sg, k, g_scratch_ptr[dev], kStaticScratchBytes, st, &ctx, nullptr, false, kScoreWindow, false);
     if (rc) return rc;
     return topk_finish(ctx, score, seg_off, idx_out, val_out, false, st);
 }
