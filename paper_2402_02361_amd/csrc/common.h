@@ -90,7 +90,6 @@ struct TopkCtx {
     bool large;            // the route counts first digits (not the tiny one)
     bool pick;             // ... and takes one launch behind that
     bool lists;            // ... or two
-    uint32_t window;       // where the first digit's bins are narrow (first_digit_of)
     int32_t n_sg, k;
     int64_t n, span;
     int32_t blocks;        // workgroups of a sweep launch
@@ -104,7 +103,7 @@ struct TopkCtx {
 // validates, uploads the segment table, clears the histograms (large route)
 // (defer: do not launch the upload, describe it there instead; copies: the scores are expected to hold ties by the thousand)
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t stream, TopkCtx* ctx,
-                 Upload* defer, bool with_block_max, uint32_t window, bool copies);
+                 Upload* defer, bool with_block_max, bool copies);
 // the remaining launches; have_first_digit: d_hist already holds the first digit's counts of every segment
 int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, int32_t* idx_out, float* val_out, bool have_first_digit,
                 hipStream_t stream);

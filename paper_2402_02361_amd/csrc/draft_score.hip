@@ -921,7 +921,7 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
         for (int v = 0; v < VEC; ++v) {
             if (c0 + v >= c_lo && c0 + v < c_end) {
                 uint32_t digit;
-                const uint32_t key = key_and_digit(out[v], kDraftWindow, digit);
+                const uint32_t key = key_and_digit(out[v], digit);
                 atomicAdd(&digit_hist[digit], 1u);
                 top = key > top ? key : top;
             }

@@ -38,7 +38,7 @@ extern "C" int pruner_prior_filter(const pruner_subgraph* sg, int32_t n_sg, cons
     // histograms the draft kernel adds to.
     TopkCtx ctx;
     Upload pending;
-    int rc = topk_prepare(seg_off, n_sg, k, ws + draft_bytes, workspace_bytes - draft_bytes, st, &ctx, &pending, true, kDraftWindow, false);
+    int rc = topk_prepare(seg_off, n_sg, k, ws + draft_bytes, workspace_bytes - draft_bytes, st, &ctx, &pending, true, false);
     if (rc) return rc;
     DraftPlan plan;
     rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, ctx.large, false, &plan);

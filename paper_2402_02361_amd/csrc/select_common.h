@@ -16,47 +16,47 @@ __device__ __forceinline__ uint32_t key_of(float x)
     return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// The first digit of the selection: a bin of 2048 that grows with the key.  Scores that are worth choosing among lie within a
-// few octaves, so the bins are narrow there: 32 to an octave (three per cent of a score) in a window of seventeen octaves on
-// either side of zero, two to an octave outside it.  (With the key's upper eleven bits, four bins to an octave, the bin of
-// rank k held thousands of entries; now it holds tens to hundreds, and most populations are settled by this digit alone.)
-// `window`: 32 x the biased exponent at which the window begins, a multiple of 16.  Two more digits of up to eleven bits
-// settle any bin (a bin spans 2^18 keys, or 2^22 outside the window).
-constexpr uint32_t kFine = 17 * 32;
-constexpr uint32_t kDraftWindow = (127 - 23) * 32;   // latencies: 2^-23 .. 2^-6 seconds
-constexpr uint32_t kScoreWindow = (127 - 10) * 32;   // scores in general: 2^-10 .. 2^7
-// b = x / 16 below the window, x / 16 + 15/16 of the way into it inside, again x / 16 plus a constant above (x: the magnitude
-// in units of 1/32 octave): (x + 15 clamp(x - window, 0, kFine)) / 16, five instructions.  0 .. 1021.
-__device__ __forceinline__ uint32_t magnitude_bin(uint32_t bits, uint32_t window)
+// The first digit of the selection: a bin of 2048 that grows with the key.  Scores lie within a few dozen octaves, so the bins
+// are narrow there: 16 to an octave (four to six per cent of a score) in a window of thirty-four octaves on either side of
+// zero (latencies of a tenth of a microsecond and scores in the thousands lie inside), two to an octave outside it.  (With the
+// key's upper eleven bits, four bins to an octave, the bin of rank k held thousands of entries; now it holds tens to hundreds,
+// and most populations are settled by this digit alone.)  Two more digits of up to eleven bits settle any bin (a bin spans
+// 2^19 keys, or 2^22 outside the window).
+constexpr uint32_t kFine = 34 * 16;
+constexpr uint32_t kWindow = (127 - 23) * 16;   // in units of 1/16 octave: 2^-23
+// b = x / 8 below the window, x / 8 + 7/8 of the way into it inside, again x / 8 plus a constant above (x: the magnitude in
+// units of 1/16 octave): (x + 7 clamp(x - window, 0, kFine)) / 8, five instructions.  0 .. 987.
+__device__ __forceinline__ uint32_t magnitude_bin(uint32_t bits)
 {
-    const uint32_t x = (bits >> 18) & 0x1FFFu;
-    int d = (int)x - (int)window;
+    const uint32_t x = (bits >> 19) & 0xFFFu;
+    int d = (int)x - (int)kWindow;
     d = d > 0 ? d : 0;
     d = d < (int)kFine ? d : (int)kFine;
-    return ((uint32_t)__umul24((uint32_t)d, 15u) + x) >> 4;
+    return ((uint32_t)__umul24((uint32_t)d, 7u) + x) >> 3;
 }
 // 1024 + b, or 1023 - b for a negative score
-__device__ __forceinline__ uint32_t first_digit_of(uint32_t key, uint32_t window)
+__device__ __forceinline__ uint32_t first_digit_of(uint32_t key)
 {
     const uint32_t below_zero = ~(uint32_t)((int32_t)key >> 31);   // all ones for a negative score
-    return (magnitude_bin(key ^ below_zero, window) + 1024u) ^ (below_zero >> 21);
+    return (magnitude_bin(key ^ below_zero) + 1024u) ^ (below_zero >> 21);
 }
 // The key and the first digit of a score at once.
-__device__ __forceinline__ uint32_t key_and_digit(float score, uint32_t window, uint32_t& digit)
+__device__ __forceinline__ uint32_t key_and_digit(float score, uint32_t& digit)
 {
     uint32_t u = __float_as_uint(score);
     if (u == 0x80000000u) u = 0u;
     const uint32_t below_zero = (uint32_t)((int32_t)u >> 31);
-    digit = (magnitude_bin(u, window) + 1024u) ^ (below_zero >> 21);
+    digit = (magnitude_bin(u) + 1024u) ^ (below_zero >> 21);
     return u ^ (below_zero | 0x80000000u);
 }
 // The keys of a bin: lowest .. lowest + width.
-__device__ __forceinline__ void first_digit_range(uint32_t bin, uint32_t window, uint32_t& lowest, uint32_t& width)
+__device__ __forceinline__ void first_digit_range(uint32_t bin, uint32_t& lowest, uint32_t& width)
 {
+    static_assert(kWindow % 8 == 0 && kFine % 8 == 0, "bins outside the window are whole");
     const bool negative = bin < 1024u;
     const uint32_t b = negative ? 1023u - bin : bin - 1024u;
-    auto begin = [&](uint32_t v) { return v < (window >> 4) ? v << 4 : v < (window >> 4) + kFine ? window + (v - (window >> 4)) : window + kFine + ((v - (window >> 4) - kFine) << 4); };
-    const uint32_t from = begin(b) << 18, to = begin(b + 1) << 18;
+    auto begin = [](uint32_t v) { return v < kWindow / 8 ? v * 8 : v < kWindow / 8 + kFine ? kWindow + (v - kWindow / 8) : kWindow + kFine + (v - kWindow / 8 - kFine) * 8; };
+    const uint32_t from = begin(b) << 19, to = begin(b + 1) << 19;
     lowest = negative ? 0x80000000u - to : 0x80000000u + from;
     width = to - from - 1u;
 }

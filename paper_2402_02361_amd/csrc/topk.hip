@@ -278,7 +278,7 @@ __device__ __forceinline__ void bucket_of_pass(const uint32_t* __restrict__ ghis
 }
 
 __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
-                                                            int64_t span, int R, uint32_t window, uint32_t* __restrict__ ghist /* [R][n_seg][kBins] */,
+                                                            int64_t span, int R, uint32_t* __restrict__ ghist /* [R][n_seg][kBins] */,
                                                             uint32_t* __restrict__ block_max /* or null */)
 {
     __shared__ uint32_t hist[kBins];
@@ -296,7 +296,7 @@ __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restr
         for (int j = 0; j < kBigPer; ++j) {
             const int64_t i = sweep_index(row, j);
             const uint32_t key = key_of(val[j]);
-            light_hist_add(hist, first_digit_of(key, window), i < hi);
+            light_hist_add(hist, first_digit_of(key), i < hi);
             if (i < hi && key > top[j >> 2]) top[j >> 2] = key;
         }
         // a wavefront's q-th load is one block of 256 neighbouring entries (spans are whole sweeps from the segment's begin)
@@ -319,7 +319,7 @@ __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restr
 // (held to 64 registers: a compute unit then holds two of these workgroups, and a launch of up to 512 runs in one round)
 template <bool BLK>
 __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(8))) funnel_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
-                                                             int64_t span, int R, uint32_t window, int k, const uint32_t* __restrict__ ghist0,
+                                                             int64_t span, int R, int k, const uint32_t* __restrict__ ghist0,
                                                              uint32_t* __restrict__ ghist1, SelState* __restrict__ state,
                                                              Stage* __restrict__ stage, const uint32_t* __restrict__ block_max)
 {
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
     const uint32_t k_rem = found[1];
     uint32_t lowest, width;
-    first_digit_range(found[0], window, lowest, width);
+    first_digit_range(found[0], lowest, width);
     const int shift = next_shift(width);
     if constexpr (BLK) {
         // how many of the span's (first 1024) blocks will have to be read
@@ -859,7 +859,10 @@ constexpr int kPickMax = 65536;
 constexpr int kXcds = 8;                                        // parts of the device with a cache of their own; workgroups go to them in turn
 constexpr int kPickCap = 8192;                                  // words a workgroup collects
 constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
-static_assert(kPickCap >= 2 * PRUNER_MAX_K, "the entries above rank k's bin fit, and as many of the bin's");
+// What is collected is ranked word against word, so it has to be little more than k: otherwise the bin is split first (two
+// values shared by 20,000 entries, k = 512: 84 us ranked at once).
+__device__ __forceinline__ uint32_t pick_limit(int k) { return (uint32_t)(k + k / 4 + 256); }
+static_assert(kPickCap >= PRUNER_MAX_K + PRUNER_MAX_K / 4 + 256, "a collection fits");
 
 // The lists route: at most 32 spans per segment, so that a segment that has to be gone through again by one workgroup is still
 // a matter of microseconds.
@@ -898,13 +901,33 @@ __device__ __forceinline__ uint32_t reserve(uint32_t* fill, uint32_t mine)
     return (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1) + upto - mine;
 }
 
+// The least and the largest key of the bin lowest .. lowest + width among what the workgroup's threads saw, in two LDS words that
+// start as 0 (the least as its complement): a bin that holds one value only, as those of measured copies do, is then known for
+// it and is not split digit by digit.
+__device__ __forceinline__ void note_range(uint32_t not_least, uint32_t largest, uint32_t* range)
+{
+#pragma unroll
+    for (int step = 1; step < kWave; step *= 2) {
+        const uint32_t a = __shfl_xor(not_least, step), b = __shfl_xor(largest, step);
+        not_least = a > not_least ? a : not_least;
+        largest = b > largest ? b : largest;
+    }
+    if (lane_id() == 0 && largest != 0u) {
+        atomicMax(&range[0], not_least);
+        atomicMax(&range[1], largest);
+    }
+}
+
 __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(8))) list_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
-                                                                                                    int64_t span, int R, uint32_t window, int k,
-                                                                                                    const uint32_t* __restrict__ ghist0, Stage* __restrict__ stage)
+                                                                                                    int64_t span, int R, int k,
+                                                                                                    const uint32_t* __restrict__ ghist0,
+                                                                                                    uint32_t* __restrict__ ghist1, uint32_t* __restrict__ granges,
+                                                                                                    Stage* __restrict__ stage)
 {
     __shared__ uint32_t hist[kBins];
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t found[3];
+    __shared__ uint32_t range[2];
     __shared__ uint32_t fill;
     const int s = segment_of_block(segs, n_seg, blockIdx.x);
     const SegT seg = segs[s];
@@ -914,30 +937,53 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     load_sweep(score, lo, hi, val);   // the first sweep travels while the bin is looked up
     bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
     uint32_t lowest, width;
-    first_digit_range(found[0], window, lowest, width);
+    first_digit_range(found[0], lowest, width);
     const float t0 = threshold_of(lowest);
-    if (threadIdx.x == 0) fill = 0;
+    const int shift = next_shift(width);
+    const bool crowded = (uint32_t)k - found[1] + found[2] > pick_limit(k);   // the second digit will be asked for
+    __syncthreads();
+    if (threadIdx.x == 0) fill = range[0] = range[1] = 0;
+    if (crowded)
+        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
     __syncthreads();
     List& mine = *reinterpret_cast<List*>(&stage[blockIdx.x]);
+    uint32_t not_least = 0, largest = 0;
     for (int64_t row = lo; row < hi; row += kRow) {
         if (row > lo) load_sweep(score, row, hi, val);
         uint32_t mask = mask_of_sweep(val, t0, row, hi);
+        if (crowded) {
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) {
+                const uint32_t key = key_of(val[j]);
+                const bool in = ((mask >> j) & 1u) != 0u && key - lowest <= width;
+                light_hist_add(hist, (key - lowest) >> shift, in);
+                not_least = in && ~key > not_least ? ~key : not_least;
+                largest = in && key > largest ? key : largest;
+            }
+        }
         uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
         while (mask) {
             const int64_t i = sweep_index(row, __ffs(mask) - 1);
             mask &= mask - 1;
             if (at < (uint32_t)kListCap) mine.word[at] = compose(key_of(score[i]), (uint32_t)i);
+            else break;   // (the count says that there are more)
             ++at;
         }
     }
+    if (crowded) note_range(not_least, largest, range);
     __syncthreads();
     if (threadIdx.x == 0) mine.count = fill;
+    if (crowded) {
+        flush_hist<kBigThreads>(hist, ghist1, 1, n_seg, s);
+        if (threadIdx.x < 2 && range[threadIdx.x] != 0u) atomicMax(&granges[(size_t)s * kBins + threadIdx.x], range[threadIdx.x]);
+    }
 }
 
 // LISTS: the lists route.
 template <bool LISTS>
 __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int n_total, int R,
-                                                           uint32_t window, int k, int share, const uint32_t* __restrict__ ghist0,
+                                                           int k, int share, const uint32_t* __restrict__ ghist0,
+                                                           const uint32_t* __restrict__ ghist1, const uint32_t* __restrict__ granges,
                                                            const Stage* __restrict__ stage, int n_stages, int32_t* __restrict__ idx_out,
                                                            float* __restrict__ val_out)
 {
@@ -946,7 +992,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     __shared__ uint32_t hist[kBins];          // later: the ranking's counts
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t found[3];
-    __shared__ uint32_t fill, n_own;
+    __shared__ uint32_t fill, n_own, range[2];
     uint16_t* own = reinterpret_cast<uint16_t*>(place);
     // The workgroups of a segment go to one of the eight parts of the device: its cache then reads the segment once for all.
     const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
@@ -978,51 +1024,134 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     }
     bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
     uint32_t lowest, width, k_rem = found[1], in_bin = found[2];
-    first_digit_range(found[0], window, lowest, width);
-    if (threadIdx.x == 0) fill = n_own = 0;
+    first_digit_range(found[0], lowest, width);
+    if (threadIdx.x == 0) fill = n_own = range[0] = range[1] = 0;
     __syncthreads();
-    // more than fits: split the bin (the same decision in every workgroup of the segment)
-    bool whole = true;   // the bin is the first digit's, as the lists know it
-    while ((uint32_t)k - k_rem + in_bin > (uint32_t)kPickCap && width != 0u) {
-        whole = false;
-        const int shift = next_shift(width);
-        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
-        __syncthreads();
-#pragma unroll 1
-        for (int row = 0; row < len; row += kRow) {
-            float again[kBigPer];
-            load_sweep(seg_score, row, len, again);
+    // More than the limit: the bin is split (the same decision in every workgroup of the segment), in the lists route first by
+    // the second digit, which the launch before has counted.
+    const uint32_t limit = pick_limit(k);
+    const bool lists_whole = LISTS && __ballot(my_count > (uint32_t)kListCap) == 0ull;   // (every wavefront holds all counts)
+    uint32_t least = 0u, largest = 0xFFFFFFFFu;   // of the bin's keys
+    auto between = [&] {
+        const uint32_t last_key = lowest + width < largest ? lowest + width : largest;
+        lowest = lowest > least ? lowest : least;
+        width = last_key - lowest;
+    };
+    bool second = !LISTS;
+    if ((uint32_t)k - k_rem + in_bin > limit) {
+        if constexpr (LISTS) {
+            least = ~granges[(size_t)s * kBins];
+            largest = granges[(size_t)s * kBins + 1];
+        } else {
+            uint32_t a = 0, b = 0;
 #pragma unroll
-            for (int j = 0; j < kBigPer; ++j) {
-                const uint32_t key = sweep_index(row, j) < len ? key_of(again[j]) : 0u;
-                light_hist_add(hist, (key - lowest) >> shift, key != 0u && key - lowest <= width);
+            for (int g = 0; g < kGroups; ++g) {
+                if (g * 4 * kBigThreads < len) {
+                    const int i = group_begin(g), begun = i < last ? i : last;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t key = key_of(val[g][e]);
+                        const bool in = (uint32_t)(begun + e) < (uint32_t)len && key - lowest <= width;
+                        a = in && ~key > a ? ~key : a;
+                        b = in && key > b ? key : b;
+                    }
+                }
             }
+            note_range(a, b, range);
+            __syncthreads();
+            least = ~range[0];
+            largest = range[1];
+            between();
         }
-        __syncthreads();
-        find_bucket(hist, k_rem, wave_tot, found);
+    }
+    while ((uint32_t)k - k_rem + in_bin > limit && width != 0u) {
+        const int shift = next_shift(width);
+        if (!second) {
+            // (its bins begin at the first bin's lowest key)
+            if (least == largest) {
+                between();
+                break;
+            }
+            bucket_of_pass<1>(ghist1, 1, n_seg, s, k_rem, hist, wave_tot, found);
+            second = true;
+        } else {
+            for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+            __syncthreads();
+            if (lists_whole) {
+                for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
+                    const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
+                    const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
+                    for (uint32_t e = 0; e < cnt; e += kWave) {
+                        const uint32_t key = e + lane < cnt ? (uint32_t)(from[e + lane] >> 32) : 0u;
+                        light_hist_add(hist, (key - lowest) >> shift, key != 0u && key - lowest <= width);
+                    }
+                }
+            } else {
+#pragma unroll 1
+                for (int row = 0; row < len; row += kRow) {
+                    float again[kBigPer];
+                    load_sweep(seg_score, row, len, again);
+#pragma unroll
+                    for (int j = 0; j < kBigPer; ++j) {
+                        const uint32_t key = sweep_index(row, j) < len ? key_of(again[j]) : 0u;
+                        light_hist_add(hist, (key - lowest) >> shift, key != 0u && key - lowest <= width);
+                    }
+                }
+            }
+            __syncthreads();
+            find_bucket(hist, k_rem, wave_tot, found);
+        }
         lowest += found[0] << shift;
         width = (1u << shift) - 1u;
         k_rem = found[1];
         in_bin = found[2];
+        between();
         __syncthreads();
     }
     // entries at or above `lowest` are collected; if the ties alone are too many, those above it
-    const bool ties_apart = (uint32_t)k - k_rem + in_bin > (uint32_t)kPickCap;
-    const int n = (int)(ties_apart ? (uint32_t)k - k_rem : (uint32_t)k - k_rem + in_bin);
-    const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
-    bool from_lists = false;
+    bool ties_apart = (uint32_t)k - k_rem + in_bin > limit;
+    int n = (int)(ties_apart ? (uint32_t)k - k_rem : (uint32_t)k - k_rem + in_bin);
+    uint64_t tie_lists = ~0ull;   // the lists whose ties are collected
     if constexpr (LISTS) {
-        // (every wavefront holds the counts: at most 33 lists)
-        from_lists = whole && !ties_apart && __ballot(my_count > (uint32_t)kListCap) == 0ull;
-        if (from_lists) {
-            const uint32_t upto = wave_inclusive_sum(my_count);
-            for (int l = wave; l < n_lists; l += kBigThreads / kWave) {   // a wavefront copies whole lists
-                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l), at = (uint32_t)__builtin_amdgcn_readlane((int)upto, l) - cnt;
+        // Whole lists hold the ties as well, and lie in index order: those up to the one in which the k_rem-th tie lies are
+        // ranked with the rest, at most one list's more than k.
+        static_assert(kPickCap >= PRUNER_MAX_K + kListCap, "k and a list more fit");
+        if (ties_apart && lists_whole) {
+            for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
+                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
                 const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
-                for (uint32_t e = lane; e < cnt; e += kWave)
-                    if (at + e < (uint32_t)n) sel[slot(at + e)] = from[e];
+                uint32_t ties = 0;
+                for (uint32_t e = 0; e < cnt; e += kWave) ties += (uint32_t)__popcll(__ballot(e + lane < cnt && (uint32_t)(from[e + lane] >> 32) == lowest));
+                if (lane == 0) hist[l] = ties;
             }
-        } else {
+            __syncthreads();
+            const uint32_t upto = wave_inclusive_sum(lane < n_lists ? hist[lane] : 0u);
+            const int enough = __popcll(__ballot(upto < k_rem));   // the list of the k_rem-th tie
+            n += __builtin_amdgcn_readlane((int)upto, enough);
+            tie_lists = (2ull << enough) - 1ull;
+            ties_apart = false;
+            __syncthreads();
+        }
+    }
+    const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
+    if constexpr (LISTS) {
+        if (lists_whole) {
+            for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
+                const uint32_t from_key = (tie_lists >> l) & 1ull ? lowest : lowest + 1u;
+                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
+                const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
+                for (uint32_t e = 0; e < cnt; e += kWave) {
+                    const uint64_t w = e + lane < cnt ? from[e + lane] : 0ull;
+                    const unsigned long long in = __ballot((uint32_t)(w >> 32) >= from_key && w != 0ull);
+                    if (in == 0ull) continue;
+                    const int leader = __ffsll(in) - 1;
+                    uint32_t base = 0;
+                    if (lane == leader) base = atomicAdd(&fill, (uint32_t)__popcll(in));
+                    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(in & ((1ull << lane) - 1ull));
+                    if (((in >> lane) & 1ull) && at < (uint32_t)n) sel[slot(at)] = w;
+                }
+            }
+        } else if (n > 0) {
 #pragma unroll 1
             for (int row = 0; row < len; row += kRow) {
                 float again[kBigPer];
@@ -1064,7 +1193,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
         if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
     __syncthreads();
-    if (!from_lists) {
+    if (!lists_whole) {
         for (int e = threadIdx.x; e < n; e += kBigThreads) {
             const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
             sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
@@ -1184,7 +1313,7 @@ static int topk_check(const int64_t* seg_off, int32_t n_sg, int32_t k, int64_t* 
 }
 
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t st, TopkCtx* ctx,
-                 Upload* defer, bool with_block_max, uint32_t window, bool copies)
+                 Upload* defer, bool with_block_max, bool copies)
 {
     int64_t longest = 0;
     const int bad = topk_check(seg_off, n_sg, k, &longest);
@@ -1213,7 +1342,6 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     ctx->pick = pick;
     // (a population of copies, as the explorer loop keeps it, would have its lists overflow as a rule: it takes the spans route)
     ctx->lists = !tiny && !pick && longest <= kListsMax && !copies;
-    ctx->window = window;
     ctx->n_sg = n_sg;
     ctx->k = k;
     ctx->n = n;
@@ -1248,7 +1376,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     if ((size_t)blocks > L.stage_slots) return PRUNER_EWORKSPACE;   // cannot happen: spans are sized for at most that many
     // segment table, and histograms cleared, in one launch
     const size_t per_pass = (size_t)n_sg * kBins;
-    const size_t hist_bytes = ((size_t)L.R + (pick || ctx->lists ? 0 : 2)) * per_pass * sizeof(uint32_t);
+    const size_t hist_bytes = ((size_t)L.R + (pick ? 0 : 2)) * per_pass * sizeof(uint32_t);
     if (defer) {
         defer->bytes.assign(reinterpret_cast<const char*>(segs), reinterpret_cast<const char*>(segs + n_sg));
         defer->dst = d_segs;
@@ -1289,7 +1417,7 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     // (the draft kernel writes the block maxima when it counts the first digit)
     uint32_t* const block_max = ctx.d_block_max;
     if (!have_first_digit) {
-        hipLaunchKernelGGL(hist0_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, hist0, block_max);
+        hipLaunchKernelGGL(hist0_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, hist0, block_max);
         PRUNER_LAUNCH_CHECK();
     }
     // the ranking of a segment's k rows is shared out over up to k / 32 workgroups, as long as the launch is one
@@ -1301,19 +1429,19 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     if (ctx.pick || ctx.lists) {
         const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
         if (ctx.lists) {
-            hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, k, hist0, d_stage);
+            hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, hist2, d_stage);
             PRUNER_LAUNCH_CHECK();
-            hipLaunchKernelGGL(pick_kernel<true>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, ctx.window, k, share, hist0, d_stage,
+            hipLaunchKernelGGL(pick_kernel<true>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         } else {
-            hipLaunchKernelGGL(pick_kernel<false>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, ctx.window, k, share, hist0, d_stage,
+            hipLaunchKernelGGL(pick_kernel<false>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         }
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }
-    if (block_max) hipLaunchKernelGGL(funnel_kernel<true>, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, k, hist0, hist1, d_state, d_stage, block_max);
-    else hipLaunchKernelGGL(funnel_kernel<false>, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, ctx.window, k, hist0, hist1, d_state, d_stage, block_max);
+    if (block_max) hipLaunchKernelGGL(funnel_kernel<true>, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, d_state, d_stage, block_max);
+    else hipLaunchKernelGGL(funnel_kernel<false>, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, d_state, d_stage, block_max);
     PRUNER_LAUNCH_CHECK();
     hipLaunchKernelGGL(refine_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, hist1, hist2, d_state, d_stage);
     PRUNER_LAUNCH_CHECK();
@@ -1336,7 +1464,7 @@ extern "C" int pruner_topk(const float* score, const int64_t* seg_off, int32_t n
     if (!aligned(score, 4) || !aligned(idx_out, 4) || (val_out && !aligned(val_out, 4))) return PRUNER_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     TopkCtx ctx;
-    const int rc = topk_prepare(seg_off, n_sg, k, workspace, workspace_bytes, st, &ctx, nullptr, true, kScoreWindow, false);
+    const int rc = topk_prepare(seg_off, n_sg, k, workspace, workspace_bytes, st, &ctx, nullptr, true, false);
     if (rc) return rc;
     return topk_finish(ctx, score, seg_off, idx_out, val_out, false, st);
 }
@@ -1374,7 +1502,7 @@ extern "C" int pruner_topk_static(const float* score, const int64_t* seg_off, in
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
     TopkCtx ctx;
-    const int rc = topk_prepare(seg_off, n_sg, k, g_scratch_ptr[dev], kStaticScratchBytes, st, &ctx, nullptr, false, kScoreWindow, false);
+    const int rc = topk_prepare(seg_off, n_sg, k, g_scratch_ptr[dev], kStaticScratchBytes, st, &ctx, nullptr, false, false);
     if (rc) return rc;
     return topk_finish(ctx, score, seg_off, idx_out, val_out, false, st);
 }

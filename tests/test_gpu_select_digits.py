@@ -49,18 +49,22 @@ def values(kind, n, rng):
     if kind == "two values":
         return np.where(rng.random(n) < 0.3, np.float32(-0.25), np.float32(-0.75)).astype(np.float32)
     if kind == "window edges":         # the powers of two where bins change width, and their neighbours
-        e = np.exp2(np.array([-24, -23, -22, -10, -11, -7, -6, -5, 6, 7, 8], np.float64))
+        e = np.exp2(np.array([-24, -23, -22, -10, -11, -7, -6, -5, 6, 7, 8, 10, 11, 12], np.float64))
         y = (rng.choice(e, n) * rng.choice([1, -1], n)).astype(np.float32)
         return np.nextafter(y, np.float32(rng.choice([-1, 1]) * 1e30)).astype(np.float32) if rng.random() < 0.5 else y
+    if kind == "300 values":           # every value shared by a few hundred to a few thousand
+        return (-1.0 - rng.integers(0, 300, n) / 8).astype(np.float32)
+    if kind == "one value a bin":      # ties that fill a bin, others in the bins beside it
+        return np.where(rng.random(n) < 0.05, np.float32(2.0), (0.5 * x).astype(np.float32)).astype(np.float32)
     return np.full(n, np.float32(-3.5))
 
 
-KINDS = ["normal", "latencies", "every exponent", "tiny", "huge", "zeros", "one bin", "two values", "window edges", "equal"]
+KINDS = ["normal", "latencies", "every exponent", "tiny", "huge", "zeros", "one bin", "two values", "window edges", "300 values", "one value a bin", "equal"]
 
 
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("lens,ks", [([8193], [1, 64, 65, 4096]), ([16383, 16384, 16385, 70], [1, 33, 70]), ([65536], [1, 512, 4096]), ([65535, 5, 32769], [5]),
-                                     ([65537], [1, 31, 4096]), ([300001], [100, 4096]), ([50001] * 7, [512])])
+                                     ([65537], [1, 31, 4096]), ([300001], [100, 4096]), ([50001] * 7, [512]), ([333333] * 3, [33, 512]), ([524288, 524287], [4096])])
 def test_routes_and_values(P, kind, lens, ks):
     rng = np.random.default_rng(sum(lens) + len(kind))
     seg = np.concatenate([[0], np.cumsum(lens)])
