@@ -2,15 +2,13 @@
 //   n_steps times { costs = C_SA(S_x);  S_spec = PriorFilter(S_x U S_spec);  S_x = SchMutation(S_x, costs) }.
 //
 // C_SA and the k best of S_x are the launches of pruner_prior_filter.  The rest of a step:
-//   lse_keys    one thread per entry of the union: score key and schedule hash (the k best sit at random places of
-//               the population; many workgroups share those reads)
-//   lse_merge   one workgroup per subgraph: the union of S_spec and the k best of S_x as a union of SETS (a schedule
-//               counts once; identity = score and a 64-bit hash of the tile factors): the order is (score descending,
-//               hash ascending, position ascending); the k best of S_x are sorted in LDS, S_spec is in that order
-//               already, the two are merged by bisection; copies of a predecessor are dropped, the first k of the
-//               rest are the new S_spec
-//   lse_copy    the tile factors of the new S_spec, from the old S_spec or from the population; also as one 64-byte
-//               record per schedule, from which the mutation reads its parents
+//   lse_keys    sixteen lanes per schedule: the records, score keys and schedule hashes of the k best (they sit at random
+//               places of the population)
+//   lse_rank    every entry's place in the union of S_spec and the k best: the order is (score descending, hash ascending,
+//               position ascending); S_spec is in that order already, the k best in runs, places are found by bisection
+//   lse_unite   the union as a union of SETS (a schedule counts once; identity = score and a 64-bit hash of the tile
+//               factors): copies of a predecessor are dropped, the first k of the rest are the new S_spec; one 64-byte record
+//               per schedule, from which the mutation reads its parents
 //   lse_mutate  one thread per child: a parent drawn uniformly from S_spec (truncation selection: the paper names a
 //               genetic algorithm guided by the draft fitness and gives no operator), and with the given probability
 //               one prime factor of one tile factor moved to another level of the same axis, fragment multiples kept
@@ -44,19 +42,6 @@ __device__ __forceinline__ uint64_t splitmix64_draw(uint64_t seed, uint64_t c)
     return z ^ (z >> 31);
 }
 
-// identity of a schedule: its own tile slots, in slot order (all slots are requested before the first is hashed)
-__device__ __forceinline__ uint64_t schedule_hash(const uint16_t* __restrict__ col, int64_t stride, int n_slots)
-{
-    uint16_t f[PRUNER_MAX_SLOTS];
-#pragma unroll
-    for (int r = 0; r < PRUNER_MAX_SLOTS; ++r) f[r] = r < n_slots ? col[r * stride] : (uint16_t)0;
-    uint64_t h = (uint64_t)n_slots;
-#pragma unroll
-    for (int r = 0; r < PRUNER_MAX_SLOTS; ++r)
-        if (r < n_slots) h = splitmix64_draw(h, (uint64_t)f[r] + 1);
-    return h;
-}
-
 __device__ __forceinline__ uint32_t lse_key_of(float x)   // larger score <=> larger key; -0 and +0 share a key
 {
     uint32_t u = __float_as_uint(x);
@@ -65,231 +50,7 @@ __device__ __forceinline__ uint32_t lse_key_of(float x)   // larger score <=> la
 }
 __device__ __forceinline__ float lse_score_of(uint32_t key) { return __uint_as_float((key & 0x80000000u) ? (key & 0x7FFFFFFFu) : ~key); }
 
-constexpr int32_t kNoSource = (int32_t)0x80000000;
-
-// Entry e of the sort arrays sits at pad(e): one spare entry after every 32, so that threads that walk groups of 8
-// neighbouring entries do not all land in the same LDS banks.
-__device__ __forceinline__ int pad(int e) { return e + (e >> 5); }
-constexpr int padded(int n) { return n + (n >> 5) + 2; }
-
-// 2^LOG entries base + i*s of a bitonic merge of `size`: the strides 2^(LOG-1) s ... s permute them among themselves,
-// and they lie in one half of the merge, so they share the direction.
-template <int LOG> __device__ __forceinline__ void sort_group(uint64_t* hi, uint64_t* lo, int g, int s, int size)
-{
-    constexpr int N = 1 << LOG;
-    const int base = (g / s) * (N * s) + (g % s);
-    const bool down = (base & size) == 0;
-    uint64_t xh[N], xl[N];
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        xh[i] = hi[pad(base + i * s)];
-        xl[i] = lo[pad(base + i * s)];
-    }
-#pragma unroll
-    for (int h = N >> 1; h > 0; h >>= 1) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            if ((i & h) == 0) {
-                const uint64_t ah = xh[i], al = xl[i], bh = xh[i + h], bl = xl[i + h];
-                const bool a_less = ah < bh || (ah == bh && al < bl);
-                const bool swap = a_less == down;
-                xh[i] = swap ? bh : ah;
-                xl[i] = swap ? bl : al;
-                xh[i + h] = swap ? ah : bh;
-                xl[i + h] = swap ? al : bl;
-            }
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-        hi[pad(base + i * s)] = xh[i];
-        lo[pad(base + i * s)] = xl[i];
-    }
-}
-
-// The sort keys of the union's P entries per subgraph (old S_spec first, then the k best of S_x, then padding), one
-// thread per entry: hi = score key << 32 | upper half of ~hash, lo = lower half of ~hash << 32 | ~position.  The
-// schedules of the k best sit at random places of the population: many workgroups share those reads.
-// (One wavefront per workgroup: the reads are random single elements of a population far larger than the caches, and
-// what bounds them is how many misses a compute unit keeps in flight; the launch therefore spreads over all units.)
-constexpr int kKeysThreads = 64;
-__global__ void __launch_bounds__(kKeysThreads) lse_keys_kernel(const LseSeg* __restrict__ segs, int k, int P, const uint16_t* __restrict__ tiles,
-                                                       int64_t pitch, const int32_t* __restrict__ best_idx, const float* __restrict__ best_val,
-                                                       const uint16_t* __restrict__ old_tiles, const float* __restrict__ old_score,
-                                                       const int32_t* __restrict__ old_count, int64_t spec_pitch,
-                                                       uint64_t* __restrict__ key_hi, uint64_t* __restrict__ key_lo)
-{
-    const int s = blockIdx.y;
-    const int i = blockIdx.x * kKeysThreads + threadIdx.x;
-    if (i >= P) return;
-    const int n_slots = segs[s].n_slots;
-    const int64_t col0 = (int64_t)s * k;
-    const int n_old = old_count[s] < 0 ? 0 : old_count[s] > k ? k : old_count[s];
-    uint64_t h = 0, l = 0;   // padding sorts last: every real entry has a non-zero key
-    if (i < n_old + k) {
-        float sc;
-        uint64_t hash;
-        if (i < n_old) {
-            sc = old_score[col0 + i];
-            hash = schedule_hash(old_tiles + col0 + i, spec_pitch, n_slots);
-        } else {
-            const int r = i - n_old;
-            sc = best_val[col0 + r];
-            hash = schedule_hash(tiles + best_idx[col0 + r], pitch, n_slots);
-        }
-        const uint64_t inv = ~hash;
-        h = ((uint64_t)lse_key_of(sc) << 32) | (inv >> 32);
-        l = (inv << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)i);
-    }
-    key_hi[(int64_t)s * P + i] = h;
-    key_lo[(int64_t)s * P + i] = l;
-}
-
-// One workgroup per subgraph.  The old S_spec arrives in order (it is an earlier call's output: keys strictly
-// descending), so only the k best of S_x are sorted (Pn = 2^m >= k entries, padding last), and the union's order is
-// a merge: an entry's place is its place in its own list plus the number of entries of the other list that precede
-// it, found by bisection.  Dynamic LDS: the old keys (2 x k words), the new ones (2 x padded(Pn) words), and which
-// entry holds each place of the union (2 k half-words).  P is the stride of the key arrays.
 __device__ __forceinline__ bool key_greater(uint64_t ah, uint64_t al, uint64_t bh, uint64_t bl) { return ah > bh || (ah == bh && al > bl); }
-
-__global__ void __launch_bounds__(kLseThreads) lse_merge_kernel(int k, int P, int Pn, const uint64_t* __restrict__ key_hi,
-                                                                const uint64_t* __restrict__ key_lo, const int32_t* __restrict__ best_idx,
-                                                                const int32_t* __restrict__ old_count, float* __restrict__ new_score,
-                                                                int32_t* __restrict__ new_count, int32_t* __restrict__ source)
-{
-    extern __shared__ uint64_t words[];
-    uint64_t* oh = words;
-    uint64_t* ol = oh + k;
-    uint64_t* hi = ol + k;
-    uint64_t* lo = hi + padded(Pn);
-    uint16_t* who = reinterpret_cast<uint16_t*>(lo + padded(Pn));
-    __shared__ uint32_t wave_tot[kLseThreads / kWave];
-    const int s = blockIdx.x;
-    const int64_t col0 = (int64_t)s * k;
-    const int n_old = old_count[s] < 0 ? 0 : old_count[s] > k ? k : old_count[s];
-    const int m = n_old + k;
-    for (int i = threadIdx.x; i < n_old; i += kLseThreads) {
-        oh[i] = key_hi[(int64_t)s * P + i];
-        ol[i] = key_lo[(int64_t)s * P + i];
-    }
-    for (int i = threadIdx.x; i < Pn; i += kLseThreads) {
-        hi[pad(i)] = i < k ? key_hi[(int64_t)s * P + n_old + i] : 0ull;   // padding sorts last: every real entry has a non-zero key
-        lo[pad(i)] = i < k ? key_lo[(int64_t)s * P + n_old + i] : 0ull;
-    }
-    // bitonic sort, largest (hi, lo) first; one round trip through LDS performs up to three consecutive strides
-    // (a thread takes the 8, 4 or 2 entries those strides permute among themselves and exchanges them in registers)
-    for (int size = 2; size <= Pn; size <<= 1) {
-        int stride = size >> 1;
-        while (stride > 0) {
-            __syncthreads();
-            if (stride >= 4) {
-                const int st = stride >> 2;
-                for (int g = threadIdx.x; g < (Pn >> 3); g += kLseThreads) sort_group<3>(hi, lo, g, st, size);
-                stride >>= 3;
-            } else if (stride == 2) {
-                for (int g = threadIdx.x; g < (Pn >> 2); g += kLseThreads) sort_group<2>(hi, lo, g, 1, size);
-                stride = 0;
-            } else {
-                for (int g = threadIdx.x; g < (Pn >> 1); g += kLseThreads) sort_group<1>(hi, lo, g, 1, size);
-                stride = 0;
-            }
-        }
-    }
-    __syncthreads();
-    // places in the union (all 128-bit keys differ: they carry the position)
-    for (int i = threadIdx.x; i < m; i += kLseThreads) {
-        const bool is_old = i < n_old;
-        const int j = is_old ? i : i - n_old;
-        const uint64_t xh = is_old ? oh[j] : hi[pad(j)], xl = is_old ? ol[j] : lo[pad(j)];
-        int a = 0, e = is_old ? k : n_old;   // entries of the other list that are greater
-        while (a < e) {
-            const int mid = (a + e) >> 1;
-            const bool g = is_old ? key_greater(hi[pad(mid)], lo[pad(mid)], xh, xl) : key_greater(oh[mid], ol[mid], xh, xl);
-            if (g) a = mid + 1; else e = mid;
-        }
-        who[j + a] = (uint16_t)(is_old ? j : k + j);
-    }
-    __syncthreads();
-    // a copy has the key and the hash of its predecessor; number the rest.  A thread takes kPer neighbouring places, so
-    // that one scan over the workgroup numbers a whole sweep of kPer * kLseThreads places (all 2 k of them as a rule).
-    constexpr int kPer = 8;
-    uint32_t carry = 0;
-    for (int base = 0; base < m; base += kPer * kLseThreads) {
-        const int first = base + (int)threadIdx.x * kPer;
-        uint64_t mh[kPer], ml[kPer];
-        uint32_t keep = 0;   // bit j: place first + j stays
-        uint64_t ph = 0, pl = 0;
-        if (first > 0 && first < m) {
-            const int pid = who[first - 1];
-            ph = pid < k ? oh[pid] : hi[pad(pid - k)];
-            pl = pid < k ? ol[pid] : lo[pad(pid - k)];
-        }
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            mh[j] = ml[j] = 0;
-            if (first + j < m) {
-                const int id = who[first + j];
-                mh[j] = id < k ? oh[id] : hi[pad(id - k)];
-                ml[j] = id < k ? ol[id] : lo[pad(id - k)];
-                const bool same = first + j > 0 && mh[j] == ph && (ml[j] >> 32) == (pl >> 32);
-                keep |= same ? 0u : 1u << j;
-                ph = mh[j], pl = ml[j];
-            }
-        }
-        // exclusive scan of the kept counts over the workgroup
-        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-        const uint32_t mine = (uint32_t)__popc(keep);
-        const uint32_t incl = wave_inclusive_sum(mine);
-        __syncthreads();
-        if (lane == kWave - 1) wave_tot[wave] = incl;
-        __syncthreads();
-        uint32_t before = 0, all = 0;
-        for (int w2 = 0; w2 < kLseThreads / kWave; ++w2) {
-            const uint32_t t = wave_tot[w2];
-            before += w2 < wave ? t : 0u;
-            all += t;
-        }
-        uint32_t rank = carry + before + incl - mine;
-#pragma unroll
-        for (int j = 0; j < kPer; ++j) {
-            if ((keep >> j) & 1u) {
-                if (rank < (uint32_t)k) {
-                    const uint32_t pos = 0xFFFFFFFFu - (uint32_t)ml[j];
-                    new_score[col0 + rank] = lse_score_of((uint32_t)(mh[j] >> 32));
-                    source[col0 + rank] = pos < (uint32_t)n_old ? -1 - (int32_t)pos : best_idx[col0 + (pos - n_old)];
-                }
-                ++rank;
-            }
-        }
-        carry += all;
-    }
-    const uint32_t count = carry < (uint32_t)k ? carry : (uint32_t)k;
-    for (int r = count + threadIdx.x; r < k; r += kLseThreads) {
-        new_score[col0 + r] = -__builtin_inff();
-        source[col0 + r] = kNoSource;
-    }
-    if (threadIdx.x == 0) new_count[s] = (int32_t)count;
-}
-
-// ---- short segments: selection and PriorFilter in one launch -----------------------------------------------------------
-// One workgroup of 1024 threads per subgraph; thread t holds entries t, t + 1024, ... of the segment as keys.
-//   1. the key of rank k: histograms of 2048 bins over the range the keys span, then over the range of the bin that holds
-//      rank k, and so on until that bin holds exactly what is still to take, or few entries (then ranked by counting), or one
-//      key value only (then its first entries in index order are taken).  Keys are ordered like logarithms: a bin of the
-//      first pass is a fraction of a per cent to a few per cent of a score;
-//   2. the chosen entries' schedules (one per thread; from the second step on the draft kernels leave the children as records
-//      too, a record being one or two requests where a column's rows are one each), their hashes, and their order by (score,
-//      hash, age): every wavefront sorts its 64 in registers, and neighbouring runs are merged, an entry's place being its
-//      place in its run plus, by bisection, the greater ones in the other;
-//   3. the union with the old S_spec, whose keys come in order from the step before, as in lse_merge; every thread then
-//      writes the record it holds to the record's new place.
-// Bound: the latency of these dependent stages (a compute unit works alone on a subgraph).  8,000 entries, k = 512: 23 us
-// where selection (26), keys (9), merge (18) and copy (7) took 60 in four launches.
-
-constexpr int kShortPer = 32;
-constexpr int kShortMax = kLseThreads * kShortPer;   // entries of a segment
-constexpr int kShortK = 1024;                        // S_spec: one old and one new member per thread
-constexpr int kShortBin = 256;                       // entries of rank k's bin that are ranked by counting instead of split further
 
 __device__ __forceinline__ void wave_sort_descending(uint64_t& hi, uint64_t& lo)   // the wavefront's 64 pairs over its lanes, largest first
 {
@@ -313,19 +74,246 @@ __device__ __forceinline__ void wave_sort_descending(uint64_t& hi, uint64_t& lo)
     }
 }
 
-// S_spec between the steps of the short route: its keys in order and its records, by subgraph
-struct ShortSpec {
+// S_spec between the steps: its sort keys in order and its records, by subgraph.  A sort key is 128 bits, larger first:
+// hi = score key << 32 | upper half of ~hash, lo = lower half of ~hash << 32 | ~position in the union.
+struct Spec {
     uint64_t *hi, *lo;   // [n_sg][k]
     uint4* aos;          // [n_sg][k][kAosSlots / 8]
     int32_t* count;      // [n_sg]
 };
+
+__device__ __forceinline__ int spec_members(const int32_t* count, int s, int k)
+{
+    const int n = count[s];
+    return n < 0 ? 0 : n > k ? k : n;
+}
+
+// ---- PriorFilter over the union of S_spec and the k best, for segments of any length: lse_keys, lse_rank, lse_unite ------
+// Three launches over the whole device instead of a sort by one workgroup per subgraph.  21 million programs in one segment,
+// k = 4096, a step: 11 + 7 + 6 us, where keys, sort and copies took 22 + 53 + 10.
+
+// The records and sort keys of the k best of S_x, 64 per workgroup, which leaves their keys in order.  The schedules sit at
+// random places of the population, two bytes a row: sixteen lanes per schedule, so that all misses are under way at once.
+constexpr int kRun = kWave;   // neighbours of the k best whose keys are in order
+__global__ void __launch_bounds__(kLseThreads) lse_keys_kernel(const LseSeg* __restrict__ segs, int k, bool first, const int32_t* __restrict__ old_count,
+                                                               const uint16_t* __restrict__ tiles, int64_t pitch,
+                                                               const int32_t* __restrict__ best_idx, const float* __restrict__ best_val,
+                                                               uint64_t* __restrict__ fresh_hi, uint64_t* __restrict__ fresh_lo,
+                                                               uint32_t* __restrict__ fresh_aos)
+{
+    static_assert(kLseThreads == kRun * kAosWords, "a thread takes two slots of a schedule");
+    __shared__ uint32_t record[kRun][kAosWords + 1];
+    const int s = blockIdx.y, c = threadIdx.x / kAosWords, w = threadIdx.x % kAosWords;
+    const int n_slots = segs[s].n_slots;
+    const int64_t col0 = (int64_t)s * k;
+    const int r = blockIdx.x * kRun + c;
+    uint32_t word = 0;
+    if (r < k) {
+        const uint16_t* col = tiles + best_idx[col0 + r];
+        const uint32_t low = 2 * w < n_slots ? col[(int64_t)(2 * w) * pitch] : 0u, high = 2 * w + 1 < n_slots ? col[(int64_t)(2 * w + 1) * pitch] : 0u;
+        word = low | high << 16;
+        fresh_aos[(col0 + r) * kAosWords + w] = word;
+    }
+    record[c][w] = word;
+    __syncthreads();
+    if (threadIdx.x >= kRun) return;
+    const int mine = blockIdx.x * kRun + (int)threadIdx.x;
+    uint64_t hi = 0, lo = 0;   // padding sorts last: every real entry has a key above 0
+    if (mine < k) {
+        uint64_t h = (uint64_t)n_slots;   // identity of a schedule: its own tile slots, in slot order
+        for (int row = 0; row < n_slots; ++row) {
+            const uint32_t pair = record[threadIdx.x][row >> 1];
+            h = splitmix64_draw(h, (uint64_t)(row & 1 ? pair >> 16 : pair & 0xFFFFu) + 1);
+        }
+        const uint64_t inv = ~h;
+        const uint32_t position = (uint32_t)((first ? 0 : spec_members(old_count, s, k)) + mine);
+        hi = ((uint64_t)lse_key_of(best_val[col0 + mine]) << 32) | (inv >> 32);
+        lo = (inv << 32) | (uint64_t)(0xFFFFFFFFu - position);
+    }
+    wave_sort_descending(hi, lo);
+    if (mine < k) {
+        fresh_hi[col0 + mine] = hi;
+        fresh_lo[col0 + mine] = lo;
+    }
+}
+
+// How many of the SIZE (a power of two) keys in descending order at hi, lo are above each of xh, xl.
+template <int SIZE> __device__ __forceinline__ uint32_t count_above(const uint64_t* hi, const uint64_t* lo, uint64_t xh, uint64_t xl)
+{
+    uint32_t n = 0;
+#pragma unroll
+    for (int step = SIZE / 2; step > 0; step >>= 1) n += key_greater(hi[n + step - 1], lo[n + step - 1], xh, xl) ? (uint32_t)step : 0u;
+    return n + (key_greater(hi[n], lo[n], xh, xl) ? 1u : 0u);
+}
+
+// Every entry's place in the union's order: 64 entries of one list per workgroup, one to a lane of each wavefront.  S_spec is
+// in that order already, the k best are in runs of 64: a place is the number of greater entries in each run and, for one of the
+// k best, in S_spec, found by bisection, the runs and the windows of S_spec shared out over the wavefronts.  (Comparing with
+// every entry of the same score instead took 12 us without shared scores, 41 us with the many that later steps have.)
+// Dynamic LDS: both lists' keys.
+constexpr int kOldWindow = 256;
+__host__ __device__ constexpr int rank_words(int k) { return (k + kRun - 1) / kRun * kRun + (k + kOldWindow - 1) / kOldWindow * kOldWindow; }
+__global__ void __launch_bounds__(kLseThreads) lse_rank_kernel(int k, bool first, Spec before, const uint64_t* __restrict__ fresh_hi,
+                                                               const uint64_t* __restrict__ fresh_lo, uint64_t* __restrict__ union_hi,
+                                                               uint64_t* __restrict__ union_lo)
+{
+    constexpr int kWaves = kLseThreads / kWave, kRuns = PRUNER_MAX_K / kRun / kWaves;   // runs per wavefront, at most
+    static_assert(PRUNER_MAX_K <= kWaves * kOldWindow, "a window of S_spec per wavefront");
+    extern __shared__ uint64_t words[];
+    __shared__ uint32_t place[kWave];
+    const int s = blockIdx.y, lane = lane_id(), wave = threadIdx.x >> 6, runs = (k + kRun - 1) / kRun;
+    const int64_t col0 = (int64_t)s * k;
+    const int n_old = first ? 0 : spec_members(before.count, s, k);
+    const bool old_side = (int)blockIdx.x < runs;
+    const int base = ((int)blockIdx.x - (old_side ? 0 : runs)) * kRun;
+    const int left = (old_side ? n_old : k) - base, n_mine = left < kRun ? left : kRun;
+    if (n_mine <= 0) return;
+    const int n_fresh = runs * kRun, n_window = old_side ? 0 : (n_old + kOldWindow - 1) / kOldWindow * kOldWindow;
+    uint64_t *hi = words, *lo = hi + n_fresh, *oh = lo + n_fresh, *ol = oh + n_window;
+    for (int i = threadIdx.x; i < n_fresh; i += kLseThreads) {
+        hi[i] = i < k ? fresh_hi[col0 + i] : 0ull;
+        lo[i] = i < k ? fresh_lo[col0 + i] : 0ull;
+    }
+    for (int i = threadIdx.x; i < n_window; i += kLseThreads) {
+        oh[i] = i < n_old ? before.hi[col0 + i] : 0ull;
+        ol[i] = i < n_old ? before.lo[col0 + i] : 0ull;
+    }
+    uint64_t my_hi = ~0ull, my_lo = ~0ull;
+    if (lane < n_mine) {
+        my_hi = (old_side ? before.hi : fresh_hi)[col0 + base + lane];
+        my_lo = (old_side ? before.lo : fresh_lo)[col0 + base + lane];
+    }
+    if (threadIdx.x < kWave) place[threadIdx.x] = old_side ? base + threadIdx.x : 0;
+    __syncthreads();
+    uint32_t above = 0;
+#pragma unroll
+    for (int j = 0; j < kRuns; ++j) {
+        const int run = j * kWaves + wave;
+        if (run < runs) above += count_above<kRun>(hi + run * kRun, lo + run * kRun, my_hi, my_lo);
+    }
+    if (wave * kOldWindow < n_window) above += count_above<kOldWindow>(oh + wave * kOldWindow, ol + wave * kOldWindow, my_hi, my_lo);
+    if (above) atomicAdd(&place[lane], above);
+    __syncthreads();
+    if ((int)threadIdx.x < n_mine) {
+        const uint32_t at = place[lane];
+        if (at < 2u * (uint32_t)k) {   // (all keys differ: they hold the position)
+            union_hi[2 * col0 + at] = my_hi;
+            union_lo[2 * col0 + at] = my_lo;
+        }
+    }
+}
+
+// The union as a set, 64 places per workgroup: an entry with the score and the hash of its predecessor is a copy; the others'
+// ranks are the number of such entries before them (every workgroup counts those before its own places itself: 128 KB at
+// most, against a launch more).  The first k are the new S_spec; the last step writes the caller's arrays as well.
+__global__ void __launch_bounds__(kLseThreads) lse_unite_kernel(int k, bool first, Spec before, const uint32_t* __restrict__ fresh_aos,
+                                                                const uint64_t* __restrict__ union_hi, const uint64_t* __restrict__ union_lo, Spec now,
+                                                                int64_t spec_pitch, int rows, uint16_t* __restrict__ spec_tiles /* or null */,
+                                                                float* __restrict__ spec_score, int32_t* __restrict__ spec_count)
+{
+    constexpr int kPer = 2 * PRUNER_MAX_K / kLseThreads;
+    static_assert(kLseThreads == kWave * kAosWords, "a thread copies one word");
+    __shared__ uint32_t before_mine, all_mine, from[kWave], to[kWave];
+    const int s = blockIdx.y, lane = lane_id(), base = (int)blockIdx.x * kWave;
+    const int64_t col0 = (int64_t)s * k;
+    const int n_old = first ? 0 : spec_members(before.count, s, k), m = n_old + k;
+    if (base >= m) return;
+    const uint64_t *uh = union_hi + 2 * col0, *ul = union_lo + 2 * col0;
+    uint64_t h[kPer], ph[kPer];
+    uint32_t l[kPer], pl[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int p = j * kLseThreads + (int)threadIdx.x;
+        h[j] = ph[j] = 0;
+        l[j] = pl[j] = 0;
+        if (p < base) {
+            const int q = p > 0 ? p - 1 : 0;
+            h[j] = uh[p];
+            l[j] = (uint32_t)(ul[p] >> 32);
+            ph[j] = uh[q];
+            pl[j] = (uint32_t)(ul[q] >> 32);
+        }
+    }
+    if (threadIdx.x == 0) before_mine = 0;
+    __syncthreads();
+    uint32_t kept = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int p = j * kLseThreads + (int)threadIdx.x;
+        kept += (uint32_t)__popcll(__ballot(p < base && (p == 0 || h[j] != ph[j] || l[j] != pl[j])));
+    }
+    if (lane == 0 && kept) atomicAdd(&before_mine, kept);
+    __syncthreads();
+    const uint32_t rank0 = before_mine;
+    const bool last_places = base + kWave >= m;
+    if (rank0 >= (uint32_t)k && !last_places) return;
+    if (threadIdx.x < kWave) {
+        const int p = base + lane;
+        const uint64_t mh = p < m ? uh[p] : 0ull, ml = p < m ? ul[p] : 0ull;
+        const bool keep = p < m && (p == 0 || mh != uh[p - 1] || (ml >> 32) != (ul[p - 1] >> 32));
+        const unsigned long long kept_lanes = __ballot(keep);
+        const uint32_t rank = rank0 + (uint32_t)__popcll(kept_lanes & ((1ull << lane) - 1ull));
+        const bool stays = keep && rank < (uint32_t)k;
+        to[lane] = stays ? rank : 0xFFFFFFFFu;
+        from[lane] = 0xFFFFFFFFu - (uint32_t)ml;
+        if (lane == 0) all_mine = (uint32_t)__popcll(kept_lanes);
+        if (stays) {
+            now.hi[col0 + rank] = mh;
+            now.lo[col0 + rank] = (ml & 0xFFFFFFFF00000000ull) | (uint64_t)(0xFFFFFFFFu - rank);
+            if (spec_tiles) spec_score[col0 + rank] = lse_score_of((uint32_t)(mh >> 32));
+        }
+    }
+    __syncthreads();
+    const int e = threadIdx.x / kAosWords, w = threadIdx.x % kAosWords;
+    if (to[e] != 0xFFFFFFFFu) {
+        const int pos = (int)from[e];
+        const uint32_t word = pos < n_old ? reinterpret_cast<const uint32_t*>(before.aos)[(col0 + pos) * kAosWords + w] : fresh_aos[(col0 + (pos - n_old)) * kAosWords + w];
+        const int64_t at = col0 + to[e];
+        reinterpret_cast<uint32_t*>(now.aos)[at * kAosWords + w] = word;
+        if (spec_tiles) {
+            if (2 * w < rows) spec_tiles[(int64_t)(2 * w) * spec_pitch + at] = (uint16_t)word;
+            if (2 * w + 1 < rows) spec_tiles[(int64_t)(2 * w + 1) * spec_pitch + at] = (uint16_t)(word >> 16);
+        }
+    }
+    if (last_places) {
+        const uint32_t total = rank0 + all_mine, count = total < (uint32_t)k ? total : (uint32_t)k;
+        if (threadIdx.x == 0) now.count[s] = (int32_t)count;
+        if (spec_tiles) {
+            if (threadIdx.x == 0) spec_count[s] = (int32_t)count;
+            for (int r = (int)count + (int)threadIdx.x; r < k; r += kLseThreads) {
+                spec_score[col0 + r] = -__builtin_inff();
+                for (int row = 0; row < rows; ++row) spec_tiles[(int64_t)row * spec_pitch + col0 + r] = 0;
+            }
+        }
+    }
+}
+
+// ---- short segments: selection and PriorFilter in one launch -----------------------------------------------------------
+// One workgroup of 1024 threads per subgraph; thread t holds entries t, t + 1024, ... of the segment as keys.
+//   1. the key of rank k: histograms of 2048 bins over the range the keys span, then over the range of the bin that holds
+//      rank k, and so on until that bin holds exactly what is still to take, or few entries (then ranked by counting), or one
+//      key value only (then its first entries in index order are taken).  Keys are ordered like logarithms: a bin of the
+//      first pass is a fraction of a per cent to a few per cent of a score;
+//   2. the chosen entries' schedules (one per thread; from the second step on the draft kernels leave the children as records
+//      too, a record being one or two requests where a column's rows are one each), their hashes, and their order by (score,
+//      hash, age): every wavefront sorts its 64 in registers, and neighbouring runs are merged, an entry's place being its
+//      place in its run plus, by bisection, the greater ones in the other;
+//   3. the union with the old S_spec, whose keys come in order from the step before, every place found by bisection; every thread then
+//      writes the record it holds to the record's new place.
+// Bound: the latency of these dependent stages (a compute unit works alone on a subgraph).  8,000 entries, k = 512: 23 us
+// where selection (26), keys (9), merge (18) and copy (7) took 60 in four launches.
+
+constexpr int kShortPer = 32;
+constexpr int kShortMax = kLseThreads * kShortPer;   // entries of a segment
+constexpr int kShortK = 1024;                        // S_spec: one old and one new member per thread
+constexpr int kShortBin = 256;                       // entries of rank k's bin that are ranked by counting instead of split further
 
 // PER: entries of a segment per thread (the longest segment decides).  first: there is no S_spec yet.  spec_tiles,
 // spec_score and spec_count are written when they are not null (the last step).
 template <int PER>
 __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* __restrict__ segs, int k, bool first, const float* __restrict__ score,
                                                                  const uint16_t* __restrict__ tiles, int64_t pitch,
-                                                                 const uint4* __restrict__ child_aos /* or null */, ShortSpec before, ShortSpec now,
+                                                                 const uint4* __restrict__ child_aos /* or null */, Spec before, Spec now,
                                                                  int64_t spec_pitch, int rows, uint16_t* __restrict__ spec_tiles,
                                                                  float* __restrict__ spec_score, int32_t* __restrict__ spec_count)
 {
@@ -647,33 +635,6 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
     }
 }
 
-// The tile factors of the new S_spec; rows a subgraph does not own and entries past the count are cleared.  A second
-// copy holds each schedule's factors side by side (32 x uint16 = 64 bytes): the mutation reads a parent from there
-// with four loads instead of one per factor.
-__global__ void __launch_bounds__(256) lse_copy_kernel(const LseSeg* __restrict__ segs, int n_sg, int k, int rows, const uint16_t* __restrict__ tiles,
-                                                       int64_t pitch, const uint16_t* __restrict__ old_tiles, int64_t spec_pitch,
-                                                       const int32_t* __restrict__ source, uint16_t* __restrict__ new_tiles,
-                                                       uint4* __restrict__ new_aos)
-{
-    const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (c >= (int64_t)n_sg * k) return;
-    const int s = (int)(c / k);
-    const int n_slots = segs[s].n_slots;
-    const int32_t src = source[c];
-    uint32_t packed[kAosSlots / 2];
-#pragma unroll
-    for (int i = 0; i < kAosSlots / 2; ++i) packed[i] = 0u;
-#pragma unroll
-    for (int row = 0; row < PRUNER_MAX_SLOTS; ++row) {
-        uint16_t v = 0;
-        if (row < n_slots && src != kNoSource) v = src < 0 ? old_tiles[row * spec_pitch + (int64_t)s * k + (-1 - src)] : tiles[row * pitch + src];
-        if (row < rows) new_tiles[row * spec_pitch + c] = v;
-        packed[row >> 1] |= (uint32_t)v << (16 * (row & 1));
-    }
-#pragma unroll
-    for (int q = 0; q < kAosSlots / 8; ++q) new_aos[c * (kAosSlots / 8) + q] = make_uint4(packed[4 * q], packed[4 * q + 1], packed[4 * q + 2], packed[4 * q + 3]);
-}
-
 // The segment of child j: the last one that begins at or before j (empty ones are skipped over).
 __device__ __forceinline__ int lse_segment_of(const LseSeg* __restrict__ segs, int n_sg, int64_t j)
 {
@@ -758,7 +719,7 @@ __global__ void __launch_bounds__(256) lse_mutate_kernel(const LseSeg* __restric
 }
 
 struct LseLayout {
-    size_t filter, table, best_idx, best_val, alt_tiles, alt_score, alt_count, zero_count, source, key_hi, key_lo, aos, aos_b, children, total;
+    size_t filter, table, best_idx, best_val, zero_count, alt_count, keys[2], fresh, fresh_aos, merged, aos, aos_b, children, total;
 };
 
 LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
@@ -775,23 +736,22 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
     L.table = take((size_t)n_sg * sizeof(LseSeg));
     L.best_idx = take(cols * sizeof(int32_t));
     L.best_val = take(cols * sizeof(float));
-    L.alt_tiles = take((size_t)rows * cols * sizeof(uint16_t));
-    L.alt_score = take(cols * sizeof(float));
-    L.alt_count = take((size_t)n_sg * sizeof(int32_t));
     L.zero_count = take((size_t)n_sg * sizeof(int32_t));
-    L.source = take(cols * sizeof(int32_t));
-    L.key_hi = take(4 * cols * sizeof(uint64_t));   // P < 4k entries per subgraph (2k rounded up to a power of two)
-    L.key_lo = take(4 * cols * sizeof(uint64_t));
+    L.alt_count = take((size_t)n_sg * sizeof(int32_t));
+    for (size_t& keys : L.keys) keys = take(2 * cols * sizeof(uint64_t));   // S_spec's, in turns
+    L.fresh = take(2 * cols * sizeof(uint64_t));                            // those of the k best
+    L.merged = take(4 * cols * sizeof(uint64_t));                           // the union's
+    L.fresh_aos = take(cols * kAosSlots * sizeof(uint16_t));
     L.aos = take(cols * kAosSlots * sizeof(uint16_t));
-    // the short route's records take turns, and so a population that may take it has its children as records
+    L.aos_b = take(cols * kAosSlots * sizeof(uint16_t));   // S_spec's records, in turns
+    // a population that may take the short route has its children as records
     const bool may_be_short = k <= kShortK && n <= (int64_t)n_sg * kShortMax;
-    L.aos_b = take((may_be_short ? cols : 0) * kAosSlots * sizeof(uint16_t));
     L.children = take((may_be_short ? (size_t)n : 0) * kAosSlots * sizeof(uint16_t));
     L.total = off;
     return L;
 }
 
-PerDeviceFlag g_merge_ready;   // the merge kernel's allowance of dynamic LDS has been raised
+PerDeviceFlag g_rank_ready;   // the rank kernel's allowance of dynamic LDS has been raised
 
 }  // namespace
 
@@ -839,33 +799,14 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
                           {frag ? sg[s].frag[0] : 0, frag ? sg[s].frag[1] : 0, frag ? sg[s].frag[2] : 0}, 0};
     }
 
-    int P = 2;
-    while (P < 2 * k) P <<= 1;
-    int Pn = 2;
-    while (Pn < k) Pn <<= 1;
-    const size_t merge_lds = (size_t)k * 16 + (size_t)padded(Pn) * 16 + (size_t)k * 4;
-    const int dev = current_device(nullptr);
-    if (dev < 0) return PRUNER_EHIP;
-    if (!g_merge_ready.get(dev)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&lse_merge_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(PRUNER_MAX_K * 20 + padded(PRUNER_MAX_K) * 16)) != hipSuccess)
-            return PRUNER_EHIP;
-        g_merge_ready.mark(dev);
-    }
-
     LseSeg* d_table = reinterpret_cast<LseSeg*>(ws + L.table);
     int32_t* best_idx = reinterpret_cast<int32_t*>(ws + L.best_idx);
     float* best_val = reinterpret_cast<float*>(ws + L.best_val);
-    int32_t* source = reinterpret_cast<int32_t*>(ws + L.source);
-    int32_t* zero_count = reinterpret_cast<int32_t*>(ws + L.zero_count);
-    uint64_t* key_hi = reinterpret_cast<uint64_t*>(ws + L.key_hi);
-    uint64_t* key_lo = reinterpret_cast<uint64_t*>(ws + L.key_lo);
-    uint4* aos = reinterpret_cast<uint4*>(ws + L.aos);
-    // S_spec alternates between the caller's arrays and the workspace's, ending in the caller's
-    uint16_t* spec_t[2] = {spec_tiles, reinterpret_cast<uint16_t*>(ws + L.alt_tiles)};
-    float* spec_s[2] = {spec_score, reinterpret_cast<float*>(ws + L.alt_score)};
-    int32_t* spec_n[2] = {spec_count, reinterpret_cast<int32_t*>(ws + L.alt_count)};
     const int64_t spec_pitch = (int64_t)n_sg * k;
+    auto words = [&](size_t at) { return reinterpret_cast<uint64_t*>(ws + at); };
+    // S_spec alternates between two sets of arrays; the last step writes the caller's as well
+    const Spec spec[2] = {Spec{words(L.keys[0]), words(L.keys[0]) + spec_pitch, reinterpret_cast<uint4*>(ws + L.aos), reinterpret_cast<int32_t*>(ws + L.zero_count)},
+                          Spec{words(L.keys[1]), words(L.keys[1]) + spec_pitch, reinterpret_cast<uint4*>(ws + L.aos_b), reinterpret_cast<int32_t*>(ws + L.alt_count)}};
 
     auto mutate = [&](int32_t t, const int32_t* count, const uint4* records) {   // SchMutation of step t, in place (parents come from S_spec, not from S_x)
         if (tiles_pitch % 4 == 0 && aligned(tiles, 8))
@@ -891,11 +832,8 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         pending.dst = d_table;
         rc = draft_upload(plan, draft_ws, st, &pending);
         if (rc) return rc;
-        uint64_t* const keys[2] = {key_hi, key_lo};
-        const ShortSpec spec[2] = {ShortSpec{keys[0], keys[0] + spec_pitch, aos, zero_count},
-                                   ShortSpec{keys[1], keys[1] + spec_pitch, reinterpret_cast<uint4*>(ws + L.aos_b), reinterpret_cast<int32_t*>(ws + L.alt_count)}};
         for (int32_t t = 0; t < n_steps; ++t) {
-            const ShortSpec &now = spec[t & 1], &before = spec[(t & 1) ^ 1];
+            const Spec &now = spec[t & 1], &before = spec[(t & 1) ^ 1];
             uint4* const children = reinterpret_cast<uint4*>(ws + L.children);
             const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, children};
             const bool made = t > 0 && plan.makes;
@@ -921,8 +859,15 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         return PRUNER_OK;
     }
 
-    // the table, and the "no S_spec yet" counts of the first step, in one launch
-    rc = put_table(d_table, table.data(), table.size() * sizeof(LseSeg), st, zero_count, round_up((size_t)n_sg * sizeof(int32_t), 4));
+    const int dev = current_device(nullptr);
+    if (dev < 0) return PRUNER_EHIP;
+    if (!g_rank_ready.get(dev)) {
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&lse_rank_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                rank_words(PRUNER_MAX_K) * 16) != hipSuccess)
+            return PRUNER_EHIP;
+        g_rank_ready.mark(dev);
+    }
+    rc = put_table(d_table, table.data(), table.size() * sizeof(LseSeg), st);
     if (rc) return rc;
 
     const size_t filter_bytes = L.table - L.filter;
@@ -930,7 +875,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     // children in one pass if their launch shape allows it, else it runs as a launch of its own first.
     DraftPlan plan_first, plan_later;
     for (int32_t t = 0; t < n_steps; ++t) {
-        const int now = (n_steps - 1 - t) & 1, before = now ^ 1;   // the last step writes the caller's arrays (index 0)
+        const Spec &now = spec[t & 1], &before = spec[(t & 1) ^ 1];
         // C_SA over S_x and its k best: the launches of pruner_prior_filter
         TopkCtx ctx;
         Upload pending;
@@ -940,9 +885,9 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, true, &plan_later);
         if (rc) return rc;
         const DraftPlan& plan = t == 0 ? plan_first : plan_later;
-        const MutArgs owed{d_table, aos, spec_n[before], seed, (uint64_t)(t - 1), mutate_q16, k, nullptr};
+        const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, nullptr};
         if (t > 0 && !plan.makes) {
-            mutate(t - 1, spec_n[before], aos);
+            mutate(t - 1, before.count, before.aos);
             PRUNER_LAUNCH_CHECK();
         }
         if (pending.dst) ctx.d_segs = place_behind(plan, draft_ws, &pending);
@@ -953,20 +898,23 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         if (rc) return rc;
         rc = topk_finish(ctx, score, seg_off, best_idx, best_val, ctx.large && plan.counts, st);
         if (rc) return rc;
-        // PriorFilter over the union, then the new S_spec's tile factors
-        const int32_t* old_n = t == 0 ? zero_count : spec_n[before];
-        hipLaunchKernelGGL(lse_keys_kernel, dim3((unsigned)((P + kKeysThreads - 1) / kKeysThreads), (unsigned)n_sg), dim3(kKeysThreads), 0, st, d_table, k, P, tiles, tiles_pitch,
-                           best_idx, best_val, spec_t[before], spec_s[before], old_n, spec_pitch, key_hi, key_lo);
+        // PriorFilter over the union
+        uint64_t *fresh = words(L.fresh), *merged = words(L.merged);
+        uint32_t* const fresh_aos = reinterpret_cast<uint32_t*>(ws + L.fresh_aos);
+        hipLaunchKernelGGL(lse_keys_kernel, dim3((unsigned)((k + kRun - 1) / kRun), (unsigned)n_sg), dim3(kLseThreads), 0, st, d_table, k, t == 0,
+                           before.count, tiles, tiles_pitch, best_idx, best_val, fresh, fresh + spec_pitch, fresh_aos);
         PRUNER_LAUNCH_CHECK();
-        hipLaunchKernelGGL(lse_merge_kernel, dim3(n_sg), dim3(kLseThreads), merge_lds, st, k, P, Pn, key_hi, key_lo, best_idx, old_n, spec_s[now],
-                           spec_n[now], source);
+        hipLaunchKernelGGL(lse_rank_kernel, dim3((unsigned)(2 * ((k + kRun - 1) / kRun)), (unsigned)n_sg), dim3(kLseThreads), (size_t)rank_words(k) * 16, st, k, t == 0, before,
+                           fresh, fresh + spec_pitch, merged, merged + 2 * spec_pitch);
         PRUNER_LAUNCH_CHECK();
-        hipLaunchKernelGGL(lse_copy_kernel, dim3((unsigned)((spec_pitch + 255) / 256)), dim3(256), 0, st, d_table, n_sg, k, tile_rows, tiles,
-                           tiles_pitch, spec_t[before], spec_pitch, source, spec_t[now], aos);
+        const bool last = t + 1 == n_steps;
+        hipLaunchKernelGGL(lse_unite_kernel, dim3((unsigned)((2 * k + kWave - 1) / kWave), (unsigned)n_sg), dim3(kLseThreads), 0, st, k, t == 0, before,
+                           fresh_aos, merged, merged + 2 * spec_pitch, now, spec_pitch, tile_rows, last ? spec_tiles : nullptr,
+                           last ? spec_score : nullptr, last ? spec_count : nullptr);
         PRUNER_LAUNCH_CHECK();
     }
     // the last step's mutation: S_x as the caller receives it
-    mutate(n_steps - 1, spec_n[0], aos);
+    mutate(n_steps - 1, spec[(n_steps - 1) & 1].count, spec[(n_steps - 1) & 1].aos);
     PRUNER_LAUNCH_CHECK();
     return PRUNER_OK;
 }
