@@ -277,6 +277,8 @@ __device__ __forceinline__ void bucket_of_pass(const uint32_t* __restrict__ ghis
     find_bucket(hist, k_rem, wave_tot, found);
 }
 
+constexpr uint32_t kCounted = 0xFFFFFFFFu;   // Stage::n_cand of a span whose entries above the second digit's bin are staged, and in n_tie the bin's counted
+
 __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
                                                             int64_t span, int R, uint32_t* __restrict__ ghist /* [R][n_seg][kBins] */,
                                                             uint32_t* __restrict__ block_max /* or null */)
@@ -345,6 +347,9 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     }
     bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
     const uint32_t k_rem = found[1];
+    // A bin that the segment's lists would not hold (a population of copies): nothing is staged in this launch, which only counts
+    // the second digit; the next one stages what that digit leaves.
+    const bool crowded = found[2] > (uint32_t)((seg.end - seg.begin + span - 1) / span) * (uint32_t)(kCandCap / 2);
     uint32_t lowest, width;
     first_digit_range(found[0], lowest, width);
     const int shift = next_shift(width);
@@ -356,7 +361,10 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     __syncthreads();
     if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[s] = SelState{lowest, k_rem, (uint32_t)k - k_rem, (uint32_t)shift};
     for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
-    if (threadIdx.x == 0) n_gt = n_cand = 0;
+    if (threadIdx.x == 0) {
+        n_gt = 0;
+        n_cand = crowded ? (uint32_t)kCandCap + 1u : 0u;   // (above the capacity: the list is closed)
+    }
     __syncthreads();
     // Where most blocks hold an entry of the bucket (a population of copies: ties by the hundred thousand), stepping over
     // the others gains nothing and the plain sweeps, whole rows of loads in flight, are the faster way through the span.
@@ -441,6 +449,22 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     }
     for (int64_t row = lo; (!BLK || dense) && row < hi; row += kRow) {
         if (BLK || row > lo) load_sweep(score, row, hi, val);
+        if (crowded) {
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) {
+                const int64_t i = sweep_index(row, j);
+                const uint32_t key = i < hi ? key_of(val[j]) : 0u;
+                const bool inside = key != 0u && key - lowest <= width;
+                if (__ballot(key > lowest && !inside) != 0ull) {
+                    if (key > lowest && !inside) {
+                        const uint32_t at = atomicAdd(&n_gt, 1u);
+                        if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
+                    }
+                }
+                light_hist_add(hist, (key - lowest) >> shift, inside);
+            }
+            continue;
+        }
         // once the candidate list has overflowed, the later passes read the span again: nothing more is staged in it
         // (the count only has to stay above the list's capacity)
         const bool list_open = n_cand <= (uint32_t)kCandCap;
@@ -460,14 +484,16 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     flush_hist<kBigThreads>(hist, ghist1, 1, n_seg, s);   // few contributors as a rule: one copy
 }
 
-__global__ void __launch_bounds__(kBigThreads) refine_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
+// (held to 64 registers, as the funnel: two workgroups per compute unit)
+__global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(8))) refine_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
                                                              int64_t span, const uint32_t* __restrict__ ghist1,
                                                              uint32_t* __restrict__ ghist2, SelState* __restrict__ state,
-                                                             const Stage* __restrict__ stage)
+                                                             Stage* __restrict__ stage)
 {
     __shared__ uint32_t hist[kBins];
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t found[3];
+    __shared__ uint32_t n_staged, n_gt;
     const int s = segment_of_block(segs, n_seg, blockIdx.x);
     const SegT seg = segs[s];
     const SelState before = state[s];
@@ -476,7 +502,7 @@ __global__ void __launch_bounds__(kBigThreads) refine_kernel(const float* __rest
     __syncthreads();
     for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
     __syncthreads();
-    const Stage& mine = stage[blockIdx.x];
+    Stage& mine = stage[blockIdx.x];
     const uint32_t n_cand = mine.n_cand;
     if (n_cand <= (uint32_t)kCandCap) {
         for (uint32_t base = 0; base < n_cand; base += kBigThreads) {
@@ -485,23 +511,85 @@ __global__ void __launch_bounds__(kBigThreads) refine_kernel(const float* __rest
             light_hist_add(hist, key - lowest, i < n_cand && key - lowest <= width);
         }
     } else {
+        // The list did not hold the bin's entries.  Those that the second digit leaves in play, in its bin and above it up to the
+        // first bin's end, are staged now; where its bin alone is still too much (ties), only those above it, and the bin's
+        // entries are counted span by span.  (Explorer loop, 21 M programs, a step full of copies: funnel, refine and settle
+        // took 42 + 22 + 25 us with three readings of the scores, 35 + 28 + 5 with two.)
+        const bool crowded = found[2] > (uint32_t)((seg.end - seg.begin + span - 1) / span) * (uint32_t)(kCandCap / 2);
+        const uint32_t first_width = ((uint32_t)kBins << before.shift) - 1u;
         const int64_t lo = seg.begin + (int64_t)(blockIdx.x - seg.first_block) * span;
         const int64_t hi = lo + span < seg.end ? lo + span : seg.end;
-        for (int64_t row = lo; row < hi; row += kRow) {
-            float val[kBigPer];
-            load_sweep(score, row, hi, val);
+        if (threadIdx.x == 0) {
+            n_staged = 0;
+            n_gt = mine.n_gt;
+        }
+        __syncthreads();
+        uint32_t n_inside = 0;
+        if (crowded) {
+            const bool some_above = k_rem != before.k_rem;   // then key - next <= above_width tells them
+            const uint32_t next = lowest + width + 1u, above_width = before.lowest + first_width - next;
+            for (int64_t row = lo; row < hi; row += kRow) {
+                float val[kBigPer];
+                load_sweep(score, row, hi, val);
 #pragma unroll
-            for (int j = 0; j < kBigPer; ++j) {
-                const int64_t i = sweep_index(row, j);
-                const uint32_t key = key_of(val[j]);
-                light_hist_add(hist, key - lowest, i < hi && key - lowest <= width);
+                for (int j = 0; j < kBigPer; ++j) {
+                    const uint32_t key = key_of(val[j]);
+                    light_hist_add(hist, key - lowest, sweep_index(row, j) < hi && key - lowest <= width);
+                }
+                bool any = false;
+#pragma unroll
+                for (int j = 0; j < kBigPer; ++j) any = any || key_of(val[j]) - next <= above_width;
+                if (some_above && __ballot(any) != 0ull) {
+#pragma unroll
+                    for (int j = 0; j < kBigPer; ++j) {
+                        const int64_t i = sweep_index(row, j);
+                        if (i < hi && key_of(val[j]) - next <= above_width) {
+                            const uint32_t at = atomicAdd(&n_gt, 1u);
+                            if (at < (uint32_t)kStageCap) mine.gt[at] = compose(key_of(val[j]), (uint32_t)i);
+                        }
+                    }
+                }
+            }
+        } else {
+            for (int64_t row = lo; row < hi; row += kRow) {
+                float val[kBigPer];
+                load_sweep(score, row, hi, val);
+#pragma unroll
+                for (int j = 0; j < kBigPer; ++j) {
+                    const int64_t i = sweep_index(row, j);
+                    const uint32_t key = key_of(val[j]);
+                    const bool in_play = i < hi && key >= lowest && key - before.lowest <= first_width;
+                    const unsigned long long these = __ballot(in_play);
+                    if (these == 0ull) continue;
+                    if (n_staged <= (uint32_t)kCandCap) {
+                        const int leader = __ffsll(these) - 1;
+                        uint32_t base = 0;
+                        if (lane_id() == leader) base = atomicAdd(&n_staged, (uint32_t)__popcll(these));
+                        const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(these & ((1ull << lane_id()) - 1ull));
+                        if (in_play && at < (uint32_t)kCandCap) mine.cand[at] = compose(key, (uint32_t)i);
+                    }
+                    light_hist_add(hist, key - lowest, in_play && key - lowest <= width);
+                }
+            }
+        }
+        __syncthreads();
+        if (crowded) {   // the span's entries inside the bin
+            uint32_t inside = 0;
+            for (int i = threadIdx.x; i < kBins; i += kBigThreads) inside += hist[i];
+            block_excl_scan<kBigThreads>(inside, wave_tot, &n_inside);
+        }
+        if (threadIdx.x == 0) {
+            mine.n_cand = crowded ? kCounted : n_staged;
+            if (crowded) {
+                mine.n_gt = n_gt;
+                mine.n_tie = n_inside;
             }
         }
     }
     __syncthreads();
     flush_hist<kBigThreads>(hist, ghist2, 1, n_seg, s);
     // every workgroup of the segment has read the old state before this launch ends; the new one is for the next launch
-    if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[n_seg + s] = SelState{lowest, k_rem, before.n_gt, before.shift};
+    if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[n_seg + s] = SelState{lowest, k_rem, found[2], before.shift};
 }
 
 __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
@@ -521,6 +609,16 @@ __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __rest
     if (blockIdx.x == seg.first_block && threadIdx.x == 0) state[2 * n_seg + s] = SelState{T, k_eq, (uint32_t)k - k_eq, 0u};
     Stage& mine = stage[blockIdx.x];
     const uint32_t n_cand = mine.n_cand;
+    const bool counted = n_cand == kCounted;
+    if (counted && found[2] == before.n_gt) {
+        // One value fills the second digit's bin: the span's ties are counted already.  Only spans before rank k that have few
+        // of them need the list; the ranking reads the others itself.
+        uint32_t earlier = 0;
+        for (int b = seg.first_block + (int)threadIdx.x; b < (int)blockIdx.x; b += kBigThreads) earlier += stage[b].n_tie;
+        uint32_t ties_before;
+        block_excl_scan<kBigThreads>(earlier, wave_tot, &ties_before);
+        if (mine.n_tie == 0u || mine.n_tie > (uint32_t)kStageCap || ties_before >= k_eq) return;
+    }
     if (n_cand <= (uint32_t)kCandCap) {
         // winners staged so far keep their places; candidates above T follow them
         if (threadIdx.x == 0) {
@@ -540,7 +638,12 @@ __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __rest
             }
         }
     } else {
-        if (threadIdx.x == 0) n_gt = n_tie = 0;
+        // (counted: the entries above the second digit's bin, `last` its last key, are staged)
+        const uint32_t last = counted ? before.lowest + ((1u << before.shift) - 1u) : 0xFFFFFFFFu;
+        if (threadIdx.x == 0) {
+            n_gt = counted ? mine.n_gt : 0u;
+            n_tie = 0;
+        }
         __syncthreads();
         const int64_t lo = seg.begin + (int64_t)(blockIdx.x - seg.first_block) * span;
         const int64_t hi = lo + span < seg.end ? lo + span : seg.end;
@@ -551,9 +654,9 @@ __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __rest
             for (int j = 0; j < kBigPer; ++j) {
                 const int64_t i = sweep_index(row, j);
                 const uint32_t key = i < hi ? key_of(val[j]) : 0u;   // 0 is below every key of a number
-                const unsigned long long above = __ballot(key > T), ties = __ballot(key == T);
+                const unsigned long long above = __ballot(key > T && key <= last), ties = __ballot(key == T);
                 if (above) {
-                    if (key > T) {
+                    if (key > T && key <= last) {
                         const uint32_t at = atomicAdd(&n_gt, 1u);
                         if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
                     }
@@ -860,9 +963,9 @@ constexpr int kXcds = 8;                                        // parts of the 
 constexpr int kPickCap = 8192;                                  // words a workgroup collects
 constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
 // What is collected is ranked word against word, so it has to be little more than k: otherwise the bin is split first (two
-// values shared by 20,000 entries, k = 512: 84 us ranked at once).
-__device__ __forceinline__ uint32_t pick_limit(int k) { return (uint32_t)(k + k / 4 + 256); }
-static_assert(kPickCap >= PRUNER_MAX_K + PRUNER_MAX_K / 4 + 256, "a collection fits");
+// values shared by 20,000 entries, k = 512: 84 us with all of the bin ranked, 25 with the limit).
+__host__ __device__ constexpr int collect_limit(int k) { return k + k / 4 + 256; }
+static_assert(kPickCap >= collect_limit(PRUNER_MAX_K), "a collection fits");
 
 // The lists route: at most 32 spans per segment, so that a segment that has to be gone through again by one workgroup is still
 // a matter of microseconds.
@@ -940,7 +1043,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     first_digit_range(found[0], lowest, width);
     const float t0 = threshold_of(lowest);
     const int shift = next_shift(width);
-    const bool crowded = (uint32_t)k - found[1] + found[2] > pick_limit(k);   // the second digit will be asked for
+    const bool crowded = (uint32_t)k - found[1] + found[2] > (uint32_t)collect_limit(k);   // the second digit will be asked for
     __syncthreads();
     if (threadIdx.x == 0) fill = range[0] = range[1] = 0;
     if (crowded)
@@ -1029,7 +1132,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     __syncthreads();
     // More than the limit: the bin is split (the same decision in every workgroup of the segment), in the lists route first by
     // the second digit, which the launch before has counted.
-    const uint32_t limit = pick_limit(k);
+    const uint32_t limit = (uint32_t)collect_limit(k);
     const bool lists_whole = LISTS && __ballot(my_count > (uint32_t)kListCap) == 0ull;   // (every wavefront holds all counts)
     uint32_t least = 0u, largest = 0xFFFFFFFFu;   // of the bin's keys
     auto between = [&] {

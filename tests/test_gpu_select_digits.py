@@ -64,7 +64,8 @@ KINDS = ["normal", "latencies", "every exponent", "tiny", "huge", "zeros", "one 
 
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("lens,ks", [([8193], [1, 64, 65, 4096]), ([16383, 16384, 16385, 70], [1, 33, 70]), ([65536], [1, 512, 4096]), ([65535, 5, 32769], [5]),
-                                     ([65537], [1, 31, 4096]), ([300001], [100, 4096]), ([50001] * 7, [512]), ([333333] * 3, [33, 512]), ([524288, 524287], [4096])])
+                                     ([65537], [1, 31, 4096]), ([300001], [100, 4096]), ([50001] * 7, [512]), ([333333] * 3, [33, 512]), ([524288, 524287], [4096]), ([524289], [1, 4096]),
+                                     ([540001, 600000, 33], [33]), ([3000001], [512, 4096])])
 def test_routes_and_values(P, kind, lens, ks):
     rng = np.random.default_rng(sum(lens) + len(kind))
     seg = np.concatenate([[0], np.cumsum(lens)])
