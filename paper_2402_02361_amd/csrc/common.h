@@ -147,11 +147,6 @@ void* place_behind(const DraftPlan& plan, void* workspace, Upload* also);
 // S_spec, store them over `tiles` (which is then written) and score them in one pass.
 int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tiles, float* score, int64_t* symbols, hipStream_t stream,
               uint32_t* first_digit, uint32_t* block_max, int copies, const MutArgs* mut);
-// the three in one
-int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch,
-                 int32_t flags, float* score, int64_t* symbols, void* workspace, size_t workspace_bytes, hipStream_t stream,
-                 uint32_t* first_digit, uint32_t* block_max, int copies, bool* counted, const Upload* also = nullptr);
-
 // workspace needs of the entry points (each defined next to its kernels)
 size_t draft_workspace_bytes(int32_t n_sg);
 size_t topk_workspace_bytes(int64_t n, int32_t n_sg, int32_t k);

@@ -1575,23 +1575,6 @@ int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tile
     return PRUNER_OK;
 }
 
-int draft_launch(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch,
-                 int32_t flags, float* score, int64_t* symbols, void* workspace, size_t workspace_bytes, hipStream_t st,
-                 uint32_t* first_digit, uint32_t* block_max, int copies, bool* counted, const Upload* also)
-{
-    if (counted) *counted = false;
-    DraftPlan plan;
-    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes,
-                        first_digit != nullptr && copies >= 1, false, &plan);
-    if (rc) return rc;
-    rc = draft_upload(plan, workspace, st, also);
-    if (rc) return rc;
-    rc = draft_run(plan, workspace, tiles, score, symbols, st, first_digit, block_max, copies, nullptr);
-    if (rc) return rc;
-    if (counted) *counted = plan.counts;
-    return PRUNER_OK;
-}
-
 }  // namespace pruner
 
 using namespace pruner;
@@ -1600,8 +1583,13 @@ extern "C" int pruner_draft_score(const pruner_subgraph* sg, int32_t n_sg, const
                                   int64_t tiles_pitch, int32_t flags, float* score, int64_t* symbols, void* workspace,
                                   size_t workspace_bytes, void* stream)
 {
-    return draft_launch(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes,
-                        static_cast<hipStream_t>(stream), nullptr, nullptr, 0, nullptr);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    DraftPlan plan;
+    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes, false, false, &plan);
+    if (rc) return rc;
+    rc = draft_upload(plan, workspace, st, nullptr);
+    if (rc) return rc;
+    return draft_run(plan, workspace, tiles, score, symbols, st, nullptr, nullptr, 0, nullptr);
 }
 
 extern "C" int pruner_time_dominant_draft_launch(void* start_event, void* stop_event, int64_t* algorithmic_bytes)

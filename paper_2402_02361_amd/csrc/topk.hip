@@ -14,12 +14,12 @@
 //   lists  - segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
 //            16384-entry sweeps, one workgroup each) and sets the entries at or above the bin aside in a list per span; the
 //            workgroups of a segment then collect from its lists (and go through the segment themselves only if a list
-//            overflowed or the collection does not fit);
+//            overflowed);
 //   spans  - longer segments are cut into spans of whole 16384-entry sweeps, one workgroup of 1024 threads each; the scores
 //            are read twice at most (first-digit histogram, which also notes the largest key of every 256 entries; then
 //            everything at or above that digit's rank-k bin is set aside, a few thousand entries as a rule, and blocks of
-//            256 whose largest key lies below the bin are not read again) and the later passes work on what was set aside;
-//            six launches.
+//            256 whose largest key lies below the bin are not read again) and the later passes work on what was set aside
+//            (where the bin holds too much for that, the second digit is counted first: one more reading); six launches.
 #include "select_common.h"
 
 #include <string.h>
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(kTinyThreads) topk_tiny_kernel(const float* __
     tiny_select(L, score, seg.begin, seg.end, blockIdx.x, k, idx_out, val_out);
 }
 
-// ---- large route ------------------------------------------------------------------------------------------------
+// ---- spans route ------------------------------------------------------------------------------------------------
 //
 // Workgroups of 1024 threads each own `span` consecutive entries of one segment (span = a multiple of 16384, sized
 // so that a launch is a single wave of workgroups).  No global atomics with a return value, no cross-workgroup
@@ -531,10 +531,11 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
             for (int64_t row = lo; row < hi; row += kRow) {
                 float val[kBigPer];
                 load_sweep(score, row, hi, val);
+                const int left = hi - row < kRow ? (int)(hi - row) : kRow;
 #pragma unroll
                 for (int j = 0; j < kBigPer; ++j) {
                     const uint32_t key = key_of(val[j]);
-                    light_hist_add(hist, key - lowest, sweep_index(row, j) < hi && key - lowest <= width);
+                    light_hist_add(hist, key - lowest, (int)sweep_index(0, j) < left && key - lowest <= width);
                 }
                 bool any = false;
 #pragma unroll
@@ -542,10 +543,10 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
                 if (some_above && __ballot(any) != 0ull) {
 #pragma unroll
                     for (int j = 0; j < kBigPer; ++j) {
-                        const int64_t i = sweep_index(row, j);
-                        if (i < hi && key_of(val[j]) - next <= above_width) {
+                        const int i = (int)sweep_index(0, j);
+                        if (i < left && key_of(val[j]) - next <= above_width) {
                             const uint32_t at = atomicAdd(&n_gt, 1u);
-                            if (at < (uint32_t)kStageCap) mine.gt[at] = compose(key_of(val[j]), (uint32_t)i);
+                            if (at < (uint32_t)kStageCap) mine.gt[at] = compose(key_of(val[j]), (uint32_t)row + (uint32_t)i);
                         }
                     }
                 }
@@ -554,11 +555,12 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
             for (int64_t row = lo; row < hi; row += kRow) {
                 float val[kBigPer];
                 load_sweep(score, row, hi, val);
+                const int left = hi - row < kRow ? (int)(hi - row) : kRow;
 #pragma unroll
                 for (int j = 0; j < kBigPer; ++j) {
-                    const int64_t i = sweep_index(row, j);
+                    const int i = (int)sweep_index(0, j);
                     const uint32_t key = key_of(val[j]);
-                    const bool in_play = i < hi && key >= lowest && key - before.lowest <= first_width;
+                    const bool in_play = i < left && key >= lowest && key - before.lowest <= first_width;
                     const unsigned long long these = __ballot(in_play);
                     if (these == 0ull) continue;
                     if (n_staged <= (uint32_t)kCandCap) {
@@ -566,7 +568,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
                         uint32_t base = 0;
                         if (lane_id() == leader) base = atomicAdd(&n_staged, (uint32_t)__popcll(these));
                         const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(these & ((1ull << lane_id()) - 1ull));
-                        if (in_play && at < (uint32_t)kCandCap) mine.cand[at] = compose(key, (uint32_t)i);
+                        if (in_play && at < (uint32_t)kCandCap) mine.cand[at] = compose(key, (uint32_t)row + (uint32_t)i);
                     }
                     light_hist_add(hist, key - lowest, in_play && key - lowest <= width);
                 }
@@ -1354,7 +1356,7 @@ constexpr int kComputeUnits = 256;   // of the part this library is written for 
 
 int hist_copies(int32_t n_sg) { return n_sg <= 16 ? 8 : n_sg <= 64 ? 4 : 1; }
 
-// entries per workgroup of the large route: whole sweeps, and at most 512 workgroups per launch, which is what 256
+// entries per workgroup of the spans and lists routes: whole sweeps, and at most 512 workgroups per launch, which is what 256
 // CUs hold at once (two workgroups of 1024 threads each): a launch then runs as a single wave of workgroups
 // (quarter sweeps for populations that leave CUs idle were measured: more workgroups add to the segment's histograms
 // and lists, 11 -> 14 us for the funnel launch on a million entries)
