@@ -11,17 +11,22 @@
 // binary32, the softmax is binary32.
 //
 // Three launches:
-//   pacm_stmt_kernel   the two statement layers on the matrix cores, tiles of 64 valid rows that hold whole candidates,
-//                      the sum over a candidate's rows as one more matrix product; a wavefront owns 64 hidden units and
-//                      keeps its W1/W2 slices in registers
-//   pacm_flow_kernel   the dataflow branch, a wavefront per tile of 32 valid blocks that hold whole candidates, the chain
-//                      from the features to the pooled vector in registers
+//   pacm_stmt_kernel   the two statement layers on the matrix cores, tiles of 64 valid rows that hold whole candidates;
+//                      a wavefront owns 64 hidden units and keeps its W1/W2 slices in registers
+//   pacm_flow_kernel   the dataflow branch, a wavefront per tile of 32 block slots in quads, the chain from the features to
+//                      the pooled vector in registers but for V
 //   pacm_head_kernel   the head's hidden layer on the matrix cores (64 candidates per tile) and its output dot product
 // The pooled vectors travel through the workspace as the bfloat16 operands that the head's layer takes.
 //
-// Measured, before = eight padded slots per candidate in either branch and binary32 pooled vectors (statement counts 3..8,
-// blocks 0..5): 131,072 candidates: statement kernel 345 -> 180 us, dataflow 170 -> 55, head 43 -> 28, the call 512-560 -> 246;
-// 8,192 candidates: 29.8 -> 17.6, 23.7 -> 12.3, 10.7 -> 9.6, the call 60.4 -> 37.1.
+// A score is a function of its candidate alone: the same bits wherever in a set it stands and whatever stands beside it.  A
+// matrix product of depth 16 adds its products in two groups of eight, one after the other (inside a group the order does not
+// matter), so every product here has a candidate's own row or column to itself, and sums over rows run in a fixed order of
+// the candidate's slots.
+//
+// Measured, before = eight padded slots per candidate in either branch and binary32 pooled vectors, the same bits (statement
+// counts 3..8, blocks 0..5): 131,072 candidates: statement kernel 345 -> 212 us, dataflow 170 -> 66, head 43 -> 28, the call
+// 515 -> 296; 8,192 candidates: 29.8 -> 19.7, 23.7 -> 9.4, 10.7 -> 9.4, the call 61 -> 38.  (With the sums over rows on the matrix
+// cores too, by the rows' places in a tile, 246 and 38: two scores in a thousand then changed with the neighbours.)
 #include "common.h"
 #include "mfma_tile.h"
 
@@ -48,50 +53,7 @@ static_assert(kS == 8 && kT == 8 && kE == 64 && kTM == 64, "the lane arithmetic 
 
 __device__ __forceinline__ int clamp8(int v) { return v < 0 ? 0 : v > 8 ? 8 : v; }
 
-// x = hi + mid + lo exactly, each a bfloat16 (3 x 8 significand bits; an infinity or a NaN is its own first piece)
-struct Pieces {
-    uint32_t hi, mid, lo;   // bit patterns
-};
-__device__ __forceinline__ Pieces split3(float x)
-{
-    const __bf16 hi = (__bf16)x;
-    const float rest = x - (float)hi;
-    const __bf16 mid = (__bf16)rest;
-    const __bf16 lo = (__bf16)(rest - (float)mid);
-    return Pieces{__builtin_bit_cast(uint16_t, hi), __builtin_bit_cast(uint16_t, mid), __builtin_bit_cast(uint16_t, lo)};
-}
-
-// Registers 8 q .. 8 q + 7 of a product as the operand of the next one: rounded to bfloat16 in pairs (with ReLU or without),
-// or as three operands whose sum they are.
-__device__ __forceinline__ bf16x8 relu_fragment(const floatx16& a, int q)
-{
-    const u32x4 f = {relu_bf16x2(a[8 * q], a[8 * q + 1]), relu_bf16x2(a[8 * q + 2], a[8 * q + 3]), relu_bf16x2(a[8 * q + 4], a[8 * q + 5]),
-                     relu_bf16x2(a[8 * q + 6], a[8 * q + 7])};
-    return __builtin_bit_cast(bf16x8, f);
-}
 __device__ __forceinline__ uint32_t bf16x2_of(float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2)); }
-__device__ __forceinline__ bf16x8 plain_fragment(const floatx16& a, int q)
-{
-    const u32x4 f = {bf16x2_of(a[8 * q], a[8 * q + 1]), bf16x2_of(a[8 * q + 2], a[8 * q + 3]), bf16x2_of(a[8 * q + 4], a[8 * q + 5]),
-                     bf16x2_of(a[8 * q + 6], a[8 * q + 7])};
-    return __builtin_bit_cast(bf16x8, f);
-}
-__device__ __forceinline__ void split_fragment(const floatx16& a, int q, bf16x8 (&piece)[3])
-{
-    u32x4 f[3];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        float x = a[8 * q + 2 * p], y = a[8 * q + 2 * p + 1];
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            f[k][p] = bf16x2_of(x, y);
-            x -= __uint_as_float(f[k][p] << 16);
-            y -= __uint_as_float(f[k][p] & 0xFFFF0000u);
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) piece[k] = __builtin_bit_cast(bf16x8, f[k]);
-}
 // What this wavefront's lanes wrote to LDS before is there for its other lanes after (LDS serves a wavefront in order; this
 // keeps the compiler's order).
 __device__ __forceinline__ void wave_lds_fence()
@@ -114,41 +76,16 @@ __device__ __forceinline__ void load_slices(bf16x8 (&wr)[2][KS], const uint16_t*
     }
 }
 
-// ---- pooling on the matrix cores -------------------------------------------------------------------------------------
-// A layer computed with the rows as the A operand leaves a lane one output unit (l32) of 16 rows: register i is row
-// 8 (i / 4) + 4 half + i % 4 of its 32-row block.  Rounded to bfloat16 in pairs, registers 8 q .. 8 q + 7 are, as they
-// stand, one operand of a further MFMA whose depth is 16 of those rows; the other operand is the 0/1 matrix that says
-// which candidate a row belongs to.  The product holds the sums over each candidate's rows, whatever their number, for
-// 32 units x 32 candidates, a lane holding 16 units of ONE candidate.  Products with 1 are exact and the sums are binary32.
-
-// A tile takes whole candidates; `rows` of lane (l32, half) is the set of rows of its l32-th candidate, one bit per row.
-// Fragment q of the 0/1 matrix: rows 16 q + 8 (j / 4) + 4 half + j % 4 for j = 0..7.
-__device__ __forceinline__ bf16x8 member_fragment(uint32_t rows32, int q, int half)
-{
-    const uint32_t n0 = rows32 >> (16 * q + 4 * half), n1 = rows32 >> (16 * q + 8 + 4 * half);
-    auto two = [](uint32_t b) { return (uint32_t)__umul24((b & 1u) | ((b & 2u) << 15), 0x3F80u); };   // 1.0 where the bit is set
-    const u32x4 f = {two(n0), two(n0 >> 2), two(n1), two(n1 >> 2)};
-    return __builtin_bit_cast(bf16x8, f);
-}
-// the lowest n bits, n = 0..64
-__device__ __forceinline__ uint64_t low_bits(uint32_t n) { return n >= 64 ? ~0ull : (1ull << n) - 1ull; }
-
-// The lane's 16 units (block of 32, registers of one product) of its candidate, rounded, to the pooled vectors.
-__device__ __forceinline__ void store_pooled(const floatx16& acc, int g, uint16_t* __restrict__ to)   // four units: 8 g + 4 half ..
-{
-    const f32x2 lo = {acc[4 * g + 0], acc[4 * g + 1]}, hi = {acc[4 * g + 2], acc[4 * g + 3]};
-    u32x2 o;
-    o[0] = __builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2));
-    o[1] = __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2));
-    *reinterpret_cast<u32x2*>(to) = o;
-}
-
 // ---- statement branch ------------------------------------------------------------------------------------------------
-// Bound: the matrix cores (and the chip's power) at scale, weights and first rows on their way for small sets.  Tiles of
-// 64 valid rows: a tile takes as many whole candidates as fit (at most 32), so the rows beyond n_stmt cost nothing, and a
-// candidate never straddles.  The candidates of a workgroup are groups of neighbours, interleaved over the workgroups as
-// in verify_mlp.hip; so are the weights in registers, b1 in the depth padding and the two halves of a tile half a layer
-// apart.
+// Tiles of 64 valid rows: a tile takes as many whole candidates as fit (at most 32), so the rows beyond n_stmt cost nothing, and
+// a candidate never straddles.  The candidates of a workgroup are groups of neighbours, interleaved over the workgroups as
+// in verify_mlp.hip; so are the weights in registers and the two halves of a tile half a layer apart.
+// The sum over a candidate's rows is ((r0 + r1) + (r2 + r3)) + ((r4 + r5) + (r6 + r7)) in binary32, missing rows 0, wherever in
+// a tile the rows lie: a score is a function of its candidate alone.  (Sums on the matrix cores, against a 0/1 matrix, add the
+// rows in groups of eight by their place in the tile, and a pooled vector then depends on the neighbours.)  A wavefront parks
+// the second hidden layer of its 64 units in LDS and reads the rows back candidate by candidate.
+// Bound: what a SIMD's one wavefront issues in turn.  131,072 candidates, by the counters: 10,600 cycles a tile, the matrix pipe
+// busy in 32 % of them, the vector ALU in 23 % (620 instructions), LDS in 30 %; weights and first rows on their way for small sets.
 
 constexpr int kRowThreads = 8;                                   // threads that share a feature row: 128 contiguous bytes per request
 constexpr int kXPass = kTM / (kThreads / kRowThreads);           // passes over the tile's rows (2)
@@ -161,13 +98,14 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1
 pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, int32_t n_d, int group_log, const uint16_t* __restrict__ W1,
                  const float* __restrict__ b1, const uint16_t* __restrict__ W2, const float* __restrict__ b2, uint16_t* __restrict__ v_s)
 {
-    __shared__ __attribute__((aligned(16))) __bf16 arena[kTM * kXs + kTM * kHs];
+    __shared__ __attribute__((aligned(16))) __bf16 arena[kTM * kXs + 2 * kTM * kHs + kHs];
+    __shared__ __attribute__((aligned(16))) float cst[2][kH];
     __shared__ uint16_t before[kLocalCap + 64 + 2];   // valid rows of this workgroup's candidates 0..l-1 (at most 8 x kLocalCap)
     __shared__ int32_t row_src[kTM];                  // what the rows of one tile are: candidate * 8 + statement, or -1
     __shared__ uint32_t scan_tot[4];
-    __shared__ uint32_t tainted[kLocalCap / 32];      // tiles to do again, by their first candidate
     __bf16* X = arena;                   // feature tile, bfloat16 [kTM][kXs]
     __bf16* H1 = arena + kTM * kXs;      // first hidden layer of the tile [kTM][kHs]
+    __bf16* H2 = H1 + kTM * kHs;         // second hidden layer, and a row of zeros [kTM + 1][kHs]; a wavefront's 64 units are its own
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, l32 = lane & 31;
 
@@ -178,25 +116,22 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
     const int n_local = (my_groups << group_log) - (owns_last ? (n_groups << group_log) - n_d : 0);
     auto global_of = [&](int l) -> int { return ((((l >> group_log) * group_stride + my_first)) << group_log) + (l & ((1 << group_log) - 1)); };
 
-    // weights: W1's rows end at depth 164; the last step holds its last four entries and b1 as three bfloat16 pieces
-    // (b = hi + mid + lo exactly), which meet the 1, 1, 1 that the feature tile holds at depths 164..166
+    // weights: W1's rows end at depth 164, the last step is four entries for half 0 and zeros otherwise
     static_assert(kK1 / 16 == kF / 16 + 1 && kF % 16 == 4, "W1's last depth step holds four entries");
     bf16x8 w1r[2][kK1 / 16], w2r[2][kH / 16];
     typedef u32x4 u32x4_a8 __attribute__((aligned(8)));   // W1's rows are 328 bytes
     load_slices<kK1 / 16, kF / 16, u32x4_a8>(w1r, W1, kF, wave, l32, half);
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
-        const int n = 64 * wave + 32 * nt + l32;
-        const u32x2 tail = *reinterpret_cast<const u32x2*>(W1 + (size_t)n * kF + 16 * (kF / 16));
+        const u32x2 tail = *reinterpret_cast<const u32x2*>(W1 + (size_t)(64 * wave + 32 * nt + l32) * kF + 16 * (kF / 16));
         u32x4 last = {0u, 0u, 0u, 0u};
-        const Pieces b = split3(b1[n]);
         last[0] = half == 0 ? tail[0] : 0u;
         last[1] = half == 0 ? tail[1] : 0u;
-        last[2] = half == 0 ? (b.hi | (b.mid << 16)) : 0u;
-        last[3] = half == 0 ? b.lo : 0u;
         w1r[nt][kF / 16] = __builtin_bit_cast(bf16x8, last);
     }
-    const float b2_mine[2] = {b2[64 * wave + l32], b2[64 * wave + 32 + l32]};
+    static_assert(kThreads == kH, "one thread per hidden unit");
+    cst[0][threadIdx.x] = b1[threadIdx.x];
+    cst[1][threadIdx.x] = b2[threadIdx.x];
 
     {   // row numbering: exclusive scan of the statement counts, a run of `per` candidates per thread
         for (int l = threadIdx.x; l < n_local; l += kThreads) before[l] = (uint16_t)clamp8(n_stmt[global_of(l)]);
@@ -231,7 +166,6 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
         uint32_t first, end;
         int cand;
     };
-    int stop = n_local, most = 32;   // tiles end before candidate `stop` and take at most `most` candidates
     auto tile_at = [&](int start) {
         Tile t;
         t.start = start;
@@ -240,14 +174,13 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
         const uint32_t base = (uint32_t)__builtin_amdgcn_readfirstlane((int)b0);
         t.first = b0 - base;
         t.end = b1v - base;
-        const bool in = start + l32 < stop && l32 < most && t.end <= (uint32_t)kTM;
+        const bool in = start + l32 < n_local && t.end <= (uint32_t)kTM;
         t.count = (int)__popcll(__ballot(in) & 0xFFFFFFFFull);   // (the counts grow, so the candidates that fit are the first ones)
         t.cand = in ? global_of(start + l32) : -1;
         t.first = in ? t.first : 0u;
         t.end = in ? t.end : 0u;
         return t;
     };
-    auto rows_of = [&](const Tile& t) { return low_bits(t.end) & ~low_bits(t.first); };
     auto write_rows = [&](const Tile& t) {   // by one wavefront
         const int used = t.count > 0 ? __builtin_amdgcn_readlane((int)t.end, t.count - 1) : 0;
         if (lane >= used) row_src[lane] = -1;
@@ -288,203 +221,212 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
     for (int nt = 0; nt < 2; ++nt)   // weights in the accumulation registers (see verify_mlp.hip)
 #pragma unroll
         for (int ks = 0; ks < kK1 / 16; ++ks) asm volatile("" : "+a"(w1r[nt][ks]));
-    // the padding of the feature tile (depth 164..183) is written once: 1, 1, 1 (times the three pieces of b1), then zeros
+    // the zero padding of the feature tile (depth 164..183) is written once
     for (int q = threadIdx.x; q < kTM * ((kXs - kF) / 4); q += kThreads) {
         const int r = q / ((kXs - kF) / 4), j = q % ((kXs - kF) / 4);
-        *reinterpret_cast<uint2*>(&X[r * kXs + kF + 4 * j]) = j == 0 ? make_uint2(0x3F803F80u, 0x00003F80u) : make_uint2(0, 0);
+        *reinterpret_cast<uint2*>(&X[r * kXs + kF + 4 * j]) = make_uint2(0, 0);
     }
-    for (int i = threadIdx.x; i < kLocalCap / 32; i += kThreads) tainted[i] = 0u;
-    floatx16 b2r[2];
+    for (int i = threadIdx.x; i < kHs; i += kThreads) H2[kTM * kHs + i] = (__bf16)0.f;
+
+    floatx16 acc0[2], acc1[2];   // rows 0..31 and 32..63
+
+    // The sums over the rows of the tile before, four candidates at a time: lanes 16 g .. 16 g + 15 take the g-th of them and
+    // four hidden units each.  The first twelve candidates' (a tile of 64 rows holds 11.6 of five and a half rows) run in the
+    // gaps between the MFMAs of two layers, a piece per gap and without a branch (one a gap cost 17 of 300 us at 131,072
+    // candidates); a tile of more candidates goes through the others behind them.
+    constexpr uint32_t kNowhere = 0xFFFF0000u;
+    uint32_t pool_rows = 0, pool_to = kNowhere;   // the l32-th candidate: first row, number of rows << 8; where its sums go (bytes from v_s), or past the end of the buffer: no store
+    int pool_count = 0;
+    const auto out = __builtin_amdgcn_make_buffer_rsrc(v_s, 0, n_d * kH * 2, 0x00027000);
+    const int p_group = lane >> 4, p_unit = 64 * wave + 4 * (lane & 15);
+    uint32_t p_n = 0, p_to = 0;
+    const __bf16* p_from = H2;
+    u32x2 p_raw[kS];
+    f32x4 p_sum[4];
+    constexpr int kPoolPieces = 13;
+    auto pool_piece = [&](int first, int piece) {   // candidates first .. first + 3 of the tile
+        if (piece == 0) {
+            const uint32_t rows = (uint32_t)__shfl((int)pool_rows, first + p_group, 64);
+            p_to = (uint32_t)__shfl((int)pool_to, first + p_group, 64) + 2u * (uint32_t)p_unit;
+            p_n = rows >> 8;
+            p_from = H2 + (rows & 0xFFu) * kHs + p_unit;
+        }
+        if (piece == 1 || piece == 2) {
+#pragma unroll
+            for (int r = 4 * (piece - 1); r < 4 * piece; ++r)
+                p_raw[r] = *reinterpret_cast<const u32x2*>((uint32_t)r < p_n ? p_from + r * kHs : H2 + kTM * kHs + p_unit);
+        }
+        if (piece >= 3 && piece < 11) {   // rows 2 q and 2 q + 1, two units
+            const int q = (piece - 3) >> 1, w = (piece - 3) & 1;
+            p_sum[q][2 * w] = __uint_as_float(p_raw[2 * q][w] << 16) + __uint_as_float(p_raw[2 * q + 1][w] << 16);
+            p_sum[q][2 * w + 1] = __uint_as_float(p_raw[2 * q][w] & 0xFFFF0000u) + __uint_as_float(p_raw[2 * q + 1][w] & 0xFFFF0000u);
+        }
+        if (piece == 11) {
+#pragma unroll
+            for (int q = 0; q < 4; q += 2)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) p_sum[q][e] += p_sum[q + 1][e];
+        }
+        if (piece == 12) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p_sum[0][e] += p_sum[2][e];
+            const u32x2 o = {bf16x2_of(p_sum[0][0], p_sum[0][1]), bf16x2_of(p_sum[0][2], p_sum[0][3])};
+            __builtin_amdgcn_raw_buffer_store_b64(o, out, (int)p_to, 0, 0);
+        }
+    };
+    constexpr int kPoolAhead = 12, kPoolGaps = 2 * (kK1 / 16 + kH / 16) / (kPoolAhead / 4);   // gaps per four candidates (18)
+    static_assert(kPoolGaps >= kPoolPieces, "a piece per gap");
+    auto pool_gap = [&](int gap) {   // (a constant after unrolling) the pieces spread evenly over the gaps
+        const int at = gap % kPoolGaps, piece = (at * kPoolPieces + kPoolGaps - 1) / kPoolGaps;
+        if (gap < kPoolAhead / 4 * kPoolGaps && piece < kPoolPieces && piece * kPoolGaps / kPoolPieces == at) pool_piece(4 * (gap / kPoolGaps), piece);
+    };
+    auto pool_rest = [&](int first) {
+        for (; first < pool_count; first += 4) {
+#pragma unroll
+            for (int piece = 0; piece < kPoolPieces; ++piece) pool_piece(first, piece);
+        }
+    };
+
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) b2r[nt][i] = b2_mine[nt];
+        for (int i = 0; i < 16; ++i) acc1[nt][i] = 0.f;
+    Tile cur = tile_at(0);
+    if (wave == 0) write_rows(cur);
+    __syncthreads();
+    fetch_read();
+#pragma unroll
+    for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
+    Tile nxt = tile_at(cur.start + cur.count);
+    __syncthreads();   // everyone has read the first tile's rows
+    if (wave == 0) write_rows(nxt);
+#pragma unroll
+    for (int i = 0; i < kXLoads; ++i) park_piece(i);
+    bias_init(acc0, cst[0], wave, half);
+    __syncthreads();
+    fetch_read();
+#pragma unroll
+    for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
 
-    floatx16 acc0[2], acc1[2];   // rows 0..31 and 32..63
-    floatx16 pooled[2];          // sums of the tile in the making: units 64 wave + 32 nt + .. of the lane's candidate
-    uint32_t pk[16];             // a half's second hidden layer, pairs of neighbouring rows
-    bf16x8 member[4];            // the 0/1 matrix of the tile being pooled: 16 rows each
-    uint32_t top;                // the largest of a half's activations (a lane's pairs), as 16-bit integers
-    bool special;                // the tile being pooled holds an infinity or a NaN
-    int pool_start, pool_count;
-    uint32_t pool_to;            // where the lane's candidate goes (bytes from v_s), or past the end of the buffer: no store
-    constexpr uint32_t kNowhere = 0xFFFF0000u;
-    const auto out = __builtin_amdgcn_make_buffer_rsrc(v_s, 0, n_d * kH * 2, 0x00027000);
-
-    auto pack_pair = [&](const floatx16(&acc)[2], int pair) {
-        const int nt = pair >> 3, j = pair & 7;
-        pk[pair] = relu_bf16x2(acc[nt][2 * j], acc[nt][2 * j + 1]);
-        // (not negative, so the order of the bit patterns is the order of the values, infinity and NaN last)
-        top = pair == 0 ? pk[0] : __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(i16x2, top), __builtin_bit_cast(i16x2, pk[pair])));
-    };
-    auto is_special = [&]() { return __ballot((top & 0xFFFFu) >= 0x7F80u || (top >> 16) >= 0x7F80u) != 0ull; };
-    auto pool_mfma = [&](int hh, int q) {   // q = 2 nt + hq
-        const u32x4 h = {pk[4 * q], pk[4 * q + 1], pk[4 * q + 2], pk[4 * q + 3]};
-        if (hh == 0 && (q & 1) == 0) {
-            floatx16 zero;
+    // A tile in four stages, each a layer of one half of the rows with other work between its MFMAs.  At the loop's head
+    // X holds this tile's rows and the next tile's are on their way to registers.
+    while (cur.count > 0) {
+        // layer 1, rows 0..31.  Meanwhile: the previous tile's second hidden layer of rows 32..63 to LDS.
+        layer<kK1 / 16>(acc0, w1r, X, kXs, l32, half, [&](int i) {
+            if (i < 16 && !(i & 1)) park_hidden(acc1, i >> 1, H2 + 32 * kHs, kHs, wave, l32, half);
+            if (i == 18) bias_init(acc1, cst[0], wave, half);
+            if (i == 20) wave_lds_fence();
+        });
+        // layer 1, rows 32..63.  Meanwhile: hidden layer 1 of rows 0..31 to LDS, sums over the previous tile's rows.
+        layer<kK1 / 16>(acc1, w1r, X + 32 * kXs, kXs, l32, half, [&](int i) {
+            pool_gap(i);
+            if (i >= 4 && i < 20 && !(i & 1)) park_hidden(acc0, (i - 4) >> 1, H1, kHs, wave, l32, half);
+            if (i == 20) bias_init(acc0, cst[1], wave, half);
+        });
+        __syncthreads();   // rows 0..31 of H1 complete; X no longer read
+        // layer 2, rows 0..31.  Meanwhile: hidden layer 1 of rows 32..63 and the next tile's features to LDS, more of the sums, and
+        // what the rows of the tile after next are.
 #pragma unroll
-            for (int i = 0; i < 16; ++i) zero[i] = 0.f;
-            pooled[q >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, h), member[2 * hh + (q & 1)], zero, 0, 0, 0);
-        } else {
-            pooled[q >> 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, h), member[2 * hh + (q & 1)], pooled[q >> 1], 0, 0, 0);
-        }
-    };
-    auto pool_store = [&](int piece) {   // four units of the lane's candidate
-        const int nt = piece >> 2, g = piece & 3;
-        const u32x2 o = {bf16x2_of(pooled[nt][4 * g + 0], pooled[nt][4 * g + 1]), bf16x2_of(pooled[nt][4 * g + 2], pooled[nt][4 * g + 3])};
-        __builtin_amdgcn_raw_buffer_store_b64(o, out, (int)(pool_to + 2u * (uint32_t)(32 * nt + 8 * g)), 0, 0);
-    };
-    // 0 times an infinity or a NaN of one candidate would reach the others of its tile: such a tile is noted and done again
-    // when the others are through, one candidate at a time.
-    auto note_special = [&]() {
-        if (special && pool_count > 1 && lane == 0) atomicOr(&tainted[pool_start >> 5], 1u << (pool_start & 31));
-    };
-
-    int begin = 0, again = 0;   // candidates from `again` on may belong to noted tiles (second and later rounds)
-    for (;;) {
-        special = false;
-        pool_start = pool_count = 0;
-        pool_to = kNowhere;
-        top = 0u;
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) acc0[nt][i] = acc1[nt][i] = pooled[nt][i] = 0.f;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) member[q] = __builtin_bit_cast(bf16x8, u32x4{0u, 0u, 0u, 0u});
-        Tile cur = tile_at(begin);
-        if (wave == 0) write_rows(cur);
-        __syncthreads();
-        fetch_read();
-#pragma unroll
-        for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
-        Tile nxt = tile_at(cur.start + cur.count);
-        __syncthreads();   // everyone has read the first tile's rows
-        if (wave == 0) write_rows(nxt);
-#pragma unroll
-        for (int i = 0; i < kXLoads; ++i) park_piece(i);
-        __syncthreads();
-        fetch_read();
-#pragma unroll
-        for (int i = 0; i < kXLoads; ++i) fetch_issue(i);
-
-        // A tile in four stages, each a layer of one half of the rows with other work between its MFMAs.  At the loop's head
-        // X holds this tile's rows and the next tile's are on their way to registers.
-        while (cur.count > 0) {
-            // layer 1, rows 0..31.  Meanwhile: the sums of the previous tile's rows 32..63.
-            layer_from<kK1 / 16>(acc0, nullptr, w1r, X, kXs, l32, half, [&](int i) {
-                if (i < 8) {
-                    pack_pair(acc1, 2 * i);
-                    pack_pair(acc1, 2 * i + 1);
-                    if (i & 1) pool_mfma(1, i >> 1);
-                }
-                if (i == 8) special = special || is_special();
-            });
-            // layer 1, rows 32..63.  Meanwhile: hidden layer 1 of rows 0..31 to LDS, the previous tile's sums to memory.
-            layer_from<kK1 / 16>(acc1, nullptr, w1r, X + 32 * kXs, kXs, l32, half, [&](int i) {
-                if (i >= 4 && i < 20 && !(i & 1)) park_hidden(acc0, (i - 4) >> 1, H1, kHs, wave, l32, half);
-                if (i >= 1 && i < 17 && (i & 1)) pool_store(i >> 1);
-                if (i == 17) note_special();
-                if (i == 18) {
-                    pool_start = cur.start;
-                    pool_count = cur.count;
-                    pool_to = cur.cand >= 0 ? 2u * ((uint32_t)cur.cand * kH + 64 * wave + 4 * half) : kNowhere;
-                }
-                if (i >= 18) member[i - 18] = member_fragment((uint32_t)(rows_of(cur) >> (i >= 20 ? 32 : 0)), (i - 18) & 1, half);
-            });
-            __syncthreads();   // rows 0..31 of H1 complete; X no longer read
-            // layer 2, rows 0..31.  Meanwhile: hidden layer 1 of rows 32..63 and the next tile's features to LDS, and what
-            // the rows of the tile after next are.
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)   // (no instruction: the register class, and in the first tile the wait for the matrix)
-                asm volatile("" : "+a"(w2r[nt][0]), "+a"(w2r[nt][1]), "+a"(w2r[nt][2]), "+a"(w2r[nt][3]), "+a"(w2r[nt][4]), "+a"(w2r[nt][5]),
-                                  "+a"(w2r[nt][6]), "+a"(w2r[nt][7]), "+a"(w2r[nt][8]), "+a"(w2r[nt][9]), "+a"(w2r[nt][10]), "+a"(w2r[nt][11]),
-                                  "+a"(w2r[nt][12]), "+a"(w2r[nt][13]), "+a"(w2r[nt][14]), "+a"(w2r[nt][15]));
-            static_assert(kH / 16 == 16, "the second layer's sixteen depth steps are listed above");
-            Tile after = nxt;
-            layer_rows<kH / 16>(acc0, b2r, w2r, H1, kHs, l32, half, [&](int i) {
-                if (i & 1) {
-                    if (i >= 2 * (kH / 16 - kXLoads)) park_piece((i - 2 * (kH / 16 - kXLoads)) >> 1);   // as late as the layer allows
-                    return;
-                }
-                if (i < 16) park_hidden(acc1, i >> 1, H1 + 32 * kHs, kHs, wave, l32, half);
-                if (i == 18) after = tile_at(nxt.start + nxt.count);
-                if (i == 26 && wave == 0) write_rows(after);
-            });
-            __syncthreads();   // rows 32..63 of H1, X (the next tile's rows) and the rows' table complete
-            // layer 2, rows 32..63.  Meanwhile: the sums of rows 0..31, and the requests for the rows of the tile after next.
-            layer_rows<kH / 16>(acc1, b2r, w2r, H1 + 32 * kHs, kHs, l32, half, [&](int i) {
-                if (!(i & 1) && i < 16) {
-                    pack_pair(acc0, i);
-                    pack_pair(acc0, i + 1);
-                }
-                if ((i & 3) == 3 && i < 16) pool_mfma(0, i >> 2);
-                if (i == 0) fetch_read();
-                if ((i & 1) && i < 2 * kXLoads) fetch_issue(i >> 1);
-                if (i == 18) special = is_special();
-            });
-            cur = nxt;
-            nxt = after;
-        }
-        // the last tile's second half
-#pragma unroll
-        for (int pair = 0; pair < 16; ++pair) pack_pair(acc1, pair);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) pool_mfma(1, q);
-        special = special || is_special();
-#pragma unroll
-        for (int piece = 0; piece < 8; ++piece) pool_store(piece);
-        note_special();
-        // the next noted tile, if there is one
-        __syncthreads();
-        int found = -1;
-        for (int w = again >> 5; w < (n_local + 31) / 32 && found < 0; ++w) {
-            const uint32_t bits = tainted[w] & (w == again >> 5 ? ~0u << (again & 31) : ~0u);
-            if (bits) found = 32 * w + __builtin_ctz(bits);
-        }
-        if (found < 0) break;
-        begin = again = found;
-        stop = n_local;
-        most = 32;
-        const Tile t = tile_at(found);   // (the tile as it was: its first candidate names it)
-        stop = found + t.count;
-        most = 1;
-        again = stop;
+        for (int nt = 0; nt < 2; ++nt)   // (no instruction: the register class, and in the first tile the wait for the matrix)
+            asm volatile("" : "+a"(w2r[nt][0]), "+a"(w2r[nt][1]), "+a"(w2r[nt][2]), "+a"(w2r[nt][3]), "+a"(w2r[nt][4]), "+a"(w2r[nt][5]),
+                              "+a"(w2r[nt][6]), "+a"(w2r[nt][7]), "+a"(w2r[nt][8]), "+a"(w2r[nt][9]), "+a"(w2r[nt][10]), "+a"(w2r[nt][11]),
+                              "+a"(w2r[nt][12]), "+a"(w2r[nt][13]), "+a"(w2r[nt][14]), "+a"(w2r[nt][15]));
+        static_assert(kH / 16 == 16, "the second layer's sixteen depth steps are listed above");
+        Tile after = nxt;
+        layer<kH / 16>(acc0, w2r, H1, kHs, l32, half, [&](int i) {
+            pool_gap(2 * (kK1 / 16) + i);
+            if (i & 1) {
+                if (i >= 2 * (kH / 16 - kXLoads)) park_piece((i - 2 * (kH / 16 - kXLoads)) >> 1);   // as late as the layer allows
+                return;
+            }
+            if (i < 16) park_hidden(acc1, i >> 1, H1 + 32 * kHs, kHs, wave, l32, half);
+            if (i == 18) after = tile_at(nxt.start + nxt.count);
+            if (i == 20) bias_init(acc1, cst[1], wave, half);
+            if (i == 26 && wave == 0) write_rows(after);
+        });
+        pool_rest(kPoolAhead);
+        pool_count = cur.count;
+        pool_rows = cur.first | ((cur.end - cur.first) << 8);
+        pool_to = cur.cand >= 0 ? 2u * (uint32_t)cur.cand * (uint32_t)kH : kNowhere;
+        wave_lds_fence();
+        __syncthreads();   // rows 32..63 of H1, X (the next tile's rows) and the rows' table complete
+        // layer 2, rows 32..63.  Meanwhile: the second hidden layer of rows 0..31 to LDS, and the requests for the rows of the
+        // tile after next.
+        layer<kH / 16>(acc1, w2r, H1 + 32 * kHs, kHs, l32, half, [&](int i) {
+            if (!(i & 1) && i < 16) park_hidden(acc0, i >> 1, H2, kHs, wave, l32, half);
+            if (i == 0) fetch_read();
+            if ((i & 1) && i < 2 * kXLoads) fetch_issue(i >> 1);
+            if (i == 26) bias_init(acc0, cst[0], wave, half);
+        });
+        cur = nxt;
+        nxt = after;
     }
+    // the last tile's second half
+#pragma unroll
+    for (int piece = 0; piece < 8; ++piece) park_hidden(acc1, piece, H2 + 32 * kHs, kHs, wave, l32, half);
+    wave_lds_fence();
+    pool_rest(0);
 }
 
 // ---- dataflow branch -------------------------------------------------------------------------------------------------
-// A wavefront works on tiles of 32 block slots: as many whole candidates as fit, so slots beyond n_blk cost nothing.  The
-// whole chain stays in registers.  A layer computed transposed (weights as the A operand) leaves a lane 16 units of its
-// row, computed straight (rows as the A operand) 16 rows of its unit; rounded in pairs, either is the operand of the next
-// product as it stands, as long as the other operand numbers the depth the same way (the weight matrices are read in that
-// order once).  So:
-//   E (both ways) from the features; Q, K (units per lane) and V (rows per lane) from E; the scores with a query per lane and
-//   its 32 keys over two lanes: keys of other candidates are masked, the softmax is lane-local but for one exchange; the
-//   binary32 attention weights go to the matrix cores as three bfloat16 pieces (p = hi + mid + lo exactly, products exact,
-//   binary32 sums); O rounded is the operand of Wo; Z = Wo O, in three pieces again, and E are summed over each candidate's
-//   rows by the 0/1 matrix of the statement branch.
-// 0 times an infinity or a NaN of one candidate would reach the others of its tile: a tile whose sums hold a NaN is done
-// again candidate by candidate.
-// Bound: vector instructions (the softmax, the pieces).  Eight slots per candidate, softmax and products with the weights on
-// the vector ALU and every stage through LDS took 170 us where this takes 55 (131,072 candidates, 2.8 blocks on average).
+// A wavefront works on tiles of 32 block slots, eight quads of four: a candidate of up to four blocks takes one quad, of more two
+// neighbouring ones that begin at an even quad, one of none takes no slot.  The chain stays in registers: every layer is
+// computed transposed (weights as the A operand), which leaves a lane 16 units of its row, and the rounded result is the
+// operand of the next product once the two halves of the wavefront have exchanged half of it (half 0 then holds the lower eight
+// of sixteen neighbouring units, as the weights do).  The scores come with a query per lane and the keys of one parity of
+// quads per half: four of them are the query's.  Only V goes through LDS, from which a query's lane reads its candidate's rows.
+// Every sum runs over a candidate's own slots in a fixed order, wherever in a tile they lie (softmax and pooled vectors ((0 + 1)
+// + (2 + 3)) + ((4 + 5) + (6 + 7)), the products with the attention weights one key after the other): a score is a function of
+// its candidate alone, and nothing of one candidate reaches another.
+// Bound: vector instructions and the waits between dependent stages (131,072 candidates, 2.5 blocks on average, by the counters:
+// vector ALU busy in 47 % of the cycles, matrix pipe in 12 %, two wavefronts per SIMD).
 
 constexpr int kFlowWaves = 4;                 // wavefronts per workgroup, each with tiles of its own
 constexpr int kFlowThreads = 64 * kFlowWaves;
 constexpr int kFlowGroup = 8;                 // neighbouring candidates that go to one wavefront together
 constexpr int kFlowRows = 32;
+constexpr int kFlowQuads = kFlowRows / 4;
 constexpr int kFlowBlocksPerCu = 2;
-constexpr int kDk = 32;                       // 23 padded to the MFMA depth: 1, 1, 1 meet the three pieces of the bias
+constexpr int kDk = 32;                       // 23 padded to the MFMA depth
+constexpr int kVs = kE + 8;                   // LDS row stride of V (bfloat16 elements)
 constexpr int kFlowLocalCap = 1024;           // most candidates of one wavefront in a launch
+
+// Exchanges inside a group of eight neighbouring lanes at the vector ALU's own rate: CTRL 0xB1 brings the neighbour's value
+// (lane ^ 1), 0x4E the other pair's (lane ^ 2), 0x141 mirrors the row half (lane 7 - j of the eight, i.e. the other quad).
+template <int CTRL> __device__ __forceinline__ float across8(float x)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float sum4(float x)
+{
+    x += across8<0xB1>(x);
+    x += across8<0x4E>(x);
+    return x;
+}
+
+// Pairs of neighbouring units as a product leaves them (units 8 (p / 2) + 4 half + 2 (p % 2) and the next, p = 0..3) as an operand:
+// units 8 half + 2 p and the next.
+__device__ __forceinline__ bf16x8 operand_of(uint32_t p0, uint32_t p1, uint32_t p2, uint32_t p3)
+{
+    const auto a = __builtin_amdgcn_permlane32_swap(p0, p2, false, false), b = __builtin_amdgcn_permlane32_swap(p1, p3, false, false);
+    return __builtin_bit_cast(bf16x8, u32x4{a[0], b[0], a[1], b[1]});
+}
+__device__ __forceinline__ bf16x8 plain_operand(const floatx16& a, int q)   // registers 8 q .. 8 q + 7
+{
+    return operand_of(bf16x2_of(a[8 * q], a[8 * q + 1]), bf16x2_of(a[8 * q + 2], a[8 * q + 3]), bf16x2_of(a[8 * q + 4], a[8 * q + 5]),
+                      bf16x2_of(a[8 * q + 6], a[8 * q + 7]));
+}
 
 __global__ void __launch_bounds__(kFlowThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 pacm_flow_kernel(const float* __restrict__ flow, const int32_t* __restrict__ n_blk, int32_t n_d, const uint16_t* __restrict__ We,
                  const float* __restrict__ be, const uint16_t* __restrict__ Wq, const uint16_t* __restrict__ Wk,
                  const uint16_t* __restrict__ Wv, const uint16_t* __restrict__ Wo, uint16_t* __restrict__ v_d)
 {
-    __shared__ uint8_t counts[kFlowWaves][kFlowLocalCap];       // blocks of the wavefront's candidates
-    __shared__ uint32_t row_tab[kFlowWaves][2][kFlowRows];      // what the rows of a tile are (two tiles are in the making)
+    __shared__ uint8_t counts[kFlowWaves][kFlowLocalCap];            // blocks of the wavefront's candidates
+    __shared__ uint32_t quad_tab[kFlowWaves][2][kFlowQuads];         // what the quads of a tile are (two tiles are in the making)
     __shared__ __attribute__((aligned(16))) u32x4 wv_lds[2][kE / 16][64], wo_lds[2][kE / 16][64];   // Wv's and Wo's fragments (registers hold the others)
+    __shared__ __attribute__((aligned(16))) __bf16 v_lds[kFlowWaves][(kFlowRows + 1) * kVs];        // a tile's V, and a row of zeros
+    __shared__ __attribute__((aligned(16))) float be_lds[kE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, l32 = lane & 31;
 
@@ -496,33 +438,25 @@ pacm_flow_kernel(const float* __restrict__ flow, const int32_t* __restrict__ n_b
     auto global_of = [&](int l) -> int { return kFlowGroup * ((l / kFlowGroup) * group_stride + my_first) + l % kFlowGroup; };
     for (int l = lane; l < n_local; l += 64) counts[wave][l] = (uint8_t)clamp8(n_blk[global_of(l)]);
 
-    // Weights, lane (l32, half): row 32 nt + l32 of the matrix.  We: eight depths 16 ks + 8 half + j (the features' order).
-    // The others: the order in which a lane holds the units of a product, 16 ks + 8 (j / 4) + 4 half + j % 4.
+    // Weights as A operands, lane (l32, half): eight depths 16 ks + 8 half + j of row 32 nt + l32.
     bf16x8 wer[2][kDk / 16], wqr[2][kE / 16], wkr[2][kE / 16];
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
         const int n = 32 * nt + l32;
-        const Pieces b = split3(be[n]);
 #pragma unroll
         for (int ks = 0; ks < kDk / 16; ++ks) {
             uint32_t pk[4];
 #pragma unroll
             for (int p = 0; p < 4; ++p) {
-                uint32_t two[2];
-#pragma unroll
-                for (int e = 0; e < 2; ++e) {
-                    const int k0 = 16 * ks + 8 * half + 2 * p + e;
-                    two[e] = k0 < kD ? (uint32_t)We[n * kD + (k0 < kD ? k0 : 0)] : k0 == kD ? b.hi : k0 == kD + 1 ? b.mid : k0 == kD + 2 ? b.lo : 0u;
-                }
-                pk[p] = two[0] | (two[1] << 16);
+                const int k0 = 16 * ks + 8 * half + 2 * p;
+                const uint32_t lo = k0 < kD ? We[n * kD + k0] : 0u, hi = k0 + 1 < kD ? We[n * kD + k0 + 1] : 0u;
+                pk[p] = lo | (hi << 16);
             }
             wer[nt][ks] = __builtin_bit_cast(bf16x8, u32x4{pk[0], pk[1], pk[2], pk[3]});
         }
         auto fragment = [&](const uint16_t* W, int ks) {
-            const uint16_t* r = W + (size_t)n * kE + 16 * ks + 4 * half;
-            typedef u32x2 u32x2_a2 __attribute__((aligned(2)));
-            const u32x2 lo = *reinterpret_cast<const u32x2_a2*>(r), hi = *reinterpret_cast<const u32x2_a2*>(r + 8);
-            return u32x4{lo[0], lo[1], hi[0], hi[1]};
+            typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+            return u32x4(*reinterpret_cast<const u32x4_a2*>(W + (size_t)n * kE + 16 * ks + 8 * half));
         };
 #pragma unroll
         for (int ks = 0; ks < kE / 16; ++ks) {
@@ -532,13 +466,14 @@ pacm_flow_kernel(const float* __restrict__ flow, const int32_t* __restrict__ n_b
             if (wave == 1) wv_lds[nt][ks][lane] = fragment(Wv, ks);
         }
     }
+    if (threadIdx.x < kE) be_lds[threadIdx.x] = be[threadIdx.x];
+    __bf16* const V = v_lds[wave];
+    for (int i = lane; i < kVs; i += 64) V[kFlowRows * kVs + i] = (__bf16)0.f;
     __syncthreads();   // (the only one: from here on every wavefront goes its own way)
 
     struct Tile {
         int start, count;
-        uint32_t first, end;   // rows of the lane's (l32-th) candidate
-        int cand;              // its place, -1 past the last
-        uint32_t row;          // of the lane's (l32-th) row: first and end row of its candidate (8 bits each)
+        uint32_t quad;         // of the lane's (l32-th) row: its candidate's first quad | blocks << 8 | place among the tile's candidates << 16
         f32x4 x[4];            // the lane's eight plus eight (half 1: eight) features of that row
     };
     auto zero16 = []() {
@@ -547,31 +482,37 @@ pacm_flow_kernel(const float* __restrict__ flow, const int32_t* __restrict__ n_b
         for (int i = 0; i < 16; ++i) z[i] = 0.f;
         return z;
     };
-    // The tile from local candidate `start` on, at most `most` candidates; its features are requested.
-    auto tile_at = [&](int start, int most, int buffer) {
+    // The tile from local candidate `start` on; its features are requested.
+    auto tile_at = [&](int start, int buffer) {
         Tile t;
         t.start = start;
-        const bool there = l32 < most && start + l32 < n_local;
-        const uint32_t n = there && half == 0 ? counts[wave][start + l32] : 0u;
-        const uint32_t upto = wave_inclusive_sum(n);   // (lanes 32..63 add nothing)
-        const uint32_t n_all = (uint32_t)__shfl((int)n, l32, 64), upto_all = (uint32_t)__shfl((int)upto, l32, 64);
-        const bool in = there && upto_all <= (uint32_t)kFlowRows;
-        t.count = (int)__popcll(__ballot(in) & 0xFFFFFFFFull);
-        t.cand = in ? global_of(start + l32) : -1;
-        t.end = in ? upto_all : 0u;
-        t.first = in ? upto_all - n_all : 0u;
-        uint32_t* tab = row_tab[wave][buffer];
-        if (half == 0) tab[l32] = 0u;
+        const bool there = start + l32 < n_local;
+        const uint32_t n = there ? counts[wave][start + l32] : 0u;
+        // places: a candidate of two quads begins at an even one, so the parity before it is that of the candidates of one
+        // quad since the last of two
+        const uint32_t one = (uint32_t)__ballot(n >= 1u && n <= 4u), two = (uint32_t)__ballot(n > 4u), lower = (1u << l32) - 1u;
+        const uint32_t behind = two & lower ? ~0u << (31 - __clz((int)(two & lower))) : ~0u;
+        const uint32_t padded = (uint32_t)__ballot(n > 4u && (__popc(one & lower & behind) & 1)) & (lower | (1u << l32));
+        const uint32_t first = (uint32_t)(__popc(one & lower) + 2 * __popc(two & lower) + __popc(padded)), quads = n == 0u ? 0u : n <= 4u ? 1u : 2u;
+        const bool in = there && first + quads <= (uint32_t)kFlowQuads;
+        t.count = (int)__popc((uint32_t)__ballot(in));   // (the places grow, so the candidates that fit are the first ones)
+        uint32_t* tab = quad_tab[wave][buffer];
+        if (lane < kFlowQuads) tab[lane] = 0u;
         wave_lds_fence();
-        if (half == 0) {
+        if (in && half == 0) {
+            const uint32_t what = first | (n << 8) | ((uint32_t)l32 << 16);
+            if (quads >= 1u) tab[first] = what;
+            if (quads == 2u) tab[first + 1] = what;
+        }
+        if (in && quads == 0u) {   // no blocks: its vector is zero
+            u32x4* to = reinterpret_cast<u32x4*>(v_d + (size_t)global_of(start + l32) * kE + 32 * half);
 #pragma unroll
-            for (int b = 0; b < kT; ++b)   // (candidate of the tile, slot), first and end row; an empty row has first = end = 0
-                if (t.first + (uint32_t)b < t.end) tab[t.first + (uint32_t)b] = t.first | (t.end << 8) | ((uint32_t)(l32 * kT + b) << 16);
+            for (int i = 0; i < 4; ++i) to[i] = u32x4{0u, 0u, 0u, 0u};
         }
         wave_lds_fence();
-        t.row = tab[l32];
-        const int at = (int)(t.row >> 16);
-        const int64_t src = (t.row & 0xFFFFu) == 0u ? 0 : (int64_t)global_of(start + at / kT) * kT + at % kT;
+        t.quad = tab[l32 >> 2];
+        const uint32_t slot = (uint32_t)l32 - 4u * (t.quad & 0xFFu);
+        const int64_t src = slot < ((t.quad >> 8) & 0xFFu) ? (int64_t)global_of(start + (int)(t.quad >> 16)) * kT + slot : 0;
         typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
         const float* r = flow + src * kD;
         t.x[0] = *reinterpret_cast<const f32x4_a4*>(r + 8 * half);
@@ -581,176 +522,165 @@ pacm_flow_kernel(const float* __restrict__ flow, const int32_t* __restrict__ n_b
         return t;
     };
 
-    int alone_until = 0;   // candidates before this one are done one by one
-    Tile cur = tile_at(0, kFlowRows, 0);
+    Tile cur = tile_at(0, 0);
     int buffer = 1;
     while (cur.count > 0) {
-        const int next = cur.start + cur.count;
-        const Tile nxt = tile_at(next, next < alone_until ? 1 : kFlowRows, buffer);
+        const Tile nxt = tile_at(cur.start + cur.count, buffer);
         buffer ^= 1;
-        const uint32_t row_first = cur.row & 0xFFu, row_end = (cur.row >> 8) & 0xFFu;
-        const bool row_there = row_end != 0u;
-        // features, bfloat16, with 1, 1, 1 at depths 23..25
+        const int first_quad = (int)(cur.quad & 0xFFu), n_mine = (int)((cur.quad >> 8) & 0xFFu), slot = l32 - 4 * first_quad;
+        const bool row_there = slot < n_mine;   // (a quad that is not taken has n_mine = 0)
+        // features, bfloat16, depth 23..31 zero
         bf16x8 d[2];
         {
             const uint32_t there = row_there ? ~0u : 0u;
-            auto two = [](float a, float b) { return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2)); };
-            const u32x4 d0 = {two(cur.x[0][0], cur.x[0][1]) & there, two(cur.x[0][2], cur.x[0][3]) & there, two(cur.x[1][0], cur.x[1][1]) & there,
-                              two(cur.x[1][2], cur.x[1][3]) & there};
-            u32x4 d1 = {two(cur.x[2][0], cur.x[2][1]) & there, two(cur.x[2][2], cur.x[2][3]) & there, two(cur.x[3][1], cur.x[3][2]) & there,
-                        (two(cur.x[3][3], 0.f) & there) | 0x3F800000u};
-            d1[0] = half ? 0x3F803F80u : d1[0];
-            d1[1] = half ? 0u : d1[1];
-            d1[2] = half ? 0u : d1[2];
-            d1[3] = half ? 0u : d1[3];
+            const u32x4 d0 = {bf16x2_of(cur.x[0][0], cur.x[0][1]) & there, bf16x2_of(cur.x[0][2], cur.x[0][3]) & there,
+                              bf16x2_of(cur.x[1][0], cur.x[1][1]) & there, bf16x2_of(cur.x[1][2], cur.x[1][3]) & there};
+            const uint32_t low = half ? 0u : there;
+            const u32x4 d1 = {bf16x2_of(cur.x[2][0], cur.x[2][1]) & low, bf16x2_of(cur.x[2][2], cur.x[2][3]) & low,
+                              bf16x2_of(cur.x[3][1], cur.x[3][2]) & low, bf16x2_of(cur.x[3][3], 0.f) & low};
             d[0] = __builtin_bit_cast(bf16x8, d0);
             d[1] = __builtin_bit_cast(bf16x8, d1);
         }
-        const uint32_t my_rows = (uint32_t)(low_bits(cur.end) & ~low_bits(cur.first));
-        bf16x8 member[2];
+        uint32_t e_pair[16];   // E as the product leaves it: pairs of units 32 nt + 8 (p / 2) + 4 half + 2 (p % 2), p = index - 8 nt
+        bf16x8 e[kE / 16];     // ... and as an operand
 #pragma unroll
-        for (int q = 0; q < 2; ++q) member[q] = member_fragment(my_rows, q, half);
-
-        floatx16 sum[2];   // v_d of the lane's candidate
-        bf16x8 e[kE / 16];   // E, units per lane: operand ks = 2 nt + hq
-        {
-            floatx16 acc[2];
+        for (int nt = 0; nt < 2; ++nt) {
+            floatx16 acc;
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {   // rows per lane, summed right away
-                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[0], wer[nt][0], zero16(), 0, 0, 0);
-                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(d[1], wer[nt][1], acc[nt], 0, 0, 0);
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 b = *reinterpret_cast<const f32x4*>(&be_lds[32 * nt + 8 * g + 4 * half]);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[4 * g + j] = b[j];
             }
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wer[nt][0], d[0], acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wer[nt][1], d[1], acc, 0, 0, 0);
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
+            for (int p = 0; p < 8; ++p) e_pair[8 * nt + p] = relu_bf16x2(acc[2 * p], acc[2 * p + 1]);
 #pragma unroll
-                for (int hq = 0; hq < 2; ++hq) {
-                    const bf16x8 f = relu_fragment(acc[nt], hq);
-                    sum[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f, member[hq], hq == 0 ? zero16() : sum[nt], 0, 0, 0);
-                }
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {   // units per lane
-                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wer[nt][0], d[0], zero16(), 0, 0, 0);
-                acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wer[nt][1], d[1], acc[nt], 0, 0, 0);
+            for (int hq = 0; hq < 2; ++hq) {
+                const int p = 8 * nt + 4 * hq;
+                e[2 * nt + hq] = operand_of(e_pair[p], e_pair[p + 1], e_pair[p + 2], e_pair[p + 3]);
             }
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int hq = 0; hq < 2; ++hq) e[2 * nt + hq] = relu_fragment(acc[nt], hq);
         }
         floatx16 sc;
         {
             bf16x8 q[kE / 16], k[kE / 16];
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) {
-                floatx16 aq = zero16(), ak = zero16();
+                floatx16 aq = zero16(), ak = zero16(), av = zero16();
 #pragma unroll
                 for (int ks = 0; ks < kE / 16; ++ks) {
                     aq = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wqr[nt][ks], e[ks], aq, 0, 0, 0);
                     ak = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wkr[nt][ks], e[ks], ak, 0, 0, 0);
+                    av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wv_lds[nt][ks][lane]), e[ks], av, 0, 0, 0);
+                }
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const u32x2 o = {bf16x2_of(av[4 * g], av[4 * g + 1]), bf16x2_of(av[4 * g + 2], av[4 * g + 3])};
+                    *reinterpret_cast<u32x2*>(&V[l32 * kVs + 32 * nt + 8 * g + 4 * half]) = o;
                 }
 #pragma unroll
                 for (int hq = 0; hq < 2; ++hq) {
-                    q[2 * nt + hq] = plain_fragment(aq, hq);
-                    k[2 * nt + hq] = plain_fragment(ak, hq);
+                    q[2 * nt + hq] = plain_operand(aq, hq);
+                    k[2 * nt + hq] = plain_operand(ak, hq);
                 }
             }
             sc = zero16();
 #pragma unroll
             for (int ks = 0; ks < kE / 16; ++ks) sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k[ks], q[ks], sc, 0, 0, 0);   // lane: query l32, keys 8 (i / 4) + 4 half + i % 4
         }
-        bf16x8 v[2][2];   // V, rows per lane: [nt][hq]
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            floatx16 av = zero16();
-#pragma unroll
-            for (int ks = 0; ks < kE / 16; ++ks) av = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e[ks], __builtin_bit_cast(bf16x8, wv_lds[nt][ks][lane]), av, 0, 0, 0);
-#pragma unroll
-            for (int hq = 0; hq < 2; ++hq) v[nt][hq] = plain_fragment(av, hq);
-        }
-        // softmax over the query's own keys
-        float scale;
+        wave_lds_fence();
+        // Softmax.  Of the candidate's one or two quads of keys this half holds the one of its parity (four registers), the other
+        // half the other.
+        float weight[kT];   // of the candidate's keys in order; 0 past its last
         {
-            const uint32_t own = (uint32_t)(low_bits(row_end) & ~low_bits(row_first)) >> (4 * half);   // bit 8 (i / 4) + i % 4: register i's key is one
-            float mx = -__builtin_inff();
+            const int mine = first_quad + ((first_quad ^ half) & 1), key0 = 4 * (mine - first_quad);
+            const int left = n_mine - key0;   // of the quad's keys, those that are there
+            float p[4], mx = -__builtin_inff();
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                sc[i] = (own >> (8 * (i / 4) + i % 4)) & 1u ? sc[i] * 0.125f : -__builtin_inff();
-                mx = fmaxf(mx, sc[i]);
+            for (int r = 0; r < 4; ++r) {
+                const int b = mine >> 1;
+                const float s = b == 0 ? sc[r] : b == 1 ? sc[4 + r] : b == 2 ? sc[8 + r] : sc[12 + r];
+                p[r] = r < left ? s * 0.125f : -__builtin_inff();
+                mx = fmaxf(mx, p[r]);
             }
             mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-            mx = row_there ? mx : 0.f;
-            float den = 0.f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                sc[i] = (own >> (8 * (i / 4) + i % 4)) & 1u ? expf(sc[i] - mx) : 0.f;
-                den += sc[i];
-            }
+            for (int r = 0; r < 4; ++r) p[r] = r < left ? expf(p[r] - mx) : 0.f;
+            float den = (p[0] + p[1]) + (p[2] + p[3]);
             den += __shfl_xor(den, 32, 64);
-            scale = row_there ? 1.0f / den : 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const float w = n_mine > 0 ? p[r] / den : 0.f, other = __shfl_xor(w, 32, 64);
+                weight[r] = key0 == 0 ? w : other;
+                weight[4 + r] = key0 == 0 ? other : w;
+            }
         }
-        // O^T[unit][query] = (sum over keys of V p) / den, the weights in three bfloat16 pieces
+        // o = sum over the keys of weight v in binary32, one key after the other; the lane has its query's units 16 ks + 8 half ..
         bf16x8 o[kE / 16];
         {
-            floatx16 acc[2];
+            float acc[kE / 16][8];
 #pragma unroll
-            for (int hq = 0; hq < 2; ++hq) {
-                bf16x8 piece[3];
-                split_fragment(sc, hq, piece);
+            for (int ks = 0; ks < kE / 16; ++ks)
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt)
+                for (int j = 0; j < 8; ++j) acc[ks][j] = 0.f;
+            const bool two_quads = __ballot(n_mine > 4) != 0ull;
+            const __bf16* const own = V + (4 * first_quad) * kVs + 8 * half;
+            const __bf16* const none = V + kFlowRows * kVs + 8 * half;
+            auto add_keys = [&](int from) {
 #pragma unroll
-                    for (int p = 0; p < 3; ++p)
-                        acc[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v[nt][hq], piece[2 - p], hq == 0 && p == 0 ? zero16() : acc[nt], 0, 0, 0);
-            }
+                for (int j = from; j < from + 4; ++j) {
+                    const __bf16* row = j < n_mine ? own + j * kVs : none;
 #pragma unroll
-            for (int nt = 0; nt < 2; ++nt) {
+                    for (int ks = 0; ks < kE / 16; ++ks) {
+                        const u32x4 v = *reinterpret_cast<const u32x4*>(row + 16 * ks);
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[nt][i] *= scale;
+                        for (int c = 0; c < 4; ++c) {
+                            acc[ks][2 * c] = __builtin_fmaf(weight[j], __uint_as_float(v[c] << 16), acc[ks][2 * c]);
+                            acc[ks][2 * c + 1] = __builtin_fmaf(weight[j], __uint_as_float(v[c] & 0xFFFF0000u), acc[ks][2 * c + 1]);
+                        }
+                    }
+                }
+            };
+            add_keys(0);
+            if (two_quads) add_keys(4);
 #pragma unroll
-                for (int hq = 0; hq < 2; ++hq) o[2 * nt + hq] = plain_fragment(acc[nt], hq);
+            for (int ks = 0; ks < kE / 16; ++ks) {
+                const u32x4 f = {bf16x2_of(acc[ks][0], acc[ks][1]), bf16x2_of(acc[ks][2], acc[ks][3]), bf16x2_of(acc[ks][4], acc[ks][5]),
+                                 bf16x2_of(acc[ks][6], acc[ks][7])};
+                o[ks] = __builtin_bit_cast(bf16x8, f);
             }
         }
-        // Z = O Wo^T, rows per lane, in three pieces into the sums
+        // z = e + Wo o, summed over the candidate's blocks: every lane of its quads then holds the sums, and lane j of the first
+        // quad stores the units 32 nt + 8 j + 4 half ..
+        const bool stores = n_mine > 0 && (l32 >> 2) == first_quad;
+        uint16_t* const to = v_d + (size_t)(stores ? global_of(cur.start + (int)(cur.quad >> 16)) : 0) * kE + 8 * (l32 & 3) + 4 * half;
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
             floatx16 z = zero16();
 #pragma unroll
-            for (int ks = 0; ks < kE / 16; ++ks) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(o[ks], __builtin_bit_cast(bf16x8, wo_lds[nt][ks][lane]), z, 0, 0, 0);
+            for (int ks = 0; ks < kE / 16; ++ks) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, wo_lds[nt][ks][lane]), o[ks], z, 0, 0, 0);
+            f32x4 run = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int hq = 0; hq < 2; ++hq) {
-                bf16x8 piece[3];
-                split_fragment(z, hq, piece);
-#pragma unroll
-                for (int p = 0; p < 3; ++p) sum[nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(piece[2 - p], member[hq], sum[nt], 0, 0, 0);
+            for (int i = 0; i < 16; ++i) {
+                const uint32_t pair = e_pair[8 * nt + i / 2];
+                const float e_res = __uint_as_float(i & 1 ? pair & 0xFFFF0000u : pair << 16);
+                float sum = sum4(row_there ? e_res + z[i] : 0.f);
+                const float both = sum + across8<0x141>(sum);
+                sum = n_mine > 4 ? both : sum;
+                run[i & 3] = (l32 & 3) == i / 4 ? sum : run[i & 3];
             }
-        }
-        float any = 0.f;   // NaN if one of the sums is (opposite infinities add up to one too: such a tile is merely done twice)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) any += sum[nt][i];
-        if (cur.count > 1 && __ballot(any != any) != 0ull) {
-            alone_until = next;
-            cur = tile_at(cur.start, 1, buffer);
-            buffer ^= 1;
-            continue;
-        }
-        if (cur.cand >= 0) {
-            uint16_t* to = v_d + (size_t)cur.cand * kE + 4 * half;
-#pragma unroll
-            for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-                for (int g = 0; g < 4; ++g) store_pooled(sum[nt], g, to + 32 * nt + 8 * g);
+            if (stores) *reinterpret_cast<u32x2*>(to + 32 * nt) = u32x2{bf16x2_of(run[0], run[1]), bf16x2_of(run[2], run[3])};
         }
         cur = nxt;
     }
 }
 
 // ---- head ------------------------------------------------------------------------------------------------------------
-// The two 32-row halves of a tile run one after the other on the matrix cores; rounding, the output dot product (matrix cores
-// as well, see last_layer_mfma) and the stores of one half, and the next tile's way into LDS, are issued between the MFMAs
-// of the other.  Two tiles' operands in LDS: one barrier per tile.  Bound: memory at scale (640 bytes per candidate), weights
-// and launch for small sets.
+// The two 32-row halves of a tile run one after the other on the matrix cores; rounding, the output dot product (binary32, in
+// the order of a lane's units) and the stores of one half, and the next tile's way into LDS, are issued between the MFMAs
+// of the other.  Two tiles' operands in LDS, two barriers per tile.  131,072 candidates: 640 bytes each at 3 TB/s, matrix pipe
+// busy in 27 % of the cycles, vector ALU in 21 %; weights and launch for small sets.
 
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ v_d, int32_t n_d, const uint16_t* __restrict__ Wh,
@@ -758,7 +688,6 @@ pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ 
 {
     __shared__ __attribute__((aligned(16))) __bf16 U[2][kTM * kUs];   // a tile's concatenated pooled vectors
     __shared__ __attribute__((aligned(16))) float cst[kH];
-    __shared__ __attribute__((aligned(16))) uint16_t wo_lds[kH];
     __shared__ float red[2][4][kTM];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, l32 = lane & 31;
@@ -784,9 +713,12 @@ pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ 
     for (int i = 0; i < kPieces; ++i) fetch_piece(tile, i);
     bf16x8 whr[2][kU / 16];
     load_slices<kU / 16, kU / 16, u32x4>(whr, Wh, kU, wave, l32, half);
-    static_assert(kThreads == kH, "one thread per hidden unit");
     cst[threadIdx.x] = bh[threadIdx.x];
-    wo_lds[threadIdx.x] = wo[threadIdx.x];
+    float wor[2][16];   // this lane's output weights, in accumulator order
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) wor[nt][i] = __uint_as_float((uint32_t)wo[64 * wave + 32 * nt + 8 * (i / 4) + 4 * half + (i % 4)] << 16);
 #pragma unroll
     for (int i = 0; i < kPieces; ++i) park_piece(0, i);
 #pragma unroll
@@ -794,18 +726,26 @@ pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ 
     __syncthreads();
     floatx16 bhr[2];
     bias_init(bhr, cst, wave, half);
-    bf16x8 wof[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) wof[q] = last_layer_weights(wo_lds + 64 * wave, q, l32, half);
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int ks = 0; ks < kU / 16; ++ks) asm volatile("" : "+a"(whr[nt][ks]));
 
-    floatx16 acc0[2], acc1[2], y0, y1;
-    uint32_t pk[16];
+    floatx16 acc0[2], acc1[2];
+    float part = 0.f;
+    // the output of a half's rows, pair by pair of a lane's units
+    auto dot_pair = [&](const floatx16(&acc)[2], int pair) {
+        const int nt = pair >> 3, p = pair & 7;
+        const uint32_t pr = relu_bf16x2(acc[nt][2 * p], acc[nt][2 * p + 1]);
+        part = __builtin_fmaf(__uint_as_float(pr << 16), wor[nt][2 * p], pair == 0 ? 0.f : part);
+        part = __builtin_fmaf(__uint_as_float(pr & 0xFFFF0000u), wor[nt][2 * p + 1], part);
+    };
+    auto dot_park = [&](int buf, int hh) {
+        part += __shfl_xor(part, 32, 64);
+        if (half == 0) red[buf][wave][32 * hh + l32] = part;
+    };
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc1[0][i] = acc1[1][i] = y0[i] = y1[i] = 0.f;
+    for (int i = 0; i < 16; ++i) acc1[0][i] = acc1[1][i] = 0.f;
     auto store_rows = [&](int t, int buf) {   // a finished tile: the four wavefronts' shares of each row
         const int cand = t * kTM + (int)threadIdx.x;
         if (threadIdx.x < kTM && cand < n_d)
@@ -815,35 +755,25 @@ pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ 
     for (; tile < n_tiles; tile += gridDim.x, buf ^= 1, ++done) {
         // rows 0..31.  Meanwhile: the output of the previous tile's rows 32..63, the next tile's vectors to LDS.
         layer_from<kU / 16>(acc0, bhr, whr, U[buf], kUs, l32, half, [&](int i) {
-            if (i < 8) {
-                last_layer_pack(acc1, 2 * i, pk);
-                last_layer_pack(acc1, 2 * i + 1, pk);
-                if (i & 1) last_layer_mfma(y1, i >> 1, wof, pk);
-            }
-            if (i == 16 && half == 0) red[buf ^ 1][wave][32 + l32] = y1[0];
+            if (i < 16) dot_pair(acc1, i);
+            if (i == 16) dot_park(buf ^ 1, 1);
             if (i >= 20 && !(i & 1)) park_piece(buf ^ 1, (i - 20) >> 1);
         });
         static_assert(kPieces == 10 && kU / 16 == 20, "the ten pieces fit the layer's last twenty gaps");
         __syncthreads();   // the next tile's vectors and the previous tile's row outputs complete
         // rows 32..63.  Meanwhile: the output of rows 0..31, the requests for the tile after next, the previous tile's scores.
         layer_from<kU / 16>(acc1, bhr, whr, U[buf] + 32 * kUs, kUs, l32, half, [&](int i) {
-            if (i < 8) {
-                last_layer_pack(acc0, 2 * i, pk);
-                last_layer_pack(acc0, 2 * i + 1, pk);
-                if (i & 1) last_layer_mfma(y0, i >> 1, wof, pk);
-            }
+            if (i < 16) dot_pair(acc0, i);
             if (i >= 8 && i < 8 + kPieces) fetch_piece(tile + 2 * (int)gridDim.x, i - 8);
-            if (i == 20 && half == 0) red[buf][wave][l32] = y0[0];
+            if (i == 20) dot_park(buf, 0);
             if (i == 24 && done > 0) store_rows(tile - (int)gridDim.x, buf ^ 1);
         });
         __syncthreads();   // this tile's buffer may be written again
     }
     // the last tile's rows 32..63
 #pragma unroll
-    for (int pair = 0; pair < 16; ++pair) last_layer_pack(acc1, pair, pk);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) last_layer_mfma(y1, q, wof, pk);
-    if (half == 0) red[buf ^ 1][wave][32 + l32] = y1[0];
+    for (int pair = 0; pair < 16; ++pair) dot_pair(acc1, pair);
+    dot_park(buf ^ 1, 1);
     __syncthreads();
     store_rows(tile - (int)gridDim.x, buf ^ 1);
 }
