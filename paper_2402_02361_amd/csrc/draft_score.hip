@@ -23,6 +23,7 @@
 //   integer-to-float conversions round to nearest even.  Quotients are correctly rounded (see div_rn).
 #include "lse_child.h"
 #include "select_common.h"
+#include "wide_load.h"
 
 #include <string.h>
 
@@ -774,7 +775,7 @@ __device__ __forceinline__ void analyze_fused(const SgDesc& d, const Symbols (&y
 }
 
 // raw holds candidates c0 .. c0 + VEC - 1; those in [c_lo, c_end) are scored (c_lo is c0 but for the thread that would read past
-// the end of a row: it reads the row's last VEC and leaves the first of them to its neighbour).
+// the end of the population: it reads its last VEC and leaves the first of them to its neighbour).
 template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST>
 __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles<Nest, VEC>& raw, int64_t c0, int64_t c_lo, int64_t c_end,
                                                  int32_t flags, const float* p2m_tab, float* __restrict__ score,
@@ -958,8 +959,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
 {
     const int64_t step = (int64_t)seg.blocks * kBlock * VEC;
     RawTiles<Nest, VEC> cur{}, nxt{};
-    // where a thread's loads start: its first candidate, or the last place from which VEC candidates still lie inside a row
-    auto inside = [&](int64_t c) { return c + VEC <= pitch ? c : pitch - VEC; };
+    auto inside = [&](int64_t c) { return load_begin<VEC>(c, n_total); };
     int64_t c0 = seg.begin + ((int64_t)(b - seg.first_block) * kBlock + threadIdx.x) * VEC;
     if constexpr (MUT) {
         static_assert(VEC == 4, "children are made four at a time");
@@ -1446,8 +1446,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
         return PRUNER_OK;
     }
 
-    // four candidates per thread wherever a row holds that many
-    const int vec = tiles_pitch >= 4 ? 4 : 1;
+    const int vec = load_width(n);
     bool in_fours = tiles_pitch % 4 == 0 && aligned(tiles, 8) && aligned(score, 16);   // every thread's candidates start at a multiple of four
     for (int32_t s = 0; s < n_sg; ++s) in_fours = in_fours && seg_off[s] % 4 == 0;
 

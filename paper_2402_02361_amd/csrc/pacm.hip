@@ -26,7 +26,7 @@
 // Measured, before = eight padded slots per candidate in either branch and binary32 pooled vectors, the same bits (statement
 // counts 3..8, blocks 0..5): 131,072 candidates: statement kernel 345 -> 212 us, dataflow 170 -> 66, head 43 -> 28, the call
 // 515 -> 296; 8,192 candidates: 29.8 -> 19.7, 23.7 -> 9.4, 10.7 -> 9.4, the call 61 -> 38.  (With the sums over rows on the matrix
-// cores too, by the rows' places in a tile, 246 and 38: two scores in a thousand then changed with the neighbours.)
+// cores too, by the rows' places in a tile, 246 and 38: one score in a thousand then changed with the neighbours.)
 #include "common.h"
 #include "mfma_tile.h"
 
@@ -378,7 +378,7 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
 // Every sum runs over a candidate's own slots in a fixed order, wherever in a tile they lie (softmax and pooled vectors ((0 + 1)
 // + (2 + 3)) + ((4 + 5) + (6 + 7)), the products with the attention weights one key after the other): a score is a function of
 // its candidate alone, and nothing of one candidate reaches another.
-// Bound: vector instructions and the waits between dependent stages (131,072 candidates, 2.5 blocks on average, by the counters:
+// Bound: vector instructions and the waits between dependent stages (131,072 candidates, 2.8 blocks on average, by the counters:
 // vector ALU busy in 47 % of the cycles, matrix pipe in 12 %, two wavefronts per SIMD).
 
 constexpr int kFlowWaves = 4;                 // wavefronts per workgroup, each with tiles of its own
