@@ -193,7 +193,8 @@ int pruner_time_dominant_draft_launch(void* start_event, void* stop_event, int64
 /*
  * Selection: for every segment the k best entries, best first, ordered by (score descending, index ascending).
  *
- *   score    device float [n]       must not hold NaN; -0.0 and +0.0 compare equal; infinities are ordinary values
+ *   score    device float [n]       -0.0 and +0.0 compare equal; infinities are ordinary values; a NaN is ordered by its bits:
+ *                                   above +infinity without the sign bit, below -infinity with it
  *   seg_off  host   [n_sg+1]        as above; every segment must hold at least k entries
  *   k                               1..PRUNER_MAX_K
  *   idx_out  device int32 [n_sg*k]  idx_out[s*k + r] = global index of rank r of segment s

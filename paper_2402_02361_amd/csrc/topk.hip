@@ -376,9 +376,10 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     const float t0 = score_of_key(low_key);
     // What happens to one entry (every lane of the wavefront calls it, `mine_to_look_at` says whether the lane holds one).
     auto look_at = [&](float x, int64_t i, bool mine_to_look_at, bool list_open) {
-        const uint32_t key = mine_to_look_at && i < hi ? key_of(x) : 0u;   // 0 is below every key of a number
-        const bool inside = key != 0u && key - lowest <= width;
-        if (key > lowest && !inside) {
+        const bool there = mine_to_look_at && i < hi;
+        const uint32_t key = key_of(x);
+        const bool inside = there && key - lowest <= width;
+        if (there && key > lowest && !inside) {
             const uint32_t at = atomicAdd(&n_gt, 1u);
             if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
         } else if (inside && list_open) {
@@ -453,10 +454,10 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
 #pragma unroll
             for (int j = 0; j < kBigPer; ++j) {
                 const int64_t i = sweep_index(row, j);
-                const uint32_t key = i < hi ? key_of(val[j]) : 0u;
-                const bool inside = key != 0u && key - lowest <= width;
-                if (__ballot(key > lowest && !inside) != 0ull) {
-                    if (key > lowest && !inside) {
+                const uint32_t key = key_of(val[j]);
+                const bool inside = i < hi && key - lowest <= width, above = i < hi && key > lowest && !inside;
+                if (__ballot(above) != 0ull) {
+                    if (above) {
                         const uint32_t at = atomicAdd(&n_gt, 1u);
                         if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
                     }
@@ -655,10 +656,11 @@ __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __rest
 #pragma unroll
             for (int j = 0; j < kBigPer; ++j) {
                 const int64_t i = sweep_index(row, j);
-                const uint32_t key = i < hi ? key_of(val[j]) : 0u;   // 0 is below every key of a number
-                const unsigned long long above = __ballot(key > T && key <= last), ties = __ballot(key == T);
+                const uint32_t key = key_of(val[j]);
+                const bool is_above = i < hi && key > T && key <= last, is_tie = i < hi && key == T;
+                const unsigned long long above = __ballot(is_above), ties = __ballot(is_tie);
                 if (above) {
-                    if (key > T && key <= last) {
+                    if (is_above) {
                         const uint32_t at = atomicAdd(&n_gt, 1u);
                         if (at < kStageCap) mine.gt[at] = compose(key, (uint32_t)i);
                     }
@@ -668,7 +670,7 @@ __global__ void __launch_bounds__(kBigThreads) settle_kernel(const float* __rest
                     const int leader = __ffsll(ties) - 1;
                     if (lane_id() == leader) base = atomicAdd(&n_tie, (uint32_t)__popcll(ties));
                     const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(ties & ((1ull << lane_id()) - 1ull));
-                    if (key == T && at < kStageCap) mine.tie[at] = (uint32_t)i;
+                    if (is_tie && at < kStageCap) mine.tie[at] = (uint32_t)i;
                 }
             }
         }
@@ -975,23 +977,24 @@ constexpr int64_t kListsMax = 32 * (int64_t)kRow;
 constexpr int kListCap = 1280;
 struct List {                 // the entries of one span at or above the bin (lies in the span's Stage)
     uint32_t count, pad;      // may exceed the capacity
-    uint64_t word[kListCap];  // in no order
+    uint64_t word[kListCap];  // in no order; where there are NaN, some below the bin may be among them
 };
 static_assert(sizeof(List) <= sizeof(Stage), "a list lies where the spans route keeps its stage");
 
-// A thread's sixteen entries of a sweep as a mask (bit j: entry j is at or above t0).
+// A thread's sixteen entries of a sweep as a mask (bit j: entry j is not below t0, which a NaN never is: the mask holds every entry
+// whose key is at or above t0's and, where there are NaN, some others; whoever needs exactly those looks at the keys).
 __device__ __forceinline__ uint32_t mask_of_sweep(const float (&val)[kBigPer], float t0, int64_t row, int64_t hi)
 {
     uint32_t mask = 0;
 #pragma unroll
-    for (int j = kBigPer - 1; j >= 0; --j) mask = 2 * mask + (val[j] >= t0 ? 1u : 0u);
+    for (int j = kBigPer - 1; j >= 0; --j) mask = 2 * mask + (val[j] < t0 ? 0u : 1u);
     if (row + kRow > hi) {   // the last sweep: entries past the end (read as 0) are none
 #pragma unroll
         for (int j = 0; j < kBigPer; ++j) mask &= sweep_index(row, j) < hi ? ~0u : ~(1u << j);
     }
     return mask;
 }
-// The smallest score at or above a key (a key beyond the infinities' names a NaN: then every number is).
+// A score that nothing with a key at or above `key` is below (a key beyond the infinities' names a NaN: then no number is below).
 __device__ __forceinline__ float threshold_of(uint32_t key)
 {
     const float t = score_of_key(key);
@@ -1017,7 +1020,7 @@ __device__ __forceinline__ void note_range(uint32_t not_least, uint32_t largest,
         not_least = a > not_least ? a : not_least;
         largest = b > largest ? b : largest;
     }
-    if (lane_id() == 0 && largest != 0u) {
+    if (lane_id() == 0 && (not_least | largest) != 0u) {
         atomicMax(&range[0], not_least);
         atomicMax(&range[1], largest);
     }
@@ -1169,7 +1172,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
             between();
         }
     }
-    while ((uint32_t)k - k_rem + in_bin > limit && width != 0u) {
+    for (int digits = 0; digits < 3 && (uint32_t)k - k_rem + in_bin > limit && width != 0u; ++digits) {   // (a bin spans 2^22 keys at most)
         const int shift = next_shift(width);
         if (!second) {
             // (its bins begin at the first bin's lowest key)
@@ -1188,7 +1191,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                     const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
                     for (uint32_t e = 0; e < cnt; e += kWave) {
                         const uint32_t key = e + lane < cnt ? (uint32_t)(from[e + lane] >> 32) : 0u;
-                        light_hist_add(hist, (key - lowest) >> shift, key != 0u && key - lowest <= width);
+                        light_hist_add(hist, (key - lowest) >> shift, e + lane < cnt && key - lowest <= width);
                     }
                 }
             } else {
@@ -1198,8 +1201,8 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                     load_sweep(seg_score, row, len, again);
 #pragma unroll
                     for (int j = 0; j < kBigPer; ++j) {
-                        const uint32_t key = sweep_index(row, j) < len ? key_of(again[j]) : 0u;
-                        light_hist_add(hist, (key - lowest) >> shift, key != 0u && key - lowest <= width);
+                        const uint32_t key = key_of(again[j]);
+                        light_hist_add(hist, (key - lowest) >> shift, sweep_index(row, j) < len && key - lowest <= width);
                     }
                 }
             }
@@ -1242,12 +1245,13 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     if constexpr (LISTS) {
         if (lists_whole) {
             for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
-                const uint32_t from_key = (tie_lists >> l) & 1ull ? lowest : lowest + 1u;
+                const bool with_ties = ((tie_lists >> l) & 1ull) != 0ull;
                 const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
                 const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
                 for (uint32_t e = 0; e < cnt; e += kWave) {
                     const uint64_t w = e + lane < cnt ? from[e + lane] : 0ull;
-                    const unsigned long long in = __ballot((uint32_t)(w >> 32) >= from_key && w != 0ull);
+                    const uint32_t key = (uint32_t)(w >> 32);
+                    const unsigned long long in = __ballot(e + lane < cnt && (with_ties ? key >= lowest : key > lowest));
                     if (in == 0ull) continue;
                     const int leader = __ffsll(in) - 1;
                     uint32_t base = 0;
@@ -1271,13 +1275,13 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
             }
         }
     } else {
-        uint64_t mask = 0;   // bit 4 g + e: entry e of group g is at or above the threshold
+        uint64_t mask = 0;   // bit 4 g + e: entry e of group g is not below the threshold
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
             if (g * 4 * kBigThreads < len) {
                 uint32_t four = 0;
 #pragma unroll
-                for (int e = 3; e >= 0; --e) four = 2 * four + (val[g][e] >= t0 ? 1u : 0u);
+                for (int e = 3; e >= 0; --e) four = 2 * four + (val[g][e] < t0 ? 0u : 1u);
                 if ((g + 1) * 4 * kBigThreads > len) {   // the segment's last groups
                     const int i = group_begin(g), begun = i < last ? i : last, left = len - i;
                     four = left <= 0 ? 0u : (four >> (i - begun)) & (left < 4 ? (1u << left) - 1u : 15u);
@@ -1299,6 +1303,31 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
     __syncthreads();
     if (!lists_whole) {
+        if (n > 0 && fill != (uint32_t)n) {
+            // The counts come from keys, the places from comparisons with a threshold: where these found more, there are NaN
+            // among the scores, and the places are collected again by key.
+            __syncthreads();
+            if (threadIdx.x == 0) fill = 0;
+            __syncthreads();
+#pragma unroll 1
+            for (int row = 0; row < len; row += kRow) {
+                float again[kBigPer];
+                load_sweep(seg_score, row, len, again);
+                uint32_t mask = 0;
+#pragma unroll
+                for (int j = 0; j < kBigPer; ++j) {
+                    const uint32_t key = key_of(again[j]);
+                    mask |= sweep_index(row, j) < len && (ties_apart ? key > lowest : key >= lowest) ? 1u << j : 0u;
+                }
+                uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
+                while (mask) {
+                    if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, __ffs(mask) - 1);
+                    mask &= mask - 1;
+                    ++at;
+                }
+            }
+            __syncthreads();
+        }
         for (int e = threadIdx.x; e < n; e += kBigThreads) {
             const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
             sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
