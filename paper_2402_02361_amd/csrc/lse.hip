@@ -744,9 +744,10 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
     L.fresh_aos = take(cols * kAosSlots * sizeof(uint16_t));
     L.aos = take(cols * kAosSlots * sizeof(uint16_t));
     L.aos_b = take(cols * kAosSlots * sizeof(uint16_t));   // S_spec's records, in turns
-    // a population that may take the short route has its children as records
-    const bool may_be_short = k <= kShortK && n <= (int64_t)n_sg * kShortMax;
-    L.children = take((may_be_short ? (size_t)n : 0) * kAosSlots * sizeof(uint16_t));
+    // The short route has its children as records.  The room is there whatever the route: a workspace for more candidates or a
+    // larger k serves every smaller call.
+    const int64_t most_short = (int64_t)n_sg * kShortMax;
+    L.children = take((size_t)(n < most_short ? n : most_short) * kAosSlots * sizeof(uint16_t));
     L.total = off;
     return L;
 }

@@ -48,6 +48,18 @@ def test_workspace_sizes_grow_with_the_problem():
     assert P.workspace_bytes(99, 1, 1, 1) == 0
 
 
+def test_a_workspace_serves_every_smaller_call():
+    """A tuner allocates once for its largest population and its largest k: no smaller one needs more."""
+    sizes = [1, 300, 4096, 20000, 32767, 32768, 32769, 65536, 65537, 262144, 262145, 524288, 524289, 1000000, 1 << 24]
+    ks = [1, 64, 65, 512, 1024, 1025, 4096]
+    for which in (P.WS_TOPK, P.WS_PRIOR_FILTER, P.WS_LSE):
+        for n_sg in (1, 2, 8, 20, 300):
+            need = np.array([[P.workspace_bytes(which, n, n_sg, k) for k in ks] for n in sizes])
+            assert np.all(np.diff(need, axis=0) >= 0) and np.all(np.diff(need, axis=1) >= 0), (which, n_sg)
+    for which in (P.WS_VERIFY, P.WS_PACM):
+        assert np.all(np.diff([P.workspace_bytes(which, n, 0, 0) for n in sizes]) >= 0)
+
+
 def _draft(lib, sgs, seg, tiles=FAKE, pitch=None, flags=0, score=FAKE, ws=FAKE, ws_bytes=1 << 20):
     arr = P.to_c_subgraphs(sgs)
     seg = np.asarray(seg, dtype=np.int64)
