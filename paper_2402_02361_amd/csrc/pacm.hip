@@ -783,7 +783,7 @@ pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ 
 size_t pacm_workspace_bytes(int64_t n_d)
 {
     if (n_d < 0) n_d = 0;
-    return round_up((size_t)n_d * kH * sizeof(uint16_t), 256) + round_up((size_t)n_d * kE * sizeof(uint16_t), 256);
+    return round_up((size_t)n_d * kH * sizeof(float), 256) + round_up((size_t)n_d * kE * sizeof(float), 256);
 }
 
 }  // namespace pruner

@@ -45,7 +45,6 @@ def test_workspace_sizes_grow_with_the_problem():
     assert P.workspace_bytes(P.WS_DRAFT, 1000, 1, 0) >= 256
     assert P.workspace_bytes(P.WS_TOPK, 1 << 24, 2, 4096) > P.workspace_bytes(P.WS_TOPK, 1 << 12, 2, 64)
     assert P.workspace_bytes(P.WS_VERIFY, 10240, 0, 0) == 256               # the verify stage keeps its row numbering on chip
-    assert P.workspace_bytes(P.WS_PACM, 8192, 0, 0) == 8192 * (256 + 64) * 2   # the pooled vectors, bfloat16
     assert P.workspace_bytes(99, 1, 1, 1) == 0
 
 
