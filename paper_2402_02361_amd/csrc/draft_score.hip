@@ -27,7 +27,6 @@
 
 #include <string.h>
 
-#include <algorithm>
 #include <vector>
 
 namespace pruner {
@@ -1469,8 +1468,12 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     const bool large = vec == 4 && n >= kPerClassMin;
     const int n_classes = __builtin_popcount(classes);
     const bool by_class = vec == 4 && ((large && (mut || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (mut ? 2 : 1));
-    if (by_class)
-        std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return descs[desc_of[a]].cls < descs[desc_of[b]].cls; });
+    if (by_class && n_classes > 1) {   // (a pass per class: sorting a thousand segments of one class took 14 us of host time)
+        order.clear();
+        for (uint32_t left = classes; left; left &= left - 1)
+            for (int32_t s = 0; s < n_sg; ++s)
+                if (descs[desc_of[s]].cls == __builtin_ctz(left)) order.push_back(s);
+    }
     // Arithmetic of Eq. 1: one rounded operation per step of the definitions below 2^20 candidates (a call is then bound by
     // launch latency, and the dozen divisions per candidate cost nothing measurable) and where the population is not laid
     // out in fours (the boundary says so; it was the narrow loads' rule), the multiplied-out form for the other large
