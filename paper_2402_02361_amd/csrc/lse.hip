@@ -203,18 +203,21 @@ __global__ void __launch_bounds__(kLseThreads) lse_rank_kernel(int k, bool first
     }
 }
 
-// The union as a set, 64 places per workgroup: an entry with the score and the hash of its predecessor is a copy; the others'
+// The union as a set, 64 PER places per workgroup: an entry with the score and the hash of its predecessor is a copy; the others'
 // ranks are the number of such entries before them (every workgroup counts those before its own places itself: 128 KB at
 // most, against a launch more).  The first k are the new S_spec; the last step writes the caller's arrays as well.
-__global__ void __launch_bounds__(kLseThreads) lse_unite_kernel(int k, bool first, Spec before, const uint32_t* __restrict__ fresh_aos,
+// PER = 4 where there are workgroups for several rounds of the device: fewer of them count what lies before theirs (200
+// subgraphs, k = 1025: 39 -> 16 us).
+template <int PER> __global__ void __launch_bounds__(kLseThreads) lse_unite_kernel(int k, bool first, Spec before, const uint32_t* __restrict__ fresh_aos,
                                                                 const uint64_t* __restrict__ union_hi, const uint64_t* __restrict__ union_lo, Spec now,
                                                                 int64_t spec_pitch, int rows, uint16_t* __restrict__ spec_tiles /* or null */,
                                                                 float* __restrict__ spec_score, int32_t* __restrict__ spec_count)
 {
     constexpr int kPer = 2 * PRUNER_MAX_K / kLseThreads;
     static_assert(kLseThreads == kWave * kAosWords, "a thread copies one word");
-    __shared__ uint32_t before_mine, all_mine, from[kWave], to[kWave];
-    const int s = blockIdx.y, lane = lane_id(), base = (int)blockIdx.x * kWave;
+    constexpr int kPlaces = kWave * PER;
+    __shared__ uint32_t before_mine, wave_kept[PER], from[kPlaces], to[kPlaces];
+    const int s = blockIdx.y, lane = lane_id(), wave = threadIdx.x >> 6, base = (int)blockIdx.x * kPlaces;
     const int64_t col0 = (int64_t)s * k;
     const int n_old = first ? 0 : spec_members(before.count, s, k), m = n_old + k;
     if (base >= m) return;
@@ -245,18 +248,30 @@ __global__ void __launch_bounds__(kLseThreads) lse_unite_kernel(int k, bool firs
     if (lane == 0 && kept) atomicAdd(&before_mine, kept);
     __syncthreads();
     const uint32_t rank0 = before_mine;
-    const bool last_places = base + kWave >= m;
+    const bool last_places = base + kPlaces >= m;
     if (rank0 >= (uint32_t)k && !last_places) return;
-    if (threadIdx.x < kWave) {
-        const int p = base + lane;
-        const uint64_t mh = p < m ? uh[p] : 0ull, ml = p < m ? ul[p] : 0ull;
-        const bool keep = p < m && (p == 0 || mh != uh[p - 1] || (ml >> 32) != (ul[p - 1] >> 32));
-        const unsigned long long kept_lanes = __ballot(keep);
-        const uint32_t rank = rank0 + (uint32_t)__popcll(kept_lanes & ((1ull << lane) - 1ull));
+    const int p = base + (int)threadIdx.x;
+    uint64_t mh = 0, ml = 0;
+    bool keep = false;
+    if (threadIdx.x < kPlaces && p < m) {
+        mh = uh[p];
+        ml = ul[p];
+        keep = p == 0 || mh != uh[p - 1] || (ml >> 32) != (ul[p - 1] >> 32);
+    }
+    const unsigned long long kept_lanes = __ballot(keep);
+    if (wave < PER && lane == 0) wave_kept[wave] = (uint32_t)__popcll(kept_lanes);
+    __syncthreads();
+    uint32_t all_mine = 0, kept_before = 0;   // of this workgroup's places; of those before this wavefront's
+#pragma unroll
+    for (int w = 0; w < PER; ++w) {
+        kept_before += w < wave ? wave_kept[w] : 0u;
+        all_mine += wave_kept[w];
+    }
+    if (threadIdx.x < kPlaces) {
+        const uint32_t rank = rank0 + kept_before + (uint32_t)__popcll(kept_lanes & ((1ull << lane) - 1ull));
         const bool stays = keep && rank < (uint32_t)k;
-        to[lane] = stays ? rank : 0xFFFFFFFFu;
-        from[lane] = 0xFFFFFFFFu - (uint32_t)ml;
-        if (lane == 0) all_mine = (uint32_t)__popcll(kept_lanes);
+        to[threadIdx.x] = stays ? rank : 0xFFFFFFFFu;
+        from[threadIdx.x] = 0xFFFFFFFFu - (uint32_t)ml;
         if (stays) {
             now.hi[col0 + rank] = mh;
             now.lo[col0 + rank] = (ml & 0xFFFFFFFF00000000ull) | (uint64_t)(0xFFFFFFFFu - rank);
@@ -264,8 +279,11 @@ __global__ void __launch_bounds__(kLseThreads) lse_unite_kernel(int k, bool firs
         }
     }
     __syncthreads();
-    const int e = threadIdx.x / kAosWords, w = threadIdx.x % kAosWords;
-    if (to[e] != 0xFFFFFFFFu) {
+    const int w = threadIdx.x % kAosWords;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int e = q * kWave + (int)threadIdx.x / kAosWords;
+        if (to[e] == 0xFFFFFFFFu) continue;
         const int pos = (int)from[e];
         const uint32_t word = pos < n_old ? reinterpret_cast<const uint32_t*>(before.aos)[(col0 + pos) * kAosWords + w] : fresh_aos[(col0 + (pos - n_old)) * kAosWords + w];
         const int64_t at = col0 + to[e];
@@ -752,6 +770,8 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
     return L;
 }
 
+constexpr int kManyUniters = 2048;   // workgroups of 64 places: four times what the device holds at once
+
 PerDeviceFlag g_rank_ready;   // the rank kernel's allowance of dynamic LDS has been raised
 
 }  // namespace
@@ -909,9 +929,12 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
                            fresh, fresh + spec_pitch, merged, merged + 2 * spec_pitch);
         PRUNER_LAUNCH_CHECK();
         const bool last = t + 1 == n_steps;
-        hipLaunchKernelGGL(lse_unite_kernel, dim3((unsigned)((2 * k + kWave - 1) / kWave), (unsigned)n_sg), dim3(kLseThreads), 0, st, k, t == 0, before,
-                           fresh_aos, merged, merged + 2 * spec_pitch, now, spec_pitch, tile_rows, last ? spec_tiles : nullptr,
-                           last ? spec_score : nullptr, last ? spec_count : nullptr);
+#define PRUNER_UNITE(PER) hipLaunchKernelGGL(lse_unite_kernel<PER>, dim3((unsigned)((2 * k + PER * kWave - 1) / (PER * kWave)), (unsigned)n_sg), dim3(kLseThreads), 0, st, k, t == 0, before, \
+                                             fresh_aos, merged, merged + 2 * spec_pitch, now, spec_pitch, tile_rows, last ? spec_tiles : nullptr, last ? spec_score : nullptr, \
+                                             last ? spec_count : nullptr)
+        if ((int64_t)n_sg * ((2 * k + kWave - 1) / kWave) > kManyUniters) PRUNER_UNITE(4);
+        else PRUNER_UNITE(1);
+#undef PRUNER_UNITE
         PRUNER_LAUNCH_CHECK();
     }
     // the last step's mutation: S_x as the caller receives it

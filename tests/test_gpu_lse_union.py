@@ -33,3 +33,11 @@ def test_a_population_of_copies(P, distinct, q16):
     seg, tiles = lse_population([GEMM], [33000], seed=3)
     tiles[:, distinct:] = tiles[:, np.arange(33000 - distinct) % distinct]
     check_lse_against_oracle(P, [GEMM], seg, tiles, 2048, 3, 12, q16)
+
+
+def test_many_segments(P):
+    """as many subgraphs as make the union's workgroups take 256 places each"""
+    lens = [1100 + 4 * (t % 7) for t in range(64)]
+    sgs = [GEMM, CONV] * 32
+    seg, tiles = lse_population(sgs, lens, seed=5)
+    check_lse_against_oracle(P, sgs, seg, tiles, 1030, 3, 11, 40000)
