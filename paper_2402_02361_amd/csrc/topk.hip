@@ -13,8 +13,7 @@
 //            few entries at or above rank k's bin, and ranks its share of them;
 //   lists  - segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
 //            16384-entry sweeps, one workgroup each) and sets the entries at or above the bin aside in a list per span; the
-//            workgroups of a segment then collect from its lists (and go through the segment themselves only if a list
-//            overflowed);
+//            workgroups of a segment then collect from its lists (and go through the span of a list that overflowed themselves);
 //   spans  - longer segments are cut into spans of whole 16384-entry sweeps, one workgroup of 1024 threads each; the scores
 //            are read twice at most (first-digit histogram, which also notes the largest key of every 256 entries; then
 //            everything at or above that digit's rank-k bin is set aside, a few thousand entries as a rule, and blocks of
@@ -1090,7 +1089,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
 // LISTS: the lists route.
 template <bool LISTS>
 __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int n_total, int R,
-                                                           int k, int share, const uint32_t* __restrict__ ghist0,
+                                                           int k, int share, int span, const uint32_t* __restrict__ ghist0,
                                                            const uint32_t* __restrict__ ghist1, const uint32_t* __restrict__ granges,
                                                            const Stage* __restrict__ stage, int n_stages, int32_t* __restrict__ idx_out,
                                                            float* __restrict__ val_out)
@@ -1138,7 +1137,20 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     // More than the limit: the bin is split (the same decision in every workgroup of the segment), in the lists route first by
     // the second digit, which the launch before has counted.
     const uint32_t limit = (uint32_t)collect_limit(k);
-    const bool lists_whole = LISTS && __ballot(my_count > (uint32_t)kListCap) == 0ull;   // (every wavefront holds all counts)
+    const unsigned long long overflowed = LISTS ? __ballot(my_count > (uint32_t)kListCap) : 0ull;   // (every wavefront holds all counts)
+    // The spans of lists that overflowed (a stretch of good entries, as a sorted segment has it) are gone through by the whole
+    // workgroup: what(row, hi, val) for each of their sweeps.
+    auto through_overflowed = [&](auto&& what) {
+        for (unsigned long long left = overflowed; left; left &= left - 1ull) {
+            const int lo = (__ffsll(left) - 1) * span, hi = lo + span < len ? lo + span : len;
+#pragma unroll 1
+            for (int row = lo; row < hi; row += kRow) {
+                float again[kBigPer];
+                load_sweep(seg_score, row, hi, again);
+                what(row, hi, again);
+            }
+        }
+    };
     uint32_t least = 0u, largest = 0xFFFFFFFFu;   // of the bin's keys
     auto between = [&] {
         const uint32_t last_key = lowest + width < largest ? lowest + width : largest;
@@ -1185,25 +1197,29 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         } else {
             for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
             __syncthreads();
-            if (lists_whole) {
+            auto count_sweep = [&](int row, int hi, const float (&again)[kBigPer]) {
+#pragma unroll
+                for (int j = 0; j < kBigPer; ++j) {
+                    const uint32_t key = key_of(again[j]);
+                    light_hist_add(hist, (key - lowest) >> shift, sweep_index(row, j) < hi && key - lowest <= width);
+                }
+            };
+            if constexpr (LISTS) {
                 for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
-                    const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
+                    const uint32_t cnt = (overflowed >> l) & 1ull ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
                     const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
                     for (uint32_t e = 0; e < cnt; e += kWave) {
                         const uint32_t key = e + lane < cnt ? (uint32_t)(from[e + lane] >> 32) : 0u;
                         light_hist_add(hist, (key - lowest) >> shift, e + lane < cnt && key - lowest <= width);
                     }
                 }
+                through_overflowed(count_sweep);
             } else {
 #pragma unroll 1
                 for (int row = 0; row < len; row += kRow) {
                     float again[kBigPer];
                     load_sweep(seg_score, row, len, again);
-#pragma unroll
-                    for (int j = 0; j < kBigPer; ++j) {
-                        const uint32_t key = key_of(again[j]);
-                        light_hist_add(hist, (key - lowest) >> shift, sweep_index(row, j) < len && key - lowest <= width);
-                    }
+                    count_sweep(row, len, again);
                 }
             }
             __syncthreads();
@@ -1224,7 +1240,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         // Whole lists hold the ties as well, and lie in index order: those up to the one in which the k_rem-th tie lies are
         // ranked with the rest, at most one list's more than k.
         static_assert(kPickCap >= PRUNER_MAX_K + kListCap, "k and a list more fit");
-        if (ties_apart && lists_whole) {
+        if (ties_apart && overflowed == 0ull) {
             for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
                 const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
                 const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
@@ -1241,40 +1257,37 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
             __syncthreads();
         }
     }
-    const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
-    if constexpr (LISTS) {
-        if (lists_whole) {
-            for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
-                const bool with_ties = ((tie_lists >> l) & 1ull) != 0ull;
-                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
-                const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
-                for (uint32_t e = 0; e < cnt; e += kWave) {
-                    const uint64_t w = e + lane < cnt ? from[e + lane] : 0ull;
-                    const uint32_t key = (uint32_t)(w >> 32);
-                    const unsigned long long in = __ballot(e + lane < cnt && (with_ties ? key >= lowest : key > lowest));
-                    if (in == 0ull) continue;
-                    const int leader = __ffsll(in) - 1;
-                    uint32_t base = 0;
-                    if (lane == leader) base = atomicAdd(&fill, (uint32_t)__popcll(in));
-                    const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(in & ((1ull << lane) - 1ull));
-                    if (((in >> lane) & 1ull) && at < (uint32_t)n) sel[slot(at)] = w;
-                }
-            }
-        } else if (n > 0) {
-#pragma unroll 1
-            for (int row = 0; row < len; row += kRow) {
-                float again[kBigPer];
-                load_sweep(seg_score, row, len, again);
-                uint32_t mask = mask_of_sweep(again, t0, row, len);
-                uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
-                while (mask) {
-                    if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, __ffs(mask) - 1);
-                    mask &= mask - 1;
-                    ++at;
-                }
+    auto collected = [&](uint32_t key, bool with_ties) { return with_ties ? key >= lowest : key > lowest; };
+    if (LISTS && n == 0) {
+        // (nothing above the ties)
+    } else if constexpr (LISTS) {
+        for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
+            const bool with_ties = !ties_apart && ((tie_lists >> l) & 1ull) != 0ull;
+            const uint32_t cnt = (overflowed >> l) & 1ull ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
+            const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
+            for (uint32_t e = 0; e < cnt; e += kWave) {
+                const uint64_t w = e + lane < cnt ? from[e + lane] : 0ull;
+                const unsigned long long in = __ballot(e + lane < cnt && collected((uint32_t)(w >> 32), with_ties));
+                if (in == 0ull) continue;
+                const int leader = __ffsll(in) - 1;
+                uint32_t base = 0;
+                if (lane == leader) base = atomicAdd(&fill, (uint32_t)__popcll(in));
+                const uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(in & ((1ull << lane) - 1ull));
+                if (((in >> lane) & 1ull) && at < (uint32_t)n) sel[slot(at)] = w;
             }
         }
+        through_overflowed([&](int row, int hi, const float (&again)[kBigPer]) {
+            uint32_t mask = 0;
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) mask |= sweep_index(row, j) < hi && collected(key_of(again[j]), !ties_apart) ? 1u << j : 0u;
+            uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
+            for (; mask; mask &= mask - 1, ++at) {
+                const int i = (int)sweep_index(row, __ffs(mask) - 1);
+                if (at < (uint32_t)n) sel[slot(at)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + (uint32_t)i);
+            }
+        });
     } else {
+        const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
         uint64_t mask = 0;   // bit 4 g + e: entry e of group g is not below the threshold
 #pragma unroll
         for (int g = 0; g < kGroups; ++g) {
@@ -1302,7 +1315,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
         if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
     __syncthreads();
-    if (!lists_whole) {
+    if constexpr (!LISTS) {
         if (n > 0 && fill != (uint32_t)n) {
             // The counts come from keys, the places from comparisons with a threshold: where these found more, there are NaN
             // among the scores, and the places are collected again by key.
@@ -1315,10 +1328,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                 load_sweep(seg_score, row, len, again);
                 uint32_t mask = 0;
 #pragma unroll
-                for (int j = 0; j < kBigPer; ++j) {
-                    const uint32_t key = key_of(again[j]);
-                    mask |= sweep_index(row, j) < len && (ties_apart ? key > lowest : key >= lowest) ? 1u << j : 0u;
-                }
+                for (int j = 0; j < kBigPer; ++j) mask |= sweep_index(row, j) < len && collected(key_of(again[j]), !ties_apart) ? 1u << j : 0u;
                 uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
                 while (mask) {
                     if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, __ffs(mask) - 1);
@@ -1541,6 +1551,14 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
         return PRUNER_OK;
     }
 
+    // the ranking of a segment's k rows is shared out over up to k / 32 workgroups, as long as the launch is one
+    // workgroup per compute unit at most (a compute unit holds one of these workgroups at a time: a launch of more
+    // takes a second round, which costs more than longer rankings do)
+    int share = (k + 31) / 32;
+    if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
+    if (share < 1) share = 1;
+    const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
+
     SelState* d_state = static_cast<SelState*>(ctx.d_state);
     Stage* d_stage = static_cast<Stage*>(ctx.d_stage);
     const int R = ctx.copies;
@@ -1554,21 +1572,14 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
         hipLaunchKernelGGL(hist0_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, hist0, block_max);
         PRUNER_LAUNCH_CHECK();
     }
-    // the ranking of a segment's k rows is shared out over up to k / 32 workgroups, as long as the launch is one
-    // workgroup per compute unit at most (a compute unit holds one of these workgroups at a time: a launch of more
-    // takes a second round, which costs more than longer rankings do)
-    int share = (k + 31) / 32;
-    if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
-    if (share < 1) share = 1;
     if (ctx.pick || ctx.lists) {
-        const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
         if (ctx.lists) {
             hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, hist2, d_stage);
             PRUNER_LAUNCH_CHECK();
-            hipLaunchKernelGGL(pick_kernel<true>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, hist0, hist1, hist2, d_stage,
+            hipLaunchKernelGGL(pick_kernel<true>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         } else {
-            hipLaunchKernelGGL(pick_kernel<false>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, hist0, hist1, hist2, d_stage,
+            hipLaunchKernelGGL(pick_kernel<false>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         }
         PRUNER_LAUNCH_CHECK();

@@ -1,0 +1,32 @@
+"""Selections at the edges of the one- and two-launch routes' ways of ranking and collecting: one launch for everything (segments of
+up to 32,768), words ranked in rounds or sorted, with or without the last bin's surplus, stretches of good entries that
+overflow a span's list.  Against the oracle's stable sort."""
+import numpy as np
+import pytest
+
+from test_gpu_parity import P  # noqa: F401  (a fixture)
+from test_gpu_select_digits import check, values
+
+pytestmark = pytest.mark.gpu
+
+
+def of(kind, n, rng):
+    if kind in ("ascending", "descending"):
+        x = np.sort(values("latencies", n, rng))
+        return x if kind == "ascending" else x[::-1].copy()
+    if kind == "clump":   # a stretch of good entries in the middle, in no order
+        x = values("latencies", n, rng)
+        m = min(n, 3000)
+        x[n // 2 - m // 2: n // 2 - m // 2 + m] = -np.exp2(rng.uniform(-30, -27, m)).astype(np.float32)
+        return x
+    return values(kind, n, rng)
+
+
+@pytest.mark.parametrize("kind", ["ascending", "clump", "one bin", "300 values", "equal"])
+@pytest.mark.parametrize("lens,ks", [([100001, 65537], [512, 1100, 4096]), ([300001] * 3, [33, 2048]), ([524288], [512, 4096]), ([70000] * 130, [512])])
+def test_lists_that_overflow(P, kind, lens, ks):
+    rng = np.random.default_rng(len(kind) + len(lens))
+    seg = np.concatenate([[0], np.cumsum(lens)])
+    score = np.concatenate([of(kind, n, rng) for n in lens])
+    for k in ks:
+        check(P, score, seg, k)
