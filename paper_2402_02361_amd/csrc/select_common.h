@@ -95,28 +95,8 @@ template <typename Seg> __device__ __forceinline__ int segment_of_block(const Se
     return lo;
 }
 
-// LDS histogram increment.  Leading digits of scores take few values, and lanes that add to one bin queue on its
-// address; so the lanes that share the first pending lane's bin are counted with one atomic, up to four bins in turn
-// (a segment of equal scores, or of two or three neighbouring leading digits, costs a wavefront a handful of atomics
-// instead of sixty-four); lanes still pending after that (digits that scatter) add 1 to their own bins.
-__device__ __forceinline__ void wave_hist_add(uint32_t* hist, uint32_t digit, bool active)
-{
-    unsigned long long pending = __ballot(active);
-#pragma unroll
-    for (int round = 0; round < 4; ++round) {
-        if (__popcll(pending) < 4) break;   // (same for every lane) a few stragglers add one by one
-        const int leader = __ffsll(pending) - 1;
-        const uint32_t d0 = __builtin_amdgcn_readlane(digit, leader);
-        const unsigned long long same = __ballot(active && digit == d0);
-        if (lane_id() == leader) atomicAdd(&hist[d0], (uint32_t)__popcll(same));
-        active = active && digit != d0;
-        pending &= ~same;
-    }
-    if (active) atomicAdd(&hist[digit], 1u);
-}
-
-// The same for digits that scatter as a rule: the lanes that share the first active lane's bin are counted with one atomic
-// only when they are sixteen or more, everyone else adds 1 (a dozen instructions where wave_hist_add has fifty).
+// LDS histogram increment for digits that scatter as a rule: lanes that add to one bin queue on its address, so the lanes that
+// share the first active lane's bin are counted with one atomic when they are sixteen or more, everyone else adds 1.
 __device__ __forceinline__ void light_hist_add(uint32_t* hist, uint32_t digit, bool active)
 {
     const unsigned long long there = __ballot(active);
