@@ -297,7 +297,7 @@ __global__ void __launch_bounds__(kBigThreads) hist0_kernel(const float* __restr
         for (int j = 0; j < kBigPer; ++j) {
             const int64_t i = sweep_index(row, j);
             const uint32_t key = key_of(val[j]);
-            light_hist_add(hist, first_digit_of(key), i < hi);
+            light_hist_add<true>(hist, first_digit_of(key), i < hi);
             if (i < hi && key > top[j >> 2]) top[j >> 2] = key;
         }
         // a wavefront's q-th load is one block of 256 neighbouring entries (spans are whole sweeps from the segment's begin)
