@@ -106,25 +106,25 @@ __device__ __forceinline__ int pow2_at_least(int k)
     return P;
 }
 
-// Sort the k selected words and write the result rows of one segment.
+// Sort n selected words and write the result rows lo .. hi - 1 of one segment (hi <= n).
 template <int NT>
-__device__ __forceinline__ void finish_segment(uint64_t* sel, int k, const float* __restrict__ score, int32_t* __restrict__ idx_out,
+__device__ __forceinline__ void finish_segment(uint64_t* sel, int n, int lo, int hi, const float* __restrict__ score, int32_t* __restrict__ idx_out,
                                                float* __restrict__ val_out, int64_t row, int64_t seg_begin, int64_t seg_end, int row_len)
 {
-    const int P = pow2_at_least(k);
-    for (int i = k + threadIdx.x; i < P; i += NT) sel[slot(i)] = 0;  // below every real word
+    const int P = pow2_at_least(n);
+    for (int i = n + threadIdx.x; i < P; i += NT) sel[slot(i)] = 0;  // below every real word
     sort_descending<NT>(sel, P);
-    for (int r0 = threadIdx.x; r0 < k; r0 += 4 * NT) {
+    for (int r0 = lo + threadIdx.x; r0 < hi; r0 += 4 * NT) {
         uint32_t gi[4];
         float v[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {   // the scores of four rows are requested together
-            gi[u] = r0 + u * NT < k ? index_of(sel[slot(r0 + u * NT)]) : 0xFFFFFFFFu;
+            gi[u] = r0 + u * NT < hi ? index_of(sel[slot(r0 + u * NT)]) : 0xFFFFFFFFu;
             v[u] = val_out && gi[u] >= seg_begin && gi[u] < seg_end ? score[gi[u]] : 0.f;   // never read outside the segment
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            if (r0 + u * NT < k) {
+            if (r0 + u * NT < hi) {
                 idx_out[row * row_len + r0 + u * NT] = (int32_t)gi[u];
                 if (val_out) val_out[row * row_len + r0 + u * NT] = v[u];
             }
@@ -928,7 +928,7 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
     }
     if (n_gt == 0) return;
     if (share == 1) {
-        finish_segment<kSmallThreads>(sel, (int)n_gt, score, idx_out, val_out, s, seg.begin, seg.end, k);
+        finish_segment<kSmallThreads>(sel, (int)n_gt, 0, (int)n_gt, score, idx_out, val_out, s, seg.begin, seg.end, k);
     } else {
         // Which words this workgroup ranks.  Copied from the lists alone, the words have the same places in every
         // workgroup of the segment, and the places are dealt out in turn: no workgroup gets more than the others.
@@ -969,6 +969,11 @@ constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
 // values shared by 20,000 entries, k = 512: 84 us with all of the bin ranked, 25 with the limit).
 __host__ __device__ constexpr int collect_limit(int k) { return k + k / 4 + 256; }
 static_assert(kPickCap >= collect_limit(PRUNER_MAX_K), "a collection fits");
+
+// A round of ranking (64 words against all n) takes about n / 750 us, a sort of P words by a workgroup P / 230.
+constexpr int kSortFactor = 3;   // rounds x n beyond this many times P: sort
+constexpr int kTrimMax = 512;
+static_assert(kTrimMax <= kBigThreads, "a word of the last bin per thread");
 
 // The lists route: at most 32 spans per segment, so that a segment that has to be gone through again by one workgroup is still
 // a matter of microseconds.
@@ -1095,7 +1100,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                                                            float* __restrict__ val_out)
 {
     __shared__ __align__(16) uint64_t sel[kPickWords];
-    __shared__ uint32_t place[kPickCap];      // indices inside the segment; later: which words this workgroup ranks
+    __shared__ __align__(16) uint32_t place[kPickCap];   // indices inside the segment; later: which words this workgroup ranks
     __shared__ uint32_t hist[kBins];          // later: the ranking's counts
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t found[3];
@@ -1344,6 +1349,52 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         }
         __syncthreads();
     }
+    // The words are ranked in rounds of 64 per workgroup, or sorted, all of them by every workgroup of the segment, whatever costs
+    // less (see kSortFactor).
+    const int n_last = n - (int)((uint32_t)k - k_rem);   // the words of the last bin
+    const bool trim = n > k && n_last <= kTrimMax && pow2_at_least(n) > pow2_at_least(k);
+    const int rounds = (n + 64 * share - 1) / (64 * share);
+    if (rounds * n > kSortFactor * pow2_at_least(trim ? k : n)) {
+        if (trim) {
+            // the sort is half as long without those of the last bin that are not selected: their places go to what lies behind k
+            uint64_t* bin_word = reinterpret_cast<uint64_t*>(place);
+            uint16_t *bin_at = reinterpret_cast<uint16_t*>(place + 2 * kTrimMax), *hole = bin_at + kTrimMax;
+            static_assert(sizeof(place) >= kTrimMax * (sizeof(uint64_t) + 2 * sizeof(uint16_t)), "the lists fit");
+            __syncthreads();
+            if (threadIdx.x == 0) fill = 0;
+            __syncthreads();
+            for (int e = threadIdx.x; e < n; e += kBigThreads) {
+                const uint64_t w = sel[slot((uint32_t)e)];
+                if ((uint32_t)(w >> 32) - lowest <= width) {
+                    const uint32_t at = atomicAdd(&fill, 1u);
+                    if (at < (uint32_t)kTrimMax) bin_word[at] = w, bin_at[at] = (uint16_t)e;
+                }
+            }
+            __syncthreads();
+            if ((int)threadIdx.x < n_last) {
+                const uint64_t me = bin_word[threadIdx.x];
+                const int at = bin_at[threadIdx.x];
+                uint32_t better = 0;
+                for (int x = 0; x < n_last; ++x) better += bin_word[x] > me ? 1u : 0u;
+                if (better >= k_rem) {
+                    sel[slot((uint32_t)at)] = 0;
+                    if (at < k) hole[atomicAdd(&n_own, 1u)] = (uint16_t)at;
+                }
+            }
+            if (threadIdx.x == 0) fill = 0;
+            __syncthreads();
+            for (int e = k + (int)threadIdx.x; e < n; e += kBigThreads) {
+                const uint64_t w = sel[slot((uint32_t)e)];
+                if (w != 0ull) sel[slot(hole[atomicAdd(&fill, 1u)])] = w;
+            }
+            __syncthreads();
+            n = k;
+        }
+        const int rows = n < k ? n : k, per = (rows + share - 1) / share, lo = part * per < rows ? part * per : rows;   // each writes its part of the rows
+        finish_segment<kBigThreads>(sel, n, lo, lo + per < rows ? lo + per : rows, score, idx_out, val_out, s, seg.begin, seg.end, k);
+        n = 0;
+    }
+    const uint32_t behind = (uint32_t)k - k_rem;   // (ties apart: rows before theirs)
     // (every workgroup has its own order of the words: a hash of the index decides who ranks a word)
     for (int e = threadIdx.x; e < n; e += kBigThreads) {
         const uint32_t h = (index_of(sel[slot((uint32_t)e)]) * 2654435761u) >> 16;
@@ -1352,7 +1403,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     __syncthreads();
     if (n > 0) rank_rows<kBigThreads>(sel, n, own, 0, 1, (int)n_own, hist, score, idx_out, val_out, s, seg.begin, seg.end, k);
     if (ties_apart && part == 0) {
-        // ties, all of the key `lowest`, in index order: the tie of rank r owns row n + r.  A wavefront takes 16 x 64
+        // ties, all of the key `lowest`, in index order: the tie of rank r owns row behind + r.  A wavefront takes 16 x 64
         // neighbouring entries; one exchange of the wavefronts' counts per sweep.
         uint32_t before = 0;
         for (int row = 0; row < len && before < k_rem; row += kRow) {
@@ -1378,7 +1429,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
 #pragma unroll
             for (int j = 0; j < kBigPer; ++j)
                 if (before_mine[j] != 0xFFFFFFFFu && wave_before + before_mine[j] < k_rem)
-                    put_tie_row(k, (uint32_t)n + wave_before + before_mine[j], (uint32_t)(seg.begin + first + j * kWave), lowest, score, idx_out, val_out, s, seg.begin, seg.end);
+                    put_tie_row(k, behind + wave_before + before_mine[j], (uint32_t)(seg.begin + first + j * kWave), lowest, score, idx_out, val_out, s, seg.begin, seg.end);
             before += all;
         }
     }

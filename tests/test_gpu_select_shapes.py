@@ -30,3 +30,13 @@ def test_lists_that_overflow(P, kind, lens, ks):
     score = np.concatenate([of(kind, n, rng) for n in lens])
     for k in ks:
         check(P, score, seg, k)
+
+
+@pytest.mark.parametrize("kind", ["latencies", "ascending", "descending", "one bin", "two values", "300 values", "equal"])
+@pytest.mark.parametrize("lens,ks", [([40000] * 20, [4096]), ([33000] * 130, [65, 512, 2047, 2048]), ([65536] * 40, [1023, 4096]), ([32769, 5000], [4096]), ([40000] * 300, [600])])
+def test_sorted_or_ranked(P, kind, lens, ks):
+    rng = np.random.default_rng(len(kind) + len(lens))
+    seg = np.concatenate([[0], np.cumsum(lens)])
+    score = np.concatenate([of(kind, n, rng) for n in lens])
+    for k in ks:
+        check(P, score, seg, k)
