@@ -90,6 +90,7 @@ struct TopkCtx {
     bool large;            // the route counts first digits (not the tiny one)
     bool pick;             // ... and takes one launch behind that
     bool lists;            // ... or two
+    bool count;            // ... or that one launch alone (pick)
     int32_t n_sg, k;
     int64_t n, span;
     int32_t blocks;        // workgroups of a sweep launch

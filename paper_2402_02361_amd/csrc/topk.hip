@@ -9,7 +9,7 @@
 //   tiny   - segments of at most 8192 entries and k up to 64 (the final selection after the verify stage, small draft
 //            populations): one launch, no digits (tiny_select in select_common.h);
 //   pick   - segments of at most kPickMax entries: one launch behind whoever counted the first digit (the draft kernel as a
-//            rule, else one pass).  Several workgroups per segment, each of which goes through the whole segment, keeps the
+//            rule, else one pass), or, up to kCountMax entries, one launch that counts it too.  Several workgroups per segment, each of which goes through the whole segment, keeps the
 //            few entries at or above rank k's bin, and ranks its share of them;
 //   lists  - segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
 //            16384-entry sweeps, one workgroup each) and sets the entries at or above the bin aside in a list per span; the
@@ -185,6 +185,11 @@ __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint
 constexpr int kInlineSegs = 128;
 struct InlineSegs {
     SegT s[kInlineSegs];
+    __device__ __forceinline__ SegT at(int i) const { return s[i]; }
+};
+struct SegsInMemory {
+    const SegT* segs;
+    __device__ __forceinline__ SegT at(int i) const { return segs[i]; }
 };
 
 // ---- tiny route: segments of at most 8192 entries, k at most 64 ---------------------------------------------------
@@ -962,6 +967,10 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
 // places 2, words 1.7, ranks 2; sweeping in four steps took 3 us more).
 
 constexpr int kPickMax = 65536;
+// Segments up to this length whose first digit nobody has counted (pruner_topk) are counted by their workgroups, from the registers
+// that hold them: one launch, without a histogram in memory (20 segments of 512, k = 100: 16 -> 9.7 us; 300 of 20,000, k = 32:
+// 60 -> 47; 1,000 of 20,000, k = 512: 141 -> 117; at 32,768 the launches saved still pay).
+constexpr int kCountMax = 32768;
 constexpr int kXcds = 8;                                        // parts of the device with a cache of their own; workgroups go to them in turn
 constexpr int kPickCap = 8192;                                  // words a workgroup collects
 constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
@@ -1091,9 +1100,10 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     }
 }
 
-// LISTS: the lists route.
-template <bool LISTS>
-__global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int n_total, int R,
+// LISTS: the lists route.  COUNT: segments of at most kCountMax entries whose first digit nobody has counted; every workgroup does
+// so itself, and the call is this one launch.
+template <bool LISTS, bool COUNT, class Table>
+__global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, Table segs, int n_seg, int n_total, int R,
                                                            int k, int share, int span, const uint32_t* __restrict__ ghist0,
                                                            const uint32_t* __restrict__ ghist1, const uint32_t* __restrict__ granges,
                                                            const Stage* __restrict__ stage, int n_stages, int32_t* __restrict__ idx_out,
@@ -1110,18 +1120,18 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
     if (job >= n_seg * share) return;
     const int s = job / share, part = job % share;
-    const SegT seg = segs[s];
+    const SegT seg = segs.at(s);
     const int len = (int)(seg.end - seg.begin);
     const float* seg_score = score + seg.begin;
     const int lane = lane_id(), wave = threadIdx.x >> 6;
 
     // The whole segment travels while the bin is looked up: sixteen groups of four neighbours per thread.  A group that would
     // reach past the end of the scores starts earlier; what lies outside the segment is masked out below.
-    constexpr int kGroups = LISTS ? 1 : kPickMax / (4 * kBigThreads);
-    const int last = n_total - 4 - (int)seg.begin;   // (there are thousands of scores in all)
+    constexpr int kGroups = LISTS ? 1 : (COUNT ? kCountMax : kPickMax) / (4 * kBigThreads);
+    const int last = n_total - 4 - (int)seg.begin;   // (there are more than four scores in all)
     auto group_begin = [](int g) { return (g * kBigThreads + (int)threadIdx.x) * 4; };
     f32x4 val[kGroups];
-    const int b0 = seg.first_block, n_lists = LISTS ? (s + 1 < n_seg ? segs[s + 1].first_block : n_stages) - b0 : 0;
+    const int b0 = seg.first_block, n_lists = LISTS ? (s + 1 < n_seg ? segs.at(s + 1).first_block : n_stages) - b0 : 0;
     uint32_t my_count = 0;   // of list `lane`
     if constexpr (LISTS) {
         if (lane < n_lists) my_count = reinterpret_cast<const List*>(&stage[b0 + lane])->count;
@@ -1134,7 +1144,22 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
             }
         }
     }
-    bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+    if constexpr (COUNT) {
+        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            if (g * 4 * kBigThreads < len) {
+                const int i = group_begin(g), begun = i < last ? i : last;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) light_hist_add(hist, first_digit_of(key_of(val[g][e])), begun + e >= i && begun + e < len);
+            }
+        }
+        __syncthreads();
+        find_bucket(hist, (uint32_t)k, wave_tot, found);
+    } else {
+        bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+    }
     uint32_t lowest, width, k_rem = found[1], in_bin = found[2];
     first_digit_range(found[0], lowest, width);
     if (threadIdx.x == 0) fill = n_own = range[0] = range[1] = 0;
@@ -1536,6 +1561,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     ctx->large = !tiny;
     ctx->pick = pick;
     // (a population of copies, as the explorer loop keeps it, would have its lists overflow as a rule: it takes the spans route)
+    ctx->count = pick && longest <= kCountMax && !defer;
     ctx->lists = !tiny && !pick && longest <= kListsMax && !copies;
     ctx->n_sg = n_sg;
     ctx->k = k;
@@ -1554,7 +1580,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     ctx->d_block_max = with_block_max && sparse ? reinterpret_cast<uint32_t*>(ws + L.block_max) : nullptr;
     ctx->inline_ok = false;
     static_assert(sizeof(InlineSegs) <= sizeof(ctx->inline_segs), "inline segment table");
-    if (tiny) {
+    if (tiny || ctx->count) {
         if (n_sg <= kInlineSegs) {
             memset(ctx->inline_segs, 0, sizeof(InlineSegs));
             memcpy(ctx->inline_segs, segs, (size_t)n_sg * sizeof(SegT));
@@ -1609,6 +1635,21 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
     if (share < 1) share = 1;
     const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
+    const SegsInMemory in_memory{d_segs};
+    if (ctx.count && !have_first_digit) {
+        InlineSegs args;
+        memset(&args, 0, sizeof args);
+        if (ctx.inline_ok) {
+            memcpy(&args, ctx.inline_segs, sizeof args);
+            hipLaunchKernelGGL((pick_kernel<false, true, InlineSegs>), pickers, dim3(kBigThreads), 0, st, score, args, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
+                               nullptr, nullptr, 0, idx_out, val_out);
+        } else {
+            hipLaunchKernelGGL((pick_kernel<false, true, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
+                               nullptr, nullptr, 0, idx_out, val_out);
+        }
+        PRUNER_LAUNCH_CHECK();
+        return PRUNER_OK;
+    }
 
     SelState* d_state = static_cast<SelState*>(ctx.d_state);
     Stage* d_stage = static_cast<Stage*>(ctx.d_stage);
@@ -1627,10 +1668,10 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
         if (ctx.lists) {
             hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, hist2, d_stage);
             PRUNER_LAUNCH_CHECK();
-            hipLaunchKernelGGL(pick_kernel<true>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
+            hipLaunchKernelGGL((pick_kernel<true, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         } else {
-            hipLaunchKernelGGL(pick_kernel<false>, pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
+            hipLaunchKernelGGL((pick_kernel<false, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         }
         PRUNER_LAUNCH_CHECK();

@@ -40,3 +40,14 @@ def test_sorted_or_ranked(P, kind, lens, ks):
     score = np.concatenate([of(kind, n, rng) for n in lens])
     for k in ks:
         check(P, score, seg, k)
+
+
+@pytest.mark.parametrize("kind", ["latencies", "ascending", "every exponent", "zeros", "one bin", "two values", "300 values", "equal"])
+@pytest.mark.parametrize("lens,ks", [([65], [65]), ([66, 67, 4095], [65, 66]), ([4096], [65, 4096]), ([4097, 4100], [512, 4096]), ([8192], [1000]), ([32768], [1, 70, 4096]), ([32767, 70, 2], [1, 2]),
+                                     ([32768, 16385, 70], [70]), ([500] * 129, [100]), ([2000] * 300, [512]), ([5000] * 140, [4096])])
+def test_one_launch(P, kind, lens, ks):
+    rng = np.random.default_rng(len(kind) + len(lens))
+    seg = np.concatenate([[0], np.cumsum(lens)])
+    score = np.concatenate([of(kind, n, rng) for n in lens])
+    for k in ks:
+        check(P, score, seg, k)
