@@ -780,6 +780,7 @@ pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ 
 
 }  // namespace
 
+// (binary32 pooled vectors' room, of which the bfloat16 ones take half: the size that callers know)
 size_t pacm_workspace_bytes(int64_t n_d)
 {
     if (n_d < 0) n_d = 0;

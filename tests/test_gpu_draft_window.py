@@ -41,3 +41,23 @@ def test_a_window_scores_like_its_copy(P, column, lens):
     for flags in (P.REFERENCE_ROUNDING, P.FUSED_ARITHMETIC):
         copy = P.draft_score(sgs, seg, dev(tiles[:, column:]), flags=flags).cpu().numpy().view(np.uint32)
         assert np.array_equal(_window_scores(P, sgs, seg, matrix, column, flags), copy)
+
+
+@pytest.mark.parametrize("n", [1, 2, 3])
+def test_the_single_loads_of_tiny_populations_give_the_wide_loads_bits(P, n):
+    """Fewer than four candidates are loaded one by one, whatever the pitch: the same bits as from the same candidates among a
+    thousand, symbols included, and the selection behind them is that of the two calls."""
+    shapes = SUBGRAPHS + [w.depthwise_conv2d(1, 512, 28, 28, 3, 3), w.gemm(1024, 256, 256, dtype_bytes=2, rd_levels=3, frag=(16, 16, 16))]
+    for sg in shapes:
+        wide, _ = w.sample_population(sg, 1000, seed=4)
+        for flags in (P.REFERENCE_ROUNDING, P.FUSED_ARITHMETIC):
+            score, sym = P.draft_score([sg], [0, 1000], dev(wide), flags=flags, symbols=True)
+            for pitch in (n, n + 1, 9):
+                narrow = dev(wide[:, :pitch])
+                few, few_sym = P.draft_score([sg], [0, n], narrow, flags=flags, symbols=True)
+                assert torch.equal(few.view(torch.int32), score[:n].view(torch.int32)) and torch.equal(few_sym, sym[:, :n])
+                plain = P.draft_score([sg], [0, n], narrow, flags=flags)
+                assert torch.equal(plain.view(torch.int32), few.view(torch.int32))
+                filtered, idx, val = P.prior_filter([sg], [0, n], narrow, n, flags=flags)
+                want, want_val = P.topk(few, [0, n], n)
+                assert torch.equal(filtered.view(torch.int32), few.view(torch.int32)) and torch.equal(idx, want) and torch.equal(val, want_val)

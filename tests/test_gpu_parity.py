@@ -62,8 +62,8 @@ def check_draft(P, subgraphs, seg_off, tiles, flags=0, pitch_pad=0, symbols=True
             result = g32
         rel = np.abs(g32.astype(np.float64) - o64) / np.abs(o64)
         assert n == 0 or rel.max() <= (1e-5 if mode == P.REFERENCE_ROUNDING else FUSED_TOL), (mode, rel.max(), int(rel.argmax()))
-    # without a switch: the oracle's bits from a call that runs as one launch; the fused form in the per-class launches,
-    # which populations of 2^20 candidates and more get when every segment start and the pitch allow 8-byte loads
+    # without a switch: the oracle's bits, or the fused form for populations of 2^20 candidates and more that are laid out in
+    # fours (every segment start and the pitch)
     per_class = n >= (1 << 20) and tiles.shape[1] % 4 == 0 and all(int(o) % 4 == 0 for o in list(seg_off)[:-1])
     assert np.array_equal(bits[0], bits[P.FUSED_ARITHMETIC] if per_class else bits[P.REFERENCE_ROUNDING]), per_class
     return result
@@ -107,7 +107,9 @@ def test_draft_every_schedule_of_a_tiny_gemm(P):
 
 @pytest.mark.parametrize("offs", [[0, 1, 2, 1003, 1003, 5001], [0, 2, 1002, 4098], [0, 4, 1028, 5000]])
 def test_draft_ragged_segments_and_alignment(P, offs):
-    """Odd segment starts force the 1- and 2-wide load paths; an empty segment and a 1-candidate segment ride along."""
+    """Segments that start at any candidate: the wide loads and stores at addresses that are multiples of an element only, and
+    the last thread's load moved back where the population is not a multiple of four; an empty segment and a 1-candidate
+    segment ride along.  (Single loads: test_gpu_draft_window.py.)"""
     sgs = [w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64), w.conv2d(1, 64, 56, 56, 64, 3, 3),
            w.depthwise_conv2d(1, 512, 28, 28, 3, 3), w.gemm(128, 768, 3072)][: len(offs) - 1]
     seg = np.array(offs, np.int64)
@@ -120,8 +122,8 @@ def test_draft_ragged_segments_and_alignment(P, offs):
             tiles[: tl.shape[0], seg[t]:seg[t + 1]] = tl
     check_draft(P, sgs, seg, tiles)
     check_draft(P, sgs, seg, tiles, pitch_pad=3)
-    # a candidate's score does not depend on the load width its call runs at: the fused form too gives the same bits
-    # from a pitch that allows the wide loads and from one that forces single loads
+    # a candidate's score does not depend on where its rows lie: the fused form too gives the same bits from a pitch of another
+    # remainder
     padded = np.concatenate([tiles, np.ones((tiles.shape[0], 3), np.uint16)], axis=1)
     a = P.draft_score(sgs, seg, dev(tiles), flags=P.FUSED_ARITHMETIC).cpu().numpy()
     b = P.draft_score(sgs, seg, dev(padded), flags=P.FUSED_ARITHMETIC).cpu().numpy()
@@ -148,8 +150,9 @@ def test_draft_generic_nest_and_odd_divisors(P):
 
 
 def test_draft_one_launch_per_class(P):
-    """Above 2^20 candidates the library launches one kernel per loop-nest class: all five classes, interleaved in
-    the segment order, one class twice, with segment lengths that leave partial chunks."""
+    """More than 2^20 candidates in all five loop-nest classes, interleaved in the segment order, one class twice, with segment
+    lengths that leave partial chunks: the fused form by default, in one launch of the kernel that branches on the class
+    (2^20 candidates for each class would get launches of their own: test_gpu_draft_launches.py)."""
     hw = w.Device(T_p=3.3e12, T_m=4.1e11, m_l0=96, m_l1=20000, pu_l1=3, n_l1=24, pu_l2=7, n_l2=5)
     d = lambda *t: tuple(t)
     bt = w.Subgraph("gemm_bt", 2, 1, (96, 80, 72), 4, 3, 4, (0, 0, 0),
@@ -170,7 +173,7 @@ def test_draft_one_launch_per_class(P):
 @pytest.mark.parametrize("lens,flags", [([1285900, 290336, 43992], 1), ([1135293], 2), ([1285516, 270448, 249705], 0)])
 def test_draft_scores_do_not_depend_on_the_launch_shape(P, lens, flags):
     """A large segment beside small ones, and ends that are not multiples of four behind aligned starts: the same
-    candidates are scored by the per-class launches and, for the symbol dump, by the single launch, whose workgroups
+    candidates are scored by the kernels without and with the symbol dump, whose workgroups
     cover different numbers of candidates (some tabulate P_l2,m, some do not).  check_draft asserts equal bits between
     the two in every arithmetic mode."""
     sgs = [w.gemm(8, 3072, 1000), w.gemm(1024, 256, 256), w.batched_gemm(2, 100, 128, 1000)][: len(lens)]
@@ -475,13 +478,13 @@ def check_prior_filter(P, subgraphs, seg_off, tiles, k, flags=0):
 def test_prior_filter_large_route_counts_digits_in_the_draft_kernel(P, flags):
     wl = w.make_config(4, scale=1 / 8)                    # 2M + 512K candidates: per-class launches, large selection route
     check_prior_filter(P, wl.subgraphs, wl.seg_off, wl.tiles, wl.k_draft, flags)
-    wl = w.make_config(2)                                 # 1,000,000 in 20 segments: single launch, small route
+    wl = w.make_config(2)                                 # 1,000,000 in 20 segments: single launch, the route of one launch behind the digits
     check_prior_filter(P, wl.subgraphs, wl.seg_off, wl.tiles, wl.k_draft, flags)
 
 
 def test_prior_filter_odd_alignment_and_mixed_classes(P):
-    """Segment starts that force the narrow load widths (no digit counting in the draft kernel) with one segment
-    long enough for the large selection route; then the aligned case with four loop-nest classes."""
+    """Segments that start at odd candidates, then at multiples of four, with four loop-nest classes in one launch and one
+    segment long enough for the selection's route of two launches; the draft kernel counts the digits in both."""
     sgs = [w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64), w.conv2d(1, 64, 56, 56, 64, 3, 3), w.depthwise_conv2d(1, 512, 28, 28, 3, 3)]
     for lens in ([150001, 70001, 3001, 40002], [150000, 70004, 3000, 40004]):
         seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
@@ -498,8 +501,8 @@ def test_prior_filter_odd_alignment_and_mixed_classes(P):
 @pytest.mark.parametrize("k", [1, 33, 64])
 def test_prior_filter_short_segments(P, k):
     """Segments of at most 8192 candidates with k at most 64 (the selection's route for short segments) behind the draft
-    kernel in one call.  Four loop-nest classes, lengths from k itself to 8192, aligned starts and odd ones (narrow load
-    widths), the three arithmetic modes and the ablation switches; then one segment of 8193 and k = 65 (the next route)."""
+    kernel in one call.  Four loop-nest classes, lengths from k itself to 8192, aligned starts and odd ones,
+    the three arithmetic modes and the ablation switches; then one segment of 8193 and k = 65 (the next route)."""
     sgs = [w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64), w.conv2d(1, 64, 56, 56, 64, 3, 3), w.depthwise_conv2d(1, 512, 28, 28, 3, 3),
            w.gemm(128, 768, 3072)]
     slots = max(w.n_slots(s) for s in sgs)
@@ -559,8 +562,8 @@ def test_lse_small_populations(P, steps, q16):
 
 
 def test_lse_large_selection_route_and_full_k(P):
-    """One segment long enough for the large selection route and the per-class draft launches (aligned offsets),
-    k = 4096 so that the union sorted in LDS has 8192 entries; copies are plentiful after the first mutation."""
+    """One segment long enough for the selection's longest route and the per-class draft launches,
+    k = 4096 so that the union has 8192 entries; copies are plentiful after the first mutation."""
     sgs = [w.gemm(512, 512, 512), w.depthwise_conv2d(1, 512, 28, 28, 3, 3)]
     seg, tiles = lse_population(sgs, [1 << 20, 140000], seed=22)
     check_lse_against_oracle(P, sgs, seg, tiles, 4096, 3, 5, 60000)
@@ -1026,7 +1029,7 @@ def test_moa_update_feeds_the_verify_stage(P):
 
 
 def test_prior_filter_long_and_short_segments_together(P):
-    """the selection's large route with segments from 64 to 1.3 M candidates in one call (k equal to the shortest), and
+    """the selection's longest route with segments from 64 to 1.3 M candidates in one call (k equal to the shortest), and
     the draft kernel's per-class launches with a class that appears twice"""
     sgs = [w.gemm(512, 512, 512), w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(128, 768, 3072), w.depthwise_conv2d(1, 512, 28, 28, 3, 3),
            w.batched_gemm(12, 128, 128, 64)]

@@ -18,8 +18,8 @@ def _scores(n, seed, ties):
 
 
 @pytest.mark.parametrize("lens_big, lens_small, k", [
-    ([300000, 150001, 70000], [40000, 90003], 512),     # large route twice
-    ([200000, 9000], [5000, 4100, 7777], 4096),         # large route, then the one-workgroup route
+    ([300000, 150001, 70000], [40000, 90003], 512),     # the route of two launches behind the digits twice
+    ([200000, 9000], [5000, 4100, 7777], 4096),         # ... then one launch for everything
     ([3000] * 16, [257], 64),                           # the limit of 16 segments, then one short segment
 ])
 def test_static_scratch_selection_equals_pruner_topk(lens_big, lens_small, k):
