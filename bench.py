@@ -304,7 +304,7 @@ def main():
         "dtype": "f32", "data": "synthetic",
         "config": {"workload": wl.name, "candidates": n, "subgraphs": n_sg, "k_draft": wl.k_draft,
                    "verified": n_d, "k_final": wl.k_final},
-        "arithmetic": {"timed": "default: reference rounding in single-launch calls (below 2^20 candidates), fused form above",
+        "arithmetic": {"timed": "default: reference rounding below 2^20 candidates, fused form above (laid out in fours)",
                        "ms_per_step_reference_rounding": ms_reference, "value_reference_rounding": n / (ms_reference * 1e-3),
                        "ms_per_step_fused": ms_fused,
                        "draft_selection_vs_oracle": "row by row equal on this workload in either form (tests/test_gpu_parity.py)"},

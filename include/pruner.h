@@ -62,10 +62,10 @@ enum { PRUNER_SYM_S1, PRUNER_SYM_S2, PRUNER_SYM_S3, PRUNER_SYM_S4, PRUNER_SYM_S6
    Fused: the penalties of a statement group, all of them ratios, are multiplied out and divided once; the score is the
    value of Eq. 1 within 2^-20 relative, and a selection taken on it can differ from the reference's at the cut, between
    candidates whose scores lie within that distance of each other.
-   Default: reference rounding for calls that run as one launch (populations below 2^20 candidates, where a call is
-   bound by launch latency and the divisions cost nothing measurable; also larger ones that are not laid out in fours:
-   a segment start, the pitch or a pointer that is not a multiple of four candidates), fused for larger populations
-   laid out in fours (about 13 % faster there).  Either way a score is a function of its candidate
+   Default: reference rounding for populations below 2^20 candidates (where a call is bound by launch latency and the
+   divisions cost nothing measurable) and for larger ones that are not laid out in fours (a segment start, the pitch
+   or a pointer that is not a multiple of four candidates), fused for larger populations laid out in fours (about 13 %
+   faster there); into how many launches a call is cut plays no part.  Either way a score is a function of its candidate
    alone: the same candidate scores the same bits in any population, launch shape or neighbourhood.  The two switches
    force one form for every size; setting both is an error. */
 #define PRUNER_REFERENCE_ROUNDING 4
@@ -182,8 +182,8 @@ int pruner_draft_score(const pruner_subgraph* sg, int32_t n_sg, const int64_t* s
 /*
  * Measurement hook, not part of the method: from now on every call that scores a population (pruner_draft_score,
  * pruner_prior_filter, pruner_lse) records `start_event` right before and `stop_event` right after the one draft
- * kernel launch of the call that covers the most candidates (a call launches one kernel per loop-nest class), on the
- * call's stream, and stores that launch's algorithmic bytes (candidates x (2 x tile slots + 4)) in
+ * kernel launch of the call that covers the most candidates (a call is one launch or, for some populations, one per
+ * loop-nest class), on the call's stream, and stores that launch's algorithmic bytes (candidates x (2 x tile slots + 4)) in
  * *algorithmic_bytes (host, may be NULL).  Both events NULL switches the hook off.  The events are the caller's
  * (hipEvent_t); process-wide state, not thread-safe: for benchmarks.
  * Errors: PRUNER_EINVAL if exactly one event is NULL.

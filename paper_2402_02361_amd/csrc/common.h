@@ -101,7 +101,7 @@ struct TopkCtx {
     char inline_segs[4096];  // tiny route: the segment table when it travels as a kernel argument
     bool inline_ok;
 };
-// validates, uploads the segment table, clears the histograms (large route)
+// validates, uploads the segment table, clears the histograms (of the routes that count digits)
 // (defer: do not launch the upload, describe it there instead; copies: the scores are expected to hold ties by the thousand)
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t stream, TopkCtx* ctx,
                  Upload* defer, bool with_block_max, bool copies);
@@ -128,7 +128,7 @@ struct DraftPlan {
     size_t descs_at = 0;
     int64_t n = 0, tiles_pitch = 0;
     int32_t n_sg = 0, flags = 0;
-    bool counts = false;   // the kernels add every score's first selection digit to a histogram (full load width)
+    bool counts = false;   // the kernels add every score's first selection digit to a histogram (four candidates per thread, no symbol dump)
     bool makes = false;    // the kernels can make their candidates (the explorer loop's mutation) instead of reading them
 };
 // count_digits: the caller has histograms to add to (plan->counts says whether the launch shape allows it); mut: the kernels

@@ -9,8 +9,8 @@
 //   symbols are exact integers (Table 2);
 //   penalties, utilisation and latency (Sec. 4.1 "Hardware-aware Penalty", Eq. 1) are binary32, in one of two forms.
 //   analyze_fused(): the penalties of a statement group, all of them ratios, multiplied out and divided once (within
-//   2^-20 relative of Eq. 1's value); used by the per-class launches of populations of 2^20 candidates and more, or
-//   everywhere under PRUNER_FUSED_ARITHMETIC.  analyze(): one IEEE operation per step (used by single-launch calls, or
+//   2^-20 relative of Eq. 1's value); used for populations of 2^20 candidates and more that are laid out in fours, or
+//   everywhere under PRUNER_FUSED_ARITHMETIC.  analyze(): one IEEE operation per step (used for all others, or
 //   everywhere under PRUNER_REFERENCE_ROUNDING), in this order:
 //     P0m = min(m_l0 / S1, 1)          P0c = 1 + S2 / S1            P1m = min(m_l1 / S3, 1)
 //     sch = ceil(S4 / n_l1)            P1c = sch / (ceil(sch / pu_l1) * pu_l1)
@@ -1006,8 +1006,9 @@ constexpr int kProducts = -2;   // plain and batched matrix products: the kernel
 
 // One launch scores the segments of one loop-nest class (CLS), so that each class gets the register budget, and with
 // it the occupancy, of its own symbol code; CLS = kAnyClass branches on the class at run time instead and serves
-// small populations, where one launch for everything beats several, and the narrow load widths.
-// HIST: the workgroup also counts the first selection digit (top 11 bits of the order-preserving key) of its scores
+// populations of several classes where one launch for everything beats several (see the launch plan), and those of fewer
+// than four candidates, which are loaded one by one (VEC = 1).
+// HIST: the workgroup also counts the first selection digit (first_digit_of) of its scores
 // in LDS and merges the counts into one of `copies` global histograms of its segment.
 // MUT: the candidates are not read but made (SchMutation from S_spec, `mut`), stored and scored in one pass.
 template <int CLS, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
@@ -1072,7 +1073,7 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
 
 using DraftFn = void (*)(const SegEnt*, int32_t, const SgDesc*, const uint16_t*, int64_t, int32_t, float*, int64_t*, int64_t, uint32_t*, uint32_t*, int, int, MutArgs);
 
-// The digit-counting variant exists for the full load width without the symbol dump (the shape large populations run in).
+// The digit-counting variant exists for four candidates per thread without the symbol dump.
 template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, bool mut)
 {
     if constexpr (CLS == kAnyClass) {
@@ -1100,7 +1101,7 @@ template <bool DUMP, bool EXACT> DraftFn pick_class(int cls, int vec, bool hist,
         default: return pick_vec<kAnyClass, DUMP, EXACT>(vec, hist, mut);
     }
 }
-// mut is honoured for the per-class kernels at the full load width (they count the first selection digit if asked to)
+// mut is honoured for the per-class kernels with four candidates per thread (they count the first selection digit if asked to)
 DraftFn pick_kernel(int cls, int vec, bool dump, bool exact, bool hist, bool mut)
 {
     if (dump) return exact ? pick_class<true, true>(cls, vec, hist, mut) : pick_class<true, false>(cls, vec, hist, mut);
@@ -1449,7 +1450,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     bool in_fours = tiles_pitch % 4 == 0 && aligned(tiles, 8) && aligned(score, 16);   // every thread's candidates start at a multiple of four
     for (int32_t s = 0; s < n_sg; ++s) in_fours = in_fours && seg_off[s] % 4 == 0;
 
-    // Launch plan.  At the full load width: one launch per loop-nest class present, the table grouped by class, when the
+    // Launch plan.  With four candidates per thread: one launch per loop-nest class present, the table grouped by class, when the
     // population is large (with more than two classes: 2^20 candidates for each, since every launch begins and ends with a
     // partly empty device: ten segments of four classes, 3.3 M candidates, take 56 us in four launches and 43 in one), when
     // there is only one class (its own kernel needs half the registers of the one that branches
@@ -1476,8 +1477,8 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     }
     // Arithmetic of Eq. 1: one rounded operation per step of the definitions below 2^20 candidates (a call is then bound by
     // launch latency, and the dozen divisions per candidate cost nothing measurable) and where the population is not laid
-    // out in fours (the boundary says so; it was the narrow loads' rule), the multiplied-out form for the other large
-    // populations, unless a flag asks for one of them.
+    // out in fours (as the boundary promises; how many launches there are plays no part), the multiplied-out form for the
+    // other large populations, unless a flag asks for one of them.
     const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !(large && in_fours));
     const bool hist = count_digits && vec == 4 && symbols == nullptr;
     const bool fused = mut && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself

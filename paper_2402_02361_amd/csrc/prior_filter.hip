@@ -1,8 +1,8 @@
 // PriorFilter of Alg. 2 as one call: C_SA over the whole population, then the k best per subgraph.
 //
-// The same kernels as pruner_draft_score followed by pruner_topk, with one saving: when the population takes the
-// selection's large route and the draft kernel runs at its full load width, the draft kernel counts the first
-// selection digit of every score while it still holds the score in a register, and the selection skips its first
+// The same kernels as pruner_draft_score followed by pruner_topk, with one saving: where the selection counts digits
+// (segments above 8,192 entries, or k above 64) and the population has four candidates and more, the draft kernel counts the
+// first digit of every score while it still holds the score in a register, and the selection skips its first
 // pass over the score array.  The result is the same as that of the two separate calls, bit for bit.
 #include "common.h"
 #include "select_common.h"

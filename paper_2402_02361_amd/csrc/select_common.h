@@ -6,7 +6,7 @@
 
 namespace pruner {
 
-constexpr int kBins = 2048;   // 11-bit digits (the last pass uses the lower 1024 bins)
+constexpr int kBins = 2048;   // 11-bit digits
 
 // Larger score <=> larger key; -0.0 and +0.0 share a key.
 __device__ __forceinline__ uint32_t key_of(float x)

@@ -740,7 +740,7 @@ def test_step_replayed_from_a_captured_graph(P, idx, scale):
 @pytest.mark.parametrize("lens,per_class", [([300000, 40000], False), ([800000, 400000], True)])
 def test_timing_hook_brackets_the_largest_launch(P, lens, per_class):
     """the measurement hook: events recorded around one draft kernel launch, algorithmic bytes of that launch; results
-    unchanged.  Below 2^20 candidates a call is one launch; above, one per loop-nest class."""
+    unchanged.  Below 2^20 candidates this call of two loop-nest classes is one launch; above, one per class."""
     import ctypes
     sgs = [w.gemm(512, 512, 512), w.conv2d(1, 64, 56, 56, 64, 3, 3)]
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
