@@ -99,7 +99,7 @@ template <int NT> __device__ __forceinline__ void sort_descending(uint64_t* w, i
     __syncthreads();
 }
 
-__device__ __forceinline__ int pow2_at_least(int k)
+__host__ __device__ __forceinline__ int pow2_at_least(int k)
 {
     int P = 1;
     while (P < k) P <<= 1;
@@ -1102,7 +1102,8 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
 
 // LISTS: the lists route.  COUNT: segments of at most kCountMax entries whose first digit nobody has counted; every workgroup does
 // so itself, and the call is this one launch.
-template <bool LISTS, bool COUNT, class Table>
+// SORT: with the way of sorting what would take many rounds to rank (the other calls' kernel is shorter without it).
+template <bool LISTS, bool COUNT, bool SORT, class Table>
 __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, Table segs, int n_seg, int n_total, int R,
                                                            int k, int share, int span, const uint32_t* __restrict__ ghist0,
                                                            const uint32_t* __restrict__ ghist1, const uint32_t* __restrict__ granges,
@@ -1379,7 +1380,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     const int n_last = n - (int)((uint32_t)k - k_rem);   // the words of the last bin
     const bool trim = n > k && n_last <= kTrimMax && pow2_at_least(n) > pow2_at_least(k);
     const int rounds = (n + 64 * share - 1) / (64 * share);
-    if (rounds * n > kSortFactor * pow2_at_least(trim ? k : n)) {
+    if (SORT && rounds * n > kSortFactor * pow2_at_least(trim ? k : n)) {
         if (trim) {
             // the sort is half as long without those of the last bin that are not selected: their places go to what lies behind k
             uint64_t* bin_word = reinterpret_cast<uint64_t*>(place);
@@ -1634,6 +1635,7 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     int share = (k + 31) / 32;
     if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
     if (share < 1) share = 1;
+    const bool sort = (k + 64 * share - 1) / (64 * share) * k > kSortFactor * pow2_at_least(k);   // (a collection is k words and a little more)
     const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
     const SegsInMemory in_memory{d_segs};
     if (ctx.count && !have_first_digit) {
@@ -1641,10 +1643,10 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
         memset(&args, 0, sizeof args);
         if (ctx.inline_ok) {
             memcpy(&args, ctx.inline_segs, sizeof args);
-            hipLaunchKernelGGL((pick_kernel<false, true, InlineSegs>), pickers, dim3(kBigThreads), 0, st, score, args, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
+            hipLaunchKernelGGL((sort ? pick_kernel<false, true, true, InlineSegs> : pick_kernel<false, true, false, InlineSegs>), pickers, dim3(kBigThreads), 0, st, score, args, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
                                nullptr, nullptr, 0, idx_out, val_out);
         } else {
-            hipLaunchKernelGGL((pick_kernel<false, true, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
+            hipLaunchKernelGGL((sort ? pick_kernel<false, true, true, SegsInMemory> : pick_kernel<false, true, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
                                nullptr, nullptr, 0, idx_out, val_out);
         }
         PRUNER_LAUNCH_CHECK();
@@ -1668,10 +1670,10 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
         if (ctx.lists) {
             hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, hist2, d_stage);
             PRUNER_LAUNCH_CHECK();
-            hipLaunchKernelGGL((pick_kernel<true, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
+            hipLaunchKernelGGL((sort ? pick_kernel<true, false, true, SegsInMemory> : pick_kernel<true, false, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         } else {
-            hipLaunchKernelGGL((pick_kernel<false, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
+            hipLaunchKernelGGL((sort ? pick_kernel<false, false, true, SegsInMemory> : pick_kernel<false, false, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
                                ctx.blocks, idx_out, val_out);
         }
         PRUNER_LAUNCH_CHECK();
