@@ -24,9 +24,9 @@
 // the candidate's slots.
 //
 // Measured, before = eight padded slots per candidate in either branch and binary32 pooled vectors, the same bits (statement
-// counts 3..8, blocks 0..5): 131,072 candidates: statement kernel 345 -> 212 us, dataflow 170 -> 66, head 43 -> 28, the call
-// 515 -> 296; 8,192 candidates: 29.8 -> 19.7, 23.7 -> 9.4, 10.7 -> 9.4, the call 61 -> 38.  (With the sums over rows on the matrix
-// cores too, by the rows' places in a tile, 246 and 38: one score in a thousand then changed with the neighbours.)
+// counts 3..8, blocks 0..5): 131,072 candidates: statement kernel 345 -> 196 us, dataflow 170 -> 66, head 43 -> 28, the call
+// 518 -> 288; 8,192 candidates: 29.8 -> 19.3, 23.7 -> 9.8, 10.7 -> 9.5, the call 60 -> 37.  (With the sums over rows on the matrix
+// cores too, by the rows' places in a tile, 252 and 37: one score in a thousand then changed with the neighbours.)
 #include "common.h"
 #include "mfma_tile.h"
 
@@ -84,8 +84,8 @@ __device__ __forceinline__ void load_slices(bf16x8 (&wr)[2][KS], const uint16_t*
 // a tile the rows lie: a score is a function of its candidate alone.  (Sums on the matrix cores, against a 0/1 matrix, add the
 // rows in groups of eight by their place in the tile, and a pooled vector then depends on the neighbours.)  A wavefront parks
 // the second hidden layer of its 64 units in LDS and reads the rows back candidate by candidate.
-// Bound: what a SIMD's one wavefront issues in turn.  131,072 candidates, by the counters: 10,600 cycles a tile, the matrix pipe
-// busy in 32 % of them, the vector ALU in 23 % (620 instructions), LDS in 30 %; weights and first rows on their way for small sets.
+// Bound: what a SIMD's one wavefront issues in turn and waits for.  131,072 candidates, by the counters: the matrix pipe busy 36 %
+// of the time, the vector ALU 29 %, LDS 35 %; weights and first rows on their way for small sets.
 
 constexpr int kRowThreads = 8;                                   // threads that share a feature row: 128 contiguous bytes per request
 constexpr int kXPass = kTM / (kThreads / kRowThreads);           // passes over the tile's rows (2)
@@ -378,8 +378,8 @@ pacm_stmt_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_s
 // Every sum runs over a candidate's own slots in a fixed order, wherever in a tile they lie (softmax and pooled vectors ((0 + 1)
 // + (2 + 3)) + ((4 + 5) + (6 + 7)), the products with the attention weights one key after the other): a score is a function of
 // its candidate alone, and nothing of one candidate reaches another.
-// Bound: vector instructions and the waits between dependent stages (131,072 candidates, 2.8 blocks on average, by the counters:
-// vector ALU busy in 47 % of the cycles, matrix pipe in 12 %, two wavefronts per SIMD).
+// Bound: vector instructions, and the waits between dependent stages (131,072 candidates, by the counters: vector ALU busy 74 %
+// of the time where every candidate takes two quads, 47 % with 2.8 blocks on average and a third of the tiles).
 
 constexpr int kFlowWaves = 4;                 // wavefronts per workgroup, each with tiles of its own
 constexpr int kFlowThreads = 64 * kFlowWaves;
@@ -680,7 +680,7 @@ pacm_flow_kernel(const float* __restrict__ flow, const int32_t* __restrict__ n_b
 // The two 32-row halves of a tile run one after the other on the matrix cores; rounding, the output dot product (binary32, in
 // the order of a lane's units) and the stores of one half, and the next tile's way into LDS, are issued between the MFMAs
 // of the other.  Two tiles' operands in LDS, two barriers per tile.  131,072 candidates: 640 bytes each at 3 TB/s, matrix pipe
-// busy in 27 % of the cycles, vector ALU in 21 %; weights and launch for small sets.
+// busy 26 % of the time, vector ALU 20 %; weights and launch for small sets.
 
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 pacm_head_kernel(const uint16_t* __restrict__ v_s, const uint16_t* __restrict__ v_d, int32_t n_d, const uint16_t* __restrict__ Wh,

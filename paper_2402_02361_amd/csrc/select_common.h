@@ -208,7 +208,8 @@ __device__ __forceinline__ uint32_t index_of(uint64_t w) { return 0xFFFFFFFFu - 
 //      across its lanes; a maximum's rank among all 256 is its place in its own wavefront plus, by bisection, the
 //      number of larger ones in the other three sorted lists;
 //   3. the words at or above the pivot go to a list in LDS; a word's row is the number of larger words in the list.
-// 3 us where the one-workgroup route of sixteen wavefronts and three digit passes takes 12.
+// 10 us for 4,096 entries and k = 64, 8 for 512 and k = 32, where one workgroup of sixteen wavefronts and three digit passes
+// took 13.
 
 constexpr int kTinyThreads = 256;
 constexpr int kTinyPer = 32;
