@@ -990,7 +990,8 @@ constexpr int64_t kListsMax = 32 * (int64_t)kRow;
 constexpr int kListCap = 1280;
 struct List {                 // the entries of one span at or above the bin (lies in the span's Stage)
     uint32_t count, pad;      // may exceed the capacity
-    uint64_t word[kListCap];  // in no order; where there are NaN, some below the bin may be among them
+    uint64_t word[kListCap];  // in no order; where there are NaN, some below the bin may be among them, and of a span that has more than
+                              // these at or above the bin, its own k best at least
 };
 static_assert(sizeof(List) <= sizeof(Stage), "a list lies where the spans route keeps its stage");
 
@@ -1039,6 +1040,92 @@ __device__ __forceinline__ void note_range(uint32_t not_least, uint32_t largest,
     }
 }
 
+// The list of a span that has more at or above the bin than it holds: the span's own k best, for whatever is among the segment's k
+// best is among these.  They are found as the segment's are, digit by digit in the bin; ties that are too many are taken in
+// index order.  (Scores within one bin, 480,000 in one segment, k = 76: the workgroups that collect took 120 us going through
+// the spans of all lists themselves, the call takes 49 now, 52 by the spans route.)  A function of its own: list_kernel
+// as a rule does without it and keeps its registers.
+__device__ __attribute__((noinline)) void own_best(const float* __restrict__ span_score, int span_len, uint32_t first_index, int k, uint32_t lowest, uint32_t width,
+                                                   uint32_t* hist, uint32_t* wave_tot, uint32_t* found, uint32_t* fill, uint32_t* range, List* mine_list)
+{
+    List& mine = *mine_list;
+    uint32_t lo_key = lowest, w = width, rem = (uint32_t)k, in_bin = 0;
+    float val[kBigPer];
+    bool all = false;   // (with NaN below the bin in the list: the rest may fit after all)
+#pragma unroll 1
+    for (int digits = 0; digits < 3; ++digits) {
+        const int sh = next_shift(w);
+        __syncthreads();
+        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+        if (threadIdx.x == 0) *fill = range[0] = 0;
+        __syncthreads();
+        uint32_t above = 0, inside = 0;   // of this thread
+#pragma unroll 1
+        for (int row = 0; row < span_len; row += kRow) {
+            load_sweep(span_score, row, span_len, val);
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) {
+                const uint32_t key = key_of(val[j]);
+                const bool there = (int)sweep_index(0, j) < span_len - row, in = there && key - lo_key <= w;
+                if (in) atomicAdd(&hist[(key - lo_key) >> sh], 1u);
+                inside += in ? 1u : 0u;
+                above += there && key > lo_key && !in ? 1u : 0u;
+            }
+        }
+        if (digits == 0) {
+            if (above) atomicAdd(fill, above);
+            if (inside) atomicAdd(&range[0], inside);
+        }
+        __syncthreads();
+        if (digits == 0) {
+            all = *fill + range[0] <= (uint32_t)kListCap;
+            if (all) break;
+            rem = (uint32_t)k - *fill;   // (fewer than k lie above the segment's bin)
+        }
+        find_bucket(hist, rem, wave_tot, found);
+        lo_key += found[0] << sh;
+        w = (1u << sh) - 1u;
+        rem = found[1];
+        in_bin = found[2];
+        if ((uint32_t)k - rem + in_bin <= (uint32_t)kListCap || w == 0u) break;
+    }
+    const bool ties_apart = !all && (uint32_t)k - rem + in_bin > (uint32_t)kListCap;
+    __syncthreads();
+    if (threadIdx.x == 0) *fill = 0;
+    __syncthreads();
+    uint32_t ties_before = 0;
+#pragma unroll 1
+    for (int row = 0; row < span_len; row += kRow) {
+        load_sweep(span_score, row, span_len, val);
+        uint32_t mask = 0;
+#pragma unroll
+        for (int j = 0; j < kBigPer; ++j) {
+            const uint32_t key = key_of(val[j]);
+            mask |= (int)sweep_index(0, j) < span_len - row && (ties_apart ? key > lo_key : key >= lo_key) ? 1u << j : 0u;
+        }
+        uint32_t at = reserve(fill, (uint32_t)__popc(mask));
+        for (; mask; mask &= mask - 1, ++at) {
+            const int i = (int)sweep_index(row, __ffs(mask) - 1);
+            if (at < (uint32_t)kListCap) mine.word[at] = compose(key_of(span_score[i]), first_index + (uint32_t)i);
+        }
+        if (ties_apart && ties_before < rem) {
+            // behind the k - rem above them, numbered in index order: four neighbours of every thread at a time
+#pragma unroll
+            for (int q = 0; q < kBigPer / 4; ++q) {
+                uint32_t tie = 0, total;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tie |= (int)sweep_index(0, 4 * q + e) < span_len - row && key_of(val[4 * q + e]) == lo_key ? 1u << e : 0u;
+                uint32_t number = ties_before + block_excl_scan<kBigThreads>((uint32_t)__popc(tie), wave_tot, &total);
+                for (; tie && number < rem; tie &= tie - 1, ++number)
+                    mine.word[(uint32_t)k - rem + number] = compose(lo_key, first_index + (uint32_t)sweep_index(row, 4 * q + __ffs(tie) - 1));
+                ties_before += total;
+            }
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) mine.count = ties_apart ? (uint32_t)k : *fill;
+}
+
 __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_eu(8))) list_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg,
                                                                                                     int64_t span, int R, int k,
                                                                                                     const uint32_t* __restrict__ ghist0,
@@ -1061,7 +1148,9 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     first_digit_range(found[0], lowest, width);
     const float t0 = threshold_of(lowest);
     const int shift = next_shift(width);
-    const bool crowded = (uint32_t)k - found[1] + found[2] > (uint32_t)collect_limit(k);   // the second digit will be asked for
+    const uint32_t at_or_above = (uint32_t)k - found[1] + found[2];   // of the bin, in the segment
+    const bool crowded = at_or_above > (uint32_t)collect_limit(k);    // the second digit will be asked for
+    static_assert(collect_limit(kListCap) <= 6 * kListCap, "where six lists overflow the bin is crowded");
     __syncthreads();
     if (threadIdx.x == 0) fill = range[0] = range[1] = 0;
     if (crowded)
@@ -1098,6 +1187,10 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
         flush_hist<kBigThreads>(hist, ghist1, 1, n_seg, s);
         if (threadIdx.x < 2 && range[threadIdx.x] != 0u) atomicMax(&granges[(size_t)s * kBins + threadIdx.x], range[threadIdx.x]);
     }
+    // One value: its ties need no list.  Few such lists (a stretch of good entries, as in a sorted segment): whoever collects goes
+    // through their spans, 3 us each, in less time than the 18 us that this takes.
+    if (fill > (uint32_t)kListCap && k <= kListCap && at_or_above / 6u > fill && ~range[0] != range[1])
+        own_best(score + lo, (int)(hi - lo), (uint32_t)lo, k, lowest, width, hist, wave_tot, found, &fill, range, &mine);
 }
 
 // LISTS: the lists route.  COUNT: segments of at most kCountMax entries whose first digit nobody has counted; every workgroup does
@@ -1172,14 +1265,27 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     // The spans of lists that overflowed (a stretch of good entries, as a sorted segment has it) are gone through by the whole
     // workgroup: what(row, hi, val) for each of their sweeps.
     auto through_overflowed = [&](auto&& what) {
-        for (unsigned long long left = overflowed; left; left &= left - 1ull) {
-            const int lo = (__ffsll(left) - 1) * span, hi = lo + span < len ? lo + span : len;
+        unsigned long long left = overflowed;
+        int row = 0, hi = 0;
+        auto list = [&] {   // the first sweep of the next list's span
+            row = left ? (__ffsll(left) - 1) * span : 0;
+            hi = row + span < len ? row + span : len;
+        };
+        list();
+        float cur[kBigPer], nxt[kBigPer];
+        if (left) load_sweep(seg_score, row, hi, cur);
 #pragma unroll 1
-            for (int row = lo; row < hi; row += kRow) {
-                float again[kBigPer];
-                load_sweep(seg_score, row, hi, again);
-                what(row, hi, again);
+        while (left) {   // (a sweep is on its way while the one before is looked at)
+            const int this_row = row, this_hi = hi;
+            row += kRow;
+            if (row >= hi) {
+                left &= left - 1ull;
+                list();
             }
+            if (left) load_sweep(seg_score, row, hi, nxt);
+            what(this_row, this_hi, cur);
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) cur[j] = nxt[j];
         }
     };
     uint32_t least = 0u, largest = 0xFFFFFFFFu;   // of the bin's keys
@@ -1307,10 +1413,19 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                 if (((in >> lane) & 1ull) && at < (uint32_t)n) sel[slot(at)] = w;
             }
         }
+        const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
         through_overflowed([&](int row, int hi, const float (&again)[kBigPer]) {
-            uint32_t mask = 0;
+            uint32_t mask = 0, numbers = 0;   // not below the threshold; those of them that are numbers
 #pragma unroll
-            for (int j = 0; j < kBigPer; ++j) mask |= sweep_index(row, j) < hi && collected(key_of(again[j]), !ties_apart) ? 1u << j : 0u;
+            for (int j = kBigPer - 1; j >= 0; --j) {
+                mask = 2 * mask + (again[j] < t0 ? 0u : 1u);
+                numbers = 2 * numbers + (again[j] >= t0 ? 1u : 0u);
+            }
+            if (row + kRow > hi || __ballot(mask != numbers) != 0ull) {   // (an end, or NaN: the keys decide)
+                mask = 0;
+#pragma unroll
+                for (int j = 0; j < kBigPer; ++j) mask |= sweep_index(row, j) < hi && collected(key_of(again[j]), !ties_apart) ? 1u << j : 0u;
+            }
             uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
             for (; mask; mask &= mask - 1, ++at) {
                 const int i = (int)sweep_index(row, __ffs(mask) - 1);
@@ -1340,6 +1455,10 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
             if (at < (uint32_t)kPickCap) place[at] = (uint32_t)(group_begin(bit >> 2) + (bit & 3));
             ++at;
         }
+    }
+    if constexpr (LISTS) {   // (lists that hold their span's k best have fewer words than the counts say)
+        __syncthreads();
+        n = fill < (uint32_t)n ? (int)fill : n;
     }
     // spare words and those behind the last must read as "below everything"
     const int n_raw = n > 0 ? (int)slot((uint32_t)n - 1u) + 1 : 0;

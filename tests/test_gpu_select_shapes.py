@@ -19,11 +19,14 @@ def of(kind, n, rng):
         m = min(n, 3000)
         x[n // 2 - m // 2: n // 2 - m // 2 + m] = -np.exp2(rng.uniform(-30, -27, m)).astype(np.float32)
         return x
+    if kind == "ties and neighbours":   # a third of the entries share a value, a few lie just above it
+        r = rng.random(n)
+        return np.where(r < 0.3, np.float32(2.0), np.where(r < 0.3005, np.float32(2.0) + (r * 0.01).astype(np.float32), values("normal", n, rng) * np.float32(0.3))).astype(np.float32)
     return values(kind, n, rng)
 
 
-@pytest.mark.parametrize("kind", ["ascending", "clump", "one bin", "300 values", "equal"])
-@pytest.mark.parametrize("lens,ks", [([100001, 65537], [512, 1100, 4096]), ([300001] * 3, [33, 2048]), ([524288], [512, 4096]), ([70000] * 130, [512])])
+@pytest.mark.parametrize("kind", ["ascending", "clump", "one bin", "300 values", "equal", "ties and neighbours", "two values"])
+@pytest.mark.parametrize("lens,ks", [([100001, 65537], [3, 512, 1100, 1280, 1281, 4096]), ([300001] * 3, [33, 2048]), ([524288], [512, 4096]), ([70000] * 130, [512])])
 def test_lists_that_overflow(P, kind, lens, ks):
     rng = np.random.default_rng(len(kind) + len(lens))
     seg = np.concatenate([[0], np.cumsum(lens)])
