@@ -128,13 +128,13 @@ struct DraftPlan {
     size_t descs_at = 0;
     int64_t n = 0, tiles_pitch = 0;
     int32_t n_sg = 0, flags = 0;
-    bool counts = false;   // the kernels add every score's first selection digit to a histogram (four candidates per thread, no symbol dump)
+    bool counts = false;   // the kernels add every score's first selection digit to a histogram (no symbol dump)
     bool makes = false;    // the kernels can make their candidates (the explorer loop's mutation) instead of reading them
 };
 // count_digits: the caller has histograms to add to (plan->counts says whether the launch shape allows it); mut: the kernels
 // are to make their candidates from the second run on (plan->makes says whether they can).
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
-               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool mut, DraftPlan* plan);
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool block_maxima, bool mut, DraftPlan* plan);
 // (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables
 // and behind which nothing else lies that must stay.  An upload that begins right behind the tables (place_behind) shares
 // their launch.

@@ -130,6 +130,7 @@ struct alignas(8) SegEnt {
 };
 
 constexpr int kTabMax = 4096;   // longest run length the P_l2,m table covers
+constexpr int64_t kRaggedMin = 1 << 19;   // candidates from which a population that is not laid out in fours is loaded in fours all the same
 constexpr int64_t kPerClassMin = 1 << 20;   // candidates from which a call launches one kernel per loop-nest class
 
 // ---- symbols (Table 2) ---------------------------------------------------------------------------------------------
@@ -1006,8 +1007,8 @@ constexpr int kProducts = -2;   // plain and batched matrix products: the kernel
 
 // One launch scores the segments of one loop-nest class (CLS), so that each class gets the register budget, and with
 // it the occupancy, of its own symbol code; CLS = kAnyClass branches on the class at run time instead and serves
-// populations of several classes where one launch for everything beats several (see the launch plan), and those of fewer
-// than four candidates, which are loaded one by one (VEC = 1).
+// populations of several classes where one launch for everything beats several (see the launch plan), and all that are loaded
+// one by one (VEC = 1): fewer than four candidates, and small ones of several classes that are not laid out in fours.
 // HIST: the workgroup also counts the first selection digit (first_digit_of) of its scores
 // in LDS and merges the counts into one of `copies` global histograms of its segment.
 // MUT: the candidates are not read but made (SchMutation from S_spec, `mut`), stored and scored in one pass.
@@ -1073,10 +1074,13 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
 
 using DraftFn = void (*)(const SegEnt*, int32_t, const SgDesc*, const uint16_t*, int64_t, int32_t, float*, int64_t*, int64_t, uint32_t*, uint32_t*, int, int, MutArgs);
 
-// The digit-counting variant exists for four candidates per thread without the symbol dump.
+// The digit-counting variants come without the symbol dump.
 template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, bool mut)
 {
     if constexpr (CLS == kAnyClass) {
+        if constexpr (!DUMP) {
+            if (vec == 1 && hist) return draft_kernel<CLS, 1, false, EXACT, true, false>;
+        }
         if (vec == 1) return draft_kernel<CLS, 1, DUMP, EXACT, false, false>;
     }
     if constexpr (!DUMP) {
@@ -1406,7 +1410,7 @@ void* g_time_stop = nullptr;
 int64_t* g_time_bytes = nullptr;
 
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
-               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool mut, DraftPlan* out)
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool block_maxima, bool mut, DraftPlan* out)
 {
     if (!sg || !seg_off || n_sg < 1 || n_sg > PRUNER_MAX_SUBGRAPHS) return PRUNER_EINVAL;
     if (flags & ~(PRUNER_NO_COMPUTE_PENALTY | PRUNER_NO_MEMORY_PENALTY | PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) return PRUNER_EINVAL;
@@ -1446,9 +1450,15 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
         return PRUNER_OK;
     }
 
-    const int vec = load_width(n);
     bool in_fours = tiles_pitch % 4 == 0 && aligned(tiles, 8) && aligned(score, 16);   // every thread's candidates start at a multiple of four
     for (int32_t s = 0; s < n_sg; ++s) in_fours = in_fours && seg_off[s] % 4 == 0;
+    uint32_t classes = 0;
+    for (int32_t s = 0; s < n_sg; ++s) classes |= 1u << descs[desc_of[s]].cls;
+    const int n_classes = __builtin_popcount(classes);
+    // Several classes in a population that is neither large nor laid out in fours: candidates one by one, four times the threads,
+    // for the kernel that branches on the class is short of them (6 x 3,001, k = 6: 20.2 -> 17.6 us; 400,020: 23.0 -> 20.7;
+    // 900,020: no difference).  (Block maxima need fours, and so do kernels that make their candidates.)
+    const int vec = mut || block_maxima || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
 
     // Launch plan.  With four candidates per thread: one launch per loop-nest class present, the table grouped by class, when the
     // population is large (with more than two classes: 2^20 candidates for each, since every launch begins and ends with a
@@ -1461,13 +1471,8 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // half the registers, twice the workgroups at once: 20 x 50,000 candidates take 13.3 us instead of 14.8).  A
     // launch has at most as many workgroups as the device holds at once; they walk through the chunks of their segment.
     std::vector<int32_t> order(n_sg);
-    uint32_t classes = 0;
-    for (int32_t s = 0; s < n_sg; ++s) {
-        order[s] = s;
-        classes |= 1u << descs[desc_of[s]].cls;
-    }
+    for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
     const bool large = vec == 4 && n >= kPerClassMin;
-    const int n_classes = __builtin_popcount(classes);
     const bool by_class = vec == 4 && ((large && (mut || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (mut ? 2 : 1));
     if (by_class && n_classes > 1) {   // (a pass per class: sorting a thousand segments of one class took 14 us of host time)
         order.clear();
@@ -1480,7 +1485,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // out in fours (as the boundary promises; how many launches there are plays no part), the multiplied-out form for the
     // other large populations, unless a flag asks for one of them.
     const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !(large && in_fours));
-    const bool hist = count_digits && vec == 4 && symbols == nullptr;
+    const bool hist = count_digits && symbols == nullptr;
     const bool fused = mut && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
     std::vector<int64_t> chunks_of;
@@ -1588,7 +1593,7 @@ extern "C" int pruner_draft_score(const pruner_subgraph* sg, int32_t n_sg, const
 {
     hipStream_t st = static_cast<hipStream_t>(stream);
     DraftPlan plan;
-    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes, false, false, &plan);
+    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes, false, false, false, &plan);
     if (rc) return rc;
     rc = draft_upload(plan, workspace, st, nullptr);
     if (rc) return rc;

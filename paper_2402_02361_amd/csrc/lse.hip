@@ -844,7 +844,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     for (int32_t s = 0; s < n_sg; ++s) longest = seg_off[s + 1] - seg_off[s] > longest ? seg_off[s + 1] - seg_off[s] : longest;
     if (longest <= kShortMax && k <= kShortK) {
         DraftPlan plan;
-        rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, false, n_steps > 1, &plan);
+        rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, false, false, n_steps > 1, &plan);
         if (rc) return rc;
         // all tables in one launch: this route has no selection workspace, the segment table stands in its place
         d_table = reinterpret_cast<LseSeg*>(ws + L.filter + draft_bytes);
@@ -902,8 +902,8 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         Upload pending;
         rc = topk_prepare(seg_off, n_sg, k, ws + L.filter + draft_bytes, filter_bytes - draft_bytes, st, &ctx, &pending, true, true);
         if (rc) return rc;
-        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, false, &plan_first);
-        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, true, &plan_later);
+        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, false, &plan_first);
+        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, true, &plan_later);
         if (rc) return rc;
         const DraftPlan& plan = t == 0 ? plan_first : plan_later;
         const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, nullptr};

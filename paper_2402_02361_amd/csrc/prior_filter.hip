@@ -1,9 +1,8 @@
 // PriorFilter of Alg. 2 as one call: C_SA over the whole population, then the k best per subgraph.
 //
 // The same kernels as pruner_draft_score followed by pruner_topk, with one saving: where the selection counts digits
-// (segments above 8,192 entries, or k above 64) and the population has four candidates and more, the draft kernel counts the
-// first digit of every score while it still holds the score in a register, and the selection skips its first
-// pass over the score array.  The result is the same as that of the two separate calls, bit for bit.
+// (segments above 8,192 entries, or k above 64), the draft kernel counts the first digit of every score while it still holds
+// the score in a register, and the selection skips its first pass over the score array.  The result is the same as that of the two separate calls, bit for bit.
 #include "common.h"
 #include "select_common.h"
 
@@ -41,7 +40,7 @@ extern "C" int pruner_prior_filter(const pruner_subgraph* sg, int32_t n_sg, cons
     int rc = topk_prepare(seg_off, n_sg, k, ws + draft_bytes, workspace_bytes - draft_bytes, st, &ctx, &pending, true, false);
     if (rc) return rc;
     DraftPlan plan;
-    rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, ctx.large, false, &plan);
+    rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, false, &plan);
     if (rc) return rc;
     if (pending.dst) ctx.d_segs = place_behind(plan, ws, &pending);
     rc = draft_upload(plan, ws, st, &pending);

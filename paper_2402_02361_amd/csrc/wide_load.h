@@ -4,7 +4,7 @@
 
 namespace pruner {
 
-// Candidates per thread: four wherever the population holds that many.
+// Candidates per thread where loads are wide: four, if the population holds that many.
 constexpr int load_width(int64_t n) { return n >= 4 ? 4 : 1; }
 
 // The first of the VEC neighbouring candidates that the thread of candidate c reads from every row: c itself, or the last place from

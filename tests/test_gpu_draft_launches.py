@@ -1,5 +1,6 @@
 """Draft calls of several loop-nest classes, interleaved in the segment order: whether a class gets a launch of its own (two classes,
-or 2^20 candidates for each of more) or one kernel branches on the class, a segment scores as it does in a call of its own."""
+or 2^20 candidates for each of more) or one kernel branches on the class, loading candidates in fours or, in a small population that
+is not laid out in fours, one by one, a segment scores as it does in a call of its own."""
 import numpy as np
 import pytest
 
@@ -18,7 +19,9 @@ BATCHED, OTHER = w.batched_gemm(12, 128, 128, 64), w.gemm(128, 768, 3072)
     ([DEPTHWISE, GEMM, CONV, OTHER, CONV], [1100000, 600004, 500000, 500000, 600000]),          # three, 2^20 for each: three
     ([DEPTHWISE, GEMM, CONV, OTHER, CONV], [1000000, 600004, 400000, 500000, 600000]),          # three, not 2^20 for each: one
     ([GEMM, BATCHED, OTHER, BATCHED], [500004, 300000, 200000, 100003]),                        # the two kinds of matrix products
-    ([CONV, GEMM, CONV, OTHER], [30001, 25000, 0, 4003]), ([GEMM, OTHER], [4001, 300])])
+    ([CONV, GEMM, CONV, OTHER], [30001, 25000, 0, 4003]), ([GEMM, OTHER], [4001, 300]),
+    ([CONV, GEMM], [3, 2]), ([CONV, GEMM, DEPTHWISE], [3001, 2500, 9001]), ([CONV, GEMM, DEPTHWISE], [3004, 2500, 9000]),       # (9001: digits counted)
+    ([DEPTHWISE, GEMM, CONV], [200001, 200001, 124285]), ([DEPTHWISE, GEMM, CONV], [200001, 200001, 124286])])   # 2^19 - 1, 2^19
 def test_a_segment_scores_as_in_a_call_of_its_own(P, sgs, lens):
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     rows = max(w.n_slots(s) for s in sgs)

@@ -109,7 +109,7 @@ def test_draft_every_schedule_of_a_tiny_gemm(P):
 def test_draft_ragged_segments_and_alignment(P, offs):
     """Segments that start at any candidate: the wide loads and stores at addresses that are multiples of an element only, and
     the last thread's load moved back where the population is not a multiple of four; an empty segment and a 1-candidate
-    segment ride along.  (Single loads: test_gpu_draft_window.py.)"""
+    segment ride along.  (Single loads: test_gpu_draft_window.py, test_gpu_draft_launches.py.)"""
     sgs = [w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64), w.conv2d(1, 64, 56, 56, 64, 3, 3),
            w.depthwise_conv2d(1, 512, 28, 28, 3, 3), w.gemm(128, 768, 3072)][: len(offs) - 1]
     seg = np.array(offs, np.int64)
