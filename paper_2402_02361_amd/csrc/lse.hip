@@ -153,7 +153,7 @@ template <int SIZE> __device__ __forceinline__ uint32_t count_above(const uint64
 // Dynamic LDS: both lists' keys.
 constexpr int kOldWindow = 256;
 __host__ __device__ constexpr int rank_words(int k) { return (k + kRun - 1) / kRun * kRun + (k + kOldWindow - 1) / kOldWindow * kOldWindow; }
-__global__ void __launch_bounds__(kLseThreads) lse_rank_kernel(int k, bool first, Spec before, const uint64_t* __restrict__ fresh_hi,
+__global__ void __launch_bounds__(kLseThreads) lse_rank_kernel(int k, bool first, int groups, Spec before, const uint64_t* __restrict__ fresh_hi,
                                                                const uint64_t* __restrict__ fresh_lo, uint64_t* __restrict__ union_hi,
                                                                uint64_t* __restrict__ union_lo)
 {
@@ -164,11 +164,10 @@ __global__ void __launch_bounds__(kLseThreads) lse_rank_kernel(int k, bool first
     const int s = blockIdx.y, lane = lane_id(), wave = threadIdx.x >> 6, runs = (k + kRun - 1) / kRun;
     const int64_t col0 = (int64_t)s * k;
     const int n_old = first ? 0 : spec_members(before.count, s, k);
-    const bool old_side = (int)blockIdx.x < runs;
-    const int base = ((int)blockIdx.x - (old_side ? 0 : runs)) * kRun;
-    const int left = (old_side ? n_old : k) - base, n_mine = left < kRun ? left : kRun;
-    if (n_mine <= 0) return;
-    const int n_fresh = runs * kRun, n_window = old_side ? 0 : (n_old + kOldWindow - 1) / kOldWindow * kOldWindow;
+    // this workgroup's groups of 64 entries: those of S_spec are counted first, then those of the k best
+    const int g0 = (int)blockIdx.x * groups, g1 = g0 + groups < 2 * runs ? g0 + groups : 2 * runs;
+    if (g1 <= runs && g0 * kRun >= n_old) return;
+    const int n_fresh = runs * kRun, n_window = g1 <= runs ? 0 : (n_old + kOldWindow - 1) / kOldWindow * kOldWindow;
     uint64_t *hi = words, *lo = hi + n_fresh, *oh = lo + n_fresh, *ol = oh + n_window;
     for (int i = threadIdx.x; i < n_fresh; i += kLseThreads) {
         hi[i] = i < k ? fresh_hi[col0 + i] : 0ull;
@@ -178,28 +177,36 @@ __global__ void __launch_bounds__(kLseThreads) lse_rank_kernel(int k, bool first
         oh[i] = i < n_old ? before.hi[col0 + i] : 0ull;
         ol[i] = i < n_old ? before.lo[col0 + i] : 0ull;
     }
-    uint64_t my_hi = ~0ull, my_lo = ~0ull;
-    if (lane < n_mine) {
-        my_hi = (old_side ? before.hi : fresh_hi)[col0 + base + lane];
-        my_lo = (old_side ? before.lo : fresh_lo)[col0 + base + lane];
-    }
-    if (threadIdx.x < kWave) place[threadIdx.x] = old_side ? base + threadIdx.x : 0;
-    __syncthreads();
-    uint32_t above = 0;
-#pragma unroll
-    for (int j = 0; j < kRuns; ++j) {
-        const int run = j * kWaves + wave;
-        if (run < runs) above += count_above<kRun>(hi + run * kRun, lo + run * kRun, my_hi, my_lo);
-    }
-    if (wave * kOldWindow < n_window) above += count_above<kOldWindow>(oh + wave * kOldWindow, ol + wave * kOldWindow, my_hi, my_lo);
-    if (above) atomicAdd(&place[lane], above);
-    __syncthreads();
-    if ((int)threadIdx.x < n_mine) {
-        const uint32_t at = place[lane];
-        if (at < 2u * (uint32_t)k) {   // (all keys differ: they hold the position)
-            union_hi[2 * col0 + at] = my_hi;
-            union_lo[2 * col0 + at] = my_lo;
+#pragma unroll 1
+    for (int g = g0; g < g1; ++g) {
+        const bool old_side = g < runs;
+        const int base = (g - (old_side ? 0 : runs)) * kRun;
+        const int left = (old_side ? n_old : k) - base, n_mine = left < kRun ? left : kRun;
+        if (n_mine <= 0) continue;
+        uint64_t my_hi = ~0ull, my_lo = ~0ull;
+        if (lane < n_mine) {
+            my_hi = (old_side ? before.hi : fresh_hi)[col0 + base + lane];
+            my_lo = (old_side ? before.lo : fresh_lo)[col0 + base + lane];
         }
+        if (threadIdx.x < kWave) place[threadIdx.x] = old_side ? base + threadIdx.x : 0;
+        __syncthreads();
+        uint32_t above = 0;
+#pragma unroll
+        for (int j = 0; j < kRuns; ++j) {
+            const int run = j * kWaves + wave;
+            if (run < runs) above += count_above<kRun>(hi + run * kRun, lo + run * kRun, my_hi, my_lo);
+        }
+        if (!old_side && wave * kOldWindow < n_window) above += count_above<kOldWindow>(oh + wave * kOldWindow, ol + wave * kOldWindow, my_hi, my_lo);
+        if (above) atomicAdd(&place[lane], above);
+        __syncthreads();
+        if ((int)threadIdx.x < n_mine) {
+            const uint32_t at = place[lane];
+            if (at < 2u * (uint32_t)k) {   // (all keys differ: they hold the position)
+                union_hi[2 * col0 + at] = my_hi;
+                union_lo[2 * col0 + at] = my_lo;
+            }
+        }
+        __syncthreads();   // (the places are written again)
     }
 }
 
@@ -770,6 +777,7 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
     return L;
 }
 
+constexpr int kMostGroups = 8;        // of 64 entries per workgroup of the rank kernel
 constexpr int kManyUniters = 2048;   // workgroups of 64 places: four times what the device holds at once
 
 PerDeviceFlag g_rank_ready;   // the rank kernel's allowance of dynamic LDS has been raised
@@ -925,8 +933,14 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         hipLaunchKernelGGL(lse_keys_kernel, dim3((unsigned)((k + kRun - 1) / kRun), (unsigned)n_sg), dim3(kLseThreads), 0, st, d_table, k, t == 0,
                            before.count, tiles, tiles_pitch, best_idx, best_val, fresh, fresh + spec_pitch, fresh_aos);
         PRUNER_LAUNCH_CHECK();
-        hipLaunchKernelGGL(lse_rank_kernel, dim3((unsigned)(2 * ((k + kRun - 1) / kRun)), (unsigned)n_sg), dim3(kLseThreads), (size_t)rank_words(k) * 16, st, k, t == 0, before,
-                           fresh, fresh + spec_pitch, merged, merged + 2 * spec_pitch);
+        // (a workgroup loads both lists before it ranks: where there are workgroups for several rounds of the device, which holds one
+        // to two of them per compute unit, each ranks more groups.  100 subgraphs, k = 3,370, four steps: 2,269 us one group each,
+        // 1,361 with eight; sixteen and thirty-two the same, 1,376 and 1,439)
+        const int rank_groups = 2 * ((k + kRun - 1) / kRun);
+        const int64_t rank_rounds = (int64_t)n_sg * rank_groups / 1024;
+        const int groups = rank_rounds < 1 ? 1 : rank_rounds < kMostGroups ? (int)rank_rounds : kMostGroups;
+        hipLaunchKernelGGL(lse_rank_kernel, dim3((unsigned)((rank_groups + groups - 1) / groups), (unsigned)n_sg), dim3(kLseThreads), (size_t)rank_words(k) * 16, st, k, t == 0,
+                           groups, before, fresh, fresh + spec_pitch, merged, merged + 2 * spec_pitch);
         PRUNER_LAUNCH_CHECK();
         const bool last = t + 1 == n_steps;
 #define PRUNER_UNITE(PER) hipLaunchKernelGGL(lse_unite_kernel<PER>, dim3((unsigned)((2 * k + PER * kWave - 1) / (PER * kWave)), (unsigned)n_sg), dim3(kLseThreads), 0, st, k, t == 0, before, \

@@ -41,3 +41,16 @@ def test_many_segments(P):
     sgs = [GEMM, CONV] * 32
     seg, tiles = lse_population(sgs, lens, seed=5)
     check_lse_against_oracle(P, sgs, seg, tiles, 1030, 3, 11, 40000)
+
+
+@pytest.mark.parametrize("n_sg,k,distinct", [(17, 2050, 3000), (40, 4096, 100), (40, 4096, 4200), (260, 1025, 1300)])
+def test_several_groups_per_ranking_workgroup(P, n_sg, k, distinct):
+    """two, five and eight groups of 64 entries: groups of S_spec and of the k best in one workgroup, S_spec of few members, a last
+    workgroup with fewer groups, and a k that no multiple of 64 is"""
+    lens = [k + 4 * (t % 5) for t in range(n_sg)]
+    sgs = [GEMM if t % 2 else FRAG for t in range(n_sg)]
+    seg, tiles = lse_population(sgs, lens, seed=n_sg)
+    for t in range(n_sg):
+        mine = tiles[:, seg[t]:seg[t + 1]]
+        mine[:, distinct:] = mine[:, np.arange(max(0, lens[t] - distinct)) % distinct]
+    check_lse_against_oracle(P, sgs, seg, tiles, k, 3, 13, 30000)
