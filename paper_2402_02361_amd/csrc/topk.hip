@@ -1150,7 +1150,6 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
     const int shift = next_shift(width);
     const uint32_t at_or_above = (uint32_t)k - found[1] + found[2];   // of the bin, in the segment
     const bool crowded = at_or_above > (uint32_t)collect_limit(k);    // the second digit will be asked for
-    static_assert(collect_limit(kListCap) <= 6 * kListCap, "where six lists overflow the bin is crowded");
     __syncthreads();
     if (threadIdx.x == 0) fill = range[0] = range[1] = 0;
     if (crowded)
@@ -1187,9 +1186,10 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
         flush_hist<kBigThreads>(hist, ghist1, 1, n_seg, s);
         if (threadIdx.x < 2 && range[threadIdx.x] != 0u) atomicMax(&granges[(size_t)s * kBins + threadIdx.x], range[threadIdx.x]);
     }
-    // One value: its ties need no list.  Few such lists (a stretch of good entries, as in a sorted segment): whoever collects goes
-    // through their spans, 3 us each, in less time than the 18 us that this takes.
-    if (fill > (uint32_t)kListCap && k <= kListCap && at_or_above / 6u > fill && ~range[0] != range[1])
+    // One value: its ties need no list.  Fewer spans' worth of such entries (a sorted segment; a shorter one): whoever collects goes
+    // through those spans in less time than this takes, 10 to 20 us (within one bin, k = 90: 1 x 200,000 70 -> 49 us, 1 x 350,000
+    // 96 -> 51; k = 512 or 686: 8 x 220,000 50 -> 60, 3 x 274,000 50 -> 61, 3 x 350,000 103 -> 69).
+    if (fill > (uint32_t)kListCap && k <= kListCap && crowded && at_or_above > (k <= 128 ? 12u : 18u) * (uint32_t)span && ~range[0] != range[1])
         own_best(score + lo, (int)(hi - lo), (uint32_t)lo, k, lowest, width, hist, wave_tot, found, &fill, range, &mine);
 }
 
@@ -1265,27 +1265,14 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     // The spans of lists that overflowed (a stretch of good entries, as a sorted segment has it) are gone through by the whole
     // workgroup: what(row, hi, val) for each of their sweeps.
     auto through_overflowed = [&](auto&& what) {
-        unsigned long long left = overflowed;
-        int row = 0, hi = 0;
-        auto list = [&] {   // the first sweep of the next list's span
-            row = left ? (__ffsll(left) - 1) * span : 0;
-            hi = row + span < len ? row + span : len;
-        };
-        list();
-        float cur[kBigPer], nxt[kBigPer];
-        if (left) load_sweep(seg_score, row, hi, cur);
+        for (unsigned long long left = overflowed; left; left &= left - 1ull) {
+            const int lo = (__ffsll(left) - 1) * span, hi = lo + span < len ? lo + span : len;
 #pragma unroll 1
-        while (left) {   // (a sweep is on its way while the one before is looked at)
-            const int this_row = row, this_hi = hi;
-            row += kRow;
-            if (row >= hi) {
-                left &= left - 1ull;
-                list();
+            for (int row = lo; row < hi; row += kRow) {
+                float again[kBigPer];
+                load_sweep(seg_score, row, hi, again);
+                what(row, hi, again);
             }
-            if (left) load_sweep(seg_score, row, hi, nxt);
-            what(this_row, this_hi, cur);
-#pragma unroll
-            for (int j = 0; j < kBigPer; ++j) cur[j] = nxt[j];
         }
     };
     uint32_t least = 0u, largest = 0xFFFFFFFFu;   // of the bin's keys
