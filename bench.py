@@ -29,8 +29,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 # HBM bytes per launch of the draft kernel from rocprofv3 counters (profiles/draft_kernel_cfg4_traffic.txt), valid for
 # the kernel source with this SHA-256 only; any other source reports null.
-MEASURED_TRAFFIC = {"workload": "cfg4_stress_gemm4096_dwconv_20M", "source_sha256": "d48335e7812681657145a240f8f88666dfa5fbe4f711968c0a69910aa4d157a3",
-                    "bytes": 590916468, "dominant_bytes": 404874628}
+MEASURED_TRAFFIC = {"workload": "cfg4_stress_gemm4096_dwconv_20M", "source_sha256": "699e75caccf56bcd85af3c90fd041cb02c6a345f2d689bf039d693e5902d8562",
+                    "bytes": 590905627, "dominant_bytes": 404877572}
 
 
 def draft_traffic(workload, which="bytes"):
