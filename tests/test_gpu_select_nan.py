@@ -36,10 +36,13 @@ def scores(kind, n, rng):
     elif kind == "last key":
         u[some[: n // 2]] = 0xFFFFFFFF
         u[some[n // 2:]] = 0x7FFFFFFF
+    elif kind == "a crowded bin":   # the rest of it within one bin, in which lists hold their span's best
+        x[:] = np.float32(1.0) + rng.integers(0, 1 << 16, n) * np.float32(2.0 ** -23)
+        u[some[:40]], u[some[40: n // 50]] = 0x7FC00000, 0xFFC00000
     return x
 
 
-@pytest.mark.parametrize("kind", ["one", "few of either sign", "many positive", "many negative", "payloads", "all one", "last key"])
+@pytest.mark.parametrize("kind", ["one", "few of either sign", "many positive", "many negative", "payloads", "all one", "last key", "a crowded bin"])
 @pytest.mark.parametrize("lens,ks", [([8000, 70], [1, 64]), ([4000, 300], [65, 300]), ([50001] * 3, [30, 512]), ([65536], [4096]), ([100001, 65537], [33, 4096]), ([500000], [512, 4096]),
                                      ([700001, 5000], [33, 4096]), ([3000001], [512])])
 def test_nan_by_its_bits(P, kind, lens, ks):

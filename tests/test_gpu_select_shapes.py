@@ -22,12 +22,26 @@ def of(kind, n, rng):
     if kind == "ties and neighbours":   # a third of the entries share a value, a few lie just above it
         r = rng.random(n)
         return np.where(r < 0.3, np.float32(2.0), np.where(r < 0.3005, np.float32(2.0) + (r * 0.01).astype(np.float32), values("normal", n, rng) * np.float32(0.3))).astype(np.float32)
+    if kind == "neighbours":            # one bin: mostly one value, a few just above it
+        return (np.float32(2.0) + (rng.random(n) < 0.0001) * rng.integers(1, 5, n) * np.float32(2.0 ** -22)).astype(np.float32)
     return values(kind, n, rng)
 
 
 @pytest.mark.parametrize("kind", ["ascending", "clump", "one bin", "300 values", "equal", "ties and neighbours", "two values"])
 @pytest.mark.parametrize("lens,ks", [([100001, 65537], [3, 512, 1100, 1280, 1281, 4096]), ([300001] * 3, [33, 2048]), ([524288], [512, 4096]), ([70000] * 130, [512])])
 def test_lists_that_overflow(P, kind, lens, ks):
+    rng = np.random.default_rng(len(kind) + len(lens))
+    seg = np.concatenate([[0], np.cumsum(lens)])
+    score = np.concatenate([of(kind, n, rng) for n in lens])
+    for k in ks:
+        check(P, score, seg, k)
+
+
+@pytest.mark.parametrize("kind", ["one bin", "neighbours", "two values", "300 values", "ascending"])
+@pytest.mark.parametrize("lens,ks", [([524288], [1, 40, 128, 129, 1279, 1280, 1281]), ([480001] * 18, [40]), ([300001, 200000, 524287, 196608, 196609, 294912, 294914], [2, 128, 900])])
+def test_lists_of_a_crowded_bin(P, kind, lens, ks):
+    """around 12 and 18 spans' worth of entries in the bin, spans of one sweep and of two, the k best of a span with and without
+    ties that fill it"""
     rng = np.random.default_rng(len(kind) + len(lens))
     seg = np.concatenate([[0], np.cumsum(lens)])
     score = np.concatenate([of(kind, n, rng) for n in lens])
