@@ -1043,7 +1043,7 @@ __device__ __forceinline__ void note_range(uint32_t not_least, uint32_t largest,
 // The list of a span that has more at or above the bin than it holds: the span's own k best, for whatever is among the segment's k
 // best is among these.  They are found as the segment's are, digit by digit in the bin; ties that are too many are taken in
 // index order.  (Scores within one bin, 480,000 in one segment, k = 76: the workgroups that collect took 120 us going through
-// the spans of all lists themselves, the call takes 49 now, 52 by the spans route.)  A function of its own: list_kernel
+// the spans of all lists themselves, the call takes 51 now, 52 by the spans route.)  A function of its own: list_kernel
 // as a rule does without it and keeps its registers.
 __device__ __attribute__((noinline)) void own_best(const float* __restrict__ span_score, int span_len, uint32_t first_index, int k, uint32_t lowest, uint32_t width,
                                                    uint32_t* hist, uint32_t* wave_tot, uint32_t* found, uint32_t* fill, uint32_t* range, List* mine_list)
