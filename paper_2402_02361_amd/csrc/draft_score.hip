@@ -1004,10 +1004,11 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
 
 constexpr int kAnyClass = -1;
 constexpr int kProducts = -2;   // plain and batched matrix products: the kernel branches between these two only
+constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers where the others need 128 at most
 
 // One launch scores the segments of one loop-nest class (CLS), so that each class gets the register budget, and with
 // it the occupancy, of its own symbol code; CLS = kAnyClass branches on the class at run time instead and serves
-// populations of several classes where one launch for everything beats several (see the launch plan), and all that are loaded
+// populations of several classes where one launch for everything beats several (see the launch plan), kAnyClass also all that are loaded
 // one by one (VEC = 1): fewer than four candidates, and small ones of several classes that are not laid out in fours.
 // HIST: the workgroup also counts the first selection digit (first_digit_of) of its scores
 // in LDS and merges the counts into one of `copies` global histograms of its segment.
@@ -1056,6 +1057,14 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
         if (d.cls == kGemm) PRUNER_WALK(NestGemm);
         else PRUNER_WALK(NestBatchedGemm);
     }
+    else if constexpr (CLS == kClosedForms) {
+        switch (d.cls) {
+            case kGemm: PRUNER_WALK(NestGemm); break;
+            case kBatchedGemm: PRUNER_WALK(NestBatchedGemm); break;
+            case kConv2d: PRUNER_WALK(NestConv2d); break;
+            default: PRUNER_WALK(NestDepthwiseConv2d); break;
+        }
+    }
     else {
         switch (d.cls) {
             case kGemm: PRUNER_WALK(NestGemm); break;
@@ -1085,7 +1094,7 @@ template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, b
     }
     if constexpr (!DUMP) {
         if constexpr (CLS != kAnyClass) {
-            if constexpr (CLS != kProducts) {
+            if constexpr (CLS >= kGeneric) {
                 if (mut) return draft_kernel<CLS, 4, false, EXACT, true, true>;
             }
         }
@@ -1102,6 +1111,7 @@ template <bool DUMP, bool EXACT> DraftFn pick_class(int cls, int vec, bool hist,
         case kDepthwiseConv2d: return pick_vec<kDepthwiseConv2d, DUMP, EXACT>(vec, hist, mut);
         case kGeneric: return pick_vec<kGeneric, DUMP, EXACT>(vec, hist, mut);
         case kProducts: return pick_vec<kProducts, DUMP, EXACT>(vec, hist, mut);
+        case kClosedForms: return pick_vec<kClosedForms, DUMP, EXACT>(vec, hist, mut);
         default: return pick_vec<kAnyClass, DUMP, EXACT>(vec, hist, mut);
     }
 }
@@ -1466,9 +1476,11 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // there is only one class (its own kernel needs half the registers of the one that branches
     // on the class and a fraction of its code: 4,096 GEMM candidates take 5.7 us in the one and 6.4 in the other,
     // 65,536 convolution candidates 7.7 and 9.6), and, when the kernels make their candidates, up to two classes
-    // (a launch of the mutation is then saved); otherwise a single launch of the kernel that branches on the class, or
-    // of the one that branches between the two kinds of matrix products where there are no others (an encoder's tasks:
-    // half the registers, twice the workgroups at once: 20 x 50,000 candidates take 13.3 us instead of 14.8).  A
+    // (a launch of the mutation is then saved); otherwise a single launch of a kernel that branches on the class: between the
+    // two kinds of matrix products where there are no others (an encoder's tasks: 20 x 50,000 candidates take 13.3 us
+    // instead of 14.8), between the four classes with closed forms where none is generic (128 registers, four wavefronts per
+    // SIMD, where the access tables of the generic class take 178 and leave two: ten segments of these four classes, 3.3 M
+    // candidates, take 38 us instead of 43), else among all five.  A
     // launch has at most as many workgroups as the device holds at once; they walk through the chunks of their segment.
     std::vector<int32_t> order(n_sg);
     for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
@@ -1491,7 +1503,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     std::vector<int64_t> chunks_of;
     for (int32_t i = 0; i < n_sg; ++i) {
         const int32_t s = order[i];
-        const int cls = by_class ? descs[desc_of[s]].cls : vec == 4 && classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : kAnyClass;
+        const int cls = by_class ? descs[desc_of[s]].cls : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : kClosedForms;
         if (out->launches.empty() || out->launches.back().cls != cls) {
             out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, fused)),
                                                       reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, false))});

@@ -1,0 +1,40 @@
+"""Populations of several loop-nest classes: one kernel branches over the four classes with closed forms, another over those and the
+generic one.  A candidate's score has the same bits from either as from the kernel of its class alone, and the selection behind it
+is that of the two calls."""
+import numpy as np
+import pytest
+
+import workloads as w
+from test_gpu_parity import P, dev  # noqa: F401  (P is a fixture)
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+HW = w.Device(T_p=3.3e12, T_m=4.1e11, m_l0=96, m_l1=20000, pu_l1=3, n_l1=24, pu_l2=7, n_l2=5)
+CLOSED = [w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), w.depthwise_conv2d(1, 512, 28, 28, 3, 3), w.batched_gemm(12, 128, 128, 64),
+          w.gemm(1024, 256, 256, dtype_bytes=2, rd_levels=3, frag=(16, 16, 16))]
+GENERIC = w.Subgraph("gemm_bt", 2, 1, (96, 80, 72), 4, 3, 4, (0, 0, 0), (w.Buffer((((0, 1),), ((2, 1),))), w.Buffer((((1, 1),), ((2, 1),)))),
+                     w.Buffer((((0, 1),), ((1, 1),))), HW)
+
+
+@pytest.mark.parametrize("lens", [[1024, 1025, 4, 2000, 1], [140000, 131073, 120001, 90003, 60002], [300001, 290000, 280004, 270008, 300003]])
+@pytest.mark.parametrize("generic", [False, True])
+def test_a_class_among_others_scores_as_alone(P, lens, generic):
+    sgs = CLOSED + ([GENERIC] if generic else [])
+    lens = lens + ([777] if generic else [])
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n, rows = int(seg[-1]), max(w.n_slots(s) for s in sgs)
+    tiles = np.ones((rows, n), np.uint16)
+    for t, sg in enumerate(sgs):
+        tl, _ = w.sample_population(sg, lens[t], seed=12, stream=t)
+        tiles[: tl.shape[0], seg[t]:seg[t + 1]] = tl
+    device_tiles = dev(tiles)
+    for flags in (P.REFERENCE_ROUNDING, P.FUSED_ARITHMETIC, P.FUSED_ARITHMETIC | P.NO_COMPUTE_PENALTY):
+        together = P.draft_score(sgs, seg, device_tiles, flags=flags)
+        k = min(lens)
+        score, idx, val = P.prior_filter(sgs, seg, device_tiles, k, flags=flags)
+        want, want_val = P.topk(together, seg, k)
+        assert torch.equal(score.view(torch.int32), together.view(torch.int32)) and torch.equal(idx, want) and torch.equal(val, want_val)
+        for t, sg in enumerate(sgs):
+            alone = P.draft_score([sg], [0, lens[t]], device_tiles[:, int(seg[t]):int(seg[t + 1])].contiguous(), flags=flags)
+            assert torch.equal(alone.view(torch.int32), together[int(seg[t]):int(seg[t + 1])].view(torch.int32))
