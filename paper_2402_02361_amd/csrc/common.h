@@ -114,8 +114,8 @@ int draft_check(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off,
                 const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes);
 struct MutArgs;   // lse_child.h
 
-// The draft launches of a call: planned once (everything pruner_draft_score refuses is refused here), their tables uploaded
-// to the workspace's begin, then run, as often as the population's shape stays the same.
+// The draft launches of a call: planned once (everything pruner_draft_score refuses is refused here), their tables, where they are
+// too large for the launches to bring along, uploaded to the workspace's begin, then run, as often as the population's shape stays the same.
 struct DraftPlan {
     struct Launch {
         int cls;
@@ -126,6 +126,7 @@ struct DraftPlan {
     std::vector<Launch> launches;
     std::vector<char> image;   // the tables
     size_t descs_at = 0;
+    bool in_launch = false;    // they travel with the launches themselves and are not uploaded (draft_upload decides)
     int64_t n = 0, tiles_pitch = 0;
     int32_t n_sg = 0, flags = 0;
     bool counts = false;   // the kernels add every score's first selection digit to a histogram (no symbol dump)
@@ -138,7 +139,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
 // (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables
 // and behind which nothing else lies that must stay.  An upload that begins right behind the tables (place_behind) shares
 // their launch.
-int draft_upload(const DraftPlan& plan, void* workspace, hipStream_t stream, const Upload* also);
+int draft_upload(DraftPlan& plan, void* workspace, hipStream_t stream, const Upload* also);
 // Moves the pending table to the first free place behind the plan's tables in the same workspace (it was prepared for a later
 // one, so it fits); returns where it will lie.
 void* place_behind(const DraftPlan& plan, void* workspace, Upload* also);

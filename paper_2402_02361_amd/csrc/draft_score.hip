@@ -1002,6 +1002,11 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
     }
 }
 
+// Tables of up to this size travel as an argument of the launch, which carries 4 KB (twenty segments of eight different subgraphs).
+struct DraftTables {
+    uint4 q[3840 / 16];
+};
+
 constexpr int kAnyClass = -1;
 constexpr int kProducts = -2;   // plain and batched matrix products: the kernel branches between these two only
 constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers where the others need 128 at most
@@ -1013,17 +1018,23 @@ constexpr int kClosedForms = -3;   // any class but the generic one, whose acces
 // HIST: the workgroup also counts the first selection digit (first_digit_of) of its scores
 // in LDS and merges the counts into one of `copies` global histograms of its segment.
 // MUT: the candidates are not read but made (SchMutation from S_spec, `mut`), stored and scored in one pass.
+// The tables of segments and subgraphs come as the launch's first argument, so that no launch has to bring them before; tables that
+// do not fit there lie in the workspace (`tables`).
 template <int CLS, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
-__global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict__ segs, int32_t n_seg,
-                                                       const SgDesc* __restrict__ descs, const uint16_t* __restrict__ tiles,
-                                                       int64_t pitch, int32_t flags, float* __restrict__ score,
+__global__ void __launch_bounds__(kBlock) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
+                                                       int32_t descs_at, const uint16_t* __restrict__ tiles, int64_t pitch, int32_t flags, float* __restrict__ score,
                                                        int64_t* __restrict__ symbols, int64_t n_total,
                                                        uint32_t* __restrict__ first_digit, uint32_t* __restrict__ block_max, int copies,
                                                        int n_sg_all, MutArgs mut)
 {
     const int32_t b = blockIdx.x;
+    // (both places as constant memory, which no store of this kernel reaches: entries that a whole wavefront asks for come through
+    // the scalar cache)
+    typedef const __attribute__((address_space(4))) char* ConstantMemory;
+    const ConstantMemory table = tables ? (ConstantMemory)(uintptr_t)tables : (ConstantMemory)__builtin_amdgcn_kernarg_segment_ptr();
+    const SegEnt* const segs = reinterpret_cast<const SegEnt*>((const char*)table) + first_seg;
     const SegEnt seg = segs[segment_of_block(segs, n_seg, b)];
-    const SgDesc& d = descs[seg.desc];
+    const SgDesc& d = reinterpret_cast<const SgDesc*>((const char*)(table + descs_at))[seg.desc];
 
     // P_l2,m = S7 / (ceil(S7 / n_l2) * n_l2) depends on the run length alone: when a block scores enough candidates,
     // the quotients for all possible run lengths (their inverses for the fused evaluation) are formed once and the
@@ -1081,7 +1092,7 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(const SegEnt* __restrict_
     }
 }
 
-using DraftFn = void (*)(const SegEnt*, int32_t, const SgDesc*, const uint16_t*, int64_t, int32_t, float*, int64_t*, int64_t, uint32_t*, uint32_t*, int, int, MutArgs);
+using DraftFn = void (*)(DraftTables, const void*, int32_t, int32_t, int32_t, const uint16_t*, int64_t, int32_t, float*, int64_t*, int64_t, uint32_t*, uint32_t*, int, int, MutArgs);
 
 // The digit-counting variants come without the symbol dump.
 template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, bool mut)
@@ -1128,7 +1139,7 @@ DraftFn pick_kernel(int cls, int vec, bool dump, bool exact, bool hist, bool mut
 int64_t resident_blocks(DraftFn fn)
 {
     struct Known { DraftFn fn; int dev; int64_t blocks; };
-    static Known known[64];
+    static Known known[128];
     static int n_known = 0;
     int cus = 0;
     const int dev = current_device(&cus);
@@ -1143,7 +1154,7 @@ int64_t resident_blocks(DraftFn fn)
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlock, 0) != hipSuccess || per_cu < 1) per_cu = 1;
     (void)hipGetLastError();
     const int64_t blocks = (int64_t)per_cu * cus;
-    if (have < 64) {
+    if (have < 128) {
         known[have] = Known{fn, dev, blocks};
         n_known = have + 1;
     }
@@ -1550,11 +1561,16 @@ void* place_behind(const DraftPlan& plan, void* workspace, Upload* also)
     return also->dst;
 }
 
-int draft_upload(const DraftPlan& plan, void* workspace, hipStream_t st, const Upload* also)
+int draft_upload(DraftPlan& plan, void* workspace, hipStream_t st, const Upload* also)
 {
     char* ws = static_cast<char*>(workspace);
-    if (plan.n == 0) return also && also->dst ? put_table(also->dst, also->bytes.data(), also->bytes.size(), st, also->zero, also->zero_bytes) : PRUNER_OK;
-    if (!also || !also->dst) return put_table(ws, plan.image.data(), plan.image.size(), st);
+    const bool pending = also && also->dst;
+    if (plan.n == 0) return pending ? put_table(also->dst, also->bytes.data(), also->bytes.size(), st, also->zero, also->zero_bytes) : PRUNER_OK;
+    // (where something else is uploaded anyway the tables go with it: from the workspace, through the caches, a launch has
+    // them 0.3 us sooner than from its arguments)
+    plan.in_launch = !pending && plan.image.size() <= sizeof(DraftTables);
+    if (plan.in_launch) return PRUNER_OK;
+    if (!pending) return put_table(ws, plan.image.data(), plan.image.size(), st);
     // the other table rides along in the same launch if it starts shortly behind this call's tables (with many
     // subgraphs that share descriptors the reserved room is much larger than the tables: then it travels by itself)
     const ptrdiff_t at = static_cast<const char*>(also->dst) - ws;
@@ -1573,8 +1589,8 @@ int draft_upload(const DraftPlan& plan, void* workspace, hipStream_t st, const U
 int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tiles, float* score, int64_t* symbols, hipStream_t st,
               uint32_t* first_digit, uint32_t* block_max, int copies, const MutArgs* mut)
 {
-    const SegEnt* d_segs = static_cast<const SegEnt*>(workspace);
-    const SgDesc* d_descs = reinterpret_cast<const SgDesc*>(static_cast<const char*>(workspace) + plan.descs_at);
+    DraftTables tables = {};
+    if (plan.in_launch) memcpy(&tables, plan.image.data(), plan.image.size());
     // measurement hook: events around the launch that covers the most candidates
     const DraftPlan::Launch* timed = nullptr;
     if (g_time_start && g_time_stop) {
@@ -1587,7 +1603,7 @@ int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tile
         if (L.blocks == 0) continue;
         if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_start), st) != hipSuccess) return PRUNER_EHIP;
         const DraftFn fn = reinterpret_cast<DraftFn>(const_cast<void*>(mut ? L.fn : L.fn_read));
-        hipLaunchKernelGGL(fn, dim3((unsigned)L.blocks), dim3(kBlock), 0, st, d_segs + L.first_seg, L.n_seg, d_descs, tiles, plan.tiles_pitch,
+        hipLaunchKernelGGL(fn, dim3((unsigned)L.blocks), dim3(kBlock), 0, st, tables, plan.in_launch ? nullptr : workspace, L.first_seg, L.n_seg, (int32_t)plan.descs_at, tiles, plan.tiles_pitch,
                            plan.flags, score, symbols, plan.n, first_digit, block_max, copies, plan.n_sg, mut ? *mut : MutArgs{});
         if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_stop), st) != hipSuccess) return PRUNER_EHIP;
         PRUNER_LAUNCH_CHECK();

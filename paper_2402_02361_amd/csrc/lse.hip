@@ -913,7 +913,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, false, &plan_first);
         if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, true, &plan_later);
         if (rc) return rc;
-        const DraftPlan& plan = t == 0 ? plan_first : plan_later;
+        DraftPlan& plan = t == 0 ? plan_first : plan_later;
         const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, nullptr};
         if (t > 0 && !plan.makes) {
             mutate(t - 1, before.count, before.aos);

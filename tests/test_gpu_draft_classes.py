@@ -31,10 +31,24 @@ def test_a_class_among_others_scores_as_alone(P, lens, generic):
     device_tiles = dev(tiles)
     for flags in (P.REFERENCE_ROUNDING, P.FUSED_ARITHMETIC, P.FUSED_ARITHMETIC | P.NO_COMPUTE_PENALTY):
         together = P.draft_score(sgs, seg, device_tiles, flags=flags)
-        k = min(lens)
+        k = min(*lens, 4096)
         score, idx, val = P.prior_filter(sgs, seg, device_tiles, k, flags=flags)
         want, want_val = P.topk(together, seg, k)
         assert torch.equal(score.view(torch.int32), together.view(torch.int32)) and torch.equal(idx, want) and torch.equal(val, want_val)
         for t, sg in enumerate(sgs):
             alone = P.draft_score([sg], [0, lens[t]], device_tiles[:, int(seg[t]):int(seg[t + 1])].contiguous(), flags=flags)
             assert torch.equal(alone.view(torch.int32), together[int(seg[t]):int(seg[t + 1])].view(torch.int32))
+
+
+@pytest.mark.parametrize("n_sg", [1, 7, 8, 9, 10, 40])
+def test_tables_that_fit_a_launch_and_tables_that_do_not(P, n_sg):
+    """different subgraphs, so that every one has a table entry of its own: those of a few travel with the launch itself"""
+    sgs = [w.gemm(64 + 32 * t, 128, 256) for t in range(n_sg)]
+    seg = np.concatenate([[0], np.cumsum([300 + t for t in range(n_sg)])]).astype(np.int64)
+    tiles = P.random_init(sgs, seg, max(w.n_slots(s) for s in sgs), 5)
+    score = P.draft_score(sgs, seg, tiles)
+    filtered, idx, _ = P.prior_filter(sgs, seg, tiles, 70)
+    assert torch.equal(filtered.view(torch.int32), score.view(torch.int32)) and torch.equal(idx, P.topk(score, seg, 70)[0])
+    for t, sg in enumerate(sgs):
+        alone = P.draft_score([sg], [0, int(seg[t + 1] - seg[t])], tiles[:, int(seg[t]):int(seg[t + 1])].contiguous())
+        assert torch.equal(alone.view(torch.int32), score[int(seg[t]):int(seg[t + 1])].view(torch.int32))
