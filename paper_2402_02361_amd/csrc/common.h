@@ -32,18 +32,18 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v)
 
 // Inclusive running maximum over the active lanes of a wavefront, by the same moves: the last active lane ends up
 // with the maximum of all active lanes when these are lanes 0..m (a lane without a source, or whose source is switched
-// off, keeps its own value).
-__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v)
+// off, keeps its own value).  In two parts: inside each row of 16 lanes, then across the rows.
+template <int CTRL, int ROWS> __device__ __forceinline__ uint32_t max_with(uint32_t v)
 {
-    auto step = [](uint32_t x, uint32_t y) { return x > y ? x : y; };
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x111, 0xf, 0xf, false));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x112, 0xf, 0xf, false));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x114, 0xf, 0xf, false));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x118, 0xf, 0xf, false));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x142, 0xa, 0xf, false));
-    v = step(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x143, 0xc, 0xf, false));
-    return v;
+    const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xf, false);
+    return v > y ? v : y;
 }
+__device__ __forceinline__ uint32_t row_inclusive_max(uint32_t v)
+{
+    return max_with<0x118, 0xf>(max_with<0x114, 0xf>(max_with<0x112, 0xf>(max_with<0x111, 0xf>(v))));
+}
+__device__ __forceinline__ uint32_t rows_inclusive_max(uint32_t v) { return max_with<0x143, 0xc>(max_with<0x142, 0xa>(v)); }
+__device__ __forceinline__ uint32_t wave_inclusive_max(uint32_t v) { return rows_inclusive_max(row_inclusive_max(v)); }
 
 // After a launch: PRUNER_EHIP if the runtime reports an error.  hipGetLastError returns (and clears) the last error
 // of the calling thread, so an error left by an earlier, unrelated runtime call is reported here as well; launches that
@@ -87,26 +87,32 @@ struct Upload {
 // Selection in two steps, so that a caller inside the library can produce the first-digit histograms itself
 // between them (the draft kernel does, while the scores are still in registers).
 struct TopkCtx {
-    bool large;            // the route counts first digits (not the tiny one)
-    bool pick;             // ... and takes one launch behind that
-    bool lists;            // ... or two
-    bool count;            // ... or that one launch alone (pick)
+    bool digits;           // the route counts first digits (lists and spans)
+    bool tiny, pick, levels, lists;   // the route; none of them: spans
     int32_t n_sg, k;
-    int64_t n, span;
+    int64_t n, longest, span;
     int32_t blocks;        // workgroups of a sweep launch
     int copies;            // copies of the first digit's histogram
     void *d_segs, *d_state, *d_stage;
     uint32_t* d_hist;      // [copies][n_sg][2048] first digit, then one copy each for the second and third
-    uint32_t* d_block_max; // largest key of every 256 neighbouring entries (block_max_slot), or null: the workspace holds none
-    char inline_segs[4096];  // tiny route: the segment table when it travels as a kernel argument
+    uint32_t* d_max256;    // largest key of every 256 neighbouring entries (block_max_slot), or null: the route does without
+    uint32_t *d_max64, *d_max16;   // ... of every 64 (block64_slot) and 16 (block16_slot), or null
+    char inline_segs[4096];  // tiny, pick and levels: the segment table when it travels as a kernel argument
     bool inline_ok;
 };
+// What the selection would have whoever holds the scores in registers leave behind (null pointers: nothing of the kind).
+struct ScoreNotes {
+    uint32_t* first_digit = nullptr;   // every score's first digit added to one of `copies` histograms
+    int copies = 1;
+    uint32_t *max256 = nullptr, *max64 = nullptr, *max16 = nullptr;   // (with the first digits: the former alone; else the latter and the others as well)
+};
+inline ScoreNotes notes_for(const TopkCtx& ctx) { return ScoreNotes{ctx.digits ? ctx.d_hist : nullptr, ctx.copies, ctx.d_max256, ctx.d_max64, ctx.d_max16}; }
 // validates, uploads the segment table, clears the histograms (of the routes that count digits)
 // (defer: do not launch the upload, describe it there instead; copies: the scores are expected to hold ties by the thousand)
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t stream, TopkCtx* ctx,
                  Upload* defer, bool with_block_max, bool copies);
-// the remaining launches; have_first_digit: d_hist already holds the first digit's counts of every segment
-int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, int32_t* idx_out, float* val_out, bool have_first_digit,
+// the remaining launches; noted: what notes_for(ctx) asks for is in place
+int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, int32_t* idx_out, float* val_out, bool noted,
                 hipStream_t stream);
 
 // Everything pruner_draft_score refuses, without enqueuing anything.
@@ -129,13 +135,12 @@ struct DraftPlan {
     bool in_launch = false;    // they travel with the launches themselves and are not uploaded (draft_upload decides)
     int64_t n = 0, tiles_pitch = 0;
     int32_t n_sg = 0, flags = 0;
-    bool counts = false;   // the kernels add every score's first selection digit to a histogram (no symbol dump)
     bool makes = false;    // the kernels can make their candidates (the explorer loop's mutation) instead of reading them
 };
-// count_digits: the caller has histograms to add to (plan->counts says whether the launch shape allows it); mut: the kernels
+// notes: what the selection would have the kernels leave behind; mut: the kernels
 // are to make their candidates from the second run on (plan->makes says whether they can).
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
-               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool block_maxima, bool mut, DraftPlan* plan);
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, const ScoreNotes& notes, bool mut, DraftPlan* plan);
 // (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables
 // and behind which nothing else lies that must stay.  An upload that begins right behind the tables (place_behind) shares
 // their launch.
@@ -143,12 +148,10 @@ int draft_upload(DraftPlan& plan, void* workspace, hipStream_t stream, const Upl
 // Moves the pending table to the first free place behind the plan's tables in the same workspace (it was prepared for a later
 // one, so it fits); returns where it will lie.
 void* place_behind(const DraftPlan& plan, void* workspace, Upload* also);
-// Draft scores.  With plan.counts, every score's first selection digit is added to first_digit ([copies][n_sg][2048], cleared
-// by the caller), when that is not null, and the largest key of every 256 neighbouring candidates of a segment goes to
-// block_max (block_max_slot), when that is not null either.  mut (needs plan.makes): the kernels make the children of
+// Draft scores, and what `notes` asks for (as the plan was made for).  mut (needs plan.makes): the kernels make the children of
 // S_spec, store them over `tiles` (which is then written) and score them in one pass.
 int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tiles, float* score, int64_t* symbols, hipStream_t stream,
-              uint32_t* first_digit, uint32_t* block_max, int copies, const MutArgs* mut);
+              const ScoreNotes& notes, const MutArgs* mut);
 // workspace needs of the entry points (each defined next to its kernels)
 size_t draft_workspace_bytes(int32_t n_sg);
 size_t topk_workspace_bytes(int64_t n, int32_t n_sg, int32_t k);

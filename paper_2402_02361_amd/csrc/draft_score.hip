@@ -776,11 +776,11 @@ __device__ __forceinline__ void analyze_fused(const SgDesc& d, const Symbols (&y
 
 // raw holds candidates c0 .. c0 + VEC - 1; those in [c_lo, c_end) are scored (c_lo is c0 but for the thread that would read past
 // the end of the population: it reads its last VEC and leaves the first of them to its neighbour).
-template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST>
+template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
 __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles<Nest, VEC>& raw, int64_t c0, int64_t c_lo, int64_t c_end,
                                                  int32_t flags, const float* p2m_tab, float* __restrict__ score,
                                                  int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist, bool count_digits,
-                                                 uint32_t* __restrict__ block_max, int seg_index)
+                                                 uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, int seg_index)
 {
     constexpr int NSP = Nest::NSP, NRD = Nest::NRD;
     uint32_t sp[NSP][4][VEC];   // grid, virtual thread, thread, inner
@@ -939,6 +939,21 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
         }
     }
 
+    if constexpr (!DUMP && (!HIST || MUT)) {
+        if (max16) {
+            // The largest keys of neighbouring candidates, by which the selection finds those that can matter.  The lanes at work are lanes
+            // 0..m (as above).  Without the special case of -0, which is put right once.
+            uint32_t top = 0;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                const uint32_t u = __float_as_uint(out[v]), key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+                top = c0 + v >= c_lo && c0 + v < c_end && key > top ? key : top;
+            }
+            top = top == ~0x80000000u ? 0x80000000u : top;
+            note_maxima<VEC>(top, c_lo, 63 - __clzll(__ballot(true)), c_end, seg_index, max16, max64, block_max);
+        }
+    }
+
     if (VEC == 4 && c0 >= c_lo && c0 + VEC <= c_end) {
         *reinterpret_cast<f32x4_a4*>(score + c0) = f32x4{out[0], out[1 % VEC], out[2 % VEC], out[3 % VEC]};
     } else {
@@ -955,7 +970,7 @@ template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
 __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg, int32_t b, const uint16_t* __restrict__ tiles,
                                              int64_t pitch, int32_t flags, const float* p2m_tab, float* __restrict__ score,
                                              int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist, bool count_digits,
-                                             uint32_t* __restrict__ block_max, const MutArgs& mut)
+                                             uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, const MutArgs& mut)
 {
     const int64_t step = (int64_t)seg.blocks * kBlock * VEC;
     RawTiles<Nest, VEC> cur{}, nxt{};
@@ -973,7 +988,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
             for (int it = 0; it < seg.iters; ++it) {
                 if (c0 < seg.end) {
                     make_children<Nest>(d, ms, mut, out, pitch, c0, seg.end, cur);
-                    score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, c0, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
+                    score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, c0, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
                 }
                 c0 += step;
             }
@@ -986,7 +1001,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
         for (int it = 0; it < seg.iters; ++it) {
             if (c0 < seg.end) {
                 load_tiles<Nest, VEC>(d, tiles, pitch, inside(c0), cur);
-                score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, inside(c0), c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
+                score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, inside(c0), c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
             }
             c0 += step;
         }
@@ -996,7 +1011,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
     for (int it = 0; it < seg.iters; ++it) {
         const int64_t c1 = c0 + step;
         if (it + 1 < seg.iters && c1 < seg.end) load_tiles<Nest, VEC>(d, tiles, pitch, inside(c1), nxt);
-        if (c0 < seg.end) score_candidates<Nest, VEC, DUMP, EXACT, HIST>(d, cur, inside(c0), c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, seg.seg);
+        if (c0 < seg.end) score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, inside(c0), c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
         cur = nxt;
         c0 = c1;
     }
@@ -1024,7 +1039,7 @@ template <int CLS, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
 __global__ void __launch_bounds__(kBlock) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
                                                        int32_t descs_at, const uint16_t* __restrict__ tiles, int64_t pitch, int32_t flags, float* __restrict__ score,
                                                        int64_t* __restrict__ symbols, int64_t n_total,
-                                                       uint32_t* __restrict__ first_digit, uint32_t* __restrict__ block_max, int copies,
+                                                       uint32_t* __restrict__ first_digit, uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, int copies,
                                                        int n_sg_all, MutArgs mut)
 {
     const int32_t b = blockIdx.x;
@@ -1058,7 +1073,7 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(DraftTables /* read throu
     }
     const float* p2m_tab = seg.use_tab ? tab : nullptr;
 
-#define PRUNER_WALK(NEST) walk_segment<NEST, VEC, DUMP, EXACT, HIST, MUT>(d, seg, b, tiles, pitch, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, mut)
+#define PRUNER_WALK(NEST) walk_segment<NEST, VEC, DUMP, EXACT, HIST, MUT>(d, seg, b, tiles, pitch, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, mut)
     if constexpr (CLS == kGemm) PRUNER_WALK(NestGemm);
     else if constexpr (CLS == kBatchedGemm) PRUNER_WALK(NestBatchedGemm);
     else if constexpr (CLS == kConv2d) PRUNER_WALK(NestConv2d);
@@ -1092,7 +1107,7 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(DraftTables /* read throu
     }
 }
 
-using DraftFn = void (*)(DraftTables, const void*, int32_t, int32_t, int32_t, const uint16_t*, int64_t, int32_t, float*, int64_t*, int64_t, uint32_t*, uint32_t*, int, int, MutArgs);
+using DraftFn = void (*)(DraftTables, const void*, int32_t, int32_t, int32_t, const uint16_t*, int64_t, int32_t, float*, int64_t*, int64_t, uint32_t*, uint32_t*, uint32_t*, uint32_t*, int, int, MutArgs);
 
 // The digit-counting variants come without the symbol dump.
 template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, bool mut)
@@ -1431,7 +1446,7 @@ void* g_time_stop = nullptr;
 int64_t* g_time_bytes = nullptr;
 
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
-               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, bool count_digits, bool block_maxima, bool mut, DraftPlan* out)
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, const ScoreNotes& notes, bool mut, DraftPlan* out)
 {
     if (!sg || !seg_off || n_sg < 1 || n_sg > PRUNER_MAX_SUBGRAPHS) return PRUNER_EINVAL;
     if (flags & ~(PRUNER_NO_COMPUTE_PENALTY | PRUNER_NO_MEMORY_PENALTY | PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) return PRUNER_EINVAL;
@@ -1466,10 +1481,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     out->n_sg = n_sg;
     out->flags = flags;
     out->tiles_pitch = tiles_pitch;
-    if (n == 0) {
-        out->counts = count_digits;   // nothing to count
-        return PRUNER_OK;
-    }
+    if (n == 0) return PRUNER_OK;
 
     bool in_fours = tiles_pitch % 4 == 0 && aligned(tiles, 8) && aligned(score, 16);   // every thread's candidates start at a multiple of four
     for (int32_t s = 0; s < n_sg; ++s) in_fours = in_fours && seg_off[s] % 4 == 0;
@@ -1478,8 +1490,8 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     const int n_classes = __builtin_popcount(classes);
     // Several classes in a population that is neither large nor laid out in fours: candidates one by one, four times the threads,
     // for the kernel that branches on the class is short of them (6 x 3,001, k = 6: 20.2 -> 17.6 us; 400,020: 23.0 -> 20.7;
-    // 900,020: no difference).  (Block maxima need fours, and so do kernels that make their candidates.)
-    const int vec = mut || block_maxima || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
+    // 900,020: no difference).  (Maxima of 256 neighbours need fours, and so do kernels that make their candidates.)
+    const int vec = mut || notes.max256 || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
 
     // Launch plan.  With four candidates per thread: one launch per loop-nest class present, the table grouped by class, when the
     // population is large (with more than two classes: 2^20 candidates for each, since every launch begins and ends with a
@@ -1508,7 +1520,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // out in fours (as the boundary promises; how many launches there are plays no part), the multiplied-out form for the
     // other large populations, unless a flag asks for one of them.
     const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !(large && in_fours));
-    const bool hist = count_digits && symbols == nullptr;
+    const bool hist = notes.first_digit && symbols == nullptr;
     const bool fused = mut && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
     std::vector<int64_t> chunks_of;
@@ -1549,7 +1561,6 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     out->image.assign(out->descs_at + descs.size() * sizeof(SgDesc), 0);
     memcpy(out->image.data(), segs.data(), segs.size() * sizeof(SegEnt));
     memcpy(out->image.data() + out->descs_at, descs.data(), descs.size() * sizeof(SgDesc));
-    out->counts = hist;
     out->makes = fused;
     return PRUNER_OK;
 }
@@ -1587,7 +1598,7 @@ int draft_upload(DraftPlan& plan, void* workspace, hipStream_t st, const Upload*
 }
 
 int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tiles, float* score, int64_t* symbols, hipStream_t st,
-              uint32_t* first_digit, uint32_t* block_max, int copies, const MutArgs* mut)
+              const ScoreNotes& notes, const MutArgs* mut)
 {
     DraftTables tables = {};
     if (plan.in_launch) memcpy(&tables, plan.image.data(), plan.image.size());
@@ -1598,13 +1609,12 @@ int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tile
             if (L.blocks > 0 && (!timed || L.candidates > timed->candidates)) timed = &L;
         if (g_time_bytes) *g_time_bytes = timed ? timed->bytes : 0;
     }
-    if (!plan.counts) first_digit = block_max = nullptr;
     for (const DraftPlan::Launch& L : plan.launches) {
         if (L.blocks == 0) continue;
         if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_start), st) != hipSuccess) return PRUNER_EHIP;
         const DraftFn fn = reinterpret_cast<DraftFn>(const_cast<void*>(mut ? L.fn : L.fn_read));
         hipLaunchKernelGGL(fn, dim3((unsigned)L.blocks), dim3(kBlock), 0, st, tables, plan.in_launch ? nullptr : workspace, L.first_seg, L.n_seg, (int32_t)plan.descs_at, tiles, plan.tiles_pitch,
-                           plan.flags, score, symbols, plan.n, first_digit, block_max, copies, plan.n_sg, mut ? *mut : MutArgs{});
+                           plan.flags, score, symbols, plan.n, notes.first_digit, notes.max256, notes.max64, notes.max16, notes.copies, plan.n_sg, mut ? *mut : MutArgs{});
         if (&L == timed && hipEventRecord(static_cast<hipEvent_t>(g_time_stop), st) != hipSuccess) return PRUNER_EHIP;
         PRUNER_LAUNCH_CHECK();
     }
@@ -1621,11 +1631,11 @@ extern "C" int pruner_draft_score(const pruner_subgraph* sg, int32_t n_sg, const
 {
     hipStream_t st = static_cast<hipStream_t>(stream);
     DraftPlan plan;
-    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes, false, false, false, &plan);
+    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes, ScoreNotes{}, false, &plan);
     if (rc) return rc;
     rc = draft_upload(plan, workspace, st, nullptr);
     if (rc) return rc;
-    return draft_run(plan, workspace, tiles, score, symbols, st, nullptr, nullptr, 0, nullptr);
+    return draft_run(plan, workspace, tiles, score, symbols, st, ScoreNotes{}, nullptr);
 }
 
 extern "C" int pruner_time_dominant_draft_launch(void* start_event, void* stop_event, int64_t* algorithmic_bytes)

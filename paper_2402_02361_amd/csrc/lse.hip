@@ -852,7 +852,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     for (int32_t s = 0; s < n_sg; ++s) longest = seg_off[s + 1] - seg_off[s] > longest ? seg_off[s + 1] - seg_off[s] : longest;
     if (longest <= kShortMax && k <= kShortK) {
         DraftPlan plan;
-        rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, false, false, n_steps > 1, &plan);
+        rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ScoreNotes{}, n_steps > 1, &plan);
         if (rc) return rc;
         // all tables in one launch: this route has no selection workspace, the segment table stands in its place
         d_table = reinterpret_cast<LseSeg*>(ws + L.filter + draft_bytes);
@@ -870,7 +870,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
                 mutate(t - 1, before.count, before.aos);
                 PRUNER_LAUNCH_CHECK();
             }
-            rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, nullptr, nullptr, 1, made ? &owed : nullptr);
+            rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, ScoreNotes{}, made ? &owed : nullptr);
             if (rc) return rc;
             const bool last = t + 1 == n_steps;
             uint16_t* const to_tiles = last ? spec_tiles : nullptr;
@@ -910,8 +910,8 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         Upload pending;
         rc = topk_prepare(seg_off, n_sg, k, ws + L.filter + draft_bytes, filter_bytes - draft_bytes, st, &ctx, &pending, true, true);
         if (rc) return rc;
-        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, false, &plan_first);
-        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, true, &plan_later);
+        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), false, &plan_first);
+        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), true, &plan_later);
         if (rc) return rc;
         DraftPlan& plan = t == 0 ? plan_first : plan_later;
         const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, nullptr};
@@ -922,10 +922,10 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         if (pending.dst) ctx.d_segs = place_behind(plan, draft_ws, &pending);
         rc = draft_upload(plan, draft_ws, st, &pending);
         if (rc) return rc;
-        rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, ctx.large ? ctx.d_hist : nullptr, ctx.large ? ctx.d_block_max : nullptr, ctx.copies,
+        rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, notes_for(ctx),
                        t > 0 && plan.makes ? &owed : nullptr);
         if (rc) return rc;
-        rc = topk_finish(ctx, score, seg_off, best_idx, best_val, ctx.large && plan.counts, st);
+        rc = topk_finish(ctx, score, seg_off, best_idx, best_val, true, st);
         if (rc) return rc;
         // PriorFilter over the union
         uint64_t *fresh = words(L.fresh), *merged = words(L.merged);

@@ -1,8 +1,8 @@
 // PriorFilter of Alg. 2 as one call: C_SA over the whole population, then the k best per subgraph.
 //
-// The same kernels as pruner_draft_score followed by pruner_topk, with one saving: where the selection counts digits
-// (segments above 8,192 entries, or k above 64), the draft kernel counts the first digit of every score while it still holds
-// the score in a register, and the selection skips its first pass over the score array.  The result is the same as that of the two separate calls, bit for bit.
+// The same kernels as pruner_draft_score followed by pruner_topk, with one saving: where the selection begins with a pass over the
+// scores (segments above 65,536 entries: the largest of every 64, or first digits counted), the draft kernel does its work while it
+// still holds the scores in registers.  The result is the same as that of the two separate calls, bit for bit.
 #include "common.h"
 #include "select_common.h"
 
@@ -34,19 +34,19 @@ extern "C" int pruner_prior_filter(const pruner_subgraph* sg, int32_t n_sg, cons
     if (!idx_out || !aligned(idx_out, 4) || (val_out && !aligned(val_out, 4))) return PRUNER_EINVAL;
 
     // The selection's tables are prepared first and travel with the draft tables in one launch, which also clears the
-    // histograms the draft kernel adds to.
+    // histograms the draft kernel may add to (few segments: both travel with the launches that read them).
     TopkCtx ctx;
     Upload pending;
     int rc = topk_prepare(seg_off, n_sg, k, ws + draft_bytes, workspace_bytes - draft_bytes, st, &ctx, &pending, true, false);
     if (rc) return rc;
     DraftPlan plan;
-    rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, ctx.large, ctx.d_block_max != nullptr, false, &plan);
+    rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, notes_for(ctx), false, &plan);
     if (rc) return rc;
     if (pending.dst) ctx.d_segs = place_behind(plan, ws, &pending);
     rc = draft_upload(plan, ws, st, &pending);
     if (rc) return rc;
-    rc = draft_run(plan, ws, tiles, score, nullptr, st, ctx.large ? ctx.d_hist : nullptr, ctx.large ? ctx.d_block_max : nullptr, ctx.copies, nullptr);
+    rc = draft_run(plan, ws, tiles, score, nullptr, st, notes_for(ctx), nullptr);
     if (rc) return rc;
     if (scored_event && hipEventRecord(static_cast<hipEvent_t>(scored_event), st) != hipSuccess) return PRUNER_EHIP;
-    return topk_finish(ctx, score, seg_off, idx_out, val_out, ctx.large && plan.counts, st);
+    return topk_finish(ctx, score, seg_off, idx_out, val_out, true, st);
 }

@@ -187,10 +187,38 @@ __device__ __forceinline__ void flush_hist(const uint32_t* hist, uint32_t* __res
 // Blocks of 256 neighbouring entries of a segment, counted from the segment's begin: the block whose first entry has the
 // global index `first` in segment s keeps its largest key in slot (first >> 8) + s of the block-maximum array.  Slots of
 // different blocks differ (inside a segment `first` grows by 256 from block to block; the next segment begins behind
-// the last block's first entry and adds one more), so the array needs (n >> 8) + n_seg + 1 words.  Whoever holds the
-// scores in registers (the draft kernel, or the first-digit pass) writes it; the pass that sets entries aside reads it and
-// steps over every block whose maximum lies below the rank-k bucket: nearly all of them.
+// the last block's first entry and adds one more), so the array needs (n >> 8) + n_seg + 1 words.  The same for blocks of 64.
+// Whoever holds the scores in registers (the draft kernel, or a pass of its own) writes them.
 __device__ __forceinline__ int64_t block_max_slot(int64_t first, int s) { return (first >> 8) + s; }
+__device__ __forceinline__ int64_t block64_slot(int64_t first, int s) { return (first >> 6) + s; }
+__device__ __forceinline__ int64_t block16_slot(int64_t first, int s) { return (first >> 4) + s; }
+
+// Leaves the largest keys of the blocks of 16, 64 and 256 neighbours (the latter two where they are asked for) that a wavefront
+// holds, VEC = 4 or 1 entries per lane, lane 0 at the begin of a block: `top` is the largest key of the lane's own, `first` the index
+// of the first of these; entries at or past `end` are none.  The active lanes are 0 .. last.
+template <int VEC>
+__device__ __forceinline__ void note_maxima(uint32_t top, int64_t first, int last, int64_t end, int s, uint32_t* __restrict__ max16, uint32_t* __restrict__ max64,
+                                            uint32_t* __restrict__ max256)
+{
+    // (a lane whose source is switched off keeps its own)
+    const int lane = lane_id(), in_row = lane & 15;
+    top = max_with<0x4E, 0xf>(max_with<0xB1, 0xf>(top));   // quad_perm: the neighbour's, the other pair's
+    if constexpr (VEC == 4) {
+        if ((lane & 3) == 0 && first < end) max16[block16_slot(first, s)] = top;
+        if (!max64) return;
+        top = max_with<0x118, 0xf>(max_with<0x114, 0xf>(top));   // row_shr:4, row_shr:8: the last lane of a row of 16 has all four
+        if ((in_row == 15 || lane == last) && first - 4 * in_row < end) max64[block64_slot(first - 4 * in_row, s)] = top;
+        if (!max256) return;
+        top = rows_inclusive_max(top);
+        if (lane == last && first - 4 * last < end) max256[block_max_slot(first - 4 * last, s)] = top;
+    } else {
+        top = max_with<0x118, 0xf>(max_with<0x114, 0xf>(top));
+        if ((in_row == 15 || lane == last) && first - in_row < end) max16[block16_slot(first - in_row, s)] = top;
+        if (!max64) return;
+        top = rows_inclusive_max(top);
+        if (lane == last && first - last < end) max64[block64_slot(first - last, s)] = top;
+    }
+}
 
 // (key, index) packed so that a larger word is a better entry: key descending, then index ascending.
 __device__ __forceinline__ uint64_t compose(uint32_t key, uint32_t gidx) { return ((uint64_t)key << 32) | (uint64_t)(0xFFFFFFFFu - gidx); }

@@ -5,13 +5,15 @@
 // order; the k survivors are ranked by (key descending, index ascending).  Nothing depends on the order in which blocks or
 // wavefronts run.
 //
-// Four routes, same result:
+// Five routes, same result:
 //   tiny   - segments of at most 8192 entries and k up to 64 (the final selection after the verify stage, small draft
 //            populations): one launch, no digits (tiny_select in select_common.h);
-//   pick   - segments of at most kPickMax entries: one launch behind whoever counted the first digit (the draft kernel as a
-//            rule, else one pass), or, up to kCountMax entries, one launch that counts it too.  Several workgroups per segment, each of which goes through the whole segment, keeps the
-//            few entries at or above rank k's bin, and ranks its share of them;
-//   lists  - segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
+//   pick   - short segments: one launch, in which several workgroups per segment hold it in registers, count the first digit, keep
+//            the few entries at or above rank k's bin, and each rank their share of them (k above kLevelK: also segments of at
+//            most kPickMax entries, behind whoever counted the digit, the draft kernel or a pass);
+//   levels - longer ones, k up to kLevelK: the same launch behind whoever held the scores and left the largest key of every sixteen
+//            neighbours (the draft kernel, else a pass): a workgroup holds the few blocks of sixteen that can matter;
+//   lists  - a larger k, segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
 //            16384-entry sweeps, one workgroup each) and sets the entries at or above the bin aside in a list per span; the
 //            workgroups of a segment then collect from its lists (and go through the span of a list that overflowed themselves);
 //   spans  - longer segments are cut into spans of whole 16384-entry sweeps, one workgroup of 1024 threads each; the scores
@@ -138,7 +140,7 @@ __device__ __forceinline__ void finish_segment(uint64_t* sel, int n, int lo, int
 // R = 64, 32 or 16 of the n words at a time (the fewest lanes that still hold them all: idle lanes would cost the same
 // as busy ones) and 64 / R parts of its sixteenth of the k words to compare with; the lanes of one part read the same
 // word at a time (a broadcast LDS access).  Cheap when the k words' ranks are shared out over many workgroups; a full
-// sort in one workgroup is better served by the bitonic network.  cnt: NT LDS words.  All NT threads call.
+// sort in one workgroup is better served by the bitonic network.  cnt: 64 LDS words.  All NT threads call.
 template <int NT>
 __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint16_t* which, int first, int stride, int n, uint32_t* cnt,
                                           const float* __restrict__ score, int32_t* __restrict__ idx_out, float* __restrict__ val_out, int64_t row,
@@ -155,6 +157,7 @@ __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint
     const int per_piece = (((n_raw + W * parts - 1) / (W * parts)) + 1) & ~1;
     const int j_lo = piece * per_piece < n_raw ? piece * per_piece : n_raw, j_hi = j_lo + per_piece < n_raw ? j_lo + per_piece : n_raw;
     for (int e0 = 0; e0 < n; e0 += R) {
+        if (threadIdx.x < kWave) cnt[threadIdx.x] = 0;
         const bool live = e0 + mine_at < n;
         const uint64_t mine = live ? sel[slot(which ? (uint32_t)which[e0 + mine_at] : (uint32_t)(first + (e0 + mine_at) * stride))] : ~0ull;
         uint32_t c = 0;
@@ -164,12 +167,11 @@ __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint
             c += w.x > mine ? 1u : 0u;
             c += w.y > mine ? 1u : 0u;
         }
-        cnt[threadIdx.x] = c;
+        __syncthreads();
+        if (c) atomicAdd(&cnt[mine_at], c);
         __syncthreads();
         if (wave == 0 && lane < R && live) {
-            uint32_t r = 0;
-            for (int q = lane; q < NT; q += R) r += cnt[q];   // the counts of this word from every piece
-            const uint32_t gi = index_of(mine);
+            const uint32_t r = cnt[lane], gi = index_of(mine);
             if (r < (uint32_t)row_len) {
                 idx_out[row * row_len + r] = (int32_t)gi;
                 // a key names its score (no read to wait for), except the one that -0.0 and +0.0 share
@@ -195,12 +197,12 @@ struct SegsInMemory {
 // ---- tiny route: segments of at most 8192 entries, k at most 64 ---------------------------------------------------
 // (tiny_select in select_common.h: the final selection after the verify stage and small draft populations)
 
-template <bool INLINE>
-__global__ void __launch_bounds__(kTinyThreads) topk_tiny_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, InlineSegs inl,
-                                                                 int k, int32_t* __restrict__ idx_out, float* __restrict__ val_out)
+template <class Table>
+__global__ void __launch_bounds__(kTinyThreads) topk_tiny_kernel(const float* __restrict__ score, Table segs, int k, int32_t* __restrict__ idx_out,
+                                                                 float* __restrict__ val_out)
 {
     __shared__ TinyLds L;
-    const SegT seg = INLINE ? inl.s[blockIdx.x] : segs[blockIdx.x];
+    const SegT seg = segs.at(blockIdx.x);
     tiny_select(L, score, seg.begin, seg.end, blockIdx.x, k, idx_out, val_out);
 }
 
@@ -955,25 +957,36 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
     }
 }
 
-// ---- pick route ---------------------------------------------------------------------------------------------------------
-// `share` workgroups per segment of at most kPickMax entries.  Each finds rank k's bin from the first digit's histogram, goes
-// through the whole segment (it comes from the cache: 256 KB at most), notes the places of the entries at or above the bin,
-// and ranks those whose index hashes to it among all of them: no lists between launches, no second and third digit as long as
-// the collection fits (its size follows from the histogram).  Where it does not, the bin is split by two more passes over the
-// segment; ties beyond that are written in index order by the segment's first workgroup.
-// Bound: the latency of its stages.  The whole segment is requested at once, before the histogram is looked at, and a thread's
-// sixty-four comparisons leave a mask; places, not scores, are noted, so nothing is selected out of registers.  20 segments of
-// 50,000 entries, k = 512: 12 us where staging, refining, settling and ranking took 31 in four launches (bin 2.6 us, masks and
-// places 2, words 1.7, ranks 2; sweeping in four steps took 3 us more).
+// ---- pick and levels routes ---------------------------------------------------------------------------------------------
+// `share` workgroups per segment.  Each holds what can matter of the segment in registers (sixteen entries per thread), collects all
+// entries at or above a bound that at least k entries reach, and ranks those whose index hashes to it among all of them: no lists
+// between launches.
+//   pick: segments of at most kRow entries are held whole, their first digits counted where they lie.  (k above kLevelK: of at most
+// kPickMax entries, read in rows of kRow, the digits counted by the launch before as a rule.)
+//   levels: of longer ones blocks of sixteen neighbours are held.  Whoever held the scores left the largest key of every sixteen (and
+// of every 64 and 256 where segments are long).  The k best entries lie in the k best blocks (by largest key, then in index order):
+// an entry of another block has the largest entries of k blocks before it.  So the k best of the maxima are found, of 256 first,
+// then of the 64s in those, then of the sixteens, and the bound that the k-th best maximum gives is one that few more than k entries
+// reach: of m maxima in no particular order about m ln(m / (m - k)).  All steps are bounded for any values, ties and sorted
+// segments included.
+//   A collection that is larger than the limit (ties, entries side by side) is split by up to three digits of the keys' range; ties
+// beyond that are written in index order by the segment's first workgroup.
+// Bound: the latency of the stages, and what one compute unit draws from beyond its cache: about 50 GB/s, so that a segment of
+// 65,536 entries held whole took 5.3 us to arrive; the maxima and blocks of a segment of 50,000, k = 512, are 50 KB.
+// Measured, before = digits counted in the draft kernel and segments held whole (above 65,536 a launch that set entries aside first):
+// 20 x 50,000, k = 512: draft 13.9 -> 12.8 us, the launch that cleared histograms 2.6 -> none, this one 13.5 -> 14.2; 65,536, k = 128:
+// 7.9 -> 7.6, 2.3 -> none, 10.9 -> 9.8; ten segments of 333,333, k = 512: the selection 3 + 7.5 + 8.5 -> 16.5; a kernel of this kind
+// is bound by its instructions too (16 wavefronts share four pipes: one more per thread costs 7 ns).
 
 constexpr int kPickMax = 65536;
-// Segments up to this length whose first digit nobody has counted (pruner_topk) are counted by their workgroups, from the registers
-// that hold them: one launch, without a histogram in memory (20 segments of 512, k = 100: 16 -> 9.7 us; 300 of 20,000, k = 32:
-// 60 -> 47; 1,000 of 20,000, k = 512: 141 -> 117; at 32,768 the launches saved still pay).
-constexpr int kCountMax = 32768;
+constexpr int kCountMax = 32768;                                // entries held in registers where there are no blocks
 constexpr int kXcds = 8;                                        // parts of the device with a cache of their own; workgroups go to them in turn
 constexpr int kPickCap = 8192;                                  // words a workgroup collects
 constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
+constexpr int kLevelK = 1024;                                   // blocks of sixteen that registers hold
+static_assert(kLevelK * 16 == kRow, "selected blocks are held as a short segment is");
+constexpr int kDirectBlocks = 16384;                             // up to here all maxima of a level are looked at, above it those in the best of the next
+constexpr int64_t kLevelMax = (int64_t)1 << 25;                 // (every workgroup reads the maxima of the segment's blocks of 256: 512 KB)
 // What is collected is ranked word against word, so it has to be little more than k: otherwise the bin is split first (two
 // values shared by 20,000 entries, k = 512: 84 us with all of the bin ranked, 25 with the limit).
 __host__ __device__ constexpr int collect_limit(int k) { return k + k / 4 + 256; }
@@ -1193,23 +1206,243 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
         own_best(score + lo, (int)(hi - lo), (uint32_t)lo, k, lowest, width, hist, wave_tot, found, &fill, range, &mine);
 }
 
-// LISTS: the lists route.  COUNT: segments of at most kCountMax entries whose first digit nobody has counted; every workgroup does
-// so itself, and the call is this one launch.
-// SORT: with the way of sorting what would take many rounds to rank (the other calls' kernel is shorter without it).
-template <bool LISTS, bool COUNT, bool SORT, class Table>
-__global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, Table segs, int n_seg, int n_total, int R,
-                                                           int k, int share, int span, const uint32_t* __restrict__ ghist0,
-                                                           const uint32_t* __restrict__ ghist1, const uint32_t* __restrict__ granges,
-                                                           const Stage* __restrict__ stage, int n_stages, int32_t* __restrict__ idx_out,
+// The n words in sel to the rows (those below row_len = k) of one segment: ranked in rounds of 64 per workgroup, the words shared out over the
+// segment's workgroups, or sorted, all of them by every workgroup, whatever costs less (see kSortFactor).
+// SORT: with the way of sorting (the other calls' kernel is shorter without it).  k_rem of the words with keys lowest .. lowest + width
+// are selected, and all above; in_trim: these two facts are exact, so that the sort may leave the surplus out.
+template <bool SORT>
+__device__ __forceinline__ void write_collection(uint64_t* sel, uint32_t* place, uint32_t* cnt, uint32_t* fill, uint32_t* n_own, int n, int k, int share, int part,
+                                                 uint32_t k_rem, uint32_t lowest, uint32_t width, bool exact, const float* __restrict__ score,
+                                                 int32_t* __restrict__ idx_out, float* __restrict__ val_out, int s, const SegT& seg)
+{
+    uint16_t* own = reinterpret_cast<uint16_t*>(place);
+    const int n_last = n - (int)((uint32_t)k - k_rem);   // the words of the last bin
+    const bool trim = exact && n > k && n_last <= kTrimMax && pow2_at_least(n) > pow2_at_least(k);
+    const int rounds = (n + 64 * share - 1) / (64 * share);
+    if (SORT && rounds * n > kSortFactor * pow2_at_least(trim ? k : n)) {
+        if (trim) {
+            // the sort is half as long without those of the last bin that are not selected: their places go to what lies behind k
+            uint64_t* bin_word = reinterpret_cast<uint64_t*>(place);
+            uint16_t *bin_at = reinterpret_cast<uint16_t*>(place + 2 * kTrimMax), *hole = bin_at + kTrimMax;
+            static_assert(kPickCap * sizeof(uint32_t) >= kTrimMax * (sizeof(uint64_t) + 2 * sizeof(uint16_t)), "the lists fit");
+            __syncthreads();
+            if (threadIdx.x == 0) *fill = 0;
+            __syncthreads();
+            for (int e = threadIdx.x; e < n; e += kBigThreads) {
+                const uint64_t w = sel[slot((uint32_t)e)];
+                if ((uint32_t)(w >> 32) - lowest <= width) {
+                    const uint32_t at = atomicAdd(fill, 1u);
+                    if (at < (uint32_t)kTrimMax) bin_word[at] = w, bin_at[at] = (uint16_t)e;
+                }
+            }
+            __syncthreads();
+            if ((int)threadIdx.x < n_last) {
+                const uint64_t me = bin_word[threadIdx.x];
+                const int at = bin_at[threadIdx.x];
+                uint32_t better = 0;
+                for (int x = 0; x < n_last; ++x) better += bin_word[x] > me ? 1u : 0u;
+                if (better >= k_rem) {
+                    sel[slot((uint32_t)at)] = 0;
+                    if (at < k) hole[atomicAdd(n_own, 1u)] = (uint16_t)at;
+                }
+            }
+            if (threadIdx.x == 0) *fill = 0;
+            __syncthreads();
+            for (int e = k + (int)threadIdx.x; e < n; e += kBigThreads) {
+                const uint64_t w = sel[slot((uint32_t)e)];
+                if (w != 0ull) sel[slot(hole[atomicAdd(fill, 1u)])] = w;
+            }
+            __syncthreads();
+            n = k;
+        }
+        const int rows = n < k ? n : k, per = (rows + share - 1) / share, lo = part * per < rows ? part * per : rows;   // each writes its part of the rows
+        finish_segment<kBigThreads>(sel, n, lo, lo + per < rows ? lo + per : rows, score, idx_out, val_out, s, seg.begin, seg.end, k);
+        n = 0;
+    }
+    // (every workgroup has its own order of the words: a hash of the index decides who ranks a word)
+    for (int e = threadIdx.x; e < n; e += kBigThreads) {
+        const uint32_t h = (index_of(sel[slot((uint32_t)e)]) * 2654435761u) >> 16;
+        if ((int)(h % (uint32_t)share) == part) own[atomicAdd(n_own, 1u)] = (uint16_t)e;
+    }
+    __syncthreads();
+    if (n > 0) rank_rows<kBigThreads>(sel, n, own, 0, 1, (int)*n_own, cnt, score, idx_out, val_out, s, seg.begin, seg.end, k);
+}
+
+// Four neighbouring maxima from number `at` on, 0 for those past the last.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 u32x4_a4 __attribute__((aligned(4)));
+__device__ __forceinline__ u32x4 maxima_at(const uint32_t* maxima, int at, int n)
+{
+    u32x4 w = *reinterpret_cast<const u32x4_a4*>(maxima + at);
+#pragma unroll
+    for (int e = 1; e < 4; ++e) w[e] = at + e < n ? w[e] : 0u;
+    return w;
+}
+// The blocks whose maxima reach a bound that at least k of them reach, at most kLevelK, in index order, in `out`; the bound is
+// returned.  Where more reach it, it is raised digit by digit, and of maxima that all equal it the first ones are taken.
+// parents (n_parents > 0): only the blocks that these numbers, in order, name four each, and `bound` is one that k of them reach; else 0.  All threads of the workgroup; hist,
+// wave_tot, found, range: its LDS.  (The loops are kept rolled: a workgroup runs this once or twice, and what unrolled code costs is its
+// way into the instruction cache.)
+__device__ __forceinline__ uint32_t best_blocks(const uint32_t* __restrict__ maxima, int n, const uint32_t* parents, int n_parents, uint32_t bound, uint32_t k, uint32_t* hist,
+                                                uint32_t* wave_tot, uint32_t* found, uint32_t* range, uint32_t* out, int* n_out)
+{
+    // Quads of maxima per thread and row, neighbours: the order of the threads is that of the blocks.
+    constexpr int kQuads = 4;
+    const int n_quads = n_parents > 0 ? n_parents : (n + 3) >> 2;
+    const int of = n_quads > 3 * kBigThreads ? 4 : n_quads > 2 * kBigThreads ? 3 : n_quads > kBigThreads ? 2 : 1, rows = (n_quads + of * kBigThreads - 1) / (of * kBigThreads);
+    auto first = [&](int q) -> int { return n_parents > 0 ? 4 * (int)parents[q] : 4 * q; };
+    uint32_t v[4 * kQuads];
+    int n_mine = 0;   // quads of this thread
+    auto load = [&](int row) {
+        const int q0 = (row * kBigThreads + (int)threadIdx.x) * of;
+        n_mine = n_quads - q0 < of ? n_quads - q0 : of;
+        u32x4 w[kQuads];
+#pragma unroll
+        for (int j = 0; j < kQuads; ++j)
+            if (j < of) w[j] = maxima_at(maxima, first(q0 + j < n_quads ? q0 + j : n_quads - 1), n);
+#pragma unroll
+        for (int j = 0; j < kQuads; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[4 * j + e] = j < of && j < n_mine ? w[j][e] : 0u;
+    };
+    if (rows == 1) load(0);
+    // maxima of sixteen and of four of the maxima serve as well where there are enough of them
+    int together = of == 4 && n_quads >= 16 * (int)k ? 16 : n_quads >= 4 * (int)k ? 4 : 1;
+    uint32_t lowest = bound, width = ~0u - bound, k_rem = k, in_bin = 0, taken = 0, largest = 0;
+#pragma unroll 1
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        // first: the bin of k maxima, split once where it holds many (among the parts of blocks chosen already their bound does as
+        // well); again, from that bound on and with every block's own, where more than kLevelK blocks reach it
+        const uint32_t enough = attempt == 0 ? (uint32_t)collect_limit((int)k) : (uint32_t)kLevelK;
+#pragma unroll 1
+        for (int digit = 0; digit < (attempt == 0 ? (n_parents > 0 ? 0 : 2) : 3) && width != 0u; ++digit) {
+            const bool narrow_bins = attempt == 0 && digit == 0;
+            const int shift = next_shift(width);
+            __syncthreads();
+            for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+            __syncthreads();
+            auto add = [&](uint32_t key, bool there) {
+                const uint32_t digit = narrow_bins ? first_digit_of(key) : (key - lowest) >> shift;
+                const bool counts = there && key >= lowest && key - lowest <= width;
+                if (of > 1) light_hist_add(hist, digit, counts);
+                else if (counts) atomicAdd(&hist[digit], 1u);   // (few: also where they queue on one address)
+            };
+#pragma unroll 1
+            for (int row = 0; row < rows; ++row) {
+                if (rows > 1) load(row);
+                uint32_t best = 0;
+#pragma unroll
+                for (int j = 0; j < kQuads; ++j) {
+                    if (j >= of) continue;
+                    if (together == 1) {
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) add(v[4 * j + e], j < n_mine);
+                    } else {
+                        const uint32_t a = v[4 * j] > v[4 * j + 1] ? v[4 * j] : v[4 * j + 1], b = v[4 * j + 2] > v[4 * j + 3] ? v[4 * j + 2] : v[4 * j + 3];
+                        const uint32_t top = a > b ? a : b;
+                        if (together == 4) add(top, j < n_mine);
+                        else best = top > best ? top : best;
+                    }
+                }
+                if (together == 16) add(best, n_mine > 0);
+            }
+            __syncthreads();
+            find_bucket(hist, k_rem, wave_tot, found);
+            if (narrow_bins) {
+                first_digit_range(found[0], lowest, width);
+            } else {
+                lowest += found[0] << shift;
+                width = (1u << shift) - 1u;
+                width = attempt == 1 && largest - lowest < width ? largest - lowest : width;
+            }
+            k_rem = found[1];
+            in_bin = found[2];
+            if (k - k_rem + in_bin <= enough) break;
+        }
+        // the blocks at or above the bound (ties apart: above it, and the first k_rem that equal it), in order
+        const bool ties_apart = attempt == 1 && k - k_rem + in_bin > (uint32_t)kLevelK;
+        uint32_t ties_before = 0, total;
+        taken = 0;
+#pragma unroll 1
+        for (int row = 0; row < rows; ++row) {
+            if (rows > 1) load(row);
+            uint32_t mask = 0, equal = 0;
+#pragma unroll
+            for (int j = 0; j < kQuads; ++j) {
+                if (j >= of) continue;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) mask |= v[4 * j + e] >= lowest ? 1u << (4 * j + e) : 0u;
+            }
+            const uint32_t there = n_mine > 0 ? (1u << (4 * n_mine)) - 1u : 0u;
+            mask &= there;
+            if (ties_apart) {
+#pragma unroll
+                for (int j = 0; j < 4 * kQuads; ++j) equal |= v[j] == lowest ? 1u << j : 0u;
+                equal &= there;
+                mask ^= equal;
+                uint32_t number = ties_before + block_excl_scan<kBigThreads>((uint32_t)__popc(equal), wave_tot, &total);
+#pragma unroll 1
+                for (; equal && number < k_rem; equal &= equal - 1u, ++number) mask |= equal & (0u - equal);
+                ties_before += total;
+            }
+            uint32_t at = taken + block_excl_scan<kBigThreads>((uint32_t)__popc(mask), wave_tot, &total);
+#pragma unroll 1
+            for (; mask; mask &= mask - 1u, ++at) {
+                const int j = __ffs((int)mask) - 1;
+                if (at < (uint32_t)kLevelK) out[at] = (uint32_t)(first((row * kBigThreads + (int)threadIdx.x) * of + (j >> 2)) + (j & 3));
+            }
+            taken += total;
+        }
+        if (taken <= (uint32_t)kLevelK || attempt == 1) break;
+        // (a range that holds one key only is known for it and not split)
+        if (threadIdx.x == 0) range[0] = range[1] = 0;
+        __syncthreads();
+        uint32_t not_least = 0;
+#pragma unroll 1
+        for (int row = 0; row < rows; ++row) {
+            if (rows > 1) load(row);
+#pragma unroll
+            for (int j = 0; j < 4 * kQuads; ++j) {
+                const bool in = (j >> 2) < n_mine && v[j] >= lowest;
+                not_least = in && ~v[j] > not_least ? ~v[j] : not_least;
+                largest = in && v[j] > largest ? v[j] : largest;
+            }
+        }
+        note_range(not_least, largest, range);
+        __syncthreads();
+        lowest = ~range[0];
+        largest = range[1];
+        width = largest - lowest;
+        together = 1;
+        k_rem = k;
+        in_bin = taken;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) range[0] = range[1] = 0;
+    *n_out = (int)(taken < (uint32_t)kLevelK ? taken : (uint32_t)kLevelK);
+    return lowest;
+}
+
+// The largest keys of every 16, 64 and 256 neighbouring entries; the latter two may be null where no segment has more than
+// kDirectBlocks blocks of 16 (of 64).
+struct Maxima {
+    const uint32_t *of16, *of64, *of256;
+};
+
+// LEVELS: segments longer than kRow, by blocks.  ghist0 (or null): the first digits' histogram, in R copies.
+template <bool LEVELS, bool SORT, class Table>
+__global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restrict__ score, Table segs, int n_seg, int n_total, int k, int share,
+                                                           Maxima maxima, const uint32_t* __restrict__ ghist0, int R, int32_t* __restrict__ idx_out,
                                                            float* __restrict__ val_out)
 {
+    constexpr int kQ = (LEVELS ? kRow : kCountMax) / (4 * kBigThreads);
     __shared__ __align__(16) uint64_t sel[kPickWords];
-    __shared__ __align__(16) uint32_t place[kPickCap];   // indices inside the segment; later: which words this workgroup ranks
+    __shared__ __align__(16) uint32_t place[kPickCap];   // selected blocks of the level before; then indices inside the segment; then which words this workgroup ranks
     __shared__ uint32_t hist[kBins];          // later: the ranking's counts
+    __shared__ uint32_t blocks[LEVELS ? kLevelK : 1];
     __shared__ uint32_t wave_tot[16];
     __shared__ uint32_t found[3];
     __shared__ uint32_t fill, n_own, range[2];
-    uint16_t* own = reinterpret_cast<uint16_t*>(place);
     // The workgroups of a segment go to one of the eight parts of the device: its cache then reads the segment once for all.
     const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
     if (job >= n_seg * share) return;
@@ -1217,51 +1450,284 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     const SegT seg = segs.at(s);
     const int len = (int)(seg.end - seg.begin);
     const float* seg_score = score + seg.begin;
-    const int lane = lane_id(), wave = threadIdx.x >> 6;
 
-    // The whole segment travels while the bin is looked up: sixteen groups of four neighbours per thread.  A group that would
-    // reach past the end of the scores starts earlier; what lies outside the segment is masked out below.
-    constexpr int kGroups = LISTS ? 1 : (COUNT ? kCountMax : kPickMax) / (4 * kBigThreads);
+    int n_blocks = 0;
+    uint32_t lowest = 0, width = ~0u, k_rem = (uint32_t)k, in_bin = 0;
+    const bool whole = !LEVELS || len <= kRow;
+    if (!whole) {
+        const int n16 = (len + 15) >> 4, n64 = (len + 63) >> 6;
+        const int top = n16 <= kDirectBlocks ? 0 : n64 <= kDirectBlocks ? 1 : 2;
+#pragma unroll 1
+        for (int level = top; level >= 0; --level) {
+            if (level < top) {
+                for (int i = threadIdx.x; i < n_blocks; i += kBigThreads) place[i] = blocks[i];
+                __syncthreads();
+            }
+            const uint32_t* const of = level == 0 ? maxima.of16 + block16_slot(seg.begin, s) : level == 1 ? maxima.of64 + block64_slot(seg.begin, s) : maxima.of256 + block_max_slot(seg.begin, s);
+            lowest = best_blocks(of, level == 0 ? n16 : level == 1 ? n64 : (len + 255) >> 8, place, level < top ? n_blocks : 0, lowest, (uint32_t)k, hist, wave_tot, found, range, blocks, &n_blocks);
+        }
+        width = ~0u - lowest;
+    }
+
+    // Groups of four neighbours, at multiples of four from the segment's begin: kQ per thread and row.
     const int last = n_total - 4 - (int)seg.begin;   // (there are more than four scores in all)
-    auto group_begin = [](int g) { return (g * kBigThreads + (int)threadIdx.x) * 4; };
-    f32x4 val[kGroups];
-    const int b0 = seg.first_block, n_lists = LISTS ? (s + 1 < n_seg ? segs.at(s + 1).first_block : n_stages) - b0 : 0;
-    uint32_t my_count = 0;   // of list `lane`
-    if constexpr (LISTS) {
-        if (lane < n_lists) my_count = reinterpret_cast<const List*>(&stage[b0 + lane])->count;
-    } else {
+    const int held = whole ? len : 16 * n_blocks, rows = (held + kQ * 4 * kBigThreads - 1) / (kQ * 4 * kBigThreads);
+    auto group_begin = [&](int g) -> int {
+        const int at = g * kBigThreads + (int)threadIdx.x;
+        if (!LEVELS || whole) return 4 * at;
+        return (at >> 2) < n_blocks ? (int)(16u * blocks[at >> 2]) + 4 * (at & 3) : len;
+    };
+    // (a group that would reach past the end of the scores starts earlier: there_of tells which of the four are the group's)
+    auto load_group = [&](int i) { return f32x4(*reinterpret_cast<const f32x4_a4*>(seg_score + (i < last ? i : last))); };
+    auto there_of = [&](int i) -> uint32_t {
+        const int left = len - i, moved = i < last ? 0 : i - last;
+        return left <= 0 ? 0u : ((left < 4 ? (1u << left) - 1u : 15u) << moved) & 15u;
+    };
+    f32x4 row_of[kQ];
+    auto load_row = [&](int row) {
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            if (g * 4 * kBigThreads < len) {
-                const int i = group_begin(g);
-                val[g] = *reinterpret_cast<const f32x4_a4*>(seg_score + (i < last ? i : last));
+        for (int q = 0; q < kQ; ++q)
+            if ((kQ * row + q) * 4 * kBigThreads < held) row_of[q] = load_group(group_begin(kQ * row + q));
+    };
+    auto each_key = [&](auto&& what) {   // what(index, key, whether it is the segment's); a single row is read once
+#pragma unroll 1
+        for (int row = 0; row < rows; ++row) {
+            if (rows > 1) load_row(row);
+#pragma unroll
+            for (int q = 0; q < kQ; ++q) {
+                if ((kQ * row + q) * 4 * kBigThreads >= held) continue;
+                const int i = group_begin(kQ * row + q);
+                const uint32_t there = there_of(i);
+                uint32_t keys[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) keys[e] = key_of(row_of[q][e]);
+                what(i < last ? i : last, keys, there);
             }
         }
-    }
-    if constexpr (COUNT) {
-        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
-        __syncthreads();
+    };
+    if (rows == 1) load_row(0);
+    // (every group that is held is held whole: the segment's end lies in none of them)
+    const bool all_whole = whole || (len & 15) == 0 || blocks[n_blocks - 1] != (uint32_t)(len >> 4);
+    const uint32_t limit = (uint32_t)collect_limit(k);
+    bool exact = whole;   // k_rem, in_bin: of the bin lowest .. lowest + width, by count
+    if (whole) {
+        if (ghist0) {
+            bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+        } else {
+            for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+            __syncthreads();
+            each_key([&](int, const uint32_t (&keys)[4], uint32_t there) {
 #pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            if (g * 4 * kBigThreads < len) {
-                const int i = group_begin(g), begun = i < last ? i : last;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) light_hist_add(hist, first_digit_of(key_of(val[g][e])), begun + e >= i && begun + e < len);
-            }
+                for (int e = 0; e < 4; ++e) light_hist_add(hist, first_digit_of(keys[e]), ((there >> e) & 1u) != 0u);
+            });
+            __syncthreads();
+            find_bucket(hist, (uint32_t)k, wave_tot, found);
         }
-        __syncthreads();
-        find_bucket(hist, (uint32_t)k, wave_tot, found);
-    } else {
-        bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+        first_digit_range(found[0], lowest, width);
+        k_rem = found[1];
+        in_bin = found[2];
     }
-    uint32_t lowest, width, k_rem = found[1], in_bin = found[2];
-    first_digit_range(found[0], lowest, width);
     if (threadIdx.x == 0) fill = n_own = range[0] = range[1] = 0;
     __syncthreads();
-    // More than the limit: the bin is split (the same decision in every workgroup of the segment), in the lists route first by
-    // the second digit, which the launch before has counted.
+    bool ties_apart = false;
+#pragma unroll 1
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        if ((uint32_t)k - k_rem + in_bin > limit && !ties_apart) {
+            // Too many (ties, entries side by side).  The bound is raised digit by digit; a range that holds one key only is known for it
+            // and not split.
+            uint32_t not_least = 0, largest = 0;
+            each_key([&](int, const uint32_t (&keys)[4], uint32_t there) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool in = ((there >> e) & 1u) != 0u && keys[e] >= lowest && keys[e] - lowest <= width;
+                    not_least = in && ~keys[e] > not_least ? ~keys[e] : not_least;
+                    largest = in && keys[e] > largest ? keys[e] : largest;
+                }
+            });
+            note_range(not_least, largest, range);
+            __syncthreads();
+            largest = range[1];
+            lowest = ~range[0];
+            width = largest - lowest;
+            exact = true;
+#pragma unroll 1
+            for (int digits = 0; digits < 3 && width != 0u && (uint32_t)k - k_rem + in_bin > limit; ++digits) {   // (32 bits at most)
+                const int shift = next_shift(width);
+                for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+                __syncthreads();
+                each_key([&](int, const uint32_t (&keys)[4], uint32_t there) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) light_hist_add(hist, (keys[e] - lowest) >> shift, ((there >> e) & 1u) != 0u && keys[e] >= lowest && keys[e] - lowest <= width);
+                });
+                __syncthreads();
+                find_bucket(hist, k_rem, wave_tot, found);
+                lowest += found[0] << shift;
+                width = (1u << shift) - 1u;
+                width = largest - lowest < width ? largest - lowest : width;
+                k_rem = found[1];
+                in_bin = found[2];
+                __syncthreads();
+            }
+            ties_apart = (uint32_t)k - k_rem + in_bin > limit;
+        }
+        // the places of the entries at or above the bound (ties apart: above it).  (Words straight out of the registers, sixteen stores
+        // under a condition each, took 2 us more than the places and the second look at the scores.)  At first by comparison: what is
+        // not below includes every NaN, which the ranking then orders by its bits, unless that makes too many.
+        const uint32_t expected = ties_apart ? (uint32_t)k - k_rem : (uint32_t)k - k_rem + in_bin;
+        const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
+#pragma unroll 1
+        for (int row = 0; row < rows; ++row) {
+            if (rows > 1) load_row(row);
+            uint32_t mask = 0;   // bit 4 q + e
+            if (attempt == 0) {
+#pragma unroll
+                for (int q = kQ - 1; q >= 0; --q) {
+                    uint32_t four = 0;
+                    if ((kQ * row + q) * 4 * kBigThreads < held) {
+#pragma unroll
+                        for (int e = 3; e >= 0; --e) four = 2u * four + (row_of[q][e] < t0 ? 0u : 1u);
+                        if (!all_whole || (kQ * row + q + 1) * 4 * kBigThreads > held) four &= there_of(group_begin(kQ * row + q));
+                    }
+                    mask = 16u * mask + four;
+                }
+            } else {
+#pragma unroll
+                for (int q = 0; q < kQ; ++q) {
+                    if ((kQ * row + q) * 4 * kBigThreads >= held) continue;
+                    uint32_t four = 0;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint32_t key = key_of(row_of[q][e]);
+                        four |= key > lowest || (!ties_apart && key == lowest) ? 1u << e : 0u;
+                    }
+                    mask |= (four & there_of(group_begin(kQ * row + q))) << (4 * q);
+                }
+            }
+            uint32_t to = reserve(&fill, (uint32_t)__popc(mask));
+#pragma unroll 1
+            for (; mask; mask &= mask - 1u, ++to) {
+                const int bit = __ffs((int)mask) - 1, i = group_begin(kQ * row + (bit >> 2));
+                if (to < (uint32_t)kPickCap) place[to] = (uint32_t)((i < last ? i : last) + (bit & 3));
+            }
+        }
+        __syncthreads();
+        const uint32_t collected = fill;
+        if (exact ? collected == expected : collected <= limit) break;
+        __syncthreads();
+        if (threadIdx.x == 0) fill = 0;
+        if (!exact) in_bin = collected;
+    }
+    if (ties_apart && part == 0) {
+        // ties, all of the key `lowest`, in index order: the tie of rank r owns row k - k_rem + r (groups and threads are in that order)
+        uint32_t before = 0;
+#pragma unroll 1
+        for (int g = 0; g * 4 * kBigThreads < held && before < k_rem; ++g) {
+            const int i = group_begin(g);
+            const f32x4 again = load_group(i);
+            uint32_t four = 0, total;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) four |= key_of(again[e]) == lowest ? 1u << e : 0u;
+            four &= there_of(i);
+            uint32_t number = before + block_excl_scan<kBigThreads>((uint32_t)__popc(four), wave_tot, &total);
+#pragma unroll 1
+            for (; four && number < k_rem; four &= four - 1u, ++number)
+                put_tie_row(k, (uint32_t)k - k_rem + number, (uint32_t)(seg.begin + (i < last ? i : last) + __ffs((int)four) - 1), lowest, score, idx_out, val_out, s, seg.begin, seg.end);
+            before += total;
+        }
+    }
+    const int n = (int)(fill < (uint32_t)kPickCap ? fill : (uint32_t)kPickCap);
+    for (int e = threadIdx.x; e < n; e += kBigThreads) {
+        const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
+        sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
+    }
+    if (SORT && !exact && n > k && pow2_at_least(n) > pow2_at_least(k)) {
+        // what the sort may leave out: the words up to the end of rank k's bin that are not selected
+        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+        __syncthreads();   // (and the words are there)
+        for (int e = threadIdx.x; e < n; e += kBigThreads) atomicAdd(&hist[first_digit_of((uint32_t)(sel[slot((uint32_t)e)] >> 32))], 1u);
+        __syncthreads();
+        find_bucket(hist, (uint32_t)k, wave_tot, found);
+        uint32_t bin_lowest, bin_width;
+        first_digit_range(found[0], bin_lowest, bin_width);
+        width = bin_lowest + bin_width - lowest;
+        k_rem = found[1];
+        exact = true;
+    }
+    // spare words and those behind the last must read as "below everything"
+    const int n_raw = n > 0 ? (int)slot((uint32_t)n - 1u) + 1 : 0;
+    for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
+        if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
+    __syncthreads();
+    write_collection<SORT>(sel, place, hist, &fill, &n_own, n, k, share, part, k_rem, lowest, width, exact, score, idx_out, val_out, s, seg);
+}
+
+// The largest keys of blocks (max64, max256 may be null), for scores that nobody has held before.  Bound by the scores' way from memory.
+template <class Table>
+__global__ void __launch_bounds__(256) maxima_kernel(const float* __restrict__ score, Table segs, uint32_t* __restrict__ max16, uint32_t* __restrict__ max64,
+                                                     uint32_t* __restrict__ max256)
+{
+    const int s = blockIdx.y;
+    const SegT seg = segs.at(s);
+    const int64_t base = seg.begin + (int64_t)blockIdx.x * 4096 + 4 * (int64_t)threadIdx.x;
+    f32x4 val[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int64_t i = base + 1024 * g;
+        val[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (i + 4 <= seg.end) {
+            val[g] = *reinterpret_cast<const f32x4_a4*>(score + i);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (i + e < seg.end) val[g][e] = score[i + e];
+        }
+    }
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int64_t i = base + 1024 * g;
+        uint32_t top = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t key = i + e < seg.end ? key_of(val[g][e]) : 0u;
+            top = key > top ? key : top;
+        }
+        note_maxima<4>(top, i, kWave - 1, seg.end, s, max16, max64, max256);
+    }
+}
+
+// The workgroups of a segment collect from its lists, and rank as pick_kernel does.
+template <bool SORT>
+__global__ void __launch_bounds__(kBigThreads) pick_lists_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int R,
+                                                                 int k, int share, int span, const uint32_t* __restrict__ ghist0,
+                                                                 const uint32_t* __restrict__ ghist1, const uint32_t* __restrict__ granges,
+                                                                 const Stage* __restrict__ stage, int n_stages, int32_t* __restrict__ idx_out,
+                                                                 float* __restrict__ val_out)
+{
+    __shared__ __align__(16) uint64_t sel[kPickWords];
+    __shared__ __align__(16) uint32_t place[kPickCap];   // which words this workgroup ranks
+    __shared__ uint32_t hist[kBins];          // later: the ranking's counts
+    __shared__ uint32_t wave_tot[16];
+    __shared__ uint32_t found[3];
+    __shared__ uint32_t fill, n_own;
+    const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    if (job >= n_seg * share) return;
+    const int s = job / share, part = job % share;
+    const SegT seg = segs[s];
+    const int len = (int)(seg.end - seg.begin);
+    const float* seg_score = score + seg.begin;
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    const int b0 = seg.first_block, n_lists = (s + 1 < n_seg ? segs[s + 1].first_block : n_stages) - b0;
+    uint32_t my_count = 0;   // of list `lane`
+    if (lane < n_lists) my_count = reinterpret_cast<const List*>(&stage[b0 + lane])->count;
+    bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+    uint32_t lowest, width, k_rem = found[1], in_bin = found[2];
+    first_digit_range(found[0], lowest, width);
+    if (threadIdx.x == 0) fill = n_own = 0;
+    __syncthreads();
+    // More than the limit: the bin is split (the same decision in every workgroup of the segment), first by the second
+    // digit, which the launch before has counted.
     const uint32_t limit = (uint32_t)collect_limit(k);
-    const unsigned long long overflowed = LISTS ? __ballot(my_count > (uint32_t)kListCap) : 0ull;   // (every wavefront holds all counts)
+    const unsigned long long overflowed = __ballot(my_count > (uint32_t)kListCap);   // (every wavefront holds all counts)
     // The spans of lists that overflowed (a stretch of good entries, as a sorted segment has it) are gone through by the whole
     // workgroup: what(row, hi, val) for each of their sweeps.
     auto through_overflowed = [&](auto&& what) {
@@ -1281,32 +1747,10 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         lowest = lowest > least ? lowest : least;
         width = last_key - lowest;
     };
-    bool second = !LISTS;
+    bool second = false;
     if ((uint32_t)k - k_rem + in_bin > limit) {
-        if constexpr (LISTS) {
-            least = ~granges[(size_t)s * kBins];
-            largest = granges[(size_t)s * kBins + 1];
-        } else {
-            uint32_t a = 0, b = 0;
-#pragma unroll
-            for (int g = 0; g < kGroups; ++g) {
-                if (g * 4 * kBigThreads < len) {
-                    const int i = group_begin(g), begun = i < last ? i : last;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const uint32_t key = key_of(val[g][e]);
-                        const bool in = (uint32_t)(begun + e) < (uint32_t)len && key - lowest <= width;
-                        a = in && ~key > a ? ~key : a;
-                        b = in && key > b ? key : b;
-                    }
-                }
-            }
-            note_range(a, b, range);
-            __syncthreads();
-            least = ~range[0];
-            largest = range[1];
-            between();
-        }
+        least = ~granges[(size_t)s * kBins];
+        largest = granges[(size_t)s * kBins + 1];
     }
     for (int digits = 0; digits < 3 && (uint32_t)k - k_rem + in_bin > limit && width != 0u; ++digits) {   // (a bin spans 2^22 keys at most)
         const int shift = next_shift(width);
@@ -1328,24 +1772,15 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                     light_hist_add(hist, (key - lowest) >> shift, sweep_index(row, j) < hi && key - lowest <= width);
                 }
             };
-            if constexpr (LISTS) {
-                for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
-                    const uint32_t cnt = (overflowed >> l) & 1ull ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
-                    const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
-                    for (uint32_t e = 0; e < cnt; e += kWave) {
-                        const uint32_t key = e + lane < cnt ? (uint32_t)(from[e + lane] >> 32) : 0u;
-                        light_hist_add(hist, (key - lowest) >> shift, e + lane < cnt && key - lowest <= width);
-                    }
-                }
-                through_overflowed(count_sweep);
-            } else {
-#pragma unroll 1
-                for (int row = 0; row < len; row += kRow) {
-                    float again[kBigPer];
-                    load_sweep(seg_score, row, len, again);
-                    count_sweep(row, len, again);
+            for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
+                const uint32_t cnt = (overflowed >> l) & 1ull ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
+                const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
+                for (uint32_t e = 0; e < cnt; e += kWave) {
+                    const uint32_t key = e + lane < cnt ? (uint32_t)(from[e + lane] >> 32) : 0u;
+                    light_hist_add(hist, (key - lowest) >> shift, e + lane < cnt && key - lowest <= width);
                 }
             }
+            through_overflowed(count_sweep);
             __syncthreads();
             find_bucket(hist, k_rem, wave_tot, found);
         }
@@ -1360,31 +1795,27 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     bool ties_apart = (uint32_t)k - k_rem + in_bin > limit;
     int n = (int)(ties_apart ? (uint32_t)k - k_rem : (uint32_t)k - k_rem + in_bin);
     uint64_t tie_lists = ~0ull;   // the lists whose ties are collected
-    if constexpr (LISTS) {
-        // Whole lists hold the ties as well, and lie in index order: those up to the one in which the k_rem-th tie lies are
-        // ranked with the rest, at most one list's more than k.
-        static_assert(kPickCap >= PRUNER_MAX_K + kListCap, "k and a list more fit");
-        if (ties_apart && overflowed == 0ull) {
-            for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
-                const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
-                const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
-                uint32_t ties = 0;
-                for (uint32_t e = 0; e < cnt; e += kWave) ties += (uint32_t)__popcll(__ballot(e + lane < cnt && (uint32_t)(from[e + lane] >> 32) == lowest));
-                if (lane == 0) hist[l] = ties;
-            }
-            __syncthreads();
-            const uint32_t upto = wave_inclusive_sum(lane < n_lists ? hist[lane] : 0u);
-            const int enough = __popcll(__ballot(upto < k_rem));   // the list of the k_rem-th tie
-            n += __builtin_amdgcn_readlane((int)upto, enough);
-            tie_lists = (2ull << enough) - 1ull;
-            ties_apart = false;
-            __syncthreads();
+    // Whole lists hold the ties as well, and lie in index order: those up to the one in which the k_rem-th tie lies are
+    // ranked with the rest, at most one list's more than k.
+    static_assert(kPickCap >= PRUNER_MAX_K + kListCap, "k and a list more fit");
+    if (ties_apart && overflowed == 0ull) {
+        for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
+            const uint64_t* from = reinterpret_cast<const List*>(&stage[b0 + l])->word;
+            uint32_t ties = 0;
+            for (uint32_t e = 0; e < cnt; e += kWave) ties += (uint32_t)__popcll(__ballot(e + lane < cnt && (uint32_t)(from[e + lane] >> 32) == lowest));
+            if (lane == 0) hist[l] = ties;
         }
+        __syncthreads();
+        const uint32_t upto = wave_inclusive_sum(lane < n_lists ? hist[lane] : 0u);
+        const int enough = __popcll(__ballot(upto < k_rem));   // the list of the k_rem-th tie
+        n += __builtin_amdgcn_readlane((int)upto, enough);
+        tie_lists = (2ull << enough) - 1ull;
+        ties_apart = false;
+        __syncthreads();
     }
     auto collected = [&](uint32_t key, bool with_ties) { return with_ties ? key >= lowest : key > lowest; };
-    if (LISTS && n == 0) {
-        // (nothing above the ties)
-    } else if constexpr (LISTS) {
+    if (n > 0) {
         for (int l = wave; l < n_lists; l += kBigThreads / kWave) {
             const bool with_ties = !ties_apart && ((tie_lists >> l) & 1ull) != 0ull;
             const uint32_t cnt = (overflowed >> l) & 1ull ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)my_count, l);
@@ -1419,121 +1850,16 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
                 if (at < (uint32_t)n) sel[slot(at)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + (uint32_t)i);
             }
         });
-    } else {
-        const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
-        uint64_t mask = 0;   // bit 4 g + e: entry e of group g is not below the threshold
-#pragma unroll
-        for (int g = 0; g < kGroups; ++g) {
-            if (g * 4 * kBigThreads < len) {
-                uint32_t four = 0;
-#pragma unroll
-                for (int e = 3; e >= 0; --e) four = 2 * four + (val[g][e] < t0 ? 0u : 1u);
-                if ((g + 1) * 4 * kBigThreads > len) {   // the segment's last groups
-                    const int i = group_begin(g), begun = i < last ? i : last, left = len - i;
-                    four = left <= 0 ? 0u : (four >> (i - begun)) & (left < 4 ? (1u << left) - 1u : 15u);
-                }
-                mask |= (uint64_t)four << (4 * g);
-            }
-        }
-        uint32_t at = reserve(&fill, (uint32_t)__popcll(mask));
-        while (mask) {
-            const int bit = __ffsll((unsigned long long)mask) - 1;
-            mask &= mask - 1;
-            if (at < (uint32_t)kPickCap) place[at] = (uint32_t)(group_begin(bit >> 2) + (bit & 3));
-            ++at;
-        }
     }
-    if constexpr (LISTS) {   // (lists that hold their span's k best have fewer words than the counts say)
-        __syncthreads();
-        n = fill < (uint32_t)n ? (int)fill : n;
-    }
+    __syncthreads();
+    n = fill < (uint32_t)n ? (int)fill : n;   // (lists that hold their span's k best have fewer words than the counts say)
     // spare words and those behind the last must read as "below everything"
     const int n_raw = n > 0 ? (int)slot((uint32_t)n - 1u) + 1 : 0;
     for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
         if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
     __syncthreads();
-    if constexpr (!LISTS) {
-        if (n > 0 && fill != (uint32_t)n) {
-            // The counts come from keys, the places from comparisons with a threshold: where these found more, there are NaN
-            // among the scores, and the places are collected again by key.
-            __syncthreads();
-            if (threadIdx.x == 0) fill = 0;
-            __syncthreads();
-#pragma unroll 1
-            for (int row = 0; row < len; row += kRow) {
-                float again[kBigPer];
-                load_sweep(seg_score, row, len, again);
-                uint32_t mask = 0;
-#pragma unroll
-                for (int j = 0; j < kBigPer; ++j) mask |= sweep_index(row, j) < len && collected(key_of(again[j]), !ties_apart) ? 1u << j : 0u;
-                uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
-                while (mask) {
-                    if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, __ffs(mask) - 1);
-                    mask &= mask - 1;
-                    ++at;
-                }
-            }
-            __syncthreads();
-        }
-        for (int e = threadIdx.x; e < n; e += kBigThreads) {
-            const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
-            sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
-        }
-        __syncthreads();
-    }
-    // The words are ranked in rounds of 64 per workgroup, or sorted, all of them by every workgroup of the segment, whatever costs
-    // less (see kSortFactor).
-    const int n_last = n - (int)((uint32_t)k - k_rem);   // the words of the last bin
-    const bool trim = n > k && n_last <= kTrimMax && pow2_at_least(n) > pow2_at_least(k);
-    const int rounds = (n + 64 * share - 1) / (64 * share);
-    if (SORT && rounds * n > kSortFactor * pow2_at_least(trim ? k : n)) {
-        if (trim) {
-            // the sort is half as long without those of the last bin that are not selected: their places go to what lies behind k
-            uint64_t* bin_word = reinterpret_cast<uint64_t*>(place);
-            uint16_t *bin_at = reinterpret_cast<uint16_t*>(place + 2 * kTrimMax), *hole = bin_at + kTrimMax;
-            static_assert(sizeof(place) >= kTrimMax * (sizeof(uint64_t) + 2 * sizeof(uint16_t)), "the lists fit");
-            __syncthreads();
-            if (threadIdx.x == 0) fill = 0;
-            __syncthreads();
-            for (int e = threadIdx.x; e < n; e += kBigThreads) {
-                const uint64_t w = sel[slot((uint32_t)e)];
-                if ((uint32_t)(w >> 32) - lowest <= width) {
-                    const uint32_t at = atomicAdd(&fill, 1u);
-                    if (at < (uint32_t)kTrimMax) bin_word[at] = w, bin_at[at] = (uint16_t)e;
-                }
-            }
-            __syncthreads();
-            if ((int)threadIdx.x < n_last) {
-                const uint64_t me = bin_word[threadIdx.x];
-                const int at = bin_at[threadIdx.x];
-                uint32_t better = 0;
-                for (int x = 0; x < n_last; ++x) better += bin_word[x] > me ? 1u : 0u;
-                if (better >= k_rem) {
-                    sel[slot((uint32_t)at)] = 0;
-                    if (at < k) hole[atomicAdd(&n_own, 1u)] = (uint16_t)at;
-                }
-            }
-            if (threadIdx.x == 0) fill = 0;
-            __syncthreads();
-            for (int e = k + (int)threadIdx.x; e < n; e += kBigThreads) {
-                const uint64_t w = sel[slot((uint32_t)e)];
-                if (w != 0ull) sel[slot(hole[atomicAdd(&fill, 1u)])] = w;
-            }
-            __syncthreads();
-            n = k;
-        }
-        const int rows = n < k ? n : k, per = (rows + share - 1) / share, lo = part * per < rows ? part * per : rows;   // each writes its part of the rows
-        finish_segment<kBigThreads>(sel, n, lo, lo + per < rows ? lo + per : rows, score, idx_out, val_out, s, seg.begin, seg.end, k);
-        n = 0;
-    }
+    write_collection<SORT>(sel, place, hist, &fill, &n_own, n, k, share, part, k_rem, lowest, width, true, score, idx_out, val_out, s, seg);
     const uint32_t behind = (uint32_t)k - k_rem;   // (ties apart: rows before theirs)
-    // (every workgroup has its own order of the words: a hash of the index decides who ranks a word)
-    for (int e = threadIdx.x; e < n; e += kBigThreads) {
-        const uint32_t h = (index_of(sel[slot((uint32_t)e)]) * 2654435761u) >> 16;
-        if ((int)(h % (uint32_t)share) == part) own[atomicAdd(&n_own, 1u)] = (uint16_t)e;
-    }
-    __syncthreads();
-    if (n > 0) rank_rows<kBigThreads>(sel, n, own, 0, 1, (int)n_own, hist, score, idx_out, val_out, s, seg.begin, seg.end, k);
     if (ties_apart && part == 0) {
         // ties, all of the key `lowest`, in index order: the tie of rank r owns row behind + r.  A wavefront takes 16 x 64
         // neighbouring entries; one exchange of the wavefronts' counts per sweep.
@@ -1568,7 +1894,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
 }
 
 struct Layout {
-    size_t segs, state, hist, stage, block_max, total;
+    size_t segs, state, hist, stage, max256, max64, max16, total;
     size_t stage_slots;
     int R;
 };
@@ -1588,7 +1914,7 @@ int64_t span_for(int64_t n, int32_t n_sg)
     return kRow * ((sweeps + 511) / 512);
 }
 
-// with_block_max: room for the largest key of every 256 entries (4 bytes per 256 entries: the one part that grows with n)
+// with_block_max: room for the largest key of every 16, 64 and 256 entries (the one part that grows with n, 21 bytes per 64 entries)
 Layout layout(int64_t n, int32_t n_sg, int32_t k, bool with_block_max)
 {
     (void)k;
@@ -1608,7 +1934,10 @@ Layout layout(int64_t n, int32_t n_sg, int32_t k, bool with_block_max)
     L.hist = take(((size_t)L.R + 2) * n_sg * kBins * sizeof(uint32_t));   // first digit in R copies, one each for the others
     L.stage = take(blocks * sizeof(Stage));
     L.stage_slots = blocks;
-    L.block_max = with_block_max ? take(((size_t)(n >> 8) + (size_t)n_sg + 1) * sizeof(uint32_t)) : 0;
+    // (three words more: the maxima are read in fours)
+    L.max256 = with_block_max ? take(((size_t)(n >> 8) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
+    L.max64 = with_block_max ? take(((size_t)(n >> 6) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
+    L.max16 = with_block_max ? take(((size_t)(n >> 4) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
     L.total = off;
     return L;
 }
@@ -1652,7 +1981,13 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
 
     char* ws = static_cast<char*>(workspace);
     SegT* d_segs = reinterpret_cast<SegT*>(ws + L.segs);
-    const bool tiny = longest <= kTinyMax && k <= kTinyK, pick = !tiny && longest <= kPickMax;
+    // (without room for maxima: as for a large k)
+    const bool tiny = longest <= kTinyMax && k <= kTinyK;
+    const bool levels = with_block_max && !tiny && longest > (defer ? kRow : kCountMax) && k <= kLevelK && longest <= kLevelMax;
+    const bool pick = !tiny && !levels && longest <= kPickMax;
+    // Segments of up to two rows are counted where they are held as cheaply as by a launch of its own (20 of 30,000, k = 4,096: 44 us
+    // either way), unless the draft kernel does it.
+    const bool counted = pick && longest > (defer ? kRow : kCountMax);
     const int64_t span = span_for(n, n_sg);
 
     // the segment table: on the stack when it is short (a call that must not allocate stays off the heap as well)
@@ -1665,11 +2000,14 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
         segs[s] = SegT{seg_off[s], seg_off[s + 1], (int32_t)blocks, 0};
         blocks += (seg_off[s + 1] - seg_off[s] + span - 1) / span;
     }
-    ctx->large = !tiny;
-    ctx->pick = pick;
     // (a population of copies, as the explorer loop keeps it, would have its lists overflow as a rule: it takes the spans route)
-    ctx->count = pick && longest <= kCountMax && !defer;
-    ctx->lists = !tiny && !pick && longest <= kListsMax && !copies;
+    const bool lists = !tiny && !pick && !levels && longest <= kListsMax && !copies;
+    ctx->tiny = tiny;
+    ctx->pick = pick;
+    ctx->levels = levels;
+    ctx->lists = lists;
+    ctx->digits = !tiny && !levels && (!pick || counted);
+    ctx->longest = longest;
     ctx->n_sg = n_sg;
     ctx->k = k;
     ctx->n = n;
@@ -1683,11 +2021,13 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     // Block maxima pay where nearly every block of 256 entries can be stepped over: at most one entry in 1024 selected
     // in the longest segment (with k = 512 of 50,000 nine blocks in ten hold a selected entry and the maxima are one
     // more read: 10.7 -> 11.5 us measured).
-    const bool sparse = !pick && !ctx->lists && longest >= (int64_t)k * 1024;
-    ctx->d_block_max = with_block_max && sparse ? reinterpret_cast<uint32_t*>(ws + L.block_max) : nullptr;
+    const bool sparse = ctx->digits && !pick && !lists && longest >= (int64_t)k * 1024;
+    ctx->d_max16 = levels ? reinterpret_cast<uint32_t*>(ws + L.max16) : nullptr;
+    ctx->d_max64 = levels && longest > 16 * (int64_t)kDirectBlocks ? reinterpret_cast<uint32_t*>(ws + L.max64) : nullptr;
+    ctx->d_max256 = with_block_max && (sparse || (levels && longest > 64 * (int64_t)kDirectBlocks)) ? reinterpret_cast<uint32_t*>(ws + L.max256) : nullptr;
     ctx->inline_ok = false;
     static_assert(sizeof(InlineSegs) <= sizeof(ctx->inline_segs), "inline segment table");
-    if (tiny || ctx->count) {
+    if (!ctx->digits) {
         if (n_sg <= kInlineSegs) {
             memset(ctx->inline_segs, 0, sizeof(InlineSegs));
             memcpy(ctx->inline_segs, segs, (size_t)n_sg * sizeof(SegT));
@@ -1715,22 +2055,19 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     return put_table(d_segs, segs, (size_t)n_sg * sizeof(SegT), st, ctx->d_hist, hist_bytes);
 }
 
-int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, int32_t* idx_out, float* val_out, bool have_first_digit,
+int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, int32_t* idx_out, float* val_out, bool noted,
                 hipStream_t st)
 {
     if (!score || !idx_out) return PRUNER_EINVAL;
     if (!aligned(score, 4) || !aligned(idx_out, 4) || (val_out && !aligned(val_out, 4))) return PRUNER_EINVAL;
     const int32_t n_sg = ctx.n_sg, k = ctx.k;
     const SegT* d_segs = static_cast<const SegT*>(ctx.d_segs);
-    if (!ctx.large) {
-        InlineSegs args;
-        memset(&args, 0, sizeof args);
-        if (ctx.inline_ok) {
-            memcpy(&args, ctx.inline_segs, sizeof args);
-            hipLaunchKernelGGL(topk_tiny_kernel<true>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
-        } else {
-            hipLaunchKernelGGL(topk_tiny_kernel<false>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, d_segs, args, k, idx_out, val_out);
-        }
+    const SegsInMemory in_memory{d_segs};
+    InlineSegs inl;
+    if (ctx.inline_ok) memcpy(&inl, ctx.inline_segs, sizeof inl);
+    if (ctx.tiny) {
+        if (ctx.inline_ok) hipLaunchKernelGGL(topk_tiny_kernel<InlineSegs>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, inl, k, idx_out, val_out);
+        else hipLaunchKernelGGL(topk_tiny_kernel<SegsInMemory>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, in_memory, k, idx_out, val_out);
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }
@@ -1743,18 +2080,23 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     if (share < 1) share = 1;
     const bool sort = (k + 64 * share - 1) / (64 * share) * k > kSortFactor * pow2_at_least(k);   // (a collection is k words and a little more)
     const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
-    const SegsInMemory in_memory{d_segs};
-    if (ctx.count && !have_first_digit) {
-        InlineSegs args;
-        memset(&args, 0, sizeof args);
-        if (ctx.inline_ok) {
-            memcpy(&args, ctx.inline_segs, sizeof args);
-            hipLaunchKernelGGL((sort ? pick_kernel<false, true, true, InlineSegs> : pick_kernel<false, true, false, InlineSegs>), pickers, dim3(kBigThreads), 0, st, score, args, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
-                               nullptr, nullptr, 0, idx_out, val_out);
-        } else {
-            hipLaunchKernelGGL((sort ? pick_kernel<false, true, true, SegsInMemory> : pick_kernel<false, true, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, 0, k, share, 0, nullptr, nullptr,
-                               nullptr, nullptr, 0, idx_out, val_out);
+#define PRUNER_PICK(LEVELS, TABLE, SEGS, GHIST, COPIES) \
+    hipLaunchKernelGGL((sort ? pick_kernel<LEVELS, true, TABLE> : pick_kernel<LEVELS, false, TABLE>), pickers, dim3(kBigThreads), 0, st, score, SEGS, n_sg, (int)ctx.n, k, share, (Maxima{ctx.d_max16, ctx.d_max64, ctx.d_max256}), GHIST, COPIES, idx_out, val_out)
+    if (ctx.levels) {
+        if (!noted) {
+            const dim3 grid((unsigned)((ctx.longest + 4095) / 4096), (unsigned)n_sg);
+            if (ctx.inline_ok) hipLaunchKernelGGL(maxima_kernel<InlineSegs>, grid, dim3(256), 0, st, score, inl, ctx.d_max16, ctx.d_max64, ctx.d_max256);
+            else hipLaunchKernelGGL(maxima_kernel<SegsInMemory>, grid, dim3(256), 0, st, score, in_memory, ctx.d_max16, ctx.d_max64, ctx.d_max256);
+            PRUNER_LAUNCH_CHECK();
         }
+        if (ctx.inline_ok) PRUNER_PICK(true, InlineSegs, inl, nullptr, 0);
+        else PRUNER_PICK(true, SegsInMemory, in_memory, nullptr, 0);
+        PRUNER_LAUNCH_CHECK();
+        return PRUNER_OK;
+    }
+    if (ctx.pick && !ctx.digits) {
+        if (ctx.inline_ok) PRUNER_PICK(false, InlineSegs, inl, nullptr, 0);
+        else PRUNER_PICK(false, SegsInMemory, in_memory, nullptr, 0);
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }
@@ -1767,21 +2109,22 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     uint32_t *hist0 = ctx.d_hist, *hist1 = ctx.d_hist + (size_t)R * per_pass, *hist2 = hist1 + per_pass;
     const dim3 chunks((unsigned)ctx.blocks);
     // (the draft kernel writes the block maxima when it counts the first digit)
-    uint32_t* const block_max = ctx.d_block_max;
-    if (!have_first_digit) {
+    uint32_t* const block_max = ctx.d_max256;
+    if (!noted) {
         hipLaunchKernelGGL(hist0_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, hist0, block_max);
         PRUNER_LAUNCH_CHECK();
     }
-    if (ctx.pick || ctx.lists) {
-        if (ctx.lists) {
-            hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, hist2, d_stage);
-            PRUNER_LAUNCH_CHECK();
-            hipLaunchKernelGGL((sort ? pick_kernel<true, false, true, SegsInMemory> : pick_kernel<true, false, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
-                               ctx.blocks, idx_out, val_out);
-        } else {
-            hipLaunchKernelGGL((sort ? pick_kernel<false, false, true, SegsInMemory> : pick_kernel<false, false, false, SegsInMemory>), pickers, dim3(kBigThreads), 0, st, score, in_memory, n_sg, (int)ctx.n, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
-                               ctx.blocks, idx_out, val_out);
-        }
+    if (ctx.pick) {
+        PRUNER_PICK(false, SegsInMemory, in_memory, hist0, R);
+        PRUNER_LAUNCH_CHECK();
+        return PRUNER_OK;
+    }
+#undef PRUNER_PICK
+    if (ctx.lists) {
+        hipLaunchKernelGGL(list_kernel, chunks, dim3(kBigThreads), 0, st, score, d_segs, n_sg, span, R, k, hist0, hist1, hist2, d_stage);
+        PRUNER_LAUNCH_CHECK();
+        hipLaunchKernelGGL((sort ? pick_lists_kernel<true> : pick_lists_kernel<false>), pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, R, k, share, (int)span, hist0, hist1, hist2, d_stage,
+                           ctx.blocks, idx_out, val_out);
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }

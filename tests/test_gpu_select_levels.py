@@ -1,0 +1,54 @@
+"""Selections by the largest keys of blocks of 16, 64 and 256 neighbours: segment lengths around those at which a level is added, short
+segments beside long ones, k from 1 to all blocks that are held, stretches of good entries, ties within and across blocks, NaN.
+Against the oracle's stable sort, and with the maxima left by the draft kernel against the two separate calls."""
+import numpy as np
+import pytest
+
+import workloads as w
+from test_gpu_parity import P, dev  # noqa: F401  (P is a fixture)
+from test_gpu_select_nan import by_bits, scores as with_nan
+from test_gpu_select_shapes import check, of
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
+@pytest.mark.parametrize("lens,ks", [([32769], [1, 64, 1023, 1024]), ([40001, 16384, 16385, 1024], [65, 1024]), ([262144, 70], [3, 70]), ([262145, 16400], [512, 1024]),
+                                     ([262161] * 3, [33]), ([1048576], [700]), ([1048577, 16385], [1, 1000]), ([33000] * 129, [100])])
+def test_edges_of_the_levels(P, kind, lens, ks):
+    rng = np.random.default_rng(len(kind) + len(lens))
+    seg = np.concatenate([[0], np.cumsum(lens)])
+    score = np.concatenate([of(kind, n, rng) for n in lens])
+    for k in ks:
+        check(P, score, seg, k)
+
+
+@pytest.mark.parametrize("kind", ["few of either sign", "many positive", "many negative", "payloads", "all one", "last key"])
+@pytest.mark.parametrize("lens", [[32769, 1100], [262145], [1048577]])
+def test_nan_among_the_blocks(P, kind, lens):
+    rng = np.random.default_rng(len(kind) + sum(lens))
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    score = np.concatenate([with_nan(kind, n, rng) for n in lens])
+    for k in (30, 1024):
+        idx, val = P.topk(dev(score), seg, k)
+        want = by_bits(score, seg, k)
+        assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), score.view(np.uint32)[want])
+
+
+CONV, GEMM, BATCHED = w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64)
+
+
+@pytest.mark.parametrize("sgs,lens,k", [([GEMM], [16384], 500), ([GEMM], [16385], 500), ([GEMM], [70003], 1024), ([GEMM, CONV], [20001, 30003], 33), ([GEMM, CONV, BATCHED], [16386, 50001, 3], 3),
+                                        ([GEMM, CONV, BATCHED], [300001, 200003, 120002], 700), ([CONV, GEMM], [1048580, 17001], 1000), ([CONV], [1048576], 64), ([GEMM], [40000], 4096),
+                                        ([CONV, GEMM, GEMM], [1700001, 900002, 50], 50)])
+def test_maxima_left_by_the_draft_kernel(P, sgs, lens, k):
+    """one candidate per thread and four, ends of segments inside a block, a population with few distinct scores (GEMM)"""
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    tiles = P.random_init(sgs, seg, max(w.n_slots(s) for s in sgs), 23)
+    for flags in (P.REFERENCE_ROUNDING, P.FUSED_ARITHMETIC):
+        score, idx, val = P.prior_filter(sgs, seg, tiles, k, flags=flags)
+        want, want_val = P.topk(score, seg, k)
+        assert torch.equal(idx, want) and torch.equal(val.view(torch.int32), want_val.view(torch.int32))
+        host = score.cpu().numpy()
+        assert np.array_equal(idx.cpu().numpy(), by_bits(host, seg, k))
