@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libpruner_hip.so")
-SOURCES = ("common.hip", "draft_score.hip", "topk.hip", "verify_mlp.hip", "prior_filter.hip", "lse.hip", "random_init.hip", "moa.hip", "pacm.hip")
+SOURCES = ("common.hip", "draft_score.hip", "draft_score.hip:1", "draft_score.hip:2", "topk.hip", "verify_mlp.hip", "prior_filter.hip", "lse.hip", "random_init.hip", "moa.hip", "pacm.hip")
 
 # -packed-fp32-ops off: no v_pk_*_f32.  Contraction off and correctly rounded division: the draft model's
 # binary32 sequence is one IEEE operation per step.  MFMA accumulators in ordinary vector registers (the weights
@@ -28,10 +28,11 @@ def build(verbose=False, keep_temps=False):
     os.makedirs(objdir, exist_ok=True)
     procs = []
     objs = []
-    for src in SOURCES:
-        obj = os.path.join(objdir, src.replace(".hip", ".o"))
+    for entry in SOURCES:
+        src, _, part = entry.partition(":")   # (a source with many kernels is compiled in parts, side by side)
+        obj = os.path.join(objdir, src.replace(".hip", f"{part}.o"))
         objs.append(obj)
-        cmd = [hipcc, *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc, *FLAGS, f"-DPRUNER_DRAFT_PART={part or 0}", "-c", os.path.join(CSRC, src), "-o", obj]
         if keep_temps:
             cmd += ["-save-temps=obj"]
         if verbose:

@@ -21,6 +21,8 @@
 //         P2m = S7 / (ceil(S7 / n_l2) * n_l2);  Um = ((T_m * P0m) * P1m) * P2m;  L = L + S5 / Um
 //     score = -L
 //   integer-to-float conversions round to nearest even.  Quotients are correctly rounded (see div_rn).
+// Compiled three times, side by side, since there are many kernels: PRUNER_DRAFT_PART 0 holds the host code and the kernels of
+// analyze(), 1 those of analyze_fused(), 2 the ones that write the symbols.
 #include "lse_child.h"
 #include "select_common.h"
 #include "wide_load.h"
@@ -130,8 +132,6 @@ struct alignas(8) SegEnt {
 };
 
 constexpr int kTabMax = 4096;   // longest run length the P_l2,m table covers
-constexpr int64_t kRaggedMin = 1 << 19;   // candidates from which a population that is not laid out in fours is loaded in fours all the same
-constexpr int64_t kPerClassMin = 1 << 20;   // candidates from which a call launches one kernel per loop-nest class
 
 // ---- symbols (Table 2) ---------------------------------------------------------------------------------------------
 
@@ -445,18 +445,18 @@ struct MutSeg {
     int32_t sub, count;   // count < 1: the subgraph has no S_spec, its population stays as it is
 };
 
-template <class Nest, int NP>
+template <class Nest, int VEC, int NP>
 __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& ms, const MutArgs& mut, uint16_t* __restrict__ tiles,
-                                                 int64_t pitch, int64_t c0, int64_t c_end, RawTiles<Nest, 4>& raw)
+                                                 int64_t pitch, int64_t c0, int64_t c_end, RawTiles<Nest, VEC>& raw)
 {
     constexpr int NSP = Nest::NSP, NRD = Nest::NRD;
     constexpr int kRows = 8 * NP < PRUNER_MAX_SLOTS ? 8 * NP : PRUNER_MAX_SLOTS;
-    const int live = c_end - c0 < 4 ? (int)(c_end - c0) : 4;
+    const int live = c_end - c0 < VEC ? (int)(c_end - c0) : VEC;
     const uint64_t z0 = lse_child_state(mut.seed, mut.step, c0);
-    uint32_t f[4][kAosWords];
+    uint32_t f[VEC][kAosWords];
     lse_child<NP>(ms.seg, ms.sub, ms.count, mut.k, z0, mut.spec_aos, mut.mutate_q16, f[0]);
 #pragma unroll
-    for (int e = 1; e < 4; ++e) {
+    for (int e = 1; e < VEC; ++e) {
         if (e < live) {
             lse_child<NP>(ms.seg, ms.sub, ms.count, mut.k, z0 + (uint64_t)(2 * e) * kGamma, mut.spec_aos, mut.mutate_q16, f[e]);
         } else {
@@ -467,7 +467,7 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
     }
     if (mut.child_aos) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int e = 0; e < VEC; ++e) {
             if (e < live) {
 #pragma unroll
                 for (int q = 0; q < NP; ++q)
@@ -475,16 +475,19 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
             }
         }
     }
-    // row by row: the factor of each of the four children, as a column load would deliver it
-    u32x2 T[kAosSlots];
+    // row by row: the factor of each of the children, as a column load would deliver it
+    typedef typename Packed<VEC>::type Column;
+    Column T[kAosSlots];
 #pragma unroll
     for (int row = 0; row < kAosSlots; ++row) {
-        if (row < kRows) {
+        T[row] = Column{};
+        if (row >= kRows) continue;
+        uint16_t* dst = tiles + (int64_t)row * pitch + c0;
+        if constexpr (VEC == 4) {
             const uint32_t half = row & 1 ? 0x07060302u : 0x05040100u;
             T[row].x = __builtin_amdgcn_perm(f[1][row >> 1], f[0][row >> 1], half);
             T[row].y = __builtin_amdgcn_perm(f[3][row >> 1], f[2][row >> 1], half);
             if (row < ms.seg.n_slots) {
-                uint16_t* dst = tiles + (int64_t)row * pitch + c0;
                 if (live == 4) {
                     *reinterpret_cast<u32x2_a2*>(dst) = T[row];
                 } else {
@@ -494,7 +497,8 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
                 }
             }
         } else {
-            T[row] = u32x2{0u, 0u};
+            T[row] = (f[0][row >> 1] >> (16 * (row & 1))) & 0xFFFFu;
+            if (row < ms.seg.n_slots) dst[0] = (uint16_t)T[row];
         }
     }
 #pragma unroll
@@ -504,7 +508,7 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
             if (Nest::FIXED || a < d.n_sp) raw.sp[a][l] = T[a * 4 + l];
     }
     // the reduction slots follow the spatial ones: at a row that depends on the number of spatial axes and of levels
-    u32x2 U[NRD * 3];
+    Column U[NRD * 3];
 #pragma unroll
     for (int i = 0; i < NRD * 3; ++i) {
         if constexpr (Nest::FIXED) {
@@ -525,16 +529,16 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
     }
 }
 
-template <class Nest>
+template <class Nest, int VEC>
 __device__ __forceinline__ void make_children(const SgDesc& d, const MutSeg& ms, const MutArgs& mut, uint16_t* __restrict__ tiles, int64_t pitch,
-                                              int64_t c0, int64_t c_end, RawTiles<Nest, 4>& raw)
+                                              int64_t c0, int64_t c_end, RawTiles<Nest, VEC>& raw)
 {
     switch ((ms.seg.n_slots + 7) >> 3) {   // the same for the whole workgroup
         case 0:
-        case 1: make_children_np<Nest, 1>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
-        case 2: make_children_np<Nest, 2>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
-        case 3: make_children_np<Nest, 3>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
-        default: make_children_np<Nest, 4>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
+        case 1: make_children_np<Nest, VEC, 1>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
+        case 2: make_children_np<Nest, VEC, 2>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
+        case 3: make_children_np<Nest, VEC, 3>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
+        default: make_children_np<Nest, VEC, 4>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
     }
 }
 
@@ -977,7 +981,6 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
     auto inside = [&](int64_t c) { return load_begin<VEC>(c, n_total); };
     int64_t c0 = seg.begin + ((int64_t)(b - seg.first_block) * kBlock + threadIdx.x) * VEC;
     if constexpr (MUT) {
-        static_assert(VEC == 4, "children are made four at a time");
         MutSeg ms;
         ms.seg = mut.segs[seg.seg];
         ms.sub = seg.seg;
@@ -987,7 +990,7 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
             uint16_t* out = const_cast<uint16_t*>(tiles);
             for (int it = 0; it < seg.iters; ++it) {
                 if (c0 < seg.end) {
-                    make_children<Nest>(d, ms, mut, out, pitch, c0, seg.end, cur);
+                    make_children<Nest, VEC>(d, ms, mut, out, pitch, c0, seg.end, cur);
                     score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, c0, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
                 }
                 c0 += step;
@@ -1117,6 +1120,8 @@ template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, b
             if (vec == 1 && hist) return draft_kernel<CLS, 1, false, EXACT, true, false>;
         }
         if (vec == 1) return draft_kernel<CLS, 1, DUMP, EXACT, false, false>;
+    } else if constexpr (!DUMP && CLS >= kGeneric) {
+        if (vec == 1) return mut ? draft_kernel<CLS, 1, false, EXACT, true, true> : draft_kernel<CLS, 1, false, EXACT, false, false>;
     }
     if constexpr (!DUMP) {
         if constexpr (CLS != kAnyClass) {
@@ -1141,11 +1146,32 @@ template <bool DUMP, bool EXACT> DraftFn pick_class(int cls, int vec, bool hist,
         default: return pick_vec<kAnyClass, DUMP, EXACT>(vec, hist, mut);
     }
 }
-// mut is honoured for the per-class kernels with four candidates per thread (they count the first selection digit if asked to)
-DraftFn pick_kernel(int cls, int vec, bool dump, bool exact, bool hist, bool mut)
+}  // namespace
+
+// mut is honoured for the per-class kernels (they count the first selection digit if asked to)
+#if PRUNER_DRAFT_PART == 1
+const void* fused_draft_kernel(int cls, int vec, bool hist, bool mut) { return reinterpret_cast<const void*>(pick_class<false, false>(cls, vec, hist, mut)); }
+}  // namespace pruner
+#elif PRUNER_DRAFT_PART == 2
+const void* dumping_draft_kernel(int cls, int vec, bool exact)
 {
-    if (dump) return exact ? pick_class<true, true>(cls, vec, hist, mut) : pick_class<true, false>(cls, vec, hist, mut);
-    return exact ? pick_class<false, true>(cls, vec, hist, mut) : pick_class<false, false>(cls, vec, hist, mut);
+    return reinterpret_cast<const void*>(exact ? pick_class<true, true>(cls, vec, false, false) : pick_class<true, false>(cls, vec, false, false));
+}
+}  // namespace pruner
+#else
+const void* fused_draft_kernel(int cls, int vec, bool hist, bool mut);
+const void* dumping_draft_kernel(int cls, int vec, bool exact);
+
+namespace {
+
+constexpr int64_t kRaggedMin = 1 << 19;   // candidates from which a population that is not laid out in fours is loaded in fours all the same
+constexpr int64_t kSpreadMax = 1 << 18;   // candidates up to which those of one class are scored one to a thread
+constexpr int64_t kPerClassMin = 1 << 20;   // candidates from which a call launches one kernel per loop-nest class
+
+const void* draft_kernel_for(int cls, int vec, bool dump, bool exact, bool hist, bool mut)
+{
+    if (dump) return dumping_draft_kernel(cls, vec, exact);
+    return exact ? reinterpret_cast<const void*>(pick_class<false, true>(cls, vec, hist, mut)) : fused_draft_kernel(cls, vec, hist, mut);
 }
 
 // Workgroups of a kernel instance that the device holds at once (its register budget decides).  Asked of the runtime
@@ -1491,7 +1517,12 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // Several classes in a population that is neither large nor laid out in fours: candidates one by one, four times the threads,
     // for the kernel that branches on the class is short of them (6 x 3,001, k = 6: 20.2 -> 17.6 us; 400,020: 23.0 -> 20.7;
     // 900,020: no difference).  (Maxima of 256 neighbours need fours, and so do kernels that make their candidates.)
-    const int vec = mut || notes.max256 || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
+    // One class (two where the kernels make their candidates) and few candidates: one by one, on four times the compute units, a
+    // thread's chain of divisions a quarter as long (reading: 4,096 GEMM candidates 5.8 -> 5.0 us, 65,536 of a convolution 7.4 -> 5.8,
+    // 262,144 7.7 -> 7.0; making: 8,000 10.6 -> 5.6, 65,536 13.2 -> 7.7, 262,144 13.8 -> 11.8; at 400,000 a tenth less as well, but
+    // the maxima of 256 neighbours want fours).
+    const bool spread = n <= kSpreadMax && n_classes <= (mut ? 2 : 1) && !notes.max256 && !notes.first_digit && !symbols;
+    const int vec = spread ? 1 : mut || notes.max256 || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
 
     // Launch plan.  With four candidates per thread: one launch per loop-nest class present, the table grouped by class, when the
     // population is large (with more than two classes: 2^20 candidates for each, since every launch begins and ends with a
@@ -1508,7 +1539,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     std::vector<int32_t> order(n_sg);
     for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
     const bool large = vec == 4 && n >= kPerClassMin;
-    const bool by_class = vec == 4 && ((large && (mut || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (mut ? 2 : 1));
+    const bool by_class = spread || (vec == 4 && ((large && (mut || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (mut ? 2 : 1)));
     if (by_class && n_classes > 1) {   // (a pass per class: sorting a thousand segments of one class took 14 us of host time)
         order.clear();
         for (uint32_t left = classes; left; left &= left - 1)
@@ -1528,8 +1559,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
         const int32_t s = order[i];
         const int cls = by_class ? descs[desc_of[s]].cls : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : kClosedForms;
         if (out->launches.empty() || out->launches.back().cls != cls) {
-            out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, fused)),
-                                                      reinterpret_cast<const void*>(pick_kernel(cls, vec, symbols != nullptr, exact, hist, false))});
+            out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, fused), draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, false)});
             chunks_of.push_back(0);
         }
         DraftPlan::Launch& L = out->launches.back();
@@ -1650,3 +1680,4 @@ extern "C" int pruner_time_dominant_draft_launch(void* start_event, void* stop_e
 namespace pruner {
 size_t draft_workspace_bytes(int32_t n_sg) { return table_bytes(n_sg < 1 ? 1 : n_sg); }
 }
+#endif  // PRUNER_DRAFT_PART

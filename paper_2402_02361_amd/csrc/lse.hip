@@ -777,6 +777,7 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
     return L;
 }
 
+constexpr int64_t kSpreadChildren = 1 << 17;   // children up to which a launch makes one per thread (8,000: 6.3 -> 4.0 us)
 constexpr int kMostGroups = 8;        // of 64 entries per workgroup of the rank kernel
 constexpr int kManyUniters = 2048;   // workgroups of 64 places: four times what the device holds at once
 
@@ -838,7 +839,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
                           Spec{words(L.keys[1]), words(L.keys[1]) + spec_pitch, reinterpret_cast<uint4*>(ws + L.aos_b), reinterpret_cast<int32_t*>(ws + L.alt_count)}};
 
     auto mutate = [&](int32_t t, const int32_t* count, const uint4* records) {   // SchMutation of step t, in place (parents come from S_spec, not from S_x)
-        if (tiles_pitch % 4 == 0 && aligned(tiles, 8))
+        if (n > kSpreadChildren && tiles_pitch % 4 == 0 && aligned(tiles, 8))   // (few: one to a thread, on four times the compute units; 8,000: 6.3 -> 4.0 us)
             hipLaunchKernelGGL(lse_mutate_kernel<4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, d_table, n_sg, k, n, tiles, tiles_pitch,
                                records, count, seed, (uint64_t)t, mutate_q16);
         else

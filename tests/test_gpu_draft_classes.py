@@ -52,3 +52,14 @@ def test_tables_that_fit_a_launch_and_tables_that_do_not(P, n_sg):
     for t, sg in enumerate(sgs):
         alone = P.draft_score([sg], [0, int(seg[t + 1] - seg[t])], tiles[:, int(seg[t]):int(seg[t + 1])].contiguous())
         assert torch.equal(alone.view(torch.int32), score[int(seg[t]):int(seg[t + 1])].view(torch.int32))
+
+
+@pytest.mark.parametrize("sg", CLOSED + [GENERIC])
+@pytest.mark.parametrize("n", [1, 63, 65, 1025, 262144, 262145])
+def test_one_candidate_per_thread_and_four(P, sg, n):
+    """a class's own kernel at either width: the symbol dump's launch has four to a thread at any size"""
+    tiles = P.random_init([sg], [0, n], w.n_slots(sg), 31)
+    for flags in (0, P.FUSED_ARITHMETIC, P.REFERENCE_ROUNDING | P.NO_MEMORY_PENALTY):
+        score = P.draft_score([sg], [0, n], tiles, flags=flags)
+        dumped, _ = P.draft_score([sg], [0, n], tiles, flags=flags, symbols=True)
+        assert torch.equal(score.view(torch.int32), dumped.view(torch.int32))
