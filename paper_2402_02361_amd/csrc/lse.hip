@@ -325,8 +325,11 @@ template <int PER> __global__ void __launch_bounds__(kLseThreads) lse_unite_kern
 //      place in its run plus, by bisection, the greater ones in the other;
 //   3. the union with the old S_spec, whose keys come in order from the step before, every place found by bisection; every thread then
 //      writes the record it holds to the record's new place.
-// Bound: the latency of these dependent stages (a compute unit works alone on a subgraph).  8,000 entries, k = 512: 23 us
+// Bound: the latency of these dependent stages (a compute unit works alone on a subgraph).  8,000 entries, k = 512: 22 us
+// (loads 2.5, the range of the keys 1.3, histograms 3.4, taking 2.5, records 1.5, hashes 1, sorting 1.5 and merging 2.8, the union 3.6)
 // where selection (26), keys (9), merge (18) and copy (7) took 60 in four launches.
+
+struct alignas(16) Sorted { uint64_t hi, lo; };   // a sort key
 
 constexpr int kShortPer = 32;
 constexpr int kShortMax = kLseThreads * kShortPer;   // entries of a segment
@@ -343,16 +346,19 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
                                                                  float* __restrict__ spec_score, int32_t* __restrict__ spec_count)
 {
     __shared__ uint32_t hist[kBins];                 // later: which entry holds each place of the union, and its rank in the new S_spec
-    __shared__ __attribute__((aligned(16))) uint64_t list_hi[2 * kShortK], list_lo[2 * kShortK];   // the chosen entries: sorted runs, merged from one half into the other (list_hi
-                                                                       // first holds the chosen words, list_lo the words of rank k's bin)
-    __shared__ uint64_t old_hi[kShortK], old_lo[kShortK];
+    __shared__ Sorted list[2 * kShortK];             // the chosen entries: sorted runs, merged from one half into the other (first: the chosen entries' places
+                                                     // in the segment, in the other half the words of rank k's bin)
+    __shared__ Sorted old_list[kShortK];
     __shared__ __attribute__((aligned(16))) uint16_t record[kShortK * kAosSlots];   // the chosen entries' schedules
     __shared__ uint32_t wave_tot[16], found[3], low_of[16], high_of[16];
     __shared__ uint32_t fill, bin_fill, bin_rank[kShortBin];
+    uint32_t* const chosen_at = reinterpret_cast<uint32_t*>(list);
+    uint64_t* const bin_word = reinterpret_cast<uint64_t*>(list + kShortK);
     uint16_t* who = reinterpret_cast<uint16_t*>(hist);
     uint16_t* rank_of = who + 2 * kShortK;
     static_assert(sizeof(hist) >= 4 * kShortK * sizeof(uint16_t), "places and ranks of the union's 2 k entries");
     const int s = blockIdx.x, tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
+    int n_old = first ? 0 : before.count[s];   // (asked for at once with the segment)
     const LseSeg seg = segs[s];
     const int len = (int)(seg.end - seg.begin);
     const int64_t col0 = (int64_t)s * k;
@@ -368,7 +374,6 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
     const bool side_by_side = k <= kLseThreads / 2;
     const int old_at = side_by_side ? tid - kLseThreads / 2 : tid;
     // the old S_spec travels meanwhile
-    int n_old = first ? 0 : before.count[s];
     n_old = n_old < 0 ? 0 : n_old > k ? k : n_old;
     uint64_t oh = 0, ol = 0;
     uint4 old_rec[kAosSlots / 8];
@@ -425,9 +430,33 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
         width = (1u << shift) - 1u;
         k_rem = found[1];
         in_bin = found[2];
-        __syncthreads();
         if (shift == 0 || in_bin == k_rem || in_bin <= (uint32_t)kShortBin) break;
+        // the keys that the bin holds: one value is as much as another pass would find, and shared scores are what fills bins
+        uint32_t most = 0, not_least = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const bool in = key[j] != 0u && key[j] - lo_key <= width;
+            most = in && key[j] > most ? key[j] : most;
+            not_least = in && ~key[j] > not_least ? ~key[j] : not_least;
+        }
+        most = wave_inclusive_max(most);
+        not_least = wave_inclusive_max(not_least);
+        if (lane == kWave - 1) {
+            high_of[wave] = most;
+            low_of[wave] = not_least;
+        }
+        __syncthreads();
+        most = not_least = 0;
+#pragma unroll
+        for (int w = 0; w < kLseThreads / kWave; ++w) {
+            most = high_of[w] > most ? high_of[w] : most;
+            not_least = low_of[w] > not_least ? low_of[w] : not_least;
+        }
+        lo_key = ~not_least;
+        width = most - lo_key;
+        if (width == 0u) break;
     }
+    __syncthreads();
     // entries above the bin are taken; of the bin's all, or the best k_rem: by rank among a few, or (ties) in index order
     const bool all = in_bin == k_rem, few = !all && in_bin <= (uint32_t)kShortBin, ties = !all && !few;
     if (ties) {
@@ -468,33 +497,30 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
         }
         uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)base, kWave - 1) + ((upto - mine) & 0xFFFFu);
         uint32_t at_few = (uint32_t)__builtin_amdgcn_readlane((int)few_base, kWave - 1) + ((upto - mine) >> 16);
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const uint32_t i = (uint32_t)(j * kLseThreads + tid);
-            if ((take >> j) & 1u) {
-                if (at < (uint32_t)k) list_hi[at] = compose(key[j], i);
-                ++at;
-            }
-            if ((in_few >> j) & 1u) {
-                if (at_few < (uint32_t)kShortBin) list_lo[at_few] = compose(key[j], i);
-                ++at_few;
-            }
+        // (places only: stores of keys out of the registers, each under a condition, are longer code)
+#pragma unroll 1
+        for (; take; take &= take - 1u, ++at)
+            if (at < (uint32_t)k) chosen_at[at] = (uint32_t)((__ffs((int)take) - 1) * kLseThreads + tid);
+#pragma unroll 1
+        for (; in_few; in_few &= in_few - 1u, ++at_few) {
+            const uint32_t i = (uint32_t)((__ffs((int)in_few) - 1) * kLseThreads + tid);
+            if (at_few < (uint32_t)kShortBin) bin_word[at_few] = compose(key_of(score[seg.begin + i]), i);
         }
     }
     __syncthreads();
     if (few) {
         const int n_bin = (int)in_bin, e = tid & (kShortBin - 1), quarter = tid / kShortBin;
         static_assert(kLseThreads == 4 * kShortBin, "four threads count for an entry");
-        const uint64_t me = e < n_bin ? list_lo[e] : ~0ull;
+        const uint64_t me = e < n_bin ? bin_word[e] : ~0ull;
         uint32_t greater = 0;
         const int per = (n_bin + 3) >> 2, from = quarter * per, to = from + per < n_bin ? from + per : n_bin;
 #pragma unroll 4
-        for (int x = from; x < to; ++x) greater += list_lo[x] > me ? 1u : 0u;
+        for (int x = from; x < to; ++x) greater += bin_word[x] > me ? 1u : 0u;
         if (e < n_bin && greater) atomicAdd(&bin_rank[e], greater);
         __syncthreads();
         if (tid < n_bin && bin_rank[tid] < k_rem) {
             const uint32_t at = atomicAdd(&fill, 1u);
-            if (at < (uint32_t)k) list_hi[at] = me;
+            if (at < (uint32_t)k) chosen_at[at] = index_of(me);
         }
         __syncthreads();
     }
@@ -504,8 +530,8 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
     uint64_t nh = 0, nl = 0;
     const bool has_new = tid < k;
     if (has_new) {
-        const uint64_t w = list_hi[tid];
-        const uint32_t i = index_of(w) < (uint32_t)len ? index_of(w) : 0u;   // (always inside the segment)
+        const uint32_t i = chosen_at[tid] < (uint32_t)len ? chosen_at[tid] : 0u;   // (always inside the segment)
+        const float its_score = score[seg.begin + i];
         uint16_t* rec = record + tid * kAosSlots;
         if (child_aos) {
             const uint4* from = child_aos + (seg.begin + i) * (kAosSlots / 8);
@@ -534,63 +560,66 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
 #pragma unroll 1
         for (int r = 0; r < seg.n_slots; ++r) h = splitmix64_draw(h, (uint64_t)rec[r] + 1);
         const uint64_t inv = ~h;
-        nh = (w & 0xFFFFFFFF00000000ull) | (inv >> 32);
-        nl = (inv << 32) | (uint64_t)(0xFFFFFFFFu - ((uint32_t)k + i));   // younger than S_spec's members, then by index
+        nh = ((uint64_t)key_of(its_score) << 32) | (inv >> 32);
+        // younger than S_spec's members, then by index; and which thread holds the record
+        static_assert(((uint64_t)(kShortK + kShortMax) << 10) < (1ull << 32) && kLseThreads <= 1024, "an age and a thread in 32 bits");
+        nl = (inv << 32) | (uint64_t)(0xFFFFFFFFu - ((((uint32_t)k + i) << 10) | (uint32_t)tid));
     }
-    if (has_old) {
-        old_hi[old_at] = oh;
-        old_lo[old_at] = ol;
-    }
+    if (has_old) old_list[old_at] = Sorted{oh, ol};
     int sorted = kWave;   // 64 or the power of two at or above k
     while (sorted < k) sorted <<= 1;
     if (!has_new) nl = (uint64_t)tid;   // fillers: behind every entry (no entry has hi = 0), and distinct
-    __syncthreads();   // the chosen words have been read
+    __syncthreads();   // the chosen places have been read
+    // From here on thread t has the entry that the sort of its wavefront brings it.
     if (tid < sorted) {
-        uint64_t sh = nh, sl = nl;
-        wave_sort_descending(sh, sl);
-        list_hi[tid] = sh;
-        list_lo[tid] = sl;
+        wave_sort_descending(nh, nl);
+        list[tid] = Sorted{nh, nl};
     }
     __syncthreads();
-    // entries of a run of n that are greater than (xh, xl)
-    auto greater_in = [](const uint64_t* hi, const uint64_t* lo, int n, uint64_t xh, uint64_t xl) {
-        int a = 0;
+    // entries of a run of n that are greater than (xh, xl): the run in quarters, three looks at a time
+    auto greater_in = [](const Sorted* run, int n, uint64_t xh, uint64_t xl) {
+        int a = 0, size = n > 1 ? 1 << (32 - __clz(n - 1)) : 1;   // a power of two at or above n
 #pragma unroll 1
-        for (int step = 1 << (31 - __clz(n | 1)); step > 0; step >>= 1) {
-            const bool there = a + step <= n;
-            const int at = there ? a + step - 1 : 0;
-            a += there && key_greater(hi[at], lo[at], xh, xl) ? step : 0;
+        for (; size >= 4; size >>= 2) {
+            const int q = size >> 2;
+            Sorted at[3];
+            int past = 0;
+#pragma unroll
+            for (int i = 0; i < 3; ++i) at[i] = run[a + (i + 1) * q - 1 < n ? a + (i + 1) * q - 1 : 0];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) past += a + (i + 1) * q <= n && key_greater(at[i].hi, at[i].lo, xh, xl) ? 1 : 0;
+            a += past * q;
         }
+        if (size == 2) a += a < n && key_greater(run[a].hi, run[a].lo, xh, xl) ? 1 : 0;
+        if (a < n && key_greater(run[a].hi, run[a].lo, xh, xl)) ++a;
         return a;
     };
-    int rank = 0, from = 0;   // the entry's place in its run; the half of the lists that holds the runs
-    if (tid < sorted) rank = greater_in(list_hi + 64 * wave, list_lo + 64 * wave, kWave, nh, nl);
+    int rank = lane, from = 0;   // the entry's place in its run; the half of the lists that holds the runs
 #pragma unroll 1
     for (int run = kWave; run < sorted; run *= 2) {
         if (tid < sorted) {
-            const int other = from + ((tid & ~(run - 1)) ^ run);
-            rank += greater_in(list_hi + other, list_lo + other, run, nh, nl);
-            const int to = (from ^ kShortK) + (tid & ~(2 * run - 1)) + rank;
-            list_hi[to] = nh;
-            list_lo[to] = nl;
+            rank += greater_in(list + from + ((tid & ~(run - 1)) ^ run), run, nh, nl);
+            list[(from ^ kShortK) + (tid & ~(2 * run - 1)) + rank] = Sorted{nh, nl};
         }
         from ^= kShortK;
         __syncthreads();
     }
-    const uint64_t *new_hi = list_hi + from, *new_lo = list_lo + from;   // all chosen entries in order
+    const Sorted* new_list = list + from;   // all chosen entries in order
+    const bool is_new = nh != 0ull;         // (not a filler)
+    const int holder = (int)((0xFFFFFFFFu - (uint32_t)nl) & 1023u);   // of the entry's record
 
     // 3. places in the union (all 128-bit keys differ: they carry the age): one's own rank and the greater ones of the other list
     int place_new = 0, place_old = 0;
     if (side_by_side) {
         const bool mine_new = tid < kLseThreads / 2;
-        const int greater = greater_in(mine_new ? old_hi : new_hi, mine_new ? old_lo : new_lo, mine_new ? n_old : k, mine_new ? nh : oh, mine_new ? nl : ol);
+        const int greater = greater_in(mine_new ? old_list : new_list, mine_new ? n_old : k, mine_new ? nh : oh, mine_new ? nl : ol);
         place_new = rank + greater;
         place_old = old_at + greater;
     } else {
-        place_new = rank + greater_in(old_hi, old_lo, n_old, nh, nl);
-        place_old = old_at + greater_in(new_hi, new_lo, k, oh, ol);
+        place_new = rank + greater_in(old_list, n_old, nh, nl);
+        place_old = old_at + greater_in(new_list, k, oh, ol);
     }
-    if (has_new) who[place_new] = (uint16_t)(kShortK + rank);
+    if (is_new) who[place_new] = (uint16_t)(kShortK + rank);
     if (has_old) who[place_old] = (uint16_t)old_at;
     __syncthreads();
     const int m = n_old + k;
@@ -603,8 +632,9 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
             uint64_t xh = 0, xl = 0;
             if (at >= 0 && at < m) {
                 const int id = who[at];
-                xh = id < kShortK ? old_hi[id] : new_hi[id - kShortK];
-                xl = id < kShortK ? old_lo[id] : new_lo[id - kShortK];
+                const Sorted x = id < kShortK ? old_list[id] : new_list[id - kShortK];
+                xh = x.hi;
+                xl = x.lo;
             }
             // a copy has the key and the hash of its predecessor
             if (j >= 0 && at < m && !(at > 0 && xh == ph && (xl >> 32) == (pl >> 32))) keep |= 1u << j;
@@ -637,7 +667,7 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
             }
         }
     };
-    const int r_new = has_new ? (int)rank_of[place_new] : 0xFFFF, r_old = has_old ? (int)rank_of[place_old] : 0xFFFF;
+    const int r_new = is_new ? (int)rank_of[place_new] : 0xFFFF, r_old = has_old ? (int)rank_of[place_old] : 0xFFFF;
 #pragma unroll 1
     for (int turn = side_by_side ? 1 : 0; turn < 2; ++turn) {   // (side by side a thread has one of the two)
         const bool mine_new = side_by_side ? tid < kLseThreads / 2 : turn == 0;
@@ -645,7 +675,7 @@ __global__ void __launch_bounds__(kLseThreads) lse_select_kernel(const LseSeg* _
         uint4 w[kAosSlots / 8];
 #pragma unroll
         for (int q = 0; q < kAosSlots / 8; ++q) {
-            const uint4 mine = *reinterpret_cast<const uint4*>(record + tid * kAosSlots + 8 * q);
+            const uint4 mine = *reinterpret_cast<const uint4*>(record + holder * kAosSlots + 8 * q);
             w[q] = make_uint4(mine_new ? mine.x : old_rec[q].x, mine_new ? mine.y : old_rec[q].y, mine_new ? mine.z : old_rec[q].z, mine_new ? mine.w : old_rec[q].w);
         }
         if (r != 0xFFFF) write(r, mine_new ? nh : oh, mine_new ? nl : ol, w);
@@ -839,7 +869,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
                           Spec{words(L.keys[1]), words(L.keys[1]) + spec_pitch, reinterpret_cast<uint4*>(ws + L.aos_b), reinterpret_cast<int32_t*>(ws + L.alt_count)}};
 
     auto mutate = [&](int32_t t, const int32_t* count, const uint4* records) {   // SchMutation of step t, in place (parents come from S_spec, not from S_x)
-        if (n > kSpreadChildren && tiles_pitch % 4 == 0 && aligned(tiles, 8))   // (few: one to a thread, on four times the compute units; 8,000: 6.3 -> 4.0 us)
+        if (n > kSpreadChildren && tiles_pitch % 4 == 0 && aligned(tiles, 8))   // (few: one to a thread, on four times the compute units)
             hipLaunchKernelGGL(lse_mutate_kernel<4>, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, d_table, n_sg, k, n, tiles, tiles_pitch,
                                records, count, seed, (uint64_t)t, mutate_q16);
         else
