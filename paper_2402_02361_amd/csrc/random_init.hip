@@ -9,7 +9,8 @@
 // first) and C_i = binom(e_i + L - 1, L - 1).  Candidate c (global index), axis a takes R = floor(u * count / 2^64),
 // u = draw number 8 c + a + 1 of SplitMix64 (Steele/Lea/Flood, OOPSLA 2014) started from the seed.
 //
-// Two launches: ri_table_kernel writes, for every distinct axis space of the call, the table R -> factors (a few
+// Few candidates: one launch, in which every workgroup makes the tables it needs (ri_direct_kernel).
+// Else two launches: ri_table_kernel writes, for every distinct axis space of the call, the table R -> factors (a few
 // hundred rows as a rule); ri_fill_kernel gives every candidate one draw, one multiply-high and one 8-byte table
 // read per axis, and stores the factors of four neighbouring candidates at a time.  The fill is bound by its stores
 // (2 bytes per slot and candidate).
@@ -36,7 +37,7 @@ static_assert(sizeof(RiSpace) % 16 == 0, "tables are uploaded 16 bytes at a time
 
 struct alignas(16) RiAxis {
     uint32_t table_off, count;
-    int32_t levels, pad;
+    int32_t levels, space;       // space: its place among the distinct ones
 };
 
 struct alignas(16) RiSeg {
@@ -58,38 +59,99 @@ __device__ __forceinline__ uint32_t compositions(int m, int parts)
     return parts == 1 ? 1u : parts == 2 ? (uint32_t)(m + 1) : (uint32_t)((m + 2) * (m + 1) / 2);
 }
 
-// Row R of a space's table: the factors of the R-th ordered factorisation, level 0 in the low half of .x
-__global__ void __launch_bounds__(256) ri_table_kernel(const RiSpace* __restrict__ spaces, uint2* __restrict__ table)
+// The factors of the R-th ordered factorisation of a space, outermost level first (0 past the last).
+// (by reference: a copy would put its arrays, indexed by a loop, into scratch memory)
+__device__ __forceinline__ void factors_of(const RiSpace& sp, uint32_t R, uint32_t (&f)[4])
 {
-    const RiSpace& sp = spaces[blockIdx.y];   // (by reference: a copy would put its arrays, indexed by a loop, into scratch memory)
-    uint32_t R = blockIdx.x * 256 + threadIdx.x;
-    if (R >= sp.count) return;
-    const uint32_t row = sp.table_off + R;
-    uint32_t f[4] = {1u, 1u, 1u, 1u};
-    for (int i = 0; i < sp.n_primes; ++i) {
-        uint32_t r = R % sp.C[i];
-        R /= sp.C[i];
-        // the composition of e into `levels` parts with lexicographic rank r
-        int rest = (int)sp.e[i];
 #pragma unroll
-        for (int l = 0; l < 4; ++l) {
-            if (l >= sp.levels) continue;
-            int v = rest;   // the last part takes what is left
-            if (l < sp.levels - 1) {
-                const int after = sp.levels - l - 1;   // parts after this one
-                for (v = 0;; ++v) {
-                    const uint32_t cnt = compositions(rest - v, after);
-                    if (r < cnt) break;
-                    r -= cnt;
-                }
-            }
-            for (int j = 0; j < v; ++j) f[l] *= sp.p[i];
-            rest -= v;
+    for (int l = 0; l < 4; ++l) f[l] = 1u;
+    const int levels = sp.levels;
+    for (int i = 0; i < sp.n_primes; ++i) {
+        const uint32_t p = sp.p[i], C = sp.C[i], r0 = R / C;
+        uint32_t r = R - r0 * C;
+        R = r0;
+        // The composition of e into `levels` parts with lexicographic rank r.  A step gives the level another p or goes on to the
+        // next one: e + levels - 1 steps for every rank, none of which diverges.
+        int rest = (int)sp.e[i], level = 0;
+        for (int step = rest + levels - 1; step > 0; --step) {
+            const int after = levels - 1 - level;   // parts after this one; the last takes what is left
+            const uint32_t cnt = after == 0 ? 0u : compositions(rest, after);
+            const bool on = r < cnt;
+            r -= on ? 0u : cnt;
+#pragma unroll
+            for (int l = 0; l < 4; ++l) f[l] = !on && l == level ? f[l] * p : f[l];
+            rest -= on ? 0 : 1;
+            level += on ? 1 : 0;
         }
     }
 #pragma unroll
-    for (int l = 0; l < 4; ++l) f[l] = l == sp.levels - 1 ? f[l] * (uint32_t)sp.frag : l >= sp.levels ? 0u : f[l];
-    table[row] = make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16));
+    for (int l = 0; l < 4; ++l) f[l] = l == levels - 1 ? f[l] * (uint32_t)sp.frag : l >= levels ? 0u : f[l];
+}
+
+// Row R of a space's table: the factors of the R-th ordered factorisation, level 0 in the low half of .x
+__global__ void __launch_bounds__(256) ri_table_kernel(const RiSpace* __restrict__ spaces, uint2* __restrict__ table)
+{
+    const RiSpace& sp = spaces[blockIdx.y];
+    const uint32_t R = blockIdx.x * 256 + threadIdx.x;
+    if (R >= sp.count) return;
+    uint32_t f[4];
+    factors_of(sp, R, f);
+    table[sp.table_off + R] = make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16));
+}
+
+// Few candidates: one launch.  The tables that describe the spaces travel with it; every workgroup writes the tables of factors of
+// its segment's axes in LDS, and then draws for one candidate per thread.  Bound by the latency of these stages.  8,000 candidates of
+// a matrix product: 7.8 us where an upload, the tables and the filling took 2 + 4.6 + 5.3 in three launches.
+struct RiTables {
+    uint4 q[3840 / 16];
+};
+constexpr int64_t kDirectMax = 1 << 16;   // candidates
+constexpr int kDirectRows = 1024;         // of a segment's tables
+
+__global__ void __launch_bounds__(kFillThreads) ri_direct_kernel(RiTables /* read through the argument segment, below */, int axes_at, int segs_at, uint16_t* __restrict__ tiles,
+                                                                 int64_t pitch, int rows, uint64_t seed)
+{
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    __shared__ u32x4 image[sizeof(RiTables) / 16];
+    __shared__ uint2 table[kDirectRows];
+    const int tid = threadIdx.x;
+    static_assert(sizeof(image) / 16 <= kFillThreads, "one thread copies sixteen bytes");
+    if (tid < (int)sizeof(image) / 16) {
+        typedef const __attribute__((address_space(4))) u32x4* ConstantMemory;
+        image[tid] = ((ConstantMemory)__builtin_amdgcn_kernarg_segment_ptr())[tid];
+    }
+    __syncthreads();
+    const char* tables = reinterpret_cast<const char*>(image);
+    const RiSeg seg = reinterpret_cast<const RiSeg*>(tables + segs_at)[blockIdx.y];
+    const RiAxis* axes = reinterpret_cast<const RiAxis*>(tables + axes_at) + seg.first_axis;
+    const int64_t first = seg.begin + (int64_t)blockIdx.x * kFillThreads;
+    if (first >= seg.end) return;
+    uint32_t made = 0;
+    for (int a = 0; a < seg.n_axes; ++a) {
+        if (axes[a].table_off != made) continue;   // (as an axis before)
+        const RiSpace& sp = reinterpret_cast<const RiSpace*>(tables)[axes[a].space];
+        for (uint32_t R = tid; R < axes[a].count; R += kFillThreads) {
+            uint32_t f[4];
+            factors_of(sp, R, f);
+            table[made + R] = make_uint2(f[0] | (f[1] << 16), f[2] | (f[3] << 16));
+        }
+        made += axes[a].count;
+    }
+    __syncthreads();
+    const int64_t c = first + tid;
+    if (c >= seg.end) return;
+    uint64_t z = seed + (8ull * (uint64_t)c + 1ull) * kRiGamma;
+    uint16_t* at = tiles + c;
+    int slot = 0;
+    for (int a = 0; a < seg.n_axes; ++a, z += kRiGamma) {
+        const RiAxis& ax = axes[a];
+        const uint2 f = table[ax.table_off + (uint32_t)__umul64hi(ri_splitmix64_mix(z), (uint64_t)ax.count)];
+#pragma unroll
+        for (int l = 0; l < 4; ++l)
+            if (l < ax.levels) at[(int64_t)(slot + l) * pitch] = (uint16_t)((l < 2 ? f.x : f.y) >> (16 * (l & 1)));
+        slot += ax.levels;
+    }
+    for (; slot < rows; ++slot) at[(int64_t)slot * pitch] = 0;   // rows the subgraph does not own
 }
 
 // VEC neighbouring candidates per thread, stored VEC at a time (the stores are what this kernel costs); blockIdx.y =
@@ -236,7 +298,7 @@ int make_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, P
                 if (sp.count > plan->max_count) plan->max_count = sp.count;
                 plan->spaces.push_back(sp);
             }
-            plan->axes.push_back(RiAxis{plan->spaces[hit].table_off, plan->spaces[hit].count, levels, 0});
+            plan->axes.push_back(RiAxis{plan->spaces[hit].table_off, plan->spaces[hit].count, levels, (int32_t)hit});
         }
         plan->segs.push_back(seg);
     }
@@ -299,6 +361,37 @@ extern "C" int pruner_random_init(const pruner_subgraph* sg, int32_t n_sg, const
 
     hipStream_t st = static_cast<hipStream_t>(stream);
     char* ws = static_cast<char*>(workspace);
+    int64_t longest = 0;
+    for (int32_t s = 0; s < n_sg; ++s)
+        if (seg_off[s + 1] - seg_off[s] > longest) longest = seg_off[s + 1] - seg_off[s];
+    const size_t axes_at = plan.spaces.size() * sizeof(RiSpace), segs_at = axes_at + plan.axes.size() * sizeof(RiAxis);
+    if (n <= kDirectMax && segs_at + plan.segs.size() * sizeof(RiSeg) <= sizeof(RiTables)) {
+        // the tables of a segment's axes lie one behind the other in a workgroup's LDS
+        std::vector<RiAxis> axes = plan.axes;
+        uint32_t most_rows = 0;
+        for (const RiSeg& seg : plan.segs) {
+            uint32_t made = 0;
+            for (int a = 0; a < seg.n_axes; ++a) {
+                RiAxis* own = axes.data() + seg.first_axis;
+                int same = 0;
+                while (own[same].space != own[a].space) ++same;
+                own[a].table_off = same < a ? own[same].table_off : made;
+                made += same < a ? 0u : own[a].count;
+            }
+            most_rows = made > most_rows ? made : most_rows;
+        }
+        if (most_rows <= (uint32_t)kDirectRows) {
+            RiTables tables = {};
+            char* image = reinterpret_cast<char*>(&tables);
+            memcpy(image, plan.spaces.data(), plan.spaces.size() * sizeof(RiSpace));
+            memcpy(image + axes_at, axes.data(), axes.size() * sizeof(RiAxis));
+            memcpy(image + segs_at, plan.segs.data(), plan.segs.size() * sizeof(RiSeg));
+            hipLaunchKernelGGL(ri_direct_kernel, dim3((unsigned)((longest + kFillThreads - 1) / kFillThreads), (unsigned)n_sg), dim3(kFillThreads), 0, st, tables, (int)axes_at,
+                               (int)segs_at, tiles, tiles_pitch, (int)tile_rows, seed);
+            PRUNER_LAUNCH_CHECK();
+            return PRUNER_OK;
+        }
+    }
     {   // the three tables lie one behind the other: one upload (a launch as a rule)
         std::vector<char> image(L.segs + plan.segs.size() * sizeof(RiSeg), 0);
         memcpy(image.data() + L.spaces, plan.spaces.data(), plan.spaces.size() * sizeof(RiSpace));
@@ -311,9 +404,6 @@ extern "C" int pruner_random_init(const pruner_subgraph* sg, int32_t n_sg, const
     hipLaunchKernelGGL(ri_table_kernel, dim3((plan.max_count + 255) / 256, (unsigned)plan.spaces.size()), dim3(256), 0, st,
                        reinterpret_cast<const RiSpace*>(ws + L.spaces), table);
     PRUNER_LAUNCH_CHECK();
-    int64_t longest = 0;
-    for (int32_t s = 0; s < n_sg; ++s)
-        if (seg_off[s + 1] - seg_off[s] > longest) longest = seg_off[s + 1] - seg_off[s];
     // (a segment that does not begin at a multiple of the vector width needs one thread more)
     if (tiles_pitch % 4 == 0 && aligned(tiles, 8))
         hipLaunchKernelGGL(ri_fill_kernel<4>, dim3((unsigned)((longest + 4 + 4 * kFillThreads - 1) / (4 * kFillThreads)), (unsigned)n_sg),
