@@ -236,11 +236,10 @@ __device__ __forceinline__ uint32_t index_of(uint64_t w) { return 0xFFFFFFFFu - 
 //      across its lanes; a maximum's rank among all 256 is its place in its own wavefront plus, by bisection, the
 //      number of larger ones in the other three sorted lists;
 //   3. the words at or above the pivot go to a list in LDS; a word's row is the number of larger words in the list.
-// 10 us for 4,096 entries and k = 64, 8 for 512 and k = 32, where one workgroup of sixteen wavefronts and three digit passes
-// took 13.
+// 8.7 us for 4,096 entries and k = 64 (10.5 with 32 words per thread and bisections one after the other).
 
 constexpr int kTinyThreads = 256;
-constexpr int kTinyPer = 32;
+constexpr int kTinyPer = 32;   // words per thread, at most
 constexpr int kTinyMax = kTinyThreads * kTinyPer;   // 8192 entries per segment
 constexpr int kTinyK = 64;
 constexpr int kTinyList = kTinyK * kTinyPer;        // words that can reach the pivot
@@ -304,7 +303,9 @@ struct TinyLds {
 
 // The k best entries of score[seg_begin .. seg_end) as rows idx_out[row * k ..] (and val_out), best first.  A workgroup of
 // kTinyThreads threads calls it with all its threads; it begins and ends with everything it read or wrote in L settled
-// (callers need no barrier around it except for their own data).
+// (callers need no barrier around it except for their own data).  PER: words per thread (at most kTinyThreads PER entries): a word costs
+// a dozen instructions whether or not there is an entry for it.
+template <int PER>
 __device__ __forceinline__ void tiny_select(TinyLds& L, const float* __restrict__ score, int64_t seg_begin, int64_t seg_end, int64_t row, int k,
                                             int32_t* __restrict__ idx_out, float* __restrict__ val_out)
 {
@@ -312,35 +313,39 @@ __device__ __forceinline__ void tiny_select(TinyLds& L, const float* __restrict_
     const float* seg_score = score + seg_begin;
     const int len = (int)(seg_end - seg_begin);
 
-    uint64_t w[kTinyPer], best = 0;   // 0: no entry (below every word of a number)
+    uint64_t w[PER], best = 0;   // 0: no entry (below every word of a number)
 #pragma unroll
-    for (int j = 0; j < kTinyPer; ++j) {
+    for (int j = 0; j < PER; ++j) {
         const int i = j * kTinyThreads + (int)threadIdx.x;
         w[j] = i < len ? compose(key_of(seg_score[i]), (uint32_t)(seg_begin + i)) : 0ull;
     }
 #pragma unroll
-    for (int j = 0; j < kTinyPer; ++j) best = w[j] > best ? w[j] : best;
+    for (int j = 0; j < PER; ++j) best = w[j] > best ? w[j] : best;
     if (threadIdx.x == 0) L.fill = 0;
 
     const uint64_t mine = wave_sort_descending(best);   // lane p of this wavefront holds its p-th largest maximum
     L.sorted[wave][lane] = mine;
     __syncthreads();
     // rank of `mine` among the 256 maxima = larger ones in this wavefront (lane) + larger ones in the others.  At least k
-    // maxima are words of entries (a segment holds at least k entries); the fillers rank behind all of them.
+    // maxima are words of entries (a segment holds at least k entries); the fillers rank behind all of them.  The other lists are
+    // searched side by side, in quarters: three looks at each at a time.
+    constexpr int kOthers = kTinyThreads / kWave - 1;
+    int past[kOthers];
+#pragma unroll
+    for (int o = 0; o < kOthers; ++o) past[o] = 0;
+#pragma unroll
+    for (int q = kWave / 4; q >= 1; q >>= 2) {
+#pragma unroll
+        for (int o = 0; o < kOthers; ++o) {
+            const uint64_t* other = L.sorted[(wave + o + 1) % (kTinyThreads / kWave)] + past[o];
+            const uint64_t x = other[q - 1], y = other[2 * q - 1], z = other[3 * q - 1];
+            past[o] += q * ((x > mine ? 1 : 0) + (y > mine ? 1 : 0) + (z > mine ? 1 : 0));
+        }
+    }
+    static_assert(kWave == 64, "quarters down to one");
     uint32_t rank = (uint32_t)lane;
 #pragma unroll
-    for (int o = 1; o < kTinyThreads / kWave; ++o) {
-        const uint64_t* other = L.sorted[(wave + o) % (kTinyThreads / kWave)];
-        int lo = 0, hi = kWave;   // other[0 .. lo) > mine >= other[hi .. 64): lo ends as the number of larger ones
-#pragma unroll
-        for (int step = 0; step < 7; ++step) {   // the range halves from 64 to nothing
-            const int mid = (lo + hi) >> 1;
-            const bool larger = lo < hi && other[mid < kWave ? mid : kWave - 1] > mine;
-            lo = larger ? mid + 1 : lo;
-            hi = larger ? hi : mid;
-        }
-        rank += (uint32_t)lo;
-    }
+    for (int o = 0; o < kOthers; ++o) rank += (uint32_t)past[o] + (L.sorted[(wave + o + 1) % (kTinyThreads / kWave)][past[o]] > mine ? 1u : 0u);
     if (mine != 0 && rank == (uint32_t)(k - 1)) L.pivot_slot = mine;
     __syncthreads();
     const uint64_t pivot = L.pivot_slot;
@@ -348,14 +353,14 @@ __device__ __forceinline__ void tiny_select(TinyLds& L, const float* __restrict_
     // range that one of them reserves (one atomic per wavefront, not one per word).
     uint32_t mine_count = 0;
 #pragma unroll
-    for (int j = 0; j < kTinyPer; ++j) mine_count += w[j] >= pivot && w[j] != 0 ? 1u : 0u;
+    for (int j = 0; j < PER; ++j) mine_count += w[j] >= pivot && w[j] != 0 ? 1u : 0u;
     const uint32_t upto = wave_inclusive_sum(mine_count);
     uint32_t wave_base = 0;
     if (lane == kWave - 1 && upto != 0) wave_base = atomicAdd(&L.fill, upto);
     uint32_t at = (uint32_t)__builtin_amdgcn_readlane((int)wave_base, kWave - 1) + upto - mine_count;
     if (mine_count != 0) {
 #pragma unroll
-        for (int j = 0; j < kTinyPer; ++j)
+        for (int j = 0; j < PER; ++j)
             if (w[j] >= pivot && w[j] != 0) L.list[at++] = w[j];
     }
     __syncthreads();
@@ -363,15 +368,20 @@ __device__ __forceinline__ void tiny_select(TinyLds& L, const float* __restrict_
     if (threadIdx.x == 0) L.list[n_list] = L.list[n_list + 1] = 0;   // the comparison below reads two words at a time
     __syncthreads();
     typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-    for (int e = threadIdx.x; e < n_list; e += kTinyThreads) {
-        const uint64_t me = L.list[e];
+    // four neighbouring lanes to a word, each counting in its own part of the list
+    const int part = lane & 3, pairs = (n_list + 1) >> 1;
+    for (int e0 = 0; e0 < n_list; e0 += kTinyThreads / 4) {
+        const int e = e0 + ((int)threadIdx.x >> 2);
+        const uint64_t me = e < n_list ? L.list[e] : ~0ull;
         uint32_t r = 0;
-        for (int f = 0; f < n_list; f += 2) {
-            const u64x2 two = *reinterpret_cast<const u64x2*>(L.list + f);
+        for (int f = part; f < pairs; f += 4) {
+            const u64x2 two = *reinterpret_cast<const u64x2*>(L.list + 2 * f);
             r += two.x > me ? 1u : 0u;
             r += two.y > me ? 1u : 0u;
         }
-        if (r < (uint32_t)k) {
+        r += dpp_move<0xB1>(r);   // quad_perm: the neighbour's, the other pair's
+        r += dpp_move<0x4E>(r);
+        if (part == 0 && e < n_list && r < (uint32_t)k) {
             const uint32_t gi = index_of(me), kk = (uint32_t)(me >> 32);
             idx_out[row * k + r] = (int32_t)gi;
             // a key names its score, except the one that -0.0 and +0.0 share

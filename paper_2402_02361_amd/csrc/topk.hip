@@ -197,13 +197,13 @@ struct SegsInMemory {
 // ---- tiny route: segments of at most 8192 entries, k at most 64 ---------------------------------------------------
 // (tiny_select in select_common.h: the final selection after the verify stage and small draft populations)
 
-template <class Table>
+template <int PER, class Table>
 __global__ void __launch_bounds__(kTinyThreads) topk_tiny_kernel(const float* __restrict__ score, Table segs, int k, int32_t* __restrict__ idx_out,
                                                                  float* __restrict__ val_out)
 {
     __shared__ TinyLds L;
     const SegT seg = segs.at(blockIdx.x);
-    tiny_select(L, score, seg.begin, seg.end, blockIdx.x, k, idx_out, val_out);
+    tiny_select<PER>(L, score, seg.begin, seg.end, blockIdx.x, k, idx_out, val_out);
 }
 
 // ---- spans route ------------------------------------------------------------------------------------------------
@@ -2066,8 +2066,16 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     InlineSegs inl;
     if (ctx.inline_ok) memcpy(&inl, ctx.inline_segs, sizeof inl);
     if (ctx.tiny) {
-        if (ctx.inline_ok) hipLaunchKernelGGL(topk_tiny_kernel<InlineSegs>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, inl, k, idx_out, val_out);
-        else hipLaunchKernelGGL(topk_tiny_kernel<SegsInMemory>, dim3(n_sg), dim3(kTinyThreads), 0, st, score, in_memory, k, idx_out, val_out);
+#define PRUNER_TINY(PER) \
+    do { \
+        if (ctx.inline_ok) hipLaunchKernelGGL((topk_tiny_kernel<PER, InlineSegs>), dim3(n_sg), dim3(kTinyThreads), 0, st, score, inl, k, idx_out, val_out); \
+        else hipLaunchKernelGGL((topk_tiny_kernel<PER, SegsInMemory>), dim3(n_sg), dim3(kTinyThreads), 0, st, score, in_memory, k, idx_out, val_out); \
+    } while (0)
+        if (ctx.longest <= 2 * kTinyThreads) PRUNER_TINY(2);
+        else if (ctx.longest <= 8 * kTinyThreads) PRUNER_TINY(8);
+        else if (ctx.longest <= 16 * kTinyThreads) PRUNER_TINY(16);
+        else PRUNER_TINY(kTinyPer);
+#undef PRUNER_TINY
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }

@@ -52,3 +52,14 @@ def test_maxima_left_by_the_draft_kernel(P, sgs, lens, k):
         assert torch.equal(idx, want) and torch.equal(val.view(torch.int32), want_val.view(torch.int32))
         host = score.cpu().numpy()
         assert np.array_equal(idx.cpu().numpy(), by_bits(host, seg, k))
+
+
+@pytest.mark.parametrize("longest", [512, 513, 2048, 2049, 4096, 4097, 8192])
+@pytest.mark.parametrize("kind", ["latencies", "ascending", "two values", "equal"])
+def test_words_per_thread_of_short_selections(P, longest, kind):
+    rng = np.random.default_rng(longest)
+    lens = [longest, 64, longest - 1]
+    seg = np.concatenate([[0], np.cumsum(lens)])
+    score = np.concatenate([of(kind, n, rng) for n in lens])
+    for k in (1, 33, 64):
+        check(P, score, seg, k)
