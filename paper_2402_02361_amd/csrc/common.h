@@ -88,12 +88,12 @@ struct Upload {
 // between them (the draft kernel does, while the scores are still in registers).
 struct TopkCtx {
     bool digits;           // the route counts first digits (lists and spans)
-    bool tiny, pick, levels, lists;   // the route; none of them: spans
+    bool tiny, pick, levels, blocks_route, lists;   // the route; none of them: spans
     int32_t n_sg, k;
     int64_t n, longest, span;
     int32_t blocks;        // workgroups of a sweep launch
     int copies;            // copies of the first digit's histogram
-    void *d_segs, *d_state, *d_stage;
+    void *d_segs, *d_state, *d_stage, *d_parts;
     uint32_t* d_hist;      // [copies][n_sg][2048] first digit, then one copy each for the second and third
     uint32_t* d_max256;    // largest key of every 256 neighbouring entries (block_max_slot), or null: the route does without
     uint32_t *d_max64, *d_max16;   // ... of every 64 (block64_slot) and 16 (block16_slot), or null

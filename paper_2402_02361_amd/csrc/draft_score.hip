@@ -944,7 +944,7 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
     }
 
     if constexpr (!DUMP && (!HIST || MUT)) {
-        if (max16) {
+        if (max16 || (block_max && !(HIST && count_digits))) {
             // The largest keys of neighbouring candidates, by which the selection finds those that can matter.  The lanes at work are lanes
             // 0..m (as above).  Without the special case of -0, which is put right once.
             uint32_t top = 0;

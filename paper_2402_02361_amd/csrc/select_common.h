@@ -193,7 +193,7 @@ __device__ __forceinline__ int64_t block_max_slot(int64_t first, int s) { return
 __device__ __forceinline__ int64_t block64_slot(int64_t first, int s) { return (first >> 6) + s; }
 __device__ __forceinline__ int64_t block16_slot(int64_t first, int s) { return (first >> 4) + s; }
 
-// Leaves the largest keys of the blocks of 16, 64 and 256 neighbours (the latter two where they are asked for) that a wavefront
+// Leaves the largest keys of the blocks of 16, 64 and 256 neighbours (those that are asked for) that a wavefront
 // holds, VEC = 4 or 1 entries per lane, lane 0 at the begin of a block: `top` is the largest key of the lane's own, `first` the index
 // of the first of these; entries at or past `end` are none.  The active lanes are 0 .. last.
 template <int VEC>
@@ -204,16 +204,16 @@ __device__ __forceinline__ void note_maxima(uint32_t top, int64_t first, int las
     const int lane = lane_id(), in_row = lane & 15;
     top = max_with<0x4E, 0xf>(max_with<0xB1, 0xf>(top));   // quad_perm: the neighbour's, the other pair's
     if constexpr (VEC == 4) {
-        if ((lane & 3) == 0 && first < end) max16[block16_slot(first, s)] = top;
-        if (!max64) return;
+        if (max16 && (lane & 3) == 0 && first < end) max16[block16_slot(first, s)] = top;
+        if (!max64 && !max256) return;
         top = max_with<0x118, 0xf>(max_with<0x114, 0xf>(top));   // row_shr:4, row_shr:8: the last lane of a row of 16 has all four
-        if ((in_row == 15 || lane == last) && first - 4 * in_row < end) max64[block64_slot(first - 4 * in_row, s)] = top;
+        if (max64 && (in_row == 15 || lane == last) && first - 4 * in_row < end) max64[block64_slot(first - 4 * in_row, s)] = top;
         if (!max256) return;
         top = rows_inclusive_max(top);
         if (lane == last && first - 4 * last < end) max256[block_max_slot(first - 4 * last, s)] = top;
     } else {
         top = max_with<0x118, 0xf>(max_with<0x114, 0xf>(top));
-        if ((in_row == 15 || lane == last) && first - in_row < end) max16[block16_slot(first - in_row, s)] = top;
+        if (max16 && (in_row == 15 || lane == last) && first - in_row < end) max16[block16_slot(first - in_row, s)] = top;
         if (!max64) return;
         top = rows_inclusive_max(top);
         if (lane == last && first - last < end) max64[block64_slot(first - last, s)] = top;

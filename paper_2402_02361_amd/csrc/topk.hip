@@ -5,7 +5,7 @@
 // order; the k survivors are ranked by (key descending, index ascending).  Nothing depends on the order in which blocks or
 // wavefronts run.
 //
-// Five routes, same result:
+// Six routes, same result:
 //   tiny   - segments of at most 8192 entries and k up to 64 (the final selection after the verify stage, small draft
 //            populations): one launch, no digits (tiny_select in select_common.h);
 //   pick   - short segments: one launch, in which several workgroups per segment hold it in registers, count the first digit, keep
@@ -13,6 +13,8 @@
 //            most kPickMax entries, behind whoever counted the digit, the draft kernel or a pass);
 //   levels - longer ones, k up to kLevelK: the same launch behind whoever held the scores and left the largest key of every sixteen
 //            neighbours (the draft kernel, else a pass): a workgroup holds the few blocks of sixteen that can matter;
+//   blocks - a larger k of a few segments at least 768 times as long: two launches behind whoever held the scores and left the largest key of every 256 neighbours
+//            (the draft kernel, else a pass): the entries of the best blocks that reach a bound are set aside, and picked;
 //   lists  - a larger k, segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
 //            16384-entry sweeps, one workgroup each) and sets the entries at or above the bin aside in a list per span; the
 //            workgroups of a segment then collect from its lists (and go through the span of a list that overflowed themselves);
@@ -1209,11 +1211,13 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
 // The n words in sel to the rows (those below row_len = k) of one segment: ranked in rounds of 64 per workgroup, the words shared out over the
 // segment's workgroups, or sorted, all of them by every workgroup, whatever costs less (see kSortFactor).
 // SORT: with the way of sorting (the other calls' kernel is shorter without it).  k_rem of the words with keys lowest .. lowest + width
-// are selected, and all above; in_trim: these two facts are exact, so that the sort may leave the surplus out.
+// are selected, and all above; exact: these two facts are, so that the sort may leave the surplus out.  same_places: the words lie in the same
+// places in every workgroup, which are dealt out in turn (by the hash some have half as many again as others, and with them a round more:
+// 5,179 words, 128 workgroups, 40 each: 23.5 us, dealt out 15.0).
 template <bool SORT>
 __device__ __forceinline__ void write_collection(uint64_t* sel, uint32_t* place, uint32_t* cnt, uint32_t* fill, uint32_t* n_own, int n, int k, int share, int part,
                                                  uint32_t k_rem, uint32_t lowest, uint32_t width, bool exact, const float* __restrict__ score,
-                                                 int32_t* __restrict__ idx_out, float* __restrict__ val_out, int s, const SegT& seg)
+                                                 int32_t* __restrict__ idx_out, float* __restrict__ val_out, int s, const SegT& seg, bool same_places = false)
 {
     uint16_t* own = reinterpret_cast<uint16_t*>(place);
     const int n_last = n - (int)((uint32_t)k - k_rem);   // the words of the last bin
@@ -1258,6 +1262,11 @@ __device__ __forceinline__ void write_collection(uint64_t* sel, uint32_t* place,
         const int rows = n < k ? n : k, per = (rows + share - 1) / share, lo = part * per < rows ? part * per : rows;   // each writes its part of the rows
         finish_segment<kBigThreads>(sel, n, lo, lo + per < rows ? lo + per : rows, score, idx_out, val_out, s, seg.begin, seg.end, k);
         n = 0;
+    }
+    if (same_places) {
+        __syncthreads();
+        if (n > 0) rank_rows<kBigThreads>(sel, n, nullptr, part, share, n > part ? (n - part + share - 1) / share : 0, cnt, score, idx_out, val_out, s, seg.begin, seg.end, k);
+        return;
     }
     // (every workgroup has its own order of the words: a hash of the index decides who ranks a word)
     for (int e = threadIdx.x; e < n; e += kBigThreads) {
@@ -1661,7 +1670,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     write_collection<SORT>(sel, place, hist, &fill, &n_own, n, k, share, part, k_rem, lowest, width, exact, score, idx_out, val_out, s, seg);
 }
 
-// The largest keys of blocks (max64, max256 may be null), for scores that nobody has held before.  Bound by the scores' way from memory.
+// The largest keys of blocks (those that are asked for), for scores that nobody has held before.  Bound by the scores' way from memory.
 template <class Table>
 __global__ void __launch_bounds__(256) maxima_kernel(const float* __restrict__ score, Table segs, uint32_t* __restrict__ max16, uint32_t* __restrict__ max64,
                                                      uint32_t* __restrict__ max256)
@@ -1893,8 +1902,487 @@ __global__ void __launch_bounds__(kBigThreads) pick_lists_kernel(const float* __
     }
 }
 
+// ---- blocks route -------------------------------------------------------------------------------------------------------
+// More than kLevelK of a few long segments, at most one entry in 768: two launches, with the largest keys of 256 neighbours that
+// whoever held the scores left.
+//   1. kParts workgroups per segment.  Each finds, for itself, at least k blocks by (maximum, then index), at most kMostBlocks, and goes through its part of
+//      them, neighbours in index order: what exceeds the bound to a list, and the indices of what equals it, in order, to another.
+//      An entry of another block has the largest entries of k blocks before it.  Where a part alone has k or more above the bound (a
+//      stretch of good entries), the part has a higher bound of its own.
+//   2. `share` workgroups per segment collect from the lists and rank as pick_kernel does.  On scores in no particular order all
+//      of the lists: of m blocks about m ln(m / (m - k)) entries reach the bound.  Where fewer than k are above it, as among the copies
+//      of the explorer's later steps, the first of those that equal it; else the lists are narrowed digit by digit.
+// The bound: every eighth maximum is counted (their keys' range, then digits of it) and a rank a little beyond the k-th block's
+// taken; how many blocks reach that is then known exactly, and where they are too many or too few all maxima are counted.
+// Bound by latencies, and by the way of the maxima (256 KB for 16.8 M entries) into each compute unit: 5.4 us of the first launch's
+// 22.4 until they are there, 6.2 for the bound, 2.6 for the blocks' numbers, 2.5 until the blocks are there, 4.3 for the lists.
+// 16.8 M and 4.2 M, k = 4,096: 22.4 + 15.0 us, where clearing histograms and the four launches of the spans route took 4.5 + 41; on the
+// explorer's populations of copies 32.6 + 17.1 against 4.7 + 79.  From 768 entries per selected one on: 1 x 3.2 M, k = 4,096, 44 -> 38 us for
+// the call, 1 x 800,000, k = 1,025, 38.5 -> 29.6; below, the bound that k blocks reach leaves too many entries (390 of them: 42 -> 49).  A stretch of
+// 20,000 good entries among 3.2 M sorted ones takes longer (50 -> 61).  More segments: the spans route shares out the scores as well.
+constexpr int kHeldQuads = 16;                                                        // of maxima, per thread
+constexpr int64_t kBlocksMax = (int64_t)4 * kHeldQuads * kBigThreads * 256;           // entries of a segment
+constexpr int kBlocksSegments = 4;
+constexpr int64_t kBlocksSparse = 768;                                                // entries per selected one, at least: 3 k blocks (see above)
+__host__ __device__ constexpr int parts_limit(int k) { return k + 3 * k / 4 + 256; }  // words that are ranked without narrowing
+constexpr int kParts = kWave;                                                         // lists of a segment: a lane knows one's counts
+constexpr int kPartBlocks = 6 * (kBigThreads / kWave);                                // blocks of a part
+constexpr int kMostBlocks = kParts * kPartBlocks;
+static_assert(kMostBlocks >= PRUNER_MAX_K, "the k best blocks fit");
+
+static_assert(kPickCap >= parts_limit(PRUNER_MAX_K), "a collection fits");
+
+struct PartList {
+    uint32_t above, ties, bound, top;     // top: the part's largest key
+    uint64_t word[PRUNER_MAX_K];          // of entries above `bound`
+    uint32_t tie[PRUNER_MAX_K];           // indices, in order, of entries that equal it
+};
+
+// A thread's part of `four` counts per row (rows in order, the lanes' order in each), wavefront after wavefront: calls
+// put(row, first number) with the number of things before this thread's of that row.  All threads; returns the total.
+template <int ROWS, class Count, class Put>
+__device__ __forceinline__ uint32_t number_rows(uint32_t* wave_tot, Count&& count, Put&& put)
+{
+    const int lane = lane_id(), wave = threadIdx.x >> 6;
+    uint32_t before[ROWS], sum = 0;
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) {
+        const uint32_t mine = count(j), upto = wave_inclusive_sum(mine);
+        before[j] = sum + upto - mine;
+        sum += (uint32_t)__builtin_amdgcn_readlane((int)upto, kWave - 1);
+    }
+    __syncthreads();   // (wave_tot may still be read)
+    if (lane == 0) wave_tot[wave] = sum;
+    __syncthreads();
+    uint32_t total = 0, wave_before = 0;
+#pragma unroll
+    for (int w = 0; w < kBigThreads / kWave; ++w) {
+        wave_before += w < wave ? wave_tot[w] : 0u;
+        total += wave_tot[w];
+    }
+#pragma unroll
+    for (int j = 0; j < ROWS; ++j) put(j, wave_before + before[j]);
+    return total;
+}
+
+// The sum of all threads' values.
+__device__ __forceinline__ uint32_t sum_of_all(uint32_t mine, uint32_t* wave_tot)
+{
+    const uint32_t upto = wave_inclusive_sum(mine);
+    __syncthreads();
+    if (lane_id() == kWave - 1) wave_tot[threadIdx.x >> 6] = upto;
+    __syncthreads();
+    uint32_t total = 0;
+#pragma unroll
+    for (int w = 0; w < kBigThreads / kWave; ++w) total += wave_tot[w];
+    return total;
+}
+
+template <class Table>
+__global__ void __launch_bounds__(kBigThreads) block_lists_kernel(const float* __restrict__ score, Table segs, int n_total, int k, const uint32_t* __restrict__ max256,
+                                                                  PartList* __restrict__ lists)
+{
+    __shared__ __attribute__((aligned(16))) uint8_t nibble[kBigThreads * kHeldQuads];
+    __shared__ uint32_t hist[kBins], blocks[kMostBlocks], wave_tot[16], found[3], range[2], fill, top;
+    const int s = blockIdx.x / kParts, part = blockIdx.x % kParts, lane = lane_id(), wave = threadIdx.x >> 6;
+    const SegT seg = segs.at(s);
+    const int len = (int)(seg.end - seg.begin), n256 = (len + 255) >> 8, n_quads = (n256 + 3) >> 2;
+    const float* const seg_score = score + seg.begin;
+    const uint32_t* const maxima = max256 + block_max_slot(seg.begin, s);
+
+    // the maxima, `rows` rows of 64 quads per wavefront, neighbours
+    const int rows = (n_quads + kBigThreads - 1) / kBigThreads;   // at most kHeldQuads
+    auto quad = [&](int j) -> int { return (wave * rows + j) * kWave + lane; };
+    u32x4 v[kHeldQuads];
+#pragma unroll
+    for (int j = 0; j < kHeldQuads; ++j) {
+        v[j] = u32x4{0u, 0u, 0u, 0u};
+        if (j < rows && quad(j) < n_quads) v[j] = maxima_at(maxima, 4 * quad(j), n256);
+    }
+    if (threadIdx.x < 2) range[threadIdx.x] = 0;
+    if (threadIdx.x == 2) fill = top = 0;
+    __syncthreads();
+    // blocks whose maximum is at or above `key` (above zero), four bits a row; in 0 no block past the last
+    uint32_t mask[2];
+    auto reach = [&](uint32_t key) {
+        constexpr int kHalf = kHeldQuads / 2;
+        static_assert(kHeldQuads == 16, "two words of masks");
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            mask[h] = 0;
+#pragma unroll
+            for (int i = 4 * kHalf - 1; i >= 0; --i) mask[h] = 2 * mask[h] + (v[h * kHalf + (i >> 2)][i & 3] >= key ? 1u : 0u);
+        }
+        return sum_of_all((uint32_t)(__popc(mask[0]) + __popc(mask[1])), wave_tot);
+    };
+    // The bound: a digit at a time of the first maxima of every other row's quads; where what they show leaves too few or too many, of all.
+    // (A maximum of 0, which names a NaN, is not counted: a bound of 0 serves.)
+    uint32_t bound = 0, n_reach = 0, n_above = 0;
+#pragma unroll 1
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        uint32_t n_mine = 0, lowest = 1u, width = ~0u - 1u;
+        if (attempt == 0) {
+            uint32_t not_least = 0, most = 0;
+#pragma unroll
+            for (int j = 0; j < kHeldQuads; j += 2) {
+                const uint32_t x = v[j][0];
+                most = x > most ? x : most;
+                not_least = x != 0u && ~x > not_least ? ~x : not_least;
+                n_mine += x != 0u ? 1u : 0u;
+            }
+            note_range(not_least, most, range);
+        } else {
+#pragma unroll
+            for (int j = 0; j < kHeldQuads; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) n_mine += v[j][e] != 0u ? 1u : 0u;
+        }
+        const uint32_t n_counted = sum_of_all(n_mine, wave_tot);   // (a barrier: the range is there)
+        uint32_t rank = (uint32_t)k, spare = (uint32_t)(kMostBlocks - k);
+        if (attempt == 0) {
+            const float expected = (float)k * (float)n_counted / (float)n256;
+            rank = (uint32_t)(expected + 4.f * __builtin_sqrtf(expected)) + 1u;
+            rank = rank < n_counted ? rank : n_counted;
+            spare = rank / 8;
+            lowest = ~range[0];
+            width = range[1] - lowest;
+        }
+        if (rank == 0u || n_counted < rank) {
+            lowest = 0u;
+            width = 0u;
+        }
+#pragma unroll 1
+        while (width != 0u) {
+            const int shift = next_shift(width);
+            for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+            __syncthreads();
+            if (attempt == 0) {
+#pragma unroll
+                for (int j = 0; j < kHeldQuads; j += 2)
+                    if (j < rows) light_hist_add(hist, (v[j][0] - lowest) >> shift, v[j][0] >= lowest && v[j][0] - lowest <= width);
+            } else {
+#pragma unroll 1
+                for (int i = threadIdx.x; i < rows * kBigThreads; i += kBigThreads) {
+                    const u32x4 w = maxima_at(maxima, 4 * (i < n_quads ? i : 0), n256);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) light_hist_add(hist, (w[e] - lowest) >> shift, i < n_quads && w[e] >= lowest && w[e] - lowest <= width);
+                }
+            }
+            __syncthreads();
+            find_bucket(hist, rank, wave_tot, found);
+            lowest += found[0] << shift;
+            width = (1u << shift) - 1u;
+            rank = found[1];
+            if (found[2] - rank <= spare) break;
+        }
+        bound = lowest;
+        n_reach = reach(bound);
+        if (n_reach >= (uint32_t)k && n_reach <= (uint32_t)kMostBlocks) break;
+        if (n_reach < (uint32_t)k) continue;
+        n_above = bound == ~0u ? 0u : reach(bound + 1u);
+        if (n_above <= (uint32_t)kMostBlocks) break;
+    }
+    // all that reach the bound; if they are too many, those above it, and if these are fewer than k, the first that equal it
+    const bool ties_apart = n_reach > (uint32_t)kMostBlocks;
+    const uint32_t n_ties = ties_apart && n_above < (uint32_t)k ? (uint32_t)k - n_above : 0u;
+    // A thread's maxima lie row by row; their bits go to the thread that numbers 64 neighbours, through LDS.
+    auto in_order = [&](const uint32_t(&m)[2]) {
+        uint8_t* const mine = nibble + wave * (kHeldQuads * kWave);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kHeldQuads; ++j) mine[j * kWave + lane] = (uint8_t)((m[j / 8] >> (4 * (j % 8))) & 15u);
+        __syncthreads();
+        static_assert(kHeldQuads == 16, "sixteen nibbles of a row per lane");
+        const u32x4 sixteen = reinterpret_cast<const u32x4*>(mine)[lane];
+        uint64_t bits = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t x = sixteen[e];
+            x = (x | x >> 4) & 0x00FF00FFu;
+            bits |= (uint64_t)((x | x >> 8) & 0xFFFFu) << (16 * e);
+        }
+        return (lane >> 2) < rows ? bits : 0ull;
+    };
+    uint32_t total;
+    uint64_t chosen;
+    if (n_ties != 0u) {
+        const uint32_t over[2] = {bound == ~0u ? 0u : mask[0], bound == ~0u ? 0u : mask[1]};   // above it
+        reach(bound);
+        const uint32_t level[2] = {mask[0] & ~over[0], mask[1] & ~over[1]};
+        chosen = in_order(over);
+        uint64_t equal = in_order(level);
+        uint32_t number = block_excl_scan<kBigThreads>((uint32_t)__popcll(equal), wave_tot, &total);
+        if (number + (uint32_t)__popcll(equal) <= n_ties) {
+            chosen |= equal;
+        } else {
+#pragma unroll 1
+            for (; equal && number < n_ties; equal &= equal - 1ull, ++number) chosen |= equal & (0ull - equal);
+        }
+    } else {
+        chosen = in_order(mask);
+    }
+    uint32_t number = block_excl_scan<kBigThreads>((uint32_t)__popcll(chosen), wave_tot, &total);
+    const uint32_t n_blocks = total;
+#pragma unroll 1
+    for (; chosen; chosen &= chosen - 1ull, ++number)
+        if (number < (uint32_t)kMostBlocks) blocks[number] = (uint32_t)(256 * wave * rows + 64 * lane + __ffsll((unsigned long long)chosen) - 1);
+    if (ties_apart && n_ties == 0u) bound += 1u;   // (k blocks are above it)
+    __syncthreads();
+
+    // this part's blocks, six to a wavefront
+    constexpr int kPer = kPartBlocks / (kBigThreads / kWave);
+    const int nb = (int)(n_blocks < (uint32_t)kMostBlocks ? n_blocks : (uint32_t)kMostBlocks), b_lo = part * nb / kParts, b_hi = (part + 1) * nb / kParts;
+    const int last = n_total - 4 - (int)seg.begin;   // (the segment is long: at least 0 or a negative number whose entry exists)
+    int at[kPer];
+    f32x4 val[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int b = b_lo + wave * kPer + j;
+        at[j] = b < b_hi ? 256 * (int)blocks[b] + 4 * lane : len;
+        val[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (at[j] < len) val[j] = *reinterpret_cast<const f32x4_a4*>(seg_score + (at[j] < last ? at[j] : last));
+    }
+    uint32_t key[kPer][4], live[kPer];   // live: the entries that reach the bound; the others' keys are 0
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int begun = at[j] < last ? at[j] : last;
+        live[j] = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t x = key_of(val[j][e]);
+            const bool in = at[j] < len && begun + e >= at[j] && begun + e < len && x >= bound;
+            key[j][e] = in ? x : 0u;
+            live[j] |= in ? 1u << e : 0u;
+        }
+        at[j] = begun;
+    }
+    auto count = [&](auto&& what) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) n += what(key[j][e]) ? 1u : 0u;
+        return n;
+    };
+    uint32_t most = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) most = key[j][e] > most ? key[j][e] : most;
+    most = wave_inclusive_max(most);
+    if (lane == kWave - 1 && most) atomicMax(&top, most);
+    uint32_t n_list = sum_of_all(count([&](uint32_t x) { return x > bound; }), wave_tot);
+    bool with_ties = n_list < (uint32_t)k;
+    if (!with_ties) {
+        // a bound of its own, which k of this part's entries reach and at most PRUNER_MAX_K exceed
+        uint32_t lowest = bound + 1u, width = ~0u - lowest, rank = (uint32_t)k, reach = n_list;
+#pragma unroll 1
+        while (reach > (uint32_t)PRUNER_MAX_K && width != 0u) {
+            const int shift = next_shift(width);
+            __syncthreads();
+            for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kPer; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) light_hist_add(hist, (key[j][e] - lowest) >> shift, key[j][e] >= lowest && key[j][e] - lowest <= width);
+            __syncthreads();
+            find_bucket(hist, rank, wave_tot, found);
+            lowest += found[0] << shift;
+            width = (1u << shift) - 1u;
+            rank = found[1];
+            reach = (uint32_t)k - rank + found[2];
+        }
+        with_ties = reach > (uint32_t)PRUNER_MAX_K;   // (one value: fewer than k are above it)
+        bound = with_ties ? lowest : lowest - 1u;
+        n_list = sum_of_all(count([&](uint32_t x) { return x > bound; }), wave_tot);
+    }
+    PartList& mine = lists[blockIdx.x];
+    uint32_t to = reserve(&fill, count([&](uint32_t x) { return x > bound; }));
+    uint32_t equal[kPer], any = 0;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        equal[j] = 0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            if (key[j][e] > bound) {
+                if (to < (uint32_t)PRUNER_MAX_K) mine.word[to] = compose(key[j][e], (uint32_t)seg.begin + (uint32_t)(at[j] + e));
+                ++to;
+            }
+            equal[j] |= with_ties && ((live[j] >> e) & 1u) && key[j][e] == bound ? 1u << e : 0u;
+        }
+        any |= equal[j];
+    }
+    uint32_t n_equal = 0;
+    if (__syncthreads_or((int)any)) {
+        n_equal = number_rows<kPer>(wave_tot, [&](int j) { return (uint32_t)__popc(equal[j]); }, [&](int j, uint32_t number) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if ((equal[j] >> e) & 1u) {
+                    if (number < (uint32_t)k) mine.tie[number] = (uint32_t)seg.begin + (uint32_t)(at[j] + e);
+                    ++number;
+                }
+        });
+    }
+    if (threadIdx.x == 0) {
+        mine.above = n_list;
+        mine.ties = n_equal < (uint32_t)k ? n_equal : (uint32_t)k;
+        mine.bound = bound;
+        mine.top = top;
+    }
+}
+
+template <bool SORT, class Table>
+__global__ void __launch_bounds__(kBigThreads) pick_parts_kernel(const float* __restrict__ score, Table segs, int n_seg, int k, int share, const PartList* __restrict__ lists,
+                                                                 int32_t* __restrict__ idx_out, float* __restrict__ val_out)
+{
+    __shared__ __align__(16) uint64_t sel[kPickWords];
+    __shared__ __align__(16) uint32_t place[kPickCap];   // which words this workgroup ranks
+    __shared__ uint32_t hist[kBins];                     // later: the ranking's counts
+    __shared__ uint32_t wave_tot[16], found[3], fill, n_own, range[2], ties_upto[kParts], bound_of[kParts];
+    const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    if (job >= n_seg * share) return;
+    const int s = job / share, part = job % share, lane = lane_id(), wave = threadIdx.x >> 6;
+    const SegT seg = segs.at(s);
+    const PartList* const own_lists = lists + (size_t)s * kParts;
+    constexpr int kMine = kParts / (kBigThreads / kWave);   // lists of a wavefront
+    constexpr int kAhead = 2;                               // words of each that are asked for at once, per lane (the lists hold PRUNER_MAX_K: inside)
+    uint64_t ahead[kMine][kAhead];
+#pragma unroll
+    for (int q = 0; q < kMine; ++q)
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) ahead[q][a] = own_lists[wave * kMine + q].word[a * kWave + lane];
+    uint32_t my_above = own_lists[lane].above, my_ties = own_lists[lane].ties;
+    const uint32_t my_bound = own_lists[lane].bound, my_top = own_lists[lane].top;
+    if (threadIdx.x == 0) fill = n_own = range[0] = range[1] = 0;
+    __syncthreads();
+    // what a list of k or more shows: the others' entries below its bound are none of the k best
+    const uint32_t shown = (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_max(my_above + my_ties >= (uint32_t)k ? my_bound + (my_above >= (uint32_t)k ? 1u : 0u) : 0u), kWave - 1);
+    if (my_top < shown) my_above = my_ties = 0;
+    const uint32_t upto_above = wave_inclusive_sum(my_above), upto_ties = wave_inclusive_sum(my_ties);
+    const uint32_t n_above = (uint32_t)__builtin_amdgcn_readlane((int)upto_above, kWave - 1), n_ties = (uint32_t)__builtin_amdgcn_readlane((int)upto_ties, kWave - 1);
+    const bool one_bound = __ballot(my_bound != (uint32_t)__builtin_amdgcn_readfirstlane((int)my_bound)) == 0ull;
+    const uint32_t limit = (uint32_t)parts_limit(k);
+    uint32_t n = n_above + n_ties;
+    const bool whole = n <= limit, first_ties = !whole && one_bound && n_above < (uint32_t)k;
+    // Short lists are a wavefront's own; the others are gone through by all.  (One wavefront alone took 50 us with a full one.)
+    const unsigned long long lengthy = __ballot(my_above > (uint32_t)(kAhead * kWave) || my_ties > (uint32_t)(kAhead * kWave));
+    auto of_list = [&](uint32_t mine, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)mine, l); };
+    // every word: what(there, word), the lanes of a wavefront together
+    auto each = [&](auto&& what) {
+        auto some = [&](int l, uint32_t first, uint32_t step) {
+            const PartList& list = own_lists[l];
+            const uint32_t above = of_list(my_above, l), ties = of_list(my_ties, l), tie_key = of_list(my_bound, l);
+#pragma unroll 1
+            for (uint32_t e = first; e < above; e += step) what(e + lane < above, list.word[e + lane < above ? e + lane : 0u]);
+#pragma unroll 1
+            for (uint32_t e = first; e < ties; e += step) what(e + lane < ties, compose(tie_key, list.tie[e + lane < ties ? e + lane : 0u]));
+        };
+#pragma unroll 1
+        for (int q = 0; q < kMine; ++q)
+            if (!((lengthy >> (wave * kMine + q)) & 1ull)) some(wave * kMine + q, 0u, kWave);
+#pragma unroll 1
+        for (unsigned long long left = lengthy; left; left &= left - 1ull) some(__ffsll(left) - 1, (uint32_t)wave * kWave, kBigThreads);
+    };
+    if (whole || first_ties) {
+        // all entries above the bound, and the ties, or the first of them: every word's place is known
+        const uint32_t take = whole ? n_ties : (uint32_t)k - n_above;
+        n = n_above + take;
+        if (threadIdx.x < kParts) {
+            ties_upto[threadIdx.x] = upto_ties;
+            bound_of[threadIdx.x] = my_bound;
+        }
+        __syncthreads();
+        // (a tie's list by bisection: all of a thread's are under way at once, however long the lists are)
+        uint32_t from[kPickCap / kBigThreads], tie_key[kPickCap / kBigThreads];
+#pragma unroll
+        for (int i = 0; i < kPickCap / kBigThreads; ++i) {
+            const uint32_t t = (uint32_t)(i * kBigThreads) + threadIdx.x;
+            from[i] = tie_key[i] = 0;
+            if (t < take) {
+                int l = 0;   // lists that end at or before t
+#pragma unroll
+                for (int step = kParts / 2; step > 0; step >>= 1) l += ties_upto[l + step - 1] <= t ? step : 0;
+                from[i] = own_lists[l].tie[t - (l > 0 ? ties_upto[l - 1] : 0u)];
+                tie_key[i] = bound_of[l];
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kMine; ++q) {
+            const int l = wave * kMine + q;
+            const uint32_t above = of_list(my_above, l), before = of_list(upto_above, l) - above;
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a)
+                if (a * kWave + lane < (int)above) sel[slot(before + a * kWave + lane)] = ahead[q][a];
+        }
+#pragma unroll 1
+        for (unsigned long long left = __ballot(my_above > (uint32_t)(kAhead * kWave)); left; left &= left - 1ull) {
+            const int l = __ffsll(left) - 1;
+            const uint32_t above = of_list(my_above, l), before = of_list(upto_above, l) - above;
+            for (uint32_t e = kAhead * kWave + threadIdx.x; e < above; e += kBigThreads) sel[slot(before + e)] = own_lists[l].word[e];
+        }
+#pragma unroll
+        for (int i = 0; i < kPickCap / kBigThreads; ++i) {
+            const uint32_t t = (uint32_t)(i * kBigThreads) + threadIdx.x;
+            if (t < take) sel[slot(n_above + t)] = compose(tie_key[i], from[i]);
+        }
+    } else {
+        // Narrowed by the keys' digits, then, where one key remains, by its entries' indices: words at or above (lowest, index_lowest).
+        uint32_t not_least = 0, most = 0;
+        each([&](bool there, uint64_t w) {
+            const uint32_t key = (uint32_t)(w >> 32);
+            most = there && key > most ? key : most;
+            not_least = there && ~key > not_least ? ~key : not_least;
+        });
+        note_range(not_least, most, range);
+        __syncthreads();
+        uint32_t lowest = ~range[0] > shown ? ~range[0] : shown, width = range[1] - lowest, rank = (uint32_t)k, index_lowest = 0;
+        bool by_key = true;
+        if (width == 0u) by_key = false, index_lowest = 0xFFFFFFFFu - (uint32_t)(seg.end - 1), width = (uint32_t)(seg.end - seg.begin) - 1u;
+#pragma unroll 1
+        for (;;) {
+            const int shift = next_shift(width);
+            const uint32_t base = by_key ? lowest : index_lowest;
+            for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+            __syncthreads();
+            each([&](bool there, uint64_t w) {
+                const uint32_t x = by_key ? (uint32_t)(w >> 32) : (uint32_t)w;
+                light_hist_add(hist, (x - base) >> shift, there && (by_key || (uint32_t)(w >> 32) == lowest) && x >= base && x - base <= width);
+            });
+            __syncthreads();
+            find_bucket(hist, rank, wave_tot, found);
+            (by_key ? lowest : index_lowest) += found[0] << shift;
+            width = (1u << shift) - 1u;
+            rank = found[1];
+            n = (uint32_t)k - rank + found[2];
+            if (n <= limit) break;
+            if (width == 0u) {   // (an index is one entry's: this was a key)
+                by_key = false;
+                index_lowest = 0xFFFFFFFFu - (uint32_t)(seg.end - 1);
+                width = (uint32_t)(seg.end - seg.begin) - 1u;
+            }
+        }
+        const uint64_t least = ((uint64_t)lowest << 32) | index_lowest;
+        each([&](bool there, uint64_t w) {
+            const unsigned long long in = __ballot(there && w >= least);
+            if (in == 0ull) return;
+            const int leader = __ffsll(in) - 1;
+            uint32_t base = 0;
+            if (lane == leader) base = atomicAdd(&fill, (uint32_t)__popcll(in));
+            const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(in & ((1ull << lane) - 1ull));
+            if (((in >> lane) & 1ull) && to < n) sel[slot(to)] = w;
+        });
+    }
+    // spare words and those behind the last must read as "below everything"
+    const int n_raw = n > 0 ? (int)slot(n - 1u) + 1 : 0;
+    for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
+        if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
+    __syncthreads();
+    write_collection<SORT>(sel, place, hist, &fill, &n_own, (int)n, k, share, part, (uint32_t)k, 0u, ~0u, false, score, idx_out, val_out, s, seg, whole || first_ties);
+}
+
 struct Layout {
-    size_t segs, state, hist, stage, max256, max64, max16, total;
+    size_t segs, state, hist, stage, max256, max64, max16, parts, with_parts, total;
     size_t stage_slots;
     int R;
 };
@@ -1917,7 +2405,7 @@ int64_t span_for(int64_t n, int32_t n_sg)
 // with_block_max: room for the largest key of every 16, 64 and 256 entries (the one part that grows with n, 21 bytes per 64 entries)
 Layout layout(int64_t n, int32_t n_sg, int32_t k, bool with_block_max)
 {
-    (void)k;
+    (void)k;   // (what serves one k serves any)
     Layout L;
     L.R = hist_copies(n_sg);
     // workgroups of a sweep launch: at most 512 whole spans plus one partial span per segment
@@ -1939,6 +2427,8 @@ Layout layout(int64_t n, int32_t n_sg, int32_t k, bool with_block_max)
     L.max64 = with_block_max ? take(((size_t)(n >> 6) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
     L.max16 = with_block_max ? take(((size_t)(n >> 4) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
     L.total = off;
+    L.parts = off;   // (behind what every call needs; without room for it the spans route serves)
+    L.with_parts = off + (with_block_max && n_sg <= kBlocksSegments && n >= kBlocksSparse * (kLevelK + 1) ? round_up((size_t)n_sg * kParts * sizeof(PartList), 256) : 0);
     return L;
 }
 
@@ -1949,12 +2439,12 @@ size_t topk_workspace_bytes(int64_t n, int32_t n_sg, int32_t k)
     if (n < 0) n = 0;
     if (n_sg < 1) n_sg = 1;
     if (k < 1) k = 1;
-    return layout(n, n_sg, k, true).total;
+    return layout(n, n_sg, k, true).with_parts;
 }
 
 
-// what every selection call refuses about its segments and k (host pointers only); *longest: the longest segment
-static int topk_check(const int64_t* seg_off, int32_t n_sg, int32_t k, int64_t* longest)
+// what every selection call refuses about its segments and k (host pointers only); *longest, *shortest: of the segments
+static int topk_check(const int64_t* seg_off, int32_t n_sg, int32_t k, int64_t* longest, int64_t* shortest = nullptr)
 {
     if (!seg_off || n_sg < 1 || n_sg > PRUNER_MAX_SUBGRAPHS || k < 1 || k > PRUNER_MAX_K) return PRUNER_EINVAL;
     if (seg_off[0] != 0) return PRUNER_EINVAL;
@@ -1963,6 +2453,7 @@ static int topk_check(const int64_t* seg_off, int32_t n_sg, int32_t k, int64_t* 
         const int64_t len = seg_off[s + 1] - seg_off[s];
         if (len < k) return PRUNER_EINVAL;
         *longest = len > *longest ? len : *longest;
+        if (shortest) *shortest = s == 0 || len < *shortest ? len : *shortest;
     }
     if (seg_off[n_sg] > 0x7FFFFFFFll) return PRUNER_EINVAL;  // indices are int32
     return PRUNER_OK;
@@ -1971,8 +2462,8 @@ static int topk_check(const int64_t* seg_off, int32_t n_sg, int32_t k, int64_t* 
 int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspace, size_t workspace_bytes, hipStream_t st, TopkCtx* ctx,
                  Upload* defer, bool with_block_max, bool copies)
 {
-    int64_t longest = 0;
-    const int bad = topk_check(seg_off, n_sg, k, &longest);
+    int64_t longest = 0, shortest = 0;
+    const int bad = topk_check(seg_off, n_sg, k, &longest, &shortest);
     if (bad) return bad;
     const int64_t n = seg_off[n_sg];
     if (!workspace || !aligned(workspace, 256)) return PRUNER_EWORKSPACE;
@@ -1985,6 +2476,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     const bool tiny = longest <= kTinyMax && k <= kTinyK;
     const bool levels = with_block_max && !tiny && longest > (defer ? kRow : kCountMax) && k <= kLevelK && longest <= kLevelMax;
     const bool pick = !tiny && !levels && longest <= kPickMax;
+    const bool blocks_route = with_block_max && !tiny && !levels && !pick && n_sg <= kBlocksSegments && longest <= kBlocksMax && shortest >= kBlocksSparse * (int64_t)k && workspace_bytes >= L.with_parts;
     // Segments of up to two rows are counted where they are held as cheaply as by a launch of its own (20 of 30,000, k = 4,096: 44 us
     // either way), unless the draft kernel does it.
     const bool counted = pick && longest > (defer ? kRow : kCountMax);
@@ -2001,12 +2493,13 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
         blocks += (seg_off[s + 1] - seg_off[s] + span - 1) / span;
     }
     // (a population of copies, as the explorer loop keeps it, would have its lists overflow as a rule: it takes the spans route)
-    const bool lists = !tiny && !pick && !levels && longest <= kListsMax && !copies;
+    const bool lists = !tiny && !pick && !levels && !blocks_route && longest <= kListsMax && !copies;
     ctx->tiny = tiny;
     ctx->pick = pick;
     ctx->levels = levels;
+    ctx->blocks_route = blocks_route;
     ctx->lists = lists;
-    ctx->digits = !tiny && !levels && (!pick || counted);
+    ctx->digits = !tiny && !levels && !blocks_route && (!pick || counted);
     ctx->longest = longest;
     ctx->n_sg = n_sg;
     ctx->k = k;
@@ -2018,13 +2511,14 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     ctx->d_state = ws + L.state;
     ctx->d_hist = reinterpret_cast<uint32_t*>(ws + L.hist);
     ctx->d_stage = ws + L.stage;
+    ctx->d_parts = ws + L.parts;
     // Block maxima pay where nearly every block of 256 entries can be stepped over: at most one entry in 1024 selected
     // in the longest segment (with k = 512 of 50,000 nine blocks in ten hold a selected entry and the maxima are one
     // more read: 10.7 -> 11.5 us measured).
     const bool sparse = ctx->digits && !pick && !lists && longest >= (int64_t)k * 1024;
     ctx->d_max16 = levels ? reinterpret_cast<uint32_t*>(ws + L.max16) : nullptr;
     ctx->d_max64 = levels && longest > 16 * (int64_t)kDirectBlocks ? reinterpret_cast<uint32_t*>(ws + L.max64) : nullptr;
-    ctx->d_max256 = with_block_max && (sparse || (levels && longest > 64 * (int64_t)kDirectBlocks)) ? reinterpret_cast<uint32_t*>(ws + L.max256) : nullptr;
+    ctx->d_max256 = with_block_max && (sparse || blocks_route || (levels && longest > 64 * (int64_t)kDirectBlocks)) ? reinterpret_cast<uint32_t*>(ws + L.max256) : nullptr;
     ctx->inline_ok = false;
     static_assert(sizeof(InlineSegs) <= sizeof(ctx->inline_segs), "inline segment table");
     if (!ctx->digits) {
@@ -2090,12 +2584,21 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
 #define PRUNER_PICK(LEVELS, TABLE, SEGS, GHIST, COPIES) \
     hipLaunchKernelGGL((sort ? pick_kernel<LEVELS, true, TABLE> : pick_kernel<LEVELS, false, TABLE>), pickers, dim3(kBigThreads), 0, st, score, SEGS, n_sg, (int)ctx.n, k, share, (Maxima{ctx.d_max16, ctx.d_max64, ctx.d_max256}), GHIST, COPIES, idx_out, val_out)
-    if (ctx.levels) {
+    if (ctx.levels || ctx.blocks_route) {
         if (!noted) {
             const dim3 grid((unsigned)((ctx.longest + 4095) / 4096), (unsigned)n_sg);
             if (ctx.inline_ok) hipLaunchKernelGGL(maxima_kernel<InlineSegs>, grid, dim3(256), 0, st, score, inl, ctx.d_max16, ctx.d_max64, ctx.d_max256);
             else hipLaunchKernelGGL(maxima_kernel<SegsInMemory>, grid, dim3(256), 0, st, score, in_memory, ctx.d_max16, ctx.d_max64, ctx.d_max256);
             PRUNER_LAUNCH_CHECK();
+        }
+        if (ctx.blocks_route) {
+            static_assert(kBlocksSegments <= kInlineSegs, "the segment table travels with the launches");
+            PartList* const parts = static_cast<PartList*>(ctx.d_parts);
+            hipLaunchKernelGGL(block_lists_kernel<InlineSegs>, dim3((unsigned)(n_sg * kParts)), dim3(kBigThreads), 0, st, score, inl, (int)ctx.n, k, ctx.d_max256, parts);
+            PRUNER_LAUNCH_CHECK();
+            hipLaunchKernelGGL((sort ? pick_parts_kernel<true, InlineSegs> : pick_parts_kernel<false, InlineSegs>), pickers, dim3(kBigThreads), 0, st, score, inl, n_sg, k, share, parts, idx_out, val_out);
+            PRUNER_LAUNCH_CHECK();
+            return PRUNER_OK;
         }
         if (ctx.inline_ok) PRUNER_PICK(true, InlineSegs, inl, nullptr, 0);
         else PRUNER_PICK(true, SegsInMemory, in_memory, nullptr, 0);

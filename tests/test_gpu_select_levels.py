@@ -1,6 +1,8 @@
 """Selections by the largest keys of blocks of 16, 64 and 256 neighbours: segment lengths around those at which a level is added, short
 segments beside long ones, k from 1 to all blocks that are held, stretches of good entries, ties within and across blocks, NaN.
 Against the oracle's stable sort, and with the maxima left by the draft kernel against the two separate calls."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -24,6 +26,43 @@ def test_edges_of_the_levels(P, kind, lens, ks):
         check(P, score, seg, k)
 
 
+@pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
+@pytest.mark.parametrize("lens,k", [([787200], 1025), ([787199], 1025), ([1200001, 1075200, 1075203, 1200002], 1400), ([1100001] * 5, 1400), ([3145728, 3145729], 4096), ([5000001], 2000)])
+def test_few_of_long_segments(P, kind, lens, k):
+    """lists of the parts of the best blocks of 256: one entry in 768 and one less, the most segments and one more"""
+    rng = np.random.default_rng(len(kind) + len(lens))
+    check(P, np.concatenate([of(kind, n, rng) for n in lens]), np.concatenate([[0], np.cumsum(lens)]), k)
+
+
+@pytest.mark.parametrize("kind,n", [("latencies", 16777216), ("latencies", 16777217), ("ascending", 16777216)])
+def test_the_longest_segments_by_blocks(P, kind, n):
+    check(P, of(kind, n, np.random.default_rng(3)), np.array([0, n]), 4096)
+
+
+def test_a_workspace_without_room_for_the_lists(P):
+    """the query counts them for any k; with less another route serves"""
+    score = torch.rand(2000000, device="cuda")
+    seg = np.array([0, 900000, 2000000], np.int64)
+    want, want_val = P.topk(score, seg, 1100)
+    need = P.workspace_bytes(P.WS_TOPK, 2000000, 2, 1100)
+    assert need == P.workspace_bytes(P.WS_TOPK, 2000000, 2, 1)
+    ws = torch.empty(need - 256, dtype=torch.uint8, device="cuda")
+    idx, val = torch.empty_like(want), torch.empty_like(want_val)
+    rc = P.load_library().pruner_topk(C.c_void_p(score.data_ptr()), seg.ctypes.data_as(C.POINTER(C.c_int64)), 2, 1100, C.c_void_p(idx.data_ptr()), C.c_void_p(val.data_ptr()),
+                                      C.c_void_p(ws.data_ptr()), C.c_size_t(need - 256), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+    assert rc == 0 and torch.equal(idx, want) and torch.equal(val, want_val)
+
+
+@pytest.mark.parametrize("kind", ["few of either sign", "many negative", "payloads", "all one", "last key"])
+def test_nan_among_the_parts(P, kind):
+    rng = np.random.default_rng(len(kind))
+    seg = np.array([0, 1100001, 2250002], np.int64)
+    score = np.concatenate([with_nan(kind, n, rng) for n in np.diff(seg)])
+    idx, val = P.topk(dev(score), seg, 1030)
+    want = by_bits(score, seg, 1030)
+    assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), score.view(np.uint32)[want])
+
+
 @pytest.mark.parametrize("kind", ["few of either sign", "many positive", "many negative", "payloads", "all one", "last key"])
 @pytest.mark.parametrize("lens", [[32769, 1100], [262145], [1048577]])
 def test_nan_among_the_blocks(P, kind, lens):
@@ -41,7 +80,7 @@ CONV, GEMM, BATCHED = w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), 
 
 @pytest.mark.parametrize("sgs,lens,k", [([GEMM], [16384], 500), ([GEMM], [16385], 500), ([GEMM], [70003], 1024), ([GEMM, CONV], [20001, 30003], 33), ([GEMM, CONV, BATCHED], [16386, 50001, 3], 3),
                                         ([GEMM, CONV, BATCHED], [300001, 200003, 120002], 700), ([CONV, GEMM], [1048580, 17001], 1000), ([CONV], [1048576], 64), ([GEMM], [40000], 4096),
-                                        ([CONV, GEMM, GEMM], [1700001, 900002, 50], 50)])
+                                        ([CONV, GEMM, GEMM], [1700001, 900002, 50], 50), ([GEMM, CONV], [1200003, 1100001], 1050)])
 def test_maxima_left_by_the_draft_kernel(P, sgs, lens, k):
     """one candidate per thread and four, ends of segments inside a block, a population with few distinct scores (GEMM)"""
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
