@@ -9,9 +9,9 @@
 //   tiny   - segments of at most 8192 entries and k up to 64 (the final selection after the verify stage, small draft
 //            populations): one launch, no digits (tiny_select in select_common.h);
 //   pick   - short segments: one launch, in which several workgroups per segment hold it in registers, count the first digit, keep
-//            the few entries at or above rank k's bin, and each rank their share of them (k above kLevelK: also segments of at
+//            the few entries at or above rank k's bin, and each rank their share of them (k above kLevelMostK: also segments of at
 //            most kPickMax entries, behind whoever counted the digit, the draft kernel or a pass);
-//   levels - longer ones, k up to kLevelK: the same launch behind whoever held the scores and left the largest key of every sixteen
+//   levels - longer ones, k up to kLevelMostK: the same launch behind whoever held the scores and left the largest key of every sixteen
 //            neighbours (the draft kernel, else a pass): a workgroup holds the few blocks of sixteen that can matter;
 //   blocks - a larger k of a few segments at least 768 times as long: two launches behind whoever held the scores and left the largest key of every 256 neighbours
 //            (the draft kernel, else a pass): the entries of the best blocks that reach a bound are set aside, and picked;
@@ -963,7 +963,7 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
 // `share` workgroups per segment.  Each holds what can matter of the segment in registers (sixteen entries per thread), collects all
 // entries at or above a bound that at least k entries reach, and ranks those whose index hashes to it among all of them: no lists
 // between launches.
-//   pick: segments of at most kRow entries are held whole, their first digits counted where they lie.  (k above kLevelK: of at most
+//   pick: segments of at most kRow entries are held whole, their first digits counted where they lie.  (k above kLevelMostK: of at most
 // kPickMax entries, read in rows of kRow, the digits counted by the launch before as a rule.)
 //   levels: of longer ones blocks of sixteen neighbours are held.  Whoever held the scores left the largest key of every sixteen (and
 // of every 64 and 256 where segments are long).  The k best entries lie in the k best blocks (by largest key, then in index order):
@@ -986,6 +986,8 @@ constexpr int kXcds = 8;                                        // parts of the 
 constexpr int kPickCap = 8192;                                  // words a workgroup collects
 constexpr int kPickWords = kPickCap + kPickCap / 32 + 4;
 constexpr int kLevelK = 1024;                                   // blocks of sixteen that registers hold
+constexpr int kLevelMostK = kLevelK / 4 * 3;                    // a larger k leaves the bound so little room that it takes every digit: the filter of 400,000, k = 768,
+                                                                // 26.4 us (27 by digits and lists), k = 1,000 39 (27); of 3,000,000 43 (48) and 61 (49); 10 x 300,001 62 (62) and 72 (62)
 static_assert(kLevelK * 16 == kRow, "selected blocks are held as a short segment is");
 constexpr int kDirectBlocks = 16384;                             // up to here all maxima of a level are looked at, above it those in the best of the next
 constexpr int64_t kLevelMax = (int64_t)1 << 25;                 // (every workgroup reads the maxima of the segment's blocks of 256: 512 KB)
@@ -1903,7 +1905,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_lists_kernel(const float* __
 }
 
 // ---- blocks route -------------------------------------------------------------------------------------------------------
-// More than kLevelK of a few long segments, at most one entry in 768: two launches, with the largest keys of 256 neighbours that
+// More than kLevelMostK of a few long segments, at most one entry in 768: two launches, with the largest keys of 256 neighbours that
 // whoever held the scores left.
 //   1. kParts workgroups per segment.  Each finds, for itself, at least k blocks by (maximum, then index), at most kMostBlocks, and goes through its part of
 //      them, neighbours in index order: what exceeds the bound to a list, and the indices of what equals it, in order, to another.
@@ -2428,7 +2430,7 @@ Layout layout(int64_t n, int32_t n_sg, int32_t k, bool with_block_max)
     L.max16 = with_block_max ? take(((size_t)(n >> 4) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
     L.total = off;
     L.parts = off;   // (behind what every call needs; without room for it the spans route serves)
-    L.with_parts = off + (with_block_max && n_sg <= kBlocksSegments && n >= kBlocksSparse * (kLevelK + 1) ? round_up((size_t)n_sg * kParts * sizeof(PartList), 256) : 0);
+    L.with_parts = off + (with_block_max && n_sg <= kBlocksSegments && n >= kBlocksSparse * (kLevelMostK + 1) ? round_up((size_t)n_sg * kParts * sizeof(PartList), 256) : 0);
     return L;
 }
 
@@ -2474,7 +2476,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     SegT* d_segs = reinterpret_cast<SegT*>(ws + L.segs);
     // (without room for maxima: as for a large k)
     const bool tiny = longest <= kTinyMax && k <= kTinyK;
-    const bool levels = with_block_max && !tiny && longest > (defer ? kRow : kCountMax) && k <= kLevelK && longest <= kLevelMax;
+    const bool levels = with_block_max && !tiny && longest > (defer ? kRow : kCountMax) && k <= kLevelMostK && longest <= kLevelMax;
     const bool pick = !tiny && !levels && longest <= kPickMax;
     const bool blocks_route = with_block_max && !tiny && !levels && !pick && n_sg <= kBlocksSegments && longest <= kBlocksMax && shortest >= kBlocksSparse * (int64_t)k && workspace_bytes >= L.with_parts;
     // Segments of up to two rows are counted where they are held as cheaply as by a launch of its own (20 of 30,000, k = 4,096: 44 us

@@ -16,8 +16,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
-@pytest.mark.parametrize("lens,ks", [([32769], [1, 64, 1023, 1024]), ([40001, 16384, 16385, 1024], [65, 1024]), ([262144, 70], [3, 70]), ([262145, 16400], [512, 1024]),
-                                     ([262161] * 3, [33]), ([1048576], [700]), ([1048577, 16385], [1, 1000]), ([33000] * 129, [100])])
+@pytest.mark.parametrize("lens,ks", [([32769], [1, 64, 768, 769, 1024]), ([40001, 16384, 16385, 1024], [65, 1024]), ([262144, 70], [3, 70]), ([262145, 16400], [512, 768, 769]),
+                                     ([262161] * 3, [33]), ([1048576], [700]), ([1048577, 16385], [1, 768, 1000]), ([33000] * 129, [100])])
 def test_edges_of_the_levels(P, kind, lens, ks):
     rng = np.random.default_rng(len(kind) + len(lens))
     seg = np.concatenate([[0], np.cumsum(lens)])
@@ -27,7 +27,7 @@ def test_edges_of_the_levels(P, kind, lens, ks):
 
 
 @pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
-@pytest.mark.parametrize("lens,k", [([787200], 1025), ([787199], 1025), ([1200001, 1075200, 1075203, 1200002], 1400), ([1100001] * 5, 1400), ([3145728, 3145729], 4096), ([5000001], 2000)])
+@pytest.mark.parametrize("lens,k", [([787200], 1025), ([787199], 1025), ([590592], 769), ([1200001, 1075200, 1075203, 1200002], 1400), ([1100001] * 5, 1400), ([3145728, 3145729], 4096), ([5000001], 2000)])
 def test_few_of_long_segments(P, kind, lens, k):
     """lists of the parts of the best blocks of 256: one entry in 768 and one less, the most segments and one more"""
     rng = np.random.default_rng(len(kind) + len(lens))
@@ -69,7 +69,7 @@ def test_nan_among_the_blocks(P, kind, lens):
     rng = np.random.default_rng(len(kind) + sum(lens))
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
     score = np.concatenate([with_nan(kind, n, rng) for n in lens])
-    for k in (30, 1024):
+    for k in (30, 768, 1024):
         idx, val = P.topk(dev(score), seg, k)
         want = by_bits(score, seg, k)
         assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), score.view(np.uint32)[want])
