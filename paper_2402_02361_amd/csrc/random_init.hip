@@ -12,7 +12,7 @@
 // Few candidates: one launch, in which every workgroup makes the tables it needs (ri_direct_kernel).
 // Else two launches: ri_table_kernel writes, for every distinct axis space of the call, the table R -> factors (a few
 // hundred rows as a rule); ri_fill_kernel gives every candidate one draw, one multiply-high and one 8-byte table
-// read per axis, and stores the factors of four neighbouring candidates at a time.  The fill is bound by its stores
+// read per axis, and stores the factors of four or eight neighbouring candidates at a time.  The fill is bound by its stores
 // (2 bytes per slot and candidate).
 #include "common.h"
 
@@ -107,6 +107,7 @@ struct RiTables {
 };
 constexpr int64_t kDirectMax = 1 << 16;   // candidates
 constexpr int kDirectRows = 1024;         // of a segment's tables
+constexpr int64_t kWideFill = 1 << 20;    // candidates from which a thread fills eight (fewer leave compute units idle, and are as fast with four)
 
 __global__ void __launch_bounds__(kFillThreads) ri_direct_kernel(RiTables /* read through the argument segment, below */, int axes_at, int segs_at, uint16_t* __restrict__ tiles,
                                                                  int64_t pitch, int rows, uint64_t seed)
@@ -154,9 +155,20 @@ __global__ void __launch_bounds__(kFillThreads) ri_direct_kernel(RiTables /* rea
     for (; slot < rows; ++slot) at[(int64_t)slot * pitch] = 0;   // rows the subgraph does not own
 }
 
-// VEC neighbouring candidates per thread, stored VEC at a time (the stores are what this kernel costs); blockIdx.y =
+// VEC neighbouring candidates per thread, stored VEC at a time (the stores are what this kernel costs: 21 M candidates, 838 MB, in
+// eight-byte stores 156 us, in sixteen-byte ones 129.5, 6.5 TB/s; non-temporal ones were slower); blockIdx.y =
 // subgraph.  VEC > 1 needs a pitch that is a multiple of VEC and a population aligned to 2 VEC bytes; a thread's
 // candidates start at a multiple of VEC, and the threads at a segment's ragged ends store one by one.
+template <int VEC> __device__ __forceinline__ void store_factors(uint16_t* at, const uint16_t (&v)[VEC])
+{
+    if constexpr (VEC > 1) {
+        typedef uint32_t Words __attribute__((ext_vector_type(VEC / 2)));
+        Words w;
+#pragma unroll
+        for (int e = 0; e < VEC / 2; ++e) w[e] = (uint32_t)v[2 * e] | ((uint32_t)v[2 * e + 1] << 16);
+        *reinterpret_cast<Words*>(at) = w;
+    }
+}
 template <int VEC>
 __global__ void __launch_bounds__(kFillThreads) ri_fill_kernel(const RiSeg* __restrict__ segs, const RiAxis* __restrict__ axes,
                                                                const uint2* __restrict__ table, uint16_t* __restrict__ tiles, int64_t pitch,
@@ -188,11 +200,7 @@ __global__ void __launch_bounds__(kFillThreads) ri_fill_kernel(const RiSeg* __re
                 for (int e = 0; e < VEC; ++e) v[e] = (uint16_t)((l < 2 ? f[e].x : f[e].y) >> (16 * (l & 1)));
                 uint16_t* at = tiles + (int64_t)(slot + l) * pitch + c0;
                 if (whole) {
-                    uint64_t w = 0;
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) w |= (uint64_t)v[e] << (16 * e);
-                    if constexpr (VEC == 4) *reinterpret_cast<uint64_t*>(at) = w;
-                    else if constexpr (VEC == 2) *reinterpret_cast<uint32_t*>(at) = (uint32_t)w;
+                    store_factors<VEC>(at, v);
                 } else {
 #pragma unroll
                     for (int e = 0; e < VEC; ++e)
@@ -205,8 +213,8 @@ __global__ void __launch_bounds__(kFillThreads) ri_fill_kernel(const RiSeg* __re
     for (; slot < rows; ++slot) {   // rows the subgraph does not own
         uint16_t* at = tiles + (int64_t)slot * pitch + c0;
         if (whole) {
-            if constexpr (VEC == 4) *reinterpret_cast<uint64_t*>(at) = 0ull;
-            else if constexpr (VEC == 2) *reinterpret_cast<uint32_t*>(at) = 0u;
+            const uint16_t none[VEC] = {};
+            store_factors<VEC>(at, none);
         } else {
 #pragma unroll
             for (int e = 0; e < VEC; ++e)
@@ -405,7 +413,10 @@ extern "C" int pruner_random_init(const pruner_subgraph* sg, int32_t n_sg, const
                        reinterpret_cast<const RiSpace*>(ws + L.spaces), table);
     PRUNER_LAUNCH_CHECK();
     // (a segment that does not begin at a multiple of the vector width needs one thread more)
-    if (tiles_pitch % 4 == 0 && aligned(tiles, 8))
+    if (n >= kWideFill && tiles_pitch % 8 == 0 && aligned(tiles, 16))
+        hipLaunchKernelGGL(ri_fill_kernel<8>, dim3((unsigned)((longest + 8 + 8 * kFillThreads - 1) / (8 * kFillThreads)), (unsigned)n_sg), dim3(kFillThreads), 0, st,
+                           reinterpret_cast<const RiSeg*>(ws + L.segs), reinterpret_cast<const RiAxis*>(ws + L.axes), table, tiles, tiles_pitch, (int)tile_rows, seed);
+    else if (tiles_pitch % 4 == 0 && aligned(tiles, 8))
         hipLaunchKernelGGL(ri_fill_kernel<4>, dim3((unsigned)((longest + 4 + 4 * kFillThreads - 1) / (4 * kFillThreads)), (unsigned)n_sg),
                            dim3(kFillThreads), 0, st, reinterpret_cast<const RiSeg*>(ws + L.segs), reinterpret_cast<const RiAxis*>(ws + L.axes), table,
                            tiles, tiles_pitch, (int)tile_rows, seed);

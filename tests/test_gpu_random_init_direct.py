@@ -22,3 +22,15 @@ def test_one_launch_and_three(P, sgs, lens):
     P.random_init(sgs, seg, rows, 41, tiles=tiles)
     got = tiles.cpu().numpy()
     assert np.array_equal(got[:, :n], oracle.random_init(sgs, seg, rows, seed=41)) and (got[:, n:] == 0xFFFF).all()
+
+
+@pytest.mark.parametrize("lens,pad", [([1048576], 0), ([524289, 0, 524290], 5), ([7, 1048000, 590], 3), ([1048577], 3)])
+def test_eight_candidates_per_thread(P, lens, pad):
+    """from 2^20 candidates on, rows of whole groups of eight; ragged segments, and a pitch that leaves groups of four (the last)"""
+    sgs = [CONV, FRAGMENTS, GEMM][: len(lens)]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n, rows = int(seg[-1]), max(w.n_slots(s) for s in sgs) + 1
+    tiles = torch.full((rows, (n + pad) // 4 * 4), 0xFFFF, dtype=torch.uint16, device="cuda")
+    P.random_init(sgs, seg, rows, 43, tiles=tiles)
+    got = tiles.cpu().numpy()
+    assert np.array_equal(got[:, :n], oracle.random_init(sgs, seg, rows, seed=43)) and (got[:, n:] == 0xFFFF).all()
