@@ -29,8 +29,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 # HBM bytes per launch of the draft kernel from rocprofv3 counters (profiles/draft_kernel_cfg4_traffic.txt), valid for
 # the kernel source with this SHA-256 only; any other source reports null.
-MEASURED_TRAFFIC = {"workload": "cfg4_stress_gemm4096_dwconv_20M", "source_sha256": "699e75caccf56bcd85af3c90fd041cb02c6a345f2d689bf039d693e5902d8562",
-                    "bytes": 590905627, "dominant_bytes": 404877572}
+MEASURED_TRAFFIC = {"workload": "cfg4_stress_gemm4096_dwconv_20M", "source_sha256": "6821119d1c36b222b6c8ea3498d7a1fb273717219d029f2d6e0e413f7fa64669",
+                    "bytes": 588269826, "dominant_bytes": 403343876}
 
 
 def draft_traffic(workload, which="bytes"):
@@ -320,7 +320,7 @@ def main():
                      "bound": "hbm", "achieved": dom_gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": dom_gbs / HBM_PEAK_GBS,
                      "traffic": draft_traffic(wl.name, "dominant_bytes"), "algorithmic_bytes": dominant_bytes.value,
                      "avg_launch_ms": ms_dominant},
-        "roofline_draft_stage": {"what": "all of pruner_draft_score's launches: table upload + one draft_kernel launch per loop-nest class, "
+        "roofline_draft_stage": {"what": "all of pruner_draft_score's launches: one draft_kernel launch per loop-nest class, behind a table upload where the tables do not travel with them, "
                                          "with the gaps between them", "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS,
                                  "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": draft_traffic(wl.name),
                                  "algorithmic_bytes": abytes, "avg_ms": ms_draft},
