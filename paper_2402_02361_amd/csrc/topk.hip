@@ -13,7 +13,7 @@
 //            most kPickMax entries, behind whoever counted the digit, the draft kernel or a pass);
 //   levels - longer ones, k up to kLevelMostK: the same launch behind whoever held the scores and left the largest key of every sixteen
 //            neighbours (the draft kernel, else a pass): a workgroup holds the few blocks of sixteen that can matter;
-//   blocks - a larger k of a few segments at least 768 times as long: two launches behind whoever held the scores and left the largest key of every 256 neighbours
+//   blocks - a larger k of a few segments at least 768 times as long, or segments longer than kLevelMax: two launches behind whoever held the scores and left the largest key of every 256 neighbours
 //            (the draft kernel, else a pass): the entries of the best blocks that reach a bound are set aside, and picked;
 //   lists  - a larger k, segments of at most kListsMax: as pick, behind one more launch that goes through the spans of the segments (whole
 //            16384-entry sweeps, one workgroup each) and sets the entries at or above the bin aside in a list per span; the
@@ -1006,7 +1006,8 @@ constexpr int kLevelMostK = kLevelK / 4 * 3;                    // a larger k le
                                                                 // 26.4 us (27 by digits and lists), k = 1,000 39 (27); of 3,000,000 43 (48) and 61 (49); 10 x 300,001 62 (62) and 72 (62)
 static_assert(kLevelK * 16 == kRow, "selected blocks are held as a short segment is");
 constexpr int kDirectBlocks = 16384;                             // up to here all maxima of a level are looked at, above it those in the best of the next
-constexpr int64_t kLevelMax = (int64_t)1 << 25;                 // (every workgroup reads the maxima of the segment's blocks of 256: 512 KB)
+constexpr int64_t kLevelMax = 256 * (int64_t)kDirectBlocks;     // three levels at most, the top one held.  The filter of 4 M, k = 512, 44 us (51 by digits), of 9.3 M 107 (93; 92 by
+                                                                // the blocks of 256)
 // What is collected is ranked word against word, so it has to be little more than k: otherwise the bin is split first (two
 // values shared by 20,000 entries, k = 512: 84 us with all of the bin ranked, 25 with the limit).
 __host__ __device__ constexpr int collect_limit(int k) { return k + k / 4 + 256; }
@@ -1921,7 +1922,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_lists_kernel(const float* __
 }
 
 // ---- blocks route -------------------------------------------------------------------------------------------------------
-// More than kLevelMostK of a few long segments, at most one entry in 768: two launches, with the largest keys of 256 neighbours that
+// What the levels route leaves (k above kLevelMostK, or a segment above kLevelMax) of a few long segments, at most one entry in 768: two launches, with the largest keys of 256 neighbours that
 // whoever held the scores left.
 //   1. kParts workgroups per segment.  Each finds, for itself, at least k blocks by (maximum, then index), at most kMostBlocks, and goes through its part of
 //      them, neighbours in index order: what exceeds the bound to a list, and the indices of what equals it, in order, to another.
