@@ -1230,7 +1230,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
 // The n words in sel to the rows (those below row_len = k) of one segment: ranked in rounds of 64 per workgroup, the words shared out over the
 // segment's workgroups, or sorted, all of them by every workgroup, whatever costs less (see kSortFactor).
 // SORT: with the way of sorting (the other calls' kernel is shorter without it).  k_rem of the words with keys lowest .. lowest + width
-// are selected, and all above; exact: these two facts are, so that the sort may leave the surplus out.  same_places: the words lie in the same
+// are selected, and all above; exact: these two facts are, and no word lies below, so that the sort may leave the surplus out.  same_places: the words lie in the same
 // places in every workgroup, which are dealt out in turn (by the hash some have half as many again as others, and with them a round more:
 // 5,179 words, 128 workgroups, 40 each: 23.5 us, dealt out 15.0).
 template <bool SORT>
@@ -1669,7 +1669,8 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
     }
     if (SORT && !exact && n > k && pow2_at_least(n) > pow2_at_least(k)) {
-        // what the sort may leave out: the words up to the end of rank k's bin that are not selected
+        // what the sort may leave out: the words up to the end of rank k's bin that are not selected, whatever lies below the bin
+        // included (the comparison lets every NaN in, those with the sign bit below every bound)
         for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
         __syncthreads();   // (and the words are there)
         for (int e = threadIdx.x; e < n; e += kBigThreads) atomicAdd(&hist[first_digit_of((uint32_t)(sel[slot((uint32_t)e)] >> 32))], 1u);
@@ -1677,7 +1678,8 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         find_bucket(hist, (uint32_t)k, wave_tot, found);
         uint32_t bin_lowest, bin_width;
         first_digit_range(found[0], bin_lowest, bin_width);
-        width = bin_lowest + bin_width - lowest;
+        lowest = 0;
+        width = bin_lowest + bin_width;
         k_rem = found[1];
         exact = true;
     }

@@ -17,7 +17,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
 @pytest.mark.parametrize("lens,ks", [([32769], [1, 64, 768, 769, 1024]), ([40001, 16384, 16385, 1024], [65, 1024]), ([262144, 70], [3, 70]), ([262145, 16400], [512, 768, 769]),
-                                     ([262161] * 3, [33]), ([1048576], [700]), ([1048577, 16385], [1, 768, 1000]), ([33000] * 129, [100])])
+                                     ([262161] * 3, [33]), ([1048576], [700]), ([1048577, 16385], [1, 768, 1000]), ([33000] * 129, [100, 256, 512])])
 def test_edges_of_the_levels(P, kind, lens, ks):
     rng = np.random.default_rng(len(kind) + len(lens))
     seg = np.concatenate([[0], np.cumsum(lens)])
@@ -73,6 +73,26 @@ def test_nan_among_the_blocks(P, kind, lens):
         idx, val = P.topk(dev(score), seg, k)
         want = by_bits(score, seg, k)
         assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), score.view(np.uint32)[want])
+
+
+@pytest.mark.parametrize("n_sg,n,k", [(90, 33000, 400), (90, 40000, 512), (130, 33000, 256), (130, 40000, 400), (130, 33000, 512)])
+def test_nan_among_sorted_words(P, n_sg, n, k):
+    """many segments, whose collections are sorted and not ranked: the surplus that the sort leaves out is found with NaN below the
+    bound among the words, the scores spread over enough octaves that rank k's bin holds few"""
+    rng = np.random.default_rng(n_sg + k)
+    seg = np.arange(n_sg + 1, dtype=np.int64) * n
+    score = (-np.exp2(rng.uniform(-20, -3, n_sg * n))).astype(np.float32)
+    bits = score.view(np.uint32)
+    for s in range(n_sg):
+        some = s * n + rng.permutation(n)
+        bits[some[:40]] = 0xFFC00000
+        if s % 3 == 0:
+            bits[some[40:45]] = 0x7FC00000
+        if s % 5 == 0:
+            bits[some[45:90]] = 0xFFFFFFFF
+    idx, val = P.topk(dev(score), seg, k)
+    want = by_bits(score, seg, k)
+    assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), bits[want])
 
 
 CONV, GEMM, BATCHED = w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64)
