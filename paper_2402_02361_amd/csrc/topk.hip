@@ -187,7 +187,8 @@ __device__ __forceinline__ void rank_rows(const uint64_t* sel, int k, const uint
         if (c) atomicAdd(&cnt[mine_at], c);
         if (d) atomicAdd(&cnt[kWave + lane], d);
         __syncthreads();
-        if (wave == 0 ? lane < R && mine != ~0ull : pairs && wave == 1 && other != ~0ull) {   // (no word is all ones: an index is below 2^31)
+        // (by number: a word of ones throughout is an entry, the largest key at index 0)
+        if (wave == 0 ? lane < R && e0 + lane < n : pairs && wave == 1 && e0 + kWave + lane < n) {
             const uint64_t word = wave == 0 ? mine : other;
             const uint32_t r = cnt[wave * kWave + lane], gi = index_of(word);
             if (r < (uint32_t)row_len) {

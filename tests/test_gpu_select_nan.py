@@ -54,3 +54,17 @@ def test_nan_by_its_bits(P, kind, lens, ks):
         want = by_bits(score, seg, k)
         assert np.array_equal(idx.cpu().numpy(), want), (kind, k)
         assert np.array_equal(val.cpu().numpy().view(np.uint32), score.view(np.uint32)[want])
+
+
+@pytest.mark.parametrize("n,k", [(300, 40), (4000, 65), (8000, 64), (30000, 300), (40000, 100), (65536, 3000), (100001, 1000), (270000, 100), (1100001, 1025), (3000001, 4096)])
+def test_the_largest_word_of_all(P, n, k):
+    """the largest key at index 0: a word of ones throughout is a word like any other"""
+    score = (-np.exp2(np.random.default_rng(n).uniform(-26, -3, n))).astype(np.float32)
+    bits = score.view(np.uint32)
+    bits[0] = 0x7FFFFFFF
+    seg = np.array([0, n], np.int64)
+    want = by_bits(score, seg, k)
+    idx, val = torch.full((1, k), -1, dtype=torch.int32, device="cuda"), torch.zeros((1, k), dtype=torch.float32, device="cuda")
+    for call in (P.topk, P.topk_static):
+        call(dev(score), seg, k, idx.fill_(-1), val.fill_(0))
+        assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), bits[want])
