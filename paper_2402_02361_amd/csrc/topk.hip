@@ -1644,6 +1644,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
         if (exact ? collected == expected : collected <= limit) break;
         __syncthreads();
         if (threadIdx.x == 0) fill = 0;
+        __syncthreads();   // (what is known by count is collected again at once)
         if (!exact) in_bin = collected;
     }
     if (ties_apart && part == 0) {

@@ -44,7 +44,7 @@ def scores(kind, n, rng):
 
 @pytest.mark.parametrize("kind", ["one", "few of either sign", "many positive", "many negative", "payloads", "all one", "last key", "a crowded bin"])
 @pytest.mark.parametrize("lens,ks", [([8000, 70], [1, 64]), ([4000, 300], [65, 300]), ([50001] * 3, [30, 512]), ([65536], [4096]), ([100001, 65537], [33, 4096]), ([500000], [512, 4096]),
-                                     ([700001, 5000], [33, 4096]), ([3000001], [512])])
+                                     ([700001, 5000], [33, 4096]), ([3000001], [512]), ([1500] * 300, [100])])
 def test_nan_by_its_bits(P, kind, lens, ks):
     rng = np.random.default_rng(len(kind) + sum(lens))
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
