@@ -24,6 +24,7 @@
 //            256 whose largest key lies below the bin are not read again) and the later passes work on what was set aside
 //            (where the bin holds too much for that, the second digit is counted first: one more reading); six launches.
 #include "select_common.h"
+#include "wide_load.h"
 
 #include <string.h>
 
@@ -1320,8 +1321,8 @@ __device__ __forceinline__ uint32_t best_blocks(const uint32_t* __restrict__ max
     const int n_quads = n_parents > 0 ? n_parents : (n + 3) >> 2;
     const int of = n_quads > 3 * kBigThreads ? 4 : n_quads > 2 * kBigThreads ? 3 : n_quads > kBigThreads ? 2 : 1, rows = (n_quads + of * kBigThreads - 1) / (of * kBigThreads);
     auto first = [&](int q) -> int { return n_parents > 0 ? 4 * (int)parents[q] : 4 * q; };
-    uint32_t v[4 * kQuads];
-    int n_mine = 0;   // quads of this thread
+    uint32_t v[4 * kQuads], held = 0;   // held: the maxima among them, as bits
+    int n_mine = 0;                     // quads of this thread
     auto load = [&](int row) {
         const int q0 = (row * kBigThreads + (int)threadIdx.x) * of;
         n_mine = n_quads - q0 < of ? n_quads - q0 : of;
@@ -1333,6 +1334,7 @@ __device__ __forceinline__ uint32_t best_blocks(const uint32_t* __restrict__ max
         for (int j = 0; j < kQuads; ++j)
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[4 * j + e] = j < of && j < n_mine ? w[j][e] : 0u;
+        held = maxima_held(n_mine, first(q0 + n_mine - 1), n);   // (without quads: n_quads - 1, which is there)
     };
     if (rows == 1) load(0);
     // maxima of sixteen and of four of the maxima serve as well where there are enough of them
@@ -1402,12 +1404,11 @@ __device__ __forceinline__ uint32_t best_blocks(const uint32_t* __restrict__ max
 #pragma unroll
                 for (int e = 0; e < 4; ++e) mask |= v[4 * j + e] >= lowest ? 1u << (4 * j + e) : 0u;
             }
-            const uint32_t there = n_mine > 0 ? (1u << (4 * n_mine)) - 1u : 0u;
-            mask &= there;
+            mask &= held;
             if (ties_apart) {
 #pragma unroll
                 for (int j = 0; j < 4 * kQuads; ++j) equal |= v[j] == lowest ? 1u << j : 0u;
-                equal &= there;
+                equal &= held;
                 mask ^= equal;
                 uint32_t number = ties_before + block_excl_scan<kBigThreads>((uint32_t)__popc(equal), wave_tot, &total);
 #pragma unroll 1
@@ -1432,7 +1433,7 @@ __device__ __forceinline__ uint32_t best_blocks(const uint32_t* __restrict__ max
             if (rows > 1) load(row);
 #pragma unroll
             for (int j = 0; j < 4 * kQuads; ++j) {
-                const bool in = (j >> 2) < n_mine && v[j] >= lowest;
+                const bool in = ((held >> j) & 1u) != 0u && v[j] >= lowest;
                 not_least = in && ~v[j] > not_least ? ~v[j] : not_least;
                 largest = in && v[j] > largest ? v[j] : largest;
             }

@@ -95,6 +95,18 @@ def test_nan_among_sorted_words(P, n_sg, n, k):
     assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), bits[want])
 
 
+@pytest.mark.parametrize("n", [262161, 1048581, 1049601, 4194299])
+def test_a_bound_below_every_number(P, n):
+    """fewer than k blocks with anything but the least key of all, so that every block reaches the bound"""
+    score = np.full(n, 0xFFFFFFFF, np.uint32).view(np.float32)
+    score[np.random.default_rng(n).permutation(n)[:20]] = -1.5
+    seg = np.array([0, n], np.int64)
+    for k in (30, 256, 700):
+        idx, val = P.topk(dev(score), seg, k)
+        want = by_bits(score, seg, k)
+        assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), score.view(np.uint32)[want])
+
+
 CONV, GEMM, BATCHED = w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64)
 
 
