@@ -154,9 +154,9 @@ int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tile
               const ScoreNotes& notes, const MutArgs* mut);
 // workspace needs of the entry points (each defined next to its kernels)
 size_t draft_workspace_bytes(int32_t n_sg);
-size_t topk_workspace_bytes(int64_t n, int32_t n_sg, int32_t k);
+size_t topk_workspace_bytes(int64_t n, int32_t n_sg, int32_t k, bool parts);   // parts: with room for the lists of the blocks route, which a call can do without
 size_t verify_workspace_bytes(int64_t n_d);
-size_t prior_filter_workspace_bytes(int64_t n, int32_t n_sg, int32_t k);
+size_t prior_filter_workspace_bytes(int64_t n, int32_t n_sg, int32_t k, bool parts);
 size_t lse_workspace_bytes(int64_t n, int32_t n_sg, int32_t k, int32_t rows);
 size_t pacm_workspace_bytes(int64_t n_d);
 

@@ -778,7 +778,8 @@ struct LseLayout {
     size_t filter, table, best_idx, best_val, zero_count, alt_count, keys[2], fresh, fresh_aos, merged, aos, aos_b, children, total;
 };
 
-LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
+// parts: with room for the lists of the selection's blocks route
+LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows, bool parts)
 {
     LseLayout L;
     size_t off = 0;
@@ -788,7 +789,7 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
         return at;
     };
     const size_t cols = (size_t)n_sg * (size_t)k;
-    L.filter = take(prior_filter_workspace_bytes(n, n_sg, k));
+    L.filter = take(prior_filter_workspace_bytes(n, n_sg, k, parts));
     L.table = take((size_t)n_sg * sizeof(LseSeg));
     L.best_idx = take(cols * sizeof(int32_t));
     L.best_val = take(cols * sizeof(float));
@@ -822,7 +823,7 @@ size_t lse_workspace_bytes(int64_t n, int32_t n_sg, int32_t k, int32_t rows)
     if (n_sg < 1) n_sg = 1;
     if (k < 1) k = 1;
     if (rows < 1) rows = 1;
-    return lse_layout(n, n_sg, k, rows).total;
+    return lse_layout(n, n_sg, k, rows, true).total;
 }
 
 }  // namespace pruner
@@ -841,7 +842,8 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     if (!workspace || !aligned(workspace, 256)) return PRUNER_EWORKSPACE;
     const int64_t n = seg_off[n_sg];
     if (n < 0 || n > 0x7FFFFFFFll) return PRUNER_EINVAL;
-    const LseLayout L = lse_layout(n, n_sg, k, tile_rows);
+    LseLayout L = lse_layout(n, n_sg, k, tile_rows, true);
+    if (workspace_bytes < L.total) L = lse_layout(n, n_sg, k, tile_rows, false);   // (the selection then takes another route)
     if (workspace_bytes < L.total) return PRUNER_EWORKSPACE;
     char* ws = static_cast<char*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);

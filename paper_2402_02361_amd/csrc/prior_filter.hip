@@ -8,9 +8,9 @@
 
 namespace pruner {
 
-size_t prior_filter_workspace_bytes(int64_t n, int32_t n_sg, int32_t k)
+size_t prior_filter_workspace_bytes(int64_t n, int32_t n_sg, int32_t k, bool parts)
 {
-    return round_up(draft_workspace_bytes(n_sg), 256) + topk_workspace_bytes(n, n_sg, k);
+    return round_up(draft_workspace_bytes(n_sg), 256) + topk_workspace_bytes(n, n_sg, k, parts);
 }
 
 }  // namespace pruner

@@ -2426,7 +2426,11 @@ int64_t span_for(int64_t n, int32_t n_sg)
     return kRow * ((sweeps + 511) / 512);
 }
 
-// with_block_max: room for the largest key of every 16, 64 and 256 entries (the one part that grows with n, 21 bytes per 64 entries)
+// with_block_max: room for the largest key of every 16, 64 and 256 entries (the one part that grows with n, 21 bytes per 64 entries).
+// A call has histograms and staged entries, or the finer maxima, or the lists of parts: they lie in the same place, and no call
+// needs more than it did with the digits alone, up to some 17 million entries.
+// total: what a call cannot do without; with_parts: what it takes for the blocks route as well, for as many of the segments as that
+// route serves, so that room for more segments serves fewer of them by the same route.
 Layout layout(int64_t n, int32_t n_sg, int32_t k, bool with_block_max)
 {
     (void)k;   // (what serves one k serves any)
@@ -2443,27 +2447,32 @@ Layout layout(int64_t n, int32_t n_sg, int32_t k, bool with_block_max)
     };
     L.segs = take((size_t)n_sg * sizeof(SegT));
     L.state = take((size_t)3 * n_sg * sizeof(SelState));
+    // (three words more: the maxima are read in fours)
+    L.max256 = with_block_max ? take(((size_t)(n >> 8) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
+    const size_t shared = off;
     L.hist = take(((size_t)L.R + 2) * n_sg * kBins * sizeof(uint32_t));   // first digit in R copies, one each for the others
     L.stage = take(blocks * sizeof(Stage));
     L.stage_slots = blocks;
-    // (three words more: the maxima are read in fours)
-    L.max256 = with_block_max ? take(((size_t)(n >> 8) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
+    L.total = off;
+    off = shared;
     L.max64 = with_block_max ? take(((size_t)(n >> 6) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
     L.max16 = with_block_max ? take(((size_t)(n >> 4) + (size_t)n_sg + 4) * sizeof(uint32_t)) : 0;
-    L.total = off;
-    L.parts = off;   // (behind what every call needs; without room for it the spans route serves)
-    L.with_parts = off + (with_block_max && n_sg <= kBlocksSegments && n >= kBlocksSparse * (kLevelMostK + 1) ? round_up((size_t)n_sg * kParts * sizeof(PartList), 256) : 0);
+    L.total = off > L.total ? off : L.total;
+    off = shared;
+    L.parts = with_block_max && n >= kBlocksSparse * (kLevelMostK + 1) ? take((size_t)(n_sg < kBlocksSegments ? n_sg : kBlocksSegments) * kParts * sizeof(PartList)) : shared;
+    L.with_parts = off > L.total ? off : L.total;
     return L;
 }
 
 }  // namespace
 
-size_t topk_workspace_bytes(int64_t n, int32_t n_sg, int32_t k)
+size_t topk_workspace_bytes(int64_t n, int32_t n_sg, int32_t k, bool parts)
 {
     if (n < 0) n = 0;
     if (n_sg < 1) n_sg = 1;
     if (k < 1) k = 1;
-    return layout(n, n_sg, k, true).with_parts;
+    const Layout L = layout(n, n_sg, k, true);
+    return parts ? L.with_parts : L.total;
 }
 
 

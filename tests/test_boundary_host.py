@@ -56,6 +56,9 @@ def test_a_workspace_serves_every_smaller_call():
         for n_sg in (1, 2, 8, 20, 300):
             need = np.array([[P.workspace_bytes(which, n, n_sg, k) for k in ks] for n in sizes])
             assert np.all(np.diff(need, axis=0) >= 0) and np.all(np.diff(need, axis=1) >= 0), (which, n_sg)
+        for n in sizes:
+            for k in (1, 512, 768, 769, 4096):
+                assert np.all(np.diff([P.workspace_bytes(which, n, n_sg, k) for n_sg in range(1, 17)]) >= 0), (which, n, k)
     for which in (P.WS_VERIFY, P.WS_PACM):
         assert np.all(np.diff([P.workspace_bytes(which, n, 0, 0) for n in sizes]) >= 0)
 

@@ -14,6 +14,8 @@ from test_gpu_select_shapes import check, of
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
+CONV, GEMM, BATCHED = w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64)
+
 
 @pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
 @pytest.mark.parametrize("lens,ks", [([32769], [1, 64, 768, 769, 1024]), ([40001, 16384, 16385, 1024], [65, 1024]), ([262144, 70], [3, 70]), ([262145, 16400], [512, 768, 769]),
@@ -51,6 +53,30 @@ def test_a_workspace_without_room_for_the_lists(P):
     rc = P.load_library().pruner_topk(C.c_void_p(score.data_ptr()), seg.ctypes.data_as(C.POINTER(C.c_int64)), 2, 1100, C.c_void_p(idx.data_ptr()), C.c_void_p(val.data_ptr()),
                                       C.c_void_p(ws.data_ptr()), C.c_size_t(need - 256), C.c_void_p(torch.cuda.current_stream().cuda_stream))
     assert rc == 0 and torch.equal(idx, want) and torch.equal(val, want_val)
+
+
+@pytest.mark.parametrize("k", [512, 1030])
+def test_the_loop_in_a_workspace_for_other_calls(P, k):
+    """one allocated for five subgraphs serves four and two, and one without room for the lists another route"""
+    lens = [850001, 800003]
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    n, sgs = int(seg[-1]), [GEMM, CONV]
+    arr, start = P.to_c_subgraphs(sgs), P.random_init(sgs, seg, max(w.n_slots(s) for s in sgs), 9)
+    need = P.workspace_bytes(P.WS_LSE, n, 2, k)
+    for_five = P.workspace_bytes(P.WS_LSE, n, 5, k)
+    assert need <= P.workspace_bytes(P.WS_LSE, n, 4, k) <= for_five
+    want = None
+    for size in (need, for_five, need - 256):
+        tiles, score = start.clone(), torch.empty(n, dtype=torch.float32, device="cuda")
+        spec_tiles, spec_score = torch.empty((tiles.shape[0], 2 * k), dtype=torch.uint16, device="cuda"), torch.empty(2 * k, dtype=torch.float32, device="cuda")
+        count, ws = torch.empty(2, dtype=torch.int32, device="cuda"), torch.empty(size, dtype=torch.uint8, device="cuda")
+        p = lambda t: C.c_void_p(t.data_ptr())
+        rc = P.load_library().pruner_lse(arr, 2, seg.ctypes.data_as(C.POINTER(C.c_int64)), p(tiles), n, tiles.shape[0], 0, k, 3, 5, 40000, p(score), p(spec_tiles), p(spec_score), p(count),
+                                         p(ws), C.c_size_t(size), C.c_void_p(torch.cuda.current_stream().cuda_stream))
+        assert rc == 0
+        got = [t.cpu().numpy() for t in (tiles, score, spec_tiles, spec_score, count)]
+        want = want or got
+        assert all(np.array_equal(a, b) for a, b in zip(got, want))
 
 
 @pytest.mark.parametrize("kind", ["few of either sign", "many negative", "payloads", "all one", "last key"])
@@ -105,9 +131,6 @@ def test_a_bound_below_every_number(P, n):
         idx, val = P.topk(dev(score), seg, k)
         want = by_bits(score, seg, k)
         assert np.array_equal(idx.cpu().numpy(), want) and np.array_equal(val.cpu().numpy().view(np.uint32), score.view(np.uint32)[want])
-
-
-CONV, GEMM, BATCHED = w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), w.batched_gemm(12, 128, 128, 64)
 
 
 @pytest.mark.parametrize("sgs,lens,k", [([GEMM], [16384], 500), ([GEMM], [16385], 500), ([GEMM], [70003], 1024), ([GEMM, CONV], [20001, 30003], 33), ([GEMM, CONV, BATCHED], [16386, 50001, 3], 3),
