@@ -208,10 +208,12 @@ constexpr int kInlineSegs = 128;
 struct InlineSegs {
     SegT s[kInlineSegs];
     __device__ __forceinline__ SegT at(int i) const { return s[i]; }
+    __device__ __forceinline__ const SegT* table() const { return s; }
 };
 struct SegsInMemory {
     const SegT* segs;
     __device__ __forceinline__ SegT at(int i) const { return segs[i]; }
+    __device__ __forceinline__ const SegT* table() const { return segs; }
 };
 
 // ---- tiny route: segments of at most 8192 entries, k at most 64 ---------------------------------------------------
@@ -1694,14 +1696,18 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
     write_collection<SORT>(sel, place, hist, &fill, &n_own, n, k, share, part, k_rem, lowest, width, exact, score, idx_out, val_out, s, seg);
 }
 
-// The largest keys of blocks (those that are asked for), for scores that nobody has held before.  Bound by the scores' way from memory.
+// The largest keys of blocks (those that are asked for), for scores that nobody has held before: a workgroup to kMaximaChunk entries of
+// a segment (first_block counts these).  Bound by the scores' way from memory.  (A grid of segments by the longest one's chunks
+// began workgroups by the million where one segment is long among many: 1,000 of 1,000 and one of 4 M 1,762 us, 160 before there were
+// maxima.)
+constexpr int kMaximaChunk = 4096;
 template <class Table>
-__global__ void __launch_bounds__(256) maxima_kernel(const float* __restrict__ score, Table segs, uint32_t* __restrict__ max16, uint32_t* __restrict__ max64,
+__global__ void __launch_bounds__(256) maxima_kernel(const float* __restrict__ score, Table segs, int n_seg, uint32_t* __restrict__ max16, uint32_t* __restrict__ max64,
                                                      uint32_t* __restrict__ max256)
 {
-    const int s = blockIdx.y;
+    const int s = segment_of_block(segs.table(), n_seg, (int)blockIdx.x);
     const SegT seg = segs.at(s);
-    const int64_t base = seg.begin + (int64_t)blockIdx.x * 4096 + 4 * (int64_t)threadIdx.x;
+    const int64_t base = seg.begin + (int64_t)((int)blockIdx.x - seg.first_block) * kMaximaChunk + 4 * (int64_t)threadIdx.x;
     f32x4 val[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -2513,7 +2519,7 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     // Segments of up to two rows are counted where they are held as cheaply as by a launch of its own (20 of 30,000, k = 4,096: 44 us
     // either way), unless the draft kernel does it.
     const bool counted = pick && longest > (defer ? kRow : kCountMax);
-    const int64_t span = span_for(n, n_sg);
+    const int64_t span = levels || blocks_route ? kMaximaChunk : span_for(n, n_sg);   // (of the first launch that goes through the scores)
 
     // the segment table: on the stack when it is short (a call that must not allocate stays off the heap as well)
     SegT few[kFewSegs];
@@ -2619,9 +2625,9 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     hipLaunchKernelGGL((sort ? pick_kernel<LEVELS, true, TABLE> : pick_kernel<LEVELS, false, TABLE>), pickers, dim3(kBigThreads), 0, st, score, SEGS, n_sg, (int)ctx.n, k, share, (Maxima{ctx.d_max16, ctx.d_max64, ctx.d_max256}), GHIST, COPIES, idx_out, val_out)
     if (ctx.levels || ctx.blocks_route) {
         if (!noted) {
-            const dim3 grid((unsigned)((ctx.longest + 4095) / 4096), (unsigned)n_sg);
-            if (ctx.inline_ok) hipLaunchKernelGGL(maxima_kernel<InlineSegs>, grid, dim3(256), 0, st, score, inl, ctx.d_max16, ctx.d_max64, ctx.d_max256);
-            else hipLaunchKernelGGL(maxima_kernel<SegsInMemory>, grid, dim3(256), 0, st, score, in_memory, ctx.d_max16, ctx.d_max64, ctx.d_max256);
+            const dim3 grid((unsigned)ctx.blocks);
+            if (ctx.inline_ok) hipLaunchKernelGGL(maxima_kernel<InlineSegs>, grid, dim3(256), 0, st, score, inl, n_sg, ctx.d_max16, ctx.d_max64, ctx.d_max256);
+            else hipLaunchKernelGGL(maxima_kernel<SegsInMemory>, grid, dim3(256), 0, st, score, in_memory, n_sg, ctx.d_max16, ctx.d_max64, ctx.d_max256);
             PRUNER_LAUNCH_CHECK();
         }
         if (ctx.blocks_route) {

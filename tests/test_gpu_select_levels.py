@@ -19,7 +19,7 @@ CONV, GEMM, BATCHED = w.conv2d(1, 64, 56, 56, 64, 3, 3), w.gemm(512, 512, 512), 
 
 @pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
 @pytest.mark.parametrize("lens,ks", [([32769], [1, 64, 768, 769, 1024]), ([40001, 16384, 16385, 1024], [65, 1024]), ([262144, 70], [3, 70]), ([262145, 16400], [512, 768, 769]),
-                                     ([262161] * 3, [33]), ([1048576], [700]), ([1048577, 16385], [1, 768, 1000]), ([33000] * 129, [100, 256, 512])])
+                                     ([262161] * 3, [33]), ([1048576], [700]), ([1048577, 16385], [1, 768, 1000]), ([33000] * 129, [100, 256, 512]), ([700] * 60 + [300001, 4097] + [1000] * 60, [64, 500]), ([700, 4096, 8193] * 70 + [1100001] + [900] * 20, [300])])
 def test_edges_of_the_levels(P, kind, lens, ks):
     rng = np.random.default_rng(len(kind) + len(lens))
     seg = np.concatenate([[0], np.cumsum(lens)])
