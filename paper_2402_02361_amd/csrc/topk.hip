@@ -2204,10 +2204,11 @@ __global__ void __launch_bounds__(kBigThreads) block_lists_kernel(const float* _
     uint32_t n_list = sum_of_all(count([&](uint32_t x) { return x > bound; }), wave_tot);
     bool with_ties = n_list < (uint32_t)k;
     if (!with_ties) {
-        // a bound of its own, which k of this part's entries reach and at most PRUNER_MAX_K exceed
-        uint32_t lowest = bound + 1u, width = ~0u - lowest, rank = (uint32_t)k, reach = n_list;
+        // a bound of its own, which k of this part's entries reach and little more than k
+        const uint32_t enough = (uint32_t)(collect_limit(k) < PRUNER_MAX_K ? collect_limit(k) : PRUNER_MAX_K);
+        uint32_t lowest = bound + 1u, width = top - lowest, rank = (uint32_t)k, reach = n_list;
 #pragma unroll 1
-        while (reach > (uint32_t)PRUNER_MAX_K && width != 0u) {
+        while (reach > enough && width != 0u) {
             const int shift = next_shift(width);
             __syncthreads();
             for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
@@ -2223,7 +2224,7 @@ __global__ void __launch_bounds__(kBigThreads) block_lists_kernel(const float* _
             rank = found[1];
             reach = (uint32_t)k - rank + found[2];
         }
-        with_ties = reach > (uint32_t)PRUNER_MAX_K;   // (one value: fewer than k are above it)
+        with_ties = reach > enough;   // (one value: fewer than k are above it)
         bound = with_ties ? lowest : lowest - 1u;
         n_list = sum_of_all(count([&](uint32_t x) { return x > bound; }), wave_tot);
     }
@@ -2269,7 +2270,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_parts_kernel(const float* __
     __shared__ __align__(16) uint64_t sel[kPickWords];
     __shared__ __align__(16) uint32_t place[kPickCap];   // which words this workgroup ranks
     __shared__ uint32_t hist[kBins];                     // later: the ranking's counts
-    __shared__ uint32_t wave_tot[16], found[3], fill, n_own, range[2], ties_upto[kParts], bound_of[kParts];
+    __shared__ uint32_t wave_tot[16], found[3], fill, n_own, range[2], above_upto[kParts], ties_upto[kParts], bound_of[kParts];
     const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
     if (job >= n_seg * share) return;
     const int s = job / share, part = job % share, lane = lane_id(), wave = threadIdx.x >> 6;
@@ -2293,46 +2294,36 @@ __global__ void __launch_bounds__(kBigThreads) pick_parts_kernel(const float* __
     const uint32_t n_above = (uint32_t)__builtin_amdgcn_readlane((int)upto_above, kWave - 1), n_ties = (uint32_t)__builtin_amdgcn_readlane((int)upto_ties, kWave - 1);
     const bool one_bound = __ballot(my_bound != (uint32_t)__builtin_amdgcn_readfirstlane((int)my_bound)) == 0ull;
     const uint32_t limit = (uint32_t)parts_limit(k);
-    uint32_t n = n_above + n_ties;
+    const uint32_t n_listed = n_above + n_ties;
+    uint32_t n = n_listed;
     const bool whole = n <= limit, first_ties = !whole && one_bound && n_above < (uint32_t)k;
-    // Short lists are a wavefront's own; the others are gone through by all.  (One wavefront alone took 50 us with a full one.)
-    const unsigned long long lengthy = __ballot(my_above > (uint32_t)(kAhead * kWave) || my_ties > (uint32_t)(kAhead * kWave));
+    if (threadIdx.x < kParts) {
+        above_upto[threadIdx.x] = upto_above;
+        ties_upto[threadIdx.x] = upto_ties;
+        bound_of[threadIdx.x] = my_bound;
+    }
+    __syncthreads();
     auto of_list = [&](uint32_t mine, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)mine, l); };
-    // every word: what(there, word), the lanes of a wavefront together
-    auto each = [&](auto&& what) {
-        auto some = [&](int l, uint32_t first, uint32_t step) {
-            const PartList& list = own_lists[l];
-            const uint32_t above = of_list(my_above, l), ties = of_list(my_ties, l), tie_key = of_list(my_bound, l);
-#pragma unroll 1
-            for (uint32_t e = first; e < above; e += step) what(e + lane < above, list.word[e + lane < above ? e + lane : 0u]);
-#pragma unroll 1
-            for (uint32_t e = first; e < ties; e += step) what(e + lane < ties, compose(tie_key, list.tie[e + lane < ties ? e + lane : 0u]));
-        };
-#pragma unroll 1
-        for (int q = 0; q < kMine; ++q)
-            if (!((lengthy >> (wave * kMine + q)) & 1ull)) some(wave * kMine + q, 0u, kWave);
-#pragma unroll 1
-        for (unsigned long long left = lengthy; left; left &= left - 1ull) some(__ffsll(left) - 1, (uint32_t)wave * kWave, kBigThreads);
+    // the list that number t of the lists' words (or ties), one list after the other, lies in: how many end at or before t
+    auto list_of = [&](const uint32_t* upto, uint32_t t) {
+        int l = 0;
+#pragma unroll
+        for (int step = kParts / 2; step > 0; step >>= 1) l += upto[l + step - 1] <= t ? step : 0;
+        return l;
     };
-    if (whole || first_ties) {
+    constexpr int kWords = kPickCap / kBigThreads;   // of a thread at a time
+    if (__builtin_expect(whole || first_ties, 1)) {   // (nearly always)
         // all entries above the bound, and the ties, or the first of them: every word's place is known
         const uint32_t take = whole ? n_ties : (uint32_t)k - n_above;
         n = n_above + take;
-        if (threadIdx.x < kParts) {
-            ties_upto[threadIdx.x] = upto_ties;
-            bound_of[threadIdx.x] = my_bound;
-        }
-        __syncthreads();
         // (a tie's list by bisection: all of a thread's are under way at once, however long the lists are)
-        uint32_t from[kPickCap / kBigThreads], tie_key[kPickCap / kBigThreads];
+        uint32_t from[kWords], tie_key[kWords];
 #pragma unroll
-        for (int i = 0; i < kPickCap / kBigThreads; ++i) {
+        for (int i = 0; i < kWords; ++i) {
             const uint32_t t = (uint32_t)(i * kBigThreads) + threadIdx.x;
             from[i] = tie_key[i] = 0;
             if (t < take) {
-                int l = 0;   // lists that end at or before t
-#pragma unroll
-                for (int step = kParts / 2; step > 0; step >>= 1) l += ties_upto[l + step - 1] <= t ? step : 0;
+                const int l = list_of(ties_upto, t);
                 from[i] = own_lists[l].tie[t - (l > 0 ? ties_upto[l - 1] : 0u)];
                 tie_key[i] = bound_of[l];
             }
@@ -2352,56 +2343,96 @@ __global__ void __launch_bounds__(kBigThreads) pick_parts_kernel(const float* __
             for (uint32_t e = kAhead * kWave + threadIdx.x; e < above; e += kBigThreads) sel[slot(before + e)] = own_lists[l].word[e];
         }
 #pragma unroll
-        for (int i = 0; i < kPickCap / kBigThreads; ++i) {
+        for (int i = 0; i < kWords; ++i) {
             const uint32_t t = (uint32_t)(i * kBigThreads) + threadIdx.x;
             if (t < take) sel[slot(n_above + t)] = compose(tie_key[i], from[i]);
         }
     } else {
-        // Narrowed by the keys' digits, then, where one key remains, by its entries' indices: words at or above (lowest, index_lowest).
-        uint32_t not_least = 0, most = 0;
-        each([&](bool there, uint64_t w) {
-            const uint32_t key = (uint32_t)(w >> 32);
-            most = there && key > most ? key : most;
-            not_least = there && ~key > not_least ? ~key : not_least;
-        });
-        note_range(not_least, most, range);
-        __syncthreads();
-        uint32_t lowest = ~range[0] > shown ? ~range[0] : shown, width = range[1] - lowest, rank = (uint32_t)k, index_lowest = 0;
-        bool by_key = true;
-        if (width == 0u) by_key = false, index_lowest = 0xFFFFFFFFu - (uint32_t)(seg.end - 1), width = (uint32_t)(seg.end - seg.begin) - 1u;
+        // What reaches what is shown is gathered, a thread's words of kPickCap under way at once (list after list, 1,024 words at a time, a
+        // pass over full lists took 50 us).  Where that is too much it is narrowed by the keys' digits, then, where one key remains, by its
+        // entries' indices: words at or above `least`.
+        uint64_t least = (uint64_t)shown << 32;
+        bool held = false;   // sel holds the words that are looked at; else the lists do
+        uint32_t n_words = n_listed;
+        auto word_at = [&](uint32_t t) -> uint64_t {
+            if (t >= n_words) return 0ull;
+            if (held) return sel[slot(t)];
+            const bool above = t < n_above;
+            const uint32_t* const upto = above ? above_upto : ties_upto;
+            const uint32_t number = above ? t : t - n_above;
+            const int l = list_of(upto, number);
+            const uint32_t at = number - (l > 0 ? upto[l - 1] : 0u);
+            return above ? own_lists[l].word[at] : compose(bound_of[l], own_lists[l].tie[at]);
+        };
 #pragma unroll 1
-        for (;;) {
-            const int shift = next_shift(width);
-            const uint32_t base = by_key ? lowest : index_lowest;
-            for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
-            __syncthreads();
-            each([&](bool there, uint64_t w) {
-                const uint32_t x = by_key ? (uint32_t)(w >> 32) : (uint32_t)w;
-                light_hist_add(hist, (x - base) >> shift, there && (by_key || (uint32_t)(w >> 32) == lowest) && x >= base && x - base <= width);
-            });
-            __syncthreads();
-            find_bucket(hist, rank, wave_tot, found);
-            (by_key ? lowest : index_lowest) += found[0] << shift;
-            width = (1u << shift) - 1u;
-            rank = found[1];
-            n = (uint32_t)k - rank + found[2];
-            if (n <= limit) break;
-            if (width == 0u) {   // (an index is one entry's: this was a key)
-                by_key = false;
-                index_lowest = 0xFFFFFFFFu - (uint32_t)(seg.end - 1);
-                width = (uint32_t)(seg.end - seg.begin) - 1u;
+        for (int round = 0;; ++round) {
+#pragma unroll 1
+            for (uint32_t base = 0; base < n_words; base += (uint32_t)kPickCap) {
+                uint64_t word[kWords];
+                uint32_t in = 0;
+#pragma unroll
+                for (int i = 0; i < kWords; ++i) word[i] = word_at(base + (uint32_t)(i * kBigThreads) + threadIdx.x);
+#pragma unroll
+                for (int i = 0; i < kWords; ++i) in |= word[i] != 0ull && word[i] >= least ? 1u << i : 0u;
+                if (held) __syncthreads();   // (at most kPickCap: all have been read)
+                uint32_t to = reserve(&fill, (uint32_t)__popc(in));
+#pragma unroll
+                for (int i = 0; i < kWords; ++i) {
+                    if (!((in >> i) & 1u)) continue;
+                    if (to < (uint32_t)kPickCap) sel[slot(to)] = word[i];
+                    ++to;
+                }
             }
+            __syncthreads();
+            n = fill;
+            if (n <= limit) break;   // (after the second round always)
+            __syncthreads();
+            if (threadIdx.x == 0) fill = 0;
+            held = n <= (uint32_t)kPickCap;
+            if (held) n_words = n;
+            // every word: what(whether there is one, word), the lanes of a wavefront together
+            auto each = [&](auto&& what) {
+#pragma unroll 1
+                for (uint32_t t = 0; t < n_words; t += kBigThreads) {
+                    const uint64_t w = word_at(t + threadIdx.x);
+                    what(w != 0ull, w);
+                }
+            };
+            uint32_t not_least = 0, most = 0;
+            each([&](bool there, uint64_t w) {
+                const uint32_t key = (uint32_t)(w >> 32);
+                most = there && key > most ? key : most;
+                not_least = there && ~key > not_least ? ~key : not_least;
+            });
+            note_range(not_least, most, range);
+            __syncthreads();
+            uint32_t lowest = ~range[0] > shown ? ~range[0] : shown, width = range[1] - lowest, rank = (uint32_t)k, index_lowest = 0;
+            bool by_key = true;
+            if (width == 0u) by_key = false, index_lowest = 0xFFFFFFFFu - (uint32_t)(seg.end - 1), width = (uint32_t)(seg.end - seg.begin) - 1u;
+#pragma unroll 1
+            for (;;) {
+                const int shift = next_shift(width);
+                const uint32_t base = by_key ? lowest : index_lowest;
+                for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+                __syncthreads();
+                each([&](bool there, uint64_t w) {
+                    const uint32_t x = by_key ? (uint32_t)(w >> 32) : (uint32_t)w;
+                    light_hist_add(hist, (x - base) >> shift, there && (by_key || (uint32_t)(w >> 32) == lowest) && x >= base && x - base <= width);
+                });
+                __syncthreads();
+                find_bucket(hist, rank, wave_tot, found);
+                (by_key ? lowest : index_lowest) += found[0] << shift;
+                width = (1u << shift) - 1u;
+                rank = found[1];
+                if ((uint32_t)k - rank + found[2] <= limit) break;
+                if (width == 0u) {   // (an index is one entry's: this was a key)
+                    by_key = false;
+                    index_lowest = 0xFFFFFFFFu - (uint32_t)(seg.end - 1);
+                    width = (uint32_t)(seg.end - seg.begin) - 1u;
+                }
+            }
+            least = ((uint64_t)lowest << 32) | index_lowest;
         }
-        const uint64_t least = ((uint64_t)lowest << 32) | index_lowest;
-        each([&](bool there, uint64_t w) {
-            const unsigned long long in = __ballot(there && w >= least);
-            if (in == 0ull) return;
-            const int leader = __ffsll(in) - 1;
-            uint32_t base = 0;
-            if (lane == leader) base = atomicAdd(&fill, (uint32_t)__popcll(in));
-            const uint32_t to = (uint32_t)__builtin_amdgcn_readlane((int)base, leader) + (uint32_t)__popcll(in & ((1ull << lane) - 1ull));
-            if (((in >> lane) & 1ull) && to < n) sel[slot(to)] = w;
-        });
     }
     // spare words and those behind the last must read as "below everything"
     const int n_raw = n > 0 ? (int)slot(n - 1u) + 1 : 0;

@@ -28,7 +28,7 @@ def test_edges_of_the_levels(P, kind, lens, ks):
         check(P, score, seg, k)
 
 
-@pytest.mark.parametrize("kind", ["latencies", "ascending", "clump", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
+@pytest.mark.parametrize("kind", ["latencies", "ascending", "nearly ascending", "clump", "clumps", "one bin", "two values", "300 values", "equal", "neighbours", "zeros"])
 @pytest.mark.parametrize("lens,k", [([787200], 1025), ([787199], 1025), ([590592], 769), ([1200001, 1075200, 1075203, 1200002], 1400), ([1100001] * 5, 1400), ([3145728, 3145729], 4096), ([5000001], 2000), ([4194304], 64), ([4194305], 1), ([4194305, 600000], 768), ([4200003] * 2, 100)])
 def test_few_of_long_segments(P, kind, lens, k):
     """lists of the parts of the best blocks of 256: one entry in 768 and one less, the most segments and one more"""

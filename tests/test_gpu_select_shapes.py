@@ -19,6 +19,16 @@ def of(kind, n, rng):
         m = min(n, 3000)
         x[n // 2 - m // 2: n // 2 - m // 2 + m] = -np.exp2(rng.uniform(-30, -27, m)).astype(np.float32)
         return x
+    if kind == "nearly ascending":      # one in fifty elsewhere
+        x = np.sort(values("latencies", n, rng))
+        some = rng.integers(0, n, n // 50 + 1)
+        x[some] = x[some[::-1]]
+        return x
+    if kind == "clumps":                # good entries side by side in five places
+        x = values("latencies", n, rng)
+        for p in range(5):
+            x[p * (n // 7): p * (n // 7) + 3000] *= np.float32(2.0 ** -10)
+        return x
     if kind == "ties and neighbours":   # a third of the entries share a value, a few lie just above it
         r = rng.random(n)
         return np.where(r < 0.3, np.float32(2.0), np.where(r < 0.3005, np.float32(2.0) + (r * 0.01).astype(np.float32), values("normal", n, rng) * np.float32(0.3))).astype(np.float32)
