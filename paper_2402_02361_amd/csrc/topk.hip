@@ -1734,6 +1734,193 @@ __global__ void __launch_bounds__(256) maxima_kernel(const float* __restrict__ s
     }
 }
 
+// Ties, all of the key `lowest`, in index order: the tie of rank r owns row behind + r, and k_rem of them are wanted.  A wavefront takes
+// 16 x 64 neighbouring entries; one exchange of the wavefronts' counts per sweep.
+__device__ __forceinline__ void write_ties(const float* __restrict__ score, const SegT& seg, uint32_t lowest, int k, uint32_t k_rem, uint32_t* wave_tot,
+                                           int32_t* __restrict__ idx_out, float* __restrict__ val_out, int s)
+{
+    const int len = (int)(seg.end - seg.begin), lane = lane_id(), wave = threadIdx.x >> 6;
+    const float* seg_score = score + seg.begin;
+    const uint32_t behind = (uint32_t)k - k_rem;
+    uint32_t before = 0;
+    for (int row = 0; row < len && before < k_rem; row += kRow) {
+        const int first = row + wave * (kWave * kBigPer) + lane;
+        uint32_t before_mine[kBigPer], wave_ties = 0;
+#pragma unroll
+        for (int j = 0; j < kBigPer; ++j) {
+            const int i = first + j * kWave;
+            const bool tie = i < len && key_of(seg_score[i < len ? i : 0]) == lowest;
+            const unsigned long long m = __ballot(tie);
+            before_mine[j] = tie ? wave_ties + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : 0xFFFFFFFFu;
+            wave_ties += (uint32_t)__popcll(m);
+        }
+        __syncthreads();
+        if (lane == 0) wave_tot[wave] = wave_ties;
+        __syncthreads();
+        uint32_t wave_before = before, all = 0;
+#pragma unroll
+        for (int w = 0; w < kBigThreads / kWave; ++w) {
+            wave_before += w < wave ? wave_tot[w] : 0u;
+            all += wave_tot[w];
+        }
+#pragma unroll
+        for (int j = 0; j < kBigPer; ++j)
+            if (before_mine[j] != 0xFFFFFFFFu && wave_before + before_mine[j] < k_rem)
+                put_tie_row(k, behind + wave_before + before_mine[j], (uint32_t)(seg.begin + first + j * kWave), lowest, score, idx_out, val_out, s, seg.begin, seg.end);
+        before += all;
+    }
+}
+
+// Segments of up to kPickMax entries behind whoever counted the first digit: the whole segment travels to registers while the bin is looked
+// up (65,536 entries, k = 1,000: 41 us for the call; 47 read in two rows by pick_kernel).  A kernel of its own, since pick_kernel's
+// registers would not hold it.
+template <bool SORT>
+__global__ void __launch_bounds__(kBigThreads) pick_long_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int n_total, int k, int share,
+                                                                const uint32_t* __restrict__ ghist0, int R, int32_t* __restrict__ idx_out, float* __restrict__ val_out)
+{
+    __shared__ __align__(16) uint64_t sel[kPickWords];
+    __shared__ __align__(16) uint32_t place[kPickCap];   // indices inside the segment; later: which words this workgroup ranks
+    __shared__ uint32_t hist[kBins];          // later: the ranking's counts
+    __shared__ uint32_t wave_tot[16];
+    __shared__ uint32_t found[3];
+    __shared__ uint32_t fill, n_own, range[2];
+    const int per_xcd = (n_seg * share + kXcds - 1) / kXcds, job = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+    if (job >= n_seg * share) return;
+    const int s = job / share, part = job % share;
+    const SegT seg = segs[s];
+    const int len = (int)(seg.end - seg.begin);
+    const float* seg_score = score + seg.begin;
+
+    // Sixteen groups of four neighbours per thread.  A group that would reach past the end of the scores starts earlier; what lies
+    // outside the segment is masked out below.
+    constexpr int kGroups = kPickMax / (4 * kBigThreads);
+    const int last = n_total - 4 - (int)seg.begin;   // (there are more than four scores in all)
+    auto group_begin = [](int g) { return (g * kBigThreads + (int)threadIdx.x) * 4; };
+    f32x4 val[kGroups];
+#pragma unroll
+    for (int g = 0; g < kGroups; ++g) {
+        if (g * 4 * kBigThreads < len) {
+            const int i = group_begin(g);
+            val[g] = *reinterpret_cast<const f32x4_a4*>(seg_score + (i < last ? i : last));
+        }
+    }
+    bucket_of_pass<8>(ghist0, R, n_seg, s, (uint32_t)k, hist, wave_tot, found);
+    uint32_t lowest, width, k_rem = found[1], in_bin = found[2];
+    first_digit_range(found[0], lowest, width);
+    if (threadIdx.x == 0) fill = n_own = range[0] = range[1] = 0;
+    __syncthreads();
+    // More than the limit: the bin is split (the same decision in every workgroup of the segment).  (An instruction for each of a
+    // thread's sixty-four entries costs 0.4 us: a key below the range is told by the difference alone, which wraps.)
+    const uint32_t limit = (uint32_t)collect_limit(k);
+    uint32_t largest = 0;   // of the bin's keys
+    if ((uint32_t)k - k_rem + in_bin > limit) {
+        uint32_t a = 0, b = 0;
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            if (g * 4 * kBigThreads < len) {
+                const int i = group_begin(g), begun = i < last ? i : last;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t key = key_of(val[g][e]);
+                    const bool in = (uint32_t)(begun + e) < (uint32_t)len && key - lowest <= width;
+                    a = in && ~key > a ? ~key : a;
+                    b = in && key > b ? key : b;
+                }
+            }
+        }
+        note_range(a, b, range);
+        __syncthreads();
+        largest = range[1];
+        lowest = ~range[0];
+        width = largest - lowest;
+    }
+#pragma unroll 1
+    for (int digits = 0; digits < 3 && width != 0u && (uint32_t)k - k_rem + in_bin > limit; ++digits) {   // (a bin spans 2^22 keys at most)
+        const int shift = next_shift(width);
+        for (int i = threadIdx.x; i < kBins; i += kBigThreads) hist[i] = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (int row = 0; row < len; row += kRow) {
+            float again[kBigPer];
+            load_sweep(seg_score, row, len, again);
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) {
+                const uint32_t key = key_of(again[j]);
+                light_hist_add(hist, (key - lowest) >> shift, sweep_index(row, j) < len && key - lowest <= width);
+            }
+        }
+        __syncthreads();
+        find_bucket(hist, k_rem, wave_tot, found);
+        lowest += found[0] << shift;
+        width = (1u << shift) - 1u;
+        width = largest - lowest < width ? largest - lowest : width;
+        k_rem = found[1];
+        in_bin = found[2];
+        __syncthreads();
+    }
+    // entries at or above `lowest` are collected; if the ties alone are too many, those above it
+    const bool ties_apart = (uint32_t)k - k_rem + in_bin > limit;
+    const int n = (int)(ties_apart ? (uint32_t)k - k_rem : (uint32_t)k - k_rem + in_bin);
+    {
+        const float t0 = threshold_of(ties_apart ? lowest + 1u : lowest);
+        uint64_t mask = 0;   // bit 4 g + e: entry e of group g is not below the threshold
+#pragma unroll
+        for (int g = 0; g < kGroups; ++g) {
+            if (g * 4 * kBigThreads < len) {
+                uint32_t four = 0;
+#pragma unroll
+                for (int e = 3; e >= 0; --e) four = 2 * four + (val[g][e] < t0 ? 0u : 1u);
+                if ((g + 1) * 4 * kBigThreads > len) {   // the segment's last groups
+                    const int i = group_begin(g), begun = i < last ? i : last, left = len - i;
+                    four = left <= 0 ? 0u : (four >> (i - begun)) & (left < 4 ? (1u << left) - 1u : 15u);
+                }
+                mask |= (uint64_t)four << (4 * g);
+            }
+        }
+        uint32_t at = reserve(&fill, (uint32_t)__popcll(mask));
+#pragma unroll 1
+        for (; mask; mask &= mask - 1, ++at) {
+            const int bit = __ffsll((unsigned long long)mask) - 1;
+            if (at < (uint32_t)kPickCap) place[at] = (uint32_t)(group_begin(bit >> 2) + (bit & 3));
+        }
+    }
+    // spare words and those behind the last must read as "below everything"
+    const int n_raw = n > 0 ? (int)slot((uint32_t)n - 1u) + 1 : 0;
+    for (int i = threadIdx.x; i < n_raw + 3; i += kBigThreads)
+        if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
+    __syncthreads();
+    if (n > 0 && fill != (uint32_t)n) {
+        // The counts come from keys, the places from comparisons with a threshold: where these found more, there are NaN
+        // among the scores, and the places are collected again by key.
+        __syncthreads();
+        if (threadIdx.x == 0) fill = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (int row = 0; row < len; row += kRow) {
+            float again[kBigPer];
+            load_sweep(seg_score, row, len, again);
+            uint32_t mask = 0;
+#pragma unroll
+            for (int j = 0; j < kBigPer; ++j) {
+                const uint32_t key = key_of(again[j]);
+                mask |= sweep_index(row, j) < len && (ties_apart ? key > lowest : key >= lowest) ? 1u << j : 0u;
+            }
+            uint32_t at = reserve(&fill, (uint32_t)__popc(mask));
+#pragma unroll 1
+            for (; mask; mask &= mask - 1, ++at)
+                if (at < (uint32_t)kPickCap) place[at] = (uint32_t)sweep_index(row, __ffs((int)mask) - 1);
+        }
+        __syncthreads();
+    }
+    for (int e = threadIdx.x; e < n; e += kBigThreads) {
+        const uint32_t i = place[e] < (uint32_t)len ? place[e] : 0u;
+        sel[slot((uint32_t)e)] = compose(key_of(seg_score[i]), (uint32_t)seg.begin + i);
+    }
+    __syncthreads();
+    write_collection<SORT>(sel, place, hist, &fill, &n_own, n, k, share, part, k_rem, lowest, width, true, score, idx_out, val_out, s, seg);
+    if (ties_apart && part == 0) write_ties(score, seg, lowest, k, k_rem, wave_tot, idx_out, val_out, s);
+}
+
 // The workgroups of a segment collect from its lists, and rank as pick_kernel does.
 template <bool SORT>
 __global__ void __launch_bounds__(kBigThreads) pick_lists_kernel(const float* __restrict__ score, const SegT* __restrict__ segs, int n_seg, int R,
@@ -1898,38 +2085,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_lists_kernel(const float* __
         if (i % 33 == 32 || i >= n_raw) sel[i] = 0;
     __syncthreads();
     write_collection<SORT>(sel, place, hist, &fill, &n_own, n, k, share, part, k_rem, lowest, width, true, score, idx_out, val_out, s, seg);
-    const uint32_t behind = (uint32_t)k - k_rem;   // (ties apart: rows before theirs)
-    if (ties_apart && part == 0) {
-        // ties, all of the key `lowest`, in index order: the tie of rank r owns row behind + r.  A wavefront takes 16 x 64
-        // neighbouring entries; one exchange of the wavefronts' counts per sweep.
-        uint32_t before = 0;
-        for (int row = 0; row < len && before < k_rem; row += kRow) {
-            const int first = row + wave * (kWave * kBigPer) + lane;
-            uint32_t before_mine[kBigPer], wave_ties = 0;
-#pragma unroll
-            for (int j = 0; j < kBigPer; ++j) {
-                const int i = first + j * kWave;
-                const bool tie = i < len && key_of(seg_score[i < len ? i : 0]) == lowest;
-                const unsigned long long m = __ballot(tie);
-                before_mine[j] = tie ? wave_ties + (uint32_t)__popcll(m & ((1ull << lane) - 1ull)) : 0xFFFFFFFFu;
-                wave_ties += (uint32_t)__popcll(m);
-            }
-            __syncthreads();
-            if (lane == 0) wave_tot[wave] = wave_ties;
-            __syncthreads();
-            uint32_t wave_before = before, all = 0;
-#pragma unroll
-            for (int w = 0; w < kBigThreads / kWave; ++w) {
-                wave_before += w < wave ? wave_tot[w] : 0u;
-                all += wave_tot[w];
-            }
-#pragma unroll
-            for (int j = 0; j < kBigPer; ++j)
-                if (before_mine[j] != 0xFFFFFFFFu && wave_before + before_mine[j] < k_rem)
-                    put_tie_row(k, behind + wave_before + before_mine[j], (uint32_t)(seg.begin + first + j * kWave), lowest, score, idx_out, val_out, s, seg.begin, seg.end);
-            before += all;
-        }
-    }
+    if (ties_apart && part == 0) write_ties(score, seg, lowest, k, k_rem, wave_tot, idx_out, val_out, s);
 }
 
 // ---- blocks route -------------------------------------------------------------------------------------------------------
@@ -2696,7 +2852,8 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
         PRUNER_LAUNCH_CHECK();
     }
     if (ctx.pick) {
-        PRUNER_PICK(false, SegsInMemory, in_memory, hist0, R);
+        if (ctx.longest > kCountMax) hipLaunchKernelGGL((sort ? pick_long_kernel<true> : pick_long_kernel<false>), pickers, dim3(kBigThreads), 0, st, score, d_segs, n_sg, (int)ctx.n, k, share, hist0, R, idx_out, val_out);
+        else PRUNER_PICK(false, SegsInMemory, in_memory, hist0, R);
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }
