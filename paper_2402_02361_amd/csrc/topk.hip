@@ -1697,17 +1697,20 @@ __global__ void __launch_bounds__(kBigThreads) pick_kernel(const float* __restri
 }
 
 // The largest keys of blocks (those that are asked for), for scores that nobody has held before: a workgroup to kMaximaChunk entries of
-// a segment (first_block counts these).  Bound by the scores' way from memory.  (A grid of segments by the longest one's chunks
-// began workgroups by the million where one segment is long among many: 1,000 of 1,000 and one of 4 M 1,762 us, 160 before there were
-// maxima.)
+// a segment (first_block counts these).  Bound by the scores' way from memory.  The grid is segments by the longest one's chunks where
+// that begins few workgroups in vain, else the chunks of all segments, each of which looks its segment up (0.3 us).  (Always the
+// former began workgroups by the million where one segment is long among many: 1,000 of 1,000 and one of 4 M, k = 100, 1,762 us for
+// the call, now 57; 0.4 us for a thousand of them.)
 constexpr int kMaximaChunk = 4096;
+constexpr int64_t kMaximaSpare = 1024;
 template <class Table>
 __global__ void __launch_bounds__(256) maxima_kernel(const float* __restrict__ score, Table segs, int n_seg, uint32_t* __restrict__ max16, uint32_t* __restrict__ max64,
                                                      uint32_t* __restrict__ max256)
 {
-    const int s = segment_of_block(segs.table(), n_seg, (int)blockIdx.x);
+    const bool by_segment = (int)gridDim.y == n_seg;
+    const int s = by_segment ? (int)blockIdx.y : segment_of_block(segs.table(), n_seg, (int)blockIdx.x);
     const SegT seg = segs.at(s);
-    const int64_t base = seg.begin + (int64_t)((int)blockIdx.x - seg.first_block) * kMaximaChunk + 4 * (int64_t)threadIdx.x;
+    const int64_t base = seg.begin + (int64_t)((int)blockIdx.x - (by_segment ? 0 : seg.first_block)) * kMaximaChunk + 4 * (int64_t)threadIdx.x;
     f32x4 val[4];
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
@@ -2812,7 +2815,8 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
     hipLaunchKernelGGL((sort ? pick_kernel<LEVELS, true, TABLE> : pick_kernel<LEVELS, false, TABLE>), pickers, dim3(kBigThreads), 0, st, score, SEGS, n_sg, (int)ctx.n, k, share, (Maxima{ctx.d_max16, ctx.d_max64, ctx.d_max256}), GHIST, COPIES, idx_out, val_out)
     if (ctx.levels || ctx.blocks_route) {
         if (!noted) {
-            const dim3 grid((unsigned)ctx.blocks);
+            const int64_t most = (ctx.longest + kMaximaChunk - 1) / kMaximaChunk;
+            const dim3 grid = most * n_sg <= ctx.blocks + kMaximaSpare ? dim3((unsigned)most, (unsigned)n_sg) : dim3((unsigned)ctx.blocks);
             if (ctx.inline_ok) hipLaunchKernelGGL(maxima_kernel<InlineSegs>, grid, dim3(256), 0, st, score, inl, n_sg, ctx.d_max16, ctx.d_max64, ctx.d_max256);
             else hipLaunchKernelGGL(maxima_kernel<SegsInMemory>, grid, dim3(256), 0, st, score, in_memory, n_sg, ctx.d_max16, ctx.d_max64, ctx.d_max256);
             PRUNER_LAUNCH_CHECK();
