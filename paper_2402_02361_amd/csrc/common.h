@@ -91,6 +91,8 @@ struct TopkCtx {
     bool tiny, pick, levels, blocks_route, lists;   // the route; none of them: spans
     int32_t n_sg, k;
     int64_t n, longest, span;
+    int share;             // workgroups that rank a segment's words
+    bool sort;             // ... or sort them, if they are many
     int32_t blocks;        // workgroups of a sweep launch
     int copies;            // copies of the first digit's histogram
     void *d_segs, *d_state, *d_stage, *d_parts;

@@ -2701,9 +2701,21 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
 
     char* ws = static_cast<char*>(workspace);
     SegT* d_segs = reinterpret_cast<SegT*>(ws + L.segs);
-    // (without room for maxima: as for a large k)
+    // the ranking of a segment's k rows is shared out over up to k / 32 workgroups, as long as the launch is one
+    // workgroup per compute unit at most (a compute unit holds one of these workgroups at a time: a launch of more
+    // takes a second round, which costs more than longer rankings do)
+    int share = (k + 31) / 32;
+    if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
+    if (share < 1) share = 1;
+    const bool sort = (k + 64 * share - 1) / (64 * share) * k > kSortFactor * pow2_at_least(k);   // (a collection is k words and a little more)
+    // (without room for maxima: as for a large k.)  Where the draft kernel counts first digits on the way, segments held whole are the
+    // better ones with fewer than two blocks of sixteen per selected entry, of which the bound leaves too many entries (the filter of
+    // 6 x 16,500, k = 700: 20.3 us by digits, 27.6 by levels; of 20,000 20.4 and 20.0; 20 x 20,000 23.8 and 30.1, 25,000 24.6 and 23.2),
+    // and where few workgroups share a ranking and sort (100 x 25,000, k = 512: 45.6 and 49.0, k = 256 37.7 and 35.5; 100 x 40,000 of
+    // convolutions, k = 512, 67.5 and 74.5).
     const bool tiny = longest <= kTinyMax && k <= kTinyK;
-    const bool levels = with_block_max && !tiny && longest > (defer ? kRow : kCountMax) && k <= kLevelMostK && longest <= kLevelMax;
+    const bool better_held = defer && longest <= kPickMax && (longest < 32 * (int64_t)k || sort);
+    const bool levels = with_block_max && !tiny && !better_held && longest > (defer ? kRow : kCountMax) && k <= kLevelMostK && longest <= kLevelMax;
     const bool pick = !tiny && !levels && longest <= kPickMax;
     const bool blocks_route = with_block_max && !tiny && !levels && !pick && n_sg <= kBlocksSegments && longest <= kBlocksMax && shortest >= kBlocksSparse * (int64_t)k && workspace_bytes >= L.with_parts;
     // Segments of up to two rows are counted where they are held as cheaply as by a launch of its own (20 of 30,000, k = 4,096: 44 us
@@ -2730,6 +2742,8 @@ int topk_prepare(const int64_t* seg_off, int32_t n_sg, int32_t k, void* workspac
     ctx->lists = lists;
     ctx->digits = !tiny && !levels && !blocks_route && (!pick || counted);
     ctx->longest = longest;
+    ctx->share = share;
+    ctx->sort = sort;
     ctx->n_sg = n_sg;
     ctx->k = k;
     ctx->n = n;
@@ -2803,13 +2817,8 @@ int topk_finish(const TopkCtx& ctx, const float* score, const int64_t* seg_off, 
         return PRUNER_OK;
     }
 
-    // the ranking of a segment's k rows is shared out over up to k / 32 workgroups, as long as the launch is one
-    // workgroup per compute unit at most (a compute unit holds one of these workgroups at a time: a launch of more
-    // takes a second round, which costs more than longer rankings do)
-    int share = (k + 31) / 32;
-    if (share > kComputeUnits / n_sg) share = kComputeUnits / n_sg;
-    if (share < 1) share = 1;
-    const bool sort = (k + 64 * share - 1) / (64 * share) * k > kSortFactor * pow2_at_least(k);   // (a collection is k words and a little more)
+    const int share = ctx.share;
+    const bool sort = ctx.sort;
     const dim3 pickers((unsigned)((n_sg * share + kXcds - 1) / kXcds * kXcds));
 #define PRUNER_PICK(LEVELS, TABLE, SEGS, GHIST, COPIES) \
     hipLaunchKernelGGL((sort ? pick_kernel<LEVELS, true, TABLE> : pick_kernel<LEVELS, false, TABLE>), pickers, dim3(kBigThreads), 0, st, score, SEGS, n_sg, (int)ctx.n, k, share, (Maxima{ctx.d_max16, ctx.d_max64, ctx.d_max256}), GHIST, COPIES, idx_out, val_out)

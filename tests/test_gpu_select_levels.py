@@ -135,7 +135,8 @@ def test_a_bound_below_every_number(P, n):
 
 @pytest.mark.parametrize("sgs,lens,k", [([GEMM], [16384], 500), ([GEMM], [16385], 500), ([GEMM], [70003], 1024), ([GEMM, CONV], [20001, 30003], 33), ([GEMM, CONV, BATCHED], [16386, 50001, 3], 3),
                                         ([GEMM, CONV, BATCHED], [300001, 200003, 120002], 700), ([CONV, GEMM], [1048580, 17001], 1000), ([CONV], [1048576], 64), ([GEMM], [40000], 4096),
-                                        ([CONV, GEMM, GEMM], [1700001, 900002, 50], 50), ([GEMM, CONV], [1200003, 1100001], 1050)])
+                                        ([CONV, GEMM, GEMM], [1700001, 900002, 50], 50), ([GEMM, CONV], [1200003, 1100001], 1050), ([CONV], [22399], 700), ([CONV], [22400], 700),
+                                        ([CONV, GEMM], [65537, 20001], 768), ([GEMM, CONV] * 45, [17000] * 90, 399), ([GEMM, CONV] * 45, [17000] * 90, 400)])
 def test_maxima_left_by_the_draft_kernel(P, sgs, lens, k):
     """one candidate per thread and four, ends of segments inside a block, a population with few distinct scores (GEMM)"""
     seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
