@@ -2121,9 +2121,10 @@ static_assert(kMostBlocks >= PRUNER_MAX_K, "the k best blocks fit");
 
 static_assert(kPickCap >= parts_limit(PRUNER_MAX_K), "a collection fits");
 
+constexpr int kPartWords = collect_limit(PRUNER_MAX_K);   // (room for little more than k: for k alone a bound of a part's own takes every digit)
 struct PartList {
     uint32_t above, ties, bound, top;     // top: the part's largest key
-    uint64_t word[PRUNER_MAX_K];          // of entries above `bound`
+    uint64_t word[kPartWords];            // of entries above `bound`
     uint32_t tie[PRUNER_MAX_K];           // indices, in order, of entries that equal it
 };
 
@@ -2364,7 +2365,7 @@ __global__ void __launch_bounds__(kBigThreads) block_lists_kernel(const float* _
     bool with_ties = n_list < (uint32_t)k;
     if (!with_ties) {
         // a bound of its own, which k of this part's entries reach and little more than k
-        const uint32_t enough = (uint32_t)(collect_limit(k) < PRUNER_MAX_K ? collect_limit(k) : PRUNER_MAX_K);
+        const uint32_t enough = (uint32_t)collect_limit(k);
         uint32_t lowest = bound + 1u, width = top - lowest, rank = (uint32_t)k, reach = n_list;
 #pragma unroll 1
         while (reach > enough && width != 0u) {
@@ -2396,7 +2397,7 @@ __global__ void __launch_bounds__(kBigThreads) block_lists_kernel(const float* _
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if (key[j][e] > bound) {
-                if (to < (uint32_t)PRUNER_MAX_K) mine.word[to] = compose(key[j][e], (uint32_t)seg.begin + (uint32_t)(at[j] + e));
+                if (to < (uint32_t)kPartWords) mine.word[to] = compose(key[j][e], (uint32_t)seg.begin + (uint32_t)(at[j] + e));
                 ++to;
             }
             equal[j] |= with_ties && ((live[j] >> e) & 1u) && key[j][e] == bound ? 1u << e : 0u;
@@ -2436,7 +2437,7 @@ __global__ void __launch_bounds__(kBigThreads) pick_parts_kernel(const float* __
     const SegT seg = segs.at(s);
     const PartList* const own_lists = lists + (size_t)s * kParts;
     constexpr int kMine = kParts / (kBigThreads / kWave);   // lists of a wavefront
-    constexpr int kAhead = 2;                               // words of each that are asked for at once, per lane (the lists hold PRUNER_MAX_K: inside)
+    constexpr int kAhead = 2;                               // words of each that are asked for at once, per lane (the lists hold kPartWords: inside)
     uint64_t ahead[kMine][kAhead];
 #pragma unroll
     for (int q = 0; q < kMine; ++q)
