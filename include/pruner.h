@@ -354,7 +354,9 @@ int pruner_topk_static(const float* score, const int64_t* seg_off, int32_t n_sg,
 #define PRUNER_WS_LSE 4
 #define PRUNER_WS_PACM 5          /* n = candidates of the drafted set */
 
-/* Bytes of workspace entry point `which` needs for n items in n_sg segments with selection size k (0 if unused). */
+/* Bytes of workspace entry point `which` needs for n items in n_sg segments with selection size k (0 if unused).  For
+   TOPK, PRIOR_FILTER and LSE this counts room for lists by which large selections of few segments are faster; a call that
+   gets less, but what it cannot do without, gives the same result by another way. */
 size_t pruner_workspace_bytes(int32_t which, int64_t n, int32_t n_sg, int32_t k);
 
 /* Static, read-only description of a return code. */

@@ -1,8 +1,9 @@
 // PriorFilter of Alg. 2 as one call: C_SA over the whole population, then the k best per subgraph.
 //
 // The same kernels as pruner_draft_score followed by pruner_topk, with one saving: where the selection begins with a pass over the
-// scores (segments above 65,536 entries: the largest of every 64, or first digits counted), the draft kernel does its work while it
-// still holds the scores in registers.  The result is the same as that of the two separate calls, bit for bit.
+// scores (as a rule segments above 16,384 entries: the largest keys of neighbours noted, or first digits counted; the rules are in
+// topk.hip), the draft kernel does its work while it still holds the scores in registers.  The result is the same as that of the two
+// separate calls, bit for bit.
 #include "common.h"
 #include "select_common.h"
 

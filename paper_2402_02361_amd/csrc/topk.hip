@@ -9,8 +9,9 @@
 //   tiny   - segments of at most 8192 entries and k up to 64 (the final selection after the verify stage, small draft
 //            populations): one launch, no digits (tiny_select in select_common.h);
 //   pick   - short segments: one launch, in which several workgroups per segment hold it in registers, count the first digit, keep
-//            the few entries at or above rank k's bin, and each rank their share of them (k above kLevelMostK: also segments of at
-//            most kPickMax entries, behind whoever counted the digit, the draft kernel or a pass);
+//            the few entries at or above rank k's bin, and each rank their share of them (k above kLevelMostK, or without room for
+//            maxima, or few blocks per selected entry: also segments of at most kPickMax entries, behind whoever counted the digit,
+//            the draft kernel or a pass);
 //   levels - longer ones, k up to kLevelMostK: the same launch behind whoever held the scores and left the largest key of every sixteen
 //            neighbours (the draft kernel, else a pass): a workgroup holds the few blocks of sixteen that can matter;
 //   blocks - a larger k of a few segments at least 768 times as long, or segments longer than kLevelMax: two launches behind whoever held the scores and left the largest key of every 256 neighbours
@@ -983,8 +984,8 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
 // `share` workgroups per segment.  Each holds what can matter of the segment in registers (sixteen entries per thread), collects all
 // entries at or above a bound that at least k entries reach, and ranks those whose index hashes to it among all of them: no lists
 // between launches.
-//   pick: segments of at most kRow entries are held whole, their first digits counted where they lie.  (k above kLevelMostK: of at most
-// kPickMax entries, read in rows of kRow, the digits counted by the launch before as a rule.)
+//   pick: segments of at most kRow entries are held whole, their first digits counted where they lie; of up to kCountMax, where no maxima
+// are asked for (longer ones: pick_long_kernel below).
 //   levels: of longer ones blocks of sixteen neighbours are held.  Whoever held the scores left the largest key of every sixteen (and
 // of every 64 and 256 where segments are long).  The k best entries lie in the k best blocks (by largest key, then in index order):
 // an entry of another block has the largest entries of k blocks before it.  So the k best of the maxima are found, of 256 first,
@@ -999,6 +1000,9 @@ __global__ void __launch_bounds__(kSmallThreads) gather_sort_kernel(const float*
 // 20 x 50,000, k = 512: draft 13.9 -> 12.8 us, the launch that cleared histograms 2.6 -> none, this one 13.5 -> 14.2; 65,536, k = 128:
 // 7.9 -> 7.6, 2.3 -> none, 10.9 -> 9.8; ten segments of 333,333, k = 512: the selection 3 + 7.5 + 8.5 -> 16.5; a kernel of this kind
 // is bound by its instructions too (16 wavefronts share four pipes: one more per thread costs 7 ns).
+// Good entries side by side make the bound a weak one, and the collection is split: pruner_topk, us by digits and now, 1 x 65,536,
+// k = 512, distinct scores 40.5 and 18.4, sorted 38.4 and 25.3, five stretches of good ones 20.9 and 25.5; 1 x 260,000, k = 768, 32.3 and
+// 21.4, 32.5 and 37.5, 25.4 and 37.2; 1 x 500,000, k = 512, with ten values 29.9 and 32.5; within one bin 63.4 and 29.6.
 
 constexpr int kPickMax = 65536;
 constexpr int kCountMax = 32768;                                // entries held in registers where there are no blocks
@@ -1224,6 +1228,7 @@ __global__ void __launch_bounds__(kBigThreads) __attribute__((amdgpu_waves_per_e
         flush_hist<kBigThreads>(hist, ghist1, 1, n_seg, s);
         if (threadIdx.x < 2 && range[threadIdx.x] != 0u) atomicMax(&granges[(size_t)s * kBins + threadIdx.x], range[threadIdx.x]);
     }
+    // (k up to kLevelMostK comes here from pruner_topk_static only, which has no room for maxima.)
     // One value: its ties need no list.  Fewer spans' worth of such entries (a sorted segment; a shorter one): whoever collects goes
     // through those spans in less time than this takes, 10 to 20 us (within one bin, k = 90: 1 x 200,000 70 -> 49 us, 1 x 350,000
     // 96 -> 51; k = 512 or 686: 8 x 220,000 50 -> 60, 3 x 274,000 50 -> 61, 3 x 350,000 103 -> 69).
@@ -2106,9 +2111,10 @@ __global__ void __launch_bounds__(kBigThreads) pick_lists_kernel(const float* __
 // Bound by latencies, and by the way of the maxima (256 KB for 16.8 M entries) into each compute unit: 5.4 us of the first launch's
 // 22.4 until they are there, 6.2 for the bound, 2.6 for the blocks' numbers, 2.5 until the blocks are there, 4.3 for the lists.
 // 16.8 M and 4.2 M, k = 4,096: 22.4 + 15.0 us, where clearing histograms and the four launches of the spans route took 4.5 + 41; on the
-// explorer's populations of copies 32.6 + 17.1 against 4.7 + 79.  From 768 entries per selected one on: 1 x 3.2 M, k = 4,096, 44 -> 38 us for
-// the call, 1 x 800,000, k = 1,025, 38.5 -> 29.6; below, the bound that k blocks reach leaves too many entries (390 of them: 42 -> 49).  A stretch of
-// 20,000 good entries among 3.2 M sorted ones takes longer (50 -> 61).  More segments: the spans route shares out the scores as well.
+// explorer's populations of copies 32.6 + 17.1 against 4.7 + 79.  From 768 entries per selected one on: 1 x 3.2 M, k = 4,096, 45 -> 39 us for
+// the call, 1 x 800,000, k = 1,025, 38.5 -> 29.6; below, the bound that k blocks reach leaves too many entries (390 of them: 42 -> 49).  Sorted scores
+// 5 M, k = 100, 57 -> 36; 16 M, k = 4,096, 99 -> 67.  Slower than by spans are some at this line only: 3.2 M, k = 4,096, sorted with 20,000
+// good ones in the middle 50 -> 57.5, with 300 values 40 -> 47.5.  More segments: the spans route shares out the scores as well.
 constexpr int kHeldQuads = 16;                                                        // of maxima, per thread
 constexpr int64_t kBlocksMax = (int64_t)4 * kHeldQuads * kBigThreads * 256;           // entries of a segment
 constexpr int kBlocksSegments = 4;
