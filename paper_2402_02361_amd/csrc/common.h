@@ -137,21 +137,25 @@ struct DraftPlan {
     bool in_launch = false;    // they travel with the launches themselves and are not uploaded (draft_upload decides)
     int64_t n = 0, tiles_pitch = 0;
     int32_t n_sg = 0, flags = 0;
+    bool exact = false;    // one rounded operation per step of Eq. 1
     bool makes = false;    // the kernels can make their candidates (the explorer loop's mutation) instead of reading them
 };
 // notes: what the selection would have the kernels leave behind; mut: the kernels
-// are to make their candidates from the second run on (plan->makes says whether they can).
+// are to make their candidates from the second run on (plan->makes says whether they can): the children of S_spec as they are drawn, or
+// all that it can have (few: always a launch per class then).
+enum class Makes { kNothing, kChildren, kVariants };
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
-               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, const ScoreNotes& notes, bool mut, DraftPlan* plan);
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, const ScoreNotes& notes, Makes mut, DraftPlan* plan);
 // (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables
 // and behind which nothing else lies that must stay.  An upload that begins right behind the tables (place_behind) shares
 // their launch.
 int draft_upload(DraftPlan& plan, void* workspace, hipStream_t stream, const Upload* also);
+bool fits_launch(const DraftPlan& plan);   // the tables are small enough to travel with the launches
 // Moves the pending table to the first free place behind the plan's tables in the same workspace (it was prepared for a later
 // one, so it fits); returns where it will lie.
 void* place_behind(const DraftPlan& plan, void* workspace, Upload* also);
 // Draft scores, and what `notes` asks for (as the plan was made for).  mut (needs plan.makes): the kernels make the children of
-// S_spec, store them over `tiles` (which is then written) and score them in one pass.
+// S_spec and score them (`tiles` stays as it is), or score all children that S_spec can have, or look the children's scores up there.
 int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tiles, float* score, int64_t* symbols, hipStream_t stream,
               const ScoreNotes& notes, const MutArgs* mut);
 // workspace needs of the entry points (each defined next to its kernels)

@@ -436,31 +436,39 @@ __device__ __forceinline__ void load_tiles(const SgDesc& d, const uint16_t* __re
     }
 }
 
-// SchMutation of Alg. 2 in place of the loads (the explorer loop from its second step on): the thread's four
-// candidates are made from parents in S_spec, stored as the population's new columns, and handed on in the layout the
-// loads would have produced; the population is written once and not read back.  NP: 16-byte pieces of a record that
-// the subgraph's slots reach.
+// SchMutation of Alg. 2 in place of the loads (the explorer loop from its second step on): the thread's
+// candidates are made from parents in S_spec and handed on in the layout the loads would have produced.  They are not stored as a
+// population: a child is a function of the step, its number and S_spec, and the few that are chosen are made again (21 M children, a
+// step: 221 us with the stores).  NP: 16-byte pieces of a record that the subgraph's slots reach.
 struct MutSeg {
     LseSeg seg;
     int32_t sub, count;   // count < 1: the subgraph has no S_spec, its population stays as it is
+    int64_t begin;        // of the launch's segment (the table's entries have others than the population)
 };
 
 template <class Nest, int VEC, int NP>
-__device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& ms, const MutArgs& mut, uint16_t* __restrict__ tiles,
-                                                 int64_t pitch, int64_t c0, int64_t c_end, RawTiles<Nest, VEC>& raw)
+__device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& ms, const MutArgs& mut, int64_t c0, int64_t c_end,
+                                                 RawTiles<Nest, VEC>& raw)
 {
     constexpr int NSP = Nest::NSP, NRD = Nest::NRD;
     constexpr int kRows = 8 * NP < PRUNER_MAX_SLOTS ? 8 * NP : PRUNER_MAX_SLOTS;
     const int live = c_end - c0 < VEC ? (int)(c_end - c0) : VEC;
     const uint64_t z0 = lse_child_state(mut.seed, mut.step, c0);
     uint32_t f[VEC][kAosWords];
-    lse_child<NP>(ms.seg, ms.sub, ms.count, mut.k, z0, mut.spec_aos, mut.mutate_q16, f[0]);
+    auto make = [&](int e) {
+        Move m;
+        if (mut.variants) m = move_of_variant(ms.seg, (int)(c0 - ms.begin) + e);
+        else m = drawn_move(ms.seg, ms.count, z0 + (uint64_t)(2 * e) * kGamma, mut.mutate_q16);
+        const int n_primes = child_of_move<NP>(ms.seg, ms.sub, mut.k, m, mut.spec_aos, f[e]);
+        if (mut.variants && n_primes > primes_told_apart(ms.seg.draws)) mut.odd[ms.sub] = 1;
+    };
+    make(0);
 #pragma unroll
     for (int e = 1; e < VEC; ++e) {
         if (e < live) {
-            lse_child<NP>(ms.seg, ms.sub, ms.count, mut.k, z0 + (uint64_t)(2 * e) * kGamma, mut.spec_aos, mut.mutate_q16, f[e]);
+            make(e);
         } else {
-            // past the segment's end: a valid schedule that is neither stored nor scored
+            // past the segment's end: a valid schedule that is not scored
 #pragma unroll
             for (int w = 0; w < kAosWords; ++w) f[e][w] = f[0][w];
         }
@@ -482,25 +490,12 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
     for (int row = 0; row < kAosSlots; ++row) {
         T[row] = Column{};
         if (row >= kRows) continue;
-        uint16_t* dst = tiles + (int64_t)row * pitch + c0;
         if constexpr (VEC == 4) {
             const uint32_t half = row & 1 ? 0x07060302u : 0x05040100u;
             T[row].x = __builtin_amdgcn_perm(f[1][row >> 1], f[0][row >> 1], half);
             T[row].y = __builtin_amdgcn_perm(f[3][row >> 1], f[2][row >> 1], half);
-            if (row < ms.seg.n_slots) {
-                if (live == 4) {
-                    // (not through the caches, for the scores and their blocks' maxima are read next: 21 M children, a step of the
-                    // explorer 3 us less in this kernel and 5 in those behind it)
-                    __builtin_nontemporal_store(T[row], reinterpret_cast<u32x2_a2*>(dst));
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 3; ++e)
-                        if (e < live) dst[e] = (uint16_t)(f[e][row >> 1] >> (16 * (row & 1)));
-                }
-            }
         } else {
             T[row] = (f[0][row >> 1] >> (16 * (row & 1))) & 0xFFFFu;
-            if (row < ms.seg.n_slots) dst[0] = (uint16_t)T[row];
         }
     }
 #pragma unroll
@@ -532,15 +527,14 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
 }
 
 template <class Nest, int VEC>
-__device__ __forceinline__ void make_children(const SgDesc& d, const MutSeg& ms, const MutArgs& mut, uint16_t* __restrict__ tiles, int64_t pitch,
-                                              int64_t c0, int64_t c_end, RawTiles<Nest, VEC>& raw)
+__device__ __forceinline__ void make_children(const SgDesc& d, const MutSeg& ms, const MutArgs& mut, int64_t c0, int64_t c_end, RawTiles<Nest, VEC>& raw)
 {
     switch ((ms.seg.n_slots + 7) >> 3) {   // the same for the whole workgroup
         case 0:
-        case 1: make_children_np<Nest, VEC, 1>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
-        case 2: make_children_np<Nest, VEC, 2>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
-        case 3: make_children_np<Nest, VEC, 3>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
-        default: make_children_np<Nest, VEC, 4>(d, ms, mut, tiles, pitch, c0, c_end, raw); break;
+        case 1: make_children_np<Nest, VEC, 1>(d, ms, mut, c0, c_end, raw); break;
+        case 2: make_children_np<Nest, VEC, 2>(d, ms, mut, c0, c_end, raw); break;
+        case 3: make_children_np<Nest, VEC, 3>(d, ms, mut, c0, c_end, raw); break;
+        default: make_children_np<Nest, VEC, 4>(d, ms, mut, c0, c_end, raw); break;
     }
 }
 
@@ -780,6 +774,62 @@ __device__ __forceinline__ void analyze_fused(const SgDesc& d, const Symbols (&y
     for (int v = 0; v < VEC; ++v) score[v] = -__builtin_fmaf(sum[v], w[v], L[v]);
 }
 
+// The scores of candidates c0 .. c0 + VEC - 1, those in [c_lo, c_end): what the selection asks for, while they are in registers, and their stores.
+template <int VEC, bool DUMP, bool HIST, bool MUT>
+__device__ __forceinline__ void leave_scores(const float (&out)[VEC], int64_t c0, int64_t c_lo, int64_t c_end, float* __restrict__ score, uint32_t* digit_hist,
+                                             bool count_digits, uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16,
+                                             int seg_index)
+{
+    if (HIST && count_digits) {
+        // the selection stage's first pass, done here while the scores are in registers.  Plain LDS atomics: even
+        // when all lanes hit one bin (equal scores) their serialisation stays hidden under this kernel's loads.
+        uint32_t top = 0;   // below the key of every number
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+            if (c0 + v >= c_lo && c0 + v < c_end) {
+                uint32_t digit;
+                const uint32_t key = key_and_digit(out[v], digit);
+                atomicAdd(&digit_hist[digit], 1u);
+                top = key > top ? key : top;
+            }
+        }
+        // and the largest key of the wavefront's 256 neighbouring candidates, by which the selection's second pass steps
+        // over the block.  The lanes at work here are lanes 0..m (a thread is here when its first candidate lies inside
+        // the segment): lane m ends up with the maximum.
+        if constexpr (VEC == 4) {
+            if (block_max) {
+                top = wave_inclusive_max(top);
+                const int last = 63 - __clzll(__ballot(true));
+                if (lane_id() == last) block_max[block_max_slot(c_lo - 4 * last, seg_index)] = top;
+            }
+        }
+    }
+
+    if constexpr (!DUMP && (!HIST || MUT)) {
+        if (max16 || (block_max && !(HIST && count_digits))) {
+            // The largest keys of neighbouring candidates, by which the selection finds those that can matter.  The lanes at work are lanes
+            // 0..m (as above).  Without the special case of -0, which is put right once.
+            uint32_t top = 0;
+            const bool whole = c0 >= c_lo && c0 + VEC <= c_end;
+#pragma unroll
+            for (int v = 0; v < VEC; ++v) {
+                const uint32_t u = __float_as_uint(out[v]), key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+                top = (whole || (c0 + v >= c_lo && c0 + v < c_end)) && key > top ? key : top;
+            }
+            top = top == ~0x80000000u ? 0x80000000u : top;
+            note_maxima<VEC>(top, c_lo, 63 - __clzll(__ballot(true)), c_end, seg_index, max16, max64, block_max);
+        }
+    }
+
+    if (VEC == 4 && c0 >= c_lo && c0 + VEC <= c_end) {
+        *reinterpret_cast<f32x4_a4*>(score + c0) = f32x4{out[0], out[1 % VEC], out[2 % VEC], out[3 % VEC]};
+    } else {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v)
+            if (c0 + v >= c_lo && c0 + v < c_end) score[c0 + v] = out[v];
+    }
+}
+
 // raw holds candidates c0 .. c0 + VEC - 1; those in [c_lo, c_end) are scored (c_lo is c0 but for the thread that would read past
 // the end of the population: it reads its last VEC and leaves the first of them to its neighbour).
 template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
@@ -920,52 +970,32 @@ __device__ __forceinline__ void score_candidates(const SgDesc& d, const RawTiles
         }
     }
 
-    if (HIST && count_digits) {
-        // the selection stage's first pass, done here while the scores are in registers.  Plain LDS atomics: even
-        // when all lanes hit one bin (equal scores) their serialisation stays hidden under this kernel's loads.
-        uint32_t top = 0;   // below the key of every number
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) {
-            if (c0 + v >= c_lo && c0 + v < c_end) {
-                uint32_t digit;
-                const uint32_t key = key_and_digit(out[v], digit);
-                atomicAdd(&digit_hist[digit], 1u);
-                top = key > top ? key : top;
-            }
-        }
-        // and the largest key of the wavefront's 256 neighbouring candidates, by which the selection's second pass steps
-        // over the block.  The lanes at work here are lanes 0..m (a thread is here when its first candidate lies inside
-        // the segment): lane m ends up with the maximum.
-        if constexpr (VEC == 4) {
-            if (block_max) {
-                top = wave_inclusive_max(top);
-                const int last = 63 - __clzll(__ballot(true));
-                if (lane_id() == last) block_max[block_max_slot(c_lo - 4 * last, seg_index)] = top;
-            }
-        }
-    }
+    leave_scores<VEC, DUMP, HIST, MUT>(out, c0, c_lo, c_end, score, digit_hist, count_digits, block_max, max64, max16, seg_index);
+}
 
-    if constexpr (!DUMP && (!HIST || MUT)) {
-        if (max16 || (block_max && !(HIST && count_digits))) {
-            // The largest keys of neighbouring candidates, by which the selection finds those that can matter.  The lanes at work are lanes
-            // 0..m (as above).  Without the special case of -0, which is put right once.
-            uint32_t top = 0;
+// The scores of a segment's children where those of all children that its S_spec can have are in a table: what a child costs is its draws.
+// Bound: vector instructions (two draws of 64-bit multiplies and the place of the move; the subgraph's constants are scalars).
+template <int VEC, bool HIST, int DRAWS>
+__device__ __forceinline__ void look_children_up(const LseSeg& seg, int sub, int members, const MutArgs& mut, int64_t c0, int64_t step, int iters, int64_t end,
+                                                 float* __restrict__ score, uint32_t* digit_hist, bool count_digits, uint32_t* __restrict__ block_max,
+                                                 uint32_t* __restrict__ max64, uint32_t* __restrict__ max16)
+{
+    MoveNumbers m;
+    m.n_sp = (uint32_t)__builtin_amdgcn_readfirstlane(seg.n_sp);
+    m.n_axes = (uint32_t)__builtin_amdgcn_readfirstlane(seg.n_sp + seg.n_rd);
+    m.rd_levels = (uint32_t)__builtin_amdgcn_readfirstlane(seg.rd_levels);
+    m.per_parent = (uint32_t)__builtin_amdgcn_readfirstlane(seg.per_parent);
+    m.plain_copy = m.per_parent / DRAWS - 1u;
+    m.count = (uint32_t)__builtin_amdgcn_readfirstlane(members);
+    const float* const table = mut.table + __builtin_amdgcn_readfirstlane(seg.table_at);
+    uint64_t z = lse_child_state(mut.seed, mut.step, c0);
+    const uint64_t z_step = 2ull * (uint64_t)step * kGamma;
+    for (int it = 0; it < iters; ++it, c0 += step, z += z_step) {
+        if (c0 >= end) return;
+        float out[VEC];
 #pragma unroll
-            for (int v = 0; v < VEC; ++v) {
-                const uint32_t u = __float_as_uint(out[v]), key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
-                top = c0 + v >= c_lo && c0 + v < c_end && key > top ? key : top;
-            }
-            top = top == ~0x80000000u ? 0x80000000u : top;
-            note_maxima<VEC>(top, c_lo, 63 - __clzll(__ballot(true)), c_end, seg_index, max16, max64, block_max);
-        }
-    }
-
-    if (VEC == 4 && c0 >= c_lo && c0 + VEC <= c_end) {
-        *reinterpret_cast<f32x4_a4*>(score + c0) = f32x4{out[0], out[1 % VEC], out[2 % VEC], out[3 % VEC]};
-    } else {
-#pragma unroll
-        for (int v = 0; v < VEC; ++v)
-            if (c0 + v >= c_lo && c0 + v < c_end) score[c0 + v] = out[v];
+        for (int e = 0; e < VEC; ++e) out[e] = table[variant_drawn<DRAWS>(m, z + (uint64_t)(2 * e) * kGamma, mut.mutate_q16)];   // (a child past the end is one of the table's too; it is not stored)
+        leave_scores<VEC, false, HIST, true>(out, c0, c0, end, score, digit_hist, count_digits, block_max, max64, max16, sub);
     }
 }
 
@@ -976,7 +1006,7 @@ template <class Nest, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
 __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg, int32_t b, const uint16_t* __restrict__ tiles,
                                              int64_t pitch, int32_t flags, const float* p2m_tab, float* __restrict__ score,
                                              int64_t* __restrict__ symbols, int64_t n_total, uint32_t* digit_hist, bool count_digits,
-                                             uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, const MutArgs& mut)
+                                             uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, const MutArgs& mut, bool looked_up)
 {
     const int64_t step = (int64_t)seg.blocks * kBlock * VEC;
     RawTiles<Nest, VEC> cur{}, nxt{};
@@ -987,18 +1017,31 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
         ms.seg = mut.segs[seg.seg];
         ms.sub = seg.seg;
         ms.count = mut.spec_count[seg.seg];
+        ms.begin = seg.begin;
         if (ms.count >= 1) {
-            // (the population is this call's to write: the explorer loop hands its own buffer in)
-            uint16_t* out = const_cast<uint16_t*>(tiles);
+            int64_t end = seg.end;
+            if (mut.variants) {   // (entries of members that S_spec does not have are no one's)
+                const int64_t used = seg.begin + (int64_t)ms.count * ms.seg.per_parent;
+                end = used < end ? used : end;
+            }
+            if (looked_up) {
+#define PRUNER_LOOK_UP(DRAWS) look_children_up<VEC, HIST, DRAWS>(ms.seg, ms.sub, ms.count, mut, c0, step, seg.iters, end, score, digit_hist, count_digits, block_max, max64, max16)
+                if (ms.seg.draws == 1) PRUNER_LOOK_UP(1);
+                else if (ms.seg.draws == 2) PRUNER_LOOK_UP(2);
+                else PRUNER_LOOK_UP(4);
+#undef PRUNER_LOOK_UP
+                return;
+            }
             for (int it = 0; it < seg.iters; ++it) {
-                if (c0 < seg.end) {
-                    make_children<Nest, VEC>(d, ms, mut, out, pitch, c0, seg.end, cur);
-                    score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, c0, c0, seg.end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
+                if (c0 < end) {
+                    make_children<Nest, VEC>(d, ms, mut, c0, end, cur);
+                    score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, c0, c0, end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
                 }
                 c0 += step;
             }
             return;
         }
+        if (mut.variants) return;
     }
     if constexpr (MUT || Nest::NSP * 4 + Nest::NRD * 3 > 16) {
         // many slots: a second set of them in flight costs more in occupancy than it gains
@@ -1061,13 +1104,15 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(DraftTables /* read throu
     // three memory statements look them up.
     __shared__ float tab[kTabMax + 1];
     __shared__ uint32_t digit_hist[HIST ? kBins : 1];
+    // (the explorer loop's children, where their scores are looked up: nothing is analysed)
+    const bool looked_up = MUT && mut.table && mut.segs[seg.seg].draws > 0 && mut.odd[seg.seg] == 0, use_tab = seg.use_tab && !looked_up;
     // (the kernels that make their candidates also serve populations whose selection counts its digits itself)
     const bool count_digits = HIST && (!MUT || first_digit != nullptr);
     if (HIST && count_digits) {
         for (int i = threadIdx.x; i < kBins; i += kBlock) digit_hist[i] = 0;
-        if (!seg.use_tab) __syncthreads();
+        if (!use_tab) __syncthreads();
     }
-    if (seg.use_tab) {
+    if (use_tab) {
         for (int r = threadIdx.x; r <= d.run_max; r += kBlock) {
             const uint32_t run[1] = {r > 0 ? (uint32_t)r : 1u};
             uint32_t up[1];
@@ -1076,9 +1121,9 @@ __global__ void __launch_bounds__(kBlock) draft_kernel(DraftTables /* read throu
         }
         __syncthreads();
     }
-    const float* p2m_tab = seg.use_tab ? tab : nullptr;
+    const float* p2m_tab = use_tab ? tab : nullptr;
 
-#define PRUNER_WALK(NEST) walk_segment<NEST, VEC, DUMP, EXACT, HIST, MUT>(d, seg, b, tiles, pitch, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, mut)
+#define PRUNER_WALK(NEST) walk_segment<NEST, VEC, DUMP, EXACT, HIST, MUT>(d, seg, b, tiles, pitch, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, mut, looked_up)
     if constexpr (CLS == kGemm) PRUNER_WALK(NestGemm);
     else if constexpr (CLS == kBatchedGemm) PRUNER_WALK(NestBatchedGemm);
     else if constexpr (CLS == kConv2d) PRUNER_WALK(NestConv2d);
@@ -1474,7 +1519,7 @@ void* g_time_stop = nullptr;
 int64_t* g_time_bytes = nullptr;
 
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
-               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, const ScoreNotes& notes, bool mut, DraftPlan* out)
+               const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, const ScoreNotes& notes, Makes mut, DraftPlan* out)
 {
     if (!sg || !seg_off || n_sg < 1 || n_sg > PRUNER_MAX_SUBGRAPHS) return PRUNER_EINVAL;
     if (flags & ~(PRUNER_NO_COMPUTE_PENALTY | PRUNER_NO_MEMORY_PENALTY | PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) return PRUNER_EINVAL;
@@ -1523,8 +1568,9 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // thread's chain of divisions a quarter as long (reading: 4,096 GEMM candidates 5.8 -> 5.0 us, 65,536 of a convolution 7.4 -> 5.8,
     // 262,144 7.7 -> 7.0; making: 8,000 10.6 -> 5.6, 65,536 13.2 -> 7.7, 262,144 13.8 -> 11.8; at 400,000 a tenth less as well, but
     // the maxima of 256 neighbours want fours).
-    const bool spread = n <= kSpreadMax && n_classes <= (mut ? 2 : 1) && !notes.max256 && !notes.first_digit && !symbols;
-    const int vec = spread ? 1 : mut || notes.max256 || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
+    const bool makes = mut != Makes::kNothing;
+    const bool spread = ((n <= kSpreadMax && n_classes <= (makes ? 2 : 1)) || mut == Makes::kVariants) && !notes.max256 && !notes.first_digit && !symbols;
+    const int vec = spread ? 1 : makes || notes.max256 || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
 
     // Launch plan.  With four candidates per thread: one launch per loop-nest class present, the table grouped by class, when the
     // population is large (with more than two classes: 2^20 candidates for each, since every launch begins and ends with a
@@ -1541,7 +1587,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     std::vector<int32_t> order(n_sg);
     for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
     const bool large = vec == 4 && n >= kPerClassMin;
-    const bool by_class = spread || (vec == 4 && ((large && (mut || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (mut ? 2 : 1)));
+    const bool by_class = spread || (vec == 4 && ((large && (makes || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (makes ? 2 : 1) || mut == Makes::kVariants));
     if (by_class && n_classes > 1) {   // (a pass per class: sorting a thousand segments of one class took 14 us of host time)
         order.clear();
         for (uint32_t left = classes; left; left &= left - 1)
@@ -1553,8 +1599,9 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // out in fours (as the boundary promises; how many launches there are plays no part), the multiplied-out form for the
     // other large populations, unless a flag asks for one of them.
     const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !(large && in_fours));
+    out->exact = exact;
     const bool hist = notes.first_digit && symbols == nullptr;
-    const bool fused = mut && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself
+    const bool fused = makes && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
     std::vector<int64_t> chunks_of;
     for (int32_t i = 0; i < n_sg; ++i) {
@@ -1604,6 +1651,8 @@ void* place_behind(const DraftPlan& plan, void* workspace, Upload* also)
     return also->dst;
 }
 
+bool fits_launch(const DraftPlan& plan) { return plan.image.size() <= sizeof(DraftTables); }
+
 int draft_upload(DraftPlan& plan, void* workspace, hipStream_t st, const Upload* also)
 {
     char* ws = static_cast<char*>(workspace);
@@ -1611,7 +1660,7 @@ int draft_upload(DraftPlan& plan, void* workspace, hipStream_t st, const Upload*
     if (plan.n == 0) return pending ? put_table(also->dst, also->bytes.data(), also->bytes.size(), st, also->zero, also->zero_bytes) : PRUNER_OK;
     // (where something else is uploaded anyway the tables go with it: from the workspace, through the caches, a launch has
     // them 0.3 us sooner than from its arguments)
-    plan.in_launch = !pending && plan.image.size() <= sizeof(DraftTables);
+    plan.in_launch = !pending && fits_launch(plan);
     if (plan.in_launch) return PRUNER_OK;
     if (!pending) return put_table(ws, plan.image.data(), plan.image.size(), st);
     // the other table rides along in the same launch if it starts shortly behind this call's tables (with many
@@ -1663,7 +1712,7 @@ extern "C" int pruner_draft_score(const pruner_subgraph* sg, int32_t n_sg, const
 {
     hipStream_t st = static_cast<hipStream_t>(stream);
     DraftPlan plan;
-    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes, ScoreNotes{}, false, &plan);
+    int rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, symbols, workspace, workspace_bytes, ScoreNotes{}, Makes::kNothing, &plan);
     if (rc) return rc;
     rc = draft_upload(plan, workspace, st, nullptr);
     if (rc) return rc;

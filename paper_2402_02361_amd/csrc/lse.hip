@@ -92,11 +92,12 @@ __device__ __forceinline__ int spec_members(const int32_t* count, int s, int k)
 // Three launches over the whole device instead of a sort by one workgroup per subgraph.  21 million programs in one segment,
 // k = 4096, a step: 11 + 7 + 6 us, where keys, sort and copies took 22 + 53 + 10.
 
-// The records and sort keys of the k best of S_x, 64 per workgroup, which leaves their keys in order.  The schedules sit at
-// random places of the population, two bytes a row: sixteen lanes per schedule, so that all misses are under way at once.
+// The records and sort keys of the k best of S_x, 64 per workgroup, which leaves their keys in order.  Schedules of a population sit at
+// random places, two bytes a row: sixteen lanes per schedule, so that all misses are under way at once.  Children that the draft
+// kernels made are not stored and are made again here, one by a lane.
 constexpr int kRun = kWave;   // neighbours of the k best whose keys are in order
 __global__ void __launch_bounds__(kLseThreads) lse_keys_kernel(const LseSeg* __restrict__ segs, int k, bool first, const int32_t* __restrict__ old_count,
-                                                               const uint16_t* __restrict__ tiles, int64_t pitch,
+                                                               const uint16_t* __restrict__ tiles, int64_t pitch, MutArgs made /* spec_aos null: not */,
                                                                const int32_t* __restrict__ best_idx, const float* __restrict__ best_val,
                                                                uint64_t* __restrict__ fresh_hi, uint64_t* __restrict__ fresh_lo,
                                                                uint32_t* __restrict__ fresh_aos)
@@ -108,13 +109,23 @@ __global__ void __launch_bounds__(kLseThreads) lse_keys_kernel(const LseSeg* __r
     const int64_t col0 = (int64_t)s * k;
     const int r = blockIdx.x * kRun + c;
     uint32_t word = 0;
-    if (r < k) {
+    if (made.spec_aos) {
+        const int child = blockIdx.x * kRun + (int)threadIdx.x;
+        if (threadIdx.x < kRun && child < k) {
+            uint32_t packed[kAosWords];
+            lse_child<kAosSlots / 8>(segs[s], s, made.spec_count[s], k, lse_child_state(made.seed, made.step, best_idx[col0 + child]), made.spec_aos, made.mutate_q16, packed);
+#pragma unroll
+            for (int i = 0; i < kAosWords; ++i) record[threadIdx.x][i] = packed[i];
+        }
+        __syncthreads();
+        if (r < k) fresh_aos[(col0 + r) * kAosWords + w] = record[c][w];
+    } else if (r < k) {
         const uint16_t* col = tiles + best_idx[col0 + r];
         const uint32_t low = 2 * w < n_slots ? col[(int64_t)(2 * w) * pitch] : 0u, high = 2 * w + 1 < n_slots ? col[(int64_t)(2 * w + 1) * pitch] : 0u;
         word = low | high << 16;
         fresh_aos[(col0 + r) * kAosWords + w] = word;
     }
-    record[c][w] = word;
+    if (!made.spec_aos) record[c][w] = word;
     __syncthreads();
     if (threadIdx.x >= kRun) return;
     const int mine = blockIdx.x * kRun + (int)threadIdx.x;
@@ -809,6 +820,24 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows, bool part
     return L;
 }
 
+// The values of a move's prime draw that matter for a subgraph's schedules (LseSeg::draws): their factors divide the extents.
+int draws_of(const pruner_subgraph& s)
+{
+    int most = 0;
+    for (int a = 0; a < s.n_sp + s.n_rd; ++a) {
+        int primes = 0;
+        int32_t rest = s.extent[a];
+        for (int32_t p = 2; p * p <= rest; ++p) {
+            if (rest % p == 0) ++primes;
+            while (rest % p == 0) rest /= p;
+        }
+        if (rest > 1) ++primes;
+        most = primes > most ? primes : most;
+    }
+    return s.rd_levels < 2 ? 0 : most <= 1 ? 1 : most == 2 ? 2 : most == 3 ? 4 : 0;
+}
+constexpr int64_t kTableGain = 4;   // children per entry of a table from which one is made
+
 constexpr int64_t kSpreadChildren = 1 << 17;   // children up to which a launch makes one per thread (8,000: 6.3 -> 4.0 us)
 constexpr int kMostGroups = 8;        // of 64 entries per workgroup of the rank kernel
 constexpr int kManyUniters = 2048;   // workgroups of 64 places: four times what the device holds at once
@@ -858,7 +887,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         const int32_t n_slots = sg[s].n_sp * 4 + sg[s].n_rd * sg[s].rd_levels;
         if (n_slots > tile_rows) return PRUNER_EINVAL;
         const bool frag = sg[s].frag[0] != 0 || sg[s].frag[1] != 0 || sg[s].frag[2] != 0;
-        table[s] = LseSeg{seg_off[s], seg_off[s + 1], sg[s].n_sp, sg[s].n_rd, sg[s].rd_levels, n_slots,
+        table[s] = LseSeg{seg_off[s], seg_off[s + 1], (int8_t)sg[s].n_sp, (int8_t)sg[s].n_rd, (int8_t)sg[s].rd_levels, 0, (int16_t)n_slots, 0,
                           {frag ? sg[s].frag[0] : 0, frag ? sg[s].frag[1] : 0, frag ? sg[s].frag[2] : 0}, 0};
     }
 
@@ -886,7 +915,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     for (int32_t s = 0; s < n_sg; ++s) longest = seg_off[s + 1] - seg_off[s] > longest ? seg_off[s + 1] - seg_off[s] : longest;
     if (longest <= kShortMax && k <= kShortK) {
         DraftPlan plan;
-        rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ScoreNotes{}, n_steps > 1, &plan);
+        rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ScoreNotes{}, n_steps > 1 ? Makes::kChildren : Makes::kNothing, &plan);
         if (rc) return rc;
         // all tables in one launch: this route has no selection workspace, the segment table stands in its place
         d_table = reinterpret_cast<LseSeg*>(ws + L.filter + draft_bytes);
@@ -898,7 +927,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         for (int32_t t = 0; t < n_steps; ++t) {
             const Spec &now = spec[t & 1], &before = spec[(t & 1) ^ 1];
             uint4* const children = reinterpret_cast<uint4*>(ws + L.children);
-            const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, children};
+            const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, children, nullptr, nullptr, 0};
             const bool made = t > 0 && plan.makes;
             if (t > 0 && !plan.makes) {
                 mutate(t - 1, before.count, before.aos);
@@ -930,13 +959,36 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
             return PRUNER_EHIP;
         g_rank_ready.mark(dev);
     }
-    rc = put_table(d_table, table.data(), table.size() * sizeof(LseSeg), st);
+    // Segments with many times more children than S_spec can have different ones (k times some thirty to a few hundred: a child is
+    // one of few moves away from its parent) get a table of all of these and their scores.  It stands where the short route has its
+    // children as records.
+    std::vector<int64_t> variant_off(n_sg + 1, 0);
+    int32_t* const odd = reinterpret_cast<int32_t*>(ws + L.children);
+    float* const scores_of_all = reinterpret_cast<float*>(ws + L.children + round_up((size_t)n_sg * sizeof(int32_t), 256));
+    {
+        const int64_t room = (int64_t)(L.total - L.children) - (int64_t)round_up((size_t)n_sg * sizeof(int32_t), 256);
+        int64_t end = 0;
+        for (int32_t s = 0; s < n_sg; ++s) {
+            variant_off[s] = end;
+            const int draws = draws_of(sg[s]), per_parent = draws * move_count(sg[s].n_sp, sg[s].n_rd, sg[s].rd_levels);
+            const int64_t entries = ((int64_t)k * per_parent + 3) & ~3ll;
+            if (n_steps < 2 || draws == 0 || seg_off[s + 1] - seg_off[s] < kTableGain * entries || (end + entries) * (int64_t)sizeof(float) > room) continue;
+            table[s].draws = (int8_t)draws;
+            table[s].per_parent = (int16_t)per_parent;
+            table[s].table_at = (int32_t)end;
+            end += entries;
+        }
+        variant_off[n_sg] = end;
+    }
+    const int64_t table_end = variant_off[n_sg];
+    rc = put_table(d_table, table.data(), table.size() * sizeof(LseSeg), st, table_end > 0 ? odd : nullptr, table_end > 0 ? (size_t)n_sg * sizeof(int32_t) : 0);
     if (rc) return rc;
 
     const size_t filter_bytes = L.table - L.filter;
     // The mutation of step t - 1 is owed when step t begins: the draft kernels of step t make, store and score the
     // children in one pass if their launch shape allows it, else it runs as a launch of its own first.
-    DraftPlan plan_first, plan_later;
+    DraftPlan plan_first, plan_later, plan_table;
+    bool tabled = false;   // the children's scores are looked up
     for (int32_t t = 0; t < n_steps; ++t) {
         const Spec &now = spec[t & 1], &before = spec[(t & 1) ^ 1];
         // C_SA over S_x and its k best: the launches of pruner_prior_filter
@@ -944,20 +996,36 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         Upload pending;
         rc = topk_prepare(seg_off, n_sg, k, ws + L.filter + draft_bytes, filter_bytes - draft_bytes, st, &ctx, &pending, true, true);
         if (rc) return rc;
-        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), false, &plan_first);
-        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), true, &plan_later);
+        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), Makes::kNothing, &plan_first);
+        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), Makes::kChildren, &plan_later);
         if (rc) return rc;
+        if (t == 1 && table_end > 0 && plan_later.makes) {
+            const int32_t as_they = (flags & ~(PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) | (plan_later.exact ? PRUNER_REFERENCE_ROUNDING : PRUNER_FUSED_ARITHMETIC);
+            rc = draft_plan(sg, n_sg, variant_off.data(), tiles, table_end > tiles_pitch ? table_end : tiles_pitch, as_they, scores_of_all, nullptr, draft_ws, draft_bytes, ScoreNotes{},
+                            Makes::kVariants, &plan_table);
+            if (rc) return rc;
+            plan_table.in_launch = true;
+            tabled = fits_launch(plan_table) && plan_table.makes;
+        }
         DraftPlan& plan = t == 0 ? plan_first : plan_later;
-        const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, nullptr};
+        const bool made = t > 0 && plan.makes;
+        const MutArgs owed{d_table, before.aos, before.count, seed, (uint64_t)(t - 1), mutate_q16, k, nullptr, made && tabled ? scores_of_all : nullptr, odd, 0};
         if (t > 0 && !plan.makes) {
             mutate(t - 1, before.count, before.aos);
             PRUNER_LAUNCH_CHECK();
+        }
+        if (made && tabled) {
+            MutArgs all = owed;
+            all.table = nullptr;
+            all.variants = 1;
+            rc = draft_run(plan_table, draft_ws, tiles, scores_of_all, nullptr, st, ScoreNotes{}, &all);
+            if (rc) return rc;
         }
         if (pending.dst) ctx.d_segs = place_behind(plan, draft_ws, &pending);
         rc = draft_upload(plan, draft_ws, st, &pending);
         if (rc) return rc;
         rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, notes_for(ctx),
-                       t > 0 && plan.makes ? &owed : nullptr);
+                       made ? &owed : nullptr);
         if (rc) return rc;
         rc = topk_finish(ctx, score, seg_off, best_idx, best_val, true, st);
         if (rc) return rc;
@@ -965,7 +1033,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         uint64_t *fresh = words(L.fresh), *merged = words(L.merged);
         uint32_t* const fresh_aos = reinterpret_cast<uint32_t*>(ws + L.fresh_aos);
         hipLaunchKernelGGL(lse_keys_kernel, dim3((unsigned)((k + kRun - 1) / kRun), (unsigned)n_sg), dim3(kLseThreads), 0, st, d_table, k, t == 0,
-                           before.count, tiles, tiles_pitch, best_idx, best_val, fresh, fresh + spec_pitch, fresh_aos);
+                           before.count, tiles, tiles_pitch, made ? owed : MutArgs{}, best_idx, best_val, fresh, fresh + spec_pitch, fresh_aos);
         PRUNER_LAUNCH_CHECK();
         // (a workgroup loads both lists before it ranks: where there are workgroups for several rounds of the device, which holds one
         // to two of them per compute unit, each ranks more groups.  100 subgraphs, k = 3,370, four steps: 2,269 us one group each,

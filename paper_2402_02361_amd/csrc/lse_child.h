@@ -7,9 +7,12 @@ namespace pruner {
 
 struct alignas(8) LseSeg {
     int64_t begin, end;
-    int32_t n_sp, n_rd, rd_levels, n_slots;
-    int32_t frag[3];     // 0 outside fragment mode
-    int32_t pad;
+    int8_t n_sp, n_rd, rd_levels;
+    int8_t draws;         // values of a move's prime draw that a table of scores tells apart: 1, 2 or 4; 0: the subgraph has no table
+    int16_t n_slots;
+    int16_t per_parent;   // entries of the table that are children of one parent: move_count() x draws
+    int32_t frag[3];      // 0 outside fragment mode
+    int32_t table_at;     // where the subgraph's entries begin
 };
 
 // A member of S_spec as one record: its tile factors side by side (32 x uint16 = 64 bytes), so that a parent is read
@@ -38,16 +41,80 @@ __device__ __forceinline__ bool divides(uint32_t p, uint32_t x, uint32_t& q)
 
 constexpr int kAosWords = kAosSlots / 2;
 
-// One child of subgraph `sub` (its S_spec holds `count` >= 1 schedules) from the generator state z1 of its first draw
-// (the second draw follows it): `packed` receives its tile factors, two per word, as the parent's record holds them.
-// The two slots a mutation touches are read from the record directly, and the child differs from the record by XOR
-// masks on their two words: no slot is looked up in registers by a computed index.
-template <int NP>   // NP: the 16-byte pieces of a record that the subgraph's slots reach; words past them stay 0
-__device__ __forceinline__ void lse_child(const LseSeg& seg, int sub, int count, int k, uint64_t z1, const uint4* __restrict__ spec_aos,
-                                          uint32_t mutate_q16, uint32_t (&packed)[kAosWords])
+// What the draws of a child decide: its parent, and whether and how one of the parent's tile factors gives a prime factor to another level.
+struct Move {
+    int parent;            // the member of S_spec
+    bool moves;            // else the child is a plain copy
+    int axis, src, dst;    // dst: the destination among the other levels of the axis, 0 .. levels - 2
+    uint32_t prime_draw;   // eight bits that pick one of the distinct primes of the factor
+};
+
+__device__ __forceinline__ int levels_of(const LseSeg& seg, int axis) { return axis < seg.n_sp ? 4 : seg.rd_levels; }
+
+// The move of the child whose first draw has the generator state z1 (the second draw follows it); count: members of S_spec.
+__device__ __forceinline__ Move drawn_move(const LseSeg& seg, int count, uint64_t z1, uint32_t mutate_q16)
+{
+    Move m{};
+    const uint64_t u1 = splitmix64_mix(z1);
+    m.parent = (int)__umulhi((uint32_t)u1, (uint32_t)count);
+    m.moves = ((uint32_t)(u1 >> 32) & 0xFFFFu) < mutate_q16;
+    const uint32_t u2 = (uint32_t)splitmix64_mix(z1 + kGamma);
+    m.axis = pick8(u2, (uint32_t)(seg.n_sp + seg.n_rd));
+    const int levels = levels_of(seg, m.axis);
+    m.src = pick8(u2 >> 8, (uint32_t)levels);
+    m.dst = pick8(u2 >> 16, (uint32_t)(levels - 1));
+    m.prime_draw = u2 >> 24;
+    return m;
+}
+
+// ---- all possible children of a parent ----
+// A subgraph's moves are numbered by axis, source and destination, the plain copy last; every move has as many entries as its
+// prime draw has distinguishable values: one where a factor has one distinct prime at most, two halves for two, and the four pieces
+// that halves and thirds cut 0..255 into for three.  Subgraphs with more primes in an extent have no table.
+__host__ __device__ constexpr int move_count(int n_sp, int n_rd, int rd_levels) { return 12 * n_sp + rd_levels * (rd_levels - 1) * n_rd + 1; }
+__host__ __device__ constexpr int primes_told_apart(int draws) { return draws == 4 ? 3 : draws; }
+
+struct MoveNumbers {   // a subgraph's constants
+    uint32_t n_sp, n_axes, rd_levels, per_parent, plain_copy, count;
+};
+// The entry of the child whose first draw has the generator state z1 (drawn_move(), numbered), from the subgraph's first on.
+template <int DRAWS> __device__ __forceinline__ uint32_t variant_drawn(const MoveNumbers& m, uint64_t z1, uint32_t mutate_q16)
 {
     const uint64_t u1 = splitmix64_mix(z1);
-    const uint4* parent = spec_aos + ((int64_t)sub * k + (int64_t)__umulhi((uint32_t)u1, (uint32_t)count)) * (kAosSlots / 8);
+    const uint32_t u2 = (uint32_t)splitmix64_mix(z1 + kGamma);
+    const uint32_t parent = __umulhi((uint32_t)u1, m.count);
+    const bool moves = ((uint32_t)(u1 >> 32) & 0xFFFFu) < mutate_q16;
+    const uint32_t axis = (uint32_t)pick8(u2, m.n_axes);
+    const bool spatial = axis < m.n_sp;
+    const uint32_t others = spatial ? 3u : m.rd_levels - 1u, each = spatial ? 12u : m.rd_levels * (m.rd_levels - 1u), from = spatial ? 0u : m.n_sp * (12u - m.rd_levels * (m.rd_levels - 1u));
+    const uint32_t src = (uint32_t)pick8(u2 >> 8, others + 1u), dst = (uint32_t)pick8(u2 >> 16, others), x = u2 >> 24;
+    const uint32_t number = moves ? __umul24(axis, each) + from + __umul24(src, others) + dst : m.plain_copy;
+    const uint32_t piece = DRAWS == 1 ? 0u : DRAWS == 2 ? x >> 7 : (x >= 86u ? 1u : 0u) + (x >= 128u ? 1u : 0u) + (x >= 171u ? 1u : 0u);
+    return __umul24(parent, m.per_parent) + number * DRAWS + piece;
+}
+__device__ __forceinline__ Move move_of_variant(const LseSeg& seg, int variant)   // the other way round
+{
+    Move m{};
+    m.parent = variant / seg.per_parent;
+    const int left = variant - m.parent * seg.per_parent, number = left / seg.draws, piece = left - number * seg.draws;
+    m.moves = number + 1 < move_count(seg.n_sp, seg.n_rd, seg.rd_levels);
+    const bool spatial = number < 12 * seg.n_sp;
+    const int levels = spatial ? 4 : seg.rd_levels, each = levels * (levels - 1), in = spatial ? number : number - 12 * seg.n_sp;
+    m.axis = m.moves ? (spatial ? 0 : seg.n_sp) + in / each : 0;
+    m.src = m.moves ? in % each / (levels - 1) : 0;
+    m.dst = m.moves ? in % each % (levels - 1) : 0;
+    m.prime_draw = seg.draws == 1 ? 0u : seg.draws == 2 ? (uint32_t)piece << 7 : piece == 0 ? 0u : piece == 1 ? 86u : piece == 2 ? 128u : 171u;
+    return m;
+}
+
+// The child of subgraph `sub` that a move makes: `packed` receives its tile factors, two per word, as the parent's record holds them.
+// The two slots a mutation touches are read from the record directly, and the child differs from the record by XOR
+// masks on their two words: no slot is looked up in registers by a computed index.  Returns the number of distinct primes among
+// which the draw picked (0 for a plain copy).
+template <int NP>   // NP: the 16-byte pieces of a record that the subgraph's slots reach; words past them stay 0
+__device__ __forceinline__ int child_of_move(const LseSeg& seg, int sub, int k, const Move& m, const uint4* __restrict__ spec_aos, uint32_t (&packed)[kAosWords])
+{
+    const uint4* parent = spec_aos + ((int64_t)sub * k + (int64_t)m.parent) * (kAosSlots / 8);
 #pragma unroll
     for (int q = 0; q < kAosSlots / 8; ++q) {
         uint4 w4 = make_uint4(0u, 0u, 0u, 0u);
@@ -56,21 +123,16 @@ __device__ __forceinline__ void lse_child(const LseSeg& seg, int sub, int count,
     }
     int word_src = -1, word_dst = -1;
     uint32_t mask_src = 0, mask_dst = 0;
-    if (((uint32_t)(u1 >> 32) & 0xFFFFu) < mutate_q16) {
-        const uint32_t u2 = (uint32_t)splitmix64_mix(z1 + kGamma);
-        const int n_axes = seg.n_sp + seg.n_rd;
-        const int axis = pick8(u2, (uint32_t)n_axes);
-        const int levels = axis < seg.n_sp ? 4 : seg.rd_levels;
+    int n_primes = 0;
+    if (m.moves) {
+        const int n_axes = seg.n_sp + seg.n_rd, axis = m.axis, levels = levels_of(seg, axis), src = m.src;
         const int base = axis < seg.n_sp ? axis * 4 : seg.n_sp * 4 + (axis - seg.n_sp) * seg.rd_levels;
-        const int src = pick8(u2 >> 8, (uint32_t)levels);
-        int dst = pick8(u2 >> 16, (uint32_t)(levels - 1));
-        if (dst >= src) ++dst;
+        const int dst = m.dst >= src ? m.dst + 1 : m.dst;
         const uint16_t* slots = reinterpret_cast<const uint16_t*>(parent);
         const uint32_t v = slots[base + src], at_dst_value = slots[base + dst];
         // distinct prime factors of v in ascending order (at most six below 2^16), 16 bits each, the last found lowest
         uint64_t primes_lo = 0;
         uint32_t primes_hi = 0;
-        int n_primes = 0;
         uint32_t rest = v;
         if (rest > 1 && (rest & 1u) == 0) {   // the factor 2 by shifts: tile factors are mostly powers of two
             primes_lo = 2, n_primes = 1;
@@ -85,7 +147,7 @@ __device__ __forceinline__ void lse_child(const LseSeg& seg, int sub, int count,
         }
         if (rest > 1) primes_hi = (primes_hi << 16) | (uint32_t)(primes_lo >> 48), primes_lo = (primes_lo << 16) | rest, ++n_primes;
         if (n_primes > 0) {
-            const int back = n_primes - 1 - pick8(u2 >> 24, (uint32_t)n_primes);   // the draw picks one of them
+            const int back = n_primes - 1 - pick8(m.prime_draw, (uint32_t)n_primes);   // the draw picks one of them
             const uint32_t p = (back < 4 ? (uint32_t)(primes_lo >> (16 * (back & 3))) : primes_hi >> (16 * (back & 1))) & 0xFFFFu;
             uint32_t smaller = v >> 1;
             if (p != 2) divides(p, v, smaller);
@@ -109,6 +171,15 @@ __device__ __forceinline__ void lse_child(const LseSeg& seg, int sub, int count,
     }
 #pragma unroll
     for (int w = 0; w < 4 * NP; ++w) packed[w] ^= (w == word_src ? mask_src : 0u) ^ (w == word_dst ? mask_dst : 0u);
+    return n_primes;
+}
+
+// One child of subgraph `sub` (its S_spec holds `count` >= 1 schedules) from the generator state z1 of its first draw.
+template <int NP>
+__device__ __forceinline__ void lse_child(const LseSeg& seg, int sub, int count, int k, uint64_t z1, const uint4* __restrict__ spec_aos,
+                                          uint32_t mutate_q16, uint32_t (&packed)[kAosWords])
+{
+    (void)child_of_move<NP>(seg, sub, k, drawn_move(seg, count, z1, mutate_q16), spec_aos, packed);
 }
 
 // The generator state of child j's first draw in step `step`: child j draws outputs c + 1 and c + 2, c = step * 2^41 + 2 j.
@@ -123,6 +194,9 @@ struct MutArgs {
     uint32_t mutate_q16;
     int32_t k;
     uint4* child_aos;          // the children as records too, [n][kAosSlots / 8] (the pieces their slots reach); or null
+    const float* table;        // the scores of all possible children (LseSeg::table_at); or null: every child is made and scored
+    int32_t* odd;              // by subgraph: not 0 where a schedule of S_spec has more primes than the table tells apart (it is then not used)
+    int32_t variants;          // the launch makes and scores, instead of children, the table's entries
 };
 
 }  // namespace pruner

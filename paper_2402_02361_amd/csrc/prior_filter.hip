@@ -41,7 +41,7 @@ extern "C" int pruner_prior_filter(const pruner_subgraph* sg, int32_t n_sg, cons
     int rc = topk_prepare(seg_off, n_sg, k, ws + draft_bytes, workspace_bytes - draft_bytes, st, &ctx, &pending, true, false);
     if (rc) return rc;
     DraftPlan plan;
-    rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, notes_for(ctx), false, &plan);
+    rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, ws, draft_bytes, notes_for(ctx), Makes::kNothing, &plan);
     if (rc) return rc;
     if (pending.dst) ctx.d_segs = place_behind(plan, ws, &pending);
     rc = draft_upload(plan, ws, st, &pending);

@@ -1,0 +1,56 @@
+"""pruner_lse on segments with many times more children than S_spec can have different ones, whose scores are looked up in a table of all
+of these: subgraphs of one, two and three distinct primes (one, two and four entries per move) and of four (no table), two and three
+reduction levels, fragments, segments with and without a table in one call, and populations whose factors have more primes than the
+extents say (the table is then not used).  Against the oracle's loop, every integer and every bit of the scores."""
+import numpy as np
+import pytest
+
+import workloads as w
+from test_gpu_parity import P, dev, check_lse_against_oracle, lse_population  # noqa: F401  (P is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+ONE = w.gemm(64, 64, 64, dtype_bytes=2, hw=w.toy_device(), rd_levels=3, frag=(16, 16, 16))
+TWO = w.gemm(96, 80, 72, hw=w.toy_device())
+THREE = w.gemm(60, 90, 64, hw=w.toy_device())
+FOUR = w.gemm(210, 64, 32, hw=w.toy_device())
+CONV = w.conv2d(1, 8, 12, 12, 16, 3, 3)
+DEPTHWISE = w.depthwise_conv2d(1, 32, 28, 28, 3, 3)
+BATCHED = w.batched_gemm(4, 32, 48, 40)
+
+
+@pytest.mark.parametrize("sg", [ONE, TWO, THREE, FOUR, CONV, DEPTHWISE, BATCHED], ids=lambda s: s.name)
+@pytest.mark.parametrize("k,n,q16", [(1, 32769, 65536), (17, 40004, 52429), (130, 300003, 30000)])
+def test_one_segment(P, sg, k, n, q16):
+    seg, tiles = lse_population([sg], [n], seed=k)
+    check_lse_against_oracle(P, [sg], seg, tiles, k, 4, 3 + k, q16)
+
+
+def test_segments_with_and_without_a_table(P):
+    sgs = [TWO, CONV, FOUR, BATCHED, ONE]
+    seg, tiles = lse_population(sgs, [60000, 300, 40001, 700, 33000], seed=4)
+    check_lse_against_oracle(P, sgs[:2], seg[:3], np.ascontiguousarray(tiles[:, :seg[2]]), 40, 3, 5, 52000)
+    check_lse_against_oracle(P, sgs, seg, tiles, 40, 3, 5, 52000)   # five classes below 2^20: children by a launch of their own
+
+
+def test_classes_in_launches_of_their_own(P):
+    sgs = [TWO, CONV, DEPTHWISE, BATCHED]
+    seg, tiles = lse_population(sgs, [400000, 300000, 340002, 9000], seed=6)
+    check_lse_against_oracle(P, sgs, seg, tiles, 100, 3, 9, 52429)
+
+
+def test_more_primes_than_the_extents_have(P):
+    """tiles of 60 x 90 x 64 under a subgraph of powers of two that is large enough for them: the same as in a call of three classes, which
+    makes its children by a launch of their own (the oracle refuses such tiles)"""
+    wide = w.gemm(128, 128, 64, hw=w.toy_device())
+    results = []
+    for others in ([], [CONV, BATCHED]):
+        sgs = [THREE] + others
+        seg, tiles = lse_population(sgs, [40000] + [300] * len(others), seed=8)
+        pop = dev(tiles)
+        score, spec_t, spec_s, spec_n = P.lse([wide] + others, seg, pop, 64, 3, 2, 52429, flags=P.REFERENCE_ROUNDING)
+        rows = w.n_slots(wide)
+        results.append([pop[:rows, :40000].cpu().numpy(), score[:40000].cpu().numpy(), spec_t[:rows, :64].cpu().numpy(), spec_s[0].cpu().numpy(),
+                        spec_n[:1].cpu().numpy()])
+    for alone, beside in zip(*results):
+        assert np.array_equal(alone.view(np.uint8), beside.view(np.uint8))
