@@ -810,7 +810,7 @@ __device__ __forceinline__ void leave_scores(const float (&out)[VEC], int64_t c0
             // The largest keys of neighbouring candidates, by which the selection finds those that can matter.  The lanes at work are lanes
             // 0..m (as above).  Without the special case of -0, which is put right once.
             uint32_t top = 0;
-            const bool whole = c0 >= c_lo && c0 + VEC <= c_end;
+            const bool whole = MUT && c0 + VEC <= c_end;   // (made: from c0 on)
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
                 const uint32_t u = __float_as_uint(out[v]), key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
