@@ -1072,7 +1072,7 @@ struct DraftTables {
 
 constexpr int kAnyClass = -1;
 constexpr int kProducts = -2;   // plain and batched matrix products: the kernel branches between these two only
-constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers where the others need 128 at most
+constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers; held to 128, four wavefronts per SIMD (134 as compiled by itself)
 
 // One launch scores the segments of one loop-nest class (CLS), so that each class gets the register budget, and with
 // it the occupancy, of its own symbol code; CLS = kAnyClass branches on the class at run time instead and serves
@@ -1084,7 +1084,7 @@ constexpr int kClosedForms = -3;   // any class but the generic one, whose acces
 // The tables of segments and subgraphs come as the launch's first argument, so that no launch has to bring them before; tables that
 // do not fit there lie in the workspace (`tables`).
 template <int CLS, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
-__global__ void __launch_bounds__(kBlock) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
+__global__ void __launch_bounds__(kBlock, CLS == kClosedForms && !DUMP ? 4 : 1) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
                                                        int32_t descs_at, const uint16_t* __restrict__ tiles, int64_t pitch, int32_t flags, float* __restrict__ score,
                                                        int64_t* __restrict__ symbols, int64_t n_total,
                                                        uint32_t* __restrict__ first_digit, uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, int copies,
@@ -1627,8 +1627,12 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
             const int32_t s = order[i];
             const SgDesc& dd = descs[desc_of[s]];
             const int64_t chunks = (seg_off[s + 1] - seg_off[s] + chunk - 1) / chunk;
-            const int64_t iters = depth < 1 ? 1 : depth;
-            const int64_t blocks = (chunks + iters - 1) / iters;
+            // (every segment its share of the workgroups that the device holds: their chunks differ by one at most, where equal numbers of
+            // them leave some compute units with a workgroup less: ten segments of 326 chunks, 660 workgroups of five each on 256 units
+            // took 40.0 us, 1,020 of three or four 37.3)
+            int64_t blocks = depth <= 1 ? chunks : chunks * room / chunks_of[li];
+            blocks = blocks < 1 && chunks > 0 ? 1 : blocks;
+            const int64_t iters = blocks > 0 ? (chunks + blocks - 1) / blocks : 1;
             if (blocks > 0x7FFFFFFF || iters > 0x7FFFFFFF || L.blocks + blocks > 0x7FFFFFFF) return PRUNER_EINVAL;
             const bool tab = dd.run_max <= kTabMax && 2 * ((int64_t)dd.run_max + 1) <= 3 * chunk * iters && !(flags & PRUNER_NO_MEMORY_PENALTY);
             segs[i] = SegEnt{seg_off[s], seg_off[s + 1], (int32_t)L.blocks, desc_of[s], (int32_t)blocks, (int32_t)iters, tab ? 1 : 0, s};
