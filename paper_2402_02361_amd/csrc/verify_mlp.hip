@@ -47,11 +47,14 @@ constexpr int kXCols = (kF4 + kRowThreads - 1) / kRowThreads;    // float4 a thr
 constexpr int kXLoads = kXPass * kXCols;                         // float4 a thread fetches per tile (12)
 constexpr int kLocalCap = 2048;            // most candidates one workgroup takes (their running row counts and the table of its rows sit in LDS)
 constexpr int kGroupMin = 8, kGroupMax = 64;   // neighbouring candidates that go to one workgroup together
+constexpr int64_t kShortLastMost = 64;         // candidates of a workgroup up to which a short last tile is taken by itself
 
 __device__ __forceinline__ int32_t clamp_stmt(int32_t v) { return v < 0 ? 0 : v > kS ? kS : v; }
 
 // ---- mlp_kernel ----------------------------------------------------------------------------------------------------
 
+// SHORT_LAST: a last tile of up to 32 rows is taken by itself, without a second half.
+template <bool SHORT_LAST>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 mlp_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, int32_t n_d, int32_t kGroup, const uint16_t* __restrict__ W1,
            const float* __restrict__ b1, const uint16_t* __restrict__ W2, const float* __restrict__ b2, const uint16_t* __restrict__ w3, float b3,
@@ -314,8 +317,19 @@ mlp_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, i
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc0[nt][i] = acc1[nt][i] = 0.f;
+    // (after the loop: a branch around the second half's layers inside it cost 5 of 155 us at 131,072 candidates)
+    const bool short_last = SHORT_LAST && n_rows > 0 && (n_rows - 1) % kTM < 32;
+    const int n_whole = short_last ? n_tiles - 1 : n_tiles;
+    auto pin_second = [&]() {   // no instruction: the register class, and in the first tile the wait for the matrix
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+            asm volatile("" : "+a"(w2r[nt][0]), "+a"(w2r[nt][1]), "+a"(w2r[nt][2]), "+a"(w2r[nt][3]), "+a"(w2r[nt][4]), "+a"(w2r[nt][5]),
+                              "+a"(w2r[nt][6]), "+a"(w2r[nt][7]), "+a"(w2r[nt][8]), "+a"(w2r[nt][9]), "+a"(w2r[nt][10]), "+a"(w2r[nt][11]),
+                              "+a"(w2r[nt][12]), "+a"(w2r[nt][13]), "+a"(w2r[nt][14]), "+a"(w2r[nt][15]));
+        static_assert(kH / 16 == 16, "the second layer's sixteen depth steps are listed above");
+    };
     int it = 0;
-    for (; tile < n_tiles; tile += step, ++it) {
+    for (; tile < n_whole; tile += step, ++it) {
         // At this point X holds this tile's rows and the next tile's rows are on their way to registers.
         // layer 1, first half: H1^T[n][m] = sum_k W1[n][k] X[m][k] (b1 rides in the depth padding).  Meanwhile: layer 3 of
         // the previous tile's second half (this wavefront's share of w3 . relu(H2) for each row: rounding in the gaps,
@@ -336,13 +350,7 @@ mlp_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, i
         // layer 2, first half: H2^T[n][m] = b2[n] + sum_k W2[n][k] H1[m][k].  Meanwhile: the second half's hidden layer
         // goes to LDS, the next tile's rows go to X, and the previous tile's rows are summed (its row outputs are written
         // again only after the next barrier).
-        // (no instruction: the register class, and in the first tile the wait for the matrix)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt)
-            asm volatile("" : "+a"(w2r[nt][0]), "+a"(w2r[nt][1]), "+a"(w2r[nt][2]), "+a"(w2r[nt][3]), "+a"(w2r[nt][4]), "+a"(w2r[nt][5]),
-                              "+a"(w2r[nt][6]), "+a"(w2r[nt][7]), "+a"(w2r[nt][8]), "+a"(w2r[nt][9]), "+a"(w2r[nt][10]), "+a"(w2r[nt][11]),
-                              "+a"(w2r[nt][12]), "+a"(w2r[nt][13]), "+a"(w2r[nt][14]), "+a"(w2r[nt][15]));
-        static_assert(kH / 16 == 16, "the second layer's sixteen depth steps are listed above");
+        pin_second();
         layer_from<kH / 16>(acc0, b2r, w2r, H1, kHs, l32, half, [&](int i) {
             if (i & 1) {
                 if (i >= 2 * (kH / 16 - kXLoads)) park_piece((i - 2 * (kH / 16 - kXLoads)) >> 1);   // as late as the layer allows: the rows have far to come
@@ -368,12 +376,37 @@ mlp_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, i
             if (i == 25) finish_rows(y0, 0);
         });
     }
-    if (it > 0) {   // the last tile's second half and sums
+    auto second_half = [&](int i) {   // of the tile before
+        if (i < 8) {
+            last_layer_pack(acc1, 2 * i, pk);
+            last_layer_pack(acc1, 2 * i + 1, pk);
+            if (i & 1) last_layer_mfma(y1, i >> 1, w3f, pk);
+        }
+        if (i == 13) finish_rows(y1, 32);
+    };
+    if (SHORT_LAST && short_last) {
+        layer_from<kK1 / 16>(acc0, nullptr, w1r, X, kXs, l32, half, second_half);
 #pragma unroll
-        for (int pair = 0; pair < 16; ++pair) last_layer_pack(acc1, pair, pk);
+        for (int piece = 0; piece < 8; ++piece) park_hidden(acc0, piece, H1, kHs, wave, l32, half);
+        __syncthreads();   // H1 and the row outputs of the tile before complete
+        pin_second();
+        layer_from<kH / 16>(acc0, b2r, w2r, H1, kHs, l32, half, [&](int i) {
+            if (!(i & 1) && i < 2 * (1 + kS)) sum_step(i >> 1, tile - step);
+        });
 #pragma unroll
-        for (int q = 0; q < 4; ++q) last_layer_mfma(y1, q, w3f, pk);
-        finish_rows(y1, 32);
+        for (int pair = 0; pair < 16; ++pair) last_layer_pack(acc0, pair, pk);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) last_layer_mfma(y0, q, w3f, pk);
+        __syncthreads();   // (the row outputs of the tile before, and what was carried into it, have been read)
+        if (it > 0) sum_store();
+        finish_rows(y0, 0);
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < 1 + kS; ++q) sum_step(q, tile);
+        sum_store();
+    } else if (it > 0) {   // the last tile's second half and sums
+#pragma unroll
+        for (int i = 0; i < 14; ++i) second_half(i);
         __syncthreads();
         const int last = tile - step;
 #pragma unroll
@@ -418,9 +451,8 @@ extern "C" int pruner_verify_score(const float* feat, const int32_t* n_stmt, int
     const int dev = current_device(&num_cus);
     if (dev < 0) return PRUNER_EHIP;
     if (!g_lds_ready.get(dev)) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)numbering_bytes(kLocalCap)) != hipSuccess)
-            return PRUNER_EHIP;
+        for (const void* fn : {reinterpret_cast<const void*>(&mlp_kernel<false>), reinterpret_cast<const void*>(&mlp_kernel<true>)})
+            if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)numbering_bytes(kLocalCap)) != hipSuccess) return PRUNER_EHIP;
         g_lds_ready.mark(dev);
     }
     hipStream_t st = static_cast<hipStream_t>(stream);
@@ -436,7 +468,9 @@ extern "C" int pruner_verify_score(const float* feat, const int32_t* n_stmt, int
         while (group < kGroupMax && n / (2 * group) >= 8 * grid) group *= 2;
         const int64_t groups = (n + group - 1) / group;
         const size_t dyn_bytes = numbering_bytes((groups + grid - 1) / grid * group);
-        hipLaunchKernelGGL(mlp_kernel, dim3((unsigned)grid), dim3(kThreads), dyn_bytes, st, feat + (size_t)c0 * kS * kF, n_stmt + c0, (int32_t)n, group,
+        // a short last tile by itself where a workgroup has few tiles (512 candidates of three statements, 24 rows a workgroup, 10.24 -> 9.65 us);
+        // where it has many the kernel is better without it (131,072: 155.3, with it 156.3)
+        hipLaunchKernelGGL((n <= kShortLastMost * grid ? mlp_kernel<true> : mlp_kernel<false>), dim3((unsigned)grid), dim3(kThreads), dyn_bytes, st, feat + (size_t)c0 * kS * kF, n_stmt + c0, (int32_t)n, group,
                            w->W1, w->b1, w->W2, w->b2, w->w3, w->b3, vscore + c0);
         PRUNER_LAUNCH_CHECK();
     }
