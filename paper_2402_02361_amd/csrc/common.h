@@ -141,9 +141,9 @@ struct DraftPlan {
     bool makes = false;    // the kernels can make their candidates (the explorer loop's mutation) instead of reading them
 };
 // notes: what the selection would have the kernels leave behind; mut: the kernels
-// are to make their candidates from the second run on (plan->makes says whether they can): the children of S_spec as they are drawn, or
-// all that it can have (few: always a launch per class then).
-enum class Makes { kNothing, kChildren, kVariants };
+// are to make their candidates from the second run on (plan->makes says whether they can): the children of S_spec as they are drawn, the same
+// where all their scores are looked up, or all that S_spec can have.
+enum class Makes { kNothing, kChildren, kLookedUp, kVariants };
 int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, const uint16_t* tiles, int64_t tiles_pitch, int32_t flags,
                const float* score, const int64_t* symbols, const void* workspace, size_t workspace_bytes, const ScoreNotes& notes, Makes mut, DraftPlan* plan);
 // (also: an upload prepared by someone else whose destination lies in the same allocation shortly after the plan's own tables

@@ -456,11 +456,14 @@ __device__ __forceinline__ void make_children_np(const SgDesc& d, const MutSeg& 
     const uint64_t z0 = lse_child_state(mut.seed, mut.step, c0);
     uint32_t f[VEC][kAosWords];
     auto make = [&](int e) {
-        Move m;
-        if (mut.variants) m = move_of_variant(ms.seg, (int)(c0 - ms.begin) + e);
-        else m = drawn_move(ms.seg, ms.count, z0 + (uint64_t)(2 * e) * kGamma, mut.mutate_q16);
-        const int n_primes = child_of_move<NP>(ms.seg, ms.sub, mut.k, m, mut.spec_aos, f[e]);
-        if (mut.variants && n_primes > primes_told_apart(ms.seg.draws)) mut.odd[ms.sub] = 1;
+        const uint64_t z = z0 + (uint64_t)(2 * e) * kGamma;
+        if (mut.variants) {
+            const Move m = move_of_variant(ms.seg, (int)(c0 - ms.begin) + e);
+            const int n_primes = child_of_move<NP>(ms.seg, ms.sub, mut.k, m, mut.spec_aos, f[e], [](Move&) {});
+            if (n_primes > primes_told_apart(draws_of(ms.seg))) mut.odd[ms.sub] = 1;
+        } else {
+            lse_child<NP>(ms.seg, ms.sub, ms.count, mut.k, z, mut.spec_aos, mut.mutate_q16, f[e]);
+        }
     };
     make(0);
 #pragma unroll
@@ -980,14 +983,8 @@ __device__ __forceinline__ void look_children_up(const LseSeg& seg, int sub, int
                                                  float* __restrict__ score, uint32_t* digit_hist, bool count_digits, uint32_t* __restrict__ block_max,
                                                  uint32_t* __restrict__ max64, uint32_t* __restrict__ max16)
 {
-    MoveNumbers m;
-    m.n_sp = (uint32_t)__builtin_amdgcn_readfirstlane(seg.n_sp);
-    m.n_axes = (uint32_t)__builtin_amdgcn_readfirstlane(seg.n_sp + seg.n_rd);
-    m.rd_levels = (uint32_t)__builtin_amdgcn_readfirstlane(seg.rd_levels);
-    m.per_parent = (uint32_t)__builtin_amdgcn_readfirstlane(seg.per_parent);
-    m.plain_copy = m.per_parent / DRAWS - 1u;
-    m.count = (uint32_t)__builtin_amdgcn_readfirstlane(members);
-    const float* const table = mut.table + __builtin_amdgcn_readfirstlane(seg.table_at);
+    const MoveNumbers m = move_numbers<DRAWS>(seg, members);
+    const float* const table = mut.table + (uint32_t)__builtin_amdgcn_readfirstlane((int)table_at(seg));
     uint64_t z = lse_child_state(mut.seed, mut.step, c0);
     const uint64_t z_step = 2ull * (uint64_t)step * kGamma;
     for (int it = 0; it < iters; ++it, c0 += step, z += z_step) {
@@ -1021,13 +1018,13 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
         if (ms.count >= 1) {
             int64_t end = seg.end;
             if (mut.variants) {   // (entries of members that S_spec does not have are no one's)
-                const int64_t used = seg.begin + (int64_t)ms.count * ms.seg.per_parent;
+                const int64_t used = seg.begin + (int64_t)ms.count * entries_per_parent(ms.seg);
                 end = used < end ? used : end;
             }
             if (looked_up) {
 #define PRUNER_LOOK_UP(DRAWS) look_children_up<VEC, HIST, DRAWS>(ms.seg, ms.sub, ms.count, mut, c0, step, seg.iters, end, score, digit_hist, count_digits, block_max, max64, max16)
-                if (ms.seg.draws == 1) PRUNER_LOOK_UP(1);
-                else if (ms.seg.draws == 2) PRUNER_LOOK_UP(2);
+                if (draws_of(ms.seg) == 1) PRUNER_LOOK_UP(1);
+                else if (draws_of(ms.seg) == 2) PRUNER_LOOK_UP(2);
                 else PRUNER_LOOK_UP(4);
 #undef PRUNER_LOOK_UP
                 return;
@@ -1080,7 +1077,7 @@ constexpr int kClosedForms = -3;   // any class but the generic one, whose acces
 // one by one (VEC = 1): fewer than four candidates, and small ones of several classes that are not laid out in fours.
 // HIST: the workgroup also counts the first selection digit (first_digit_of) of its scores
 // in LDS and merges the counts into one of `copies` global histograms of its segment.
-// MUT: the candidates are not read but made (SchMutation from S_spec, `mut`), stored and scored in one pass.
+// MUT: the candidates are not read but made (SchMutation from S_spec, `mut`) and scored in one pass, or their scores are looked up.
 // The tables of segments and subgraphs come as the launch's first argument, so that no launch has to bring them before; tables that
 // do not fit there lie in the workspace (`tables`).
 template <int CLS, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
@@ -1105,7 +1102,7 @@ __global__ void __launch_bounds__(kBlock, CLS == kClosedForms && !DUMP ? 4 : 1) 
     __shared__ float tab[kTabMax + 1];
     __shared__ uint32_t digit_hist[HIST ? kBins : 1];
     // (the explorer loop's children, where their scores are looked up: nothing is analysed)
-    const bool looked_up = MUT && mut.table && mut.segs[seg.seg].draws > 0 && mut.odd[seg.seg] == 0, use_tab = seg.use_tab && !looked_up;
+    const bool looked_up = MUT && mut.table && draws_of(mut.segs[seg.seg]) > 0 && mut.odd[seg.seg] == 0, use_tab = seg.use_tab && !looked_up;
     // (the kernels that make their candidates also serve populations whose selection counts its digits itself)
     const bool count_digits = HIST && (!MUT || first_digit != nullptr);
     if (HIST && count_digits) {
@@ -1167,6 +1164,8 @@ template <int CLS, bool DUMP, bool EXACT> DraftFn pick_vec(int vec, bool hist, b
             if (vec == 1 && hist) return draft_kernel<CLS, 1, false, EXACT, true, false>;
         }
         if (vec == 1) return draft_kernel<CLS, 1, DUMP, EXACT, false, false>;
+    } else if constexpr (!DUMP && CLS == kClosedForms) {
+        if (mut) return vec == 1 ? draft_kernel<CLS, 1, false, EXACT, true, true> : draft_kernel<CLS, 4, false, EXACT, true, true>;
     } else if constexpr (!DUMP && CLS >= kGeneric) {
         if (vec == 1) return mut ? draft_kernel<CLS, 1, false, EXACT, true, true> : draft_kernel<CLS, 1, false, EXACT, false, false>;
     }
@@ -1587,7 +1586,12 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     std::vector<int32_t> order(n_sg);
     for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
     const bool large = vec == 4 && n >= kPerClassMin;
-    const bool by_class = spread || (vec == 4 && ((large && (makes || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (makes ? 2 : 1) || mut == Makes::kVariants));
+    // Children that are looked up, and the table's entries, in one launch for several closed forms: looking up is the same work for every
+    // class, and segments whose table is small (bound by the draws' instructions) run beside those whose table is large (bound by the lines
+    // of the vector cache); the entries are too few for a launch per class.  (16.8 M GEMM and 4.2 M depthwise children: 43 + 23 us in two
+    // launches, 58 in one; their entries 7.7 + 7.2, 8.1.)
+    const bool together = n_classes > 1 && !(classes >> kGeneric & 1u) && !symbols && (mut == Makes::kVariants || (mut == Makes::kLookedUp && !spread));
+    const bool by_class = !together && (spread || (vec == 4 && ((large && (makes || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (makes ? 2 : 1) || mut == Makes::kVariants)));
     if (by_class && n_classes > 1) {   // (a pass per class: sorting a thousand segments of one class took 14 us of host time)
         order.clear();
         for (uint32_t left = classes; left; left &= left - 1)
@@ -1601,12 +1605,12 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !(large && in_fours));
     out->exact = exact;
     const bool hist = notes.first_digit && symbols == nullptr;
-    const bool fused = makes && by_class && symbols == nullptr;   // every launch of the plan then makes its candidates itself
+    const bool fused = makes && (by_class || together) && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
     std::vector<int64_t> chunks_of;
     for (int32_t i = 0; i < n_sg; ++i) {
         const int32_t s = order[i];
-        const int cls = by_class ? descs[desc_of[s]].cls : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : kClosedForms;
+        const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : kClosedForms;
         if (out->launches.empty() || out->launches.back().cls != cls) {
             out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, fused), draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, false)});
             chunks_of.push_back(0);

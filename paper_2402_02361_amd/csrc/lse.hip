@@ -22,8 +22,8 @@
 // last step's mutation, whose children nobody scores, is a launch that stores them.
 // Where a segment has many times more children than S_spec can have different ones (a child is one of some thirty to a few hundred moves
 // away from its parent), all of these are made and scored first, and the children's scores are looked up: a child then costs its two
-// draws.  21 million children of two subgraphs, k = 4096, a step: 66 + 15 us for the table, where making, storing and scoring every child took
-// 221 (the call of four steps 1,334 -> 917).
+// draws.  21 million children of two subgraphs, k = 4096, a step: 58 + 8 us for the table, where making, storing and scoring every child took
+// 221 (the call of four steps 1,334 -> 874).
 // Random numbers are counter-based (SplitMix64, Steele/Lea/Flood OOPSLA 2014: draw c is the c-th output of the
 // generator started from the seed), so the result does not depend on how the work is laid out.
 #include "lse_child.h"
@@ -824,7 +824,7 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows, bool part
     return L;
 }
 
-// The values of a move's prime draw that matter for a subgraph's schedules (LseSeg::draws): their factors divide the extents.
+// The values of a move's prime draw that matter for a subgraph's schedules (1, 2 or 4; 0: more than a table tells apart): their factors divide the extents.
 int draws_of(const pruner_subgraph& s)
 {
     int most = 0;
@@ -893,7 +893,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         const int32_t n_slots = sg[s].n_sp * 4 + sg[s].n_rd * sg[s].rd_levels;
         if (n_slots > tile_rows) return PRUNER_EINVAL;
         const bool frag = sg[s].frag[0] != 0 || sg[s].frag[1] != 0 || sg[s].frag[2] != 0;
-        table[s] = LseSeg{seg_off[s], seg_off[s + 1], (int8_t)sg[s].n_sp, (int8_t)sg[s].n_rd, (int8_t)sg[s].rd_levels, 0, (int16_t)n_slots, 0,
+        table[s] = LseSeg{seg_off[s], seg_off[s + 1], sg[s].n_sp, sg[s].n_rd, sg[s].rd_levels, n_slots,
                           {frag ? sg[s].frag[0] : 0, frag ? sg[s].frag[1] : 0, frag ? sg[s].frag[2] : 0}, 0};
     }
 
@@ -968,30 +968,32 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     // Segments with many times more children than S_spec can have different ones get a table of all of these and their scores.  It
     // stands where the short route has its children as records.
     std::vector<int64_t> variant_off(n_sg + 1, 0);
+    bool all_tabled = false;
     int32_t* const odd = reinterpret_cast<int32_t*>(ws + L.children);
     float* const scores_of_all = reinterpret_cast<float*>(ws + L.children + round_up((size_t)n_sg * sizeof(int32_t), 256));
     {
         const int64_t room = (int64_t)(L.total - L.children) - (int64_t)round_up((size_t)n_sg * sizeof(int32_t), 256);
         int64_t end = 0;
+        int32_t n_tabled = 0;
         for (int32_t s = 0; s < n_sg; ++s) {
             variant_off[s] = end;
             const int draws = draws_of(sg[s]), per_parent = draws * move_count(sg[s].n_sp, sg[s].n_rd, sg[s].rd_levels);
             const int64_t entries = ((int64_t)k * per_parent + 3) & ~3ll;
             if (n_steps < 2 || draws == 0 || seg_off[s + 1] - seg_off[s] < kTableGain * entries || (end + entries) * (int64_t)sizeof(float) > room) continue;
-            table[s].draws = (int8_t)draws;
-            table[s].per_parent = (int16_t)per_parent;
-            table[s].table_at = (int32_t)end;
+            table[s].table = table_word((uint32_t)end, draws);
             end += entries;
+            ++n_tabled;
         }
         variant_off[n_sg] = end;
+        all_tabled = n_tabled == n_sg;
     }
     const int64_t table_end = variant_off[n_sg];
     rc = put_table(d_table, table.data(), table.size() * sizeof(LseSeg), st, table_end > 0 ? odd : nullptr, table_end > 0 ? (size_t)n_sg * sizeof(int32_t) : 0);
     if (rc) return rc;
 
     const size_t filter_bytes = L.table - L.filter;
-    // The mutation of step t - 1 is owed when step t begins: the draft kernels of step t make, store and score the
-    // children in one pass if their launch shape allows it, else it runs as a launch of its own first.
+    // The mutation of step t - 1 is owed when step t begins: the draft kernels of step t make and score the
+    // children in one pass, or look their scores up, if their launch shape allows it, else it runs as a launch of its own first.
     DraftPlan plan_first, plan_later, plan_table;
     bool tabled = false;   // the children's scores are looked up
     for (int32_t t = 0; t < n_steps; ++t) {
@@ -1002,15 +1004,19 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         rc = topk_prepare(seg_off, n_sg, k, ws + L.filter + draft_bytes, filter_bytes - draft_bytes, st, &ctx, &pending, true, true);
         if (rc) return rc;
         if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), Makes::kNothing, &plan_first);
-        if (t == 1) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), Makes::kChildren, &plan_later);
         if (rc) return rc;
-        if (t == 1 && table_end > 0 && plan_later.makes) {
-            const int32_t as_they = (flags & ~(PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) | (plan_later.exact ? PRUNER_REFERENCE_ROUNDING : PRUNER_FUSED_ARITHMETIC);
+        if (t == 1 && table_end > 0) {
+            const int32_t as_they = (flags & ~(PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) | (plan_first.exact ? PRUNER_REFERENCE_ROUNDING : PRUNER_FUSED_ARITHMETIC);
             rc = draft_plan(sg, n_sg, variant_off.data(), tiles, table_end > tiles_pitch ? table_end : tiles_pitch, as_they, scores_of_all, nullptr, draft_ws, draft_bytes, ScoreNotes{},
                             Makes::kVariants, &plan_table);
             if (rc) return rc;
             plan_table.in_launch = true;
             tabled = fits_launch(plan_table) && plan_table.makes;
+        }
+        if (t == 1) {
+            rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), tabled && all_tabled ? Makes::kLookedUp : Makes::kChildren,
+                            &plan_later);
+            if (rc) return rc;
         }
         DraftPlan& plan = t == 0 ? plan_first : plan_later;
         const bool made = t > 0 && plan.makes;

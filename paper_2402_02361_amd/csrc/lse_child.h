@@ -7,12 +7,10 @@ namespace pruner {
 
 struct alignas(8) LseSeg {
     int64_t begin, end;
-    int8_t n_sp, n_rd, rd_levels;
-    int8_t draws;         // values of a move's prime draw that a table of scores tells apart: 1, 2 or 4; 0: the subgraph has no table
-    int16_t n_slots;
-    int16_t per_parent;   // entries of the table that are children of one parent: move_count() x draws
-    int32_t frag[3];      // 0 outside fragment mode
-    int32_t table_at;     // where the subgraph's entries begin
+    int32_t n_sp, n_rd, rd_levels, n_slots;
+    int32_t frag[3];     // 0 outside fragment mode
+    uint32_t table;      // where the subgraph's entries of the table of all possible children begin, a multiple of four, and how many values of a
+                         // move's prime draw it tells apart in the low bits (table_word() below; those 0: no table)
 };
 
 // A member of S_spec as one record: its tile factors side by side (32 x uint16 = 64 bytes), so that a parent is read
@@ -51,20 +49,21 @@ struct Move {
 
 __device__ __forceinline__ int levels_of(const LseSeg& seg, int axis) { return axis < seg.n_sp ? 4 : seg.rd_levels; }
 
-// The move of the child whose first draw has the generator state z1 (the second draw follows it); count: members of S_spec.
-__device__ __forceinline__ Move drawn_move(const LseSeg& seg, int count, uint64_t z1, uint32_t mutate_q16)
+// The first draw of a child, and (from its generator state z1) what the second decides; count: members of S_spec.
+__device__ __forceinline__ void drawn_parent(uint64_t z1, int count, uint32_t mutate_q16, Move& m)
 {
-    Move m{};
     const uint64_t u1 = splitmix64_mix(z1);
     m.parent = (int)__umulhi((uint32_t)u1, (uint32_t)count);
     m.moves = ((uint32_t)(u1 >> 32) & 0xFFFFu) < mutate_q16;
+}
+__device__ __forceinline__ void drawn_move(const LseSeg& seg, uint64_t z1, Move& m)
+{
     const uint32_t u2 = (uint32_t)splitmix64_mix(z1 + kGamma);
     m.axis = pick8(u2, (uint32_t)(seg.n_sp + seg.n_rd));
     const int levels = levels_of(seg, m.axis);
     m.src = pick8(u2 >> 8, (uint32_t)levels);
     m.dst = pick8(u2 >> 16, (uint32_t)(levels - 1));
     m.prime_draw = u2 >> 24;
-    return m;
 }
 
 // ---- all possible children of a parent ----
@@ -73,10 +72,26 @@ __device__ __forceinline__ Move drawn_move(const LseSeg& seg, int count, uint64_
 // that halves and thirds cut 0..255 into for three.  Subgraphs with more primes in an extent have no table.
 __host__ __device__ constexpr int move_count(int n_sp, int n_rd, int rd_levels) { return 12 * n_sp + rd_levels * (rd_levels - 1) * n_rd + 1; }
 __host__ __device__ constexpr int primes_told_apart(int draws) { return draws == 4 ? 3 : draws; }
+// LseSeg::table: one, two or four values are 1, 2, 3 in the two low bits
+__host__ __device__ constexpr uint32_t table_word(uint32_t at, int draws) { return at | (draws == 4 ? 3u : (uint32_t)draws); }
+__host__ __device__ constexpr int draws_of(const LseSeg& seg) { return (int)((1u << (seg.table & 3u)) >> 1); }
+__host__ __device__ constexpr uint32_t table_at(const LseSeg& seg) { return seg.table & ~3u; }
+__host__ __device__ constexpr int entries_per_parent(const LseSeg& seg) { return draws_of(seg) * move_count(seg.n_sp, seg.n_rd, seg.rd_levels); }
 
-struct MoveNumbers {   // a subgraph's constants
+struct MoveNumbers {   // a subgraph's constants, the same for the whole wavefront
     uint32_t n_sp, n_axes, rd_levels, per_parent, plain_copy, count;
 };
+template <int DRAWS> __device__ __forceinline__ MoveNumbers move_numbers(const LseSeg& seg, int count)
+{
+    MoveNumbers m;
+    m.n_sp = (uint32_t)__builtin_amdgcn_readfirstlane(seg.n_sp);
+    m.n_axes = (uint32_t)__builtin_amdgcn_readfirstlane(seg.n_sp + seg.n_rd);
+    m.rd_levels = (uint32_t)__builtin_amdgcn_readfirstlane(seg.rd_levels);
+    m.plain_copy = (uint32_t)move_count((int)m.n_sp, (int)(m.n_axes - m.n_sp), (int)m.rd_levels) - 1u;
+    m.per_parent = DRAWS * (m.plain_copy + 1u);
+    m.count = (uint32_t)__builtin_amdgcn_readfirstlane(count);
+    return m;
+}
 // The entry of the child whose first draw has the generator state z1 (drawn_move(), numbered), from the subgraph's first on.
 template <int DRAWS> __device__ __forceinline__ uint32_t variant_drawn(const MoveNumbers& m, uint64_t z1, uint32_t mutate_q16)
 {
@@ -95,24 +110,26 @@ template <int DRAWS> __device__ __forceinline__ uint32_t variant_drawn(const Mov
 __device__ __forceinline__ Move move_of_variant(const LseSeg& seg, int variant)   // the other way round
 {
     Move m{};
-    m.parent = variant / seg.per_parent;
-    const int left = variant - m.parent * seg.per_parent, number = left / seg.draws, piece = left - number * seg.draws;
+    const int draws = draws_of(seg), per_parent = entries_per_parent(seg);
+    m.parent = variant / per_parent;
+    const int left = variant - m.parent * per_parent, number = left / draws, piece = left - number * draws;
     m.moves = number + 1 < move_count(seg.n_sp, seg.n_rd, seg.rd_levels);
     const bool spatial = number < 12 * seg.n_sp;
     const int levels = spatial ? 4 : seg.rd_levels, each = levels * (levels - 1), in = spatial ? number : number - 12 * seg.n_sp;
     m.axis = m.moves ? (spatial ? 0 : seg.n_sp) + in / each : 0;
     m.src = m.moves ? in % each / (levels - 1) : 0;
     m.dst = m.moves ? in % each % (levels - 1) : 0;
-    m.prime_draw = seg.draws == 1 ? 0u : seg.draws == 2 ? (uint32_t)piece << 7 : piece == 0 ? 0u : piece == 1 ? 86u : piece == 2 ? 128u : 171u;
+    m.prime_draw = draws == 1 ? 0u : draws == 2 ? (uint32_t)piece << 7 : piece == 0 ? 0u : piece == 1 ? 86u : piece == 2 ? 128u : 171u;
     return m;
 }
 
-// The child of subgraph `sub` that a move makes: `packed` receives its tile factors, two per word, as the parent's record holds them.
+// The child of subgraph `sub` that a move makes (rest_of(m) says the rest of a move that is one, while the parent's record is on its way):
+// `packed` receives its tile factors, two per word, as the record holds them.
 // The two slots a mutation touches are read from the record directly, and the child differs from the record by XOR
 // masks on their two words: no slot is looked up in registers by a computed index.  Returns the number of distinct primes among
 // which the draw picked (0 for a plain copy).
-template <int NP>   // NP: the 16-byte pieces of a record that the subgraph's slots reach; words past them stay 0
-__device__ __forceinline__ int child_of_move(const LseSeg& seg, int sub, int k, const Move& m, const uint4* __restrict__ spec_aos, uint32_t (&packed)[kAosWords])
+template <int NP, class Rest>   // NP: the 16-byte pieces of a record that the subgraph's slots reach; words past them stay 0
+__device__ __forceinline__ int child_of_move(const LseSeg& seg, int sub, int k, Move m, const uint4* __restrict__ spec_aos, uint32_t (&packed)[kAosWords], Rest&& rest_of)
 {
     const uint4* parent = spec_aos + ((int64_t)sub * k + (int64_t)m.parent) * (kAosSlots / 8);
 #pragma unroll
@@ -125,6 +142,7 @@ __device__ __forceinline__ int child_of_move(const LseSeg& seg, int sub, int k, 
     uint32_t mask_src = 0, mask_dst = 0;
     int n_primes = 0;
     if (m.moves) {
+        rest_of(m);
         const int n_axes = seg.n_sp + seg.n_rd, axis = m.axis, levels = levels_of(seg, axis), src = m.src;
         const int base = axis < seg.n_sp ? axis * 4 : seg.n_sp * 4 + (axis - seg.n_sp) * seg.rd_levels;
         const int dst = m.dst >= src ? m.dst + 1 : m.dst;
@@ -179,7 +197,9 @@ template <int NP>
 __device__ __forceinline__ void lse_child(const LseSeg& seg, int sub, int count, int k, uint64_t z1, const uint4* __restrict__ spec_aos,
                                           uint32_t mutate_q16, uint32_t (&packed)[kAosWords])
 {
-    (void)child_of_move<NP>(seg, sub, k, drawn_move(seg, count, z1, mutate_q16), spec_aos, packed);
+    Move m;
+    drawn_parent(z1, count, mutate_q16, m);
+    (void)child_of_move<NP>(seg, sub, k, m, spec_aos, packed, [&](Move& its) { drawn_move(seg, z1, its); });
 }
 
 // The generator state of child j's first draw in step `step`: child j draws outputs c + 1 and c + 2, c = step * 2^41 + 2 j.
@@ -194,7 +214,7 @@ struct MutArgs {
     uint32_t mutate_q16;
     int32_t k;
     uint4* child_aos;          // the children as records too, [n][kAosSlots / 8] (the pieces their slots reach); or null
-    const float* table;        // the scores of all possible children (LseSeg::table_at); or null: every child is made and scored
+    const float* table;        // the scores of all possible children (LseSeg::table); or null: every child is made and scored
     int32_t* odd;              // by subgraph: not 0 where a schedule of S_spec has more primes than the table tells apart (it is then not used)
     int32_t variants;          // the launch makes and scores, instead of children, the table's entries
 };

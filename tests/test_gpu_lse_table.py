@@ -39,6 +39,29 @@ def test_classes_in_launches_of_their_own(P):
     check_lse_against_oracle(P, sgs, seg, tiles, 100, 3, 9, 52429)
 
 
+@pytest.mark.parametrize("lens", [[60000, 50000, 40000, 33000], [60001, 50002, 40003, 33001]])
+def test_several_classes_that_all_have_a_table(P, lens):
+    """below 2^20: looked up in one launch, laid out in fours and not"""
+    sgs = [TWO, CONV, DEPTHWISE, BATCHED]
+    seg, tiles = lse_population(sgs, lens, seed=7)
+    check_lse_against_oracle(P, sgs, seg, tiles, 20, 4, 9, 52429)
+
+
+def test_two_classes_in_one_launch_of_looking_up(P):
+    """above 2^18: four to a thread; the first subgraph's primes are more than its extents', so that its children are made there"""
+    wide = w.gemm(128, 128, 64, hw=w.toy_device())
+    results = []
+    for others, more in (([DEPTHWISE], [300000]), ([DEPTHWISE, FOUR, CONV], [300000, 300, 300])):
+        sgs = [THREE] + others
+        seg, tiles = lse_population(sgs, [40000] + more, seed=8)
+        pop = dev(tiles)
+        score, spec_t, spec_s, spec_n = P.lse([wide] + others, seg, pop, 64, 3, 2, 52429, flags=P.REFERENCE_ROUNDING)
+        rows = min(w.n_slots(s) for s in (wide, DEPTHWISE))
+        results.append([pop[:rows, :340000].cpu().numpy(), score[:340000].cpu().numpy(), spec_t[:rows, :128].cpu().numpy(), spec_s[:2].cpu().numpy(), spec_n[:2].cpu().numpy()])
+    for alone, beside in zip(*results):
+        assert np.array_equal(np.ascontiguousarray(alone).view(np.uint8), np.ascontiguousarray(beside).view(np.uint8))
+
+
 def test_more_primes_than_the_extents_have(P):
     """tiles of 60 x 90 x 64 under a subgraph of powers of two that is large enough for them: the same as in a call of three classes, which
     makes its children by a launch of their own (the oracle refuses such tiles)"""
