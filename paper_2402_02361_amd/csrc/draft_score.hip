@@ -1069,7 +1069,8 @@ struct DraftTables {
 
 constexpr int kAnyClass = -1;
 constexpr int kProducts = -2;   // plain and batched matrix products: the kernel branches between these two only
-constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers; held to 128, four wavefronts per SIMD (134 as compiled by itself)
+constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers where the others need 134 at most
+constexpr int kClosedFormsHeld = -4;   // the same held to 128 registers, four wavefronts per SIMD, for populations that fill the device
 
 // One launch scores the segments of one loop-nest class (CLS), so that each class gets the register budget, and with
 // it the occupancy, of its own symbol code; CLS = kAnyClass branches on the class at run time instead and serves
@@ -1081,7 +1082,7 @@ constexpr int kClosedForms = -3;   // any class but the generic one, whose acces
 // The tables of segments and subgraphs come as the launch's first argument, so that no launch has to bring them before; tables that
 // do not fit there lie in the workspace (`tables`).
 template <int CLS, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
-__global__ void __launch_bounds__(kBlock, CLS == kClosedForms && !DUMP ? 4 : 1) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
+__global__ void __launch_bounds__(kBlock, CLS == kClosedFormsHeld || (CLS == kClosedForms && MUT) ? 4 : 1) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
                                                        int32_t descs_at, const uint16_t* __restrict__ tiles, int64_t pitch, int32_t flags, float* __restrict__ score,
                                                        int64_t* __restrict__ symbols, int64_t n_total,
                                                        uint32_t* __restrict__ first_digit, uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, int copies,
@@ -1130,7 +1131,7 @@ __global__ void __launch_bounds__(kBlock, CLS == kClosedForms && !DUMP ? 4 : 1) 
         if (d.cls == kGemm) PRUNER_WALK(NestGemm);
         else PRUNER_WALK(NestBatchedGemm);
     }
-    else if constexpr (CLS == kClosedForms) {
+    else if constexpr (CLS == kClosedForms || CLS == kClosedFormsHeld) {
         switch (d.cls) {
             case kGemm: PRUNER_WALK(NestGemm); break;
             case kBatchedGemm: PRUNER_WALK(NestBatchedGemm); break;
@@ -1189,6 +1190,7 @@ template <bool DUMP, bool EXACT> DraftFn pick_class(int cls, int vec, bool hist,
         case kGeneric: return pick_vec<kGeneric, DUMP, EXACT>(vec, hist, mut);
         case kProducts: return pick_vec<kProducts, DUMP, EXACT>(vec, hist, mut);
         case kClosedForms: return pick_vec<kClosedForms, DUMP, EXACT>(vec, hist, mut);
+        case kClosedFormsHeld: return pick_vec<kClosedFormsHeld, false, EXACT>(vec, hist, mut);
         default: return pick_vec<kAnyClass, DUMP, EXACT>(vec, hist, mut);
     }
 }
@@ -1211,6 +1213,10 @@ const void* dumping_draft_kernel(int cls, int vec, bool exact);
 namespace {
 
 constexpr int64_t kRaggedMin = 1 << 19;   // candidates from which a population that is not laid out in fours is loaded in fours all the same
+// Candidates from which the kernel for several closed forms is held to four wavefronts per SIMD: what the device holds at once of the one that
+// is not (three, 768 workgroups of 1,024 candidates).  1 M 16.8 -> 15.5 us, 3.3 M 38.9 -> 36.9; two registers spilled cost 49,350
+// candidates 8.7 -> 9.3.
+constexpr int64_t kHeldMin = 768 * 1024;
 constexpr int64_t kSpreadMax = 1 << 18;   // candidates up to which those of one class are scored one to a thread
 constexpr int64_t kPerClassMin = 1 << 20;   // candidates from which a call launches one kernel per loop-nest class
 
@@ -1610,7 +1616,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     std::vector<int64_t> chunks_of;
     for (int32_t i = 0; i < n_sg; ++i) {
         const int32_t s = order[i];
-        const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : kClosedForms;
+        const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : n >= kHeldMin && !symbols ? kClosedFormsHeld : kClosedForms;
         if (out->launches.empty() || out->launches.back().cls != cls) {
             out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, fused), draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, false)});
             chunks_of.push_back(0);
