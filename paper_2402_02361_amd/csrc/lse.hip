@@ -12,8 +12,8 @@
 //   lse_mutate  one thread per child: a parent drawn uniformly from S_spec (truncation selection: the paper names a
 //               genetic algorithm guided by the draft fitness and gives no operator), and with the given probability
 //               one prime factor of one tile factor moved to another level of the same axis, fragment multiples kept
-// Short segments with a small S_spec (kShortMax entries, k up to kShortK: the populations of an ordinary tuning round) take
-// one launch for the selection and all of PriorFilter instead:
+// Short segments with a small S_spec (kShortMax entries, k up to kShortK, but see spread_out: the populations of an ordinary tuning round)
+// take one launch for the selection and all of PriorFilter instead:
 //   lse_select  one workgroup per subgraph: the k best of S_x from keys in registers, their schedules' hashes, the union
 //               with S_spec and the new S_spec's records
 // When the population gets one draft launch per loop-nest class, the mutation of a step is not a launch of its own: the
@@ -844,6 +844,18 @@ int draws_of(const pruner_subgraph& s)
 // fifth of that and a line from the vector cache, and the table is a launch per class more.
 constexpr int64_t kTableGain = 4;
 
+// Short segments whose union the launches over the whole device form sooner than one workgroup per subgraph does: long ones (of 32 keys a
+// thread; four steps of a GEMM's 24,000, k = 512: 196 -> 155 us, 20 x 32,000, k = 64: 295 -> 200) and those whose S_spec has an old and a new
+// member for every thread (k = 1,000 of 4,000: 149 -> 133, of 9,000: 164 -> 150).  Not where subgraphs and members are many: each
+// subgraph has a compute unit to itself in the one launch, and shares the others with all (50 x 20,000, k = 512: 376 in one, 395 in several;
+// 20 x 4,000, k = 1,000: 196 and 207).
+constexpr int64_t kSpreadMembers = 20480, kSpreadPairs = 4096;
+bool spread_out(int64_t longest, int32_t n_sg, int32_t k)
+{
+    const int64_t members = (int64_t)n_sg * k;
+    return (longest > 16 * kLseThreads && members <= kSpreadMembers) || (k > kLseThreads / 2 && members <= kSpreadPairs);
+}
+
 constexpr int64_t kSpreadChildren = 1 << 17;   // children up to which a launch makes one per thread (8,000: 6.3 -> 4.0 us)
 constexpr int kMostGroups = 8;        // of 64 entries per workgroup of the rank kernel
 constexpr int kManyUniters = 2048;   // workgroups of 64 places: four times what the device holds at once
@@ -919,7 +931,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     // The short route: every segment in one workgroup's registers, S_spec's members one per thread.
     int64_t longest = 0;
     for (int32_t s = 0; s < n_sg; ++s) longest = seg_off[s + 1] - seg_off[s] > longest ? seg_off[s + 1] - seg_off[s] : longest;
-    if (longest <= kShortMax && k <= kShortK) {
+    if (longest <= kShortMax && k <= kShortK && !spread_out(longest, n_sg, k)) {
         DraftPlan plan;
         rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ScoreNotes{}, n_steps > 1 ? Makes::kChildren : Makes::kNothing, &plan);
         if (rc) return rc;
@@ -947,7 +959,9 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
             int32_t* const to_count = last ? spec_count : nullptr;
 #define PRUNER_SELECT(PER) hipLaunchKernelGGL(lse_select_kernel<PER>, dim3((unsigned)n_sg), dim3(kLseThreads), 0, st, d_table, k, t == 0, score, tiles, tiles_pitch, made ? children : nullptr, before, now, \
                                               spec_pitch, tile_rows, to_tiles, to_score, to_count)
+            // (keys that are not there cost their places in the unrolled loops: a GEMM's 16,384, four steps, k = 64: 160 -> 132 us with 16)
             if (longest <= 8 * kLseThreads) PRUNER_SELECT(8);
+            else if (longest <= 16 * kLseThreads) PRUNER_SELECT(16);
             else PRUNER_SELECT(kShortPer);
 #undef PRUNER_SELECT
             PRUNER_LAUNCH_CHECK();
