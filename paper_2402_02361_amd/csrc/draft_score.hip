@@ -23,6 +23,7 @@
 //   integer-to-float conversions round to nearest even.  Quotients are correctly rounded (see div_rn).
 // Compiled three times, side by side, since there are many kernels: PRUNER_DRAFT_PART 0 holds the host code and the kernels of
 // analyze(), 1 those of analyze_fused(), 2 the ones that write the symbols.
+#include "draft_shares.h"
 #include "lse_child.h"
 #include "select_common.h"
 #include "wide_load.h"
@@ -1228,14 +1229,15 @@ const void* draft_kernel_for(int cls, int vec, bool dump, bool exact, bool hist,
 
 // Workgroups of a kernel instance that the device holds at once (its register budget decides).  Asked of the runtime
 // once per kernel instance and device and remembered (the answer does not change, and the two queries cost a call of a
-// few thousand candidates a tenth of its time); two host threads that ask at once write the same values.
-int64_t resident_blocks(DraftFn fn)
+// few thousand candidates a tenth of its time); two host threads that ask at once write the same values.  units: the device's compute units.
+int64_t resident_blocks(DraftFn fn, int* units)
 {
     struct Known { DraftFn fn; int dev; int64_t blocks; };
     static Known known[128];
     static int n_known = 0;
     int cus = 0;
     const int dev = current_device(&cus);
+    *units = cus;
     if (dev < 0) {
         (void)hipGetLastError();
         return 256;   // (the launch that follows reports what is wrong with the device)
@@ -1613,37 +1615,29 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     const bool hist = notes.first_digit && symbols == nullptr;
     const bool fused = makes && (by_class || together) && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
-    std::vector<int64_t> chunks_of;
+    std::vector<uint32_t> chunks_of(n_sg), blocks_of(n_sg);   // by place in the launches
     for (int32_t i = 0; i < n_sg; ++i) {
         const int32_t s = order[i];
         const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : n >= kHeldMin && !symbols ? kClosedFormsHeld : kClosedForms;
         if (out->launches.empty() || out->launches.back().cls != cls) {
             out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, fused), draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, false)});
-            chunks_of.push_back(0);
         }
         DraftPlan::Launch& L = out->launches.back();
         const int64_t len = seg_off[s + 1] - seg_off[s];
-        chunks_of.back() += (len + chunk - 1) / chunk;
+        chunks_of[i] = (uint32_t)((len + chunk - 1) / chunk);
         L.n_seg += 1;
         L.candidates += len;
         L.bytes += len * (2 * (int64_t)(sg[s].n_sp * 4 + sg[s].n_rd * sg[s].rd_levels) + 4);
     }
     std::vector<SegEnt> segs(n_sg);
-    for (size_t li = 0; li < out->launches.size(); ++li) {
-        DraftPlan::Launch& L = out->launches[li];
-        const int64_t room = resident_blocks(reinterpret_cast<DraftFn>(const_cast<void*>(L.fn)));
-        const int64_t depth = (chunks_of[li] + room - 1) / room;   // chunks per workgroup when the launch fills the device once
+    for (DraftPlan::Launch& L : out->launches) {
+        int cus = 0;
+        const int64_t room = resident_blocks(reinterpret_cast<DraftFn>(const_cast<void*>(L.fn)), &cus);
+        share_workgroups(&chunks_of[L.first_seg], L.n_seg, (uint32_t)room, (uint32_t)cus, &blocks_of[L.first_seg]);
         for (int32_t i = L.first_seg; i < L.first_seg + L.n_seg; ++i) {
             const int32_t s = order[i];
             const SgDesc& dd = descs[desc_of[s]];
-            const int64_t chunks = (seg_off[s + 1] - seg_off[s] + chunk - 1) / chunk;
-            // (every segment its share of the workgroups that the device holds: their chunks differ by one at most, where equal numbers of
-            // them leave some compute units with a workgroup less: ten segments of 326 chunks, 660 workgroups of five each on 256 units
-            // took 40.0 us, 1,020 of three or four 37.3)
-            int64_t blocks = depth <= 1 ? chunks : chunks * room / chunks_of[li];
-            blocks = blocks < 1 && chunks > 0 ? 1 : blocks;
-            const int64_t iters = blocks > 0 ? (chunks + blocks - 1) / blocks : 1;
-            if (blocks > 0x7FFFFFFF || iters > 0x7FFFFFFF || L.blocks + blocks > 0x7FFFFFFF) return PRUNER_EINVAL;
+            const uint32_t blocks = blocks_of[i], iters = blocks > 0 ? (chunks_of[i] + blocks - 1) / blocks : 1;
             const bool tab = dd.run_max <= kTabMax && 2 * ((int64_t)dd.run_max + 1) <= 3 * chunk * iters && !(flags & PRUNER_NO_MEMORY_PENALTY);
             segs[i] = SegEnt{seg_off[s], seg_off[s + 1], (int32_t)L.blocks, desc_of[s], (int32_t)blocks, (int32_t)iters, tab ? 1 : 0, s};
             L.blocks += blocks;

@@ -1,0 +1,82 @@
+// How many workgroups of a draft launch walk through each of its segments: plain C++, so that the rule can be checked on the host.
+// It is asked for on every call, so it allocates nothing and divides in 32 bits.
+#pragma once
+#include <stdint.h>
+#include <string.h>
+
+namespace pruner {
+
+constexpr int32_t kSharedSegments = 256, kMostUnits = 512;
+
+// The chunks of the compute unit that has most, where workgroups go to `cus` units in turn.  A segment's workgroups have as many chunks as
+// each other, the first of them one more.
+inline uint32_t busiest_unit(const uint32_t* chunks, const uint32_t* blocks, int32_t n, uint32_t cus)
+{
+    uint32_t step[kMostUnits + 1];   // from a unit to the next (modulo 2^32)
+    memset(step, 0, (cus + 1) * sizeof(uint32_t));
+    uint32_t all = 0, at = 0;
+    auto add = [&](uint32_t whole, uint32_t left, uint32_t each) {   // to `whole` rounds of workgroups and `left` more, from `at` on
+        all += whole * each;
+        const uint32_t end = at + left;
+        step[at] += each;
+        step[end < cus ? end : cus] -= each;
+        if (end > cus) step[0] += each, step[end - cus] -= each;
+    };
+    for (int32_t i = 0; i < n; ++i) {
+        const uint32_t b = blocks[i];
+        if (b < 1) continue;
+        const uint32_t each = chunks[i] / b, longer = chunks[i] - each * b, rounds = b / cus, left = b - rounds * cus;
+        const uint32_t longer_rounds = longer < cus ? 0u : longer / cus;
+        add(longer_rounds, longer - longer_rounds * cus, 1);
+        add(rounds, left, each);
+        at += left;
+        at -= at >= cus ? cus : 0u;
+    }
+    uint32_t most = 0, here = 0;
+    for (uint32_t u = 0; u < cus; ++u) {
+        here += step[u];
+        most = here > most ? here : most;
+    }
+    return all + most;
+}
+
+// chunks[i]: pieces of segment i, one workgroup's at a time (fewer than 2^31 in all); room: workgroups that the device holds at once;
+// blocks[i]: the workgroups that segment i gets.
+// None has more chunks than the launch's mean.  What the device holds beyond that goes to the segments by their shares (one GEMM of
+// 3.3 M candidates, 806 workgroups of four 29.8 us, 1,024 of three or four 25.7; ten convolutions of 330,000 38.9 and 34.7; 20 x 100,000 of
+// four classes 20.9 and 18.6), but not where the longer workgroups of several segments meet on the same units (20 x 60,000 of a GEMM, 600
+// workgroups of two 14.5 us, 1,020 of one or two 16.7), and not where there are so many segments that asking costs as much.  Where a
+// workgroup for every mean is slightly more than fits, the shares rounded down are hardly longer (five convolutions of 2.2 M, 770 of 14 119 us,
+// 765 of 14 or 15 106); shares alone would leave 19 chunks to one where all others have ten (10.5 M candidates of a GEMM and
+// 19 x 19,456: 66 us, 52 so).
+inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, uint32_t cus, uint32_t* blocks)
+{
+    uint32_t total = 0, least = 0;
+    for (int32_t i = 0; i < n; ++i) total += chunks[i];
+    const uint32_t mean = total > room ? (total + room - 1) / room : 1;
+    for (int32_t i = 0; i < n; ++i) least += blocks[i] = mean == 1 ? chunks[i] : (chunks[i] + mean - 1) / mean;
+    if (mean == 1 || least == room || n > kSharedSegments || cus < 1 || cus > (uint32_t)kMostUnits) return;
+    const double per_chunk = (double)room / total;
+    auto share_of = [&](int32_t i) { return (uint32_t)(chunks[i] * per_chunk + 1e-6); };
+    uint32_t fuller[kSharedSegments];
+    if (least < room) {
+        const uint32_t spare = room - least;
+        uint32_t wanted = 0;
+        for (int32_t i = 0; i < n; ++i) {
+            const uint32_t share = share_of(i);
+            wanted += fuller[i] = share > blocks[i] ? share - blocks[i] : 0;
+        }
+        const double handed_out = wanted > spare ? (double)spare / wanted : 1.0;
+        for (int32_t i = 0; i < n; ++i) fuller[i] = blocks[i] + (wanted > spare ? (uint32_t)(fuller[i] * handed_out) : fuller[i]);
+    } else {
+        uint32_t sum = 0;
+        for (int32_t i = 0; i < n; ++i) {
+            fuller[i] = share_of(i);
+            sum += fuller[i] = fuller[i] > 0 || chunks[i] == 0 ? fuller[i] : 1;
+            if (chunks[i] > fuller[i] * (mean + 1 + mean / 8) || sum > least) return;
+        }
+    }
+    if (n == 1 || busiest_unit(chunks, fuller, n, cus) <= busiest_unit(chunks, blocks, n, cus)) memcpy(blocks, fuller, n * sizeof(uint32_t));
+}
+
+}  // namespace pruner
