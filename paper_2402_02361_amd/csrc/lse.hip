@@ -824,26 +824,6 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows, bool part
     return L;
 }
 
-// The values of a move's prime draw that matter for a subgraph's schedules (1, 2 or 4; 0: more than a table tells apart): their factors divide the extents.
-int draws_of(const pruner_subgraph& s)
-{
-    int most = 0;
-    for (int a = 0; a < s.n_sp + s.n_rd; ++a) {
-        int primes = 0;
-        int32_t rest = s.extent[a];
-        for (int32_t p = 2; p * p <= rest; ++p) {
-            if (rest % p == 0) ++primes;
-            while (rest % p == 0) rest /= p;
-        }
-        if (rest > 1) ++primes;
-        most = primes > most ? primes : most;
-    }
-    return s.rd_levels < 2 ? 0 : most <= 1 ? 1 : most == 2 ? 2 : most == 3 ? 4 : 0;
-}
-// Children per entry of a table from which one is made: an entry is made and scored as a child is without a table, a child with one costs a
-// fifth of that and a line from the vector cache, and the table is a launch per class more.
-constexpr int64_t kTableGain = 4;
-
 // Short segments whose union the launches over the whole device form sooner than one workgroup per subgraph does: long ones (of 32 keys a
 // thread; four steps of a GEMM's 24,000, k = 512: 196 -> 155 us, 20 x 32,000, k = 64: 295 -> 200) and those whose S_spec has an old and a new
 // member for every thread (k = 1,000 of 4,000: 149 -> 133, of 9,000: 164 -> 150).  Not where subgraphs and members are many: each
@@ -991,9 +971,10 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         int32_t n_tabled = 0;
         for (int32_t s = 0; s < n_sg; ++s) {
             variant_off[s] = end;
-            const int draws = draws_of(sg[s]), per_parent = draws * move_count(sg[s].n_sp, sg[s].n_rd, sg[s].rd_levels);
-            const int64_t entries = ((int64_t)k * per_parent + 3) & ~3ll;
-            if (n_steps < 2 || draws == 0 || seg_off[s + 1] - seg_off[s] < kTableGain * entries || (end + entries) * (int64_t)sizeof(float) > room) continue;
+            if (n_steps < 2) continue;
+            int draws;
+            const int64_t entries = table_entries(sg[s], seg_off[s + 1] - seg_off[s], k, &draws);
+            if (entries == 0 || (end + entries) * (int64_t)sizeof(float) > room) continue;
             table[s].table = table_word((uint32_t)end, draws);
             end += entries;
             ++n_tabled;

@@ -2,6 +2,7 @@
 // the draft kernel that produces and scores the children in one pass.
 #pragma once
 #include "common.h"
+#include "lse_rules.h"
 
 namespace pruner {
 
@@ -70,7 +71,6 @@ __device__ __forceinline__ void drawn_move(const LseSeg& seg, uint64_t z1, Move&
 // A subgraph's moves are numbered by axis, source and destination, the plain copy last; every move has as many entries as its
 // prime draw has distinguishable values: one where a factor has one distinct prime at most, two halves for two, and the four pieces
 // that halves and thirds cut 0..255 into for three.  Subgraphs with more primes in an extent have no table.
-__host__ __device__ constexpr int move_count(int n_sp, int n_rd, int rd_levels) { return 12 * n_sp + rd_levels * (rd_levels - 1) * n_rd + 1; }
 __host__ __device__ constexpr int primes_told_apart(int draws) { return draws == 4 ? 3 : draws; }
 // LseSeg::table: one, two or four values are 1, 2, 3 in the two low bits
 __host__ __device__ constexpr uint32_t table_word(uint32_t at, int draws) { return at | (draws == 4 ? 3u : (uint32_t)draws); }
