@@ -3,7 +3,7 @@
 //
 // C_SA and the k best of S_x are the launches of pruner_prior_filter.  The rest of a step:
 //   lse_keys    sixteen lanes per schedule: the records, score keys and schedule hashes of the k best (they sit at random
-//               places of the population)
+//               places of the population); of children that are not stored, lse_keys_made: one lane makes a child again
 //   lse_rank    every entry's place in the union of S_spec and the k best: the order is (score descending, hash ascending,
 //               position ascending); S_spec is in that order already, the k best in runs, places are found by bisection
 //   lse_unite   the union as a union of SETS (a schedule counts once; identity = score and a 64-bit hash of the tile
@@ -96,42 +96,17 @@ __device__ __forceinline__ int spec_members(const int32_t* count, int s, int k)
 // Three launches over the whole device instead of a sort by one workgroup per subgraph.  21 million programs in one segment,
 // k = 4096, a step: 11 + 7 + 6 us, where keys, sort and copies took 22 + 53 + 10.
 
-// The records and sort keys of the k best of S_x, 64 per workgroup, which leaves their keys in order.  Schedules of a population sit at
-// random places, two bytes a row: sixteen lanes per schedule, so that all misses are under way at once.  Children that the draft
-// kernels made are not stored and are made again here, one by a lane.
+// The records and sort keys of the k best of S_x, 64 per workgroup, which leaves their keys in order.
 constexpr int kRun = kWave;   // neighbours of the k best whose keys are in order
-__global__ void __launch_bounds__(kLseThreads) lse_keys_kernel(const LseSeg* __restrict__ segs, int k, bool first, const int32_t* __restrict__ old_count,
-                                                               const uint16_t* __restrict__ tiles, int64_t pitch, MutArgs made /* spec_aos null: not */,
-                                                               const int32_t* __restrict__ best_idx, const float* __restrict__ best_val,
-                                                               uint64_t* __restrict__ fresh_hi, uint64_t* __restrict__ fresh_lo,
-                                                               uint32_t* __restrict__ fresh_aos)
+struct Fresh {
+    uint64_t *hi, *lo;   // [n_sg][k]
+    uint32_t* aos;       // [n_sg][k][kAosWords]
+};
+
+// ... from their records in LDS, one to a lane of a wavefront
+__device__ __forceinline__ void leave_keys(const uint32_t (*record)[kAosWords + 1], int s, int k, int n_slots, int n_old, const float* __restrict__ best_val, const Fresh& fresh)
 {
-    static_assert(kLseThreads == kRun * kAosWords, "a thread takes two slots of a schedule");
-    __shared__ uint32_t record[kRun][kAosWords + 1];
-    const int s = blockIdx.y, c = threadIdx.x / kAosWords, w = threadIdx.x % kAosWords;
-    const int n_slots = segs[s].n_slots;
     const int64_t col0 = (int64_t)s * k;
-    const int r = blockIdx.x * kRun + c;
-    uint32_t word = 0;
-    if (made.spec_aos) {
-        const int child = blockIdx.x * kRun + (int)threadIdx.x;
-        if (threadIdx.x < kRun && child < k) {
-            uint32_t packed[kAosWords];
-            lse_child<kAosSlots / 8>(segs[s], s, made.spec_count[s], k, lse_child_state(made.seed, made.step, best_idx[col0 + child]), made.spec_aos, made.mutate_q16, packed);
-#pragma unroll
-            for (int i = 0; i < kAosWords; ++i) record[threadIdx.x][i] = packed[i];
-        }
-        __syncthreads();
-        if (r < k) fresh_aos[(col0 + r) * kAosWords + w] = record[c][w];
-    } else if (r < k) {
-        const uint16_t* col = tiles + best_idx[col0 + r];
-        const uint32_t low = 2 * w < n_slots ? col[(int64_t)(2 * w) * pitch] : 0u, high = 2 * w + 1 < n_slots ? col[(int64_t)(2 * w + 1) * pitch] : 0u;
-        word = low | high << 16;
-        fresh_aos[(col0 + r) * kAosWords + w] = word;
-    }
-    if (!made.spec_aos) record[c][w] = word;
-    __syncthreads();
-    if (threadIdx.x >= kRun) return;
     const int mine = blockIdx.x * kRun + (int)threadIdx.x;
     uint64_t hi = 0, lo = 0;   // padding sorts last: every real entry has a key above 0
     if (mine < k) {
@@ -141,15 +116,60 @@ __global__ void __launch_bounds__(kLseThreads) lse_keys_kernel(const LseSeg* __r
             h = splitmix64_draw(h, (uint64_t)(row & 1 ? pair >> 16 : pair & 0xFFFFu) + 1);
         }
         const uint64_t inv = ~h;
-        const uint32_t position = (uint32_t)((first ? 0 : spec_members(old_count, s, k)) + mine);
+        const uint32_t position = (uint32_t)(n_old + mine);
         hi = ((uint64_t)lse_key_of(best_val[col0 + mine]) << 32) | (inv >> 32);
         lo = (inv << 32) | (uint64_t)(0xFFFFFFFFu - position);
     }
     wave_sort_descending(hi, lo);
     if (mine < k) {
-        fresh_hi[col0 + mine] = hi;
-        fresh_lo[col0 + mine] = lo;
+        fresh.hi[col0 + mine] = hi;
+        fresh.lo[col0 + mine] = lo;
     }
+}
+
+// Schedules of a population sit at random places, two bytes a row: sixteen lanes per schedule, so that all misses are under way at once.
+__global__ void __launch_bounds__(kLseThreads) lse_keys_kernel(const LseSeg* __restrict__ segs, int k, bool first, const int32_t* __restrict__ old_count,
+                                                               const uint16_t* __restrict__ tiles, int64_t pitch, const int32_t* __restrict__ best_idx,
+                                                               const float* __restrict__ best_val, Fresh fresh)
+{
+    static_assert(kLseThreads == kRun * kAosWords, "a thread takes two slots of a schedule");
+    __shared__ uint32_t record[kRun][kAosWords + 1];
+    const int s = blockIdx.y, c = threadIdx.x / kAosWords, w = threadIdx.x % kAosWords;
+    const int n_slots = segs[s].n_slots;
+    const int64_t col0 = (int64_t)s * k;
+    const int r = blockIdx.x * kRun + c;
+    uint32_t word = 0;
+    if (r < k) {
+        const uint16_t* col = tiles + best_idx[col0 + r];
+        const uint32_t low = 2 * w < n_slots ? col[(int64_t)(2 * w) * pitch] : 0u, high = 2 * w + 1 < n_slots ? col[(int64_t)(2 * w + 1) * pitch] : 0u;
+        word = low | high << 16;
+        fresh.aos[(col0 + r) * kAosWords + w] = word;
+    }
+    record[c][w] = word;
+    __syncthreads();
+    if (threadIdx.x < kRun) leave_keys(record, s, k, n_slots, first ? 0 : spec_members(old_count, s, k), best_val, fresh);
+}
+
+// Children that the draft kernels made are not stored and are made again here, one by a lane.  A workgroup is one wavefront: the chain of a
+// child's draws, its parent and its prime factors is long, and what hides it are other wavefronts (1,000 subgraphs, k = 1,025, four steps:
+// extents with primes above 40,000 2,794 us by one wavefront of sixteen, 2,011 so; powers of two 2,018 and 1,760).
+__global__ void __launch_bounds__(kRun) lse_keys_made_kernel(int k, MutArgs made, const int32_t* __restrict__ best_idx, const float* __restrict__ best_val, Fresh fresh)
+{
+    __shared__ uint32_t record[kRun][kAosWords + 1];
+    const int s = blockIdx.y, first = blockIdx.x * kRun, child = first + (int)threadIdx.x;
+    const LseSeg& seg = made.segs[s];
+    const int count = made.spec_count[s];
+    const int64_t col0 = (int64_t)s * k;
+    if (child < k) {
+        uint32_t packed[kAosWords];
+        lse_child<kAosSlots / 8>(seg, s, count, k, lse_child_state(made.seed, made.step, best_idx[col0 + child]), made.spec_aos, made.mutate_q16, packed);
+#pragma unroll
+        for (int i = 0; i < kAosWords; ++i) record[threadIdx.x][i] = packed[i];
+    }
+    __syncthreads();
+    const int words = (k - first < kRun ? k - first : kRun) * kAosWords;
+    for (int i = threadIdx.x; i < words; i += kRun) fresh.aos[(col0 + first) * kAosWords + i] = record[i / kAosWords][i % kAosWords];
+    leave_keys(record, s, k, seg.n_slots, spec_members(made.spec_count, s, k), best_val, fresh);
 }
 
 // How many of the SIZE (a power of two) keys in descending order at hi, lo are above each of xh, xl.
@@ -1036,10 +1056,11 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         rc = topk_finish(ctx, score, seg_off, best_idx, best_val, true, st);
         if (rc) return rc;
         // PriorFilter over the union
-        uint64_t *fresh = words(L.fresh), *merged = words(L.merged);
-        uint32_t* const fresh_aos = reinterpret_cast<uint32_t*>(ws + L.fresh_aos);
-        hipLaunchKernelGGL(lse_keys_kernel, dim3((unsigned)((k + kRun - 1) / kRun), (unsigned)n_sg), dim3(kLseThreads), 0, st, d_table, k, t == 0,
-                           before.count, tiles, tiles_pitch, made ? owed : MutArgs{}, best_idx, best_val, fresh, fresh + spec_pitch, fresh_aos);
+        uint64_t* const merged = words(L.merged);
+        const Fresh fresh{words(L.fresh), words(L.fresh) + spec_pitch, reinterpret_cast<uint32_t*>(ws + L.fresh_aos)};
+        const dim3 runs((unsigned)((k + kRun - 1) / kRun), (unsigned)n_sg);
+        if (made) hipLaunchKernelGGL(lse_keys_made_kernel, runs, dim3(kRun), 0, st, k, owed, best_idx, best_val, fresh);
+        else hipLaunchKernelGGL(lse_keys_kernel, runs, dim3(kLseThreads), 0, st, d_table, k, t == 0, before.count, tiles, tiles_pitch, best_idx, best_val, fresh);
         PRUNER_LAUNCH_CHECK();
         // (a workgroup loads both lists before it ranks: where there are workgroups for several rounds of the device, which holds one
         // to two of them per compute unit, each ranks more groups.  100 subgraphs, k = 3,370, four steps: 2,269 us one group each,
@@ -1048,11 +1069,11 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         const int64_t rank_rounds = (int64_t)n_sg * rank_groups / 1024;
         const int groups = rank_rounds < 1 ? 1 : rank_rounds < kMostGroups ? (int)rank_rounds : kMostGroups;
         hipLaunchKernelGGL(lse_rank_kernel, dim3((unsigned)((rank_groups + groups - 1) / groups), (unsigned)n_sg), dim3(kLseThreads), (size_t)rank_words(k) * 16, st, k, t == 0,
-                           groups, before, fresh, fresh + spec_pitch, merged, merged + 2 * spec_pitch);
+                           groups, before, fresh.hi, fresh.lo, merged, merged + 2 * spec_pitch);
         PRUNER_LAUNCH_CHECK();
         const bool last = t + 1 == n_steps;
 #define PRUNER_UNITE(PER) hipLaunchKernelGGL(lse_unite_kernel<PER>, dim3((unsigned)((2 * k + PER * kWave - 1) / (PER * kWave)), (unsigned)n_sg), dim3(kLseThreads), 0, st, k, t == 0, before, \
-                                             fresh_aos, merged, merged + 2 * spec_pitch, now, spec_pitch, tile_rows, last ? spec_tiles : nullptr, last ? spec_score : nullptr, \
+                                             fresh.aos, merged, merged + 2 * spec_pitch, now, spec_pitch, tile_rows, last ? spec_tiles : nullptr, last ? spec_score : nullptr, \
                                              last ? spec_count : nullptr)
         if ((int64_t)n_sg * ((2 * k + kWave - 1) / kWave) > kManyUniters) PRUNER_UNITE(4);
         else PRUNER_UNITE(1);
