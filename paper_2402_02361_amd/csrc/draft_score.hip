@@ -443,7 +443,7 @@ __device__ __forceinline__ void load_tiles(const SgDesc& d, const uint16_t* __re
 // step: 221 us with the stores).  NP: 16-byte pieces of a record that the subgraph's slots reach.
 struct MutSeg {
     LseSeg seg;
-    int32_t sub, count;   // count < 1: the subgraph has no S_spec, its population stays as it is
+    int32_t sub, count;
     int64_t begin;        // of the launch's segment (the table's entries have others than the population)
 };
 
@@ -814,7 +814,7 @@ __device__ __forceinline__ void leave_scores(const float (&out)[VEC], int64_t c0
             // The largest keys of neighbouring candidates, by which the selection finds those that can matter.  The lanes at work are lanes
             // 0..m (as above).  Without the special case of -0, which is put right once.
             uint32_t top = 0;
-            const bool whole = MUT && c0 + VEC <= c_end;   // (made: from c0 on)
+            const bool whole = MUT && c0 + VEC <= c_end;   // (kernels that make their candidates begin with c0: c_lo is c0)
 #pragma unroll
             for (int v = 0; v < VEC; ++v) {
                 const uint32_t u = __float_as_uint(out[v]), key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
@@ -1016,34 +1016,31 @@ __device__ __forceinline__ void walk_segment(const SgDesc& d, const SegEnt& seg,
         ms.sub = seg.seg;
         ms.count = mut.spec_count[seg.seg];
         ms.begin = seg.begin;
-        if (ms.count >= 1) {
-            int64_t end = seg.end;
-            if (mut.variants) {   // (entries of members that S_spec does not have are no one's)
-                const int64_t used = seg.begin + (int64_t)ms.count * entries_per_parent(ms.seg);
-                end = used < end ? used : end;
-            }
-            if (looked_up) {
+        if (ms.count < 1) return;   // (no parents; pruner_lse asks for at least one entry per segment, so there are some)
+        int64_t end = seg.end;
+        if (mut.variants) {   // (entries of members that S_spec does not have are no one's)
+            const int64_t used = seg.begin + (int64_t)ms.count * entries_per_parent(ms.seg);
+            end = used < end ? used : end;
+        }
+        if (looked_up) {
 #define PRUNER_LOOK_UP(DRAWS) look_children_up<VEC, HIST, DRAWS>(ms.seg, ms.sub, ms.count, mut, c0, step, seg.iters, end, score, digit_hist, count_digits, block_max, max64, max16)
-                if (draws_of(ms.seg) == 1) PRUNER_LOOK_UP(1);
-                else if (draws_of(ms.seg) == 2) PRUNER_LOOK_UP(2);
-                else PRUNER_LOOK_UP(4);
+            if (draws_of(ms.seg) == 1) PRUNER_LOOK_UP(1);
+            else if (draws_of(ms.seg) == 2) PRUNER_LOOK_UP(2);
+            else PRUNER_LOOK_UP(4);
 #undef PRUNER_LOOK_UP
-                return;
-            }
-            for (int it = 0; it < seg.iters; ++it) {
-                if (c0 < end) {
-                    make_children<Nest, VEC>(d, ms, mut, c0, end, cur);
-                    score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, c0, c0, end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
-                }
-                c0 += step;
-            }
             return;
         }
-        if (mut.variants) return;
+        for (int it = 0; it < seg.iters; ++it) {
+            if (c0 < end) {
+                make_children<Nest, VEC>(d, ms, mut, c0, end, cur);
+                score_candidates<Nest, VEC, DUMP, EXACT, HIST, MUT>(d, cur, c0, c0, end, flags, p2m_tab, score, symbols, n_total, digit_hist, count_digits, block_max, max64, max16, seg.seg);
+            }
+            c0 += step;
+        }
+        return;
     }
-    if constexpr (MUT || Nest::NSP * 4 + Nest::NRD * 3 > 16) {
+    if constexpr (Nest::NSP * 4 + Nest::NRD * 3 > 16) {
         // many slots: a second set of them in flight costs more in occupancy than it gains
-        // (and in the kernels that make their candidates this path only serves a subgraph without S_spec)
         for (int it = 0; it < seg.iters; ++it) {
             if (c0 < seg.end) {
                 load_tiles<Nest, VEC>(d, tiles, pitch, inside(c0), cur);
