@@ -1070,6 +1070,14 @@ constexpr int kProducts = -2;   // plain and batched matrix products: the kernel
 constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers where the others need 134 at most
 constexpr int kClosedFormsHeld = -4;   // the same held to 128 registers, four wavefronts per SIMD, for populations that fill the device
 
+// Wavefronts per SIMD that a kernel's registers leave room for: four of the kernels for several closed forms, as above; and of those that make the
+// children of matrix products, which with the looking up take 131 (20 x 40,000, k = 512, four steps: 242 us with three wavefronts, 234 with
+// four and a register spilled).
+constexpr int waves_held(int cls, int vec, bool mut)
+{
+    return cls == kClosedFormsHeld || (mut && (cls == kClosedForms || (vec == 4 && (cls == kGemm || cls == kBatchedGemm)))) ? 4 : 1;
+}
+
 // One launch scores the segments of one loop-nest class (CLS), so that each class gets the register budget, and with
 // it the occupancy, of its own symbol code; CLS = kAnyClass branches on the class at run time instead and serves
 // populations of several classes where one launch for everything beats several (see the launch plan), kAnyClass also all that are loaded
@@ -1080,7 +1088,7 @@ constexpr int kClosedFormsHeld = -4;   // the same held to 128 registers, four w
 // The tables of segments and subgraphs come as the launch's first argument, so that no launch has to bring them before; tables that
 // do not fit there lie in the workspace (`tables`).
 template <int CLS, int VEC, bool DUMP, bool EXACT, bool HIST, bool MUT>
-__global__ void __launch_bounds__(kBlock, CLS == kClosedFormsHeld || (CLS == kClosedForms && MUT) ? 4 : 1) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
+__global__ void __launch_bounds__(kBlock, waves_held(CLS, VEC, MUT)) draft_kernel(DraftTables /* read through the argument segment, below */, const void* tables, int32_t first_seg, int32_t n_seg,
                                                        int32_t descs_at, const uint16_t* __restrict__ tiles, int64_t pitch, int32_t flags, float* __restrict__ score,
                                                        int64_t* __restrict__ symbols, int64_t n_total,
                                                        uint32_t* __restrict__ first_digit, uint32_t* __restrict__ block_max, uint32_t* __restrict__ max64, uint32_t* __restrict__ max16, int copies,
