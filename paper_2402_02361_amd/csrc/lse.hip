@@ -108,6 +108,7 @@ __device__ __forceinline__ void leave_keys(const uint32_t (*record)[kAosWords + 
 {
     const int64_t col0 = (int64_t)s * k;
     const int mine = blockIdx.x * kRun + (int)threadIdx.x;
+    const float score = mine < k ? best_val[col0 + mine] : 0.f;
     uint64_t hi = 0, lo = 0;   // padding sorts last: every real entry has a key above 0
     if (mine < k) {
         uint64_t h = (uint64_t)n_slots;   // identity of a schedule: its own tile slots, in slot order
@@ -117,7 +118,7 @@ __device__ __forceinline__ void leave_keys(const uint32_t (*record)[kAosWords + 
         }
         const uint64_t inv = ~h;
         const uint32_t position = (uint32_t)(n_old + mine);
-        hi = ((uint64_t)lse_key_of(best_val[col0 + mine]) << 32) | (inv >> 32);
+        hi = ((uint64_t)lse_key_of(score) << 32) | (inv >> 32);
         lo = (inv << 32) | (uint64_t)(0xFFFFFFFFu - position);
     }
     wave_sort_descending(hi, lo);
@@ -157,7 +158,7 @@ __global__ void __launch_bounds__(kRun) lse_keys_made_kernel(int k, MutArgs made
 {
     __shared__ uint32_t record[kRun][kAosWords + 1];
     const int s = blockIdx.y, first = blockIdx.x * kRun, child = first + (int)threadIdx.x;
-    const LseSeg& seg = made.segs[s];
+    const LseSeg seg = made.segs[s];
     const int count = made.spec_count[s];
     const int64_t col0 = (int64_t)s * k;
     if (child < k) {
@@ -168,8 +169,12 @@ __global__ void __launch_bounds__(kRun) lse_keys_made_kernel(int k, MutArgs made
     }
     __syncthreads();
     const int words = (k - first < kRun ? k - first : kRun) * kAosWords;
-    for (int i = threadIdx.x; i < words; i += kRun) fresh.aos[(col0 + first) * kAosWords + i] = record[i / kAosWords][i % kAosWords];
-    leave_keys(record, s, k, seg.n_slots, spec_members(made.spec_count, s, k), best_val, fresh);
+#pragma unroll
+    for (int j = 0; j < kAosWords; ++j) {
+        const int i = j * kRun + (int)threadIdx.x;
+        if (i < words) fresh.aos[(col0 + first) * kAosWords + i] = record[i / kAosWords][i % kAosWords];
+    }
+    leave_keys(record, s, k, seg.n_slots, count < 0 ? 0 : count > k ? k : count, best_val, fresh);
 }
 
 // How many of the SIZE (a power of two) keys in descending order at hi, lo are above each of xh, xl.
