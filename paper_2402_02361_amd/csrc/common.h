@@ -136,7 +136,7 @@ struct DraftPlan {
     size_t descs_at = 0;
     bool in_launch = false;    // they travel with the launches themselves and are not uploaded (draft_upload decides)
     int64_t n = 0, tiles_pitch = 0;
-    int32_t n_sg = 0, flags = 0;
+    int32_t n_sg = 0, flags = 0, n_classes = 0;   // (loop-nest classes)
     bool exact = false;    // one rounded operation per step of Eq. 1
     bool makes = false;    // the kernels can make their candidates (the explorer loop's mutation) instead of reading them
 };

@@ -1223,7 +1223,6 @@ constexpr int64_t kRaggedMin = 1 << 19;   // candidates from which a population 
 // is not (three, 768 workgroups of 1,024 candidates).  1 M 16.8 -> 15.5 us, 3.3 M 38.9 -> 36.9; two registers spilled cost 49,350
 // candidates 8.7 -> 9.3.
 constexpr int64_t kHeldMin = 768 * 1024;
-constexpr int64_t kSpreadMax = 1 << 18;   // candidates up to which those of one class are scored one to a thread
 constexpr int64_t kPerClassMin = 1 << 20;   // candidates from which a call launches one kernel per loop-nest class
 
 const void* draft_kernel_for(int cls, int vec, bool dump, bool exact, bool hist, bool mut)
@@ -1576,12 +1575,9 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // Several classes in a population that is neither large nor laid out in fours: candidates one by one, four times the threads,
     // for the kernel that branches on the class is short of them (6 x 3,001, k = 6: 20.2 -> 17.6 us; 400,020: 23.0 -> 20.7;
     // 900,020: no difference).  (Maxima of 256 neighbours need fours, and so do kernels that make their candidates.)
-    // One class (two where the kernels make their candidates) and few candidates: one by one, on four times the compute units, a
-    // thread's chain of divisions a quarter as long (reading: 4,096 GEMM candidates 5.8 -> 5.0 us, 65,536 of a convolution 7.4 -> 5.8,
-    // 262,144 7.7 -> 7.0; making: 8,000 10.6 -> 5.6, 65,536 13.2 -> 7.7, 262,144 13.8 -> 11.8; at 400,000 a tenth less as well, but
-    // the maxima of 256 neighbours want fours).
     const bool makes = mut != Makes::kNothing;
-    const bool spread = ((n <= kSpreadMax && n_classes <= (makes ? 2 : 1)) || mut == Makes::kVariants) && !notes.max256 && !notes.first_digit && !symbols;
+    const bool wants_fours = notes.max256 || notes.first_digit || symbols;
+    const bool spread = one_each(n, n_classes, makes, wants_fours) || (mut == Makes::kVariants && !wants_fours);
     const int vec = spread ? 1 : makes || notes.max256 || in_fours || n_classes < 2 || n >= kRaggedMin ? load_width(n) : 1;
 
     // Launch plan.  With four candidates per thread: one launch per loop-nest class present, the table grouped by class, when the
@@ -1617,6 +1613,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // other large populations, unless a flag asks for one of them.
     const bool exact = (flags & PRUNER_REFERENCE_ROUNDING) != 0 || (!(flags & PRUNER_FUSED_ARITHMETIC) && !(large && in_fours));
     out->exact = exact;
+    out->n_classes = n_classes;
     const bool hist = notes.first_digit && symbols == nullptr;
     const bool fused = makes && (by_class || together) && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;

@@ -1023,9 +1023,10 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         Upload pending;
         rc = topk_prepare(seg_off, n_sg, k, ws + L.filter + draft_bytes, filter_bytes - draft_bytes, st, &ctx, &pending, true, true);
         if (rc) return rc;
-        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), Makes::kNothing, &plan_first);
+        const ScoreNotes notes = notes_for(ctx);
+        if (t == 0) rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes, Makes::kNothing, &plan_first);
         if (rc) return rc;
-        if (t == 1 && table_end > 0) {
+        if (t == 1 && table_end > 0 && table_pays(n, plan_first.n_classes, notes.max256 || notes.first_digit)) {
             const int32_t as_they = (flags & ~(PRUNER_REFERENCE_ROUNDING | PRUNER_FUSED_ARITHMETIC)) | (plan_first.exact ? PRUNER_REFERENCE_ROUNDING : PRUNER_FUSED_ARITHMETIC);
             rc = draft_plan(sg, n_sg, variant_off.data(), tiles, table_end > tiles_pitch ? table_end : tiles_pitch, as_they, scores_of_all, nullptr, draft_ws, draft_bytes, ScoreNotes{},
                             Makes::kVariants, &plan_table);
@@ -1034,7 +1035,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
             tabled = fits_launch(plan_table) && plan_table.makes;
         }
         if (t == 1) {
-            rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes_for(ctx), tabled && all_tabled ? Makes::kLookedUp : Makes::kChildren,
+            rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, notes, tabled && all_tabled ? Makes::kLookedUp : Makes::kChildren,
                             &plan_later);
             if (rc) return rc;
         }
@@ -1055,8 +1056,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         if (pending.dst) ctx.d_segs = place_behind(plan, draft_ws, &pending);
         rc = draft_upload(plan, draft_ws, st, &pending);
         if (rc) return rc;
-        rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, notes_for(ctx),
-                       made ? &owed : nullptr);
+        rc = draft_run(plan, draft_ws, tiles, score, nullptr, st, notes, made ? &owed : nullptr);
         if (rc) return rc;
         rc = topk_finish(ctx, score, seg_off, best_idx, best_val, true, st);
         if (rc) return rc;

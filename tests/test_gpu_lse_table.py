@@ -20,15 +20,16 @@ BATCHED = w.batched_gemm(4, 32, 48, 40)
 
 
 @pytest.mark.parametrize("sg", [ONE, TWO, THREE, FOUR, CONV, DEPTHWISE, BATCHED], ids=lambda s: s.name)
-@pytest.mark.parametrize("k,n,q16", [(1, 32769, 65536), (17, 40004, 52429), (130, 300003, 30000)])
+@pytest.mark.parametrize("k,n,q16", [(1, 32769, 65536), (17, 40004, 52429), (17, 262144, 52429), (1, 262145, 65536), (17, 262148, 52429), (130, 300003, 30000)])   # (up to 2^18 children are made one to a thread)
 def test_one_segment(P, sg, k, n, q16):
     seg, tiles = lse_population([sg], [n], seed=k)
     check_lse_against_oracle(P, [sg], seg, tiles, k, 4, 3 + k, q16)
 
 
-def test_segments_with_and_without_a_table(P):
+@pytest.mark.parametrize("n", [60000, 262000])
+def test_segments_with_and_without_a_table(P, n):
     sgs = [TWO, CONV, FOUR, BATCHED, ONE]
-    seg, tiles = lse_population(sgs, [60000, 300, 40001, 700, 33000], seed=4)
+    seg, tiles = lse_population(sgs, [n, 300, 40001, 700, 33000], seed=4)
     check_lse_against_oracle(P, sgs[:2], seg[:3], np.ascontiguousarray(tiles[:, :seg[2]]), 40, 3, 5, 52000)
     check_lse_against_oracle(P, sgs, seg, tiles, 40, 3, 5, 52000)   # five classes below 2^20: children by a launch of their own
 
@@ -62,18 +63,19 @@ def test_two_classes_in_one_launch_of_looking_up(P):
         assert np.array_equal(np.ascontiguousarray(alone).view(np.uint8), np.ascontiguousarray(beside).view(np.uint8))
 
 
-def test_more_primes_than_the_extents_have(P):
+@pytest.mark.parametrize("n", [40000, 270000])
+def test_more_primes_than_the_extents_have(P, n):
     """tiles of 60 x 90 x 64 under a subgraph of powers of two that is large enough for them: the same as in a call of three classes, which
     makes its children by a launch of their own (the oracle refuses such tiles)"""
     wide = w.gemm(128, 128, 64, hw=w.toy_device())
     results = []
     for others in ([], [CONV, BATCHED]):
         sgs = [THREE] + others
-        seg, tiles = lse_population(sgs, [40000] + [300] * len(others), seed=8)
+        seg, tiles = lse_population(sgs, [n] + [300] * len(others), seed=8)
         pop = dev(tiles)
         score, spec_t, spec_s, spec_n = P.lse([wide] + others, seg, pop, 64, 3, 2, 52429, flags=P.REFERENCE_ROUNDING)
         rows = w.n_slots(wide)
-        results.append([pop[:rows, :40000].cpu().numpy(), score[:40000].cpu().numpy(), spec_t[:rows, :64].cpu().numpy(), spec_s[0].cpu().numpy(),
+        results.append([pop[:rows, :n].cpu().numpy(), score[:n].cpu().numpy(), spec_t[:rows, :64].cpu().numpy(), spec_s[0].cpu().numpy(),
                         spec_n[:1].cpu().numpy()])
     for alone, beside in zip(*results):
         assert np.array_equal(alone.view(np.uint8), beside.view(np.uint8))

@@ -34,6 +34,9 @@ static int check(pruner_subgraph s, int values, int k)
 int main()
 {
     int bad = 0;
+    // where children are made one to a thread they are not looked up
+    bad += pruner::table_pays(33000, 1, false) || pruner::table_pays(1 << 18, 1, false) || pruner::table_pays(1 << 18, 2, false);
+    bad += !pruner::table_pays((1 << 18) + 1, 1, false) || !pruner::table_pays(100000, 3, false) || !pruner::table_pays(100000, 1, true);
     for (int k : {1, 17, 512, 4096}) {
         bad += check(gemm(64, 1, 65536 / 2), 1, k) + check(gemm(97, 13, 25), 1, k) + check(gemm(96, 80, 72), 2, k) + check(gemm(60, 90, 64), 4, k);
         bad += pruner::told_apart(gemm(210, 64, 32)) != 0 || pruner::told_apart(gemm(64, 64, 30030)) != 0;
