@@ -36,8 +36,6 @@
 namespace pruner {
 namespace {
 
-constexpr int kLseThreads = 1024;
-
 __device__ __forceinline__ uint64_t splitmix64_draw(uint64_t seed, uint64_t c)
 {
     uint64_t z = seed + c * 0x9E3779B97F4A7C15ull;
@@ -849,18 +847,6 @@ LseLayout lse_layout(int64_t n, int32_t n_sg, int32_t k, int32_t rows, bool part
     return L;
 }
 
-// Short segments whose union the launches over the whole device form sooner than one workgroup per subgraph does: long ones (of 32 keys a
-// thread; four steps of a GEMM's 24,000, k = 512: 196 -> 155 us, 20 x 32,000, k = 64: 295 -> 200) and those whose S_spec has an old and a new
-// member for every thread (k = 1,000 of 4,000: 149 -> 133, of 9,000: 164 -> 150).  Not where subgraphs and members are many: each
-// subgraph has a compute unit to itself in the one launch, and shares the others with all (50 x 20,000, k = 512: 376 in one, 395 in several;
-// 20 x 4,000, k = 1,000: 196 and 207).
-constexpr int64_t kSpreadMembers = 20480, kSpreadPairs = 4096;
-bool spread_out(int64_t longest, int32_t n_sg, int32_t k)
-{
-    const int64_t members = (int64_t)n_sg * k;
-    return (longest > 16 * kLseThreads && members <= kSpreadMembers) || (k > kLseThreads / 2 && members <= kSpreadPairs);
-}
-
 constexpr int64_t kSpreadChildren = 1 << 17;   // children up to which a launch makes one per thread (8,000: 6.3 -> 4.0 us)
 constexpr int kMostGroups = 8;        // of 64 entries per workgroup of the rank kernel
 constexpr int kManyUniters = 2048;   // workgroups of 64 places: four times what the device holds at once
@@ -936,7 +922,7 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
     // The short route: every segment in one workgroup's registers, S_spec's members one per thread.
     int64_t longest = 0;
     for (int32_t s = 0; s < n_sg; ++s) longest = seg_off[s + 1] - seg_off[s] > longest ? seg_off[s + 1] - seg_off[s] : longest;
-    if (longest <= kShortMax && k <= kShortK && !spread_out(longest, n_sg, k)) {
+    if (longest <= kShortMax && k <= kShortK && !spread_out(n, longest, n_sg, k)) {
         DraftPlan plan;
         rc = draft_plan(sg, n_sg, seg_off, tiles, tiles_pitch, flags, score, nullptr, draft_ws, draft_bytes, ScoreNotes{}, n_steps > 1 ? Makes::kChildren : Makes::kNothing, &plan);
         if (rc) return rc;

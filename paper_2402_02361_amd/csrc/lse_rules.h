@@ -13,6 +13,27 @@ namespace pruner {
 constexpr int64_t kSpreadMax = 1 << 18;
 constexpr bool one_each(int64_t n, int n_classes, bool makes, bool wants_fours) { return n <= kSpreadMax && n_classes <= (makes ? 2 : 1) && !wants_fours; }
 
+// ---- one launch for the selection and the union, or several ----
+
+constexpr int kLseThreads = 1024;   // of the workgroup that a subgraph has in the one launch
+
+// Short segments whose union the launches over the whole device form sooner than one workgroup per subgraph does.
+// Long ones, of 32 keys a thread, where most are long or there are few: the one launch is as long as its longest segment, the others
+// take longer for every subgraph and member (four steps; one 17,000 and m - 1 of 1,500 of a GEMM: m = 32, k = 64, 6 % less in several
+// launches, k = 512 4 %, m = 128 7 and 51 % more; 24,000, k = 512: m = 32 8 % less, m = 64 5 % more; 32,768: m = 64 as long; 1,000 of 300
+// beside a 17,000, k = 8: 516 us in one, 722 in several; 128 x 32,768, k = 64, 34 % less).
+// And those whose S_spec has an old and a new member for every thread, where k is not just above half the threads' number or the
+// segments are not as short (k = 1,024 of 1,024: 142 -> 133 us, of 4,000 149 -> 133; k = 600 of 600 124 -> 128, of 4,000 5 % less).
+// Not where members are many: each subgraph has a compute unit to itself in the one launch, and shares the others with all
+// (50 x 20,000, k = 512: 376 in one, 395 in several; 20 x 4,000, k = 1,000: 196 and 207).
+constexpr int64_t kSpreadMembers = 20480, kSpreadPairs = 4096, kShortPairs = 1536;
+constexpr bool spread_out(int64_t n, int64_t longest, int32_t n_sg, int32_t k)
+{
+    const int64_t members = (int64_t)n_sg * k, many_keys = 16 * kLseThreads;
+    if (longest > many_keys && members <= kSpreadMembers && (n > n_sg * many_keys || 2 * n_sg * (k + 512ll) <= 5 * longest)) return true;
+    return k > kLseThreads / 2 && members <= kSpreadPairs && (k >= 704 || longest > kShortPairs);
+}
+
 // ---- the table of all children that a subgraph's S_spec can have (lse_child.h numbers them) ----
 
 // Moves of a schedule: a source and a destination among the levels of an axis, and the plain copy.

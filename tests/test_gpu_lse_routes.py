@@ -38,6 +38,20 @@ def test_long_segments_of_many_subgraphs(P, n_sg):
     check_lse_against_oracle(P, sgs, seg, tiles, 1000, 2, 13, 52429)
 
 
+@pytest.mark.parametrize("n_sg", [78, 79])
+def test_a_long_segment_among_many_short_ones(P, n_sg):
+    """k = 8 beside one of 16,400: 78 subgraphs stay below the line, 79 do not"""
+    sgs = [GEMM, BATCHED] * (n_sg // 2) + [GEMM] * (n_sg % 2)
+    seg, tiles = lse_population(sgs, [16400] + [300 + i % 5 for i in range(n_sg - 1)], seed=n_sg)
+    check_lse_against_oracle(P, sgs, seg, tiles, 8, 3, 17, 52429)
+
+
+@pytest.mark.parametrize("n,k", [(720, 703), (720, 704), (1536, 600), (1537, 600)])
+def test_members_above_half_the_threads_of_short_segments(P, n, k):
+    seg, tiles = lse_population([CONV], [n], seed=n + k)
+    check_lse_against_oracle(P, [CONV], seg, tiles, k, 3, 19, 52429)
+
+
 def test_copies_in_either_kernel(P):
     """five schedules over and over: ties at rank k by the thousand, with 16 keys a thread and by the launches over the device"""
     for n in (16000, 17000):

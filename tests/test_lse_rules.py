@@ -1,5 +1,5 @@
-"""The rules of the explorer loop's routes, on the host: which segments get a table of all their children, and that asking costs nothing
-where the answer is no."""
+"""The rules of the explorer loop's routes, on the host: which segments get a table of all their children, that asking costs nothing where the
+answer is no, and which short segments leave the one launch."""
 import os
 import subprocess
 
@@ -12,7 +12,7 @@ COMMON = r"""
 #include <chrono>
 #include <cstdio>
 #include <vector>
-static pruner_subgraph gemm(int m, int n, int k)
+[[maybe_unused]] static pruner_subgraph gemm(int m, int n, int k)
 {
     pruner_subgraph s{};
     s.n_sp = 2, s.n_rd = 1, s.rd_levels = 2;
@@ -45,6 +45,27 @@ int main()
 }
 """
 
+# the routes that were the faster ones, by a GEMM's, an encoder's and four classes' subgraphs together
+ROUTES = r"""
+int main()
+{
+    int bad = 0;
+    auto several = [&](int64_t longest, int n_sg, int64_t others, int k, bool want) {
+        if (pruner::spread_out(longest + (n_sg - 1) * others, longest, n_sg, k) != want) bad += std::printf("%ld, %d subgraphs of %ld, k %d\n", (long)longest, n_sg, (long)others, k);
+    };
+    for (int k : {1, 8, 64, 512}) several(16384, 1, 0, k, false), several(32768, 1, 0, k, true), several(24000, 16, 1500, k, true);
+    for (int m : {301, 1001, 2501}) several(17000, m, 300, 8, false);
+    for (int k : {16, 64, 256}) several(17000, 128, 1500, k, false), several(17000, 32, 1500, k, true);
+    several(17000, 64, 1500, 256, false), several(17000, 64, 1500, 512, false), several(24000, 64, 1500, 64, true), several(24000, 128, 1500, 256, false);
+    several(24000, 64, 1500, 512, false), several(32768, 64, 1500, 256, true), several(32768, 128, 1500, 512, false), several(32000, 101, 1500, 64, true);
+    several(32768, 128, 32768, 64, true), several(32768, 300, 32768, 64, true), several(24000, 64, 24000, 256, true), several(20000, 50, 20000, 512, false);
+    several(520, 1, 0, 513, false), several(600, 1, 0, 600, false), several(1000, 7, 1000, 513, false), several(1100, 7, 1100, 600, false);
+    several(1000, 1, 0, 1000, true), several(1024, 4, 1024, 1024, true), several(720, 1, 0, 704, true), several(2000, 7, 2000, 585, true), several(8000, 7, 8000, 520, true);
+    several(4000, 20, 4000, 1000, false), several(4000, 1, 0, 512, false);
+    return bad != 0;
+}
+"""
+
 # the largest primes that three axes may have, a thousand subgraphs: for segments that are too short, and for long ones
 TIME = r"""
 static double seconds(int64_t len)
@@ -74,8 +95,8 @@ int main()
 """
 
 
-@pytest.mark.parametrize("program", [ENTRIES, TIME], ids=["entries", "time"])
-def test_table_rule(tmp_path, program):
+@pytest.mark.parametrize("program", [ENTRIES, TIME, ROUTES], ids=["entries", "time", "routes"])
+def test_rule(tmp_path, program):
     src, exe = tmp_path / "rules.cpp", tmp_path / "rules"
     src.write_text(COMMON + program)
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-I", os.path.join(ROOT, "paper_2402_02361_amd", "csrc"), "-I", os.path.join(ROOT, "include"), str(src), "-o", str(exe)])
