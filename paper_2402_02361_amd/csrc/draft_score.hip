@@ -1068,7 +1068,7 @@ struct DraftTables {
 constexpr int kAnyClass = -1;
 constexpr int kProducts = -2;   // plain and batched matrix products: the kernel branches between these two only
 constexpr int kClosedForms = -3;   // any class but the generic one, whose access tables alone take 178 registers where the others need 134 at most
-constexpr int kClosedFormsHeld = -4;   // the same held to 128 registers, four wavefronts per SIMD, for populations that fill the device
+constexpr int kClosedFormsHeld = -4;   // the same held to 128 registers, four wavefronts per SIMD (four_waves_pay)
 
 // Wavefronts per SIMD that a kernel's registers leave room for: four of the kernels for several closed forms, as above; and of those that make the
 // children of matrix products, which with the looking up take 131 (20 x 40,000, k = 512, four steps: 242 us with three wavefronts, 234 with
@@ -1219,10 +1219,6 @@ const void* dumping_draft_kernel(int cls, int vec, bool exact);
 namespace {
 
 constexpr int64_t kRaggedMin = 1 << 19;   // candidates from which a population that is not laid out in fours is loaded in fours all the same
-// Candidates from which the kernel for several closed forms is held to four wavefronts per SIMD: what the device holds at once of the one that
-// is not (three, 768 workgroups of 1,024 candidates).  1 M 16.8 -> 15.5 us, 3.3 M 38.9 -> 36.9; two registers spilled cost 49,350
-// candidates 8.7 -> 9.3.
-constexpr int64_t kHeldMin = 768 * 1024;
 constexpr int64_t kPerClassMin = 1 << 20;   // candidates from which a call launches one kernel per loop-nest class
 
 const void* draft_kernel_for(int cls, int vec, bool dump, bool exact, bool hist, bool mut)
@@ -1617,16 +1613,22 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     const bool hist = notes.first_digit && symbols == nullptr;
     const bool fused = makes && (by_class || together) && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
+    const int chunk_log = __builtin_ctzll((uint64_t)chunk);   // (a power of two: divisions by it were a tenth of the plan of 3,000 segments)
     std::vector<uint32_t> chunks_of(n_sg), blocks_of(n_sg);   // by place in the launches
+    int64_t all_chunks = 0;
+    for (int32_t s = 0; s < n_sg; ++s) all_chunks += (seg_off[s + 1] - seg_off[s] + chunk - 1) >> chunk_log;
+    int units = 0;
+    if (current_device(&units) < 0) units = 256, (void)hipGetLastError();
+    const bool held = four_waves_pay(all_chunks, units);
     for (int32_t i = 0; i < n_sg; ++i) {
         const int32_t s = order[i];
-        const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : n >= kHeldMin && !symbols ? kClosedFormsHeld : kClosedForms;
+        const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : held && !symbols ? kClosedFormsHeld : kClosedForms;
         if (out->launches.empty() || out->launches.back().cls != cls) {
             out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, fused), draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, false)});
         }
         DraftPlan::Launch& L = out->launches.back();
         const int64_t len = seg_off[s + 1] - seg_off[s];
-        chunks_of[i] = (uint32_t)((len + chunk - 1) / chunk);
+        chunks_of[i] = (uint32_t)((len + chunk - 1) >> chunk_log);
         L.n_seg += 1;
         L.candidates += len;
         L.bytes += len * (2 * (int64_t)(sg[s].n_sp * 4 + sg[s].n_rd * sg[s].rd_levels) + 4);

@@ -79,4 +79,10 @@ inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, u
     if (n == 1 || busiest_unit(chunks, fuller, n, cus) <= busiest_unit(chunks, blocks, n, cus)) memcpy(blocks, fuller, n * sizeof(uint32_t));
 }
 
+// Whether the draft kernel for several closed forms is taken with four wavefronts per SIMD, two registers spilled, instead of three: where the
+// device then has a workgroup for every chunk and otherwise not (ten segments of 100,000 15.7 -> 13.8 us), and where there are chunks for more than
+// two rounds of three (20 x 100,000 20.3 -> 18.7, ten of 400,000 36.2 -> 35.4).  With two rounds either way the spilled registers are what is left of
+// it (ten of 120,000 14.3 and 15.7), and with one (ten of 70,000 12.8 and 13.3).
+constexpr bool four_waves_pay(int64_t chunks, int64_t units) { return chunks > 3 * units && (chunks <= 4 * units || chunks > 6 * units); }
+
 }  // namespace pruner
