@@ -184,7 +184,8 @@ int pruner_draft_score(const pruner_subgraph* sg, int32_t n_sg, const int64_t* s
  * pruner_prior_filter, pruner_lse) records `start_event` right before and `stop_event` right after the one draft
  * kernel launch of the call that covers the most candidates (a call is one launch or, for some populations, one per
  * loop-nest class), on the call's stream, and stores that launch's algorithmic bytes (candidates x (2 x tile slots + 4)) in
- * *algorithmic_bytes (host, may be NULL).  Both events NULL switches the hook off.  The events are the caller's
+ * *algorithmic_bytes (host, may be NULL).  In pruner_lse: of the launches that read their candidates, which are the first step's
+ * and, where later steps read theirs as well, the last step's.  Both events NULL switches the hook off.  The events are the caller's
  * (hipEvent_t); process-wide state, not thread-safe: for benchmarks.
  * Errors: PRUNER_EINVAL if exactly one event is NULL.
  */

@@ -1695,9 +1695,10 @@ int draft_run(const DraftPlan& plan, const void* workspace, const uint16_t* tile
 {
     DraftTables tables = {};
     if (plan.in_launch) memcpy(&tables, plan.image.data(), plan.image.size());
-    // measurement hook: events around the launch that covers the most candidates
+    // measurement hook: events around the launch that covers the most candidates (not around launches that make or look up theirs, which
+    // read none of the bytes that it reports)
     const DraftPlan::Launch* timed = nullptr;
-    if (g_time_start && g_time_stop) {
+    if (g_time_start && g_time_stop && !mut) {
         for (const DraftPlan::Launch& L : plan.launches)
             if (L.blocks > 0 && (!timed || L.candidates > timed->candidates)) timed = &L;
         if (g_time_bytes) *g_time_bytes = timed ? timed->bytes : 0;

@@ -2,8 +2,11 @@
 of these: subgraphs of one, two and three distinct primes (one, two and four entries per move) and of four (no table), two and three
 reduction levels, fragments, segments with and without a table in one call, and populations whose factors have more primes than the
 extents say (the table is then not used).  Against the oracle's loop, every integer and every bit of the scores."""
+import ctypes
+
 import numpy as np
 import pytest
+import torch
 
 import workloads as w
 from test_gpu_parity import P, dev, check_lse_against_oracle, lse_population  # noqa: F401  (P is a fixture)
@@ -79,3 +82,28 @@ def test_more_primes_than_the_extents_have(P, n):
                         spec_n[:1].cpu().numpy()])
     for alone, beside in zip(*results):
         assert np.array_equal(alone.view(np.uint8), beside.view(np.uint8))
+
+
+@pytest.mark.parametrize("sgs,lens", [([TWO], [300004]), ([TWO], [8000]), ([TWO, CONV], [1 << 20, 40000])], ids=["table", "made", "classes"])
+def test_timing_hook_brackets_a_launch_that_reads(P, sgs, lens):
+    """four steps of which the first one alone reads its candidates: the events stand around a launch of that step, results unchanged"""
+    seg, tiles = lse_population(sgs, lens, seed=12)
+    begin, e0, e1, end = (torch.cuda.Event(enable_timing=True) for _ in range(4))
+    for e in (begin, e0, e1, end):
+        e.record()
+    plain = P.lse(sgs, seg, dev(tiles), 17, 4, 3, 52429)
+    pop = dev(tiles)
+    got = ctypes.c_int64(-1)
+    P.time_dominant_draft_launch(e0, e1, got)
+    try:
+        begin.record()
+        timed = P.lse(sgs, seg, pop, 17, 4, 3, 52429)
+        end.record()
+        torch.cuda.synchronize()
+    finally:
+        P.time_dominant_draft_launch(None, None)
+    assert got.value == lens[0] * (2 * w.n_slots(sgs[0]) + 4)
+    assert 0.0 < e0.elapsed_time(e1) < 50.0
+    assert begin.elapsed_time(e0) < e1.elapsed_time(end)
+    for a, b in zip(plain, timed):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
