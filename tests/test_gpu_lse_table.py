@@ -107,3 +107,22 @@ def test_timing_hook_brackets_a_launch_that_reads(P, sgs, lens):
     assert begin.elapsed_time(e0) < e1.elapsed_time(end)
     for a, b in zip(plain, timed):
         assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+FRAGMENT = w.gemm(512, 512, 512, dtype_bytes=2, rd_levels=3, frag=(16, 16, 16))
+
+
+@pytest.mark.parametrize("flags", ["0", "FUSED_ARITHMETIC", "NO_COMPUTE_PENALTY", "NO_MEMORY_PENALTY", "NO_COMPUTE_PENALTY|FUSED_ARITHMETIC"])
+@pytest.mark.parametrize("sgs,lens", [([FRAGMENT], [1 << 20]), ([TWO, DEPTHWISE], [1 << 20, 300004]), ([TWO, CONV, BATCHED], [700000, 300000, 60000])],
+                         ids=["one", "two", "three"])
+def test_scores_are_those_of_the_children(P, sgs, lens, flags):
+    """in fours from 2^20 on, where the arithmetic is the multiplied-out one unless a flag says otherwise: the scores that t + 1 steps leave, which
+    are looked up, are the scores of the population that t steps leave, which reads them"""
+    bits = sum(getattr(P, f) for f in flags.split("|") if f != "0")
+    seg, tiles = lse_population(sgs, lens, seed=13)
+    for steps in (1, 2):
+        pop = dev(tiles)
+        P.lse(sgs, seg, pop, 100, steps, 5, 52429, flags=bits)
+        want = P.draft_score(sgs, seg, pop, flags=bits)
+        got = P.lse(sgs, seg, dev(tiles), 100, steps + 1, 5, 52429, flags=bits)[0]
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), (steps, int((got.view(torch.int32) != want.view(torch.int32)).sum()))
