@@ -1584,9 +1584,9 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // 65,536 convolution candidates 7.7 and 9.6), and, when the kernels make their candidates, up to two classes
     // (a launch of the mutation is then saved); otherwise a single launch of a kernel that branches on the class: between the
     // two kinds of matrix products where there are no others (an encoder's tasks: 20 x 50,000 candidates take 13.3 us
-    // instead of 14.8), between the four classes with closed forms where none is generic (128 registers, four wavefronts per
-    // SIMD, where the access tables of the generic class take 178 and leave two: ten segments of these four classes, 3.3 M
-    // candidates, take 38 us instead of 43), else among all five.  A
+    // instead of 14.8), between the four classes with closed forms where none is generic (134 registers or, where four_waves_pay, 128,
+    // where the access tables of the generic class take 178 and leave two wavefronts per SIMD: ten segments of these four classes, 3.3 M
+    // candidates, take 31 us instead of 43), else among all five.  A
     // launch has at most as many workgroups as the device holds at once; they walk through the chunks of their segment.
     std::vector<int32_t> order(n_sg);
     for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
@@ -1596,7 +1596,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // of the vector cache); the entries are too few for a launch per class.  (16.8 M GEMM and 4.2 M depthwise children: 43 + 23 us in two
     // launches, 58 in one; their entries 7.7 + 7.2, 8.1.)
     const bool together = n_classes > 1 && !(classes >> kGeneric & 1u) && !symbols && (mut == Makes::kVariants || (mut == Makes::kLookedUp && !spread));
-    const bool by_class = !together && (spread || (vec == 4 && ((large && (makes || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (makes ? 2 : 1) || mut == Makes::kVariants)));
+    const bool by_class = !together && (spread || (vec == 4 && ((large && (makes || n_classes <= 2 || n >= n_classes * kPerClassMin)) || n_classes <= (makes ? 2 : 1))));
     if (by_class && n_classes > 1) {   // (a pass per class: sorting a thousand segments of one class took 14 us of host time)
         order.clear();
         for (uint32_t left = classes; left; left &= left - 1)

@@ -92,7 +92,7 @@ constexpr int kXPass = kTM / (kThreads / kRowThreads);           // passes over 
 constexpr int kXCols = (kF4 + kRowThreads - 1) / kRowThreads;    // float4 a thread fetches per row (6)
 constexpr int kXLoads = kXPass * kXCols;                         // float4 a thread fetches per tile (12)
 constexpr int kLocalCap = 2048;                                  // most candidates one workgroup takes in a launch
-constexpr int kGroupMin = 8, kGroupMax = 64;                     // neighbouring candidates that go to one workgroup together
+constexpr int kGroupMinLog = 3, kGroupMin = 1 << kGroupMinLog, kGroupMax = 64;   // neighbouring candidates that go to one workgroup together
 
 // The candidates of a workgroup: groups first, first + stride, ... of 2^log neighbours.
 struct Share {
@@ -900,7 +900,7 @@ static_assert(sizeof(FlowLds<kSmallMost>) <= kArena * sizeof(__bf16), "the dataf
 
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, 1)))
 pacm_small_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, const float* __restrict__ flow, const int32_t* __restrict__ n_blk,
-                  int32_t n_d, int group_log, pruner_pacm w, float* __restrict__ y)
+                  int32_t n_d, pruner_pacm w, float* __restrict__ y)
 {
     __shared__ __attribute__((aligned(16))) __bf16 arena[kArena];
     __shared__ __attribute__((aligned(16))) float cst[2][kH];
@@ -913,7 +913,7 @@ pacm_small_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_
     __shared__ float red[4][kTM];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, l32 = lane & 31;
-    const Share share(n_d, group_log, (int)blockIdx.x, (int)gridDim.x);
+    const Share share(n_d, kGroupMinLog, (int)blockIdx.x, (int)gridDim.x);
     // the wavefront's candidates in the dataflow branch
     const int per = (share.n_local + kFlowWaves - 1) / kFlowWaves, from = wave * per < share.n_local ? wave * per : share.n_local;
     const int mine = from + per < share.n_local ? per : share.n_local - from;
@@ -994,7 +994,7 @@ extern "C" int pruner_pacm_score(const float* feat, const int32_t* n_stmt, const
     // has no room for a second tile beside the statement branch's).
     if (n_d <= (int64_t)kSmallMost * pacm_cus) {
         const int64_t grid = (n_d + kGroupMin - 1) / kGroupMin < pacm_cus ? (n_d + kGroupMin - 1) / kGroupMin : pacm_cus;
-        hipLaunchKernelGGL(pacm_small_kernel, dim3((unsigned)grid), dim3(kThreads), 0, st, feat, n_stmt, flow, n_blk, n, 3, *w, y);
+        hipLaunchKernelGGL(pacm_small_kernel, dim3((unsigned)grid), dim3(kThreads), 0, st, feat, n_stmt, flow, n_blk, n, *w, y);
         PRUNER_LAUNCH_CHECK();
         return PRUNER_OK;
     }
@@ -1003,7 +1003,7 @@ extern "C" int pruner_pacm_score(const float* feat, const int32_t* n_stmt, const
     for (int64_t c0 = 0; c0 < n_d; c0 += per_launch) {
         const int64_t m = n_d - c0 < per_launch ? n_d - c0 : per_launch;
         const int64_t grid = (m + kGroupMin - 1) / kGroupMin < pacm_cus ? (m + kGroupMin - 1) / kGroupMin : pacm_cus;
-        int group_log = 3;
+        int group_log = kGroupMinLog;
         while ((1 << group_log) < kGroupMax && m / (2 << group_log) >= 8 * grid) ++group_log;
         hipLaunchKernelGGL(pacm_stmt_kernel, dim3((unsigned)grid), dim3(kThreads), 0, st, feat + (size_t)c0 * kS * kF, n_stmt + c0, (int32_t)m, group_log,
                            w->W1, w->b1, w->W2, w->b2, v_s + (size_t)c0 * kH);

@@ -570,8 +570,8 @@ def test_lse_large_selection_route_and_full_k(P):
 
 
 def test_lse_children_made_in_the_draft_kernels(P):
-    """Above 2^20 candidates, with aligned offsets, the draft kernels of every step after the first make, store and
-    score the children themselves (one launch per loop-nest class).  All five classes, the generic one included, a
+    """Above 2^20 candidates, with aligned offsets, the draft kernels of every step after the first make and score the
+    children themselves, or look them up (here one launch per loop-nest class); the chosen ones are made again.  All five classes, the generic one included, a
     fragment GEMM with three reduction levels, slot counts that reach two, three and four 16-byte record pieces, and a
     last segment that ends two candidates into a thread's four (the pitch is padded to a multiple of 4)."""
     hw = w.Device(T_p=3.3e12, T_m=4.1e11, m_l0=96, m_l1=20000, pu_l1=3, n_l1=24, pu_l2=7, n_l2=5)
