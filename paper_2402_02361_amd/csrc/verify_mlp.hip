@@ -318,6 +318,9 @@ mlp_kernel(const float* __restrict__ feat, const int32_t* __restrict__ n_stmt, i
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc0[nt][i] = acc1[nt][i] = 0.f;
+    // (no instruction: where the loop may be left out, zeros that are known as such are made a second time for what comes after it; eight
+    // statements of 4,096 candidates 14.26 -> 14.18 us)
+    if constexpr (SHORT_LAST) asm volatile("" : "+v"(acc1[0]), "+v"(acc1[1]), "+v"(y1));
     // (after the loop: a branch around the second half's layers inside it cost 5 of 155 us at 131,072 candidates)
     const bool short_last = SHORT_LAST && n_rows > 0 && (n_rows - 1) % kTM < 32;
     const int n_whole = short_last ? n_tiles - 1 : n_tiles;
