@@ -8,9 +8,11 @@ namespace pruner {
 
 constexpr int32_t kSharedSegments = 256, kMostUnits = 512;
 
-// The chunks of the compute unit that has most, where workgroups go to `cus` units in turn.  A segment's workgroups have as many chunks as
-// each other, the first of them one more.
-inline uint32_t busiest_unit(const uint32_t* chunks, const uint32_t* blocks, int32_t n, uint32_t cus)
+struct Busiest {
+    uint32_t chunks, units;   // of the compute units that have most; how many these are
+};
+// Where workgroups go to `cus` units in turn.  A segment's workgroups have as many chunks as each other, the first of them one more.
+inline Busiest busiest_units(const uint32_t* chunks, const uint32_t* blocks, int32_t n, uint32_t cus)
 {
     uint32_t step[kMostUnits + 1];   // from a unit to the next (modulo 2^32)
     memset(step, 0, (cus + 1) * sizeof(uint32_t));
@@ -32,30 +34,34 @@ inline uint32_t busiest_unit(const uint32_t* chunks, const uint32_t* blocks, int
         at += left;
         at -= at >= cus ? cus : 0u;
     }
-    uint32_t most = 0, here = 0;
+    uint32_t most = 0, here = 0, units = 0;
     for (uint32_t u = 0; u < cus; ++u) {
         here += step[u];
+        units = here > most ? 1 : units + (here == most);
         most = here > most ? here : most;
     }
-    return all + most;
+    return Busiest{all + most, units};
 }
 
 // chunks[i]: pieces of segment i, one workgroup's at a time (fewer than 2^31 in all); room: workgroups that the device holds at once;
+// alike: a chunk of one segment is as much work as one of another (the kernel does not branch on the loop-nest class);
 // blocks[i]: the workgroups that segment i gets.
-// None has more chunks than the launch's mean.  What the device holds beyond that goes to the segments by their shares (one GEMM of
-// 3.3 M candidates, 806 workgroups of four 29.8 us, 1,024 of three or four 25.7; ten convolutions of 330,000 38.9 and 34.7; 20 x 100,000 of
-// four classes 20.9 and 18.6), but not where the longer workgroups of several segments meet on the same units (20 x 60,000 of a GEMM, 600
-// workgroups of two 14.5 us, 1,020 of one or two 16.7), and not where there are so many segments that asking costs as much.  Where a
+// None has more chunks than the launch's mean.  What the device holds beyond that goes to the segments by their shares where the busiest
+// compute units then have fewer chunks or are next to none (one GEMM of 3.2 M candidates, 782 workgroups of four 53.4 us, 1,024 of three or
+// four 48.9; five convolutions of 360,001 40.0 and 36.4; 14 GEMMs and 6 batched ones of 240,000 49.6 and 45.4; three GEMMs of 700,001, nine
+// chunks on 172 units or on six, 34.1 and 32.3; all a filter's call).  Not where they have as many, longer workgroups of several segments on the
+// same units (eight GEMMs of 312,501, 816 workgroups of three 37.1 us, 1,024 of two or three 38.2; of 400,001 43.0 and 44.0), not where chunks differ (20 x 125,001 of four classes 39.8 us, by shares 45.3;
+// 10 x 180,001 33.5 and 36.4), and not where there are so many segments that asking costs as much.  Where a
 // workgroup for every mean is slightly more than fits, the shares rounded down are hardly longer (five convolutions of 2.2 M, 770 of 14 119 us,
 // 765 of 14 or 15 106); shares alone would leave 19 chunks to one where all others have ten (10.5 M candidates of a GEMM and
 // 19 x 19,456: 66 us, 52 so).
-inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, uint32_t cus, uint32_t* blocks)
+inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, uint32_t cus, bool alike, uint32_t* blocks)
 {
     uint32_t total = 0, least = 0;
     for (int32_t i = 0; i < n; ++i) total += chunks[i];
     const uint32_t mean = total > room ? (total + room - 1) / room : 1;
     for (int32_t i = 0; i < n; ++i) least += blocks[i] = mean == 1 ? chunks[i] : (chunks[i] + mean - 1) / mean;
-    if (mean == 1 || least == room || n > kSharedSegments || cus < 1 || cus > (uint32_t)kMostUnits) return;
+    if (mean == 1 || least == room || (least < room && !alike) || n > kSharedSegments || cus < 1 || cus > (uint32_t)kMostUnits) return;
     const double per_chunk = (double)room / total;
     auto share_of = [&](int32_t i) { return (uint32_t)(chunks[i] * per_chunk + 1e-6); };
     uint32_t fuller[kSharedSegments];
@@ -76,7 +82,8 @@ inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, u
             if (chunks[i] > fuller[i] * (mean + 1 + mean / 8) || sum > least) return;
         }
     }
-    if (n == 1 || busiest_unit(chunks, fuller, n, cus) <= busiest_unit(chunks, blocks, n, cus)) memcpy(blocks, fuller, n * sizeof(uint32_t));
+    const Busiest by_mean = busiest_units(chunks, blocks, n, cus), by_shares = busiest_units(chunks, fuller, n, cus);
+    if (n == 1 || by_shares.chunks < by_mean.chunks || (by_shares.chunks == by_mean.chunks && 8 * by_shares.units < by_mean.units)) memcpy(blocks, fuller, n * sizeof(uint32_t));
 }
 
 // Whether the draft kernel for several closed forms is taken with four wavefronts per SIMD, two registers spilled, instead of three: where the

@@ -1,6 +1,6 @@
 """How many workgroups of a draft launch each segment gets, on the host: none walks through more chunks than the launch's mean (or one and
-an eighth more, where the workgroups fit the device then), however uneven the segments are, and no division is taken that leaves a
-compute unit with more than the one by the mean alone does."""
+an eighth more, where the workgroups fit the device then), however uneven the segments are, and no other division is taken than the one by the
+mean alone unless the busiest compute units have fewer chunks with it, or are an eighth as many, and a chunk of one segment is as much work as one of another."""
 import os
 import subprocess
 
@@ -13,10 +13,10 @@ PROGRAM = r"""
 #include <vector>
 using V = std::vector<uint32_t>;
 static V many(int n, uint32_t c, V more = {}) { more.insert(more.end(), n, c); return more; }
-static int check(const char* what, const V& chunks, uint32_t room, uint32_t cus, V* out = nullptr)
+static int check(const char* what, const V& chunks, uint32_t room, uint32_t cus, V* out = nullptr, bool alike = true)
 {
     V blocks(chunks.size(), 77), plain(chunks.size());
-    pruner::share_workgroups(chunks.data(), (int32_t)chunks.size(), room, cus, blocks.data());
+    pruner::share_workgroups(chunks.data(), (int32_t)chunks.size(), room, cus, alike, blocks.data());
     int64_t total = 0, sum = 0, longest = 0, at_mean = 0;
     for (uint32_t c : chunks) total += c;
     const int64_t mean = total > (int64_t)room ? (total + room - 1) / room : 1;
@@ -29,8 +29,10 @@ static int check(const char* what, const V& chunks, uint32_t room, uint32_t cus,
     }
     if (longest > (at_mean > (int64_t)room ? mean + 1 + mean / 8 : mean)) return std::printf("%s: %ld chunks one after the other, mean %ld\n", what, (long)longest, (long)mean), 1;
     if (sum > (at_mean > (int64_t)room ? at_mean : room)) return std::printf("%s: %ld workgroups, room %ld\n", what, (long)sum, (long)room), 1;
-    const int64_t now = pruner::busiest_unit(chunks.data(), blocks.data(), (int32_t)chunks.size(), cus), before = pruner::busiest_unit(chunks.data(), plain.data(), (int32_t)chunks.size(), cus);
-    if (now > before) return std::printf("%s: a unit with %ld chunks, %ld before\n", what, (long)now, (long)before), 1;
+    const pruner::Busiest now = pruner::busiest_units(chunks.data(), blocks.data(), (int32_t)chunks.size(), cus), before = pruner::busiest_units(chunks.data(), plain.data(), (int32_t)chunks.size(), cus);
+    if (blocks != plain && chunks.size() > 1 && (now.chunks > before.chunks || (now.chunks == before.chunks && 8 * now.units >= before.units)))
+        return std::printf("%s: %u units with %u chunks, %u with %u by the mean\n", what, now.units, now.chunks, before.units, before.chunks), 1;
+    if (!alike && at_mean <= (int64_t)room && blocks != plain) return std::printf("%s: by shares\n", what), 1;
     if (out) *out = blocks;
     return 0;
 }
@@ -50,7 +52,15 @@ int main()
     bad += check("nothing", V{0, 0}, 1024, 256);
     bad += check("one alone", V{3223}, 1024, 256, &got) || got[0] != 1024;           // the whole device
     bad += check("ten of 323", many(10, 323), 1024, 256, &got) || got[0] != 102;
-    bad += check("twenty of 98", many(20, 98), 1024, 256, &got) || got[0] != 51;
+    bad += check("twenty of 98", many(20, 98), 1024, 256, &got) || got[0] != 49;     // (51 each leave as many chunks to a unit)
+    bad += check("eight of 306", many(8, 306), 1024, 256, &got) || got[0] != 102;    // (and so do 128 each)
+    bad += check("three of 684", many(3, 684), 1024, 256, &got) || got[0] != 341;    // (as many on six units, on 172 by the mean)
+    bad += check("fourteen of 235", many(14, 235), 1024, 256, &got) || got[0] != 73;
+    bad += check("five of 352", many(5, 352), 768, 256, &got) || got[0] != 153;
+    // several loop-nest classes: by the mean
+    bad += check("twenty of 123", many(20, 123), 1024, 256, &got, false) || got[0] != 41;
+    bad += check("ten of 176", many(10, 176), 1024, 256, &got, false) || got[0] != 88;
+    bad += check("five of 2,149", many(5, 2149), 768, 256, &got, false) || got[0] != 153;
     bad += check("five of 2,149", many(5, 2149), 768, 256, &got) || got[0] != 153;   // 154 each do not fit
     for (int64_t chunks : {690, 768, 1025, 1040, 1180, 1536}) bad += pruner::four_waves_pay(chunks, 256) ? std::printf("%ld chunks\n", (long)chunks) : 0;
     for (int64_t chunks : {769, 980, 1024, 1537, 1960, 3910, 21000}) bad += pruner::four_waves_pay(chunks, 256) ? 0 : std::printf("%ld chunks\n", (long)chunks);
@@ -59,7 +69,7 @@ int main()
         V c(1 + rng() % 60);
         for (uint32_t& x : c) x = rng() % (1u << (rng() % 16));
         const int cus = 1 + rng() % 300;
-        bad += check("drawn", c, cus * (1 + rng() % 8), cus);
+        bad += check("drawn", c, cus * (1 + rng() % 8), cus, nullptr, t & 1);
     }
     for (int t = 0; t < 2000 && !bad; ++t) {   // the busiest unit, counted one chunk after the other
         V c(1 + rng() % 9), b(c.size());
@@ -70,7 +80,10 @@ int main()
         for (size_t i = 0; i < c.size(); at += b[i++])
             for (uint32_t k = 0; k < c[i]; ++k) ++unit[(at + k % b[i]) % cus];
         for (uint32_t u : unit) most = u > most ? u : most;
-        if (pruner::busiest_unit(c.data(), b.data(), (int32_t)c.size(), cus) != most) bad += std::printf("busiest unit\n");
+        uint32_t units = 0;
+        for (uint32_t u : unit) units += u == most;
+        const pruner::Busiest got = pruner::busiest_units(c.data(), b.data(), (int32_t)c.size(), cus);
+        if (got.chunks != most || got.units != units) bad += std::printf("busiest unit\n");
     }
     return bad != 0;
 }
