@@ -86,10 +86,11 @@ inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, u
     if (n == 1 || by_shares.chunks < by_mean.chunks || (by_shares.chunks == by_mean.chunks && 8 * by_shares.units < by_mean.units)) memcpy(blocks, fuller, n * sizeof(uint32_t));
 }
 
-// Whether the draft kernel for several closed forms is taken with four wavefronts per SIMD, two registers spilled, instead of three: where the
-// device then has a workgroup for every chunk and otherwise not (ten segments of 100,000 15.7 -> 13.8 us), and where there are chunks for more than
-// two rounds of three (20 x 100,000 20.3 -> 18.7, ten of 400,000 36.2 -> 35.4).  With two rounds either way the spilled registers are what is left of
-// it (ten of 120,000 14.3 and 15.7), and with one (ten of 70,000 12.8 and 13.3).
-constexpr bool four_waves_pay(int64_t chunks, int64_t units) { return chunks > 3 * units && (chunks <= 4 * units || chunks > 6 * units); }
+// Whether the draft kernel for several closed forms is taken with four wavefronts per SIMD, two registers spilled, instead of three: where its
+// workgroups then walk through fewer chunks one after the other (a filter's call, 176,000 candidates of ten segments 30.4 -> 27.5 us, 270,000 37.9 ->
+// 36.5, 333,333 52.9 -> 49.3).  With as many either way the spilled registers are what is left of it (seven of 300,001, three chunks,
+// 38.6 and 40.8; ten of 120,000, two, the kernel 14.3 and 15.7; of 70,000, one, 12.8 and 13.3).
+constexpr int64_t rounds_of(int64_t chunks, int64_t at_once) { return (chunks + at_once - 1) / at_once; }
+constexpr bool four_waves_pay(int64_t chunks, int64_t units) { return rounds_of(chunks, 4 * units) < rounds_of(chunks, 3 * units); }
 
 }  // namespace pruner

@@ -62,8 +62,8 @@ int main()
     bad += check("ten of 176", many(10, 176), 1024, 256, &got, false) || got[0] != 88;
     bad += check("five of 2,149", many(5, 2149), 768, 256, &got, false) || got[0] != 153;
     bad += check("five of 2,149", many(5, 2149), 768, 256, &got) || got[0] != 153;   // 154 each do not fit
-    for (int64_t chunks : {690, 768, 1025, 1040, 1180, 1536}) bad += pruner::four_waves_pay(chunks, 256) ? std::printf("%ld chunks\n", (long)chunks) : 0;
-    for (int64_t chunks : {769, 980, 1024, 1537, 1960, 3910, 21000}) bad += pruner::four_waves_pay(chunks, 256) ? 0 : std::printf("%ld chunks\n", (long)chunks);
+    for (int64_t chunks : {0, 690, 768, 1025, 1040, 1180, 1536, 2049, 2051, 2304}) bad += pruner::four_waves_pay(chunks, 256) ? std::printf("%ld chunks\n", (long)chunks) : 0;
+    for (int64_t chunks : {769, 980, 1024, 1537, 1960, 2048, 2305, 2640, 3910, 21000}) bad += pruner::four_waves_pay(chunks, 256) ? 0 : std::printf("%ld chunks\n", (long)chunks);
     std::mt19937 rng(1);
     for (int t = 0; t < 20000 && !bad; ++t) {
         V c(1 + rng() % 60);
