@@ -980,14 +980,15 @@ extern "C" int pruner_lse(const pruner_subgraph* sg, int32_t n_sg, const int64_t
         const int64_t room = (int64_t)(L.total - L.children) - (int64_t)round_up((size_t)n_sg * sizeof(int32_t), 256);
         int64_t end = 0;
         int32_t n_tabled = 0;
+        std::vector<int64_t> entries(n_sg, 0);
+        std::vector<int> draws(n_sg, 0);
+        for (int32_t s = 0; s < n_sg && n_steps > 1; ++s) entries[s] = table_entries(sg[s], seg_off[s + 1] - seg_off[s], k, &draws[s]);
+        drop_partial(seg_off, n_sg, entries.data());
         for (int32_t s = 0; s < n_sg; ++s) {
             variant_off[s] = end;
-            if (n_steps < 2) continue;
-            int draws;
-            const int64_t entries = table_entries(sg[s], seg_off[s + 1] - seg_off[s], k, &draws);
-            if (entries == 0 || (end + entries) * (int64_t)sizeof(float) > room) continue;
-            table[s].table = table_word((uint32_t)end, draws);
-            end += entries;
+            if (entries[s] == 0 || (end + entries[s]) * (int64_t)sizeof(float) > room) continue;
+            table[s].table = table_word((uint32_t)end, draws[s]);
+            end += entries[s];
             ++n_tabled;
         }
         variant_off[n_sg] = end;

@@ -60,6 +60,11 @@ inline int told_apart(const pruner_subgraph& s)
 // Children per entry of a table from which one is made: an entry is made and scored as a child is without a table, a child with one costs a
 // fifth of that and a line from the vector cache, and the table is a launch more.
 constexpr int64_t kTableGain = 4;
+// Where not every segment of a call has a table, the launches that make children remain, each as long as it takes for its other segments, and
+// the table's launch is paid for by one segment at least that has more children per entry (four steps of 20 x 60,000 of an encoder layer, k = 264,
+// tables of the plain products at 4.2 and none of the batched ones: 277 us without, 285 with; 6 x 200,000, k = 740, at 5 288 and 293;
+// four classes of 300,000, k = 793, tables at 7, 4.9 and none 432 and 420).
+constexpr int64_t kPartialGain = 6;
 
 // Not where children are made one to a thread: that launch is bound by latency, looking up is no shorter a chain, and the table is a launch
 // before it (four steps of a GEMM's 33,000 136 us without a table, 147 with; 65,536 142 and 154; 262,144 161 and 171; two classes of
@@ -77,6 +82,15 @@ inline int64_t table_entries(const pruner_subgraph& s, int64_t len, int32_t k, i
     if (len < kTableGain * entries(1)) return 0;
     *draws = told_apart(s);
     return *draws > 0 && len >= kTableGain * entries(*draws) ? entries(*draws) : 0;
+}
+
+// Drops the tables of a call that has segments without one, unless they pay; entries[s]: of the table of segment s, 0 where there is none.
+inline void drop_partial(const int64_t* seg_off, int32_t n_sg, int64_t* entries)
+{
+    bool pay = true;
+    for (int32_t s = 0; s < n_sg; ++s) pay = pay && entries[s] > 0;
+    for (int32_t s = 0; s < n_sg; ++s) pay = pay || (entries[s] > 0 && seg_off[s + 1] - seg_off[s] >= kPartialGain * entries[s]);
+    for (int32_t s = 0; s < n_sg; ++s) entries[s] = pay ? entries[s] : 0;
 }
 
 }  // namespace pruner

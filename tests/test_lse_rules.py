@@ -39,6 +39,17 @@ int main()
     bad += !pruner::table_pays((1 << 18) + 1, 1, false) || !pruner::table_pays(100000, 3, false) || !pruner::table_pays(100000, 1, true);
     for (int k : {1, 17, 512, 4096}) {
         bad += check(gemm(64, 1, 65536 / 2), 1, k) + check(gemm(97, 13, 25), 1, k) + check(gemm(96, 80, 72), 2, k) + check(gemm(60, 90, 64), 4, k);
+        // five children per entry are enough where all segments have a table, or one of them has six
+        const int64_t e = ((int64_t)k * 2 * 27 + 3) / 4 * 4, off[4] = {0, 5 * e, 10 * e, 16 * e};
+        for (int kept : {0, 1, 2, 3, 4, 5, 6, 7}) {
+            int64_t entries[3] = {kept & 1 ? e : 0, kept & 2 ? e : 0, kept & 4 ? e : 0};
+            pruner::drop_partial(off, 3, entries);
+            for (int s = 0; s < 3; ++s) bad += entries[s] != (kept >> s & 1 && kept & 4 ? e : 0);
+            if (kept != 3) continue;
+            int64_t two[2] = {e, e};
+            pruner::drop_partial(off, 2, two);
+            bad += two[0] != e || two[1] != e;
+        }
         bad += pruner::told_apart(gemm(210, 64, 32)) != 0 || pruner::told_apart(gemm(64, 64, 30030)) != 0;
     }
     return bad;
