@@ -1637,7 +1637,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     for (DraftPlan::Launch& L : out->launches) {
         int cus = 0;
         const int64_t room = resident_blocks(reinterpret_cast<DraftFn>(const_cast<void*>(L.fn)), &cus);
-        share_workgroups(&chunks_of[L.first_seg], L.n_seg, (uint32_t)room, (uint32_t)cus, L.cls >= 0, &blocks_of[L.first_seg]);
+        share_workgroups(&chunks_of[L.first_seg], L.n_seg, (uint32_t)room, (uint32_t)cus, &blocks_of[L.first_seg]);
         for (int32_t i = L.first_seg; i < L.first_seg + L.n_seg; ++i) {
             const int32_t s = order[i];
             const SgDesc& dd = descs[desc_of[s]];

@@ -44,24 +44,24 @@ inline Busiest busiest_units(const uint32_t* chunks, const uint32_t* blocks, int
 }
 
 // chunks[i]: pieces of segment i, one workgroup's at a time (fewer than 2^31 in all); room: workgroups that the device holds at once;
-// alike: a chunk of one segment is as much work as one of another (the kernel does not branch on the loop-nest class);
 // blocks[i]: the workgroups that segment i gets.
 // None has more chunks than the launch's mean.  What the device holds beyond that goes to the segments by their shares where the busiest
-// compute units then have fewer chunks or are next to none (one GEMM of 3.2 M candidates, 782 workgroups of four 53.4 us, 1,024 of three or
-// four 48.9; five convolutions of 360,001 40.0 and 36.4; 14 GEMMs and 6 batched ones of 240,000 49.6 and 45.4; three GEMMs of 700,001, nine
-// chunks on 172 units or on six, 34.1 and 32.3; all a filter's call).  Not where they have as many, longer workgroups of several segments on the
-// same units (eight GEMMs of 312,501, 816 workgroups of three 37.1 us, 1,024 of two or three 38.2; of 400,001 43.0 and 44.0), not where chunks differ (20 x 125,001 of four classes 39.8 us, by shares 45.3;
-// 10 x 180,001 33.5 and 36.4), and not where there are so many segments that asking costs as much.  Where a
+// compute units then have fewer chunks or are next to none (a filter's call: one GEMM of 3.2 M candidates, 782 workgroups of four 53.4 us,
+// 1,024 of three or four 48.9; five convolutions of 960,001 75.5 and 70.4; 14 GEMMs and 6 batched ones of 240,000 51.0 and 46.6; 40 x 83,333 of
+// four classes 56.6 and 53.9; three GEMMs of 700,001, nine chunks on 172 units or on six, 34.1 and 32.3).  Not where they have as many, longer
+// workgroups of several segments on the same units (eight GEMMs of 312,501, 816 workgroups of three 37.1 us, 1,024 of two or three 38.2; 20 x 166,667
+// of four classes 49.2 and 54.7), and not where there are so many segments that asking costs as much.  (Of several classes a count of chunks
+// says less: 7 x 385,715 42.8 us by the mean and 45.8 by shares, which leave fewer to every unit.)  Where a
 // workgroup for every mean is slightly more than fits, the shares rounded down are hardly longer (five convolutions of 2.2 M, 770 of 14 119 us,
 // 765 of 14 or 15 106); shares alone would leave 19 chunks to one where all others have ten (10.5 M candidates of a GEMM and
 // 19 x 19,456: 66 us, 52 so).
-inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, uint32_t cus, bool alike, uint32_t* blocks)
+inline void share_workgroups(const uint32_t* chunks, int32_t n, uint32_t room, uint32_t cus, uint32_t* blocks)
 {
     uint32_t total = 0, least = 0;
     for (int32_t i = 0; i < n; ++i) total += chunks[i];
     const uint32_t mean = total > room ? (total + room - 1) / room : 1;
     for (int32_t i = 0; i < n; ++i) least += blocks[i] = mean == 1 ? chunks[i] : (chunks[i] + mean - 1) / mean;
-    if (mean == 1 || least == room || (least < room && !alike) || n > kSharedSegments || cus < 1 || cus > (uint32_t)kMostUnits) return;
+    if (mean == 1 || least == room || n > kSharedSegments || cus < 1 || cus > (uint32_t)kMostUnits) return;
     const double per_chunk = (double)room / total;
     auto share_of = [&](int32_t i) { return (uint32_t)(chunks[i] * per_chunk + 1e-6); };
     uint32_t fuller[kSharedSegments];

@@ -16,8 +16,8 @@
 // take one launch for the selection and all of PriorFilter instead:
 //   lse_select  one workgroup per subgraph: the k best of S_x from keys in registers, their schedules' hashes, the union
 //               with S_spec and the new S_spec's records
-// When the population gets one draft launch per loop-nest class, the mutation of a step is not a launch of its own: the
-// next step's draft kernels make the children and score them while they are in registers.  They are not stored: a child is a
+// When the population gets one draft launch per loop-nest class (or one for several closed forms, where all children are looked up, below), the
+// mutation of a step is not a launch of its own: the next step's draft kernels make the children and score them while they are in registers.  They are not stored: a child is a
 // function of the seed, the step, its number and S_spec, and the few that are chosen are made again where they are wanted; only the
 // last step's mutation, whose children nobody scores, is a launch that stores them.
 // Where a segment has many times more children than S_spec can have different ones (a child is one of some thirty to a few hundred moves
