@@ -1614,15 +1614,20 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     const bool fused = makes && (by_class || together) && symbols == nullptr;   // every launch of the plan then makes its candidates itself
     const int64_t chunk = (int64_t)kBlock * vec;
     const int chunk_log = __builtin_ctzll((uint64_t)chunk);   // (a power of two: divisions by it were a tenth of the plan of 3,000 segments)
-    std::vector<uint32_t> chunks_of(n_sg), blocks_of(n_sg);   // by place in the launches
-    int64_t all_chunks = 0;
-    for (int32_t s = 0; s < n_sg; ++s) all_chunks += (seg_off[s + 1] - seg_off[s] + chunk - 1) >> chunk_log;
-    int units = 0;
-    if (current_device(&units) < 0) units = 256, (void)hipGetLastError();
-    const bool held = four_waves_pay(all_chunks, units);
+    std::vector<uint32_t> chunks_and_blocks(2 * (size_t)n_sg);   // by place in the launches
+    uint32_t *const chunks_of = chunks_and_blocks.data(), *const blocks_of = chunks_of + n_sg;
+    const bool products = classes == ((1u << kGemm) | (1u << kBatchedGemm)), branches = !by_class && !together && vec == 4 && !(classes >> kGeneric & 1u) && !products;
+    bool held = false;
+    if (branches && !symbols) {
+        int64_t all_chunks = 0;
+        for (int32_t s = 0; s < n_sg; ++s) all_chunks += (seg_off[s + 1] - seg_off[s] + chunk - 1) >> chunk_log;
+        int units = 0;
+        if (current_device(&units) < 0) units = 256, (void)hipGetLastError();
+        held = four_waves_pay(all_chunks, units);
+    }
     for (int32_t i = 0; i < n_sg; ++i) {
         const int32_t s = order[i];
-        const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : vec != 4 || (classes >> kGeneric & 1u) ? kAnyClass : classes == ((1u << kGemm) | (1u << kBatchedGemm)) ? kProducts : held && !symbols ? kClosedFormsHeld : kClosedForms;
+        const int cls = by_class ? descs[desc_of[s]].cls : together ? kClosedForms : branches ? (held ? kClosedFormsHeld : kClosedForms) : vec == 4 && products ? kProducts : kAnyClass;
         if (out->launches.empty() || out->launches.back().cls != cls) {
             out->launches.push_back(DraftPlan::Launch{cls, i, 0, 0, 0, 0, draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, fused), draft_kernel_for(cls, vec, symbols != nullptr, exact, hist, false)});
         }
