@@ -29,8 +29,8 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 # HBM bytes per launch of the draft kernel from rocprofv3 counters (profiles/draft_kernel_cfg4_traffic.txt), valid for
 # the kernel source with this SHA-256 only; any other source reports null.
-MEASURED_TRAFFIC = {"workload": "cfg4_stress_gemm4096_dwconv_20M", "source_sha256": "f5db718048834b6a35a11d9671a7aa1a78846f913b9af07bad8434ec1c37f14e",
-                    "bytes": 588266447, "dominant_bytes": 403341892}
+MEASURED_TRAFFIC = {"workload": "cfg4_stress_gemm4096_dwconv_20M", "source_sha256": "2c5fdc454b2595d6242a6bf2a943fcd689ff704112e69d8d386bec8a72dfec8d",
+                    "bytes": 588267534, "dominant_bytes": 403342489}
 
 
 def draft_traffic(workload, which="bytes"):

@@ -1586,7 +1586,7 @@ int draft_plan(const pruner_subgraph* sg, int32_t n_sg, const int64_t* seg_off, 
     // two kinds of matrix products where there are no others (an encoder's tasks: 20 x 50,000 candidates take 13.3 us
     // instead of 14.8), between the four classes with closed forms where none is generic (134 registers or, where four_waves_pay, 128,
     // where the access tables of the generic class take 178 and leave two wavefronts per SIMD: ten segments of these four classes, 3.3 M
-    // candidates, take 31 us instead of 43), else among all five.  A
+    // candidates with odd lengths, took 39 us instead of 43, and 37 now), else among all five.  A
     // launch has at most as many workgroups as the device holds at once; they walk through the chunks of their segment.
     std::vector<int32_t> order(n_sg);
     for (int32_t s = 0; s < n_sg; ++s) order[s] = s;
